@@ -122,25 +122,44 @@ ic_status check_attn(const ic_attn_desc *d)
     return IC_OK;
 }
 
-// Key-slot splits per query.  MLA rows with the values in front run one workgroup per CU: one per
-// query when there are at least 256 queries, otherwise the k_sel slots are split so that about 256
-// workgroups exist.  The other layouts run two workgroups per CU and aim for 512.
+// Workgroups one launch can have resident: MLA rows with the values in front run one workgroup per CU, the other
+// layouts two.
+int64_t attn_resident(const ic_attn_desc *d) { return (d->d_qk == 576 && d->v_off == 0) ? 256 : 512; }
+
+// The most key-slot splits per query a launch uses, which sizes the workspace: one when the queries alone fill the
+// chip, otherwise what brings their number up to that.
+int64_t attn_max_splits(const ic_attn_desc *d)
+{
+    const int64_t nq = (int64_t)d->B * d->Tq, wgs = attn_resident(d), tiles = (d->k_sel + 63) / 64;
+    const int64_t want = nq >= wgs ? 1 : (wgs + nq - 1) / nq;
+    const int64_t ns = want > tiles ? tiles : want;
+    const int64_t per = (tiles + ns - 1) / ns;
+    return (tiles + per - 1) / per;
+}
+
+// Splits of a launch.  Workgroups run in rounds of attn_resident(), and a round takes as long as its longest workgroup:
+// tiles plus what a workgroup pays once (launch, Q, first rows, output: about two tiles).  The merge launch costs about
+// two tiles more.  One split too many can therefore double the time (40 queries x 7 splits of 5 tiles = 280 workgroups on
+// 256 CUs took 36 us, 6 splits of 6 tiles take 30), so the number with the fewest tile times wins, the smaller at a tie.
 void attn_splits(const ic_attn_desc *d, int *n_splits, int *split_len)
 {
-    const int64_t nq = (int64_t)d->B * d->Tq;
-    const int tiles = (d->k_sel + 63) / 64;
-    const int64_t wgs = (d->d_qk == 576 && d->v_off == 0) ? 256 : 512;
-    int64_t want = nq >= wgs ? 1 : (wgs + nq - 1) / nq;
-    if (want > tiles) want = tiles;
-    const int tiles_per = (int)((tiles + want - 1) / want);
-    *split_len = tiles_per * 64;
-    *n_splits = (tiles + tiles_per - 1) / tiles_per;
+    const int64_t nq = (int64_t)d->B * d->Tq, wgs = attn_resident(d), tiles = (d->k_sel + 63) / 64;
+    int64_t best = 0, best_per = tiles;
+    for (int64_t ns = 1, most = attn_max_splits(d); ns <= most; ++ns) {
+        const int64_t per = (tiles + ns - 1) / ns, n = (tiles + per - 1) / per;
+        const int64_t cost = (nq * n + wgs - 1) / wgs * (per + 2) + (n > 1 ? 2 : 0);
+        if (best == 0 || cost < best) {
+            best = cost;
+            best_per = per;
+        }
+    }
+    *split_len = (int)best_per * 64;
+    *n_splits = (int)((tiles + best_per - 1) / best_per);
 }
 
 size_t attn_ws_bytes(const ic_attn_desc *d)
 {
-    int ns, sl;
-    attn_splits(d, &ns, &sl);
+    const size_t ns = (size_t)attn_max_splits(d);
     if (ns <= 1) return 0;
     const size_t nq = (size_t)d->B * d->Tq;
     return align_up(nq * ns * d->H_q * d->d_v * 2) + align_up(nq * ns * d->H_q * 2 * sizeof(float));   // bf16 partial outputs, fp32 (max, sum)

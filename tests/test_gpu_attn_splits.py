@@ -1,0 +1,44 @@
+"""Split attention launches (fewer queries than the chip holds workgroups) and their merge, at the edges of the rules
+that choose the number of splits: one split, as many as fit one round, more splits than the merge handles side by side."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+from tests import parity
+import synth
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # B, Tq, Lk, Hq, d_qk, d_v, v_off, row, k_sel
+    (1, 1, 2500, 32, 576, 512, 0, 576, 2200),    # 35 splits of one tile
+    (1, 1, 2500, 5, 64, 64, 64, 128, 2200),      # 35 splits, 32 handled side by side
+    (40, 1, 700, 32, 576, 512, 0, 576, 640),     # 6 splits of 2 tiles, not 7
+    (1, 129, 900, 32, 576, 512, 0, 576, 320),    # one workgroup per query rather than two rounds
+    (1, 100, 900, 20, 576, 512, 0, 576, 449),    # two splits, the second one ragged
+    (1, 300, 400, 3, 64, 64, 64, 128, 130),      # small-tile form, two workgroups per CU
+]
+
+
+@pytest.mark.parametrize("case", CASES)
+def test_split_launches(oracle, case):
+    import paper_2603_12201_amd as ic
+    B, Tq, Lk, Hq, d_qk, d_v, v_off, row, ks = case
+    print("[case] splits B=%d Tq=%d Lk=%d Hq=%d d_qk=%d k=%d" % (B, Tq, Lk, Hq, d_qk, ks), flush=True)
+    g = torch.Generator().manual_seed(ks + Tq)
+    Q = torch.randn((B, Tq, Hq, d_qk), generator=g).to(torch.bfloat16)
+    KV = torch.randn((B, Lk, row), generator=g).to(torch.bfloat16)
+    rng = np.random.default_rng(ks)
+    idx = np.full((B, Tq, ks), -1, dtype=np.int32)
+    for b in range(B):
+        for t in range(Tq):
+            n = ks if t else ks - 70                # a row whose last split holds nothing
+            idx[b, t, :n] = np.sort(rng.choice(Lk, size=n, replace=False))
+    scale = 1.0 / math.sqrt(d_qk)
+    O, lse = ic.sparse_attn(Q.cuda(), KV.cuda(), torch.from_numpy(idx).cuda(), d_v, v_off, scale, want_lse=True)
+    torch.cuda.synchronize()
+    want, want_lse = oracle.sparse_attn(synth.bits(Q), synth.bits(KV), idx, d_v, v_off, scale)
+    parity.check_attn(O.float().cpu().numpy(), want)
+    assert np.allclose(lse.cpu().numpy(), want_lse, rtol=0, atol=2e-2)
