@@ -103,6 +103,16 @@ size_t strip_ld(const ic_indexer_desc *d) { return ((size_t)d->Lk + 63) / 64 * 6
 // Rows of the strip a workspace of `bytes` can hold.
 int64_t strip_rows(const ic_indexer_desc *d, size_t bytes) { return (int64_t)(bytes / (strip_ld(d) * sizeof(float))); }
 
+// Workspace for selecting all rows of the call in parts (few long rows): every row's scores, then the candidate lists;
+// 0 when the call does not qualify.
+size_t parts_ws(const ic_indexer_desc *d)
+{
+    const int64_t rows = (int64_t)d->B * d->Tq;
+    const size_t lists = rows > INT32_MAX ? 0 : ic::select_parts_bytes((int)rows, d->Lk);
+    const size_t strip = (size_t)rows * strip_ld(d) * sizeof(float);
+    return lists == 0 || strip > kStripBudget ? 0 : align_up(strip) + align_up(lists);
+}
+
 ic_status check_attn(const ic_attn_desc *d)
 {
     if (!d) return fail(IC_ERR_NULL, "attention descriptor is NULL");
@@ -201,6 +211,8 @@ ic_status run_indexer(const ic_indexer_desc *d, const void *q, const void *k, co
     const int Ri = (int)(d->Tq < rows_cap ? d->Tq : rows_cap);
     int64_t bc64 = rows_cap / Ri;
     const int Bc = (int)(bc64 < 1 ? 1 : (bc64 > d->B ? d->B : bc64));
+    const size_t pw = parts_ws(d);
+    void *const lists = pw != 0 && ws_bytes >= pw ? (char *)ws + align_up((size_t)d->B * d->Tq * strip_ld(d) * sizeof(float)) : nullptr;
     ic::ScoreArgs sa;
     memset(&sa, 0, sizeof sa);
     sa.q = q;
@@ -246,7 +258,9 @@ ic_status run_indexer(const ic_indexer_desc *d, const void *q, const void *k, co
             se.Ri = ri;
             {
                 ProfScope ps(1, st);
-                hipError_t e = ic::launch_select(se, bc * ri, (int)max_vis, st);
+                hipError_t e = lists && ic::select_parts(bc * ri, (int)max_vis) > 0
+                                   ? ic::launch_select_parts(se, bc * ri, d->Lk, lists, st)
+                                   : ic::launch_select(se, bc * ri, (int)max_vis, st);
                 if (e != hipSuccess) return fail(IC_ERR_HIP, "top-k select launch failed: %s", hipGetErrorString(e));
             }
         }
@@ -321,6 +335,7 @@ const char *ic_last_error(void) { return g_err; }
 size_t ic_indexer_topk_workspace(const ic_indexer_desc *d)
 {
     if (check_indexer(d) != IC_OK) return 0;
+    if (const size_t pw = parts_ws(d)) return pw;
     const size_t row_bytes = strip_ld(d) * sizeof(float);
     const size_t all = (size_t)d->B * d->Tq * row_bytes;
     // small problems keep every row in flight; larger ones at most a quarter of their rows and at most the budget,

@@ -66,6 +66,13 @@ struct SelectArgs {
     const int32_t *seq_lens;  // ragged: [B] visible lengths (nullptr: q_pos0 rule)
 };
 
+// Candidate lists of rows that are selected in parts (workspace).
+struct PartArgs {
+    uint32_t *heads;      // [rows][head_words]: threshold key, then the lengths of the row's lists
+    uint2 *lists;         // [rows][n_parts * waves][wcap] (key, position), ascending positions
+    int32_t n_parts, wcap, head_words;
+};
+
 struct AttnArgs {
     const void *Q;        // [B,Tq,H_q,d_qk] bf16
     const void *KV;       // [B,Lk,row_elems] bf16
@@ -123,6 +130,9 @@ hipError_t launch_score(const ScoreArgs &a, int dtype, int d_I, int Bc, hipStrea
 hipError_t launch_fill(float *p, int64_t n, float v, hipStream_t st);
 hipError_t launch_select(const SelectArgs &a, int n_rows, int max_row_len, hipStream_t st);
 int select_cache_limit();
+int select_parts(int n_rows, int max_row_len);
+size_t select_parts_bytes(int n_rows, int max_row_len);
+hipError_t launch_select_parts(const SelectArgs &a, int n_rows, int max_row_len, void *ws, hipStream_t st);
 hipError_t launch_attn(const AttnArgs &a, int d_qk, int d_v, hipStream_t st);
 hipError_t launch_attn_merge(const AttnArgs &a, int d_v, hipStream_t st);
 size_t overlap_ws_bytes(int n_layers);

@@ -19,8 +19,9 @@
 //            greater / equal counts.
 // Forms by row length: the radix select with the keys cached in LDS (launches whose rows have up to 8192 keys; up to
 // 32768 when k exceeds a quarter of the row), the candidate form further down (8193 to 131072 keys; two instances, the
-// one for rows of up to 32768 keys sized so that two rows are in flight per CU), and the radix select re-reading the
-// row on every sweep (whatever is longer).
+// one for rows of up to 32768 keys sized so that two rows are in flight per CU), the candidate form with a row spread
+// over several workgroups (few rows of more than 65536 keys), and the radix select re-reading the row on every sweep
+// (whatever is left).
 #include "ic_common.hpp"
 
 namespace ic {
@@ -680,6 +681,277 @@ __global__ __launch_bounds__(NT) void select_cand_kernel(SelectArgs a)
     }
 }
 
+// ---- parts form (few long rows) ---------------------------------------------------------------------------------
+// A long row of a decode step has one workgroup in the forms above, and that one CU is what bounds it (a 200 000-key row,
+// past the candidate form's bitmap, was streamed four times by it: 150 us).  Here a row is cut into parts with a
+// workgroup each, and a second launch finishes it:
+//   select_part_kernel    every part takes the candidate form's sample of the whole row (the same 4096 keys, so the same
+//                         threshold T0), then sweeps its own keys; a wave owns a contiguous stretch of them and writes its
+//                         candidates, ascending by position, to a list of its own in the workspace
+//   select_finish_kernel  one workgroup per row collects the lists in order, finds the k-th largest candidate with one
+//                         histogram and an exact ranking of its bin, and emits: the candidates are already ascending, so
+//                         a bitmap over their numbers (not over the row) gives the slots, and the row may be of any length
+// A row that the candidates cannot decide (fewer than k of them, a list that overflowed, too many ties in the boundary
+// bin) and a row too short for the sample take the generic radix select in the second launch.
+constexpr int kPartThreads = 1024;
+constexpr int kPartWaves = kPartThreads / 64;
+constexpr int kPartMax = 64;             // parts of a row
+// Where the form is the better one (score + select of a call, parts against the forms above): one row of 65536 keys 22.9
+// against 22.5 us, 100 000 keys 24.3 / 32.3, 200 000 keys 29.5 / 139, 500 000 keys 40.6 / 378; 32 rows of 65536 keys 116 /
+// 114, of 131072 keys 218 / 226; 60 rows of 131072 keys 390 / 395, of 32768 keys 114 / 112; and past the candidate form's
+// bitmap 120 rows of 140 000 keys 816 / 1002, 250 rows 1679 / 1972.
+constexpr int kPartFrom = 65536;         // rows have more keys than this ...
+constexpr int kPartRows = 64;            // ... and are at most this many: more of them fill the chip by themselves,
+constexpr int kPartRowsLong = 512;       // which holds for longer where the alternative streams the row four times
+constexpr int kFinishCap = 12288;        // candidates of a row
+
+// per row: [0] T0, then the lists' lengths; the lists follow the heads of all rows
+__host__ __device__ inline size_t part_head_words(int n_parts) { return (size_t)(4 + n_parts * kPartWaves + 63) / 64 * 64; }
+
+struct RowView {
+    int b, i, nv;
+};
+__device__ __forceinline__ RowView row_view(const SelectArgs &a, int r)
+{
+    RowView v;
+    v.b = a.b0 + r / a.Ri;
+    v.i = a.i0 + r % a.Ri;
+    const int Lk_b = a.seq_lens ? max(0, min(a.seq_lens[v.b], a.Lk)) : a.Lk;
+    const int64_t nv64 = (a.seq_lens ? (int64_t)Lk_b - a.Tq : a.q_pos0) + (int64_t)v.i + 1;
+    v.nv = (int)(nv64 < 0 ? 0 : (nv64 > Lk_b ? Lk_b : nv64));
+    return v;
+}
+// rows the sample can speak for
+__device__ __forceinline__ bool part_row(const SelectArgs &a, int nv) { return nv >= kCandMinLen && nv >= 4 * a.k_sel; }
+
+__global__ __launch_bounds__(kPartThreads) void select_part_kernel(SelectArgs a, PartArgs pa)
+{
+    constexpr int NT = kPartThreads, NW = kPartWaves;
+    __shared__ __attribute__((aligned(16))) uint32_t hist[kBins1];
+    __shared__ uint32_t wsum[2 * NW], bc[4], red[2 * NW];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int part = blockIdx.x, r = blockIdx.y;
+    const RowView rv = row_view(a, r);
+    if (rv.i >= a.Tq || !part_row(a, rv.nv)) return;
+    const int nv = rv.nv;
+    const float *row = a.strip + (int64_t)r * a.ld;
+    // this wave's stretch: whole 256-key vectors of the row, ascending over (part, wave)
+    const int span = ((nv + pa.n_parts * NW - 1) / (pa.n_parts * NW) + 255) / 256 * 256;
+    const int s0 = min((part * NW + wave) * span, nv), s1 = min(s0 + span, nv);
+    constexpr int kGroup = 4;
+    f32x4 ga[kGroup];
+    auto load_group = [&](int p0) {
+#pragma unroll
+        for (int j = 0; j < kGroup; ++j) {
+            const int p = p0 + 256 * j + 4 * lane;
+            ga[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if (p < s1) ga[j] = *(const f32x4 *)(row + p);     // may run past s1 inside the row's padding; masked below
+        }
+    };
+    const int blk = tid >> 5;                                  // 32 blocks of 128 keys spread over the row
+    const f32x4 sv = *(const f32x4 *)(row + (int)(((int64_t)blk * nv / 32) & ~(int64_t)3) + (tid & 31) * 4);
+    load_group(s0);
+    static_assert(kCandSample == 4 * NT, "one sample vector per thread");
+    for (int e = tid; e < kBins1; e += NT) hist[e] = 0;
+    uint32_t skey[4], kmx = 0u, kmn = 0xFFFFFFFFu;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        skey[e] = score_key(sv[e]);
+        kmx = max(kmx, skey[e]);
+        kmn = min(kmn, skey[e]);
+    }
+    kmx = wave_max_u32(kmx);
+    kmn = ~wave_max_u32(~kmn);
+    if (lane == 0) {
+        red[wave] = kmn;
+        red[NW + wave] = kmx;
+    }
+    __syncthreads();
+    const uint32_t smin = ~wave_max_u32(~(lane < NW ? red[lane] : 0xFFFFFFFFu));
+    const uint32_t smax = wave_max_u32(lane < NW ? red[NW + lane] : 0u);
+    const uint32_t srange = smax - smin;
+    const int sbits = srange ? 32 - __clz((int)srange) : 0;
+    const int ssh = sbits > 12 ? sbits - 12 : 0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) atomicAdd(&hist[(skey[e] - smin) >> ssh], 1u);
+    __syncthreads();
+    uint32_t want = (uint32_t)(((int64_t)kCandSample * 2 * a.k_sel) / nv) + 32u;
+    want = want > (uint32_t)kCandSample ? (uint32_t)kCandSample : want;
+    find_digit<NT, kBins1 / NT>(hist, want, wsum, bc, tid, lane, wave);
+    const uint32_t T0 = smin + (bc[0] << ssh);
+    const float T0f = key_score(T0);
+
+    uint32_t *head = pa.heads + (size_t)r * pa.head_words;
+    uint2 *list = pa.lists + ((size_t)r * pa.n_parts * NW + part * NW + wave) * pa.wcap;
+    uint32_t cnt = 0;                                          // wave-uniform
+    for (int p0 = s0; p0 < s1; p0 += 256 * kGroup) {
+        if (p0 != s0) load_group(p0);
+#pragma unroll
+        for (int j = 0; j < kGroup; ++j) {
+            uint32_t m = 0;
+            const int p = p0 + 256 * j + 4 * lane;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) m |= (uint32_t)((int)(p + e < s1) & (int)(ga[j][e] >= T0f)) << e;
+            if (__ballot(m != 0u) == 0ull) continue;           // wave-uniform
+            const uint32_t n_t = (uint32_t)__popc(m);
+            const uint32_t incl = wave_incl_scan(n_t);
+            uint32_t off = cnt + incl - n_t;
+            cnt += (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if ((m >> e) & 1u) {
+                    if (off < (uint32_t)pa.wcap) list[off] = uint2{max(score_key(ga[j][e]), T0), (uint32_t)(p + e)};
+                    ++off;
+                }
+        }
+    }
+    if (lane == 0) head[4 + part * NW + wave] = cnt;
+    if (part == 0 && tid == 0) head[0] = T0;
+}
+
+__global__ __launch_bounds__(kPartThreads) void select_finish_kernel(SelectArgs a, PartArgs pa)
+{
+    constexpr int NT = kPartThreads, NW = kPartWaves;
+    extern __shared__ __attribute__((aligned(16))) uint32_t smem[];
+    uint32_t *hist = smem;                     // [kBins1]  (the generic form's layout starts the same way)
+    uint32_t *wsum = hist + kBins1;            // [2 NW]
+    uint32_t *bc = wsum + 2 * NW;              // [4]
+    uint32_t *misc = bc + 4;                   // [16]: 1 largest candidate key, 2 boundary-list count, 3 a list overflowed
+    uint32_t *ckey = misc + 16;                // [kFinishCap]
+    uint32_t *cpos = ckey + kFinishCap;        // [kFinishCap]
+    uint32_t *bitmap = cpos + kFinishCap;      // [kFinishCap / 32]
+    uint32_t *wpre = bitmap + kFinishCap / 32; // [kFinishCap / 32]
+    uint32_t *start = wpre + kFinishCap / 32;  // [NT] first candidate of a list; later the boundary bin's members
+    uint32_t *bl = start;                      // [kBoundaryCap] candidate numbers
+    static_assert(kBoundaryCap <= NT && kPartMax * NW <= NT && kFinishCap / 32 <= NT, "one list, one bitmap word per thread");
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int r = blockIdx.x;
+    const RowView rv = row_view(a, r);
+    if (rv.i >= a.Tq) return;
+    auto finish = [&]() -> bool {              // false: the generic form takes the row (one call site, see below)
+    if (!part_row(a, rv.nv)) return false;
+    const uint32_t *head = pa.heads + (size_t)r * pa.head_words;
+    const int n_lists = pa.n_parts * NW;
+    const uint32_t T0 = head[0];
+    const uint32_t n_mine = tid < n_lists ? head[4 + tid] : 0u;
+    for (int e = tid; e < kBins1; e += NT) hist[e] = 0;
+    if (tid < kFinishCap / 32) bitmap[tid] = 0;
+    if (tid < 16) misc[tid] = 0;
+    const uint32_t incl = wave_incl_scan(n_mine);
+    if (lane == 63) wsum[wave] = incl;
+    __syncthreads();
+    if (n_mine > (uint32_t)pa.wcap) misc[3] = 1u;
+    uint32_t before = 0, n_cand = 0;
+#pragma unroll
+    for (int wv = 0; wv < NW; ++wv) {
+        if (wv < wave) before += wsum[wv];
+        n_cand += wsum[wv];
+    }
+    start[tid] = before + incl - n_mine;
+    __syncthreads();
+    const uint32_t k = (uint32_t)a.k_sel;
+    if (n_cand < k || n_cand > (uint32_t)kFinishCap || misc[3] != 0u) {   // workgroup-uniform
+        __syncthreads();
+        return false;
+    }
+    // the lists, 16 lanes to a list: all of a thread's first entries are requested together
+    {
+        constexpr int kRounds = kPartMax * NW / (NT / 16);
+        const int sub = tid & 15, grp = tid >> 4;
+        const uint2 *lists = pa.lists + (size_t)r * n_lists * pa.wcap;
+        uint2 first[kRounds];
+        uint32_t at[kRounds], n[kRounds];
+#pragma unroll
+        for (int q = 0; q < kRounds; ++q) {
+            const int l = q * (NT / 16) + grp;
+            at[q] = l < n_lists ? start[l] : 0u;
+            n[q] = l < n_lists ? (l + 1 < NT ? start[l + 1] : n_cand) - at[q] : 0u;   // (lists past the last one start at n_cand)
+            first[q] = uint2{0u, 0u};
+            if ((uint32_t)sub < n[q]) first[q] = lists[(size_t)l * pa.wcap + sub];
+        }
+        uint32_t tmax = 0;
+#pragma unroll
+        for (int q = 0; q < kRounds; ++q) {
+            const int l = q * (NT / 16) + grp;
+            for (uint32_t e = sub; e < n[q]; e += 16) {
+                const uint2 c = e == (uint32_t)sub ? first[q] : lists[(size_t)l * pa.wcap + e];
+                ckey[at[q] + e] = c.x;
+                cpos[at[q] + e] = c.y;
+                tmax = max(tmax, c.x);
+            }
+        }
+        tmax = wave_max_u32(tmax);
+        if (lane == 0 && tmax != 0u) atomicMax(&misc[1], tmax);
+    }
+    __syncthreads();
+    const uint32_t range = misc[1] - T0;
+    const int nbits = range ? 32 - __clz((int)range) : 0;
+    const int sh = nbits > 12 ? nbits - 12 : 0;
+    for (uint32_t j = tid; j < n_cand; j += NT) atomicAdd(&hist[(ckey[j] - T0) >> sh], 1u);
+    __syncthreads();
+    find_digit<NT, kBins1 / NT>(hist, k, wsum, bc, tid, lane, wave);
+    const uint32_t bstar = bc[0], need = bc[1], n_b = bc[2];
+    const bool ranked = need < n_b;            // the boundary bin is cut: rank its members exactly
+    if (ranked && n_b > (uint32_t)kBoundaryCap) {
+        __syncthreads();
+        return false;
+    }
+    for (uint32_t j = tid; j < n_cand; j += NT) {
+        const uint32_t bin = (ckey[j] - T0) >> sh;
+        if (bin > bstar || (bin == bstar && !ranked))
+            atomicOr(&bitmap[j >> 5], 1u << (j & 31u));
+        else if (bin == bstar)
+            bl[atomicAdd(&misc[2], 1u)] = j;
+    }
+    __syncthreads();
+    if (ranked) {
+        for (uint32_t m = tid; m < n_b; m += NT) {
+            const uint32_t jm = bl[m], km = ckey[jm];
+            uint32_t ahead = 0;                // members that beat this one: larger key, or equal key at a lower position
+            for (uint32_t x = 0; x < n_b; ++x) {
+                const uint32_t jx = bl[x];
+                ahead += (ckey[jx] > km || (ckey[jx] == km && jx < jm)) ? 1u : 0u;
+            }
+            if (ahead < need) atomicOr(&bitmap[jm >> 5], 1u << (jm & 31u));
+        }
+        __syncthreads();
+    }
+    // slots: selected candidates ahead of every bitmap word
+    {
+        const uint32_t mine = tid < kFinishCap / 32 ? (uint32_t)__popc(bitmap[tid]) : 0u;
+        const uint32_t inc = wave_incl_scan(mine);
+        if (lane == 63) wsum[wave] = inc;
+        __syncthreads();
+        uint32_t ahead = 0;
+#pragma unroll
+        for (int wv = 0; wv < NW; ++wv)
+            if (wv < wave) ahead += wsum[wv];
+        if (tid < kFinishCap / 32) wpre[tid] = ahead + inc - mine;
+    }
+    __syncthreads();
+    int32_t *oidx = a.idx + ((int64_t)rv.b * a.Tq + rv.i) * a.k_sel;
+    float *osel = a.sel ? a.sel + ((int64_t)rv.b * a.Tq + rv.i) * a.k_sel : nullptr;
+    for (uint32_t j = tid; j < n_cand; j += NT) {
+        const uint32_t word = bitmap[j >> 5], bit = j & 31u;
+        if ((word >> bit) & 1u) {
+            const uint32_t slot = wpre[j >> 5] + (uint32_t)__popc(word & ((1u << bit) - 1u));
+            if (slot < k) {                    // always true for a consistent select
+                oidx[slot] = (int32_t)cpos[j];
+                if (osel) osel[slot] = key_score(ckey[j]);
+            }
+        }
+    }
+    return true;
+    };
+    if (!finish()) {
+        SelectArgs ga = a;
+        constexpr int kSpace = 16 + 2 * kFinishCap;
+        ga.cache_elems = kSpace / 64 * 64;
+        select_row_generic<NT>(ga, smem);
+    }
+}
+constexpr int finish_lds_words() { return kBins1 + 2 * kPartWaves + 4 + 16 + 2 * kFinishCap + 2 * (kFinishCap / 32) + kPartThreads; }
+
 size_t select_lds_bytes(int cache_elems)
 {
     return (size_t)(kBins1 + 2 * 16 + 4 + cache_elems) * sizeof(uint32_t);
@@ -688,6 +960,54 @@ size_t select_lds_bytes(int cache_elems)
 } // namespace
 
 int select_cache_limit() { return 32768; }
+
+// Parts of a row when n_rows rows of up to max_row_len keys are selected together: enough for one workgroup per CU,
+// stretches of at least 256 keys per wave; 0 = the row-per-workgroup forms take the rows.
+int select_parts(int n_rows, int max_row_len)
+{
+    if (n_rows < 1 || max_row_len <= kPartFrom || n_rows > (max_row_len > kCandMaxLen ? kPartRowsLong : kPartRows)) return 0;
+    int p = 256 / n_rows;
+    const int most = max_row_len / (256 * kPartWaves);
+    p = p > most ? most : p;
+    return p < 1 ? 1 : (p > kPartMax ? kPartMax : p);
+}
+
+namespace {
+// list entries per wave: three times what a wave of a uniformly spread row keeps (about 2 k + 32 / 4096 of the row)
+int part_wcap(int n_parts, int max_row_len)
+{
+    const int64_t all = 3 * ((int64_t)2 * IC_MAX_K + (int64_t)max_row_len / 128);
+    const int64_t w = (all / (n_parts * kPartWaves) + 63) / 64 * 64;
+    return (int)(w < 128 ? 128 : w);
+}
+} // namespace
+
+size_t select_parts_bytes(int n_rows, int max_row_len)
+{
+    const int p = select_parts(n_rows, max_row_len);
+    if (p == 0) return 0;
+    return (size_t)n_rows * (part_head_words(p) * 4 + (size_t)p * kPartWaves * part_wcap(p, max_row_len) * sizeof(uint2));
+}
+
+hipError_t launch_select_parts(const SelectArgs &a_in, int n_rows, int max_row_len, void *ws, hipStream_t st)
+{
+    SelectArgs a = a_in;
+    a.cache_elems = 0;
+    PartArgs pa;
+    pa.n_parts = select_parts(n_rows, max_row_len);
+    pa.wcap = part_wcap(pa.n_parts, max_row_len);
+    pa.head_words = (int)part_head_words(pa.n_parts);
+    pa.heads = (uint32_t *)ws;
+    pa.lists = (uint2 *)(pa.heads + (size_t)n_rows * pa.head_words);
+    constexpr int lds = finish_lds_words() * (int)sizeof(uint32_t);
+    static hipError_t attr = hipFuncSetAttribute((const void *)select_finish_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (attr != hipSuccess) return attr;
+    hipLaunchKernelGGL(select_part_kernel, dim3((unsigned)pa.n_parts, (unsigned)n_rows), dim3(kPartThreads), 0, st, a, pa);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(select_finish_kernel, dim3((unsigned)n_rows), dim3(kPartThreads), lds, st, a, pa);
+    return hipGetLastError();
+}
 
 hipError_t launch_select(const SelectArgs &a_in, int n_rows, int max_row_len, hipStream_t st)
 {
@@ -725,8 +1045,8 @@ hipError_t launch_select(const SelectArgs &a_in, int n_rows, int max_row_len, hi
     if (max_row_len <= 8192)
         hipLaunchKernelGGL((select_kernel<256>), dim3((unsigned)n_rows), dim3(256), lds, st, a);
     else
-        // rows up to the cache limit stay in LDS after one read; longer ones (beyond the candidate form's range, or
-        // with k above a quarter of the row) are streamed on every sweep
+        // rows up to the cache limit stay in LDS after one read; longer ones (beyond the candidate form's range and
+        // too many for the parts form, or with k above a quarter of the row) are streamed on every sweep
         hipLaunchKernelGGL((select_kernel<1024>), dim3((unsigned)n_rows), dim3(1024), lds, st, a);
     return hipGetLastError();
 }
