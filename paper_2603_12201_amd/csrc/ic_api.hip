@@ -136,11 +136,11 @@ ic_status check_attn(const ic_attn_desc *d)
 // layouts two.
 int64_t attn_resident(const ic_attn_desc *d) { return (d->d_qk == 576 && d->v_off == 0) ? 256 : 512; }
 
-// The most key-slot splits per query a launch uses, which sizes the workspace: one when the queries alone fill the
-// chip, otherwise what brings their number up to that.
-int64_t attn_max_splits(const ic_attn_desc *d)
+// The most key-slot splits per query a launch of n_layers layers uses, which sizes the workspace: one when the queries
+// alone fill the chip, otherwise what brings their number up to that.
+int64_t attn_max_splits(const ic_attn_desc *d, int n_layers)
 {
-    const int64_t nq = (int64_t)d->B * d->Tq, wgs = attn_resident(d), tiles = (d->k_sel + 63) / 64;
+    const int64_t nq = (int64_t)n_layers * d->B * d->Tq, wgs = attn_resident(d), tiles = (d->k_sel + 63) / 64;
     const int64_t want = nq >= wgs ? 1 : (wgs + nq - 1) / nq;
     const int64_t ns = want > tiles ? tiles : want;
     const int64_t per = (tiles + ns - 1) / ns;
@@ -151,11 +151,11 @@ int64_t attn_max_splits(const ic_attn_desc *d)
 // tiles plus what a workgroup pays once (launch, Q, first rows, output: about two tiles).  The merge launch costs about
 // two tiles more.  One split too many can therefore double the time (40 queries x 7 splits of 5 tiles = 280 workgroups on
 // 256 CUs took 36 us, 6 splits of 6 tiles take 30), so the number with the fewest tile times wins, the smaller at a tie.
-void attn_splits(const ic_attn_desc *d, int *n_splits, int *split_len)
+void attn_splits(const ic_attn_desc *d, int n_layers, int *n_splits, int *split_len)
 {
-    const int64_t nq = (int64_t)d->B * d->Tq, wgs = attn_resident(d), tiles = (d->k_sel + 63) / 64;
+    const int64_t nq = (int64_t)n_layers * d->B * d->Tq, wgs = attn_resident(d), tiles = (d->k_sel + 63) / 64;
     int64_t best = 0, best_per = tiles;
-    for (int64_t ns = 1, most = attn_max_splits(d); ns <= most; ++ns) {
+    for (int64_t ns = 1, most = attn_max_splits(d, n_layers); ns <= most; ++ns) {
         const int64_t per = (tiles + ns - 1) / ns, n = (tiles + per - 1) / per;
         const int64_t cost = (nq * n + wgs - 1) / wgs * (per + 2) + (n > 1 ? 2 : 0);
         if (best == 0 || cost < best) {
@@ -167,12 +167,47 @@ void attn_splits(const ic_attn_desc *d, int *n_splits, int *split_len)
     *n_splits = (int)((tiles + best_per - 1) / best_per);
 }
 
-size_t attn_ws_bytes(const ic_attn_desc *d)
+size_t attn_ws_bytes(const ic_attn_desc *d, int n_layers = 1)
 {
-    const size_t ns = (size_t)attn_max_splits(d);
+    const size_t ns = (size_t)attn_max_splits(d, n_layers);
     if (ns <= 1) return 0;
-    const size_t nq = (size_t)d->B * d->Tq;
+    const size_t nq = (size_t)n_layers * d->B * d->Tq;
     return align_up(nq * ns * d->H_q * d->d_v * 2) + align_up(nq * ns * d->H_q * 2 * sizeof(float));   // bf16 partial outputs, fp32 (max, sum)
+}
+
+// Layers that one attention launch may take together: a Full layer and the Shared layers behind it read the same index
+// tensor, so what is left is that their shapes agree and that no layer's output overlaps another one's inputs or output
+// (called one after the other such layers would see each other's results).  Per layer, launches with few queries are
+// mostly latency (a launch and its merge of one decode token: 13.5 us for 2.4 MB of rows) and a last round of a few
+// workgroups; together they are taken where that saves an eighth of the tile times or more (700 queries a layer, 11 rounds
+// instead of 12, came out even: a last round with CUs to spare runs faster).
+struct Range {
+    const char *p;
+    size_t n;
+    bool meets(const Range &o) const { return p < o.p + o.n && o.p < p + n; }
+};
+int attn_batch(const ic_layer *layers, int n, const ic_paged_cache *pc)
+{
+    const ic_attn_desc &d = layers[0].at;
+    const size_t nq = (size_t)d.B * d.Tq;
+    const size_t rows = pc && pc->page_table ? (size_t)d.B * pc->max_pages * pc->page_size : (size_t)d.B * d.Lk;
+    auto q = [&](const ic_layer &l) { return Range{(const char *)l.Q, nq * d.H_q * d.d_qk * 2}; };
+    auto kv = [&](const ic_layer &l) { return Range{(const char *)l.KV, rows * d.row_elems * 2}; };
+    auto o = [&](const ic_layer &l) { return Range{(const char *)l.O, nq * d.H_q * d.d_v * 2}; };
+    int m = 1;
+    for (; m < n && m < ic::kMaxBatchLayers; ++m) {
+        const ic_layer &l = layers[m];
+        if (memcmp(&l.at, &d, sizeof d) != 0) break;
+        bool apart = true;
+        for (int j = 0; j < m && apart; ++j)
+            apart = !o(l).meets(q(layers[j])) && !o(l).meets(kv(layers[j])) && !o(l).meets(o(layers[j])) &&
+                    !o(layers[j]).meets(q(l)) && !o(layers[j]).meets(kv(l));
+        if (!apart) break;
+    }
+    // in tile times, as in attn_splits(): rounds of (tiles + 2), 2 per launch
+    const int64_t wgs = attn_resident(&d), tiles = (d.k_sel + 63) / 64;
+    const int64_t together = ((int64_t)(m * nq) + wgs - 1) / wgs * (tiles + 2) + 2, alone = m * (((int64_t)nq + wgs - 1) / wgs * (tiles + 2) + 2);
+    return together * 8 <= alone * 7 ? m : 1;
 }
 
 // ragged / paged cache description -> the kernels' view (all-zero when pc is NULL)
@@ -287,15 +322,22 @@ size_t indexer_min_ws(const ic_indexer_desc *d)
 
 // causal_pos0 >= 0: idx is this library's causal top-k for query rows at positions causal_pos0 + t (rows that can hold
 // fewer than k_sel entries end in -1s, and the kernel leaves their empty tiles out); -1: idx is the caller's own
-ic_status run_attn(const ic_attn_desc *d, const void *Q, const void *KV, const int32_t *idx, void *O, float *lse,
-                   void *ws, hipStream_t st, const ic_paged_cache *pc = nullptr, int64_t causal_pos0 = -1)
+ic_status run_attn_layers(const ic_layer *layers, int n_layers, const int32_t *idx, float *lse, void *ws, hipStream_t st,
+                          const ic_paged_cache *pc, int64_t causal_pos0)
 {
+    const ic_attn_desc *d = &layers[0].at;
     ic::AttnArgs a;
     memset(&a, 0, sizeof a);
-    a.Q = Q;
-    a.KV = KV;
+    a.Q = layers[0].Q;
+    a.KV = layers[0].KV;
+    a.O = layers[0].O;
+    for (int l = 0; l < n_layers; ++l) {
+        a.Qs[l] = layers[l].Q;
+        a.KVs[l] = layers[l].KV;
+        a.Os[l] = layers[l].O;
+    }
+    a.n_layers = n_layers;
     a.idx = idx;
-    a.O = O;
     a.lse = lse;
     a.B = d->B;
     a.Tq = d->Tq;
@@ -304,12 +346,12 @@ ic_status run_attn(const ic_attn_desc *d, const void *Q, const void *KV, const i
     a.v_off = d->v_off;
     a.row_elems = d->row_elems;
     a.k_sel = d->k_sel;
-    attn_splits(d, &a.n_splits, &a.split_len);
+    attn_splits(d, n_layers, &a.n_splits, &a.split_len);
     a.scale_log2e = d->sm_scale * 1.4426950408889634f;
     a.pv = paged_view(pc);
     a.causal_pos0 = causal_pos0;
     if (a.n_splits > 1) {
-        const size_t nq = (size_t)d->B * d->Tq;
+        const size_t nq = (size_t)n_layers * d->B * d->Tq;
         a.part_o = (__bf16 *)ws;
         a.part_ml = (float *)((char *)ws + align_up(nq * a.n_splits * d->H_q * d->d_v * 2));
     }
@@ -324,6 +366,18 @@ ic_status run_attn(const ic_attn_desc *d, const void *Q, const void *KV, const i
         if (e != hipSuccess) return fail(IC_ERR_HIP, "attention merge launch failed: %s", hipGetErrorString(e));
     }
     return IC_OK;
+}
+
+ic_status run_attn(const ic_attn_desc *d, const void *Q, const void *KV, const int32_t *idx, void *O, float *lse,
+                   void *ws, hipStream_t st, const ic_paged_cache *pc = nullptr)
+{
+    ic_layer l;
+    memset(&l, 0, sizeof l);
+    l.at = *d;
+    l.Q = Q;
+    l.KV = KV;
+    l.O = O;
+    return run_attn_layers(&l, 1, idx, lse, ws, st, pc, -1);
 }
 
 } // namespace
@@ -461,6 +515,14 @@ size_t ic_forward_stack_workspace(const ic_layer *layers, int32_t n_layers)
     for (int l = 0; l < n_layers; ++l) {
         size_t a = ic_sparse_attn_workspace(&layers[l].at);
         size_t b = layers[l].q ? ic_indexer_topk_workspace(&layers[l].ix) : 0;
+        // which layers are Full is not known here: room for any run of layers of this shape
+        if (a > 0) {
+            const int run = n_layers - l < ic::kMaxBatchLayers ? n_layers - l : ic::kMaxBatchLayers;
+            for (int m = 2; m <= run && memcmp(&layers[l + m - 1].at, &layers[l].at, sizeof layers[l].at) == 0; ++m) {
+                const size_t am = attn_ws_bytes(&layers[l].at, m);
+                if (am > a) a = am;
+            }
+        }
         if (a > need) need = a;
         if (b > need) need = b;
     }
@@ -500,8 +562,13 @@ static ic_status forward_stack_impl(const ic_layer *layers, int32_t n_layers, co
             if (s != IC_OK) return s;
             idx_pos0 = (pc && pc->seq_lens) ? -1 : (L->ix.q_pos0 >= 0 ? (int64_t)L->ix.q_pos0 : -1);
         }
-        s = run_attn(&L->at, L->Q, L->KV, idx_cache, L->O, nullptr, workspace, st, pc, idx_pos0);
+        int run = 1;                           // this layer and the Shared layers behind it
+        while (l + run < n_layers && !full_mask[l + run]) ++run;
+        int m = attn_batch(L, run, pc);
+        while (m > 1 && attn_ws_bytes(&L->at, m) > workspace_bytes) --m;
+        s = run_attn_layers(L, m, idx_cache, nullptr, workspace, st, pc, idx_pos0);
         if (s != IC_OK) return s;
+        l += m - 1;
     }
     return IC_OK;
 }

@@ -73,14 +73,17 @@ struct PartArgs {
     int32_t n_parts, wcap, head_words;
 };
 
+// One launch covers n_layers layers of one shape that read the same index tensor (a Full layer and the Shared layers
+// behind it); its queries are numbered layer by layer, layer * B * Tq + b * Tq + t.
+constexpr int kMaxBatchLayers = 8;
 struct AttnArgs {
-    const void *Q;        // [B,Tq,H_q,d_qk] bf16
+    const void *Q;        // [B,Tq,H_q,d_qk] bf16       (of the first layer; all of them: Qs, KVs, Os below)
     const void *KV;       // [B,Lk,row_elems] bf16
     const int32_t *idx;   // [B,Tq,k_sel]
     void *O;              // [B,Tq,H_q,d_v] bf16
-    float *lse;           // [B,Tq,H_q] or nullptr
-    __bf16 *part_o;       // split partials: [B*Tq, n_splits, H_q, d_v] bf16, each normalised by its own row sum
-    float *part_ml;       // [B*Tq, n_splits, H_q, 2] fp32 (running max in log2 units, sum)
+    float *lse;           // [B,Tq,H_q] or nullptr (one layer only)
+    __bf16 *part_o;       // split partials: [n_layers*B*Tq, n_splits, H_q, d_v] bf16, each normalised by its own row sum
+    float *part_ml;       // [n_layers*B*Tq, n_splits, H_q, 2] fp32 (running max in log2 units, sum)
     int32_t B, Tq, Lk, H_q, v_off, row_elems, k_sel;
     int32_t n_splits, split_len; // key slots per split (multiple of 64)
     float scale_log2e;    // sm_scale * log2(e)
@@ -89,6 +92,10 @@ struct AttnArgs {
     // holds min(k_sel, causal_pos0 + t + 1) entries followed by -1 only, and the tiles behind them need no work;
     // < 0: nothing is known about idx
     int64_t causal_pos0;
+    int32_t n_layers;
+    const void *Qs[kMaxBatchLayers];
+    const void *KVs[kMaxBatchLayers];
+    void *Os[kMaxBatchLayers];
 };
 
 // Head-aggregated attention probabilities over the selected rows (the indexer's training target).

@@ -80,7 +80,9 @@ __global__ __launch_bounds__(256, 2) void attn_kernel(AttnArgs a)
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int l16 = lane & 15, g = lane >> 4;
     const int mh = wave & 1, vh = wave >> 1;
-    const int64_t qrow = blockIdx.x;                      // flattened (b, t)
+    const int64_t gq = blockIdx.x;                        // query of the launch: flattened (layer, b, t)
+    const int layer = (int)(gq / ((int64_t)a.B * a.Tq));
+    const int64_t qrow = gq - (int64_t)layer * a.B * a.Tq;
     const int b = (int)(qrow / a.Tq);
     const int sp = blockIdx.y;
     const int slot0 = sp * a.split_len;
@@ -88,7 +90,7 @@ __global__ __launch_bounds__(256, 2) void attn_kernel(AttnArgs a)
     const int ntiles = (slot1 - slot0 + kTile - 1) / kTile;
 
     const int32_t *idx_row = a.idx + qrow * a.k_sel;
-    const unsigned short *kv_seq = (const unsigned short *)a.KV + (PG && a.pv.page_table ? 0 : (int64_t)b * a.Lk * a.row_elems);
+    const unsigned short *kv_seq = (const unsigned short *)a.KVs[layer] + (PG && a.pv.page_table ? 0 : (int64_t)b * a.Lk * a.row_elems);
     const int Lk_b = PG && a.pv.seq_lens ? min(a.pv.seq_lens[b], a.Lk) : a.Lk;     // ragged cache: rows of this sequence
 
     auto fetch_idx = [&](int it) -> int32_t {             // threads 0..31: validated row id of a slot
@@ -104,7 +106,7 @@ __global__ __launch_bounds__(256, 2) void attn_kernel(AttnArgs a)
     const bool wave_ok = 16 * mh < a.H_q;                 // wave-uniform: any valid head at all
     bf16x8 qreg[KSTEPS];
     {
-        const unsigned short *qp = (const unsigned short *)a.Q + (qrow * a.H_q + (head_ok ? head : 0)) * D_QK + 8 * g;
+        const unsigned short *qp = (const unsigned short *)a.Qs[layer] + (qrow * a.H_q + (head_ok ? head : 0)) * D_QK + 8 * g;
 #pragma unroll
         for (int ks = 0; ks < KSTEPS; ++ks) {
             u32x4 raw = u32x4{0u, 0u, 0u, 0u};
@@ -218,7 +220,7 @@ __global__ __launch_bounds__(256, 2) void attn_kernel(AttnArgs a)
     const bool split = a.n_splits > 1;
     if (vh == 0 && g == 0 && head_ok) {
         if (split) {
-            float *ml = a.part_ml + ((qrow * a.n_splits + sp) * a.H_q + head) * 2;
+            float *ml = a.part_ml + ((gq * a.n_splits + sp) * a.H_q + head) * 2;
             ml[0] = m_run;
             ml[1] = l_tot;
         } else if (a.lse) {
@@ -235,8 +237,8 @@ __global__ __launch_bounds__(256, 2) void attn_kernel(AttnArgs a)
         // a split stores its own normalised output (bf16, like the final one); the merge weighs the
         // splits by their share of the total row sum
         const float inv = (l > 0.f) ? 1.f / l : 0.f;
-        __bf16 *po = (split ? a.part_o + ((qrow * a.n_splits + sp) * a.H_q + hq) * D_V
-                            : (__bf16 *)a.O + (qrow * a.H_q + hq) * D_V) + DVW * vh;
+        __bf16 *po = (split ? a.part_o + ((gq * a.n_splits + sp) * a.H_q + hq) * D_V
+                            : (__bf16 *)a.Os[layer] + (qrow * a.H_q + hq) * D_V) + DVW * vh;
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) po[16 * nb + l16] = (__bf16)(oacc[nb][i] * inv);
     }
@@ -310,7 +312,9 @@ __device__ __forceinline__ unsigned rows_mask(unsigned long long ba, unsigned lo
 
 // SPLIT: blockIdx.y selects a.split_len key slots of the query and the result is a partial
 // (unnormalised accumulators, reference maximum, row sum) for the merge kernel.
-template <int D_QK, int D_V, bool PG, bool SPLIT>         // value columns = the first D_V features of a row; PG as above
+// MULTI: a.n_layers layers in one launch (a chain that has to know a query's layer spills seven registers more, 2 % of a
+// long chain's time, so one layer alone does without).
+template <int D_QK, int D_V, bool PG, bool SPLIT, bool MULTI>   // value columns = the first D_V features of a row; PG as above
 __global__ __launch_bounds__(256, 1) void attn_slab_kernel(AttnArgs a)
 {
     constexpr int KS = D_QK / 32;                         // contraction steps of S^T = 16-byte chunks per gather lane
@@ -338,7 +342,7 @@ __global__ __launch_bounds__(256, 1) void attn_slab_kernel(AttnArgs a)
     // queries): the workgroup walks queries blockIdx.x, + gridDim.x, ... and treats their tiles as
     // one stream, so that the gather and staging of the next query's first tiles and the load of
     // its Q run under the last steps and the output stores of the current one.
-    const int64_t nq = (int64_t)a.B * a.Tq;
+    const int64_t nq_layer = (int64_t)a.B * a.Tq, nq = MULTI ? nq_layer * a.n_layers : nq_layer;
     const bool chain = !SPLIT && ntiles >= 3 && (int64_t)gridDim.x < nq;   // workgroup-uniform
     int64_t qrow = blockIdx.x;
     if (chain && (gridDim.x & 7u) == 0) {
@@ -354,11 +358,14 @@ __global__ __launch_bounds__(256, 1) void attn_slab_kernel(AttnArgs a)
     // nt: tiles of the query in the chained stream.  When the selection is known to be a causal top-k, a row near the
     // start of a sequence holds fewer than k_sel entries and ends in -1s: its tiles behind the last entry are left
     // out (never fewer than three per query: the stream looks three tiles ahead and knows two queries at a time).
-    struct Src { const int32_t *idx_row; const unsigned short *kv; int b, len, nt; bool live; };
+    struct Src { const int32_t *idx_row; const unsigned short *kv; int64_t q; int layer, b, len, nt; bool live; };   // q: query within its layer
     auto src_of = [&](int64_t q) {
         Src r;
         r.live = q < nq;
-        const int64_t qq = r.live ? q : (int64_t)blockIdx.x;          // a dead source still reads valid memory
+        const int64_t gq = r.live ? q : (int64_t)blockIdx.x;          // a dead source still reads valid memory
+        r.layer = MULTI ? (int)(gq / nq_layer) : 0;
+        const int64_t qq = MULTI ? gq - r.layer * nq_layer : gq;
+        if constexpr (MULTI) r.q = qq;
         r.b = (int)(qq / a.Tq);
         r.nt = ntiles;
         if (!SPLIT && a.causal_pos0 >= 0) {
@@ -367,11 +374,12 @@ __global__ __launch_bounds__(256, 1) void attn_slab_kernel(AttnArgs a)
             r.nt = min(r.nt, ntiles);
         }
         r.idx_row = a.idx + qq * a.k_sel;
-        r.kv = (const unsigned short *)a.KV + (PG && a.pv.page_table ? 0 : (int64_t)r.b * a.Lk * a.row_elems);
+        r.kv = (const unsigned short *)(MULTI ? a.KVs[r.layer] : a.KV) + (PG && a.pv.page_table ? 0 : (int64_t)r.b * a.Lk * a.row_elems);
         r.len = PG && a.pv.seq_lens ? min(a.pv.seq_lens[r.b], a.Lk) : a.Lk;   // ragged cache: rows of this sequence
         return r;
     };
     Src cs = src_of(qrow), ns = src_of(qnext);            // current and next query
+    auto q_cur = [&]() { return MULTI ? cs.q : qrow; };
 
     // Loads inside the tile loop are unconditional (clamped addresses, result discarded when out
     // of range): the wait counters are positional, and a load that may or may not have been
@@ -401,12 +409,12 @@ __global__ __launch_bounds__(256, 1) void attn_slab_kernel(AttnArgs a)
     // loads are issued before anything waits for one of them, and the ids and rows of the first
     // tile are requested in their shadow.
     u32x4 qraw[2][KS];
-    auto load_q = [&](int64_t q) {
+    auto load_q = [&](int64_t q, int layer) {
 #pragma unroll
         for (int hb = 0; hb < 2; ++hb) {
             const int head = 16 * hb + l16;
             const bool ok = head < a.H_q;
-            const unsigned short *qp = (const unsigned short *)a.Q + (q * a.H_q + (ok ? head : 0)) * D_QK + 8 * g;
+            const unsigned short *qp = (const unsigned short *)(MULTI ? a.Qs[layer] : a.Q) + (q * a.H_q + (ok ? head : 0)) * D_QK + 8 * g;
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) {
                 qraw[hb][ks] = u32x4{0u, 0u, 0u, 0u};
@@ -469,14 +477,14 @@ __global__ __launch_bounds__(256, 1) void attn_slab_kernel(AttnArgs a)
     // Only wave 0 loads (each load touches 16 rows of Q, so four waves loading the same 36 KB keep the
     // CU's one address unit busy for 2.8 us); it then hands Q to the other waves through the tile
     // buffer that is free between two queries, in the very lane order the operand has.
-    auto load_q_direct = [&](int64_t q) {
+    auto load_q_direct = [&](int64_t q, int layer) {
         if (wave_u != 0) return;
         // the lane's offset into Q is recomputed from the lane id here: kept live across the tile
         // loop it would be spilled, and its reload would wait behind the gathers in flight
         int ln = lane;
         asm volatile("" : "+v"(ln));
         const int hd = ln & 15, gq = ln >> 4;
-        const unsigned short *q0 = (const unsigned short *)a.Q + q * a.H_q * D_QK + 8 * gq;
+        const unsigned short *q0 = (const unsigned short *)(MULTI ? a.Qs[layer] : a.Q) + q * a.H_q * D_QK + 8 * gq;
         if (a.H_q >= 32) {                                // workgroup-uniform: every lane has a head
 #pragma unroll
             for (int hb = 0; hb < 2; ++hb)
@@ -543,7 +551,7 @@ __global__ __launch_bounds__(256, 1) void attn_slab_kernel(AttnArgs a)
         __builtin_amdgcn_sched_barrier(0);
         // one wave loads Q (see load_q_direct above) and hands it over; its loads go out behind the
         // id fetches, so that the ids, and with them the first gather, do not wait for Q
-        if (wave_u == 0) load_q(qrow);
+        if (wave_u == 0) load_q(q_cur(), cs.layer);
         gload(d0, 0);
         __builtin_amdgcn_sched_barrier(0);
         {   // Q from wave 0 to the others through the second tile buffer (unused until step 0 stages tile 1)
@@ -807,7 +815,7 @@ __global__ __launch_bounds__(256, 1) void attn_slab_kernel(AttnArgs a)
                 }
             } else {
                 if (wave == 0 && hh == 0 && l32 < a.H_q && a.lse)
-                    a.lse[qrow * a.H_q + l32] =
+                    a.lse[q_cur() * a.H_q + l32] =
                         (l_head > 0.f) ? (m_head + __builtin_log2f(l_head)) * 0.6931471805599453f : -INFINITY;
             }
             // accumulator element i belongs to head 8 (i / 4) + 4 hh + i % 4: the sums of the lane's
@@ -828,7 +836,7 @@ __global__ __launch_bounds__(256, 1) void attn_slab_kernel(AttnArgs a)
             int tx = tid;
             asm volatile("" : "+v"(tx));
             const int o_lane = 32 * (tx >> 6) + (tx & 31), o_hh = (tx >> 5) & 1;
-            __bf16 *o_row = (SPLIT ? a.part_o + (qrow * a.n_splits + sp) * a.H_q * D_V : (__bf16 *)a.O + qrow * a.H_q * D_V) + o_lane;
+            __bf16 *o_row = (SPLIT ? a.part_o + (qrow * a.n_splits + sp) * a.H_q * D_V : (__bf16 *)(MULTI ? a.Os[cs.layer] : a.O) + q_cur() * a.H_q * D_V) + o_lane;
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
                 const int hq = 8 * (i >> 2) + 4 * o_hh + (i & 3); // O row (head) of accumulator element i
@@ -878,7 +886,7 @@ __global__ __launch_bounds__(256, 1) void attn_slab_kernel(AttnArgs a)
             for (int it = 1; it < cs.nt; ++it) step(it, T, T, T, T);
             step(cs.nt, T, F, F, F);
             const bool more = qnext < nq;
-            if (more) load_q_direct(qnext);               // lands while the outputs are stored
+            if (more) load_q_direct(MULTI ? ns.q : qnext, ns.layer);               // lands while the outputs are stored
             finish();
             if (!more) break;
             qrow = qnext;
@@ -914,12 +922,14 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a)
     constexpr int LPS = D_V / 8, SLOTS = 256 / LPS, kBatch = 8;
     __shared__ __attribute__((aligned(16))) float o_sh[SLOTS][D_V];
     __shared__ float m_sh[SLOTS], l_sh[SLOTS];
-    const int64_t qrow = blockIdx.x;
+    const int64_t gq = blockIdx.x;
+    const int layer = (int)(gq / ((int64_t)a.B * a.Tq));
+    const int64_t qrow = gq - (int64_t)layer * a.B * a.Tq;
     const int h = blockIdx.y;
     const int slot = threadIdx.x / LPS, v = (threadIdx.x % LPS) * 8;
-    const float *ml = a.part_ml + ((qrow * a.n_splits) * a.H_q + h) * 2;
+    const float *ml = a.part_ml + ((gq * a.n_splits) * a.H_q + h) * 2;
     const int64_t ml_stride = (int64_t)a.H_q * 2;
-    const __bf16 *po = a.part_o + ((qrow * a.n_splits) * a.H_q + h) * D_V + v;
+    const __bf16 *po = a.part_o + ((gq * a.n_splits) * a.H_q + h) * D_V + v;
     const int64_t po_stride = (int64_t)a.H_q * D_V;
     float m = -INFINITY, l = 0.f, o[8];
 #pragma unroll
@@ -980,7 +990,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a)
     }
     const float inv = (lt > 0.f) ? 1.f / lt : 0.f;
     typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
-    *(bf16x2 *)((__bf16 *)a.O + (qrow * a.H_q + h) * D_V + c) = bf16x2{(__bf16)(t0 * inv), (__bf16)(t1 * inv)};
+    *(bf16x2 *)((__bf16 *)a.Os[layer] + (qrow * a.H_q + h) * D_V + c) = bf16x2{(__bf16)(t0 * inv), (__bf16)(t1 * inv)};
     if (threadIdx.x == 0 && a.lse)
         a.lse[qrow * a.H_q + h] = (lt > 0.f) ? (mt + __builtin_log2f(lt)) * 0.6931471805599453f : -INFINITY;
 }
@@ -996,7 +1006,7 @@ hipError_t launch_t(const AttnArgs &a, hipStream_t st)
                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (attr != hipSuccess) return attr;
     if (attr_pg != hipSuccess) return attr_pg;
-    dim3 grid((unsigned)((int64_t)a.B * a.Tq), (unsigned)a.n_splits);
+    dim3 grid((unsigned)((int64_t)a.n_layers * a.B * a.Tq), (unsigned)a.n_splits);
     if (a.pv.seq_lens || a.pv.page_table)
         hipLaunchKernelGGL((attn_kernel<D_QK, D_V, ROW_F, true>), grid, dim3(256), lds, st, a);
     else
@@ -1004,13 +1014,13 @@ hipError_t launch_t(const AttnArgs &a, hipStream_t st)
     return hipGetLastError();
 }
 
-template <int D_QK, int D_V, bool PG, bool SPLIT>
+template <int D_QK, int D_V, bool PG, bool SPLIT, bool MULTI>
 hipError_t launch_slab_t(const AttnArgs &a, size_t lds, hipStream_t st)
 {
-    static hipError_t attr = hipFuncSetAttribute((const void *)attn_slab_kernel<D_QK, D_V, PG, SPLIT>,
+    static hipError_t attr = hipFuncSetAttribute((const void *)attn_slab_kernel<D_QK, D_V, PG, SPLIT, MULTI>,
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (attr != hipSuccess) return attr;
-    int64_t wgs = (int64_t)a.B * a.Tq;
+    int64_t wgs = (int64_t)a.n_layers * a.B * a.Tq;
     if (!SPLIT && a.k_sel > 2 * kSlabTile) {
         // whole selections of three or more tiles: one workgroup per CU walks a chain of queries
         static int n_cu = 0;
@@ -1023,7 +1033,7 @@ hipError_t launch_slab_t(const AttnArgs &a, size_t lds, hipStream_t st)
         if (wgs > n_cu) wgs = n_cu;
     }
     dim3 grid((unsigned)wgs, (unsigned)(SPLIT ? a.n_splits : 1));
-    hipLaunchKernelGGL((attn_slab_kernel<D_QK, D_V, PG, SPLIT>), grid, dim3(256), lds, st, a);
+    hipLaunchKernelGGL((attn_slab_kernel<D_QK, D_V, PG, SPLIT, MULTI>), grid, dim3(256), lds, st, a);
     return hipGetLastError();
 }
 
@@ -1032,8 +1042,9 @@ hipError_t launch_slab(const AttnArgs &a, hipStream_t st)
 {
     const size_t lds = (size_t)2 * kSlabTile * (D_QK * 2 + kSlabPad) + 2 * 32 * (kSlabTile * 2 + 16) + (4 * 32 + 4 * 32) * sizeof(float);
     const bool pg = a.pv.seq_lens || a.pv.page_table;
-    if (a.n_splits > 1) return pg ? launch_slab_t<D_QK, D_V, true, true>(a, lds, st) : launch_slab_t<D_QK, D_V, false, true>(a, lds, st);
-    return pg ? launch_slab_t<D_QK, D_V, true, false>(a, lds, st) : launch_slab_t<D_QK, D_V, false, false>(a, lds, st);
+    if (a.n_splits > 1) return pg ? launch_slab_t<D_QK, D_V, true, true, true>(a, lds, st) : launch_slab_t<D_QK, D_V, false, true, true>(a, lds, st);
+    if (a.n_layers > 1) return pg ? launch_slab_t<D_QK, D_V, true, false, true>(a, lds, st) : launch_slab_t<D_QK, D_V, false, false, true>(a, lds, st);
+    return pg ? launch_slab_t<D_QK, D_V, true, false, false>(a, lds, st) : launch_slab_t<D_QK, D_V, false, false, false>(a, lds, st);
 }
 
 } // namespace
@@ -1060,7 +1071,7 @@ hipError_t launch_attn(const AttnArgs &a, int d_qk, int d_v, hipStream_t st)
 hipError_t launch_attn_merge(const AttnArgs &a, int d_v, hipStream_t st)
 {
     if ((int64_t)a.B * a.Tq <= 0) return hipSuccess;
-    dim3 grid((unsigned)((int64_t)a.B * a.Tq), (unsigned)a.H_q);
+    dim3 grid((unsigned)((int64_t)a.n_layers * a.B * a.Tq), (unsigned)a.H_q);
     if (d_v == 512)
         hipLaunchKernelGGL((attn_merge_kernel<512>), grid, dim3(256), 0, st, a);
     else if (d_v == 64)
