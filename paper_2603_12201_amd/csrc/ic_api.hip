@@ -147,16 +147,23 @@ int64_t attn_max_splits(const ic_attn_desc *d, int n_layers)
     return (tiles + per - 1) / per;
 }
 
+// Partials of `parts` (query, split) pairs: bf16 outputs, fp32 (max, sum).
+size_t split_bytes(const ic_attn_desc *d, int64_t parts)
+{
+    return align_up((size_t)parts * d->H_q * d->d_v * 2) + align_up((size_t)parts * d->H_q * 2 * sizeof(float));
+}
+
 // Splits of a launch.  Workgroups run in rounds of attn_resident(), and a round takes as long as its longest workgroup:
 // tiles plus what a workgroup pays once (launch, Q, first rows, output: about two tiles).  The merge launch costs about
 // two tiles more.  One split too many can therefore double the time (40 queries x 7 splits of 5 tiles = 280 workgroups on
 // 256 CUs took 36 us, 6 splits of 6 tiles take 30), so the number with the fewest tile times wins, the smaller at a tie.
-void attn_splits(const ic_attn_desc *d, int n_layers, int *n_splits, int *split_len)
+void attn_splits(const ic_attn_desc *d, int n_layers, size_t ws_bytes, int *n_splits, int *split_len)
 {
     const int64_t nq = (int64_t)n_layers * d->B * d->Tq, wgs = attn_resident(d), tiles = (d->k_sel + 63) / 64;
     int64_t best = 0, best_per = tiles;
     for (int64_t ns = 1, most = attn_max_splits(d, n_layers); ns <= most; ++ns) {
         const int64_t per = (tiles + ns - 1) / ns, n = (tiles + per - 1) / per;
+        if (n > 1 && split_bytes(d, nq * n) > ws_bytes) continue;
         const int64_t cost = (nq * n + wgs - 1) / wgs * (per + 2) + (n > 1 ? 2 : 0);
         if (best == 0 || cost < best) {
             best = cost;
@@ -171,8 +178,7 @@ size_t attn_ws_bytes(const ic_attn_desc *d, int n_layers = 1)
 {
     const size_t ns = (size_t)attn_max_splits(d, n_layers);
     if (ns <= 1) return 0;
-    const size_t nq = (size_t)n_layers * d->B * d->Tq;
-    return align_up(nq * ns * d->H_q * d->d_v * 2) + align_up(nq * ns * d->H_q * 2 * sizeof(float));   // bf16 partial outputs, fp32 (max, sum)
+    return split_bytes(d, (int64_t)n_layers * d->B * d->Tq * (int64_t)ns);
 }
 
 // Layers that one attention launch may take together: a Full layer and the Shared layers behind it read the same index
@@ -320,10 +326,22 @@ size_t indexer_min_ws(const ic_indexer_desc *d)
     return align_up((size_t)rows * strip_ld(d) * sizeof(float));
 }
 
+// Leading query rows of every sequence that the dense form takes: the rows that see at most k_sel keys and so select all
+// of them.  Its workgroups walk their keys one tile after the other, so where they leave most of the chip idle and the
+// walk is long (a short chunk behind a prefix), the forms that split a selection over workgroups are the faster ones.
+int dense_queries(const ic_attn_desc *d, int n_layers, int64_t causal_pos0)
+{
+    if (n_layers != 1 || causal_pos0 < 0 || attn_resident(d) != 256 || d->d_v != 512) return 0;
+    int64_t n = (d->k_sel < d->Lk ? d->k_sel : d->Lk) - causal_pos0;
+    n = n < 0 ? 0 : (n > d->Tq ? d->Tq : n);
+    const int64_t blocks = (n * d->H_q + 63) / 64 * d->B, tiles = (causal_pos0 + n + 63) / 64;
+    return n > 0 && (blocks >= 128 || tiles <= 4) ? (int)n : 0;
+}
+
 // causal_pos0 >= 0: idx is this library's causal top-k for query rows at positions causal_pos0 + t (rows that can hold
 // fewer than k_sel entries end in -1s, and the kernel leaves their empty tiles out); -1: idx is the caller's own
-ic_status run_attn_layers(const ic_layer *layers, int n_layers, const int32_t *idx, float *lse, void *ws, hipStream_t st,
-                          const ic_paged_cache *pc, int64_t causal_pos0)
+ic_status run_attn_layers(const ic_layer *layers, int n_layers, const int32_t *idx, float *lse, void *ws, size_t ws_bytes,
+                          hipStream_t st, const ic_paged_cache *pc, int64_t causal_pos0)
 {
     const ic_attn_desc *d = &layers[0].at;
     ic::AttnArgs a;
@@ -346,10 +364,35 @@ ic_status run_attn_layers(const ic_layer *layers, int n_layers, const int32_t *i
     a.v_off = d->v_off;
     a.row_elems = d->row_elems;
     a.k_sel = d->k_sel;
-    attn_splits(d, n_layers, &a.n_splits, &a.split_len);
     a.scale_log2e = d->sm_scale * 1.4426950408889634f;
     a.pv = paged_view(pc);
     a.causal_pos0 = causal_pos0;
+    if (const int nd = dense_queries(d, n_layers, causal_pos0)) {
+        ProfScope ps(2, st);
+        const ic::DenseArgs da{nd, (int32_t)causal_pos0};
+        hipError_t e = ic::launch_attn_dense(a, da, st);
+        if (e != hipSuccess) return fail(IC_ERR_HIP, "dense attention launch failed: %s", hipGetErrorString(e));
+        if (nd == d->Tq) return IC_OK;
+        for (int b = 0; b < d->B; ++b) {       // the other rows, a sequence at a time
+            ic_layer r = layers[0];
+            r.at.B = 1;
+            r.at.Tq = d->Tq - nd;
+            const int64_t row = (int64_t)b * d->Tq + nd;
+            r.Q = (const char *)r.Q + row * d->H_q * d->d_qk * 2;
+            r.O = (char *)r.O + row * d->H_q * d->d_v * 2;
+            ic_paged_cache pb;
+            if (pc) {
+                pb = *pc;
+                if (pb.page_table) pb.page_table += (int64_t)b * pb.max_pages;
+            }
+            if (!pc || !pc->page_table) r.KV = (const char *)r.KV + (int64_t)b * d->Lk * d->row_elems * 2;
+            ic_status s = run_attn_layers(&r, 1, idx + row * d->k_sel, lse ? lse + row * d->H_q : nullptr, ws, ws_bytes, st,
+                                          pc ? &pb : nullptr, causal_pos0 + nd);
+            if (s != IC_OK) return s;
+        }
+        return IC_OK;
+    }
+    attn_splits(d, n_layers, ws_bytes, &a.n_splits, &a.split_len);
     if (a.n_splits > 1) {
         const size_t nq = (size_t)n_layers * d->B * d->Tq;
         a.part_o = (__bf16 *)ws;
@@ -369,7 +412,7 @@ ic_status run_attn_layers(const ic_layer *layers, int n_layers, const int32_t *i
 }
 
 ic_status run_attn(const ic_attn_desc *d, const void *Q, const void *KV, const int32_t *idx, void *O, float *lse,
-                   void *ws, hipStream_t st, const ic_paged_cache *pc = nullptr)
+                   void *ws, size_t ws_bytes, hipStream_t st, const ic_paged_cache *pc = nullptr)
 {
     ic_layer l;
     memset(&l, 0, sizeof l);
@@ -377,7 +420,7 @@ ic_status run_attn(const ic_attn_desc *d, const void *Q, const void *KV, const i
     l.Q = Q;
     l.KV = KV;
     l.O = O;
-    return run_attn_layers(&l, 1, idx, lse, ws, st, pc, -1);
+    return run_attn_layers(&l, 1, idx, lse, ws, ws_bytes, st, pc, -1);
 }
 
 } // namespace
@@ -429,7 +472,7 @@ ic_status ic_sparse_attn(const ic_attn_desc *d, const void *Q, const void *KV, c
     if (!Q || !KV || !idx || !O) return fail(IC_ERR_NULL, "Q, KV, idx and O must not be NULL");
     s = check_ws(workspace, workspace_bytes, attn_ws_bytes(d));
     if (s != IC_OK) return s;
-    return run_attn(d, Q, KV, idx, O, lse, workspace, (hipStream_t)stream);
+    return run_attn(d, Q, KV, idx, O, lse, workspace, workspace_bytes, (hipStream_t)stream);
 }
 
 namespace {
@@ -472,7 +515,7 @@ ic_status ic_sparse_attn_static(const ic_attn_desc *d, const void *Q, const void
         s = static_scratch(&ws);
         if (s != IC_OK) return s;
     }
-    return run_attn(d, Q, KV, idx, O, lse, ws, (hipStream_t)stream);
+    return run_attn(d, Q, KV, idx, O, lse, ws, need, (hipStream_t)stream);
 }
 
 static ic_status check_stack(const ic_layer *layers, int32_t n, const uint8_t *full_mask)
@@ -564,9 +607,9 @@ static ic_status forward_stack_impl(const ic_layer *layers, int32_t n_layers, co
         }
         int run = 1;                           // this layer and the Shared layers behind it
         while (l + run < n_layers && !full_mask[l + run]) ++run;
-        int m = attn_batch(L, run, pc);
+        int m = dense_queries(&L->at, 1, idx_pos0) ? 1 : attn_batch(L, run, pc);
         while (m > 1 && attn_ws_bytes(&L->at, m) > workspace_bytes) --m;
-        s = run_attn_layers(L, m, idx_cache, nullptr, workspace, st, pc, idx_pos0);
+        s = run_attn_layers(L, m, idx_cache, nullptr, workspace, workspace_bytes, st, pc, idx_pos0);
         if (s != IC_OK) return s;
         l += m - 1;
     }
@@ -611,7 +654,7 @@ ic_status ic_sparse_attn_paged(const ic_attn_desc *d, const ic_paged_cache *pc, 
     if (!Q || !KV_pool || !idx || !O) return fail(IC_ERR_NULL, "Q, KV_pool, idx and O must not be NULL");
     s = check_ws(workspace, workspace_bytes, attn_ws_bytes(d));
     if (s != IC_OK) return s;
-    return run_attn(d, Q, KV_pool, idx, O, lse, workspace, (hipStream_t)stream, pc);
+    return run_attn(d, Q, KV_pool, idx, O, lse, workspace, workspace_bytes, (hipStream_t)stream, pc);
 }
 
 ic_status ic_pattern_from_string(const char *fs, uint8_t *full_mask, int32_t n)
@@ -701,6 +744,7 @@ ic_status ic_similarity_matrix(const ic_layer *layers, int32_t n_layers, const i
     char *ws = (char *)workspace;
     void *o_reuse = ws;
     void *attn_ws = ws + sim_o_bytes(&layers[0].at);
+    const size_t attn_bytes = ic_similarity_matrix_workspace(layers, n_layers) - kAlign - sim_o_bytes(&layers[0].at);
     double *acc = (double *)(ws + ic_similarity_matrix_workspace(layers, n_layers) - kAlign);
     hipError_t e = ic::launch_sim_init(S, n_layers, st);
     if (e != hipSuccess) return fail(IC_ERR_HIP, "similarity init failed: %s", hipGetErrorString(e));
@@ -708,10 +752,10 @@ ic_status ic_similarity_matrix(const ic_layer *layers, int32_t n_layers, const i
     const int64_t n_rows = (int64_t)a0->B * a0->Tq, row_len = (int64_t)a0->H_q * a0->d_v;
     for (int i = 0; i < n_layers; ++i) {
         const ic_layer *L = &layers[i];
-        s = run_attn(&L->at, L->Q, L->KV, idx_layers[i], L->O, nullptr, attn_ws, st);       // own indices
+        s = run_attn(&L->at, L->Q, L->KV, idx_layers[i], L->O, nullptr, attn_ws, attn_bytes, st);       // own indices
         if (s != IC_OK) return s;
         for (int j = 0; j < i; ++j) {
-            s = run_attn(&L->at, L->Q, L->KV, idx_layers[j], o_reuse, nullptr, attn_ws, st); // as a Shared layer reading j
+            s = run_attn(&L->at, L->Q, L->KV, idx_layers[j], o_reuse, nullptr, attn_ws, attn_bytes, st); // as a Shared layer reading j
             if (s != IC_OK) return s;
             e = ic::launch_cosine(L->O, o_reuse, n_rows, row_len, S + (size_t)i * n_layers + j, nullptr, acc, st);
             if (e != hipSuccess) return fail(IC_ERR_HIP, "cosine launch failed: %s", hipGetErrorString(e));

@@ -98,6 +98,12 @@ struct AttnArgs {
     void *Os[kMaxBatchLayers];
 };
 
+// The rows of a launch whose selection is a whole prefix of the cache.
+struct DenseArgs {
+    int32_t n_queries;    // per sequence, from row 0
+    int32_t pos0;         // row t sees the keys 0 .. pos0 + t, all of them below Lk
+};
+
 // Head-aggregated attention probabilities over the selected rows (the indexer's training target).
 struct ProbsArgs {
     const void *Q;        // [B,Tq,H_q,d_qk] bf16
@@ -141,6 +147,7 @@ int select_parts(int n_rows, int max_row_len);
 size_t select_parts_bytes(int n_rows, int max_row_len);
 hipError_t launch_select_parts(const SelectArgs &a, int n_rows, int max_row_len, void *ws, hipStream_t st);
 hipError_t launch_attn(const AttnArgs &a, int d_qk, int d_v, hipStream_t st);
+hipError_t launch_attn_dense(const AttnArgs &a, const DenseArgs &da, hipStream_t st);
 hipError_t launch_attn_merge(const AttnArgs &a, int d_v, hipStream_t st);
 size_t overlap_ws_bytes(int n_layers);
 size_t overlap_lds_bytes(int n_layers, int Lk);

@@ -1,0 +1,66 @@
+"""Query rows that see at most k keys inside forward_stack (the dense attention form), alone and followed by rows with a
+real selection: edges of the 64-row blocks and 64-key tiles, head counts, offsets, a page table, logits that move the
+softmax reference."""
+import pytest
+import torch
+
+from tests import parity
+import synth
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # B, Tq, pos0, H_q, k, row_elems, page, scale
+    (1, 16, 0, 32, 64, 576, 0, 1 / 24.0),
+    (2, 65, 0, 32, 256, 576, 0, 1 / 24.0),
+    (1, 129, 0, 20, 2048, 640, 0, 1 / 24.0),
+    (3, 100, 40, 7, 512, 576, 0, 1 / 24.0),
+    (1, 200, 0, 1, 300, 576, 0, 1 / 24.0),
+    (1, 320, 0, 32, 256, 576, 0, 1 / 24.0),       # 256 dense rows, 64 with a selection
+    (2, 300, 0, 16, 130, 576, 0, 1 / 24.0),       # the same for two sequences
+    (1, 257, 0, 32, 256, 576, 0, 1 / 24.0),       # one row with a selection
+    (2, 190, 0, 32, 256, 576, 64, 1 / 24.0),      # paged
+    (2, 150, 0, 32, 128, 576, 64, 1 / 24.0),      # paged, with a selection
+    (1, 300, 700, 32, 1100, 576, 0, 1 / 24.0),    # behind a prefix
+    (1, 20, 400, 32, 500, 576, 0, 1 / 24.0),      # too few blocks for it
+    (1, 150, 0, 32, 256, 576, 0, 2.0),            # scores hundreds apart: the reference moves
+]
+
+
+@pytest.mark.parametrize("case", CASES)
+def test_dense_rows(oracle, case):
+    import paper_2603_12201_amd as ic
+    B, Tq, pos0, H_q, ks, row, page, scale = case
+    print("[case] dense B=%d Tq=%d pos0=%d H_q=%d k=%d row=%d page=%d scale=%g" % case, flush=True)
+    Lk = pos0 + Tq
+    cfg = synth.config("c2", B=B, Tq=Tq, Lk=Lk, q_pos0=pos0, H_q=H_q, k_sel=ks, row_elems=row, H_I=4, seed=Tq + H_q)
+    t = synth.indexer_layer(cfg, 0)
+    t.update(synth.attn_layer(cfg, 0))
+    g = {n: v.cuda() for n, v in t.items()}
+    out = torch.full((B, Tq, H_q, 512), 7.0, dtype=torch.bfloat16, device="cuda")
+    idx = torch.empty((B, Tq, ks), dtype=torch.int32, device="cuda")
+    if page:
+        n = -(-Lk // page)
+        order = torch.randperm(B * n, generator=torch.Generator().manual_seed(1))
+        table = order.view(B, n).to(torch.int32)
+        for name in ("k", "KV"):
+            pool = torch.full((B * n * page, g[name].shape[-1]), 300.0, dtype=torch.bfloat16, device="cuda")
+            for b in range(B):
+                for p in range(n):
+                    src = g[name][b, p * page:(p + 1) * page]
+                    pool[int(table[b, p]) * page:int(table[b, p]) * page + src.shape[0]] = src
+            g[name] = pool
+        pc = ic.paged_cache(page_table=table.cuda(), page_size=page)
+    arr = ic.make_layers([g], ks, pos0, 512, 0, scale, [out], Lk=Lk if page else None)
+    if page:
+        arr[0].ix.q_pos0 = pos0
+    ws = torch.empty(max(256, ic.forward_stack_workspace(arr)), dtype=torch.uint8, device="cuda")
+    if page:
+        ic.forward_stack_paged(arr, [True], pc, idx, ws)
+    else:
+        ic.forward_stack(arr, [True], idx, ws)
+    torch.cuda.synchronize()
+    lb = synth.bits_layer(t)
+    want, _ = oracle.sparse_attn(lb["Q"], lb["KV"], idx.cpu().numpy(), 512, 0, scale)
+    err = parity.check_attn(out.float().cpu().numpy(), want)
+    print("max abs err %.3g" % err)
