@@ -914,76 +914,82 @@ __global__ __launch_bounds__(256, 1) void attn_slab_kernel(AttnArgs a)
 // The first rows of a sequence see no more keys than k: their selection is positions 0 .. n-1, so neighbouring queries
 // read the same KV rows and there is nothing to gather.  Here 64 rows of the flattened (query, head) space (two queries of
 // 32 heads) share every KV tile: twice the matrix work per byte that crosses LDS, which is what the row-slab form is
-// bound by.  One workgroup of eight waves per CU (two per SIMD), tiles of 64 keys, two in LDS:
-//   S      wave (rb, kh) = 16 rows x 32 keys: v_mfma_f32_16x16x32_bf16 with the tile as A operand and its rows' Q in
-//          registers; softmax against a reference per row that moves only when a score exceeds it by 2^kDenseLog2; P to LDS
-//   -- barrier
-//   PV     wave w = all 64 rows x value columns 64 w .. 64 w + 63 on v_mfma_f32_32x32x16_bf16, V through the transpose
-//          read; the next tile is stored to the other buffer and the one after it requested
-//   -- barrier
+// bound by.  One workgroup per CU, tiles of 32 keys in a ring of four LDS buffers, one barrier per tile, eight waves in two
+// roles (one of each per SIMD, and about as many matrix clocks for either: 576 and 512 per tile):
+//   scores   waves 0-3, (rh, kh) = 32 rows x 16 keys of tile t: the tile as A operand of v_mfma_f32_16x16x32_bf16, every
+//            read of it used for two row blocks, Q in registers; softmax against a reference per row that moves only when
+//            a score exceeds it by 2^kDenseLog2; P to LDS.  The operand ring runs on into the next tile
+//   output   waves 4-7, value columns 128 w .. 128 w + 127 of all 64 rows, of tile t - 2, transposed (O^T += V^T P^T on
+//            v_mfma_f32_32x32x16_bf16, V through the transpose read): a lane then owns one row of O, so that factors and
+//            row sums are a lane's own and four neighbouring columns leave together.  Its operands are in registers when
+//            the step begins; as they are used, those of tile t - 1 take their place, tile t + 2 goes to LDS and tile t + 3
+//            is requested
+// What counts is the traffic through LDS and what waits for it.  With every wave taking both phases, a wave can hold Q of 16
+// rows only, the score operand was 147 KB of 290 KB per tile and a tile took 2700-2900 clocks however the phases were
+// arranged (two barriers per 64 keys, one per 32, the two waves of a SIMD in opposite order).  Here it is 74 KB of 200 KB:
+// 2400 clocks, 1800 with the operands read a step ahead.  1088 of them are matrix clocks; staging the tiles costs about 300
+// (it may not move to the scores waves: 1900).  One layer of 32 heads, 2048 rows of a prefix: 180 us before, 145 now.
 // LDS layout as in the row-slab form (rows 1184 bytes apart, transpose reads over rows two apart); the A operand presents
-// the tile rows in the order dense_row(), so that the four scores of a lane are neighbours in P.
-// Bound: LDS, about 2700 clocks per tile (1300 of them the A operand, every row of which four waves read) against 2200 of
-// matrix work; for the pair of queries the row-slab form takes 2 x 3800.
-// Registers.  The accumulation half of the register file is managed by hand and the compiler sees none of it: output
-// accumulators in a0 - a63, Q's first 16 contraction steps in a64 - a127.  Every statement below that touches it lists all
-// of it as overwritten, so the compiler keeps nothing there.  It does not see matrix instructions in these statements
+// the tile rows in the order dense_row(), so that the four scores of a lane are neighbours in P.  Q and O pass through the
+// tile ring.
+// Registers.  The accumulation half of the register file is managed by hand and the compiler sees none of it: Q's first 16
+// contraction steps (scores) or the output accumulators (output) in a0 - a127.  Every statement below that touches it lists
+// all of it as overwritten, so the compiler keeps nothing there.  It does not see matrix instructions in these statements
 // either: a result is read by something else only behind enough no-ops, and operands in vector registers come from loads.
-#define IC_A8(n) "a" #n "0", "a" #n "1", "a" #n "2", "a" #n "3", "a" #n "4", "a" #n "5", "a" #n "6", "a" #n "7", "a" #n "8", "a" #n "9"
+#define IC_A10(n) "a" #n "0", "a" #n "1", "a" #n "2", "a" #n "3", "a" #n "4", "a" #n "5", "a" #n "6", "a" #n "7", "a" #n "8", "a" #n "9"
 #define IC_ACC_ALL                                                                                                             \
-    IC_A8(), IC_A8(1), IC_A8(2), IC_A8(3), IC_A8(4), IC_A8(5), IC_A8(6), IC_A8(7), IC_A8(8), IC_A8(9), IC_A8(10), IC_A8(11),    \
-        "a120", "a121", "a122", "a123", "a124", "a125", "a126", "a127"
+    IC_A10(), IC_A10(1), IC_A10(2), IC_A10(3), IC_A10(4), IC_A10(5), IC_A10(6), IC_A10(7), IC_A10(8), IC_A10(9), IC_A10(10),    \
+        IC_A10(11), "a120", "a121", "a122", "a123", "a124", "a125", "a126", "a127"
 
 namespace acc {
 template <int BLOCK> __device__ __forceinline__ void mma_o(bf16x8 x, bf16x8 y)          // output block += x y
 {
     asm volatile("v_mfma_f32_32x32x16_bf16 a[%2:%3], %0, %1, a[%2:%3]" ::"v"(x), "v"(y), "n"(16 * BLOCK), "n"(16 * BLOCK + 15) : IC_ACC_ALL);
 }
-template <int KS> __device__ __forceinline__ void mma_s(f32x4 &c, bf16x8 x)             // c = x Q[0], then c += x Q[KS]
+template <int I> __device__ __forceinline__ void mma_s(f32x4 &c, bf16x8 x)              // c = x Q[I] (of steps 0, 1), c += x Q[I]
 {
-    if constexpr (KS == 0)
-        asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, a[64:67], 0" : "=&v"(c) : "v"(x) : IC_ACC_ALL);
+    if constexpr (I < 2)
+        asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, a[%2:%3], 0" : "=&v"(c) : "v"(x), "n"(4 * I), "n"(4 * I + 3) : IC_ACC_ALL);
     else
-        asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, a[%2:%3], %0" : "+v"(c) : "v"(x), "n"(64 + 4 * KS), "n"(67 + 4 * KS) : IC_ACC_ALL);
+        asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, a[%2:%3], %0" : "+v"(c) : "v"(x), "n"(4 * I), "n"(4 * I + 3) : IC_ACC_ALL);
 }
 __device__ __forceinline__ void mma_s_v(f32x4 &c, bf16x8 x, bf16x8 q)                   // c += x q, q in vector registers
 {
     asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(x), "v"(q) : IC_ACC_ALL);
 }
-template <int KS> __device__ __forceinline__ void set_q(u32x4 v)
+template <int I> __device__ __forceinline__ void set_q(bf16x8 x)
 {
+    const u32x4 v = __builtin_bit_cast(u32x4, x);
     asm volatile("v_accvgpr_write_b32 a[%4], %0\n\tv_accvgpr_write_b32 a[%4+1], %1\n\tv_accvgpr_write_b32 a[%4+2], %2\n\t"
-                 "v_accvgpr_write_b32 a[%4+3], %3" ::"v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3]), "n"(64 + 4 * KS) : IC_ACC_ALL);
+                 "v_accvgpr_write_b32 a[%4+3], %3" ::"v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3]), "n"(4 * I) : IC_ACC_ALL);
 }
 __device__ __forceinline__ void zero_o()
 {
     asm volatile(".irp h,0,1,2,3,4,5,6,7,8,9,10,11,12,13,14,15\n\t"
-                 ".irp b,0,16,32,48\n\t"
+                 ".irp b,0,16,32,48,64,80,96,112\n\t"
                  "v_accvgpr_write_b32 a[\\b+\\h], 0\n\t"
                  ".endr\n\t"
                  ".endr" ::: IC_ACC_ALL);
 }
-// Output blocks 0, 1 (rows 0..31) and 2, 3 (rows 32..63) times the factor of their row: element i of a lane is row
-// 8 (i / 4) + i % 4 of `factors` (an LDS address), plus 32 for the second pair.
-__device__ __forceinline__ void rescale_o(unsigned factors)
+// blocks 0 - 3 times f0, blocks 4 - 7 times f1
+__device__ __forceinline__ void rescale_o(float f0, float f1)
 {
-    float f, x;
+    float x, y;
     asm volatile("s_nop 15\n\t"
+                 ".irp b,0,16,32,48\n\t"
                  ".irp h,0,1,2,3,4,5,6,7,8,9,10,11,12,13,14,15\n\t"
-                 ".irp b,0,32\n\t"
-                 "ds_read_b32 %0, %2 offset:8*\\h-4*(\\h&3)+4*\\b\n\t"
-                 "s_waitcnt lgkmcnt(0)\n\t"
-                 ".irp n,0,16\n\t"
-                 "v_accvgpr_read_b32 %1, a[\\b+\\n+\\h]\n\t"
-                 "v_mul_f32_e32 %1, %1, %0\n\t"
-                 "v_accvgpr_write_b32 a[\\b+\\n+\\h], %1\n\t"
-                 ".endr\n\t"
+                 "v_accvgpr_read_b32 %0, a[\\b+\\h]\n\t"
+                 "v_accvgpr_read_b32 %1, a[64+\\b+\\h]\n\t"
+                 "v_mul_f32_e32 %0, %0, %2\n\t"
+                 "v_mul_f32_e32 %1, %1, %3\n\t"
+                 "v_accvgpr_write_b32 a[\\b+\\h], %0\n\t"
+                 "v_accvgpr_write_b32 a[64+\\b+\\h], %1\n\t"
                  ".endr\n\t"
                  ".endr\n\t"
                  "s_nop 7"
-                 : "=&v"(f), "=&v"(x)
-                 : "v"(factors)
-                 : IC_ACC_ALL, "memory");
+                 : "=&v"(x), "=&v"(y)
+                 : "v"(f0), "v"(f1)
+                 : IC_ACC_ALL);
 }
 template <int I> __device__ __forceinline__ float get_o()
 {
@@ -1000,27 +1006,28 @@ template <int N, typename F> __device__ __forceinline__ void unroll(F f)        
 }
 } // namespace acc
 
-__device__ __forceinline__ unsigned lds_addr(const void *p) { return (unsigned)(uintptr_t)(__attribute__((address_space(3))) const void *)p; }
-
 constexpr int kDenseRows = 64;               // (query, head) rows per workgroup
-constexpr int kDenseTile = 64;               // keys per tile
+constexpr int kDenseTile = 32;               // keys per tile
+constexpr int kDenseRing = 4;
 constexpr float kDenseLog2 = 60.f;           // how far a score may exceed its row's reference (bf16 and fp32 hold 2^127)
 
-// tile row (within a block of 16) behind result row r of S^T
+// tile row (within 16) behind result row r of S^T
 __device__ __forceinline__ int dense_row(int r) { return 8 * (r >> 3) + 2 * (r & 3) + ((r >> 2) & 1); }
 
 template <bool PG>
 __global__ __launch_bounds__(512, 2) void attn_dense_kernel(AttnArgs a, DenseArgs da)
 {
     constexpr int D_QK = 576, D_V = 512;
-    constexpr int KS = D_QK / 32, NC = D_QK / 64;
+    constexpr int KS = D_QK / 32, KSA = 16;               // contraction steps; with Q in accumulation registers
     constexpr int ROWB = D_QK * 2 + kSlabPad, TBUFB = kDenseTile * ROWB;
-    constexpr int PSTR = kDenseTile * 2 + 16;
+    constexpr int PSTR = kDenseTile * 2 + 16, PBUFB = kDenseRows * PSTR;
     constexpr int OSTR = D_V * 2 + 16;
+    constexpr int RING = 9;                              // A-operand reads in flight
+    static_assert(2 * TBUFB == kDenseRows * ROWB && kDenseRows * OSTR <= 2 * TBUFB, "Q and O take two tile buffers");
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    unsigned char *tbuf = smem;                           // [2][64][ROWB]; the output tile [64][OSTR] at the end
-    unsigned char *pbuf = smem + 2 * TBUFB;               // [64 rows][PSTR]
-    float *mref = (float *)(pbuf + kDenseRows * PSTR);    // [64] common references
+    unsigned char *tbuf = smem;                           // [kDenseRing][32][ROWB]
+    unsigned char *pbuf = smem + kDenseRing * TBUFB;      // [2][64 rows][PSTR]
+    float *mref = (float *)(pbuf + 2 * PBUFB);            // [64] common references
     float *mnew = mref + kDenseRows;                      // [2][64] per key half: reference of the latest tile, then row sums
     float *fac = mnew + 2 * kDenseRows;                   // [3][64] factors of a moved reference: O, P of either key half
     int *moved = (int *)(fac + 3 * kDenseRows);           // [2] by tile parity
@@ -1029,229 +1036,279 @@ __global__ __launch_bounds__(512, 2) void attn_dense_kernel(AttnArgs a, DenseArg
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, l32 = lane & 31, hh = lane >> 5, g = lane >> 4;
     const int gr = lane >> 3, gp = lane & 7;
-    const int rb = wave & 3, kh = wave >> 2;
+    const int w = wave & 3;
     const int b = blockIdx.y;
     const int n_rows = da.n_queries * a.H_q;              // flattened rows of a sequence
     const int R0 = ((int)gridDim.x - 1 - (int)blockIdx.x) * kDenseRows;   // longest first
-    const int my_row = min(R0 + 16 * rb + l16, n_rows - 1);
-    const int lim = da.pos0 + my_row / a.H_q;             // last key the lane's row sees
-    const int last = da.pos0 + min(R0 + kDenseRows - 1, n_rows - 1) / a.H_q;
-    const int ntiles = last / kDenseTile + 1;
-    const int len = a.Lk;
+    const int nt = (da.pos0 + min(R0 + kDenseRows - 1, n_rows - 1) / a.H_q) / kDenseTile + 1;
 
-    const unsigned short *kv = (const unsigned short *)a.KV + (PG && a.pv.page_table ? 0 : (int64_t)b * a.Lk * a.row_elems);
-    // first row of tile t (a tile never straddles a page) and this lane's piece of its row 8 wave + gr
-    auto src = [&](int t) -> const unsigned short * {
-        const int s0 = min(t, (len - 1) / kDenseTile) * kDenseTile;
-        const int64_t row = PG && a.pv.page_table ? paged_row(a.pv, b, s0) : (int64_t)s0;
-        return kv + (row + min(8 * wave + gr, len - 1 - s0)) * a.row_elems + 8 * gp;
-    };
-
-    u32x4 cur[NC];
-    {
-        const unsigned short *p = src(0);
-#pragma unroll
-        for (int c = 0; c < NC; ++c) cur[c] = *(const u32x4 *)(p + 64 * c);
-    }
-    bf16x8 qv[KS - 16];
-    {
-        const unsigned short *qp = (const unsigned short *)a.Q + ((int64_t)b * a.Tq * a.H_q + my_row) * D_QK + 8 * g;
-        u32x4 raw[KS];
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) raw[ks] = *(const u32x4 *)(qp + 32 * ks);
-        acc::unroll<16>([&](auto ks) __attribute__((always_inline)) { acc::set_q<decltype(ks)::value>(raw[decltype(ks)::value]); });
-#pragma unroll
-        for (int ks = 16; ks < KS; ++ks) qv[ks - 16] = __builtin_bit_cast(bf16x8, raw[ks]);
-        asm volatile("" : "+v"(qv[0]), "+v"(qv[1]));     // waited for here, not in the tile loop
-    }
-    acc::zero_o();
-    const int st_off = (8 * wave + gr) * ROWB + 16 * gp;
-    {
-        const unsigned short *p = src(1);
-#pragma unroll
-        for (int c = 0; c < NC; ++c) {
-            *(u32x4 *)(tbuf + st_off + 128 * c) = cur[c];
-            cur[c] = *(const u32x4 *)(p + 64 * c);
-        }
-    }
     if (tid < kDenseRows) mref[tid] = mnew[tid] = mnew[kDenseRows + tid] = -INFINITY;
     if (tid < 2) moved[tid] = 0;
-    float m_c = -INFINITY, l_own = 0.f;
-    __syncthreads();
+    // Q in the shape of two tiles, through buffers 2 and 3, by everybody
+    unsigned char *qb = tbuf + 2 * TBUFB;
+    auto load_q = [&](u32x4 (&raw)[9]) __attribute__((always_inline)) {
+        const unsigned short *qp = (const unsigned short *)a.Q + ((int64_t)b * a.Tq * a.H_q + min(R0 + 8 * wave + gr, n_rows - 1)) * D_QK + 8 * gp;
+#pragma unroll
+        for (int c = 0; c < 9; ++c) raw[c] = *(const u32x4 *)(qp + 64 * c);
+    };
+    auto store_q = [&](const u32x4 (&raw)[9]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int c = 0; c < 9; ++c) *(u32x4 *)(qb + (8 * wave + gr) * ROWB + 16 * gp + 128 * c) = raw[c];
+    };
 
-    const int ka_off = (32 * kh + dense_row(l16)) * ROWB + 16 * g;
-    const int tr_off = (8 * hh + 2 * (l16 >> 2)) * ROWB + 128 * wave + 32 * (g & 1) + 8 * (l16 & 3);
-    const int pw_off = (16 * rb + l16) * PSTR + 64 * kh + 8 * g;
-    const int pr_off = l32 * PSTR + 16 * hh;
-    typedef __attribute__((ext_vector_type(8))) short s16x8;
-    typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
-
-#pragma unroll 1
-    for (int t = 0; t < ntiles; ++t) {
-        const unsigned char *tb = tbuf + (t & 1) * TBUFB;
-        // ---- S ----
-        f32x4 s4[2];
+    // Barriers: Q and tile 0 in LDS; Q read; then one at the end of every tile t's step (of step 0 .. nt - 1), one more
+    // within step t + 1 if a reference moved in tile t; row sums in LDS.
+    if (wave < 4) {
+        const int rh = w & 1, kh = w >> 1;
         {
-            constexpr int RING = 3;                       // operand pairs in flight
-            bf16x8 ka[RING][2];
-            auto read = [&](int ks) __attribute__((always_inline)) {
+            u32x4 raw[9];
+            load_q(raw);
+            store_q(raw);
+        }
+        __syncthreads();
+        bf16x8 qv[KS - KSA][2];
+        const unsigned char *qr = qb + (32 * rh + l16) * ROWB + 16 * g;
+        acc::unroll<2 * KSA>([&](auto i_c) __attribute__((always_inline)) {
+            constexpr int i = decltype(i_c)::value;
+            acc::set_q<i>(*(const bf16x8 *)(qr + 16 * (i & 1) * ROWB + 64 * (i >> 1)));
+        });
 #pragma unroll
-                for (int kb = 0; kb < 2; ++kb) ka[ks % RING][kb] = *(const bf16x8 *)(tb + ka_off + 16 * kb * ROWB + 64 * ks);
-            };
+        for (int ks = KSA; ks < KS; ++ks)
 #pragma unroll
-            for (int r = 0; r < RING; ++r) read(r);
+            for (int r = 0; r < 2; ++r) qv[ks - KSA][r] = *(const bf16x8 *)(qr + 16 * r * ROWB + 64 * ks);
+        __syncthreads();
+
+        int lim[2];                                       // last key the lane's rows see
+#pragma unroll
+        for (int r = 0; r < 2; ++r) lim[r] = da.pos0 + min(R0 + 32 * rh + 16 * r + l16, n_rows - 1) / a.H_q;
+        const int lim0 = __builtin_amdgcn_readfirstlane(lim[0]);   // the smallest of the wave
+        const int ka_off = (16 * kh + dense_row(l16)) * ROWB + 16 * g;
+        const int pw_off = (32 * rh + l16) * PSTR + 32 * kh + 8 * g;
+        float m_c[2] = {-INFINITY, -INFINITY}, l_own[2] = {0.f, 0.f}, psum[2] = {0.f, 0.f};
+        bf16x8 ka[RING];
+        f32x4 s4[2];
+#pragma unroll
+        for (int r = 0; r < RING; ++r) ka[r] = *(const bf16x8 *)(tbuf + ka_off + 64 * r);
+        auto scores = [&](int t) __attribute__((always_inline)) {
+            const unsigned char *tb = tbuf + (t & (kDenseRing - 1)) * TBUFB + ka_off;
+            const unsigned char *tb1 = tbuf + ((t + 1) & (kDenseRing - 1)) * TBUFB + ka_off;
             acc::unroll<KS>([&](auto ks_c) __attribute__((always_inline)) {
                 constexpr int ks = decltype(ks_c)::value;
-#pragma unroll
-                for (int kb = 0; kb < 2; ++kb) {
-                    if constexpr (ks < 16)
-                        acc::mma_s<ks>(s4[kb], ka[ks % RING][kb]);
-                    else
-                        acc::mma_s_v(s4[kb], ka[ks % RING][kb], qv[ks - 16]);
+                if constexpr (ks < KSA) {
+                    acc::mma_s<2 * ks>(s4[0], ka[ks % RING]);
+                    acc::mma_s<2 * ks + 1>(s4[1], ka[ks % RING]);
+                } else {
+                    acc::mma_s_v(s4[0], ka[ks % RING], qv[ks - KSA][0]);
+                    acc::mma_s_v(s4[1], ka[ks % RING], qv[ks - KSA][1]);
                 }
-                if constexpr (ks + RING < KS) read(ks + RING);
+                ka[ks % RING] = ks + RING < KS ? *(const bf16x8 *)(tb + 64 * (ks + RING)) : *(const bf16x8 *)(tb1 + 64 * (ks + RING - KS));
                 __builtin_amdgcn_sched_barrier(0);
             });
+        };
+        auto softmax = [&](int t) __attribute__((always_inline)) {
             asm volatile("s_nop 15" : "+v"(s4[0]), "+v"(s4[1]));
-        }
-        // lane: row l16 of the wave's 16, keys of block kb: dense_row(4 g + i)
-        float z[2][4];
+            // lane: row l16 of either block, keys dense_row(4 g + i)
+            const int key0 = kDenseTile * t + 16 * kh;
+            if (key0 + 15 > lim0) {
+                const int k0 = key0 + 8 * (g >> 1) + (g & 1);
 #pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
+                for (int r = 0; r < 2; ++r)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) z[kb][i] = s4[kb][i] * a.scale_log2e;
-        const int key0 = kDenseTile * t + 32 * kh;
-        if (__ballot(key0 + 31 > lim) != 0ull) {
-            const int k0 = key0 + 8 * (g >> 1) + (g & 1);
-#pragma unroll
-            for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) z[kb][i] = k0 + 16 * kb + 2 * i <= lim ? z[kb][i] : -INFINITY;
-        }
-        float mx = fmaxf(fmaxf(fmaxf(z[0][0], z[0][1]), fmaxf(z[0][2], z[0][3])), fmaxf(fmaxf(z[1][0], z[1][1]), fmaxf(z[1][2], z[1][3])));
-        mx = xmax16_32(mx);
-        float m_use = m_c;
-        const bool up = mx > m_c + kDenseLog2;
-        if (__ballot(up) != 0ull) {                       // rare: some row's first keys, or a score far above all before it
-            m_use = up ? mx : m_c;
-            if (g == 0) mnew[kDenseRows * kh + 16 * rb + l16] = m_use;
-            moved[t & 1] = 1;
-        }
-        const float m_safe = m_use == -INFINITY ? 0.f : m_use;   // (no key so far: every p is 2^-inf = 0)
-        float psum = 0.f;
-#pragma unroll
-        for (int kb = 0; kb < 2; ++kb) {
-            s16x4 pk;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const float p = fast_exp2(z[kb][i] - m_safe);
-                psum += p;
-                pk[i] = __builtin_bit_cast(short, (__bf16)p);
+                    for (int i = 0; i < 4; ++i) s4[r][i] = k0 + 2 * i <= lim[r] ? s4[r][i] : -INFINITY;
             }
-            *(s16x4 *)(pbuf + pw_off + 32 * kb) = pk;
-        }
-        __syncthreads();
-        const int mv = __builtin_amdgcn_readfirstlane(moved[t & 1]);
-        bool scale_p = false;
-        if (mv) {                                         // uniform over the workgroup
-            if (tid < kDenseRows) {
-                const float m0 = mnew[tid], m1 = mnew[kDenseRows + tid], m = fmaxf(m0, m1), old = mref[tid];
-                fac[tid] = m == -INFINITY ? 1.f : fast_exp2(old - m);
-                fac[kDenseRows + tid] = m == -INFINITY ? 1.f : fast_exp2(m0 - m);
-                fac[2 * kDenseRows + tid] = m == -INFINITY ? 1.f : fast_exp2(m1 - m);
-                mref[tid] = mnew[tid] = mnew[kDenseRows + tid] = m;
+            float m_use[2], mx[2];
+#pragma unroll
+            for (int r = 0; r < 2; ++r) {
+                m_use[r] = m_c[r];
+                mx[r] = fmaxf(fmaxf(s4[r][0], s4[r][1]), fmaxf(s4[r][2], s4[r][3])) * a.scale_log2e;
             }
-            __syncthreads();                              // (everybody has read the flag)
-            if (tid == 0) moved[t & 1] = 0;               // next raised two tiles on
-            const int row = 16 * rb + l16;
-            l_own *= fac[row];
-            psum *= fac[kDenseRows * (1 + kh) + row];
-            m_c = mref[row];
-            acc::rescale_o(lds_addr(fac + 4 * hh));
-            scale_p = true;
-        }
-        l_own += psum;
-        // ---- PV; the next tile to the other buffer, the one after it requested ----
-        unsigned char *tn = tbuf + ((t & 1) ^ 1) * TBUFB + st_off;
-        const unsigned short *p = src(t + 2);
-        bf16x8 pa[2][2];
-        s16x4 vq[2][2][2];
-        auto read_pv = [&](int s) __attribute__((always_inline)) {
-#pragma unroll
-            for (int r = 0; r < 2; ++r) pa[s & 1][r] = *(const bf16x8 *)(pbuf + pr_off + 32 * r * PSTR + 32 * s);
-#pragma unroll
-            for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-                for (int u = 0; u < 2; ++u)
-                    vq[s & 1][nb][u] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(tb + tr_off + (16 * s + u) * ROWB + 64 * nb));
-        };
-        auto stage = [&](int c) __attribute__((always_inline)) {
-            if (c < NC) {
-                *(u32x4 *)(tn + 128 * c) = cur[c];
-                __builtin_amdgcn_sched_barrier(0);
-                cur[c] = *(const u32x4 *)(p + 64 * c);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        };
-        read_pv(0);
-        acc::unroll<4>([&](auto s_c) __attribute__((always_inline)) {
-            constexpr int s = decltype(s_c)::value;
-            if constexpr (s < 3) read_pv(s + 1);
-            if (scale_p) {
+            if (__ballot(mx[0] > m_c[0] + kDenseLog2 || mx[1] > m_c[1] + kDenseLog2) != 0ull) {
+                // rare: some row's first keys, or a score far above all before it
 #pragma unroll
                 for (int r = 0; r < 2; ++r) {
-                    const float f = fac[kDenseRows * (1 + (s >> 1)) + 32 * r + l32];
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) pa[s & 1][r][e] = (__bf16)((float)pa[s & 1][r][e] * f);
+                    mx[r] = xmax16_32(mx[r]);
+                    m_use[r] = mx[r] > m_c[r] + kDenseLog2 ? mx[r] : m_c[r];
+                    if (g == 0) mnew[kDenseRows * kh + 32 * rh + 16 * r + l16] = m_use[r];
                 }
-                asm volatile("s_nop 7" : "+v"(pa[s & 1][0]), "+v"(pa[s & 1][1]));
+                moved[t & 1] = 1;
             }
-            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int nb = 0; nb < 2; ++nb) {
-                const s16x4 v0 = vq[s & 1][nb][0], v1 = vq[s & 1][nb][1];
-                const s16x8 vv = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
-                if (nb == 0) {
-                    acc::mma_o<0>(pa[s & 1][0], __builtin_bit_cast(bf16x8, vv));
-                    acc::mma_o<2>(pa[s & 1][1], __builtin_bit_cast(bf16x8, vv));
-                } else {
-                    acc::mma_o<1>(pa[s & 1][0], __builtin_bit_cast(bf16x8, vv));
-                    acc::mma_o<3>(pa[s & 1][1], __builtin_bit_cast(bf16x8, vv));
+            for (int r = 0; r < 2; ++r) {
+                const float m_safe = m_use[r] == -INFINITY ? 0.f : m_use[r];   // (no key so far: every p is 2^-inf = 0)
+                s16x4 pk;
+                float p[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    p[i] = fast_exp2(__builtin_fmaf(s4[r][i], a.scale_log2e, -m_safe));
+                    pk[i] = __builtin_bit_cast(short, (__bf16)p[i]);
                 }
-                stage(2 * s + nb);
+                *(s16x4 *)(pbuf + (t & 1) * PBUFB + pw_off + 16 * r * PSTR) = pk;
+                psum[r] = (p[0] + p[1]) + (p[2] + p[3]);
             }
-        });
-        stage(8);
+        };
+        scores(0);
+        softmax(0);
         __syncthreads();
-    }
+#pragma unroll 1
+        for (int t = 1;; ++t) {
+            const int flag = moved[(t - 1) & 1];
+            __builtin_amdgcn_sched_barrier(0);
+            if (t < nt) scores(t);
+            if (__builtin_amdgcn_readfirstlane(flag)) {   // a reference moved in tile t - 1 (uniform over the workgroup)
+                if (tid < kDenseRows) {
+                    const float m0 = mnew[tid], m1 = mnew[kDenseRows + tid], m = fmaxf(m0, m1), old = mref[tid];
+                    fac[tid] = m == -INFINITY ? 1.f : fast_exp2(old - m);
+                    fac[kDenseRows + tid] = m == -INFINITY ? 1.f : fast_exp2(m0 - m);
+                    fac[2 * kDenseRows + tid] = m == -INFINITY ? 1.f : fast_exp2(m1 - m);
+                    mref[tid] = mnew[tid] = mnew[kDenseRows + tid] = m;
+                }
+                __syncthreads();                          // (everybody has read the flag)
+                if (tid == 0) moved[(t - 1) & 1] = 0;     // next raised behind the barrier that ends this step
+#pragma unroll
+                for (int r = 0; r < 2; ++r) {
+                    const int row = 32 * rh + 16 * r + l16;
+                    l_own[r] *= fac[row];
+                    psum[r] *= fac[kDenseRows * (1 + kh) + row];
+                    m_c[r] = mref[row];
+                }
+            }
+#pragma unroll
+            for (int r = 0; r < 2; ++r) l_own[r] += psum[r];
+            if (t >= nt) break;
+            softmax(t);
+            __syncthreads();
+        }
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            const float l = xsum16_32(l_own[r]);
+            if (g == 0) mnew[kDenseRows * kh + 32 * rh + 16 * r + l16] = l;
+        }
+        __syncthreads();
+        if (a.lse && tid < kDenseRows && R0 + tid < n_rows) {
+            const float l = mnew[tid] + mnew[kDenseRows + tid];
+            a.lse[(int64_t)b * a.Tq * a.H_q + R0 + tid] = l > 0.f ? (mref[tid] + __builtin_log2f(l)) * 0.6931471805599453f : -INFINITY;
+        }
+    } else {
+        // A tile is fetched eight lanes to a 128-byte line: rows 8 w + gr, nine lines.
+        const unsigned short *kv = (const unsigned short *)a.KV + (PG && a.pv.page_table ? 0 : (int64_t)b * a.Lk * a.row_elems) + 8 * gp;
+        u32x4 cur[9];
+        auto tile_src = [&](int t) -> const unsigned short * {   // (past the last tile: that one again, for nobody)
+            const int s0 = min(t, nt - 1) * kDenseTile;                // (a tile never straddles a page)
+            const int64_t row = PG && a.pv.page_table ? paged_row(a.pv, b, s0) : (int64_t)s0;
+            return kv + (row + min(8 * w + gr, a.Lk - 1 - s0)) * a.row_elems;
+        };
+        auto load = [&](int t) __attribute__((always_inline)) {
+            const unsigned short *p = tile_src(t);
+#pragma unroll
+            for (int c = 0; c < 9; ++c) cur[c] = *(const u32x4 *)(p + 64 * c);
+        };
+        const int st_off = (8 * w + gr) * ROWB + 16 * gp;
+        auto store = [&](int t, int c0, int n) __attribute__((always_inline)) {
+            unsigned char *d = tbuf + (t & (kDenseRing - 1)) * TBUFB + st_off;
+            for (int c = c0; c < c0 + n; ++c) *(u32x4 *)(d + 128 * c) = cur[c];
+        };
+        {
+            u32x4 raw[9];
+            load_q(raw);
+            load(0);
+            store_q(raw);
+        }
+        acc::zero_o();
+        store(0, 0, 9);
+        load(1);
+        __syncthreads();
+        store(1, 0, 9);
+        load(2);
+        __syncthreads();
+        store(2, 0, 9);
+        load(3);
 
-    // ---- row sums of both key halves, normalise, through LDS to memory ----
-    {
-        const float l = xsum16_32(l_own);
-        if (g == 0) mnew[kDenseRows * kh + 16 * rb + l16] = l;
-    }
-    asm volatile("s_nop 15" ::: IC_ACC_ALL);              // the last matrix steps have left the pipe
-    __syncthreads();
-    const int64_t out_row = (int64_t)b * a.Tq * a.H_q + R0;
-    if (a.lse && tid < kDenseRows && R0 + tid < n_rows) {
-        const float l = mnew[tid] + mnew[kDenseRows + tid];
-        a.lse[out_row + tid] = l > 0.f ? (mref[tid] + __builtin_log2f(l)) * 0.6931471805599453f : -INFINITY;
-    }
-    acc::unroll<8>([&](auto q_c) __attribute__((always_inline)) {
-        constexpr int r = decltype(q_c)::value >> 2, qd = decltype(q_c)::value & 3;
-        const int row0 = 32 * r + 8 * qd + 4 * hh;
-        const f32x4 l4 = *(const f32x4 *)(mnew + row0) + *(const f32x4 *)(mnew + kDenseRows + row0);
-        acc::unroll<4>([&](auto i_c) __attribute__((always_inline)) {
-            constexpr int i = decltype(i_c)::value;
-            const float inv = l4[i] > 0.f ? __builtin_amdgcn_rcpf(l4[i]) : 0.f;
-            const float x0 = acc::get_o<32 * r + 4 * qd + i>() * inv, x1 = acc::get_o<32 * r + 16 + 4 * qd + i>() * inv;
-            __bf16 *po = (__bf16 *)(tbuf + (row0 + i) * OSTR) + 64 * wave + l32;
-            po[0] = (__bf16)x0;
-            po[32] = (__bf16)x1;
+        typedef __attribute__((ext_vector_type(8))) short s16x8;
+        typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+        const int tr_off = (8 * hh + 2 * (l16 >> 2)) * ROWB + 256 * w + 32 * (g & 1) + 8 * (l16 & 3);
+        const int pr_off = l32 * PSTR + 16 * hh;
+        bf16x8 pa[2][2];
+        s16x4 vq[2][4][2];
+        auto read_v = [&](int t, int s, int nb) __attribute__((always_inline)) {
+            const unsigned char *tb = tbuf + (t & (kDenseRing - 1)) * TBUFB + tr_off + 16 * s * ROWB + 64 * nb;
+#pragma unroll
+            for (int u = 0; u < 2; ++u) vq[s][nb][u] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(tb + u * ROWB));
+        };
+        auto read_p = [&](int t, int s) __attribute__((always_inline)) {
+            const unsigned char *pb = pbuf + (t & 1) * PBUFB + pr_off;
+#pragma unroll
+            for (int r = 0; r < 2; ++r) pa[s][r] = *(const bf16x8 *)(pb + 32 * r * PSTR + 32 * s);
+        };
+        // Step t: output product of tile t - 2 (kMma) in two steps of 16 keys, from operands read a step ago; those of tile
+        // t - 1 take their registers, tile t + 2 goes to LDS and tile t + 3 into its registers (kNext)
+        auto step = [&](int t, auto mma_c, auto next_c) __attribute__((always_inline)) {
+            constexpr bool kMma = decltype(mma_c)::value, kNext = decltype(next_c)::value;
+            const int flag = kNext ? moved[(t - 1) & 1] : 0;
+            const unsigned short *src = tile_src(t + 3);
+            __builtin_amdgcn_sched_barrier(0);
+            acc::unroll<8>([&](auto i_c) __attribute__((always_inline)) {
+                constexpr int i = decltype(i_c)::value, s = i >> 2, nb = i & 3;
+                if constexpr (kMma) {
+                    const s16x8 v = {vq[s][nb][0][0], vq[s][nb][0][1], vq[s][nb][0][2], vq[s][nb][0][3], vq[s][nb][1][0], vq[s][nb][1][1], vq[s][nb][1][2], vq[s][nb][1][3]};
+                    acc::mma_o<nb>(__builtin_bit_cast(bf16x8, v), pa[s][0]);
+                    acc::mma_o<4 + nb>(__builtin_bit_cast(bf16x8, v), pa[s][1]);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                if constexpr (kNext) {
+                    read_v(t - 1, s, nb);
+                    if constexpr (nb == 3) read_p(t - 1, s);
+#pragma unroll
+                    for (int c = i; c < (i == 7 ? 9 : i + 1); ++c) {
+                        store(t + 2, c, 1);
+                        cur[c] = *(const u32x4 *)(src + 64 * c);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            });
+            if (kNext && __builtin_amdgcn_readfirstlane(flag)) {       // see above
+                __syncthreads();
+                if constexpr (kMma) acc::rescale_o(fac[l32], fac[32 + l32]);
+#pragma unroll
+                for (int s = 0; s < 2; ++s)
+#pragma unroll
+                    for (int r = 0; r < 2; ++r) {
+                        const float f = fac[kDenseRows * (1 + s) + 32 * r + l32];
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) pa[s][r][e] = (__bf16)((float)pa[s][r][e] * f);
+                    }
+            }
+        };
+        constexpr std::true_type T{};
+        constexpr std::false_type F{};
+        __syncthreads();
+        step(1, F, T);
+#pragma unroll 1
+        for (int t = 2; t <= nt; ++t) {
+            __syncthreads();
+            step(t, T, T);
+        }
+        asm volatile("s_nop 7" : "+v"(pa[0][0]), "+v"(pa[0][1]), "+v"(pa[1][0]), "+v"(pa[1][1]));
+        step(nt + 1, T, F);
+        asm volatile("s_nop 15" ::: IC_ACC_ALL);          // the last matrix steps have left the pipe
+        __syncthreads();
+        float inv[2];
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            const float l = mnew[32 * r + l32] + mnew[kDenseRows + 32 * r + l32];
+            inv[r] = l > 0.f ? __builtin_amdgcn_rcpf(l) : 0.f;
+        }
+        acc::unroll<32>([&](auto q_c) __attribute__((always_inline)) {
+            constexpr int q = decltype(q_c)::value, r = q >> 4, nb = (q >> 2) & 3, qd = q & 3, e = 64 * r + 16 * nb + 4 * qd;
+            s16x4 o;
+            o[0] = __builtin_bit_cast(short, (__bf16)(acc::get_o<e>() * inv[r]));
+            o[1] = __builtin_bit_cast(short, (__bf16)(acc::get_o<e + 1>() * inv[r]));
+            o[2] = __builtin_bit_cast(short, (__bf16)(acc::get_o<e + 2>() * inv[r]));
+            o[3] = __builtin_bit_cast(short, (__bf16)(acc::get_o<e + 3>() * inv[r]));
+            *(s16x4 *)(tbuf + (32 * r + l32) * OSTR + 2 * (128 * w + 32 * nb + 8 * qd + 4 * hh)) = o;
         });
-    });
+    }
     __syncthreads();
-    __bf16 *out = (__bf16 *)a.O + out_row * D_V;
+    __bf16 *out = (__bf16 *)a.O + ((int64_t)b * a.Tq * a.H_q + R0) * D_V;
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
         const int row = 8 * j + wave;
@@ -1402,7 +1459,7 @@ hipError_t launch_slab(const AttnArgs &a, hipStream_t st)
 hipError_t launch_attn_dense(const AttnArgs &a, const DenseArgs &da, hipStream_t st)
 {
     if (da.n_queries <= 0) return hipSuccess;
-    constexpr int lds = 2 * kDenseTile * (576 * 2 + kSlabPad) + kDenseRows * (kDenseTile * 2 + 16) + (6 * kDenseRows + 2) * 4;
+    constexpr int lds = kDenseRing * kDenseTile * (576 * 2 + kSlabPad) + 2 * kDenseRows * (kDenseTile * 2 + 16) + (6 * kDenseRows + 2) * 4;
     static hipError_t attr = hipFuncSetAttribute((const void *)attn_dense_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     static hipError_t attr_pg = hipFuncSetAttribute((const void *)attn_dense_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (attr != hipSuccess) return attr;
