@@ -108,6 +108,8 @@ size_t ic_sparse_attn_workspace(const ic_attn_desc *desc);
  *   0 <= idx_m < Lk (others are skipped), p = softmax(z), O[b,t,h,:] = sum_m p_m KV[b,idx_m,v_off:+d_v].
  *   O   [B,Tq,H_q,d_v] bf16 out (a row with no valid entry gives zeros)
  *   lse [B,Tq,H_q] fp32 out, nullable: log sum_m exp(z_m) (-inf for an empty row)
+ * A workspace of B * k_sel / 4 + 256 bytes or more (also where ic_sparse_attn_workspace() asks for none) lets long causal
+ * selections run faster: leading rows that hold whole prefixes are then counted and share their KV rows.
  */
 ic_status ic_sparse_attn(const ic_attn_desc *desc, const void *Q, const void *KV, const int32_t *idx,
                          void *O, float *lse, void *workspace, size_t workspace_bytes, void *stream);
@@ -264,7 +266,7 @@ ic_status ic_pattern_uniform(int32_t n, int32_t r, uint8_t *full_mask);
  * attention part (at, Q, KV, O) of n_layers layers of one shape; idx_layers: HOST array of
  * n_layers DEVICE index tensors [B,Tq,k_sel]; S: device [n_layers, n_layers] double, out;
  * workspace: ic_similarity_matrix_workspace(layers, n_layers) bytes.  n_layers (n_layers-1) / 2 + n_layers
- * attention launches on `stream`.
+ * attentions on `stream`; rows that hold the same whole prefix in both tensors of a pair are computed once.
  *
  * ic_pattern_search_dp (host only): the pattern with exactly n_full Full layers (the first layer
  * Full) that maximises the sum over the Shared layers l of S[l][src(l)], src(l) the nearest

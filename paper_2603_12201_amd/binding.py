@@ -229,7 +229,7 @@ def sparse_attn(Q, KV, idx, d_v, v_off, sm_scale, want_lse=False, workspace=None
     import torch
     d = attn_desc(Q, KV, idx, d_v, v_off, sm_scale)
     if workspace is None:
-        workspace = _workspace(sparse_attn_workspace(d), Q)
+        workspace = _workspace(max(sparse_attn_workspace(d), d.B * d.k_sel // 4 + 256), Q)
     O = out if out is not None else torch.empty((d.B, d.Tq, d.H_q, d_v), dtype=torch.bfloat16, device=Q.device)
     lse = torch.empty((d.B, d.Tq, d.H_q), dtype=torch.float32, device=Q.device) if want_lse else None
     _check(lib().ic_sparse_attn(C.byref(d), _ptr(Q), _ptr(KV), _ptr(idx), _ptr(O), _ptr(lse),

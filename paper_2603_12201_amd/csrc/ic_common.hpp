@@ -98,10 +98,49 @@ struct AttnArgs {
     void *Os[kMaxBatchLayers];
 };
 
+// Which leading rows of every sequence of an index tensor are whole prefixes, row t = 0 .. pos0 + t and then nothing: per
+// chunk of kLeadChunk rows the number of such rows before the first other one.
+constexpr int kLeadChunk = 16;
+struct LeadArgs {
+    const int32_t *idx[IC_MAX_OVERLAP_LAYERS];   // tensors [B,Tq,k_sel]
+    int32_t *lead;        // [tensors][B][n_chunks]
+    int32_t B, Tq, k_sel, pos0;
+    int32_t n_rows, n_chunks;                    // rows looked at per sequence and ceil(n_rows / kLeadChunk)
+};
+
+// number of leading rows from one sequence's chunk counts, by a whole wave
+__device__ __forceinline__ int lead_rows(const int32_t *lead, int n_chunks)
+{
+    const int lane = threadIdx.x & 63;
+    for (int c0 = 0; c0 < n_chunks; c0 += 64) {
+        const int v = c0 + lane < n_chunks ? lead[c0 + lane] : 0;
+        const unsigned long long m = __ballot(v < kLeadChunk);
+        if (m != 0ull) {
+            const int first = __builtin_ctzll(m);
+            return kLeadChunk * (c0 + first) + __builtin_amdgcn_readlane(v, first);
+        }
+    }
+    return kLeadChunk * n_chunks;
+}
+
 // The rows of a launch whose selection is a whole prefix of the cache.
 struct DenseArgs {
     int32_t n_queries;    // per sequence, from row 0
     int32_t pos0;         // row t sees the keys 0 .. pos0 + t, all of them below Lk
+    const int32_t *lead;  // [B][n_chunks] or nullptr: fewer rows where these counts say so
+    int32_t n_chunks;
+};
+
+// The rows of one sequence that are left: from the first row that is not a leading one in both tensors up to n_rows.
+struct RestArgs {
+    const int32_t *lead, *lead2;                 // [n_chunks] chunk counts
+    int32_t n_chunks, n_rows;
+};
+
+// Rows of a comparison whose second tensor is the first one: the rows that are leading in both index tensors.
+struct SameRows {
+    const int32_t *lead, *lead2;                 // [B][n_chunks] or nullptr: no such rows
+    int32_t n_chunks, Tq;
 };
 
 // Head-aggregated attention probabilities over the selected rows (the indexer's training target).
@@ -148,6 +187,8 @@ size_t select_parts_bytes(int n_rows, int max_row_len);
 hipError_t launch_select_parts(const SelectArgs &a, int n_rows, int max_row_len, void *ws, hipStream_t st);
 hipError_t launch_attn(const AttnArgs &a, int d_qk, int d_v, hipStream_t st);
 hipError_t launch_attn_dense(const AttnArgs &a, const DenseArgs &da, hipStream_t st);
+hipError_t launch_attn_rest(const AttnArgs &a, const RestArgs &ra, hipStream_t st);
+hipError_t launch_lead(const LeadArgs &a, int n_tensors, hipStream_t st);
 hipError_t launch_attn_merge(const AttnArgs &a, int d_v, hipStream_t st);
 size_t overlap_ws_bytes(int n_layers);
 size_t overlap_lds_bytes(int n_layers, int Lk);
@@ -155,7 +196,10 @@ hipError_t launch_overlap(const int32_t *const *idx_layers, int n_layers, int64_
                           unsigned long long *inter_out, unsigned long long *sizes_out, void *ws, hipStream_t st);
 hipError_t launch_cosine(const void *A, const void *B, int64_t n_rows, int64_t row_len, double *mean, float *per_row,
                          double *acc, hipStream_t st);
+hipError_t launch_cosine_sum(const void *A, const void *B, int64_t n_rows, int64_t row_len, float *per_row, double *acc,
+                             const SameRows &same, hipStream_t st);
 hipError_t launch_sim_init(double *S, int n, hipStream_t st);
+hipError_t launch_sim_finish(double *S, int n, int64_t n_rows, hipStream_t st);
 hipError_t launch_loss_finish(const double *sims, int n, double *loss, hipStream_t st);
 hipError_t launch_attn_probs(const ProbsArgs &a, int d_qk, hipStream_t st);
 hipError_t launch_distill(const DistillArgs &a, int64_t nq, double *loss_multi, double *loss_avg, hipStream_t st);

@@ -4,7 +4,7 @@
 // cosine_kernel: one wave per row (one query token's output over all heads, bf16); products
 // and squares are exact in fp32, a lane sums a few dozen of them in fp32 and everything across
 // lanes and rows is combined in fp64.  The mean over the rows goes through one fp64 atomic per
-// workgroup.  HBM-bound: both tensors are read once.
+// workgroup.  HBM-bound: both tensors are read once.  Rows that are known to be the same in both (`same`) are read once.
 #include "ic_common.hpp"
 
 namespace ic {
@@ -25,7 +25,7 @@ __device__ __forceinline__ double wave_sum(double x)
 // (one per row would queue tens of thousands of them on a single address).
 template <bool VEC>
 __global__ __launch_bounds__(256) void cosine_kernel(const unsigned short *A, const unsigned short *B, int64_t n_rows,
-                                                     int64_t row_len, float *per_row, double *acc)
+                                                     int64_t row_len, float *per_row, double *acc, SameRows same)
 {
     __shared__ double part[4];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -33,6 +33,11 @@ __global__ __launch_bounds__(256) void cosine_kernel(const unsigned short *A, co
     double mine = 0.0;                                         // sum of this wave's rows (lane 0)
     for (int64_t r = (int64_t)blockIdx.x * 4 + wave; r < n_rows; r += n_waves) {
         const unsigned short *a = A + r * row_len, *b = B + r * row_len;
+        if (same.lead) {
+            const int s = (int)(r / same.Tq), t = (int)(r - (int64_t)s * same.Tq);
+            const int64_t o = (int64_t)s * same.n_chunks;
+            if (t < lead_rows(same.lead + o, same.n_chunks) && t < lead_rows(same.lead2 + o, same.n_chunks)) b = a;
+        }
         double ab = 0.0, aa = 0.0, bb = 0.0;
         if (VEC) {
             constexpr int U = 8;
@@ -107,6 +112,14 @@ __global__ void loss_finish_kernel(const double *sims, int n, double *loss)
     *loss = t / (double)n;
 }
 
+// The lower triangle starts at 0 and collects the sums of its pairs' rows, which become means all at once at the end (a
+// kernel to clear and one to divide for every pair took 10 us of the 43 a comparison of 3000 rows takes).
+__global__ void sim_finish_kernel(double *S, int n, int64_t n_rows)
+{
+    const int e = blockIdx.x * blockDim.x + threadIdx.x;
+    if (e < n * n && e % n < e / n) S[e] /= (double)n_rows;
+}
+
 // S starts as the identity: the diagonal is 1 by definition, the upper triangle is not defined (0)
 __global__ void sim_init_kernel(double *S, int n)
 {
@@ -116,19 +129,28 @@ __global__ void sim_init_kernel(double *S, int n)
 
 } // namespace
 
-hipError_t launch_cosine(const void *A, const void *B, int64_t n_rows, int64_t row_len, double *mean, float *per_row,
-                         double *acc, hipStream_t st)
+// adds the sum of the rows' similarities to *acc
+hipError_t launch_cosine_sum(const void *A, const void *B, int64_t n_rows, int64_t row_len, float *per_row, double *acc,
+                             const SameRows &same, hipStream_t st)
 {
-    hipLaunchKernelGGL(cosine_zero_kernel, dim3(1), dim3(1), 0, st, acc);
     const bool vec = row_len % 8 == 0 && (uintptr_t)A % 16 == 0 && (uintptr_t)B % 16 == 0;
     const int64_t want = (n_rows + 3) / 4;                    // workgroups if every wave took one row
     const unsigned grid = (unsigned)(want < 2048 ? (want < 1 ? 1 : want) : 2048);   // 8 workgroups per CU at most
     if (vec)
         hipLaunchKernelGGL(cosine_kernel<true>, dim3(grid), dim3(256), 0, st, (const unsigned short *)A,
-                           (const unsigned short *)B, n_rows, row_len, per_row, acc);
+                           (const unsigned short *)B, n_rows, row_len, per_row, acc, same);
     else
         hipLaunchKernelGGL(cosine_kernel<false>, dim3(grid), dim3(256), 0, st, (const unsigned short *)A,
-                           (const unsigned short *)B, n_rows, row_len, per_row, acc);
+                           (const unsigned short *)B, n_rows, row_len, per_row, acc, same);
+    return hipGetLastError();
+}
+
+hipError_t launch_cosine(const void *A, const void *B, int64_t n_rows, int64_t row_len, double *mean, float *per_row,
+                         double *acc, hipStream_t st)
+{
+    hipLaunchKernelGGL(cosine_zero_kernel, dim3(1), dim3(1), 0, st, acc);
+    const hipError_t e = launch_cosine_sum(A, B, n_rows, row_len, per_row, acc, SameRows{}, st);
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(cosine_finish_kernel, dim3(1), dim3(1), 0, st, (const double *)acc, n_rows, mean);
     return hipGetLastError();
 }
@@ -136,6 +158,12 @@ hipError_t launch_cosine(const void *A, const void *B, int64_t n_rows, int64_t r
 hipError_t launch_loss_finish(const double *sims, int n, double *loss, hipStream_t st)
 {
     hipLaunchKernelGGL(loss_finish_kernel, dim3(1), dim3(1), 0, st, sims, n, loss);
+    return hipGetLastError();
+}
+
+hipError_t launch_sim_finish(double *S, int n, int64_t n_rows, hipStream_t st)
+{
+    hipLaunchKernelGGL(sim_finish_kernel, dim3((unsigned)((n * n + 255) / 256)), dim3(256), 0, st, S, n, n_rows);
     return hipGetLastError();
 }
 

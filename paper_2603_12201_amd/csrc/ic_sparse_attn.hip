@@ -314,9 +314,20 @@ __device__ __forceinline__ unsigned rows_mask(unsigned long long ba, unsigned lo
 // (unnormalised accumulators, reference maximum, row sum) for the merge kernel.
 // MULTI: a.n_layers layers in one launch (a chain that has to know a query's layer spills seven registers more, 2 % of a
 // long chain's time, so one layer alone does without).
-template <int D_QK, int D_V, bool PG, bool SPLIT, bool MULTI>   // value columns = the first D_V features of a row; PG as above
-__global__ __launch_bounds__(256, 1) void attn_slab_kernel(AttnArgs a)
+// REST: the rows of one sequence behind those that the dense form has taken.  How many that are is device data, so the
+// workgroups, as many as for all rows, find out first and share what is left (one round trip to memory, about 1 us).
+template <int D_QK, int D_V, bool PG, bool SPLIT, bool MULTI, bool REST>   // value columns = the first D_V features of a row; PG as above
+__global__ __launch_bounds__(256, 1) void attn_slab_kernel(AttnArgs a, RestArgs ra)
 {
+    if constexpr (REST) {
+        const int t0 = __builtin_amdgcn_readfirstlane(min(lead_rows(ra.lead, ra.n_chunks), lead_rows(ra.lead2, ra.n_chunks)));
+        if (t0 + (int)blockIdx.x >= ra.n_rows && t0 + (int)gridDim.x > ra.n_rows) return;   // no chain, and no row for it
+        a.Tq = ra.n_rows - t0;
+        a.Q = (const __bf16 *)a.Q + (int64_t)t0 * a.H_q * D_QK;
+        a.O = (__bf16 *)a.O + (int64_t)t0 * a.H_q * D_V;
+        a.idx += (int64_t)t0 * a.k_sel;
+        if (a.lse) a.lse += (int64_t)t0 * a.H_q;
+    }
     constexpr int KS = D_QK / 32;                         // contraction steps of S^T = 16-byte chunks per gather lane
     constexpr int ROWB = D_QK * 2 + kSlabPad;             // LDS row stride
     static_assert((D_QK * 2) % 128 == 0 && D_V % 128 == 0 && KS % 2 == 0, "row = whole 128-byte windows");
@@ -1038,8 +1049,11 @@ __global__ __launch_bounds__(512, 2) void attn_dense_kernel(AttnArgs a, DenseArg
     const int gr = lane >> 3, gp = lane & 7;
     const int w = wave & 3;
     const int b = blockIdx.y;
-    const int n_rows = da.n_queries * a.H_q;              // flattened rows of a sequence
+    int n_queries = da.n_queries;
+    if (da.lead) n_queries = __builtin_amdgcn_readfirstlane(min(n_queries, lead_rows(da.lead + (int64_t)b * da.n_chunks, da.n_chunks)));
+    const int n_rows = n_queries * a.H_q;                 // flattened rows of a sequence
     const int R0 = ((int)gridDim.x - 1 - (int)blockIdx.x) * kDenseRows;   // longest first
+    if (R0 >= n_rows) return;
     const int nt = (da.pos0 + min(R0 + kDenseRows - 1, n_rows - 1) / a.H_q) / kDenseTile + 1;
 
     if (tid < kDenseRows) mref[tid] = mnew[tid] = mnew[kDenseRows + tid] = -INFINITY;
@@ -1195,7 +1209,7 @@ __global__ __launch_bounds__(512, 2) void attn_dense_kernel(AttnArgs a, DenseArg
         auto tile_src = [&](int t) -> const unsigned short * {   // (past the last tile: that one again, for nobody)
             const int s0 = min(t, nt - 1) * kDenseTile;                // (a tile never straddles a page)
             const int64_t row = PG && a.pv.page_table ? paged_row(a.pv, b, s0) : (int64_t)s0;
-            return kv + (row + min(8 * w + gr, a.Lk - 1 - s0)) * a.row_elems;
+            return kv + (row + min(8 * w + gr, da.pos0 + n_queries - 1 - s0)) * a.row_elems;
         };
         auto load = [&](int t) __attribute__((always_inline)) {
             const unsigned short *p = tile_src(t);
@@ -1420,10 +1434,10 @@ hipError_t launch_t(const AttnArgs &a, hipStream_t st)
     return hipGetLastError();
 }
 
-template <int D_QK, int D_V, bool PG, bool SPLIT, bool MULTI>
-hipError_t launch_slab_t(const AttnArgs &a, size_t lds, hipStream_t st)
+template <int D_QK, int D_V, bool PG, bool SPLIT, bool MULTI, bool REST = false>
+hipError_t launch_slab_t(const AttnArgs &a, size_t lds, hipStream_t st, const RestArgs &ra = RestArgs{})
 {
-    static hipError_t attr = hipFuncSetAttribute((const void *)attn_slab_kernel<D_QK, D_V, PG, SPLIT, MULTI>,
+    static hipError_t attr = hipFuncSetAttribute((const void *)attn_slab_kernel<D_QK, D_V, PG, SPLIT, MULTI, REST>,
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (attr != hipSuccess) return attr;
     int64_t wgs = (int64_t)a.n_layers * a.B * a.Tq;
@@ -1439,21 +1453,71 @@ hipError_t launch_slab_t(const AttnArgs &a, size_t lds, hipStream_t st)
         if (wgs > n_cu) wgs = n_cu;
     }
     dim3 grid((unsigned)wgs, (unsigned)(SPLIT ? a.n_splits : 1));
-    hipLaunchKernelGGL((attn_slab_kernel<D_QK, D_V, PG, SPLIT, MULTI>), grid, dim3(256), lds, st, a);
+    hipLaunchKernelGGL((attn_slab_kernel<D_QK, D_V, PG, SPLIT, MULTI, REST>), grid, dim3(256), lds, st, a, ra);
     return hipGetLastError();
 }
+
+template <int D_QK>
+constexpr size_t slab_lds = (size_t)2 * kSlabTile * (D_QK * 2 + kSlabPad) + 2 * 32 * (kSlabTile * 2 + 16) + (4 * 32 + 4 * 32) * sizeof(float);
 
 template <int D_QK, int D_V>
 hipError_t launch_slab(const AttnArgs &a, hipStream_t st)
 {
-    const size_t lds = (size_t)2 * kSlabTile * (D_QK * 2 + kSlabPad) + 2 * 32 * (kSlabTile * 2 + 16) + (4 * 32 + 4 * 32) * sizeof(float);
+    constexpr size_t lds = slab_lds<D_QK>;
     const bool pg = a.pv.seq_lens || a.pv.page_table;
     if (a.n_splits > 1) return pg ? launch_slab_t<D_QK, D_V, true, true, true>(a, lds, st) : launch_slab_t<D_QK, D_V, false, true, true>(a, lds, st);
     if (a.n_layers > 1) return pg ? launch_slab_t<D_QK, D_V, true, false, true>(a, lds, st) : launch_slab_t<D_QK, D_V, false, false, true>(a, lds, st);
     return pg ? launch_slab_t<D_QK, D_V, true, false, false>(a, lds, st) : launch_slab_t<D_QK, D_V, false, false, false>(a, lds, st);
 }
 
+// Counts of LeadArgs: a workgroup per chunk, four waves with four rows each, a row's entries in one pass (a wave reads 1 KB
+// per instruction; 2048 rows of 2048 entries are 16 MB, 6 us).
+__global__ __launch_bounds__(256) void lead_kernel(LeadArgs a)
+{
+    constexpr int N = kLeadChunk / 4;
+    __shared__ int bad[4];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int r0 = blockIdx.x * kLeadChunk, b = blockIdx.y;
+    const int32_t *idx = a.idx[blockIdx.z] + ((int64_t)b * a.Tq + r0) * a.k_sel;
+    const bool vec = (a.k_sel & 3) == 0 && (uintptr_t)a.idx[blockIdx.z] % 16 == 0;
+    int first = kLeadChunk;                               // first row of the wave's that is no prefix
+#pragma unroll
+    for (int r = N - 1; r >= 0; --r) {
+        const int row = N * wave + r, held = a.pos0 + r0 + row + 1;
+        bool ok = r0 + row < a.n_rows;
+        if (ok) {
+            const int32_t *p = idx + (int64_t)row * a.k_sel;
+            if (vec) {
+                for (int s = 4 * lane; s < a.k_sel; s += 256) {
+                    const i32x4 v = *(const i32x4 *)(p + s);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) ok &= s + e < held ? v[e] == s + e : v[e] < 0;
+                }
+            } else {
+                for (int s = lane; s < a.k_sel; s += 64) ok &= s < held ? p[s] == s : p[s] < 0;
+            }
+        }
+        if (__ballot(!ok) != 0ull) first = row;
+    }
+    if (lane == 0) bad[wave] = first;
+    __syncthreads();
+    if (threadIdx.x == 0)
+        a.lead[((int64_t)blockIdx.z * a.B + b) * a.n_chunks + blockIdx.x] = min(min(bad[0], bad[1]), min(bad[2], bad[3]));
+}
+
 } // namespace
+
+hipError_t launch_lead(const LeadArgs &a, int n_tensors, hipStream_t st)
+{
+    hipLaunchKernelGGL(lead_kernel, dim3((unsigned)a.n_chunks, (unsigned)a.B, (unsigned)n_tensors), dim3(256), 0, st, a);
+    return hipGetLastError();
+}
+
+// The rows of a.Q's only sequence that RestArgs leaves, unsplit.
+hipError_t launch_attn_rest(const AttnArgs &a, const RestArgs &ra, hipStream_t st)
+{
+    return launch_slab_t<576, 512, false, false, false, true>(a, slab_lds<576>, st, ra);
+}
 
 // Rows 0 .. n_queries - 1 of every sequence, row t seeing exactly the keys 0 .. pos0 + t (576 / 512 rows, values in front).
 hipError_t launch_attn_dense(const AttnArgs &a, const DenseArgs &da, hipStream_t st)

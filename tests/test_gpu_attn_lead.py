@@ -1,0 +1,93 @@
+"""Index tensors of the caller's own whose leading rows are whole prefixes (counted on the device, then the dense form and
+the rest): where the count ends, what ends it, tails short and long, two sequences with counts of their own, a similarity
+matrix of layers with different counts."""
+import numpy as np
+import pytest
+import torch
+
+from tests import parity
+import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def _selection(B, Tq, Lk, k, spoil, seed):
+    rng = np.random.default_rng(seed)
+    idx = np.full((B, Tq, k), -1, dtype=np.int32)
+    for b in range(B):
+        for t in range(Tq):
+            n = Lk - Tq + t + 1
+            idx[b, t, :min(n, k)] = np.arange(n) if n <= k else np.sort(rng.choice(n, k, replace=False))
+    for b, t, how in spoil:
+        n = Lk - Tq + t + 1
+        if how == "swap":
+            idx[b, t, [0, n - 1]] = idx[b, t, [n - 1, 0]]
+        elif how == "short":
+            idx[b, t, n - 1] = -1
+        elif how == "long":
+            idx[b, t, n] = n if n < Lk else 0
+        elif how == "hole":
+            idx[b, t, n // 2] = -1
+        elif how == "behind":
+            idx[b, t, k - 1] = 0
+        elif how == "empty":
+            idx[b, t] = -1
+    return idx
+
+
+CASES = [
+    # B, Tq, Lk, k, H_q, spoiled (sequence, row, how)
+    (1, 400, 400, 1024, 32, []),
+    (1, 513, 513, 512, 32, []),                                        # one row behind the prefixes
+    (1, 700, 700, 512, 32, []),                                        # a short tail
+    (1, 900, 900, 512, 32, []),                                        # a long one
+    (2, 300, 500, 1024, 32, [(1, 37, "swap")]),                        # behind a prefix, counts 300 and 37
+    (1, 400, 400, 1022, 31, [(0, 0, "behind")]),                       # none; k not a multiple of four
+    (1, 400, 400, 1024, 32, [(0, 15, "short"), (0, 300, "hole")]),     # last row of a chunk
+    (1, 400, 400, 1024, 32, [(0, 16, "long")]),                        # first row of one
+    (1, 600, 600, 512, 32, [(0, 320, "empty")]),
+    (1, 400, 400, 1024, 32, [(0, 399, "hole")]),                       # the last row
+]
+
+
+@pytest.mark.parametrize("case", CASES)
+def test_leading_prefix_rows(oracle, case):
+    import paper_2603_12201_amd as ic
+    B, Tq, Lk, k, H_q, spoil = case
+    print("[case] lead B=%d Tq=%d Lk=%d k=%d H_q=%d %s" % case, flush=True)
+    cfg = synth.config("c2", B=B, Tq=Tq, Lk=Lk, q_pos0=Lk - Tq, H_q=H_q, k_sel=k, row_elems=576, H_I=4, seed=Tq + k)
+    t = synth.attn_layer(cfg, 0)
+    idx = _selection(B, Tq, Lk, k, spoil, Tq)
+    O, lse = ic.sparse_attn(t["Q"].cuda(), t["KV"].cuda(), torch.from_numpy(idx).cuda(), 512, 0, 1 / 24.0, want_lse=True)
+    torch.cuda.synchronize()
+    lb = synth.bits_layer(t)
+    want, want_lse = oracle.sparse_attn(lb["Q"], lb["KV"], idx, 512, 0, 1 / 24.0)
+    parity.check_attn(O.float().cpu().numpy(), want)
+    got, ref = lse.cpu().numpy(), np.asarray(want_lse, dtype=np.float64).reshape(lse.shape)
+    assert np.array_equal(np.isinf(got), np.isinf(ref))
+    ok = np.isfinite(ref)
+    assert np.abs(got[ok] - ref[ok]).max() < 1e-3
+
+
+def test_similarity_of_layers_with_leading_rows(oracle):
+    import paper_2603_12201_amd as ic
+    B, Tq, k = 2, 600, 512
+    print("[case] similarity with leading rows B=%d Tq=%d k=%d" % (B, Tq, k), flush=True)
+    cfg = synth.config("c2", B=B, Tq=Tq, Lk=Tq, q_pos0=0, H_q=32, k_sel=k, row_elems=576, H_I=4, seed=5)
+    spoil = [[], [(1, 100, "hole")], [(0, 0, "empty"), (1, 511, "swap")]]
+    layers = [synth.attn_layer(cfg, l) for l in range(3)]
+    g = [{n: v.cuda() for n, v in t.items()} for t in layers]
+    idx = [torch.from_numpy(_selection(B, Tq, Tq, k, s, 10 + l)).cuda() for l, s in enumerate(spoil)]
+    outs = [torch.empty((B, Tq, 32, 512), dtype=torch.bfloat16, device="cuda") for _ in g]
+    S = ic.similarity_matrix(ic.make_layers(g, k, 0, 512, 0, 1 / 24.0, outs), idx).cpu().numpy()
+    none = torch.empty(0, dtype=torch.uint8, device="cuda")               # no room for the counts: row by row
+    for i in range(3):
+        own = ic.sparse_attn(g[i]["Q"], g[i]["KV"], idx[i], 512, 0, 1 / 24.0, workspace=none)
+        parity.check_attn(outs[i].float().cpu().numpy(), own.double().cpu().numpy())
+        for j in range(i):
+            re = ic.sparse_attn(g[i]["Q"], g[i]["KV"], idx[j], 512, 0, 1 / 24.0, workspace=none)
+            a, b = own.double().flatten(2), re.double().flatten(2)
+            na, nb = a.norm(dim=-1), b.norm(dim=-1)
+            cs = torch.where((na == 0) & (nb == 0), torch.ones_like(na), (a * b).sum(-1) / (na * nb).clamp_min(1e-300))
+            assert abs(S[i, j] - cs.mean().item()) < 2e-4
+        assert S[i, i] == 1.0 and all(S[i, j] == 0.0 for j in range(i + 1, 3))
