@@ -851,14 +851,17 @@ ic_status ic_similarity_matrix(const ic_layer *layers, int32_t n_layers, const i
     if (!idx_layers || !S) return fail(IC_ERR_NULL, "idx_layers and S must not be NULL");
     for (int l = 0; l < n_layers; ++l)
         if (!idx_layers[l]) return fail(IC_ERR_NULL, "idx_layers[%d] is NULL", l);
-    s = check_ws(workspace, workspace_bytes, ic_similarity_matrix_workspace(layers, n_layers));
+    // the counts of leading rows only make it faster: a workspace without room for them will do
+    size_t lb = sim_lead_bytes(layers, n_layers);
+    const size_t all = ic_similarity_matrix_workspace(layers, n_layers), min_ws = all - lb;
+    s = check_ws(workspace, workspace_bytes, min_ws);
     if (s != IC_OK) return s;
+    if (workspace_bytes < all) lb = 0;
     hipStream_t st = (hipStream_t)stream;
     char *ws = (char *)workspace;
     void *o_reuse = ws;
     void *attn_ws = ws + sim_o_bytes(&layers[0].at);
-    const size_t lb = sim_lead_bytes(layers, n_layers);
-    const size_t attn_bytes = ic_similarity_matrix_workspace(layers, n_layers) - lb - sim_o_bytes(&layers[0].at);
+    const size_t attn_bytes = min_ws - sim_o_bytes(&layers[0].at);
     int32_t *const lead = (int32_t *)((char *)attn_ws + attn_bytes);
     hipError_t e = ic::launch_sim_init(S, n_layers, st);
     if (e != hipSuccess) return fail(IC_ERR_HIP, "similarity init failed: %s", hipGetErrorString(e));
