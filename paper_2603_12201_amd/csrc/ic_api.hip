@@ -470,10 +470,12 @@ ic_status run_attn_layers(const ic_layer *layers, int n_layers, const int32_t *i
     const ic_attn_desc *d = &layers[0].at;
     ic::AttnArgs a = attn_args(layers, n_layers, idx, lse, pc, causal_pos0);
     if (const int nd = dense_queries(d, n_layers, causal_pos0)) {
-        ProfScope ps(2, st);
-        const ic::DenseArgs da{nd, (int32_t)causal_pos0, nullptr, 0};
-        hipError_t e = ic::launch_attn_dense(a, da, st);
-        if (e != hipSuccess) return fail(IC_ERR_HIP, "dense attention launch failed: %s", hipGetErrorString(e));
+        {
+            ProfScope ps(2, st);               // (the rows behind them are timed by their own launch)
+            const ic::DenseArgs da{nd, (int32_t)causal_pos0, nullptr, 0};
+            hipError_t e = ic::launch_attn_dense(a, da, st);
+            if (e != hipSuccess) return fail(IC_ERR_HIP, "dense attention launch failed: %s", hipGetErrorString(e));
+        }
         if (nd == d->Tq) return IC_OK;
         for (int b = 0; b < d->B; ++b) {       // the other rows, a sequence at a time
             ic_layer r = layer_rows(layers, b, nd, d->Tq - nd);
