@@ -1041,7 +1041,7 @@ __global__ __launch_bounds__(512, 2) void attn_dense_kernel(AttnArgs a, DenseArg
     float *mref = (float *)(pbuf + 2 * PBUFB);            // [64] common references
     float *mnew = mref + kDenseRows;                      // [2][64] per key half: reference of the latest tile, then row sums
     float *fac = mnew + 2 * kDenseRows;                   // [3][64] factors of a moved reference: O, P of either key half
-    int *moved = (int *)(fac + 3 * kDenseRows);           // [2] by tile parity
+    int *moved = (int *)(fac + 3 * kDenseRows);           // [2] by tile parity; [2]: a key some row does not see has no finite score
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1057,7 +1057,7 @@ __global__ __launch_bounds__(512, 2) void attn_dense_kernel(AttnArgs a, DenseArg
     const int nt = (da.pos0 + min(R0 + kDenseRows - 1, n_rows - 1) / a.H_q) / kDenseTile + 1;
 
     if (tid < kDenseRows) mref[tid] = mnew[tid] = mnew[kDenseRows + tid] = -INFINITY;
-    if (tid < 2) moved[tid] = 0;
+    if (tid < 3) moved[tid] = 0;
     // Q in the shape of two tiles, through buffers 2 and 3, by everybody
     unsigned char *qb = tbuf + 2 * TBUFB;
     auto load_q = [&](u32x4 (&raw)[9]) __attribute__((always_inline)) {
@@ -1125,6 +1125,10 @@ __global__ __launch_bounds__(512, 2) void attn_dense_kernel(AttnArgs a, DenseArg
             const int key0 = kDenseTile * t + 16 * kh;
             if (key0 + 15 > lim0) {
                 const int k0 = key0 + 8 * (g >> 1) + (g & 1);
+                float z = 0.f;                            // NaN if any of the scores is not finite
+#pragma unroll
+                for (int i = 0; i < 4; ++i) z = __builtin_fmaf(s4[1][i], 0.f, __builtin_fmaf(s4[0][i], 0.f, z));
+                if (__ballot(z != 0.f) != 0ull) moved[2] = 1;
 #pragma unroll
                 for (int r = 0; r < 2; ++r)
 #pragma unroll
@@ -1241,8 +1245,24 @@ __global__ __launch_bounds__(512, 2) void attn_dense_kernel(AttnArgs a, DenseArg
         typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
         const int tr_off = (8 * hh + 2 * (l16 >> 2)) * ROWB + 256 * w + 32 * (g & 1) + 8 * (l16 & 3);
         const int pr_off = l32 * PSTR + 16 * hh;
+        // Tiles from this one on hold keys that some row of the workgroup does not see.  Such a row's p is 0 there, but 0 times
+        // an infinity or NaN in a later position (an unused one, another token's) would reach its output.  A key with one has
+        // no finite score, which the scores waves look for in these tiles; from there on V enters the product with infinities
+        // and NaN as 0.  (Done to every such tile without the look, four layers of 3 x 1021 rows took 600 us instead of
+        // 575.)  A row that does see such a key has its score, and so its p, from the same elements.
+        const int t_edge = (da.pos0 + R0 / a.H_q + 1) / kDenseTile;
         bf16x8 pa[2][2];
         s16x4 vq[2][4][2];
+        auto finite_v = [&]() __attribute__((always_inline)) {
+#pragma unroll
+            for (int s = 0; s < 2; ++s)
+#pragma unroll
+                for (int nb = 0; nb < 4; ++nb)
+#pragma unroll
+                    for (int u = 0; u < 2; ++u)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) vq[s][nb][u][e] = (vq[s][nb][u][e] & 0x7f80) == 0x7f80 ? (short)0 : vq[s][nb][u][e];
+        };
         auto read_v = [&](int t, int s, int nb) __attribute__((always_inline)) {
             const unsigned char *tb = tbuf + (t & (kDenseRing - 1)) * TBUFB + tr_off + 16 * s * ROWB + 64 * nb;
 #pragma unroll
@@ -1279,6 +1299,7 @@ __global__ __launch_bounds__(512, 2) void attn_dense_kernel(AttnArgs a, DenseArg
                     __builtin_amdgcn_sched_barrier(0);
                 }
             });
+            if (kNext && t - 1 >= t_edge && __builtin_amdgcn_readfirstlane(moved[2])) finite_v();                 // (the step's end is far enough from their use)
             if (kNext && __builtin_amdgcn_readfirstlane(flag)) {       // see above
                 __syncthreads();
                 if constexpr (kMma) acc::rescale_o(fac[l32], fac[32 + l32]);
@@ -1523,7 +1544,7 @@ hipError_t launch_attn_rest(const AttnArgs &a, const RestArgs &ra, hipStream_t s
 hipError_t launch_attn_dense(const AttnArgs &a, const DenseArgs &da, hipStream_t st)
 {
     if (da.n_queries <= 0) return hipSuccess;
-    constexpr int lds = kDenseRing * kDenseTile * (576 * 2 + kSlabPad) + 2 * kDenseRows * (kDenseTile * 2 + 16) + (6 * kDenseRows + 2) * 4;
+    constexpr int lds = kDenseRing * kDenseTile * (576 * 2 + kSlabPad) + 2 * kDenseRows * (kDenseTile * 2 + 16) + (6 * kDenseRows + 3) * 4;
     static hipError_t attr = hipFuncSetAttribute((const void *)attn_dense_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     static hipError_t attr_pg = hipFuncSetAttribute((const void *)attn_dense_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (attr != hipSuccess) return attr;

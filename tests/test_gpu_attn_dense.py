@@ -64,3 +64,28 @@ def test_dense_rows(oracle, case):
     want, _ = oracle.sparse_attn(lb["Q"], lb["KV"], idx.cpu().numpy(), 512, 0, scale)
     err = parity.check_attn(out.float().cpu().numpy(), want)
     print("max abs err %.3g" % err)
+
+
+@pytest.mark.parametrize("bad", [float("nan"), float("inf"), float("-inf")])
+@pytest.mark.parametrize("B, Tq, H_q, row", [(1, 300, 32, 199), (1, 300, 32, 224), (1, 300, 32, 1), (2, 200, 32, 199), (1, 500, 20, 333)])
+def test_later_keys_do_not_reach_earlier_rows(bad, B, Tq, H_q, row):
+    """One KV row of infinities or NaN: the query rows that do not see it are what they are without it, bit for bit."""
+    import paper_2603_12201_amd as ic
+    print("[case] dense, row %d of %d is %g, B=%d H_q=%d" % (row, Tq, bad, B, H_q), flush=True)
+    cfg = synth.config("c2", B=B, Tq=Tq, Lk=Tq, q_pos0=0, H_q=H_q, k_sel=512, row_elems=576, H_I=4, seed=row)
+    t = synth.indexer_layer(cfg, 0)
+    t.update(synth.attn_layer(cfg, 0))
+    g = {n: v.cuda() for n, v in t.items()}
+    outs = []
+    for spoil in (False, True):
+        kv = g["KV"].clone()
+        if spoil:
+            kv[:, row, 0::2] = bad
+        out = torch.empty((B, Tq, H_q, 512), dtype=torch.bfloat16, device="cuda")
+        arr = ic.make_layers([dict(g, KV=kv)], 512, 0, 512, 0, 1 / 24.0, [out])
+        idx = torch.empty((B, Tq, 512), dtype=torch.int32, device="cuda")
+        ic.forward_stack(arr, [True], idx, torch.empty(max(256, ic.forward_stack_workspace(arr)), dtype=torch.uint8, device="cuda"))
+        outs.append(out.cpu())
+    assert torch.equal(outs[0][:, :row].view(torch.int16), outs[1][:, :row].view(torch.int16))
+    if bad != bad:
+        assert torch.isnan(outs[1][:, row:].float()).all()
