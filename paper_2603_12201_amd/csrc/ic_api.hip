@@ -331,7 +331,7 @@ size_t indexer_min_ws(const ic_indexer_desc *d)
 // walk is long (a short chunk behind a prefix), the forms that split a selection over workgroups are the faster ones.
 int dense_queries(const ic_attn_desc *d, int n_layers, int64_t causal_pos0)
 {
-    if (n_layers != 1 || causal_pos0 < 0 || attn_resident(d) != 256 || d->d_v != 512) return 0;
+    if (n_layers != 1 || causal_pos0 < 0 || attn_resident(d) != 256 || d->d_v != 512 || d->B > 65535) return 0;   // (B: grid.y)
     int64_t n = (d->k_sel < d->Lk ? d->k_sel : d->Lk) - causal_pos0;
     n = n < 0 ? 0 : (n > d->Tq ? d->Tq : n);
     const int64_t blocks = (n * d->H_q + 63) / 64 * d->B, tiles = (causal_pos0 + n + 63) / 64;
