@@ -326,15 +326,25 @@ size_t indexer_min_ws(const ic_indexer_desc *d)
     return align_up((size_t)rows * strip_ld(d) * sizeof(float));
 }
 
-// Leading query rows of every sequence that the dense form takes: the rows that see at most k_sel keys and so select all
-// of them.  Its workgroups walk their keys one tile after the other, so where they leave most of the chip idle and the
+// What is known about an index tensor: the causal top-k of this library for query rows at positions pos0 + t over the
+// first lk keys (row t then holds the min(k_sel, pos0 + t + 1, lk) best of them and -1s behind); pos0 < 0: nothing.  lk
+// is the Full layer's: a Shared layer's cache may be longer.
+struct Causal {
+    int64_t pos0;
+    int32_t lk;
+};
+constexpr Causal kUnknown = {-1, 0};
+
+// Leading query rows of every sequence that the dense form takes: the rows that select exactly the keys 0 .. pos0 + t, of
+// which they see at most k_sel and all below lk.  Its workgroups walk their keys one tile after the other, so where they leave most of the chip idle and the
 // walk is long (a short chunk behind a prefix), the forms that split a selection over workgroups are the faster ones.
-int dense_queries(const ic_attn_desc *d, int n_layers, int64_t causal_pos0)
+int dense_queries(const ic_attn_desc *d, int n_layers, Causal c)
 {
-    if (n_layers != 1 || causal_pos0 < 0 || attn_resident(d) != 256 || d->d_v != 512 || d->B > 65535) return 0;   // (B: grid.y)
-    int64_t n = (d->k_sel < d->Lk ? d->k_sel : d->Lk) - causal_pos0;
+    if (n_layers != 1 || c.pos0 < 0 || attn_resident(d) != 256 || d->d_v != 512 || d->B > 65535) return 0;   // (B: grid.y)
+    const int32_t keys = c.lk < d->Lk ? c.lk : d->Lk;
+    int64_t n = (d->k_sel < keys ? d->k_sel : keys) - c.pos0;
     n = n < 0 ? 0 : (n > d->Tq ? d->Tq : n);
-    const int64_t blocks = (n * d->H_q + 63) / 64 * d->B, tiles = (causal_pos0 + n + 63) / 64;
+    const int64_t blocks = (n * d->H_q + 63) / 64 * d->B, tiles = (c.pos0 + n + 63) / 64;
     return n > 0 && (blocks >= 128 || tiles <= 4) ? (int)n : 0;
 }
 
@@ -348,7 +358,7 @@ int lead_queries(const ic_attn_desc *d)
 {
     const int64_t pos0 = (int64_t)d->Lk - d->Tq;
     if (pos0 < 0) return 0;
-    const int n = dense_queries(d, 1, pos0);
+    const int n = dense_queries(d, 1, Causal{pos0, d->Lk});
     return (int64_t)n * ((d->k_sel + 63) / 64) >= 16 * 256 && (int64_t)n * d->H_q >= 128 * 64 ? n : 0;
 }
 
@@ -379,7 +389,7 @@ ic_status count_lead(const ic_attn_desc *d, const int32_t *const *idx, int n_ten
 }
 
 ic::AttnArgs attn_args(const ic_layer *layers, int n_layers, const int32_t *idx, float *lse, const ic_paged_cache *pc,
-                       int64_t causal_pos0)
+                       Causal c)
 {
     const ic_attn_desc *d = &layers[0].at;
     ic::AttnArgs a;
@@ -404,12 +414,12 @@ ic::AttnArgs attn_args(const ic_layer *layers, int n_layers, const int32_t *idx,
     a.k_sel = d->k_sel;
     a.scale_log2e = d->sm_scale * 1.4426950408889634f;
     a.pv = paged_view(pc);
-    a.causal_pos0 = causal_pos0;
+    a.causal_pos0 = c.pos0;
     return a;
 }
 
 ic_status run_attn_layers(const ic_layer *layers, int n_layers, const int32_t *idx, float *lse, void *ws, size_t ws_bytes,
-                          hipStream_t st, const ic_paged_cache *pc, int64_t causal_pos0);
+                          hipStream_t st, const ic_paged_cache *pc, Causal c);
 
 // Rows row0 .. row0 + n - 1 of sequence b as a problem of their own.
 ic_layer layer_rows(const ic_layer *L, int b, int row0, int n)
@@ -434,7 +444,7 @@ ic_status run_attn_lead(const ic_layer *L, const int32_t *idx, const int32_t *le
     if (dense) {
         ProfScope ps(2, st);
         const ic::DenseArgs da{n, d->Lk - d->Tq, lead, n_chunks};
-        hipError_t e = ic::launch_attn_dense(attn_args(L, 1, idx, lse, nullptr, -1), da, st);
+        hipError_t e = ic::launch_attn_dense(attn_args(L, 1, idx, lse, nullptr, kUnknown), da, st);
         if (e != hipSuccess) return fail(IC_ERR_HIP, "dense attention launch failed: %s", hipGetErrorString(e));
     }
     // The rows behind the n candidates go along where they fill the chip; a few of them are split over it on their own.
@@ -445,7 +455,7 @@ ic_status run_attn_lead(const ic_layer *L, const int32_t *idx, const int32_t *le
         r.KV = (const char *)r.KV + (int64_t)b * d->Lk * d->row_elems * 2;
         {
             ProfScope ps(2, st);
-            ic::AttnArgs a = attn_args(&r, 1, idx + row * d->k_sel, lse ? lse + row * d->H_q : nullptr, nullptr, -1);
+            ic::AttnArgs a = attn_args(&r, 1, idx + row * d->k_sel, lse ? lse + row * d->H_q : nullptr, nullptr, kUnknown);
             a.n_splits = 1;
             a.split_len = (d->k_sel + 63) / 64 * 64;
             const ic::RestArgs ra{lead + (int64_t)b * n_chunks, lead2 + (int64_t)b * n_chunks, n_chunks, r.at.Tq};
@@ -456,23 +466,23 @@ ic_status run_attn_lead(const ic_layer *L, const int32_t *idx, const int32_t *le
         ic_layer t = layer_rows(L, b, n, d->Tq - n);
         t.KV = r.KV;
         ic_status s = run_attn_layers(&t, 1, idx + (row + n) * d->k_sel, lse ? lse + (row + n) * d->H_q : nullptr, ws, ws_bytes, st,
-                                      nullptr, -1);
+                                      nullptr, kUnknown);
         if (s != IC_OK) return s;
     }
     return IC_OK;
 }
 
-// causal_pos0 >= 0: idx is this library's causal top-k for query rows at positions causal_pos0 + t (rows that can hold
-// fewer than k_sel entries end in -1s, and the kernel leaves their empty tiles out); -1: idx is the caller's own
+// c: idx is this library's own (rows that can hold fewer than k_sel entries end in -1s, and the kernels leave their empty
+// tiles out) or the caller's (kUnknown)
 ic_status run_attn_layers(const ic_layer *layers, int n_layers, const int32_t *idx, float *lse, void *ws, size_t ws_bytes,
-                          hipStream_t st, const ic_paged_cache *pc, int64_t causal_pos0)
+                          hipStream_t st, const ic_paged_cache *pc, Causal c)
 {
     const ic_attn_desc *d = &layers[0].at;
-    ic::AttnArgs a = attn_args(layers, n_layers, idx, lse, pc, causal_pos0);
-    if (const int nd = dense_queries(d, n_layers, causal_pos0)) {
+    ic::AttnArgs a = attn_args(layers, n_layers, idx, lse, pc, c);
+    if (const int nd = dense_queries(d, n_layers, c)) {
         {
             ProfScope ps(2, st);               // (the rows behind them are timed by their own launch)
-            const ic::DenseArgs da{nd, (int32_t)causal_pos0, nullptr, 0};
+            const ic::DenseArgs da{nd, (int32_t)c.pos0, nullptr, 0};
             hipError_t e = ic::launch_attn_dense(a, da, st);
             if (e != hipSuccess) return fail(IC_ERR_HIP, "dense attention launch failed: %s", hipGetErrorString(e));
         }
@@ -487,12 +497,12 @@ ic_status run_attn_layers(const ic_layer *layers, int n_layers, const int32_t *i
             }
             if (!pc || !pc->page_table) r.KV = (const char *)r.KV + (int64_t)b * d->Lk * d->row_elems * 2;
             ic_status s = run_attn_layers(&r, 1, idx + row * d->k_sel, lse ? lse + row * d->H_q : nullptr, ws, ws_bytes, st,
-                                          pc ? &pb : nullptr, causal_pos0 + nd);
+                                          pc ? &pb : nullptr, Causal{c.pos0 + nd, c.lk});
             if (s != IC_OK) return s;
         }
         return IC_OK;
     }
-    if (const size_t lb = !pc && n_layers == 1 && causal_pos0 < 0 ? lead_bytes(d, 1) : 0) {
+    if (const size_t lb = !pc && n_layers == 1 && c.pos0 < 0 ? lead_bytes(d, 1) : 0) {
         if (ws && ws_bytes >= lb) {
             ic_status s = count_lead(d, &idx, 1, (int32_t *)ws, st);
             if (s != IC_OK) return s;
@@ -527,7 +537,7 @@ ic_status run_attn(const ic_attn_desc *d, const void *Q, const void *KV, const i
     l.Q = Q;
     l.KV = KV;
     l.O = O;
-    return run_attn_layers(&l, 1, idx, lse, ws, ws_bytes, st, pc, -1);
+    return run_attn_layers(&l, 1, idx, lse, ws, ws_bytes, st, pc, kUnknown);
 }
 
 } // namespace
@@ -704,19 +714,19 @@ static ic_status forward_stack_impl(const ic_layer *layers, int32_t n_layers, co
     s = check_ws(workspace, workspace_bytes, need);
     if (s != IC_OK) return s;
     hipStream_t st = (hipStream_t)stream;
-    int64_t idx_pos0 = -1;                     // position of query row 0 when the cached indices were selected
+    Causal known = kUnknown;                   // of the cached indices
     for (int l = 0; l < n_layers; ++l) {
         const ic_layer *L = &layers[l];
         if (full_mask[l]) {   // Full: fresh indices overwrite the cache; Shared: cache left as it is
             s = run_indexer(&L->ix, L->q, L->k, L->w, idx_cache, nullptr, workspace, workspace_bytes, st, pc);
             if (s != IC_OK) return s;
-            idx_pos0 = (pc && pc->seq_lens) ? -1 : (L->ix.q_pos0 >= 0 ? (int64_t)L->ix.q_pos0 : -1);
+            known = (pc && pc->seq_lens) || L->ix.q_pos0 < 0 ? kUnknown : Causal{L->ix.q_pos0, L->ix.Lk};
         }
         int run = 1;                           // this layer and the Shared layers behind it
         while (l + run < n_layers && !full_mask[l + run]) ++run;
-        int m = dense_queries(&L->at, 1, idx_pos0) ? 1 : attn_batch(L, run, pc);
+        int m = dense_queries(&L->at, 1, known) ? 1 : attn_batch(L, run, pc);
         while (m > 1 && attn_ws_bytes(&L->at, m) > workspace_bytes) --m;
-        s = run_attn_layers(L, m, idx_cache, nullptr, workspace, workspace_bytes, st, pc, idx_pos0);
+        s = run_attn_layers(L, m, idx_cache, nullptr, workspace, workspace_bytes, st, pc, known);
         if (s != IC_OK) return s;
         l += m - 1;
     }

@@ -89,3 +89,56 @@ def test_later_keys_do_not_reach_earlier_rows(bad, B, Tq, H_q, row):
     assert torch.equal(outs[0][:, :row].view(torch.int16), outs[1][:, :row].view(torch.int16))
     if bad != bad:
         assert torch.isnan(outs[1][:, row:].float()).all()
+
+
+@pytest.mark.parametrize("B, Tq, pos0, lk_full, lk_shared, k, page", [
+    (1, 120, 0, 100, 120, 2048, 0),               # rows 100 .. 119 select 0 .. 99 only
+    (2, 300, 10, 200, 400, 256, 0),               # fewer keys than k, then none of the later rows dense
+    (1, 70, 40, 100, 128, 2048, 64),              # paged
+])
+def test_shared_cache_longer_than_the_full_layers(oracle, B, Tq, pos0, lk_full, lk_shared, k, page):
+    """A Shared layer attends to what its Full layer selected, among the Full layer's keys, however long its own cache is."""
+    import paper_2603_12201_amd as ic
+    print("[case] dense B=%d Tq=%d pos0=%d Lk full %d shared %d k=%d page=%d" % (B, Tq, pos0, lk_full, lk_shared, k, page), flush=True)
+    mk = lambda lk, l: synth.config("c2", B=B, Tq=Tq, Lk=lk, q_pos0=pos0, H_q=32, k_sel=k, row_elems=576, H_I=4, seed=3 + l)
+    full = synth.indexer_layer(mk(lk_full, 0), 0)
+    full.update(synth.attn_layer(mk(lk_full, 0), 0))
+    shared = synth.attn_layer(mk(lk_shared, 1), 1)
+    want_kv = shared["KV"].clone()
+    shared["KV"][:, lk_full:] = 50.0              # nobody selects these
+    g = [{n: v.cuda() for n, v in t.items()} for t in (full, shared)]
+    outs = [torch.empty((B, Tq, 32, 512), dtype=torch.bfloat16, device="cuda") for _ in g]
+    idx = torch.empty((B, Tq, k), dtype=torch.int32, device="cuda")
+    pc = None
+    if page:
+        n = -(-max(lk_full, lk_shared) // page)
+        table = torch.arange(B * n, dtype=torch.int32).flip(0).view(B, n)
+        for t in g:
+            for name in ("k", "KV"):
+                if name not in t:
+                    continue
+                pool = torch.full((B * n * page, t[name].shape[-1]), 50.0, dtype=torch.bfloat16, device="cuda")
+                for b in range(B):
+                    for p in range(n):
+                        src = t[name][b, p * page:(p + 1) * page]
+                        pool[int(table[b, p]) * page:int(table[b, p]) * page + src.shape[0]] = src
+                t[name] = pool
+        pc = ic.paged_cache(page_table=table.cuda(), page_size=page)
+    arr = ic.make_layers(g, k, pos0, 512, 0, 1 / 24.0, outs, Lk=lk_full if page else None)
+    arr[1].at.Lk = lk_shared
+    for a in arr:
+        a.ix.q_pos0 = pos0
+    ws = torch.empty(max(256, ic.forward_stack_workspace(arr)), dtype=torch.uint8, device="cuda")
+    if page:
+        ic.forward_stack_paged(arr, [True, False], pc, idx, ws)
+    else:
+        ic.forward_stack(arr, [True, False], idx, ws)
+    torch.cuda.synchronize()
+    sel = idx.cpu().numpy()
+    assert sel.max() == lk_full - 1
+    lb = synth.bits_layer(dict(shared, KV=want_kv))
+    want, _ = oracle.sparse_attn(lb["Q"], lb["KV"], sel, 512, 0, 1 / 24.0)
+    parity.check_attn(outs[1].float().cpu().numpy(), want)
+    lb = synth.bits_layer(full)
+    want, _ = oracle.sparse_attn(lb["Q"], lb["KV"], sel, 512, 0, 1 / 24.0)
+    parity.check_attn(outs[0].float().cpu().numpy(), want)
