@@ -143,7 +143,9 @@ typedef struct ic_layer {
     void *O;            /* [B,Tq,H_q,d_v] bf16 out */
 } ic_layer;
 
-/* Workspace for ic_forward_stack = the largest per-layer need (layers is host memory). */
+/* Workspace for ic_forward_stack (layers is host memory): the largest need of a layer, or of a run of up to eight layers of
+ * one shape, whose attentions may share a launch.  ic_forward_stack accepts less, down to one layer's attention partials and
+ * 16 rows of scores, and then runs layer by layer. */
 size_t ic_forward_stack_workspace(const ic_layer *layers, int32_t n_layers);
 
 /*
@@ -153,8 +155,8 @@ size_t ic_forward_stack_workspace(const ic_layer *layers, int32_t n_layers);
  *             idx_cache as the nearest preceding Full layer left it); full_mask[0] must be 1
  *   idx_cache [B,Tq,k_sel] int32 device, caller-owned: the paper's T_cache, the only index
  *             buffer of the pass; on return it holds the last Full layer's indices
- * Every layer then runs sparse attention on its own Q/KV with idx_cache.  At most two kernel
- * groups per layer are enqueued on `stream`, with no host synchronisation in between.
+ * Every layer runs sparse attention on its own Q/KV with idx_cache; consecutive layers that read the
+ * same indices may share a launch.  All work is enqueued on `stream` with no host synchronisation.
  */
 ic_status ic_forward_stack(const ic_layer *layers, int32_t n_layers, const uint8_t *full_mask,
                            int32_t *idx_cache, void *workspace, size_t workspace_bytes, void *stream);
@@ -313,6 +315,8 @@ ic_status ic_pattern_search_dp(const double *S, int32_t n_layers, int32_t n_full
  *
  * Outputs (host): full_mask [n_layers]; order [n_shared], nullable: the flipped layers in commit
  * order; loss_curve [n_shared], nullable: the loss after each commit.
+ * Workspace: the queries return room for the stack's fastest form (ic_forward_stack_workspace); both calls accept what one
+ * layer at a time needs, the largest ic_sparse_attn_workspace() or strip of score rows, plus their own few kilobytes.
  * Errors: IC_ERR_NULL, IC_ERR_SHAPE (n_shared > candidates, bad block count, layer shapes),
  * IC_ERR_PATTERN never (the search keeps layer 0 Full), IC_ERR_WORKSPACE, IC_ERR_HIP.
  */

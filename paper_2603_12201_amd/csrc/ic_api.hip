@@ -326,6 +326,23 @@ size_t indexer_min_ws(const ic_indexer_desc *d)
     return align_up((size_t)rows * strip_ld(d) * sizeof(float));
 }
 
+// Strip asked for when rows are not selected in parts.
+size_t indexer_strip_ws(const ic_indexer_desc *d)
+{
+    const size_t row_bytes = strip_ld(d) * sizeof(float);
+    const size_t all = (size_t)d->B * d->Tq * row_bytes;
+    // small problems keep every row in flight; larger ones at most a quarter of their rows and at most the budget,
+    // so that the scores of a long sequence are never all resident at once
+    size_t want = all;
+    if (all > kSmallStrip) {
+        want = all / 4 > kSmallStrip ? all / 4 : kSmallStrip;
+        if (want > kStripBudget) want = kStripBudget;
+    }
+    const size_t min_b = indexer_min_ws(d);
+    if (want < min_b) want = min_b;
+    return align_up(want / row_bytes * row_bytes);
+}
+
 // What is known about an index tensor: the causal top-k of this library for query rows at positions pos0 + t over the
 // first lk keys (row t then holds the min(k_sel, pos0 + t + 1, lk) best of them and -1s behind); pos0 < 0: nothing.  lk
 // is the Full layer's: a Shared layer's cache may be longer.
@@ -550,18 +567,7 @@ size_t ic_indexer_topk_workspace(const ic_indexer_desc *d)
 {
     if (check_indexer(d) != IC_OK) return 0;
     if (const size_t pw = parts_ws(d)) return pw;
-    const size_t row_bytes = strip_ld(d) * sizeof(float);
-    const size_t all = (size_t)d->B * d->Tq * row_bytes;
-    // small problems keep every row in flight; larger ones at most a quarter of their rows and at most the budget,
-    // so that the scores of a long sequence are never all resident at once
-    size_t want = all;
-    if (all > kSmallStrip) {
-        want = all / 4 > kSmallStrip ? all / 4 : kSmallStrip;
-        if (want > kStripBudget) want = kStripBudget;
-    }
-    const size_t min_b = indexer_min_ws(d);
-    if (want < min_b) want = min_b;
-    return align_up(want / row_bytes * row_bytes);
+    return indexer_strip_ws(d);
 }
 
 ic_status ic_indexer_topk(const ic_indexer_desc *d, const void *q, const void *k, const float *w, int32_t *idx,
@@ -998,20 +1004,36 @@ ic_status greedy_core(int N, int K, int P, uint8_t *mask, int32_t *order, double
     return IC_OK;
 }
 
+// The layers' similarities and an accumulator; the stack's workspace follows them.
+size_t loss_head_bytes(int32_t n_layers) { return align_up((size_t)n_layers * sizeof(double)) + kAlign; }
+
 size_t pattern_loss_ws(const ic_layer *layers, int32_t n_layers)
 {
-    size_t fw = ic_forward_stack_workspace(layers, n_layers);
-    return align_up(fw) + align_up((size_t)n_layers * sizeof(double)) + kAlign;
+    return loss_head_bytes(n_layers) + align_up(ic_forward_stack_workspace(layers, n_layers));
+}
+
+// What has to be there: a layer at a time.  Room for runs of layers and for rows in parts only makes the stack faster.
+size_t pattern_loss_min_ws(const ic_layer *layers, int32_t n_layers)
+{
+    size_t fw = 0;
+    for (int l = 0; l < n_layers; ++l) {
+        const size_t a = attn_ws_bytes(&layers[l].at);
+        const size_t b = layers[l].q && check_indexer(&layers[l].ix) == IC_OK ? indexer_strip_ws(&layers[l].ix) : 0;
+        if (a > fw) fw = a;
+        if (b > fw) fw = b;
+    }
+    return loss_head_bytes(n_layers) + align_up(fw);
 }
 
 ic_status run_pattern_loss(const ic_layer *layers, int32_t n_layers, const uint8_t *full_mask, const void *const *O_ref,
-                           int32_t *idx_cache, double *loss, void *workspace, hipStream_t st)
+                           int32_t *idx_cache, double *loss, void *workspace, size_t workspace_bytes, hipStream_t st)
 {
     char *ws = (char *)workspace;
-    const size_t fw = align_up(ic_forward_stack_workspace(layers, n_layers));
-    double *sims = (double *)(ws + fw);
-    double *acc = (double *)(ws + fw + align_up((size_t)n_layers * sizeof(double)));
-    ic_status s = ic_forward_stack(layers, n_layers, full_mask, idx_cache, workspace, fw, (void *)st);
+    const size_t head = loss_head_bytes(n_layers), most = pattern_loss_ws(layers, n_layers);
+    double *sims = (double *)ws;
+    double *acc = (double *)(ws + head - kAlign);
+    const size_t fw = (workspace_bytes < most ? workspace_bytes : most) - head;
+    ic_status s = ic_forward_stack(layers, n_layers, full_mask, idx_cache, ws + head, fw, (void *)st);
     if (s != IC_OK) return s;
     const ic_attn_desc *a0 = &layers[0].at;
     const int64_t n_rows = (int64_t)a0->B * a0->Tq, row_len = (int64_t)a0->H_q * a0->d_v;
@@ -1076,9 +1098,9 @@ ic_status ic_pattern_loss(const ic_layer *layers, int32_t n_layers, const uint8_
     ic_status s = check_loss_args(layers, n_layers, O_ref, idx_cache);
     if (s != IC_OK) return s;
     if (!full_mask || !loss) return fail(IC_ERR_NULL, "full_mask and loss must not be NULL");
-    s = check_ws(workspace, workspace_bytes, pattern_loss_ws(layers, n_layers));
+    s = check_ws(workspace, workspace_bytes, pattern_loss_min_ws(layers, n_layers));
     if (s != IC_OK) return s;
-    return run_pattern_loss(layers, n_layers, full_mask, O_ref, idx_cache, loss, workspace, (hipStream_t)stream);
+    return run_pattern_loss(layers, n_layers, full_mask, O_ref, idx_cache, loss, workspace, workspace_bytes, (hipStream_t)stream);
 }
 
 size_t ic_greedy_search_forward_workspace(const ic_layer *layers, int32_t n_layers)
@@ -1094,17 +1116,20 @@ ic_status ic_greedy_search_forward(const ic_layer *layers, int32_t n_layers, int
     ic_status s = check_loss_args(layers, n_layers, O_ref, idx_cache);
     if (s != IC_OK) return s;
     if (!full_mask) return fail(IC_ERR_NULL, "full_mask must not be NULL");
-    s = check_ws(workspace, workspace_bytes, ic_greedy_search_forward_workspace(layers, n_layers));
+    const size_t cands_bytes = align_up((size_t)n_layers * sizeof(double));
+    s = check_ws(workspace, workspace_bytes, cands_bytes + pattern_loss_min_ws(layers, n_layers));
     if (s != IC_OK) return s;
     hipStream_t st = (hipStream_t)stream;
-    double *dev_losses = (double *)((char *)workspace + pattern_loss_ws(layers, n_layers));
+    double *dev_losses = (double *)workspace;
+    void *const loss_ws = (char *)workspace + cands_bytes;
+    const size_t loss_bytes = workspace_bytes - cands_bytes;
     return greedy_core(n_layers, n_shared, n_blocks, full_mask, order, loss_curve,
                        [&](uint8_t *m, const std::vector<int32_t> &cands, std::vector<double> &out) {
                            // one forward pass of the whole stack per candidate, all on the stream;
                            // then the host needs the losses to choose: one synchronisation per search step
                            for (size_t i = 0; i < cands.size(); ++i) {
                                m[cands[i]] = 0;
-                               ic_status r = run_pattern_loss(layers, n_layers, m, O_ref, idx_cache, dev_losses + i, workspace, st);
+                               ic_status r = run_pattern_loss(layers, n_layers, m, O_ref, idx_cache, dev_losses + i, loss_ws, loss_bytes, st);
                                m[cands[i]] = 1;
                                if (r != IC_OK) return r;
                            }

@@ -154,7 +154,7 @@ def test_forward_stack_argument_errors(ic):
     arr[1].q = None                                                  # a Shared layer may omit q,k,w ...
     arr[0].q = None                                                  # ... a Full layer may not
     assert L.ic_forward_stack(arr, 2, bytes([1, 0]), p, p, ws, None) == S.ERR_NULL
-    # workspace need does not grow with the number of Shared layers (one index buffer, one strip)
+    # one layer never needs more than two of them (here one strip of scores is the largest need of either)
     assert L.ic_forward_stack_workspace(arr, 1) <= ws
 
 
