@@ -1055,6 +1055,7 @@ __global__ __launch_bounds__(512, 2) void attn_dense_kernel(AttnArgs a, DenseArg
     const int R0 = ((int)gridDim.x - 1 - (int)blockIdx.x) * kDenseRows;   // longest first
     if (R0 >= n_rows) return;
     const int nt = (da.pos0 + min(R0 + kDenseRows - 1, n_rows - 1) / a.H_q) / kDenseTile + 1;
+    const int t_edge = (da.pos0 + R0 / a.H_q + 1) / kDenseTile;      // first tile with keys that some row does not see
 
     if (tid < kDenseRows) mref[tid] = mnew[tid] = mnew[kDenseRows + tid] = -INFINITY;
     if (tid < 3) moved[tid] = 0;
@@ -1249,8 +1250,8 @@ __global__ __launch_bounds__(512, 2) void attn_dense_kernel(AttnArgs a, DenseArg
         // an infinity or NaN in a later position (an unused one, another token's) would reach its output.  A key with one has
         // no finite score, which the scores waves look for in these tiles; from there on V enters the product with infinities
         // and NaN as 0.  (Done to every such tile without the look, four layers of 3 x 1021 rows took 600 us instead of
-        // 575.)  A row that does see such a key has its score, and so its p, from the same elements.
-        const int t_edge = (da.pos0 + R0 / a.H_q + 1) / kDenseTile;
+        // 575.)  A row that does see such a key is all NaN from its p if the score is +inf or NaN; if it is -inf, p is 0 and
+        // only the columns in which the key is not finite are NaN (0 times infinity): they are set when the rows leave.
         bf16x8 pa[2][2];
         s16x4 vq[2][4][2];
         auto finite_v = [&]() __attribute__((always_inline)) {
@@ -1344,6 +1345,22 @@ __global__ __launch_bounds__(512, 2) void attn_dense_kernel(AttnArgs a, DenseArg
     }
     __syncthreads();
     __bf16 *out = (__bf16 *)a.O + ((int64_t)b * a.Tq * a.H_q + R0) * D_V;
+    if (__builtin_amdgcn_readfirstlane(moved[2])) {       // (rare: see finite_v above)
+        const unsigned short *v0 = (const unsigned short *)a.KV + (PG && a.pv.page_table ? 0 : (int64_t)b * a.Lk * a.row_elems) + 8 * lane;
+        for (int row = wave; row < kDenseRows && R0 + row < n_rows; row += 8) {
+            u32x4 o = *(const u32x4 *)(tbuf + row * OSTR + 16 * lane);
+            for (int key = t_edge * kDenseTile; key <= da.pos0 + (R0 + row) / a.H_q; ++key) {
+                const u32x4 v = *(const u32x4 *)(v0 + (PG && a.pv.page_table ? paged_row(a.pv, b, key) : (int64_t)key) * a.row_elems);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    if ((v[e] & 0x7f80u) == 0x7f80u) o[e] |= 0x7fc0u;
+                    if ((v[e] & 0x7f800000u) == 0x7f800000u) o[e] |= 0x7fc00000u;
+                }
+            }
+            *(u32x4 *)(out + (int64_t)row * D_V + 8 * lane) = o;
+        }
+        return;
+    }
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
         const int row = 8 * j + wave;

@@ -142,3 +142,54 @@ def test_shared_cache_longer_than_the_full_layers(oracle, B, Tq, pos0, lk_full, 
     lb = synth.bits_layer(full)
     want, _ = oracle.sparse_attn(lb["Q"], lb["KV"], sel, 512, 0, 1 / 24.0)
     parity.check_attn(outs[0].float().cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("col", [0, 300, 511, 540])
+@pytest.mark.parametrize("B, Tq, H_q, row, page", [(1, 300, 32, 199, 0), (1, 300, 32, 224, 0), (1, 300, 32, 3, 0), (2, 200, 32, 198, 64),
+                                                   (1, 500, 20, 333, 0), (1, 100, 1, 70, 0)])
+def test_minus_infinity_in_a_key_that_a_row_sees(oracle, B, Tq, H_q, row, page, col):
+    """A key whose score is -inf has weight 0 like everywhere else: 0 times its infinite element is NaN in that column of the
+    rows that see it (none for an element behind the values), and the other columns are those without the key."""
+    import paper_2603_12201_amd as ic
+    print("[case] dense, -inf in column %d of row %d, B=%d Tq=%d H_q=%d page=%d" % (col, row, B, Tq, H_q, page), flush=True)
+    cfg = synth.config("c2", B=B, Tq=Tq, Lk=Tq, q_pos0=0, H_q=H_q, k_sel=512, row_elems=576, H_I=4, seed=row + col)
+    t = synth.indexer_layer(cfg, 0)
+    t.update(synth.attn_layer(cfg, 0))
+    t["Q"][..., col] = 1.0
+    want_kv = t["KV"].clone()
+    want_kv[:, row] = 0
+    t["KV"][:, row, col] = float("-inf")
+    g = {n: v.cuda() for n, v in t.items()}
+    pc = None
+    if page:
+        n = -(-Tq // page)
+        table = torch.arange(B * n, dtype=torch.int32).flip(0).view(B, n)
+        for name in ("k", "KV"):
+            pool = torch.full((B * n * page, t[name].shape[-1]), 50.0, dtype=torch.bfloat16, device="cuda")
+            for b in range(B):
+                for p in range(n):
+                    src = g[name][b, p * page:(p + 1) * page]
+                    pool[int(table[b, p]) * page:int(table[b, p]) * page + src.shape[0]] = src
+            g[name] = pool
+        pc = ic.paged_cache(page_table=table.cuda(), page_size=page)
+    out = torch.empty((B, Tq, H_q, 512), dtype=torch.bfloat16, device="cuda")
+    arr = ic.make_layers([g], 512, 0, 512, 0, 1 / 24.0, [out], Lk=Tq if page else None)
+    idx = torch.empty((B, Tq, 512), dtype=torch.int32, device="cuda")
+    ws = torch.empty(max(256, ic.forward_stack_workspace(arr)), dtype=torch.uint8, device="cuda")
+    if page:
+        ic.forward_stack_paged(arr, [True], pc, idx, ws)
+    else:
+        ic.forward_stack(arr, [True], idx, ws)
+    got = out.float().cpu()
+    nan = torch.isnan(got)
+    expect = torch.zeros_like(nan)
+    if col < 512:
+        expect[:, row:, :, col] = True
+    assert torch.equal(nan, expect)
+    sel = idx.cpu().numpy().copy()
+    sel[sel == row] = -1
+    lb = synth.bits_layer(dict(t, KV=want_kv))
+    want, _ = oracle.sparse_attn(lb["Q"], lb["KV"], sel, 512, 0, 1 / 24.0)
+    want[expect.numpy().reshape(want.shape)] = 0
+    got[expect] = 0
+    parity.check_attn(got.numpy(), want)
