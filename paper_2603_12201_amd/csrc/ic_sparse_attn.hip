@@ -929,7 +929,7 @@ __global__ __launch_bounds__(256, 1) void attn_slab_kernel(AttnArgs a, RestArgs 
 // roles (one of each per SIMD, and about as many matrix clocks for either: 576 and 512 per tile):
 //   scores   waves 0-3, (rh, kh) = 32 rows x 16 keys of tile t: the tile as A operand of v_mfma_f32_16x16x32_bf16, every
 //            read of it used for two row blocks, Q in registers; softmax against a reference per row that moves only when
-//            a score exceeds it by 2^kDenseLog2; P to LDS.  The operand ring runs on into the next tile
+//            a score exceeds it by 2^kLazyLog2; P to LDS.  The operand ring runs on into the next tile
 //   output   waves 4-7, value columns 128 w .. 128 w + 127 of all 64 rows, of tile t - 2, transposed (O^T += V^T P^T on
 //            v_mfma_f32_32x32x16_bf16, V through the transpose read): a lane then owns one row of O, so that factors and
 //            row sums are a lane's own and four neighbouring columns leave together.  Its operands are in registers when
@@ -1020,7 +1020,6 @@ template <int N, typename F> __device__ __forceinline__ void unroll(F f)        
 constexpr int kDenseRows = 64;               // (query, head) rows per workgroup
 constexpr int kDenseTile = 32;               // keys per tile
 constexpr int kDenseRing = 4;
-constexpr float kDenseLog2 = 60.f;           // how far a score may exceed its row's reference (bf16 and fp32 hold 2^127)
 
 // tile row (within 16) behind result row r of S^T
 __device__ __forceinline__ int dense_row(int r) { return 8 * (r >> 3) + 2 * (r & 3) + ((r >> 2) & 1); }
@@ -1141,12 +1140,12 @@ __global__ __launch_bounds__(512, 2) void attn_dense_kernel(AttnArgs a, DenseArg
                 m_use[r] = m_c[r];
                 mx[r] = fmaxf(fmaxf(s4[r][0], s4[r][1]), fmaxf(s4[r][2], s4[r][3])) * a.scale_log2e;
             }
-            if (__ballot(mx[0] > m_c[0] + kDenseLog2 || mx[1] > m_c[1] + kDenseLog2) != 0ull) {
+            if (__ballot(mx[0] > m_c[0] + kLazyLog2 || mx[1] > m_c[1] + kLazyLog2) != 0ull) {
                 // rare: some row's first keys, or a score far above all before it
 #pragma unroll
                 for (int r = 0; r < 2; ++r) {
                     mx[r] = xmax16_32(mx[r]);
-                    m_use[r] = mx[r] > m_c[r] + kDenseLog2 ? mx[r] : m_c[r];
+                    m_use[r] = mx[r] > m_c[r] + kLazyLog2 ? mx[r] : m_c[r];
                     if (g == 0) mnew[kDenseRows * kh + 32 * rh + 16 * r + l16] = m_use[r];
                 }
                 moved[t & 1] = 1;

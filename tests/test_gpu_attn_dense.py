@@ -193,3 +193,29 @@ def test_minus_infinity_in_a_key_that_a_row_sees(oracle, B, Tq, H_q, row, page, 
     want[expect.numpy().reshape(want.shape)] = 0
     got[expect] = 0
     parity.check_attn(got.numpy(), want)
+
+
+@pytest.mark.parametrize("power", [0, 60, 100])
+@pytest.mark.parametrize("jump", [6.0, 40.0, 59.0, 90.0])
+def test_large_values_behind_a_rising_score(oracle, jump, power):
+    """Scores that rise by 2^jump behind the first tile with values of 2^power: no partial sum leaves the range of fp32."""
+    import paper_2603_12201_amd as ic
+    B, Tq, H_q, scale = 1, 200, 32, 1.0
+    print("[case] dense, scores rise by 2^%g, values of 2^%d" % (jump, power), flush=True)
+    cfg = synth.config("c2", B=B, Tq=Tq, Lk=Tq, q_pos0=0, H_q=H_q, k_sel=512, row_elems=576, H_I=4, seed=int(jump))
+    t = synth.indexer_layer(cfg, 0)
+    t.update(synth.attn_layer(cfg, 0))
+    t["Q"].zero_()
+    t["Q"][..., 575] = 1.0
+    t["KV"][..., 575] = torch.linspace(0, 0.5, Tq).to(torch.bfloat16)
+    t["KV"][:, 40:, 575] = jump * 0.6931472
+    g = {n: v.cuda() for n, v in t.items()}
+    g["KV"][..., :512] *= 2.0 ** power
+    out = torch.empty((B, Tq, H_q, 512), dtype=torch.bfloat16, device="cuda")
+    arr = ic.make_layers([g], 512, 0, 512, 0, scale, [out])
+    idx = torch.empty((B, Tq, 512), dtype=torch.int32, device="cuda")
+    ic.forward_stack(arr, [True], idx, torch.empty(max(256, ic.forward_stack_workspace(arr)), dtype=torch.uint8, device="cuda"))
+    got = out.double().cpu() * 2.0 ** -power
+    lb = synth.bits_layer(t)
+    want, _ = oracle.sparse_attn(lb["Q"], lb["KV"], idx.cpu().numpy(), 512, 0, scale)
+    parity.check_attn(got.float().numpy(), want)
