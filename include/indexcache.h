@@ -108,11 +108,21 @@ size_t ic_sparse_attn_workspace(const ic_attn_desc *desc);
  *   0 <= idx_m < Lk (others are skipped), p = softmax(z), O[b,t,h,:] = sum_m p_m KV[b,idx_m,v_off:+d_v].
  *   O   [B,Tq,H_q,d_v] bf16 out (a row with no valid entry gives zeros)
  *   lse [B,Tq,H_q] fp32 out, nullable: log sum_m exp(z_m) (-inf for an empty row)
- * A workspace of B * k_sel / 4 + 256 bytes or more (also where ic_sparse_attn_workspace() asks for none) lets long causal
- * selections run faster: leading rows that hold whole prefixes are then counted and share their KV rows.
+ * Where ic_sparse_attn_workspace() is 0 a workspace is neither looked at nor written.
  */
 ic_status ic_sparse_attn(const ic_attn_desc *desc, const void *Q, const void *KV, const int32_t *idx,
                          void *O, float *lse, void *workspace, size_t workspace_bytes, void *stream);
+
+/*
+ * The same computation for selections whose leading rows may be whole prefixes, as a causal top-k of the last Tq of Lk
+ * positions has them (row t < k_sel - (Lk - Tq) holds 0 .. Lk - Tq + t, then -1s): such rows are counted on the device and
+ * share their KV rows, the others run as in ic_sparse_attn, whatever idx holds.  The results agree with ic_sparse_attn's to
+ * the rounding of sums in another order.  The counts live in the workspace while the call runs: it has to hold
+ * ic_sparse_attn_lead_workspace() bytes and must not be shared with calls that may run at the same time.
+ */
+size_t ic_sparse_attn_lead_workspace(const ic_attn_desc *desc);
+ic_status ic_sparse_attn_lead(const ic_attn_desc *desc, const void *Q, const void *KV, const int32_t *idx,
+                              void *O, float *lse, void *workspace, size_t workspace_bytes, void *stream);
 
 /*
  * ic_sparse_attn for callers that cannot allocate device memory (code under HIP graph capture, tight

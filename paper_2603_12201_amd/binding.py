@@ -65,6 +65,10 @@ def lib():
         L.ic_sparse_attn.argtypes = [C.POINTER(AttnDesc), vp, vp, vp, vp, vp, vp, sz, vp]
         L.ic_calibrate.restype = C.c_int
         L.ic_calibrate.argtypes = [i32, vp, vp, vp, C.c_int64, C.c_int64, i32, i32, vp]
+        L.ic_sparse_attn_lead_workspace.restype = sz
+        L.ic_sparse_attn_lead_workspace.argtypes = [C.POINTER(AttnDesc)]
+        L.ic_sparse_attn_lead.restype = C.c_int
+        L.ic_sparse_attn_lead.argtypes = [C.POINTER(AttnDesc), vp, vp, vp, vp, vp, vp, sz, vp]
         L.ic_sparse_attn_static.restype = C.c_int
         L.ic_sparse_attn_static.argtypes = [C.POINTER(AttnDesc), vp, vp, vp, vp, vp, vp]
         L.ic_forward_stack_workspace.restype = sz
@@ -225,15 +229,25 @@ def sparse_attn_workspace(desc):
 
 
 def sparse_attn(Q, KV, idx, d_v, v_off, sm_scale, want_lse=False, workspace=None, stream=None, out=None):
-    """ic_sparse_attn: returns O [B,Tq,H_q,d_v] bf16 (and lse [B,Tq,H_q] fp32 if want_lse)."""
+    """ic_sparse_attn: returns O [B,Tq,H_q,d_v] bf16 (and lse [B,Tq,H_q] fp32 if want_lse).
+
+    Long selections that may be causal run through ic_sparse_attn_lead, with a few kilobytes of its own allocated here on
+    the call's stream; an empty `workspace` asks for ic_sparse_attn on every row."""
     import torch
     d = attn_desc(Q, KV, idx, d_v, v_off, sm_scale)
-    if workspace is None:
-        workspace = _workspace(max(sparse_attn_workspace(d), d.B * d.k_sel // 4 + 256), Q)
+    fn, need = lib().ic_sparse_attn, sparse_attn_workspace(d)
+    # `workspace` is not used where ic_sparse_attn needs none, so other streams may be using it
+    may = need == 0 and (workspace is None or workspace.numel() > 0) and (stream is None or isinstance(stream, torch.cuda.Stream))
+    lead = int(lib().ic_sparse_attn_lead_workspace(C.byref(d))) if may else 0
+    if lead:
+        fn = lib().ic_sparse_attn_lead
+        with torch.cuda.stream(stream):                                  # (None: the current one)
+            workspace = _workspace(lead, Q)
+    elif workspace is None:
+        workspace = _workspace(need, Q)
     O = out if out is not None else torch.empty((d.B, d.Tq, d.H_q, d_v), dtype=torch.bfloat16, device=Q.device)
     lse = torch.empty((d.B, d.Tq, d.H_q), dtype=torch.float32, device=Q.device) if want_lse else None
-    _check(lib().ic_sparse_attn(C.byref(d), _ptr(Q), _ptr(KV), _ptr(idx), _ptr(O), _ptr(lse),
-                                _ptr(workspace), workspace.numel(), _stream(stream)))
+    _check(fn(C.byref(d), _ptr(Q), _ptr(KV), _ptr(idx), _ptr(O), _ptr(lse), _ptr(workspace), workspace.numel(), _stream(stream)))
     return (O, lse) if want_lse else O
 
 

@@ -174,6 +174,7 @@ void attn_splits(const ic_attn_desc *d, int n_layers, size_t ws_bytes, int *n_sp
     *n_splits = (int)((tiles + best_per - 1) / best_per);
 }
 
+// 0: the launch writes nothing into a workspace
 size_t attn_ws_bytes(const ic_attn_desc *d, int n_layers = 1)
 {
     const size_t ns = (size_t)attn_max_splits(d, n_layers);
@@ -387,6 +388,17 @@ size_t lead_bytes(const ic_attn_desc *d, int n_tensors)
     return n ? align_up((size_t)n_tensors * d->B * lead_chunks(n) * sizeof(int32_t)) : 0;
 }
 
+// Partials of the rows behind the candidates where they are split over the chip on their own.
+size_t lead_tail_bytes(const ic_attn_desc *d)
+{
+    const int n = lead_queries(d);
+    if (n == 0 || n == d->Tq || d->Tq - n >= 256) return 0;
+    ic_attn_desc t = *d;
+    t.B = 1;
+    t.Tq = d->Tq - n;
+    return attn_ws_bytes(&t);
+}
+
 // Counts of n_tensors index tensors into lead.
 ic_status count_lead(const ic_attn_desc *d, const int32_t *const *idx, int n_tensors, int32_t *lead, hipStream_t st)
 {
@@ -519,13 +531,6 @@ ic_status run_attn_layers(const ic_layer *layers, int n_layers, const int32_t *i
         }
         return IC_OK;
     }
-    if (const size_t lb = !pc && n_layers == 1 && c.pos0 < 0 ? lead_bytes(d, 1) : 0) {
-        if (ws && ws_bytes >= lb) {
-            ic_status s = count_lead(d, &idx, 1, (int32_t *)ws, st);
-            if (s != IC_OK) return s;
-            return run_attn_lead(layers, idx, (const int32_t *)ws, (const int32_t *)ws, true, lse, (char *)ws + lb, ws_bytes - lb, st);
-        }
-    }
     attn_splits(d, n_layers, ws_bytes, &a.n_splits, &a.split_len);
     if (a.n_splits > 1) {
         const size_t nq = (size_t)n_layers * d->B * d->Tq;
@@ -545,8 +550,7 @@ ic_status run_attn_layers(const ic_layer *layers, int n_layers, const int32_t *i
     return IC_OK;
 }
 
-ic_status run_attn(const ic_attn_desc *d, const void *Q, const void *KV, const int32_t *idx, void *O, float *lse,
-                   void *ws, size_t ws_bytes, hipStream_t st, const ic_paged_cache *pc = nullptr)
+ic_layer attn_layer(const ic_attn_desc *d, const void *Q, const void *KV, void *O)
 {
     ic_layer l;
     memset(&l, 0, sizeof l);
@@ -554,6 +558,13 @@ ic_status run_attn(const ic_attn_desc *d, const void *Q, const void *KV, const i
     l.Q = Q;
     l.KV = KV;
     l.O = O;
+    return l;
+}
+
+ic_status run_attn(const ic_attn_desc *d, const void *Q, const void *KV, const int32_t *idx, void *O, float *lse,
+                   void *ws, size_t ws_bytes, hipStream_t st, const ic_paged_cache *pc = nullptr)
+{
+    const ic_layer l = attn_layer(d, Q, KV, O);
     return run_attn_layers(&l, 1, idx, lse, ws, ws_bytes, st, pc, kUnknown);
 }
 
@@ -585,6 +596,31 @@ size_t ic_sparse_attn_workspace(const ic_attn_desc *d)
 {
     if (check_attn(d) != IC_OK) return 0;
     return attn_ws_bytes(d);
+}
+
+size_t ic_sparse_attn_lead_workspace(const ic_attn_desc *d)
+{
+    if (check_attn(d) != IC_OK) return 0;
+    const size_t lb = lead_bytes(d, 1);
+    return lb ? lb + align_up(lead_tail_bytes(d)) : attn_ws_bytes(d);
+}
+
+ic_status ic_sparse_attn_lead(const ic_attn_desc *d, const void *Q, const void *KV, const int32_t *idx, void *O,
+                              float *lse, void *workspace, size_t workspace_bytes, void *stream)
+{
+    ic_status s = check_attn(d);
+    if (s != IC_OK) return s;
+    if (!Q || !KV || !idx || !O) return fail(IC_ERR_NULL, "Q, KV, idx and O must not be NULL");
+    s = check_ws(workspace, workspace_bytes, ic_sparse_attn_lead_workspace(d));
+    if (s != IC_OK) return s;
+    hipStream_t st = (hipStream_t)stream;
+    const size_t lb = lead_bytes(d, 1);
+    if (lb == 0) return run_attn(d, Q, KV, idx, O, lse, workspace, workspace_bytes, st);
+    int32_t *const lead = (int32_t *)workspace;
+    s = count_lead(d, &idx, 1, lead, st);
+    if (s != IC_OK) return s;
+    const ic_layer l = attn_layer(d, Q, KV, O);
+    return run_attn_lead(&l, idx, lead, lead, true, lse, (char *)workspace + lb, workspace_bytes - lb, st);
 }
 
 ic_status ic_sparse_attn(const ic_attn_desc *d, const void *Q, const void *KV, const int32_t *idx, void *O,

@@ -97,3 +97,34 @@ def test_similarity_of_layers_with_leading_rows(oracle):
             cs = torch.where((na == 0) & (nb == 0), torch.ones_like(na), (a * b).sum(-1) / (na * nb).clamp_min(1e-300))
             assert abs(S[i, j] - cs.mean().item()) < 2e-4
         assert S[i, i] == 1.0 and all(S[i, j] == 0.0 for j in range(i + 1, 3))
+
+
+@pytest.mark.parametrize("B, Tq, k", [(1, 400, 1024), (1, 700, 512), (2, 600, 512)])
+def test_a_workspace_that_is_not_needed_is_not_written(oracle, B, Tq, k):
+    """Where ic_sparse_attn needs no workspace the caller may be using it elsewhere, on any stream."""
+    import ctypes as C
+    import paper_2603_12201_amd as ic
+    print("[case] unneeded workspace B=%d Tq=%d k=%d" % (B, Tq, k), flush=True)
+    cfg = synth.config("c2", B=B, Tq=Tq, Lk=Tq, q_pos0=0, H_q=32, k_sel=k, row_elems=576, H_I=4, seed=Tq + k)
+    t = synth.attn_layer(cfg, 0)
+    g = {n: v.cuda() for n, v in t.items()}
+    host = _selection(B, Tq, Tq, k, [], Tq)
+    idx = torch.from_numpy(host).cuda()
+    lb = synth.bits_layer(t)
+    want, _ = oracle.sparse_attn(lb["Q"], lb["KV"], host, 512, 0, 1 / 24.0)
+    ws = torch.full((64 << 20,), 0xA5, dtype=torch.uint8, device="cuda")
+    d = ic.AttnDesc(B, Tq, Tq, 32, 576, 512, 0, 576, k, 1 / 24.0)
+    L = ic.lib()
+    assert L.ic_sparse_attn_workspace(C.byref(d)) == 0
+    for where in ("binding", "aligned", "misaligned"):
+        out = torch.full((B, Tq, 32, 512), 7.0, dtype=torch.bfloat16, device="cuda")
+        if where == "binding":
+            ic.sparse_attn(g["Q"], g["KV"], idx, 512, 0, 1 / 24.0, workspace=ws, out=out)
+        else:
+            p = ws.data_ptr() + (6 if where == "misaligned" else 0)
+            st = L.ic_sparse_attn(C.byref(d), g["Q"].data_ptr(), g["KV"].data_ptr(), idx.data_ptr(), out.data_ptr(), None, p,
+                                  ws.numel() - 256, torch.cuda.current_stream().cuda_stream)
+            assert st == ic.Status.OK
+        torch.cuda.synchronize()
+        assert bool((ws == 0xA5).all()), where
+        parity.check_attn(out.float().cpu().numpy(), want)

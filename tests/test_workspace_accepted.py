@@ -36,3 +36,18 @@ def test_pattern_loss_and_greedy_search_need_one_layer(n, Tq, Lk, k):
     greedy = lambda b: L.ic_greedy_search_forward(arr, n, n, 1, refs, one, buf, None, None, one, b, None)   # n Shared layers: one too many
     assert greedy(need + _up(8 * n)) == S.ERR_SHAPE
     assert greedy(need + _up(8 * n) - 256) == S.ERR_WORKSPACE
+
+
+def test_lead_entry_point_checks_its_workspace():
+    import paper_2603_12201_amd as ic
+    L, S = ic.lib(), ic.Status
+    one = C.c_void_p(4096)
+    for Tq, k in ((700, 512), (2100, 2048), (100, 256)):                   # a tail split over the chip; no leading rows looked for
+        d = ic.AttnDesc(1, Tq, Tq, 32, 576, 512, 0, 576, k, 1 / 24.0)
+        need = L.ic_sparse_attn_lead_workspace(C.byref(d))
+        assert need > 0 and need % 256 == 0
+        call = lambda w, n: L.ic_sparse_attn_lead(C.byref(d), one, one, one, one, None, w, n, None)
+        assert call(None, need) == S.ERR_WORKSPACE and call(C.c_void_p(4096 + 8), need) == S.ERR_WORKSPACE
+        assert call(one, need - 1) == S.ERR_WORKSPACE
+        assert L.ic_sparse_attn_lead(C.byref(d), None, one, one, one, None, one, need, None) == S.ERR_NULL
+    assert L.ic_sparse_attn_lead_workspace(None) == 0
