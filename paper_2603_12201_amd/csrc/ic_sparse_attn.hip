@@ -943,79 +943,18 @@ __global__ __launch_bounds__(256, 1) void attn_slab_kernel(AttnArgs a, RestArgs 
 // LDS layout as in the row-slab form (rows 1184 bytes apart, transpose reads over rows two apart); the A operand presents
 // the tile rows in the order dense_row(), so that the four scores of a lane are neighbours in P.  Q and O pass through the
 // tile ring.
-// Registers.  The accumulation half of the register file is managed by hand and the compiler sees none of it: Q's first 16
-// contraction steps (scores) or the output accumulators (output) in a0 - a127.  Every statement below that touches it lists
-// all of it as overwritten, so the compiler keeps nothing there.  It does not see matrix instructions in these statements
-// either: a result is read by something else only behind enough no-ops, and operands in vector registers come from loads.
-#define IC_A10(n) "a" #n "0", "a" #n "1", "a" #n "2", "a" #n "3", "a" #n "4", "a" #n "5", "a" #n "6", "a" #n "7", "a" #n "8", "a" #n "9"
-#define IC_ACC_ALL                                                                                                             \
-    IC_A10(), IC_A10(1), IC_A10(2), IC_A10(3), IC_A10(4), IC_A10(5), IC_A10(6), IC_A10(7), IC_A10(8), IC_A10(9), IC_A10(10),    \
-        IC_A10(11), "a120", "a121", "a122", "a123", "a124", "a125", "a126", "a127"
+// Registers.  The two roles need 249 of the 256 that a wave may have: Q of 32 rows takes 144 in the scores waves, the output
+// accumulators 128 in the others.  The compiler places all of it: state that it is not told of (registers named in asm
+// statements) is only safe as long as it happens to put no value of its own there.
 
-namespace acc {
-template <int BLOCK> __device__ __forceinline__ void mma_o(bf16x8 x, bf16x8 y)          // output block += x y
-{
-    asm volatile("v_mfma_f32_32x32x16_bf16 a[%2:%3], %0, %1, a[%2:%3]" ::"v"(x), "v"(y), "n"(16 * BLOCK), "n"(16 * BLOCK + 15) : IC_ACC_ALL);
-}
-template <int I> __device__ __forceinline__ void mma_s(f32x4 &c, bf16x8 x)              // c = x Q[I] (of steps 0, 1), c += x Q[I]
-{
-    if constexpr (I < 2)
-        asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, a[%2:%3], 0" : "=&v"(c) : "v"(x), "n"(4 * I), "n"(4 * I + 3) : IC_ACC_ALL);
-    else
-        asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, a[%2:%3], %0" : "+v"(c) : "v"(x), "n"(4 * I), "n"(4 * I + 3) : IC_ACC_ALL);
-}
-__device__ __forceinline__ void mma_s_v(f32x4 &c, bf16x8 x, bf16x8 q)                   // c += x q, q in vector registers
-{
-    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(x), "v"(q) : IC_ACC_ALL);
-}
-template <int I> __device__ __forceinline__ void set_q(bf16x8 x)
-{
-    const u32x4 v = __builtin_bit_cast(u32x4, x);
-    asm volatile("v_accvgpr_write_b32 a[%4], %0\n\tv_accvgpr_write_b32 a[%4+1], %1\n\tv_accvgpr_write_b32 a[%4+2], %2\n\t"
-                 "v_accvgpr_write_b32 a[%4+3], %3" ::"v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3]), "n"(4 * I) : IC_ACC_ALL);
-}
-__device__ __forceinline__ void zero_o()
-{
-    asm volatile(".irp h,0,1,2,3,4,5,6,7,8,9,10,11,12,13,14,15\n\t"
-                 ".irp b,0,16,32,48,64,80,96,112\n\t"
-                 "v_accvgpr_write_b32 a[\\b+\\h], 0\n\t"
-                 ".endr\n\t"
-                 ".endr" ::: IC_ACC_ALL);
-}
-// blocks 0 - 3 times f0, blocks 4 - 7 times f1
-__device__ __forceinline__ void rescale_o(float f0, float f1)
-{
-    float x, y;
-    asm volatile("s_nop 15\n\t"
-                 ".irp b,0,16,32,48\n\t"
-                 ".irp h,0,1,2,3,4,5,6,7,8,9,10,11,12,13,14,15\n\t"
-                 "v_accvgpr_read_b32 %0, a[\\b+\\h]\n\t"
-                 "v_accvgpr_read_b32 %1, a[64+\\b+\\h]\n\t"
-                 "v_mul_f32_e32 %0, %0, %2\n\t"
-                 "v_mul_f32_e32 %1, %1, %3\n\t"
-                 "v_accvgpr_write_b32 a[\\b+\\h], %0\n\t"
-                 "v_accvgpr_write_b32 a[64+\\b+\\h], %1\n\t"
-                 ".endr\n\t"
-                 ".endr\n\t"
-                 "s_nop 7"
-                 : "=&v"(x), "=&v"(y)
-                 : "v"(f0), "v"(f1)
-                 : IC_ACC_ALL);
-}
-template <int I> __device__ __forceinline__ float get_o()
-{
-    float x;
-    asm volatile("v_accvgpr_read_b32 %0, a[%1]" : "=v"(x) : "n"(I) : IC_ACC_ALL);
-    return x;
-}
-template <int N, typename F> __device__ __forceinline__ void unroll(F f)                // f(integral_constant 0 .. N-1)
+// f(integral_constant 0 .. N-1), in order
+template <int N, typename F> __device__ __forceinline__ void unroll(F f)
 {
     if constexpr (N > 0) {
         unroll<N - 1>(f);
         f(std::integral_constant<int, N - 1>{});
     }
 }
-} // namespace acc
 
 constexpr int kDenseRows = 64;               // (query, head) rows per workgroup
 constexpr int kDenseTile = 32;               // keys per tile
@@ -1028,7 +967,7 @@ template <bool PG>
 __global__ __launch_bounds__(512, 2) void attn_dense_kernel(AttnArgs a, DenseArgs da)
 {
     constexpr int D_QK = 576, D_V = 512;
-    constexpr int KS = D_QK / 32, KSA = 16;               // contraction steps; with Q in accumulation registers
+    constexpr int KS = D_QK / 32;                         // contraction steps
     constexpr int ROWB = D_QK * 2 + kSlabPad, TBUFB = kDenseTile * ROWB;
     constexpr int PSTR = kDenseTile * 2 + 16, PBUFB = kDenseRows * PSTR;
     constexpr int OSTR = D_V * 2 + 16;
@@ -1080,16 +1019,12 @@ __global__ __launch_bounds__(512, 2) void attn_dense_kernel(AttnArgs a, DenseArg
             store_q(raw);
         }
         __syncthreads();
-        bf16x8 qv[KS - KSA][2];
+        bf16x8 qv[KS][2];
         const unsigned char *qr = qb + (32 * rh + l16) * ROWB + 16 * g;
-        acc::unroll<2 * KSA>([&](auto i_c) __attribute__((always_inline)) {
-            constexpr int i = decltype(i_c)::value;
-            acc::set_q<i>(*(const bf16x8 *)(qr + 16 * (i & 1) * ROWB + 64 * (i >> 1)));
-        });
 #pragma unroll
-        for (int ks = KSA; ks < KS; ++ks)
+        for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
-            for (int r = 0; r < 2; ++r) qv[ks - KSA][r] = *(const bf16x8 *)(qr + 16 * r * ROWB + 64 * ks);
+            for (int r = 0; r < 2; ++r) qv[ks][r] = *(const bf16x8 *)(qr + 16 * r * ROWB + 64 * ks);
         __syncthreads();
 
         int lim[2];                                       // last key the lane's rows see
@@ -1106,21 +1041,16 @@ __global__ __launch_bounds__(512, 2) void attn_dense_kernel(AttnArgs a, DenseArg
         auto scores = [&](int t) __attribute__((always_inline)) {
             const unsigned char *tb = tbuf + (t & (kDenseRing - 1)) * TBUFB + ka_off;
             const unsigned char *tb1 = tbuf + ((t + 1) & (kDenseRing - 1)) * TBUFB + ka_off;
-            acc::unroll<KS>([&](auto ks_c) __attribute__((always_inline)) {
+            unroll<KS>([&](auto ks_c) __attribute__((always_inline)) {
                 constexpr int ks = decltype(ks_c)::value;
-                if constexpr (ks < KSA) {
-                    acc::mma_s<2 * ks>(s4[0], ka[ks % RING]);
-                    acc::mma_s<2 * ks + 1>(s4[1], ka[ks % RING]);
-                } else {
-                    acc::mma_s_v(s4[0], ka[ks % RING], qv[ks - KSA][0]);
-                    acc::mma_s_v(s4[1], ka[ks % RING], qv[ks - KSA][1]);
-                }
+#pragma unroll
+                for (int r = 0; r < 2; ++r)
+                    s4[r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[ks % RING], qv[ks][r], ks == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : s4[r], 0, 0, 0);
                 ka[ks % RING] = ks + RING < KS ? *(const bf16x8 *)(tb + 64 * (ks + RING)) : *(const bf16x8 *)(tb1 + 64 * (ks + RING - KS));
                 __builtin_amdgcn_sched_barrier(0);
             });
         };
         auto softmax = [&](int t) __attribute__((always_inline)) {
-            asm volatile("s_nop 15" : "+v"(s4[0]), "+v"(s4[1]));
             // lane: row l16 of either block, keys dense_row(4 g + i)
             const int key0 = kDenseTile * t + 16 * kh;
             if (key0 + 15 > lim0) {
@@ -1231,7 +1161,13 @@ __global__ __launch_bounds__(512, 2) void attn_dense_kernel(AttnArgs a, DenseArg
             load(0);
             store_q(raw);
         }
-        acc::zero_o();
+        f32x16 o_acc[2][4];                               // [rows 32 r ..][columns 32 nb ..]
+#pragma unroll
+        for (int r = 0; r < 2; ++r)
+#pragma unroll
+            for (int nb = 0; nb < 4; ++nb)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) o_acc[r][nb][e] = 0.f;
         store(0, 0, 9);
         load(1);
         __syncthreads();
@@ -1280,12 +1216,13 @@ __global__ __launch_bounds__(512, 2) void attn_dense_kernel(AttnArgs a, DenseArg
             const int flag = kNext ? moved[(t - 1) & 1] : 0;
             const unsigned short *src = tile_src(t + 3);
             __builtin_amdgcn_sched_barrier(0);
-            acc::unroll<8>([&](auto i_c) __attribute__((always_inline)) {
+            unroll<8>([&](auto i_c) __attribute__((always_inline)) {
                 constexpr int i = decltype(i_c)::value, s = i >> 2, nb = i & 3;
                 if constexpr (kMma) {
                     const s16x8 v = {vq[s][nb][0][0], vq[s][nb][0][1], vq[s][nb][0][2], vq[s][nb][0][3], vq[s][nb][1][0], vq[s][nb][1][1], vq[s][nb][1][2], vq[s][nb][1][3]};
-                    acc::mma_o<nb>(__builtin_bit_cast(bf16x8, v), pa[s][0]);
-                    acc::mma_o<4 + nb>(__builtin_bit_cast(bf16x8, v), pa[s][1]);
+#pragma unroll
+                    for (int r = 0; r < 2; ++r)
+                        o_acc[r][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, v), pa[s][r], o_acc[r][nb], 0, 0, 0);
                     __builtin_amdgcn_sched_barrier(0);
                 }
                 if constexpr (kNext) {
@@ -1299,10 +1236,19 @@ __global__ __launch_bounds__(512, 2) void attn_dense_kernel(AttnArgs a, DenseArg
                     __builtin_amdgcn_sched_barrier(0);
                 }
             });
-            if (kNext && t - 1 >= t_edge && __builtin_amdgcn_readfirstlane(moved[2])) finite_v();                 // (the step's end is far enough from their use)
+            if (kNext && t - 1 >= t_edge && __builtin_amdgcn_readfirstlane(moved[2])) finite_v();
             if (kNext && __builtin_amdgcn_readfirstlane(flag)) {       // see above
                 __syncthreads();
-                if constexpr (kMma) acc::rescale_o(fac[l32], fac[32 + l32]);
+                if constexpr (kMma) {
+#pragma unroll
+                    for (int r = 0; r < 2; ++r) {
+                        const float f = fac[32 * r + l32];
+#pragma unroll
+                        for (int nb = 0; nb < 4; ++nb)
+#pragma unroll
+                            for (int e = 0; e < 16; ++e) o_acc[r][nb][e] *= f;
+                    }
+                }
 #pragma unroll
                 for (int s = 0; s < 2; ++s)
 #pragma unroll
@@ -1322,9 +1268,7 @@ __global__ __launch_bounds__(512, 2) void attn_dense_kernel(AttnArgs a, DenseArg
             __syncthreads();
             step(t, T, T);
         }
-        asm volatile("s_nop 7" : "+v"(pa[0][0]), "+v"(pa[0][1]), "+v"(pa[1][0]), "+v"(pa[1][1]));
         step(nt + 1, T, F);
-        asm volatile("s_nop 15" ::: IC_ACC_ALL);          // the last matrix steps have left the pipe
         __syncthreads();
         float inv[2];
 #pragma unroll
@@ -1332,13 +1276,11 @@ __global__ __launch_bounds__(512, 2) void attn_dense_kernel(AttnArgs a, DenseArg
             const float l = mnew[32 * r + l32] + mnew[kDenseRows + 32 * r + l32];
             inv[r] = l > 0.f ? __builtin_amdgcn_rcpf(l) : 0.f;
         }
-        acc::unroll<32>([&](auto q_c) __attribute__((always_inline)) {
-            constexpr int q = decltype(q_c)::value, r = q >> 4, nb = (q >> 2) & 3, qd = q & 3, e = 64 * r + 16 * nb + 4 * qd;
+        unroll<32>([&](auto q_c) __attribute__((always_inline)) {
+            constexpr int q = decltype(q_c)::value, r = q >> 4, nb = (q >> 2) & 3, qd = q & 3;
             s16x4 o;
-            o[0] = __builtin_bit_cast(short, (__bf16)(acc::get_o<e>() * inv[r]));
-            o[1] = __builtin_bit_cast(short, (__bf16)(acc::get_o<e + 1>() * inv[r]));
-            o[2] = __builtin_bit_cast(short, (__bf16)(acc::get_o<e + 2>() * inv[r]));
-            o[3] = __builtin_bit_cast(short, (__bf16)(acc::get_o<e + 3>() * inv[r]));
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[e] = __builtin_bit_cast(short, (__bf16)(o_acc[r][nb][4 * qd + e] * inv[r]));
             *(s16x4 *)(tbuf + (32 * r + l32) * OSTR + 2 * (128 * w + 32 * nb + 8 * qd + 4 * hh)) = o;
         });
     }

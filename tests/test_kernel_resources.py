@@ -1,0 +1,23 @@
+"""Registers of the dense attention kernel, as the compiler reports them."""
+import os
+import re
+import subprocess
+
+from paper_2603_12201_amd import build
+
+
+def test_dense_attention_registers_are_the_compilers_own():
+    """Nothing is kept in registers the compiler does not know to be in use (it counts accumulation registers only where asm
+    statements name them: this kernel's are all of one file), and nothing is spilled."""
+    src = os.path.join(build.CSRC, "ic_sparse_attn.hip")
+    p = subprocess.run(["hipcc"] + build.FLAGS + ["--offload-device-only", "-Rpass-analysis=kernel-resource-usage", "-S", src, "-o", os.devnull],
+                       stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, check=True)
+    seen = 0
+    for name, body in re.findall(r"Function Name: (\S+)(.*?)(?=Function Name|\Z)", p.stdout, re.S):
+        if "attn_dense_kernel" not in name:
+            continue
+        seen += 1
+        use = {k: int(v) for k, v in re.findall(r"(AGPRs|VGPRs Spill|VGPRs|ScratchSize \[bytes/lane\]): (\d+)", body)}
+        assert use["AGPRs"] == 0 and use["VGPRs Spill"] == 0 and use["ScratchSize [bytes/lane]"] == 0, (name, use)
+        assert use["VGPRs"] <= 256, (name, use)
+    assert seen == 2                              # contiguous and paged
