@@ -1035,7 +1035,7 @@ __global__ __launch_bounds__(512, 2) void attn_dense_kernel(AttnArgs a, DenseArg
         const int pw_off = (32 * rh + l16) * PSTR + 32 * kh + 8 * g;
         float m_c[2] = {-INFINITY, -INFINITY}, l_own[2] = {0.f, 0.f}, psum[2] = {0.f, 0.f};
         bf16x8 ka[RING];
-        f32x4 s4[2];
+        f32x4 s4[2], odd[2];                              // two accumulation chains, as in the row form: half of the roundings in one
 #pragma unroll
         for (int r = 0; r < RING; ++r) ka[r] = *(const bf16x8 *)(tbuf + ka_off + 64 * r);
         auto scores = [&](int t) __attribute__((always_inline)) {
@@ -1044,14 +1044,20 @@ __global__ __launch_bounds__(512, 2) void attn_dense_kernel(AttnArgs a, DenseArg
             unroll<KS>([&](auto ks_c) __attribute__((always_inline)) {
                 constexpr int ks = decltype(ks_c)::value;
 #pragma unroll
-                for (int r = 0; r < 2; ++r)
-                    s4[r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[ks % RING], qv[ks][r], ks == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : s4[r], 0, 0, 0);
+                for (int r = 0; r < 2; ++r) {
+                    f32x4 &c = ks % 2 ? odd[r] : s4[r];
+                    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[ks % RING], qv[ks][r], ks < 2 ? f32x4{0.f, 0.f, 0.f, 0.f} : c, 0, 0, 0);
+                }
                 ka[ks % RING] = ks + RING < KS ? *(const bf16x8 *)(tb + 64 * (ks + RING)) : *(const bf16x8 *)(tb1 + 64 * (ks + RING - KS));
                 __builtin_amdgcn_sched_barrier(0);
             });
         };
         auto softmax = [&](int t) __attribute__((always_inline)) {
             // lane: row l16 of either block, keys dense_row(4 g + i)
+#pragma unroll
+            for (int r = 0; r < 2; ++r)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) s4[r][i] += odd[r][i];
             const int key0 = kDenseTile * t + 16 * kh;
             if (key0 + 15 > lim0) {
                 const int k0 = key0 + 8 * (g >> 1) + (g & 1);
@@ -1134,7 +1140,9 @@ __global__ __launch_bounds__(512, 2) void attn_dense_kernel(AttnArgs a, DenseArg
         __syncthreads();
         if (a.lse && tid < kDenseRows && R0 + tid < n_rows) {
             const float l = mnew[tid] + mnew[kDenseRows + tid];
-            a.lse[(int64_t)b * a.Tq * a.H_q + R0 + tid] = l > 0.f ? (mref[tid] + __builtin_log2f(l)) * 0.6931471805599453f : -INFINITY;
+            // (in 64 bits: the reference of 32 keys leaves a larger logarithm, and so a coarser sum, than that of the row form's 64)
+            a.lse[(int64_t)b * a.Tq * a.H_q + R0 + tid] =
+                l > 0.f ? (float)(((double)mref[tid] + (double)__builtin_log2f(l)) * 0.6931471805599453) : -INFINITY;
         }
     } else {
         // A tile is fetched eight lanes to a 128-byte line: rows 8 w + gr, nine lines.

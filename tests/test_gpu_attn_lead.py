@@ -128,3 +128,29 @@ def test_a_workspace_that_is_not_needed_is_not_written(oracle, B, Tq, k):
         torch.cuda.synchronize()
         assert bool((ws == 0xA5).all()), where
         parity.check_attn(out.float().cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("gain", [1.0, 3.0, 6.0])
+def test_lse_is_as_exact_as_the_row_forms(gain):
+    """Both forms take a score in two accumulation chains of nine steps, so their lse differ from 64-bit sums alike; with one
+    chain of eighteen the dense form's distance was 1.05 / 1.27 / 1.45 times the row form's at these gains."""
+    import paper_2603_12201_amd as ic
+    print("[case] lse gain=%g" % gain, flush=True)
+    T, scale = 1024, 1 / 24.0
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    Q = torch.randn((1, T, 32, 576), generator=gen, device="cuda", dtype=torch.bfloat16) * gain
+    KV = torch.randn((1, T, 576), generator=gen, device="cuda", dtype=torch.bfloat16)
+    t = torch.arange(T, device="cuda")
+    idx = torch.where(t[None, :] <= t[:, None], t[None, :], -1).to(torch.int32)[None].contiguous()
+    _, dense = ic.sparse_attn(Q, KV, idx, 512, 0, scale, want_lse=True)
+    _, row = ic.sparse_attn(Q, KV, idx, 512, 0, scale, want_lse=True, workspace=torch.empty(0, dtype=torch.uint8, device="cuda"))
+    K = KV[0].double()
+    far = [0.0, 0.0]
+    for h in range(0, 32, 4):
+        z = (torch.matmul(Q[0, :, h].double(), K.t()) * scale).masked_fill(t[None, :] > t[:, None], float("-inf"))
+        want = torch.logsumexp(z, -1)
+        for i, got in enumerate((dense, row)):
+            far[i] += (got[0, :, h].double() - want).pow(2).sum().item()
+    assert not torch.equal(dense, row)                # (two forms, not one twice)
+    # 8192 values each: the ratio of two such root mean squares scatters by about 2 %
+    assert far[0] ** 0.5 <= 1.08 * far[1] ** 0.5, (far[0] ** 0.5, far[1] ** 0.5)
