@@ -1319,21 +1319,26 @@ __global__ __launch_bounds__(512, 2) void attn_dense_kernel(AttnArgs a, DenseArg
 
 // Combine the per-split partials of one (query, head): O = sum_s w_s O_s / sum_s w_s with O_s the split's own
 // normalised output and w_s = l_s 2^(m_s-m) its share of the row sum.
-// One workgroup per (query, head), D_V / 8 lanes (16 bytes each) per split, so 4 splits (32 for 64 columns) are handled
-// side by side and each slot requests all of its splits (8 per batch) together with their (maximum, sum) pairs: the
-// launch waits for memory once.  What bounds it is that latency and the launch itself; with one thread per four columns
-// walking the splits one batch after the other, a single decode token's 32 splits took 14.2 us per layer, now 5.
-template <int D_V>
+// D_V / 8 lanes (16 bytes each) per split, SLOTS splits side by side, and each slot requests all of its splits (8 per batch)
+// together with their (maximum, sum) pairs: the launch waits for memory once.  What bounds it is that latency and the launch
+// itself; with one thread per four columns walking the splits one batch after the other, a single decode token's 32 splits
+// took 14.2 us per layer, now 5.  Up to eight splits are one batch of one slot: then a wave has a (query, head) of 512
+// columns to itself, nothing passes through LDS, and no lane is left without a split (with four slots, two splits of 128
+// queries x 32 heads kept half of the lanes idle in 4096 workgroups: launch and merge took 45.6 us, 38.6 before that form).
+template <int D_V, int SLOTS>
 __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a)
 {
-    constexpr int LPS = D_V / 8, SLOTS = 256 / LPS, kBatch = 8;
-    __shared__ __attribute__((aligned(16))) float o_sh[SLOTS][D_V];
-    __shared__ float m_sh[SLOTS], l_sh[SLOTS];
+    constexpr int LPS = D_V / 8, kBatch = 8;
+    constexpr int GROUP = LPS * SLOTS, HEADS = 256 / GROUP;  // threads of a head, heads of a workgroup
+    static_assert(SLOTS == 1 || 2 * GROUP >= D_V, "two columns per thread at the end");
     const int64_t gq = blockIdx.x;
     const int layer = (int)(gq / ((int64_t)a.B * a.Tq));
     const int64_t qrow = gq - (int64_t)layer * a.B * a.Tq;
-    const int h = blockIdx.y;
-    const int slot = threadIdx.x / LPS, v = (threadIdx.x % LPS) * 8;
+    const int grp = threadIdx.x / GROUP, tid = threadIdx.x % GROUP;
+    const int head = blockIdx.y * HEADS + grp;
+    const bool live = head < a.H_q;
+    const int h = live ? head : 0;
+    const int slot = tid / LPS, v = (tid % LPS) * 8;
     const float *ml = a.part_ml + ((gq * a.n_splits) * a.H_q + h) * 2;
     const int64_t ml_stride = (int64_t)a.H_q * 2;
     const __bf16 *po = a.part_o + ((gq * a.n_splits) * a.H_q + h) * D_V + v;
@@ -1375,31 +1380,45 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a)
             }
         }
     }
-    *(f32x4 *)&o_sh[slot][v] = f32x4{o[0], o[1], o[2], o[3]};
-    *(f32x4 *)&o_sh[slot][v + 4] = f32x4{o[4], o[5], o[6], o[7]};
-    if (v == 0) {
-        m_sh[slot] = m;
-        l_sh[slot] = l;
-    }
-    __syncthreads();
-    // the slots together: two neighbouring columns per thread
-    const int c = threadIdx.x * 2;
-    if (c >= D_V) return;
-    float mt = -INFINITY, lt = 0.f, t0 = 0.f, t1 = 0.f;
+    __bf16 *const out = (__bf16 *)a.Os[layer] + (qrow * a.H_q + h) * D_V;
+    if constexpr (SLOTS == 1) {
+        if (!live) return;
+        const float inv = (l > 0.f) ? 1.f / l : 0.f;
+        typedef __attribute__((ext_vector_type(8))) __bf16 b16x8;
+        b16x8 r;
 #pragma unroll
-    for (int s = 0; s < SLOTS; ++s) mt = fmaxf(mt, m_sh[s]);
+        for (int e = 0; e < 8; ++e) r[e] = (__bf16)(o[e] * inv);
+        *(b16x8 *)(out + v) = r;
+    } else {
+        __shared__ __attribute__((aligned(16))) float o_sh[HEADS][SLOTS][D_V];
+        __shared__ float m_sh[HEADS][SLOTS], l_sh[HEADS][SLOTS];
+        *(f32x4 *)&o_sh[grp][slot][v] = f32x4{o[0], o[1], o[2], o[3]};
+        *(f32x4 *)&o_sh[grp][slot][v + 4] = f32x4{o[4], o[5], o[6], o[7]};
+        if (v == 0) {
+            m_sh[grp][slot] = m;
+            l_sh[grp][slot] = l;
+        }
+        __syncthreads();
+        // the slots together: two neighbouring columns per thread
+        const int c = tid * 2;
+        if (!live || c >= D_V) return;
+        float mt = -INFINITY, lt = 0.f, t0 = 0.f, t1 = 0.f;
 #pragma unroll
-    for (int s = 0; s < SLOTS; ++s) {
-        const float sc = (m_sh[s] == -INFINITY) ? 0.f : fast_exp2(m_sh[s] - mt);
-        lt += l_sh[s] * sc;
-        t0 += o_sh[s][c] * sc;
-        t1 += o_sh[s][c + 1] * sc;
+        for (int s = 0; s < SLOTS; ++s) mt = fmaxf(mt, m_sh[grp][s]);
+#pragma unroll
+        for (int s = 0; s < SLOTS; ++s) {
+            const float sc = (m_sh[grp][s] == -INFINITY) ? 0.f : fast_exp2(m_sh[grp][s] - mt);
+            lt += l_sh[grp][s] * sc;
+            t0 += o_sh[grp][s][c] * sc;
+            t1 += o_sh[grp][s][c + 1] * sc;
+        }
+        const float inv = (lt > 0.f) ? 1.f / lt : 0.f;
+        typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+        *(bf16x2 *)(out + c) = bf16x2{(__bf16)(t0 * inv), (__bf16)(t1 * inv)};
+        m = mt;
+        l = lt;
     }
-    const float inv = (lt > 0.f) ? 1.f / lt : 0.f;
-    typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
-    *(bf16x2 *)((__bf16 *)a.Os[layer] + (qrow * a.H_q + h) * D_V + c) = bf16x2{(__bf16)(t0 * inv), (__bf16)(t1 * inv)};
-    if (threadIdx.x == 0 && a.lse)
-        a.lse[qrow * a.H_q + h] = (lt > 0.f) ? (mt + __builtin_log2f(lt)) * 0.6931471805599453f : -INFINITY;
+    if (tid == 0 && a.lse) a.lse[qrow * a.H_q + h] = (l > 0.f) ? (m + __builtin_log2f(l)) * 0.6931471805599453f : -INFINITY;
 }
 
 template <int D_QK, int D_V, int ROW_F>
@@ -1545,11 +1564,13 @@ hipError_t launch_attn(const AttnArgs &a, int d_qk, int d_v, hipStream_t st)
 hipError_t launch_attn_merge(const AttnArgs &a, int d_v, hipStream_t st)
 {
     if ((int64_t)a.B * a.Tq <= 0) return hipSuccess;
-    dim3 grid((unsigned)((int64_t)a.n_layers * a.B * a.Tq), (unsigned)a.H_q);
-    if (d_v == 512)
-        hipLaunchKernelGGL((attn_merge_kernel<512>), grid, dim3(256), 0, st, a);
+    const unsigned nq = (unsigned)((int64_t)a.n_layers * a.B * a.Tq), H = (unsigned)a.H_q;
+    if (d_v == 512 && a.n_splits <= 8)
+        hipLaunchKernelGGL((attn_merge_kernel<512, 1>), dim3(nq, (H + 3) / 4), dim3(256), 0, st, a);
+    else if (d_v == 512)
+        hipLaunchKernelGGL((attn_merge_kernel<512, 4>), dim3(nq, H), dim3(256), 0, st, a);
     else if (d_v == 64)
-        hipLaunchKernelGGL((attn_merge_kernel<64>), grid, dim3(256), 0, st, a);
+        hipLaunchKernelGGL((attn_merge_kernel<64, 32>), dim3(nq, H), dim3(256), 0, st, a);
     else
         return hipErrorInvalidValue;
     return hipGetLastError();

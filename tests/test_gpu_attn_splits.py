@@ -1,5 +1,6 @@
 """Split attention launches (fewer queries than the chip holds workgroups) and their merge, at the edges of the rules
-that choose the number of splits: one split, as many as fit one round, more splits than the merge handles side by side."""
+that choose the number of splits: one split, as many as fit one round, more splits than the merge handles side by side or
+in one wave."""
 import math
 
 import numpy as np
@@ -18,6 +19,9 @@ CASES = [
     (40, 1, 700, 32, 576, 512, 0, 576, 640),     # 6 splits of 2 tiles, not 7
     (1, 129, 900, 32, 576, 512, 0, 576, 320),    # one workgroup per query rather than two rounds
     (1, 100, 900, 20, 576, 512, 0, 576, 449),    # two splits, the second one ragged
+    (32, 1, 700, 32, 576, 512, 0, 576, 512),     # 8 splits, a wave merges a head
+    (25, 1, 700, 31, 576, 512, 0, 576, 576),     # 9 splits, a workgroup does
+    (60, 1, 700, 6, 576, 512, 0, 576, 640),      # a last workgroup of two heads
     (1, 300, 400, 3, 64, 64, 64, 128, 130),      # small-tile form, two workgroups per CU
 ]
 
