@@ -34,6 +34,13 @@ constexpr int kTile = 32;
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
+// layer of query gq of a launch (several layers share one where they have a few thousand queries together: 32 bits do; the
+// division in 64 bits costs every workgroup about 1 us before its first load)
+__device__ __forceinline__ int layer_of(const AttnArgs &a, int64_t gq)
+{
+    return a.n_layers == 1 ? 0 : (int)((unsigned)gq / (unsigned)(a.B * a.Tq));
+}
+
 // Tile staging.  A thread owns tile row tid / 8 and the 16-byte chunks (tid % 8) + 8 r of that
 // row: eight neighbouring lanes read one full 128-byte line, and no index needs a division.
 template <int ROW_F, int LPT, bool PG>
@@ -81,7 +88,7 @@ __global__ __launch_bounds__(256, 2) void attn_kernel(AttnArgs a)
     const int l16 = lane & 15, g = lane >> 4;
     const int mh = wave & 1, vh = wave >> 1;
     const int64_t gq = blockIdx.x;                        // query of the launch: flattened (layer, b, t)
-    const int layer = (int)(gq / ((int64_t)a.B * a.Tq));
+    const int layer = layer_of(a, gq);
     const int64_t qrow = gq - (int64_t)layer * a.B * a.Tq;
     const int b = (int)(qrow / a.Tq);
     const int sp = blockIdx.y;
@@ -374,7 +381,7 @@ __global__ __launch_bounds__(256, 1) void attn_slab_kernel(AttnArgs a, RestArgs 
         Src r;
         r.live = q < nq;
         const int64_t gq = r.live ? q : (int64_t)blockIdx.x;          // a dead source still reads valid memory
-        r.layer = MULTI ? (int)(gq / nq_layer) : 0;
+        r.layer = MULTI ? layer_of(a, gq) : 0;
         const int64_t qq = MULTI ? gq - r.layer * nq_layer : gq;
         if constexpr (MULTI) r.q = qq;
         r.b = (int)(qq / a.Tq);
@@ -1332,7 +1339,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a)
     constexpr int GROUP = LPS * SLOTS, HEADS = 256 / GROUP;  // threads of a head, heads of a workgroup
     static_assert(SLOTS == 1 || 2 * GROUP >= D_V, "two columns per thread at the end");
     const int64_t gq = blockIdx.x;
-    const int layer = (int)(gq / ((int64_t)a.B * a.Tq));
+    const int layer = layer_of(a, gq);
     const int64_t qrow = gq - (int64_t)layer * a.B * a.Tq;
     const int grp = threadIdx.x / GROUP, tid = threadIdx.x % GROUP;
     const int head = blockIdx.y * HEADS + grp;
