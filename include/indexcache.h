@@ -108,7 +108,9 @@ size_t ic_sparse_attn_workspace(const ic_attn_desc *desc);
  *   0 <= idx_m < Lk (others are skipped), p = softmax(z), O[b,t,h,:] = sum_m p_m KV[b,idx_m,v_off:+d_v].
  *   O   [B,Tq,H_q,d_v] bf16 out (a row with no valid entry gives zeros)
  *   lse [B,Tq,H_q] fp32 out, nullable: log sum_m exp(z_m) (-inf for an empty row)
- * Where ic_sparse_attn_workspace() is 0 a workspace is neither looked at nor written.
+ * Where ic_sparse_attn_workspace() is 0 a workspace is neither looked at nor written.  It asks for the partial outputs of the
+ * splits in fp32 where a launch takes fewer of them than would fill the chip; less will do, down to what all of those take in
+ * bf16.
  */
 ic_status ic_sparse_attn(const ic_attn_desc *desc, const void *Q, const void *KV, const int32_t *idx,
                          void *O, float *lse, void *workspace, size_t workspace_bytes, void *stream);
@@ -130,7 +132,8 @@ ic_status ic_sparse_attn_lead(const ic_attn_desc *desc, const void *Q, const voi
  * split-attention partials in a scratch array that is part of the library's code object instead of a
  * caller workspace.  Nothing is allocated or freed, by the library or any routine it calls.
  *   - The scratch holds IC_STATIC_SCRATCH_BYTES per GPU for the life of the process.  A descriptor
- *     whose ic_sparse_attn_workspace() exceeds it is rejected with IC_ERR_WORKSPACE before any launch.
+ *     whose bf16 partials (the least that ic_sparse_attn accepts) exceed it is rejected with
+ *     IC_ERR_WORKSPACE before any launch.
  *   - The device the stream belongs to must be the current device of the calling thread.
  *   - Every call on one GPU shares that GPU's scratch: calls that overlap in time on one GPU (other
  *     streams, other threads) race.  Calls on one stream are ordered and safe.  The kernels overwrite

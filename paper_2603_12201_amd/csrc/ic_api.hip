@@ -6,6 +6,7 @@
 #include <cstdio>
 #include <cstring>
 #include <mutex>
+#include <algorithm>
 #include <vector>
 
 #include "ic_common.hpp"
@@ -147,39 +148,57 @@ int64_t attn_max_splits(const ic_attn_desc *d, int n_layers)
     return (tiles + per - 1) / per;
 }
 
-// Partials of `parts` (query, split) pairs: bf16 outputs, fp32 (max, sum).
-size_t split_bytes(const ic_attn_desc *d, int64_t parts)
+// Partials of `parts` (query, split) pairs: outputs in bf16 or fp32 (wide), fp32 (max, sum).
+size_t part_o_bytes(const ic_attn_desc *d, int64_t parts, bool wide) { return align_up((size_t)parts * d->H_q * d->d_v * (wide ? 4 : 2)); }
+size_t split_bytes(const ic_attn_desc *d, int64_t parts, bool wide)
 {
-    return align_up((size_t)parts * d->H_q * d->d_v * 2) + align_up((size_t)parts * d->H_q * 2 * sizeof(float));
+    return part_o_bytes(d, parts, wide) + align_up((size_t)parts * d->H_q * 2 * sizeof(float));
 }
 
 // Splits of a launch.  Workgroups run in rounds of attn_resident(), and a round takes as long as its longest workgroup:
 // tiles plus what a workgroup pays once (launch, Q, first rows, output: about two tiles).  The merge launch costs about
 // two tiles more.  One split too many can therefore double the time (40 queries x 7 splits of 5 tiles = 280 workgroups on
 // 256 CUs took 36 us, 6 splits of 6 tiles take 30), so the number with the fewest tile times wins, the smaller at a tie.
-void attn_splits(const ic_attn_desc *d, int n_layers, size_t ws_bytes, int *n_splits, int *split_len)
+// The rounding of bf16 partials weighs the more the fewer there are (relative distance from 64 bits: 32 of them 0.0022, 8
+// 0.0023, 2 0.00244, no split or fp32 partials 0.0020).  A query in as many as one layer's launch may have, which is what
+// the workspace is sized for, keeps them in bf16; in fewer they are fp32 (24 queries in 8 splits: 1.2 us more for the
+// launch and its merge).
+struct Splits {
+    int n, len;
+    bool wide;
+    size_t bytes;
+};
+Splits attn_splits(const ic_attn_desc *d, int n_layers, size_t ws_bytes, int64_t narrow)
 {
     const int64_t nq = (int64_t)n_layers * d->B * d->Tq, wgs = attn_resident(d), tiles = (d->k_sel + 63) / 64;
-    int64_t best = 0, best_per = tiles;
+    int64_t best = 0;
+    Splits r = {1, (int)tiles * 64, false, 0};
     for (int64_t ns = 1, most = attn_max_splits(d, n_layers); ns <= most; ++ns) {
         const int64_t per = (tiles + ns - 1) / ns, n = (tiles + per - 1) / per;
-        if (n > 1 && split_bytes(d, nq * n) > ws_bytes) continue;
+        const bool wide = n > 1 && n < narrow;
+        const size_t bytes = n > 1 ? split_bytes(d, nq * n, wide) : 0;
+        if (bytes > ws_bytes) continue;
         const int64_t cost = (nq * n + wgs - 1) / wgs * (per + 2) + (n > 1 ? 2 : 0);
         if (best == 0 || cost < best) {
             best = cost;
-            best_per = per;
+            r = {(int)n, (int)per * 64, wide, bytes};
         }
     }
-    *split_len = (int)best_per * 64;
-    *n_splits = (int)((tiles + best_per - 1) / best_per);
+    return r;
 }
 
-// 0: the launch writes nothing into a workspace
-size_t attn_ws_bytes(const ic_attn_desc *d, int n_layers = 1)
+// What one layer's launch has to have (0: it writes nothing into a workspace) and what serves it, or a run of layers, best.
+size_t attn_ws_bytes(const ic_attn_desc *d)
 {
-    const size_t ns = (size_t)attn_max_splits(d, n_layers);
+    const size_t ns = (size_t)attn_max_splits(d, 1);
     if (ns <= 1) return 0;
-    return split_bytes(d, (int64_t)n_layers * d->B * d->Tq * (int64_t)ns);
+    return split_bytes(d, (int64_t)d->B * d->Tq * (int64_t)ns, false);
+}
+size_t attn_best_bytes(const ic_attn_desc *d, int n_layers) { return attn_splits(d, n_layers, SIZE_MAX, attn_max_splits(d, 1)).bytes; }
+size_t attn_query_bytes(const ic_attn_desc *d)
+{
+    const size_t least = attn_ws_bytes(d), best = attn_best_bytes(d, 1);
+    return least > best ? least : best;
 }
 
 // Layers that one attention launch may take together: a Full layer and the Shared layers behind it read the same index
@@ -396,7 +415,7 @@ size_t lead_tail_bytes(const ic_attn_desc *d)
     ic_attn_desc t = *d;
     t.B = 1;
     t.Tq = d->Tq - n;
-    return attn_ws_bytes(&t);
+    return attn_splits(&t, 1, SIZE_MAX, INT64_MAX).bytes;
 }
 
 // Counts of n_tensors index tensors into lead.
@@ -447,8 +466,9 @@ ic::AttnArgs attn_args(const ic_layer *layers, int n_layers, const int32_t *idx,
     return a;
 }
 
+// tail: rows of a launch that has been divided; they were not split before, so their partials are fp32
 ic_status run_attn_layers(const ic_layer *layers, int n_layers, const int32_t *idx, float *lse, void *ws, size_t ws_bytes,
-                          hipStream_t st, const ic_paged_cache *pc, Causal c);
+                          hipStream_t st, const ic_paged_cache *pc, Causal c, bool tail = false);
 
 // Rows row0 .. row0 + n - 1 of sequence b as a problem of their own.
 ic_layer layer_rows(const ic_layer *L, int b, int row0, int n)
@@ -495,7 +515,7 @@ ic_status run_attn_lead(const ic_layer *L, const int32_t *idx, const int32_t *le
         ic_layer t = layer_rows(L, b, n, d->Tq - n);
         t.KV = r.KV;
         ic_status s = run_attn_layers(&t, 1, idx + (row + n) * d->k_sel, lse ? lse + (row + n) * d->H_q : nullptr, ws, ws_bytes, st,
-                                      nullptr, kUnknown);
+                                      nullptr, kUnknown, true);
         if (s != IC_OK) return s;
     }
     return IC_OK;
@@ -504,7 +524,7 @@ ic_status run_attn_lead(const ic_layer *L, const int32_t *idx, const int32_t *le
 // c: idx is this library's own (rows that can hold fewer than k_sel entries end in -1s, and the kernels leave their empty
 // tiles out) or the caller's (kUnknown)
 ic_status run_attn_layers(const ic_layer *layers, int n_layers, const int32_t *idx, float *lse, void *ws, size_t ws_bytes,
-                          hipStream_t st, const ic_paged_cache *pc, Causal c)
+                          hipStream_t st, const ic_paged_cache *pc, Causal c, bool tail)
 {
     const ic_attn_desc *d = &layers[0].at;
     ic::AttnArgs a = attn_args(layers, n_layers, idx, lse, pc, c);
@@ -526,16 +546,18 @@ ic_status run_attn_layers(const ic_layer *layers, int n_layers, const int32_t *i
             }
             if (!pc || !pc->page_table) r.KV = (const char *)r.KV + (int64_t)b * d->Lk * d->row_elems * 2;
             ic_status s = run_attn_layers(&r, 1, idx + row * d->k_sel, lse ? lse + row * d->H_q : nullptr, ws, ws_bytes, st,
-                                          pc ? &pb : nullptr, Causal{c.pos0 + nd, c.lk});
+                                          pc ? &pb : nullptr, Causal{c.pos0 + nd, c.lk}, true);
             if (s != IC_OK) return s;
         }
         return IC_OK;
     }
-    attn_splits(d, n_layers, ws_bytes, &a.n_splits, &a.split_len);
-    if (a.n_splits > 1) {
-        const size_t nq = (size_t)n_layers * d->B * d->Tq;
-        a.part_o = (__bf16 *)ws;
-        a.part_ml = (float *)((char *)ws + align_up(nq * a.n_splits * d->H_q * d->d_v * 2));
+    const Splits sp = attn_splits(d, n_layers, ws_bytes, tail ? INT64_MAX : attn_max_splits(d, 1));
+    a.n_splits = sp.n;
+    a.split_len = sp.len;
+    if (sp.n > 1) {
+        a.part_o = ws;
+        a.part_wide = sp.wide;
+        a.part_ml = (float *)((char *)ws + part_o_bytes(d, (int64_t)n_layers * d->B * d->Tq * sp.n, sp.wide));
     }
     {
         ProfScope ps(2, st);
@@ -595,14 +617,14 @@ ic_status ic_indexer_topk(const ic_indexer_desc *d, const void *q, const void *k
 size_t ic_sparse_attn_workspace(const ic_attn_desc *d)
 {
     if (check_attn(d) != IC_OK) return 0;
-    return attn_ws_bytes(d);
+    return attn_query_bytes(d);
 }
 
 size_t ic_sparse_attn_lead_workspace(const ic_attn_desc *d)
 {
     if (check_attn(d) != IC_OK) return 0;
     const size_t lb = lead_bytes(d, 1);
-    return lb ? lb + align_up(lead_tail_bytes(d)) : attn_ws_bytes(d);
+    return lb ? lb + align_up(lead_tail_bytes(d)) : attn_query_bytes(d);
 }
 
 ic_status ic_sparse_attn_lead(const ic_attn_desc *d, const void *Q, const void *KV, const int32_t *idx, void *O,
@@ -674,7 +696,7 @@ ic_status ic_sparse_attn_static(const ic_attn_desc *d, const void *Q, const void
         s = static_scratch(&ws);
         if (s != IC_OK) return s;
     }
-    return run_attn(d, Q, KV, idx, O, lse, ws, need, (hipStream_t)stream);
+    return run_attn(d, Q, KV, idx, O, lse, ws, need > 0 ? (size_t)IC_STATIC_SCRATCH_BYTES : 0, (hipStream_t)stream);
 }
 
 static ic_status check_stack(const ic_layer *layers, int32_t n, const uint8_t *full_mask)
@@ -721,7 +743,7 @@ size_t ic_forward_stack_workspace(const ic_layer *layers, int32_t n_layers)
         if (a > 0) {
             const int run = n_layers - l < ic::kMaxBatchLayers ? n_layers - l : ic::kMaxBatchLayers;
             for (int m = 2; m <= run && memcmp(&layers[l + m - 1].at, &layers[l].at, sizeof layers[l].at) == 0; ++m) {
-                const size_t am = attn_ws_bytes(&layers[l].at, m);
+                const size_t am = attn_best_bytes(&layers[l].at, m);
                 if (am > a) a = am;
             }
         }
@@ -767,7 +789,7 @@ static ic_status forward_stack_impl(const ic_layer *layers, int32_t n_layers, co
         int run = 1;                           // this layer and the Shared layers behind it
         while (l + run < n_layers && !full_mask[l + run]) ++run;
         int m = dense_queries(&L->at, 1, known) ? 1 : attn_batch(L, run, pc);
-        while (m > 1 && attn_ws_bytes(&L->at, m) > workspace_bytes) --m;
+        while (m > 1 && attn_best_bytes(&L->at, m) > workspace_bytes) --m;
         s = run_attn_layers(L, m, idx_cache, nullptr, workspace, workspace_bytes, st, pc, known);
         if (s != IC_OK) return s;
         l += m - 1;
@@ -891,7 +913,7 @@ size_t ic_similarity_matrix_workspace(const ic_layer *layers, int32_t n_layers)
     if (!layers || n_layers <= 0 || n_layers > IC_MAX_OVERLAP_LAYERS) return 0;
     size_t at = 0;
     for (int l = 0; l < n_layers; ++l) {
-        const size_t a = attn_ws_bytes(&layers[l].at);
+        const size_t a = attn_query_bytes(&layers[l].at);
         if (a > at) at = a;
     }
     return sim_o_bytes(&layers[0].at) + align_up(at) + sim_lead_bytes(layers, n_layers);
@@ -905,18 +927,19 @@ ic_status ic_similarity_matrix(const ic_layer *layers, int32_t n_layers, const i
     if (!idx_layers || !S) return fail(IC_ERR_NULL, "idx_layers and S must not be NULL");
     for (int l = 0; l < n_layers; ++l)
         if (!idx_layers[l]) return fail(IC_ERR_NULL, "idx_layers[%d] is NULL", l);
-    // the counts of leading rows only make it faster: a workspace without room for them will do
-    size_t lb = sim_lead_bytes(layers, n_layers);
-    const size_t all = ic_similarity_matrix_workspace(layers, n_layers), min_ws = all - lb;
+    // the counts of leading rows and wide partials are for more speed or precision: a workspace without room for them will do
+    size_t lb = sim_lead_bytes(layers, n_layers), at = 0;
+    for (int l = 0; l < n_layers; ++l) at = std::max(at, attn_ws_bytes(&layers[l].at));
+    const size_t min_ws = sim_o_bytes(&layers[0].at) + align_up(at);
     s = check_ws(workspace, workspace_bytes, min_ws);
     if (s != IC_OK) return s;
-    if (workspace_bytes < all) lb = 0;
+    if (workspace_bytes < min_ws + lb) lb = 0;
     hipStream_t st = (hipStream_t)stream;
     char *ws = (char *)workspace;
     void *o_reuse = ws;
-    void *attn_ws = ws + sim_o_bytes(&layers[0].at);
-    const size_t attn_bytes = min_ws - sim_o_bytes(&layers[0].at);
-    int32_t *const lead = (int32_t *)((char *)attn_ws + attn_bytes);
+    int32_t *const lead = (int32_t *)(ws + sim_o_bytes(&layers[0].at));
+    void *attn_ws = (char *)lead + lb;
+    const size_t attn_bytes = workspace_bytes - sim_o_bytes(&layers[0].at) - lb;
     hipError_t e = ic::launch_sim_init(S, n_layers, st);
     if (e != hipSuccess) return fail(IC_ERR_HIP, "similarity init failed: %s", hipGetErrorString(e));
     const ic_attn_desc *a0 = &layers[0].at;

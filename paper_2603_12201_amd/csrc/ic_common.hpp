@@ -82,7 +82,8 @@ struct AttnArgs {
     const int32_t *idx;   // [B,Tq,k_sel]
     void *O;              // [B,Tq,H_q,d_v] bf16
     float *lse;           // [B,Tq,H_q] or nullptr (one layer only)
-    __bf16 *part_o;       // split partials: [n_layers*B*Tq, n_splits, H_q, d_v] bf16, each normalised by its own row sum
+    void *part_o;         // split partials: [n_layers*B*Tq, n_splits, H_q, d_v], each normalised by its own row sum
+    int32_t part_wide;    // 1: they are fp32, 0: bf16
     float *part_ml;       // [n_layers*B*Tq, n_splits, H_q, 2] fp32 (running max in log2 units, sum)
     int32_t B, Tq, Lk, H_q, v_off, row_elems, k_sel;
     int32_t n_splits, split_len; // key slots per split (multiple of 64)

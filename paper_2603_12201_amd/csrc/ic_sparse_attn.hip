@@ -235,20 +235,28 @@ __global__ __launch_bounds__(256, 2) void attn_kernel(AttnArgs a)
                 (l_tot > 0.f) ? (m_run + __builtin_log2f(l_tot)) * 0.6931471805599453f : -INFINITY;
         }
     }
+    // a split stores its own normalised output; the merge weighs the splits by their share of the total row sum
+    auto put = [&](auto *o) __attribute__((always_inline)) {
+        typedef std::remove_pointer_t<decltype(o)> T;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int hr = 4 * g + i;                         // O row of this lane
-        const int hq = 16 * mh + hr;
-        const float l = __shfl(l_tot, hr);                // the sum lives in the lanes with l16 == hr
-        if (hq >= a.H_q) continue;
-        // a split stores its own normalised output (bf16, like the final one); the merge weighs the
-        // splits by their share of the total row sum
-        const float inv = (l > 0.f) ? 1.f / l : 0.f;
-        __bf16 *po = (split ? a.part_o + ((gq * a.n_splits + sp) * a.H_q + hq) * D_V
-                            : (__bf16 *)a.Os[layer] + (qrow * a.H_q + hq) * D_V) + DVW * vh;
+        for (int i = 0; i < 4; ++i) {
+            const int hr = 4 * g + i;                     // O row of this lane
+            const int hq = 16 * mh + hr;
+            const float l = __shfl(l_tot, hr);            // the sum lives in the lanes with l16 == hr
+            if (hq >= a.H_q) continue;
+            const float inv = (l > 0.f) ? 1.f / l : 0.f;
+            T *po = o + hq * D_V + DVW * vh;
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb) po[16 * nb + l16] = (__bf16)(oacc[nb][i] * inv);
-    }
+            for (int nb = 0; nb < NB; ++nb) po[16 * nb + l16] = (T)(oacc[nb][i] * inv);
+        }
+    };
+    const int64_t part = (gq * a.n_splits + sp) * a.H_q * D_V;
+    if (!split)
+        put((__bf16 *)a.Os[layer] + qrow * a.H_q * D_V);
+    else if (a.part_wide)
+        put((float *)a.part_o + part);
+    else
+        put((__bf16 *)a.part_o + part);
 }
 
 // ---- row-slab form (576/512 MLA rows) --------------------------------------------------
@@ -854,19 +862,30 @@ __global__ __launch_bounds__(256, 1) void attn_slab_kernel(AttnArgs a, RestArgs 
             int tx = tid;
             asm volatile("" : "+v"(tx));
             const int o_lane = 32 * (tx >> 6) + (tx & 31), o_hh = (tx >> 5) & 1;
-            __bf16 *o_row = (SPLIT ? a.part_o + (qrow * a.n_splits + sp) * a.H_q * D_V : (__bf16 *)(MULTI ? a.Os[cs.layer] : a.O) + q_cur() * a.H_q * D_V) + o_lane;
+            auto put = [&](auto *o_row) __attribute__((always_inline)) {
+                typedef std::remove_pointer_t<decltype(o_row)> T;
 #pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const int hq = 8 * (i >> 2) + 4 * o_hh + (i & 3); // O row (head) of accumulator element i
-                const float inv = inv4[i >> 2][i & 3];
-                __bf16 *po = o_row + hq * D_V;
-                if (all_heads) {
+                for (int i = 0; i < 16; ++i) {
+                    const int hq = 8 * (i >> 2) + 4 * o_hh + (i & 3); // O row (head) of accumulator element i
+                    const float inv = inv4[i >> 2][i & 3];
+                    T *po = o_row + hq * D_V;
+                    if (all_heads) {
 #pragma unroll
-                    for (int nb = 0; nb < NBW; ++nb) po[128 * nb] = (__bf16)(oacc[nb][i] * inv);
-                } else if (hq < a.H_q) {
+                        for (int nb = 0; nb < NBW; ++nb) po[128 * nb] = (T)(oacc[nb][i] * inv);
+                    } else if (hq < a.H_q) {
 #pragma unroll
-                    for (int nb = 0; nb < NBW; ++nb) po[128 * nb] = (__bf16)(oacc[nb][i] * inv);
+                        for (int nb = 0; nb < NBW; ++nb) po[128 * nb] = (T)(oacc[nb][i] * inv);
+                    }
                 }
+            };
+            if constexpr (SPLIT) {
+                const int64_t part = (qrow * a.n_splits + sp) * a.H_q * D_V + o_lane;
+                if (a.part_wide)
+                    put((float *)a.part_o + part);
+                else
+                    put((__bf16 *)a.part_o + part);
+            } else {
+                put((__bf16 *)(MULTI ? a.Os[cs.layer] : a.O) + q_cur() * a.H_q * D_V + o_lane);
             }
         }
     };
@@ -1332,7 +1351,7 @@ __global__ __launch_bounds__(512, 2) void attn_dense_kernel(AttnArgs a, DenseArg
 // took 14.2 us per layer, now 5.  Up to eight splits are one batch of one slot: then a wave has a (query, head) of 512
 // columns to itself, nothing passes through LDS, and no lane is left without a split (with four slots, two splits of 128
 // queries x 32 heads kept half of the lanes idle in 4096 workgroups: launch and merge took 45.6 us, 38.6 before that form).
-template <int D_V, int SLOTS>
+template <int D_V, int SLOTS, bool WIDE>                // WIDE: fp32 partials
 __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a)
 {
     constexpr int LPS = D_V / 8, kBatch = 8;
@@ -1345,25 +1364,28 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a)
     const int head = blockIdx.y * HEADS + grp;
     const bool live = head < a.H_q;
     const int h = live ? head : 0;
-    const int slot = tid / LPS, v = (tid % LPS) * 8;
+    constexpr int N16 = WIDE ? 2 : 1, CPL = 8 / N16;       // 16-byte loads of a split per thread, columns in each
+    const int slot = tid / LPS, v = (tid % LPS) * CPL;     // columns v + c D_V / N16 + 0 .. CPL - 1: a load of a wave is one stretch
     const float *ml = a.part_ml + ((gq * a.n_splits) * a.H_q + h) * 2;
     const int64_t ml_stride = (int64_t)a.H_q * 2;
-    const __bf16 *po = a.part_o + ((gq * a.n_splits) * a.H_q + h) * D_V + v;
-    const int64_t po_stride = (int64_t)a.H_q * D_V;
+    const unsigned char *po = (const unsigned char *)a.part_o + (((gq * a.n_splits) * a.H_q + h) * D_V + v) * (2 * N16);
+    const int64_t po_stride = (int64_t)a.H_q * D_V * (2 * N16);
     float m = -INFINITY, l = 0.f, o[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) o[e] = 0.f;
     for (int s0 = slot; s0 < a.n_splits; s0 += SLOTS * kBatch) {
-        u32x4 x[kBatch];
+        u32x4 x[kBatch][N16];
         float ms[kBatch], ls[kBatch];
 #pragma unroll
         for (int j = 0; j < kBatch; ++j) {
             const int s = s0 + SLOTS * j;
-            x[j] = u32x4{0u, 0u, 0u, 0u};
+#pragma unroll
+            for (int c = 0; c < N16; ++c) x[j][c] = u32x4{0u, 0u, 0u, 0u};
             ms[j] = -INFINITY;
             ls[j] = 0.f;
             if (s < a.n_splits) {
-                x[j] = *(const u32x4 *)(po + s * po_stride);
+#pragma unroll
+                for (int c = 0; c < N16; ++c) x[j][c] = *(const u32x4 *)(po + s * po_stride + c * (D_V / N16 * 4));
                 ms[j] = ml[s * ml_stride];
                 ls[j] = ml[s * ml_stride + 1];
             }
@@ -1382,8 +1404,13 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a)
             l += sc;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                o[2 * e] += __uint_as_float(x[j][e] << 16) * sc;               // bf16 -> fp32 is a shift
-                o[2 * e + 1] += __uint_as_float(x[j][e] & 0xFFFF0000u) * sc;
+                if constexpr (WIDE) {
+                    o[e] += __uint_as_float(x[j][0][e]) * sc;
+                    o[4 + e] += __uint_as_float(x[j][1][e]) * sc;
+                } else {
+                    o[2 * e] += __uint_as_float(x[j][0][e] << 16) * sc;        // bf16 -> fp32 is a shift
+                    o[2 * e + 1] += __uint_as_float(x[j][0][e] & 0xFFFF0000u) * sc;
+                }
             }
         }
     }
@@ -1391,16 +1418,19 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a)
     if constexpr (SLOTS == 1) {
         if (!live) return;
         const float inv = (l > 0.f) ? 1.f / l : 0.f;
-        typedef __attribute__((ext_vector_type(8))) __bf16 b16x8;
-        b16x8 r;
+        typedef __attribute__((ext_vector_type(CPL))) __bf16 bf16xc;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) r[e] = (__bf16)(o[e] * inv);
-        *(b16x8 *)(out + v) = r;
+        for (int c = 0; c < N16; ++c) {
+            bf16xc r;
+#pragma unroll
+            for (int e = 0; e < CPL; ++e) r[e] = (__bf16)(o[CPL * c + e] * inv);
+            *(bf16xc *)(out + v + c * (D_V / N16)) = r;
+        }
     } else {
         __shared__ __attribute__((aligned(16))) float o_sh[HEADS][SLOTS][D_V];
         __shared__ float m_sh[HEADS][SLOTS], l_sh[HEADS][SLOTS];
         *(f32x4 *)&o_sh[grp][slot][v] = f32x4{o[0], o[1], o[2], o[3]};
-        *(f32x4 *)&o_sh[grp][slot][v + 4] = f32x4{o[4], o[5], o[6], o[7]};
+        *(f32x4 *)&o_sh[grp][slot][WIDE ? v + D_V / 2 : v + 4] = f32x4{o[4], o[5], o[6], o[7]};
         if (v == 0) {
             m_sh[grp][slot] = m;
             l_sh[grp][slot] = l;
@@ -1426,6 +1456,17 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a)
         l = lt;
     }
     if (tid == 0 && a.lse) a.lse[qrow * a.H_q + h] = (l > 0.f) ? (m + __builtin_log2f(l)) * 0.6931471805599453f : -INFINITY;
+}
+
+template <int D_V, int SLOTS, bool WIDE>
+hipError_t launch_merge_t(const AttnArgs &a, hipStream_t st)
+{
+    const unsigned nq = (unsigned)((int64_t)a.n_layers * a.B * a.Tq), H = (unsigned)a.H_q;
+    if (D_V == 512 && a.n_splits <= 8)
+        hipLaunchKernelGGL((attn_merge_kernel<512, 1, WIDE>), dim3(nq, (H + 3) / 4), dim3(256), 0, st, a);
+    else
+        hipLaunchKernelGGL((attn_merge_kernel<D_V, SLOTS, WIDE>), dim3(nq, H), dim3(256), 0, st, a);
+    return hipGetLastError();
 }
 
 template <int D_QK, int D_V, int ROW_F>
@@ -1571,16 +1612,9 @@ hipError_t launch_attn(const AttnArgs &a, int d_qk, int d_v, hipStream_t st)
 hipError_t launch_attn_merge(const AttnArgs &a, int d_v, hipStream_t st)
 {
     if ((int64_t)a.B * a.Tq <= 0) return hipSuccess;
-    const unsigned nq = (unsigned)((int64_t)a.n_layers * a.B * a.Tq), H = (unsigned)a.H_q;
-    if (d_v == 512 && a.n_splits <= 8)
-        hipLaunchKernelGGL((attn_merge_kernel<512, 1>), dim3(nq, (H + 3) / 4), dim3(256), 0, st, a);
-    else if (d_v == 512)
-        hipLaunchKernelGGL((attn_merge_kernel<512, 4>), dim3(nq, H), dim3(256), 0, st, a);
-    else if (d_v == 64)
-        hipLaunchKernelGGL((attn_merge_kernel<64, 32>), dim3(nq, H), dim3(256), 0, st, a);
-    else
-        return hipErrorInvalidValue;
-    return hipGetLastError();
+    if (d_v == 512) return a.part_wide ? launch_merge_t<512, 4, true>(a, st) : launch_merge_t<512, 4, false>(a, st);
+    if (d_v == 64) return a.part_wide ? launch_merge_t<64, 32, true>(a, st) : launch_merge_t<64, 32, false>(a, st);
+    return hipErrorInvalidValue;
 }
 
 } // namespace ic

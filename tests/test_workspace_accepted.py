@@ -19,13 +19,35 @@ def _up(x):
     return (x + 255) // 256 * 256
 
 
+def _bf16_partials(nq, k, H=32):
+    """One layer's attention with its partials in bf16: as many splits of whole tiles as bring nq queries up to 256."""
+    tiles = -(-k // 64)
+    per = -(-tiles // min(tiles, -(-256 // nq)))
+    parts = nq * -(-tiles // per)
+    return 0 if nq >= 256 or per == tiles else _up(parts * H * 512 * 2) + _up(parts * H * 8)
+
+
+@pytest.mark.parametrize("nq", [1, 12, 40, 100, 200, 255, 256])
+def test_attention_with_bf16_partials_is_enough(nq):
+    """The query asks for fp32 partials where a query is split in fewer; what the least took before is still accepted."""
+    import paper_2603_12201_amd as ic
+    L, S = ic.lib(), ic.Status
+    one, k = C.c_void_p(4096), 2048
+    d = ic.AttnDesc(nq, 1, 5000, 32, 576, 512, 0, 576, k, 1 / 24.0)
+    least = _bf16_partials(nq, k)
+    assert L.ic_sparse_attn_workspace(C.byref(d)) >= least and (L.ic_sparse_attn_workspace(C.byref(d)) > 0) == (least > 0)
+    if least:
+        assert L.ic_sparse_attn(C.byref(d), one, one, one, one, None, one, least - 256, None) == S.ERR_WORKSPACE
+
+
 @pytest.mark.parametrize("n, Tq, Lk, k", [(4, 1, 10007, 2048), (3, 2, 100000, 2048), (8, 40, 5000, 2048), (2, 300, 4000, 512)])
 def test_pattern_loss_and_greedy_search_need_one_layer(n, Tq, Lk, k):
     ic, arr = _layers(n, Tq, Lk, k)
     L, S = ic.lib(), ic.Status
     one, refs, buf = C.c_void_p(4096), (C.c_void_p * n)(*([8192] * n)), C.create_string_buffer(n)
     # one layer's attention, or the scores of every row (fewer than 64 MB here)
-    attn = L.ic_sparse_attn_workspace(C.byref(arr[0].at))
+    attn = _bf16_partials(Tq, k)
+    assert attn <= L.ic_sparse_attn_workspace(C.byref(arr[0].at))
     strip = Tq * _up(4 * Lk)
     need = _up(max(attn, strip)) + _up(8 * n) + 256
     assert strip < 64 << 20 and need <= L.ic_pattern_loss_workspace(arr, n)
