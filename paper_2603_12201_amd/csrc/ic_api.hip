@@ -372,17 +372,69 @@ struct Causal {
 };
 constexpr Causal kUnknown = {-1, 0};
 
-// Leading query rows of every sequence that the dense form takes: the rows that select exactly the keys 0 .. pos0 + t, of
-// which they see at most k_sel and all below lk.  Its workgroups walk their keys one tile after the other, so where they leave most of the chip idle and the
-// walk is long (a short chunk behind a prefix), the forms that split a selection over workgroups are the faster ones.
-int dense_queries(const ic_attn_desc *d, int n_layers, Causal c)
+// Leading query rows of every sequence that the dense form can take: the rows that select exactly the keys 0 .. pos0 + t, of
+// which they see at most k_sel and all below lk.
+int prefix_queries(const ic_attn_desc *d, Causal c)
 {
-    if (n_layers != 1 || c.pos0 < 0 || attn_resident(d) != 256 || d->d_v != 512 || d->B > 65535) return 0;   // (B: grid.y)
+    if (c.pos0 < 0 || attn_resident(d) != 256 || d->d_v != 512 || d->B > 65535) return 0;   // (B: grid.y)
     const int32_t keys = c.lk < d->Lk ? c.lk : d->Lk;
-    int64_t n = (d->k_sel < keys ? d->k_sel : keys) - c.pos0;
-    n = n < 0 ? 0 : (n > d->Tq ? d->Tq : n);
-    const int64_t blocks = (n * d->H_q + 63) / 64 * d->B, tiles = (c.pos0 + n + 63) / 64;
-    return n > 0 && (blocks >= 128 || tiles <= 4) ? (int)n : 0;
+    const int64_t n = (d->k_sel < keys ? d->k_sel : keys) - c.pos0;
+    return (int)(n < 0 ? 0 : (n > d->Tq ? d->Tq : n));
+}
+
+// Times in tiles of 64 keys of a row-form workgroup (about 2 us), launches and what a workgroup pays once included.
+// Rows of one or more layers in the row form: attn_splits() where they are split or all resident, otherwise chains of
+// queries, which leave the tiles behind a causal row's last entry out.
+double row_time(const ic_attn_desc *d, int n_layers, Causal c, size_t ws_bytes, int64_t narrow)
+{
+    const int64_t nq = (int64_t)n_layers * d->B * d->Tq, wgs = attn_resident(d), tiles = (d->k_sel + 63) / 64;
+    if (nq <= wgs) {
+        const Splits sp = attn_splits(d, n_layers, ws_bytes, narrow);
+        return (double)((nq * sp.n + wgs - 1) / wgs * (sp.len / 64 + 2)) + (sp.n > 1 ? 2 : 0);
+    }
+    double mean = (double)tiles;
+    if (c.pos0 >= 0) mean = std::min(mean, std::max(3.0, (c.pos0 + 0.5 * (d->Tq + 1)) / 64));
+    return (double)((nq + wgs - 1) / wgs) * mean + 2;
+}
+
+// The first n rows of every sequence in the dense form: a workgroup per 64 (query, head) rows, longest first, 0.83 times per
+// 64 keys; more workgroups than CUs leave half of the longest's walk uneven at the end.
+double dense_time(const ic_attn_desc *d, int n, int64_t pos0)
+{
+    const double blocks = (double)(((int64_t)n * d->H_q + 63) / 64 * d->B), longest = (pos0 + n) / 64.0, mean = (pos0 + 0.5 * n) / 64;
+    return 0.83 * (blocks <= 256 ? longest + 2 : std::max(longest + 2, blocks * (mean + 2) / 256 + 0.5 * longest));
+}
+
+ic_attn_desc rows_behind(const ic_attn_desc *d, int n)
+{
+    ic_attn_desc t = *d;
+    t.Tq = d->Tq - n;
+    return t;
+}
+
+// How many of them it takes, for one of n_layers layers that the row form would take together.  Its workgroups walk their
+// keys one tile after the other and do not share them between sequences, so it has to fill the chip or be short; and the rows
+// behind (ws_bytes: workspace for their splits) are a launch of their own, which has to save more than it costs.  Measured,
+// four layers, k = 2048, row form / dense form and what is left: 4 x 256 rows behind 1800 keys 897 / 671 us, behind 1900 keys
+// 897 / 966; 64 x 8 rows behind 2044 keys 575 / 643; 128 x 1 rows behind 2000 keys, four layers together 222 / 261.
+int dense_queries(const ic_attn_desc *d, int n_layers, Causal c, size_t ws_bytes)
+{
+    const int n = prefix_queries(d, c);
+    const int64_t blocks = ((int64_t)n * d->H_q + 63) / 64 * d->B, tiles = (c.pos0 + n + 63) / 64;
+    if (n == 0 || (blocks < 128 && tiles > 4)) return 0;
+    const double whole = row_time(d, n_layers, c, ws_bytes, attn_max_splits(d, 1)) / n_layers, dense = dense_time(d, n, c.pos0);
+    if (n == d->Tq) return dense <= 1.08 * whole ? n : 0;
+    const ic_attn_desc t = rows_behind(d, n);
+    return dense + row_time(&t, 1, Causal{c.pos0 + n, c.lk}, ws_bytes, INT64_MAX) + 2 <= 0.85 * whole ? n : 0;
+}
+
+// Workspace that serves the rows behind best.
+size_t dense_tail_bytes(const ic_attn_desc *d, int n_layers, Causal c)
+{
+    const int n = dense_queries(d, n_layers, c, SIZE_MAX);
+    if (n == 0 || n == d->Tq) return 0;
+    const ic_attn_desc t = rows_behind(d, n);
+    return attn_splits(&t, 1, SIZE_MAX, INT64_MAX).bytes;
 }
 
 // Leading query rows of every sequence that may be whole prefixes when nothing is known about idx: in a causal selection
@@ -395,7 +447,7 @@ int lead_queries(const ic_attn_desc *d)
 {
     const int64_t pos0 = (int64_t)d->Lk - d->Tq;
     if (pos0 < 0) return 0;
-    const int n = dense_queries(d, 1, Causal{pos0, d->Lk});
+    const int n = prefix_queries(d, Causal{pos0, d->Lk});
     return (int64_t)n * ((d->k_sel + 63) / 64) >= 16 * 256 && (int64_t)n * d->H_q >= 128 * 64 ? n : 0;
 }
 
@@ -466,9 +518,10 @@ ic::AttnArgs attn_args(const ic_layer *layers, int n_layers, const int32_t *idx,
     return a;
 }
 
-// tail: rows of a launch that has been divided; they were not split before, so their partials are fp32
+// skipped > 0: the last Tq rows of every sequence, behind `skipped` others that another launch has taken (Q, O, idx and lse
+// point to sequence 0's first one).  Undivided they were not split, so their partials are fp32.
 ic_status run_attn_layers(const ic_layer *layers, int n_layers, const int32_t *idx, float *lse, void *ws, size_t ws_bytes,
-                          hipStream_t st, const ic_paged_cache *pc, Causal c, bool tail = false);
+                          hipStream_t st, const ic_paged_cache *pc, Causal c, int skipped = 0);
 
 // Rows row0 .. row0 + n - 1 of sequence b as a problem of their own.
 ic_layer layer_rows(const ic_layer *L, int b, int row0, int n)
@@ -515,7 +568,7 @@ ic_status run_attn_lead(const ic_layer *L, const int32_t *idx, const int32_t *le
         ic_layer t = layer_rows(L, b, n, d->Tq - n);
         t.KV = r.KV;
         ic_status s = run_attn_layers(&t, 1, idx + (row + n) * d->k_sel, lse ? lse + (row + n) * d->H_q : nullptr, ws, ws_bytes, st,
-                                      nullptr, kUnknown, true);
+                                      nullptr, kUnknown, n);
         if (s != IC_OK) return s;
     }
     return IC_OK;
@@ -524,34 +577,12 @@ ic_status run_attn_lead(const ic_layer *L, const int32_t *idx, const int32_t *le
 // c: idx is this library's own (rows that can hold fewer than k_sel entries end in -1s, and the kernels leave their empty
 // tiles out) or the caller's (kUnknown)
 ic_status run_attn_layers(const ic_layer *layers, int n_layers, const int32_t *idx, float *lse, void *ws, size_t ws_bytes,
-                          hipStream_t st, const ic_paged_cache *pc, Causal c, bool tail)
+                          hipStream_t st, const ic_paged_cache *pc, Causal c, int skipped)
 {
     const ic_attn_desc *d = &layers[0].at;
     ic::AttnArgs a = attn_args(layers, n_layers, idx, lse, pc, c);
-    if (const int nd = dense_queries(d, n_layers, c)) {
-        {
-            ProfScope ps(2, st);               // (the rows behind them are timed by their own launch)
-            const ic::DenseArgs da{nd, (int32_t)c.pos0, nullptr, 0};
-            hipError_t e = ic::launch_attn_dense(a, da, st);
-            if (e != hipSuccess) return fail(IC_ERR_HIP, "dense attention launch failed: %s", hipGetErrorString(e));
-        }
-        if (nd == d->Tq) return IC_OK;
-        for (int b = 0; b < d->B; ++b) {       // the other rows, a sequence at a time
-            ic_layer r = layer_rows(layers, b, nd, d->Tq - nd);
-            const int64_t row = (int64_t)b * d->Tq + nd;
-            ic_paged_cache pb;
-            if (pc) {
-                pb = *pc;
-                if (pb.page_table) pb.page_table += (int64_t)b * pb.max_pages;
-            }
-            if (!pc || !pc->page_table) r.KV = (const char *)r.KV + (int64_t)b * d->Lk * d->row_elems * 2;
-            ic_status s = run_attn_layers(&r, 1, idx + row * d->k_sel, lse ? lse + row * d->H_q : nullptr, ws, ws_bytes, st,
-                                          pc ? &pb : nullptr, Causal{c.pos0 + nd, c.lk}, true);
-            if (s != IC_OK) return s;
-        }
-        return IC_OK;
-    }
-    const Splits sp = attn_splits(d, n_layers, ws_bytes, tail ? INT64_MAX : attn_max_splits(d, 1));
+    if (d->B > 1) a.row_gap = skipped;
+    const Splits sp = attn_splits(d, n_layers, ws_bytes, skipped > 0 ? INT64_MAX : attn_max_splits(d, 1));
     a.n_splits = sp.n;
     a.split_len = sp.len;
     if (sp.n > 1) {
@@ -570,6 +601,25 @@ ic_status run_attn_layers(const ic_layer *layers, int n_layers, const int32_t *i
         if (e != hipSuccess) return fail(IC_ERR_HIP, "attention merge launch failed: %s", hipGetErrorString(e));
     }
     return IC_OK;
+}
+
+// One layer whose first nd rows of every sequence are whole prefixes: those in the dense form, then the others.
+ic_status run_attn_dense(const ic_layer *L, int nd, const int32_t *idx, void *ws, size_t ws_bytes, hipStream_t st,
+                         const ic_paged_cache *pc, Causal c)
+{
+    const ic_attn_desc *d = &L->at;
+    {
+        ProfScope ps(2, st);                   // (the rows behind them are timed by their own launch)
+        const ic::DenseArgs da{nd, (int32_t)c.pos0, nullptr, 0};
+        hipError_t e = ic::launch_attn_dense(attn_args(L, 1, idx, nullptr, pc, c), da, st);
+        if (e != hipSuccess) return fail(IC_ERR_HIP, "dense attention launch failed: %s", hipGetErrorString(e));
+    }
+    if (nd == d->Tq) return IC_OK;
+    ic_layer r = *L;
+    r.at = rows_behind(d, nd);
+    r.Q = (const char *)r.Q + (int64_t)nd * d->H_q * d->d_qk * 2;
+    r.O = (char *)r.O + (int64_t)nd * d->H_q * d->d_v * 2;
+    return run_attn_layers(&r, 1, idx + (int64_t)nd * d->k_sel, nullptr, ws, ws_bytes, st, pc, Causal{c.pos0 + nd, c.lk}, nd);
 }
 
 ic_layer attn_layer(const ic_attn_desc *d, const void *Q, const void *KV, void *O)
@@ -739,8 +789,10 @@ size_t ic_forward_stack_workspace(const ic_layer *layers, int32_t n_layers)
     for (int l = 0; l < n_layers; ++l) {
         size_t a = ic_sparse_attn_workspace(&layers[l].at);
         size_t b = layers[l].q ? ic_indexer_topk_workspace(&layers[l].ix) : 0;
+        const bool ok = check_attn(&layers[l].at) == IC_OK;
+        if (ok && layers[l].q && layers[l].ix.q_pos0 >= 0) a = std::max(a, dense_tail_bytes(&layers[l].at, 1, Causal{layers[l].ix.q_pos0, layers[l].ix.Lk}));
         // which layers are Full is not known here: room for any run of layers of this shape
-        if (a > 0) {
+        if (ok && attn_ws_bytes(&layers[l].at) > 0) {
             const int run = n_layers - l < ic::kMaxBatchLayers ? n_layers - l : ic::kMaxBatchLayers;
             for (int m = 2; m <= run && memcmp(&layers[l + m - 1].at, &layers[l].at, sizeof layers[l].at) == 0; ++m) {
                 const size_t am = attn_best_bytes(&layers[l].at, m);
@@ -788,11 +840,13 @@ static ic_status forward_stack_impl(const ic_layer *layers, int32_t n_layers, co
         }
         int run = 1;                           // this layer and the Shared layers behind it
         while (l + run < n_layers && !full_mask[l + run]) ++run;
-        int m = dense_queries(&L->at, 1, known) ? 1 : attn_batch(L, run, pc);
+        int m = attn_batch(L, run, pc);
         while (m > 1 && attn_best_bytes(&L->at, m) > workspace_bytes) --m;
-        s = run_attn_layers(L, m, idx_cache, nullptr, workspace, workspace_bytes, st, pc, known);
+        const int nd = dense_queries(&L->at, m, known, workspace_bytes);
+        s = nd ? run_attn_dense(L, nd, idx_cache, workspace, workspace_bytes, st, pc, known)
+               : run_attn_layers(L, m, idx_cache, nullptr, workspace, workspace_bytes, st, pc, known);
         if (s != IC_OK) return s;
-        l += m - 1;
+        if (!nd) l += m - 1;
     }
     return IC_OK;
 }

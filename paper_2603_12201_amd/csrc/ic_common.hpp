@@ -93,6 +93,7 @@ struct AttnArgs {
     // holds min(k_sel, causal_pos0 + t + 1) entries followed by -1 only, and the tiles behind them need no work;
     // < 0: nothing is known about idx
     int64_t causal_pos0;
+    int32_t row_gap;      // rows of Q, idx, O and lse between two sequences' Tq rows (0: one follows the other)
     int32_t n_layers;
     const void *Qs[kMaxBatchLayers];
     const void *KVs[kMaxBatchLayers];

@@ -327,8 +327,8 @@ __device__ __forceinline__ unsigned rows_mask(unsigned long long ba, unsigned lo
 
 // SPLIT: blockIdx.y selects a.split_len key slots of the query and the result is a partial
 // (unnormalised accumulators, reference maximum, row sum) for the merge kernel.
-// MULTI: a.n_layers layers in one launch (a chain that has to know a query's layer spills seven registers more, 2 % of a
-// long chain's time, so one layer alone does without).
+// MULTI: a.n_layers layers in one launch, or the last rows of several sequences (a.row_gap); a query's place in the tensors
+// is then not its number (its own instance: a chain that has to know a query's layer took 2 % longer).
 // REST: the rows of one sequence behind those that the dense form has taken.  How many that are is device data, so the
 // workgroups, as many as for all rows, find out first and share what is left (one round trip to memory, about 1 us).
 template <int D_QK, int D_V, bool PG, bool SPLIT, bool MULTI, bool REST>   // value columns = the first D_V features of a row; PG as above
@@ -384,22 +384,23 @@ __global__ __launch_bounds__(256, 1) void attn_slab_kernel(AttnArgs a, RestArgs 
     // nt: tiles of the query in the chained stream.  When the selection is known to be a causal top-k, a row near the
     // start of a sequence holds fewer than k_sel entries and ends in -1s: its tiles behind the last entry are left
     // out (never fewer than three per query: the stream looks three tiles ahead and knows two queries at a time).
-    struct Src { const int32_t *idx_row; const unsigned short *kv; int64_t q; int layer, b, len, nt; bool live; };   // q: query within its layer
+    struct Src { const int32_t *idx_row; const unsigned short *kv; int64_t q; int layer, b, len, nt; bool live; };   // q: row of the layer's tensors
     auto src_of = [&](int64_t q) {
         Src r;
         r.live = q < nq;
         const int64_t gq = r.live ? q : (int64_t)blockIdx.x;          // a dead source still reads valid memory
         r.layer = MULTI ? layer_of(a, gq) : 0;
         const int64_t qq = MULTI ? gq - r.layer * nq_layer : gq;
-        if constexpr (MULTI) r.q = qq;
         r.b = (int)(qq / a.Tq);
+        const int64_t row = MULTI ? qq + (int64_t)r.b * a.row_gap : qq;
+        if constexpr (MULTI) r.q = row;
         r.nt = ntiles;
         if (!SPLIT && a.causal_pos0 >= 0) {
             const int64_t held = a.causal_pos0 + qq % a.Tq + 1;       // entries the row can hold
             if (held < a.k_sel) r.nt = max(3, (int)((held + kSlabTile - 1) / kSlabTile));
             r.nt = min(r.nt, ntiles);
         }
-        r.idx_row = a.idx + qq * a.k_sel;
+        r.idx_row = a.idx + row * a.k_sel;
         r.kv = (const unsigned short *)(MULTI ? a.KVs[r.layer] : a.KV) + (PG && a.pv.page_table ? 0 : (int64_t)r.b * a.Lk * a.row_elems);
         r.len = PG && a.pv.seq_lens ? min(a.pv.seq_lens[r.b], a.Lk) : a.Lk;   // ragged cache: rows of this sequence
         return r;
@@ -1359,7 +1360,8 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a)
     static_assert(SLOTS == 1 || 2 * GROUP >= D_V, "two columns per thread at the end");
     const int64_t gq = blockIdx.x;
     const int layer = layer_of(a, gq);
-    const int64_t qrow = gq - (int64_t)layer * a.B * a.Tq;
+    int64_t qrow = gq - (int64_t)layer * a.B * a.Tq;
+    if (a.row_gap) qrow += (int64_t)((unsigned)qrow / (unsigned)a.Tq) * a.row_gap;
     const int grp = threadIdx.x / GROUP, tid = threadIdx.x % GROUP;
     const int head = blockIdx.y * HEADS + grp;
     const bool live = head < a.H_q;
@@ -1520,7 +1522,7 @@ hipError_t launch_slab(const AttnArgs &a, hipStream_t st)
     constexpr size_t lds = slab_lds<D_QK>;
     const bool pg = a.pv.seq_lens || a.pv.page_table;
     if (a.n_splits > 1) return pg ? launch_slab_t<D_QK, D_V, true, true, true>(a, lds, st) : launch_slab_t<D_QK, D_V, false, true, true>(a, lds, st);
-    if (a.n_layers > 1) return pg ? launch_slab_t<D_QK, D_V, true, false, true>(a, lds, st) : launch_slab_t<D_QK, D_V, false, false, true>(a, lds, st);
+    if (a.n_layers > 1 || a.row_gap) return pg ? launch_slab_t<D_QK, D_V, true, false, true>(a, lds, st) : launch_slab_t<D_QK, D_V, false, false, true>(a, lds, st);
     return pg ? launch_slab_t<D_QK, D_V, true, false, false>(a, lds, st) : launch_slab_t<D_QK, D_V, false, false, false>(a, lds, st);
 }
 

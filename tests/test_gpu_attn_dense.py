@@ -19,6 +19,10 @@ CASES = [
     (1, 320, 0, 32, 256, 576, 0, 1 / 24.0),       # 256 dense rows, 64 with a selection
     (2, 300, 0, 16, 130, 576, 0, 1 / 24.0),       # the same for two sequences
     (1, 257, 0, 32, 256, 576, 0, 1 / 24.0),       # one row with a selection
+    (5, 70, 200, 32, 256, 576, 0, 1 / 24.0),      # few rows with a selection in each of five sequences: one launch, split
+    (9, 90, 200, 32, 256, 576, 0, 1 / 24.0),      # more of them than workgroups: chains over sequences
+    (9, 90, 200, 32, 256, 576, 64, 1 / 24.0),     # paged
+    (64, 8, 252, 32, 256, 576, 0, 1 / 24.0),      # four and four rows of many sequences
     (2, 190, 0, 32, 256, 576, 64, 1 / 24.0),      # paged
     (2, 150, 0, 32, 128, 576, 64, 1 / 24.0),      # paged, with a selection
     (1, 300, 700, 32, 1100, 576, 0, 1 / 24.0),    # behind a prefix
