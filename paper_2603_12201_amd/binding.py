@@ -231,8 +231,8 @@ def sparse_attn_workspace(desc):
 def sparse_attn(Q, KV, idx, d_v, v_off, sm_scale, want_lse=False, workspace=None, stream=None, out=None):
     """ic_sparse_attn: returns O [B,Tq,H_q,d_v] bf16 (and lse [B,Tq,H_q] fp32 if want_lse).
 
-    Long selections that may be causal run through ic_sparse_attn_lead, with a few kilobytes of its own allocated here on
-    the call's stream; an empty `workspace` asks for ic_sparse_attn on every row."""
+    Long selections that may be causal run through ic_sparse_attn_lead, with a workspace of its own (up to 17 MB) allocated
+    here on the call's stream; an empty `workspace` asks for ic_sparse_attn on every row."""
     import torch
     d = attn_desc(Q, KV, idx, d_v, v_off, sm_scale)
     fn, need = lib().ic_sparse_attn, sparse_attn_workspace(d)

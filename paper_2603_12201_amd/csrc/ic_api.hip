@@ -440,16 +440,37 @@ size_t dense_tail_bytes(const ic_attn_desc *d, int n_layers, Causal c)
 // Leading query rows of every sequence that may be whole prefixes when nothing is known about idx: in a causal selection
 // for the last Tq of Lk positions, rows t < k_sel - (Lk - Tq).  Their number is then counted on the device (lead_kernel)
 // and the dense form and what follows it read the counts.  Without the dense form a row costs k_sel / 64 tile times of a CU
-// however little of it is filled; the count and the second launch cost about as much as 16 rounds of them. Measured on
-// causal selections with k = 2048: one layer of 4096 rows 890 -> 660 us; six layers' similarity matrix at 3000 rows
-// 13.7 -> 5.9 ms.
-int lead_queries(const ic_attn_desc *d)
+// however little of it is filled.  The rows behind the candidates go along with the candidates that the counts leave, or
+// are split over the chip on their own.  Whichever of the two gains more on a causal selection than it loses on any other is
+// taken if that difference is a tenth of the row form's time; the scan and the launches that find nothing to do cost 5.5
+// tile times.  Measured, k = 2048, row form / this for causal rows / for other rows: 2048 rows 414 / 161 / 429 us, 4096
+// rows 827 / 596 / 839, 4 x 2060 rows 1677 / 642 / 1703; not taken: 700 rows behind 1700 keys 160 / 173 / 166.
+struct LeadPlan {
+    int n;
+    bool along;
+};
+LeadPlan lead_plan(const ic_attn_desc *d)
 {
-    const int64_t pos0 = (int64_t)d->Lk - d->Tq;
-    if (pos0 < 0) return 0;
-    const int n = prefix_queries(d, Causal{pos0, d->Lk});
-    return (int64_t)n * ((d->k_sel + 63) / 64) >= 16 * 256 && (int64_t)n * d->H_q >= 128 * 64 ? n : 0;
+    const int64_t pos0 = (int64_t)d->Lk - d->Tq, tiles = (d->k_sel + 63) / 64;
+    const int n = pos0 < 0 ? 0 : prefix_queries(d, Causal{pos0, d->Lk});
+    const LeadPlan none = {0, false};
+    if (n == 0) return none;
+    auto unsplit = [&](int64_t rows) { return rows == 0 ? 0. : (double)((d->B * rows + 255) / 256 * tiles + 2); };
+    const double whole = row_time(d, 1, kUnknown, SIZE_MAX, attn_max_splits(d, 1)), dense = dense_time(d, n, pos0) + 5.5;
+    const ic_attn_desc t = rows_behind(d, n);
+    // gain on causal rows minus loss on others
+    const double along = whole - (dense + unsplit(t.Tq)) - (unsplit(d->Tq) + 5.5 - whole);
+    double apart = 2 * whole;
+    if (t.Tq > 0 && (int64_t)d->B * t.Tq < 256) {
+        const double tail = row_time(&t, 1, kUnknown, SIZE_MAX, INT64_MAX);
+        apart -= dense + tail + unsplit(n) + tail + 5.5;
+    } else {
+        apart = along;                         // (nothing to split)
+    }
+    if (std::max(along, apart) < 0.1 * whole) return none;
+    return {n, along >= apart};
 }
+int lead_queries(const ic_attn_desc *d) { return lead_plan(d).n; }
 
 int lead_chunks(int n) { return (n + ic::kLeadChunk - 1) / ic::kLeadChunk; }
 
@@ -459,14 +480,30 @@ size_t lead_bytes(const ic_attn_desc *d, int n_tensors)
     return n ? align_up((size_t)n_tensors * d->B * lead_chunks(n) * sizeof(int32_t)) : 0;
 }
 
+// Workgroups per sequence that share the rows left of it, in tile times: rounds of all sequences' workgroups, each as long as
+// the longest chain and two tiles.
+int rest_workgroups(const ic_attn_desc *d, int rows)
+{
+    const int64_t tiles = (d->k_sel + 63) / 64;
+    if (tiles < 3) return rows;                // (no chains)
+    int best = 1;
+    int64_t cost = INT64_MAX;
+    for (int g = 1; g <= rows && g <= 256; ++g) {
+        const int64_t c = ((int64_t)d->B * g + 255) / 256 * ((rows + g - 1) / g * tiles + 2);
+        if (c <= cost) {
+            cost = c;
+            best = g;
+        }
+    }
+    return best;
+}
+
 // Partials of the rows behind the candidates where they are split over the chip on their own.
 size_t lead_tail_bytes(const ic_attn_desc *d)
 {
-    const int n = lead_queries(d);
-    if (n == 0 || n == d->Tq || d->Tq - n >= 256) return 0;
-    ic_attn_desc t = *d;
-    t.B = 1;
-    t.Tq = d->Tq - n;
+    const LeadPlan lp = lead_plan(d);
+    if (lp.n == 0 || lp.n == d->Tq || lp.along) return 0;
+    const ic_attn_desc t = rows_behind(d, lp.n);
     return attn_splits(&t, 1, SIZE_MAX, INT64_MAX).bytes;
 }
 
@@ -523,55 +560,38 @@ ic::AttnArgs attn_args(const ic_layer *layers, int n_layers, const int32_t *idx,
 ic_status run_attn_layers(const ic_layer *layers, int n_layers, const int32_t *idx, float *lse, void *ws, size_t ws_bytes,
                           hipStream_t st, const ic_paged_cache *pc, Causal c, int skipped = 0);
 
-// Rows row0 .. row0 + n - 1 of sequence b as a problem of their own.
-ic_layer layer_rows(const ic_layer *L, int b, int row0, int n)
-{
-    const ic_attn_desc *d = &L->at;
-    ic_layer r = *L;
-    r.at.B = 1;
-    r.at.Tq = n;
-    const int64_t row = (int64_t)b * d->Tq + row0;
-    r.Q = (const char *)r.Q + row * d->H_q * d->d_qk * 2;
-    r.O = (char *)r.O + row * d->H_q * d->d_v * 2;
-    return r;
-}
-
 // One layer whose index tensor has counted leading rows: those (lead) in the dense form unless `dense` is off, then the
 // others.  lead2: counts of a second index tensor; only the rows that are leading in both are left out.
 ic_status run_attn_lead(const ic_layer *L, const int32_t *idx, const int32_t *lead, const int32_t *lead2, bool dense, float *lse,
                         void *ws, size_t ws_bytes, hipStream_t st)
 {
     const ic_attn_desc *d = &L->at;
-    const int n = lead_queries(d), n_chunks = lead_chunks(n);
+    const LeadPlan lp = lead_plan(d);
+    const int n = lp.n, n_chunks = lead_chunks(n);
     if (dense) {
         ProfScope ps(2, st);
         const ic::DenseArgs da{n, d->Lk - d->Tq, lead, n_chunks};
         hipError_t e = ic::launch_attn_dense(attn_args(L, 1, idx, lse, nullptr, kUnknown), da, st);
         if (e != hipSuccess) return fail(IC_ERR_HIP, "dense attention launch failed: %s", hipGetErrorString(e));
     }
-    // The rows behind the n candidates go along where they fill the chip; a few of them are split over it on their own.
-    const bool all = d->Tq - n >= 256;
-    for (int b = 0; b < d->B; ++b) {
-        const int64_t row = (int64_t)b * d->Tq;
-        ic_layer r = layer_rows(L, b, 0, all ? d->Tq : n);
-        r.KV = (const char *)r.KV + (int64_t)b * d->Lk * d->row_elems * 2;
-        {
-            ProfScope ps(2, st);
-            ic::AttnArgs a = attn_args(&r, 1, idx + row * d->k_sel, lse ? lse + row * d->H_q : nullptr, nullptr, kUnknown);
-            a.n_splits = 1;
-            a.split_len = (d->k_sel + 63) / 64 * 64;
-            const ic::RestArgs ra{lead + (int64_t)b * n_chunks, lead2 + (int64_t)b * n_chunks, n_chunks, r.at.Tq};
-            hipError_t e = ic::launch_attn_rest(a, ra, st);
-            if (e != hipSuccess) return fail(IC_ERR_HIP, "sparse attention launch failed: %s", hipGetErrorString(e));
-        }
-        if (all || n == d->Tq) continue;
-        ic_layer t = layer_rows(L, b, n, d->Tq - n);
-        t.KV = r.KV;
-        ic_status s = run_attn_layers(&t, 1, idx + (row + n) * d->k_sel, lse ? lse + (row + n) * d->H_q : nullptr, ws, ws_bytes, st,
-                                      nullptr, kUnknown, n);
-        if (s != IC_OK) return s;
+    const bool along = lp.along;
+    {
+        ProfScope ps(2, st);
+        ic::AttnArgs a = attn_args(L, 1, idx, lse, nullptr, kUnknown);
+        a.n_splits = 1;
+        a.split_len = (d->k_sel + 63) / 64 * 64;
+        const int rows = along ? d->Tq : n;
+        const ic::RestArgs ra{lead, lead2, n_chunks, rows, rest_workgroups(d, rows)};
+        hipError_t e = ic::launch_attn_rest(a, ra, st);
+        if (e != hipSuccess) return fail(IC_ERR_HIP, "sparse attention launch failed: %s", hipGetErrorString(e));
     }
-    return IC_OK;
+    if (along || n == d->Tq) return IC_OK;
+    ic_layer r = *L;
+    r.at = rows_behind(d, n);
+    r.Q = (const char *)r.Q + (int64_t)n * d->H_q * d->d_qk * 2;
+    r.O = (char *)r.O + (int64_t)n * d->H_q * d->d_v * 2;
+    return run_attn_layers(&r, 1, idx + (int64_t)n * d->k_sel, lse ? lse + (int64_t)n * d->H_q : nullptr, ws, ws_bytes, st, nullptr,
+                           kUnknown, n);
 }
 
 // c: idx is this library's own (rows that can hold fewer than k_sel entries end in -1s, and the kernels leave their empty
@@ -970,7 +990,9 @@ size_t ic_similarity_matrix_workspace(const ic_layer *layers, int32_t n_layers)
         const size_t a = attn_query_bytes(&layers[l].at);
         if (a > at) at = a;
     }
-    return sim_o_bytes(&layers[0].at) + align_up(at) + sim_lead_bytes(layers, n_layers);
+    const size_t lb = sim_lead_bytes(layers, n_layers);
+    if (lb) at = std::max(at, lead_tail_bytes(&layers[0].at));
+    return sim_o_bytes(&layers[0].at) + align_up(at) + lb;
 }
 
 ic_status ic_similarity_matrix(const ic_layer *layers, int32_t n_layers, const int32_t *const *idx_layers, double *S,

@@ -133,10 +133,11 @@ struct DenseArgs {
     int32_t n_chunks;
 };
 
-// The rows of one sequence that are left: from the first row that is not a leading one in both tensors up to n_rows.
+// The rows that are left: of every sequence, from the first row that is not a leading one in both tensors up to n_rows.
 struct RestArgs {
-    const int32_t *lead, *lead2;                 // [n_chunks] chunk counts
+    const int32_t *lead, *lead2;                 // [B][n_chunks] chunk counts
     int32_t n_chunks, n_rows;
+    int32_t wgs;                                 // workgroups per sequence
 };
 
 // Rows of a comparison whose second tensor is the first one: the rows that are leading in both index tensors.

@@ -329,19 +329,23 @@ __device__ __forceinline__ unsigned rows_mask(unsigned long long ba, unsigned lo
 // (unnormalised accumulators, reference maximum, row sum) for the merge kernel.
 // MULTI: a.n_layers layers in one launch, or the last rows of several sequences (a.row_gap); a query's place in the tensors
 // is then not its number (its own instance: a chain that has to know a query's layer took 2 % longer).
-// REST: the rows of one sequence behind those that the dense form has taken.  How many that are is device data, so the
+// REST: the rows of sequence blockIdx.y behind those that the dense form has taken.  How many that are is device data, so the
 // workgroups, as many as for all rows, find out first and share what is left (one round trip to memory, about 1 us).
 template <int D_QK, int D_V, bool PG, bool SPLIT, bool MULTI, bool REST>   // value columns = the first D_V features of a row; PG as above
 __global__ __launch_bounds__(256, 1) void attn_slab_kernel(AttnArgs a, RestArgs ra)
 {
     if constexpr (REST) {
-        const int t0 = __builtin_amdgcn_readfirstlane(min(lead_rows(ra.lead, ra.n_chunks), lead_rows(ra.lead2, ra.n_chunks)));
+        const int64_t bs = blockIdx.y, o = bs * ra.n_chunks;
+        const int t0 = __builtin_amdgcn_readfirstlane(min(lead_rows(ra.lead + o, ra.n_chunks), lead_rows(ra.lead2 + o, ra.n_chunks)));
         if (t0 + (int)blockIdx.x >= ra.n_rows && t0 + (int)gridDim.x > ra.n_rows) return;   // no chain, and no row for it
+        const int64_t row = bs * a.Tq + t0;
         a.Tq = ra.n_rows - t0;
-        a.Q = (const __bf16 *)a.Q + (int64_t)t0 * a.H_q * D_QK;
-        a.O = (__bf16 *)a.O + (int64_t)t0 * a.H_q * D_V;
-        a.idx += (int64_t)t0 * a.k_sel;
-        if (a.lse) a.lse += (int64_t)t0 * a.H_q;
+        a.Q = (const __bf16 *)a.Q + row * a.H_q * D_QK;
+        a.KV = (const __bf16 *)a.KV + bs * a.Lk * a.row_elems;
+        a.O = (__bf16 *)a.O + row * a.H_q * D_V;
+        a.idx += row * a.k_sel;
+        if (a.lse) a.lse += row * a.H_q;
+        a.B = 1;
     }
     constexpr int KS = D_QK / 32;                         // contraction steps of S^T = 16-byte chunks per gather lane
     constexpr int ROWB = D_QK * 2 + kSlabPad;             // LDS row stride
@@ -1508,7 +1512,8 @@ hipError_t launch_slab_t(const AttnArgs &a, size_t lds, hipStream_t st, const Re
         }
         if (wgs > n_cu) wgs = n_cu;
     }
-    dim3 grid((unsigned)wgs, (unsigned)(SPLIT ? a.n_splits : 1));
+    if (REST) wgs = ra.wgs;
+    dim3 grid((unsigned)wgs, (unsigned)(REST ? a.B : SPLIT ? a.n_splits : 1));
     hipLaunchKernelGGL((attn_slab_kernel<D_QK, D_V, PG, SPLIT, MULTI, REST>), grid, dim3(256), lds, st, a, ra);
     return hipGetLastError();
 }
@@ -1526,50 +1531,65 @@ hipError_t launch_slab(const AttnArgs &a, hipStream_t st)
     return pg ? launch_slab_t<D_QK, D_V, true, false, false>(a, lds, st) : launch_slab_t<D_QK, D_V, false, false, false>(a, lds, st);
 }
 
-// Counts of LeadArgs: a workgroup per chunk, four waves with four rows each, a row's entries in one pass (a wave reads 1 KB
-// per instruction; 2048 rows of 2048 entries are 16 MB, 6 us).
-__global__ __launch_bounds__(256) void lead_kernel(LeadArgs a)
+// Counts of LeadArgs: a workgroup per chunk, a wave per row, whose entries are all requested before the first is looked at
+// (2048 rows of 2048 entries are 16 MB: 9 us; four rows per wave, a kilobyte at a time, were one latency after the other
+// and took 23).
+__global__ __launch_bounds__(64 * kLeadChunk) void lead_kernel(LeadArgs a)
 {
-    constexpr int N = kLeadChunk / 4;
-    __shared__ int bad[4];
+    constexpr int U = 8;
+    __shared__ int bad[kLeadChunk];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int r0 = blockIdx.x * kLeadChunk, b = blockIdx.y;
-    const int32_t *idx = a.idx[blockIdx.z] + ((int64_t)b * a.Tq + r0) * a.k_sel;
+    const int row = blockIdx.x * kLeadChunk + wave, b = blockIdx.y;
+    const int held = a.pos0 + row + 1;
     const bool vec = (a.k_sel & 3) == 0 && (uintptr_t)a.idx[blockIdx.z] % 16 == 0;
-    int first = kLeadChunk;                               // first row of the wave's that is no prefix
+    bool ok = row < a.n_rows;
+    if (ok) {
+        const int32_t *p = a.idx[blockIdx.z] + ((int64_t)b * a.Tq + row) * a.k_sel;
+        if (vec) {
+            for (int s0 = 0; s0 < a.k_sel; s0 += 256 * U) {
+                i32x4 v[U];
 #pragma unroll
-    for (int r = N - 1; r >= 0; --r) {
-        const int row = N * wave + r, held = a.pos0 + r0 + row + 1;
-        bool ok = r0 + row < a.n_rows;
-        if (ok) {
-            const int32_t *p = idx + (int64_t)row * a.k_sel;
-            if (vec) {
-                for (int s = 4 * lane; s < a.k_sel; s += 256) {
-                    const i32x4 v = *(const i32x4 *)(p + s);
+                for (int u = 0; u < U; ++u) v[u] = *(const i32x4 *)(p + min(s0 + 256 * u + 4 * lane, a.k_sel - 4));
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) ok &= s + e < held ? v[e] == s + e : v[e] < 0;
+                for (int u = 0; u < U; ++u) {
+                    const int s = min(s0 + 256 * u + 4 * lane, a.k_sel - 4);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) ok &= s + e < held ? v[u][e] == s + e : v[u][e] < 0;
                 }
-            } else {
-                for (int s = lane; s < a.k_sel; s += 64) ok &= s < held ? p[s] == s : p[s] < 0;
+            }
+        } else {
+            for (int s0 = 0; s0 < a.k_sel; s0 += 64 * U) {
+                int32_t v[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) v[u] = p[min(s0 + 64 * u + lane, a.k_sel - 1)];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int s = min(s0 + 64 * u + lane, a.k_sel - 1);
+                    ok &= s < held ? v[u] == s : v[u] < 0;
+                }
             }
         }
-        if (__ballot(!ok) != 0ull) first = row;
     }
-    if (lane == 0) bad[wave] = first;
+    const bool prefix = __ballot(!ok) == 0ull;
+    if (lane == 0) bad[wave] = prefix ? kLeadChunk : wave;
     __syncthreads();
-    if (threadIdx.x == 0)
-        a.lead[((int64_t)blockIdx.z * a.B + b) * a.n_chunks + blockIdx.x] = min(min(bad[0], bad[1]), min(bad[2], bad[3]));
+    if (threadIdx.x == 0) {
+        int first = kLeadChunk;
+#pragma unroll
+        for (int w = 0; w < kLeadChunk; ++w) first = min(first, bad[w]);
+        a.lead[((int64_t)blockIdx.z * a.B + b) * a.n_chunks + blockIdx.x] = first;
+    }
 }
 
 } // namespace
 
 hipError_t launch_lead(const LeadArgs &a, int n_tensors, hipStream_t st)
 {
-    hipLaunchKernelGGL(lead_kernel, dim3((unsigned)a.n_chunks, (unsigned)a.B, (unsigned)n_tensors), dim3(256), 0, st, a);
+    hipLaunchKernelGGL(lead_kernel, dim3((unsigned)a.n_chunks, (unsigned)a.B, (unsigned)n_tensors), dim3(64 * kLeadChunk), 0, st, a);
     return hipGetLastError();
 }
 
-// The rows of a.Q's only sequence that RestArgs leaves, unsplit.
+// The rows that RestArgs leaves, unsplit.
 hipError_t launch_attn_rest(const AttnArgs &a, const RestArgs &ra, hipStream_t st)
 {
     return launch_slab_t<576, 512, false, false, false, true>(a, slab_lds<576>, st, ra);

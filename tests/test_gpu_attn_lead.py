@@ -47,6 +47,10 @@ CASES = [
     (1, 400, 400, 1024, 32, [(0, 16, "long")]),                        # first row of one
     (1, 600, 600, 512, 32, [(0, 320, "empty")]),
     (1, 400, 400, 1024, 32, [(0, 399, "hole")]),                       # the last row
+    (1, 400, 400, 1022, 32, [(0, 333, "swap")]),                       # k not a multiple of four, rows counted
+    (1, 1100, 1100, 1024, 32, []),                                     # rows behind, split on their own
+    (3, 600, 600, 512, 32, [(0, 100, "hole"), (2, 0, "behind")]),      # rows behind go along; counts 100, 512 and 0
+    (5, 600, 600, 512, 32, [(4, 200, "short")]),                       # more workgroups than rows left in four of five sequences
 ]
 
 
@@ -154,3 +158,47 @@ def test_lse_is_as_exact_as_the_row_forms(gain):
     assert not torch.equal(dense, row)                # (two forms, not one twice)
     # 8192 values each: the ratio of two such root mean squares scatters by about 2 %
     assert far[0] ** 0.5 <= 1.08 * far[1] ** 0.5, (far[0] ** 0.5, far[1] ** 0.5)
+
+
+@pytest.mark.parametrize("B, Tq, Lk, k, taken", [(1, 400, 400, 1022, True), (1, 1100, 1100, 1024, True), (3, 600, 600, 512, True),
+                                                 (2, 300, 500, 1024, True), (1, 2060, 2060, 2048, True), (4, 2100, 2100, 2048, True),
+                                                 (1, 700, 2400, 2048, False), (1, 256, 2048, 2048, False), (1, 600, 600, 512, False)])
+def test_shapes_that_look_for_leading_rows(B, Tq, Lk, k, taken):
+    """The cases above take the path that they mean to, and shapes with little to gain on causal rows do not."""
+    import ctypes as C
+    import paper_2603_12201_amd as ic
+    d = ic.AttnDesc(B, Tq, Lk, 32, 576, 512, 0, 576, k, 1 / 24.0)
+    assert ic.lib().ic_sparse_attn_workspace(C.byref(d)) == 0
+    assert (ic.lib().ic_sparse_attn_lead_workspace(C.byref(d)) > 0) == taken
+
+
+def test_similarity_with_rows_behind_the_prefixes_of_several_sequences(oracle):
+    """Few rows behind the candidates in each of three sequences: split over the chip together where the workspace has room,
+    whole where it has not; the same similarities."""
+    import ctypes as C
+    import paper_2603_12201_amd as ic
+    B, T, k, n = 3, 1040, 1024, 3
+    print("[case] similarity tails B=%d T=%d k=%d" % (B, T, k), flush=True)
+    g = torch.Generator(device="cuda").manual_seed(8)
+    layers = [{"Q": torch.randn((B, T, 32, 576), generator=g, device="cuda", dtype=torch.bfloat16),
+               "KV": torch.randn((B, T, 576), generator=g, device="cuda", dtype=torch.bfloat16)} for _ in range(n)]
+    idx = [torch.from_numpy(_selection(B, T, T, k, [(1, 900 + i, "hole")], i)).cuda() for i in range(n)]
+    S, O = [], []
+    for short in (False, True):
+        outs = [torch.full((B, T, 32, 512), 7.0, dtype=torch.bfloat16, device="cuda") for _ in layers]
+        arr = ic.make_layers(layers, k, 0, 512, 0, 1 / 24.0, outs)
+        need = int(ic.lib().ic_similarity_matrix_workspace(arr, n))
+        if short:
+            need = B * T * 32 * 512 * 2                # one output
+        ws = torch.empty(need, dtype=torch.uint8, device="cuda")
+        s = torch.empty((n, n), dtype=torch.float64, device="cuda")
+        ptrs = (C.c_void_p * n)(*[i.data_ptr() for i in idx])
+        assert ic.lib().ic_similarity_matrix(arr, n, ptrs, C.c_void_p(s.data_ptr()), C.c_void_p(ws.data_ptr()), need,
+                                             C.c_void_p(torch.cuda.current_stream().cuda_stream)) == ic.Status.OK
+        torch.cuda.synchronize()
+        S.append(s.cpu().numpy())
+        O.append([o.float() for o in outs])
+    # bf16 outputs of sums in another order: a unit in the last place of a value here and there
+    assert np.allclose(S[0], S[1], rtol=0, atol=2e-4), (S[0], S[1])
+    for a, b in zip(*O):
+        assert ((a - b).norm() / b.norm()).item() < 4e-3

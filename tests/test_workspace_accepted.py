@@ -64,7 +64,7 @@ def test_lead_entry_point_checks_its_workspace():
     import paper_2603_12201_amd as ic
     L, S = ic.lib(), ic.Status
     one = C.c_void_p(4096)
-    for Tq, k in ((700, 512), (2100, 2048), (100, 256)):                   # a tail split over the chip; no leading rows looked for
+    for Tq, k in ((1100, 1024), (2100, 2048), (100, 256)):                   # a tail split over the chip; no leading rows looked for
         d = ic.AttnDesc(1, Tq, Tq, 32, 576, 512, 0, 576, k, 1 / 24.0)
         need = L.ic_sparse_attn_lead_workspace(C.byref(d))
         assert need > 0 and need % 256 == 0
