@@ -393,7 +393,10 @@ double row_time(const ic_attn_desc *d, int n_layers, Causal c, size_t ws_bytes, 
         return (double)((nq * sp.n + wgs - 1) / wgs * (sp.len / 64 + 2)) + (sp.n > 1 ? 2 : 0);
     }
     double mean = (double)tiles;
-    if (c.pos0 >= 0) mean = std::min(mean, std::max(3.0, (c.pos0 + 0.5 * (d->Tq + 1)) / 64));
+    if (c.pos0 >= 0 && c.pos0 < d->k_sel) {    // rows that hold fewer entries than k, and the others
+        const double few = (double)std::min<int64_t>(d->Tq, d->k_sel - c.pos0);
+        mean = (few * std::min(mean, std::max(3.0, (c.pos0 + 0.5 * (few + 1)) / 64)) + (d->Tq - few) * mean) / d->Tq;
+    }
     return (double)((nq + wgs - 1) / wgs) * mean + 2;
 }
 
@@ -425,7 +428,8 @@ int dense_queries(const ic_attn_desc *d, int n_layers, Causal c, size_t ws_bytes
     const double whole = row_time(d, n_layers, c, ws_bytes, attn_max_splits(d, 1)) / n_layers, dense = dense_time(d, n, c.pos0);
     if (n == d->Tq) return dense <= 1.08 * whole ? n : 0;
     const ic_attn_desc t = rows_behind(d, n);
-    return dense + row_time(&t, 1, Causal{c.pos0 + n, c.lk}, ws_bytes, INT64_MAX) + 2 <= 0.85 * whole ? n : 0;
+    const double behind = row_time(&t, 1, Causal{c.pos0 + n, c.lk}, ws_bytes, INT64_MAX);
+    return dense + 2 <= 0.75 * (whole - behind) ? n : 0;
 }
 
 // Workspace that serves the rows behind best.
