@@ -319,7 +319,8 @@ ic_status run_indexer(const ic_indexer_desc *d, const void *q, const void *k, co
             se.Ri = ri;
             {
                 ProfScope ps(1, st);
-                hipError_t e = lists && ic::select_parts(bc * ri, (int)max_vis) > 0
+                const bool fit = se.seq_lens || ic::select_parts_fit(d->k_sel, (int)max_vis);   // (ragged: shorter than max_vis, maybe)
+                hipError_t e = lists && fit && ic::select_parts(bc * ri, (int)max_vis) > 0
                                    ? ic::launch_select_parts(se, bc * ri, d->Lk, lists, st)
                                    : ic::launch_select(se, bc * ri, (int)max_vis, st);
                 if (e != hipSuccess) return fail(IC_ERR_HIP, "top-k select launch failed: %s", hipGetErrorString(e));

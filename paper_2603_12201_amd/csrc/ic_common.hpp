@@ -83,7 +83,6 @@ struct AttnArgs {
     void *O;              // [B,Tq,H_q,d_v] bf16
     float *lse;           // [B,Tq,H_q] or nullptr (one layer only)
     void *part_o;         // split partials: [n_layers*B*Tq, n_splits, H_q, d_v], each normalised by its own row sum
-    int32_t part_wide;    // 1: they are fp32, 0: bf16
     float *part_ml;       // [n_layers*B*Tq, n_splits, H_q, 2] fp32 (running max in log2 units, sum)
     int32_t B, Tq, Lk, H_q, v_off, row_elems, k_sel;
     int32_t n_splits, split_len; // key slots per split (multiple of 64)
@@ -93,11 +92,12 @@ struct AttnArgs {
     // holds min(k_sel, causal_pos0 + t + 1) entries followed by -1 only, and the tiles behind them need no work;
     // < 0: nothing is known about idx
     int64_t causal_pos0;
-    int32_t row_gap;      // rows of Q, idx, O and lse between two sequences' Tq rows (0: one follows the other)
     int32_t n_layers;
+    int32_t row_gap;      // rows of Q, idx, O and lse between two sequences' Tq rows (0: one follows the other)
     const void *Qs[kMaxBatchLayers];
     const void *KVs[kMaxBatchLayers];
     void *Os[kMaxBatchLayers];
+    int32_t part_wide;    // 1: the partials are fp32, 0: bf16
 };
 
 // Which leading rows of every sequence of an index tensor are whole prefixes, row t = 0 .. pos0 + t and then nothing: per
@@ -186,6 +186,7 @@ hipError_t launch_fill(float *p, int64_t n, float v, hipStream_t st);
 hipError_t launch_select(const SelectArgs &a, int n_rows, int max_row_len, hipStream_t st);
 int select_cache_limit();
 int select_parts(int n_rows, int max_row_len);
+bool select_parts_fit(int k, int row_len);
 size_t select_parts_bytes(int n_rows, int max_row_len);
 hipError_t launch_select_parts(const SelectArgs &a, int n_rows, int max_row_len, void *ws, hipStream_t st);
 hipError_t launch_attn(const AttnArgs &a, int d_qk, int d_v, hipStream_t st);

@@ -690,7 +690,8 @@ __global__ __launch_bounds__(NT) void select_cand_kernel(SelectArgs a)
 //                         candidates, ascending by position, to a list of its own in the workspace
 //   select_finish_kernel  one workgroup per row collects the lists in order, finds the k-th largest candidate with one
 //                         histogram and an exact ranking of its bin, and emits: the candidates are already ascending, so
-//                         a bitmap over their numbers (not over the row) gives the slots, and the row may be of any length
+//                         a bitmap over their numbers (not over the row) gives the slots, and the row may be longer than a
+//                         bitmap over its positions; how long, select_parts_fit() says
 // A row that the candidates cannot decide (fewer than k of them, a list that overflowed, too many ties in the boundary
 // bin) and a row too short for the sample take the generic radix select in the second launch.
 constexpr int kPartThreads = 1024;
@@ -960,6 +961,12 @@ size_t select_lds_bytes(int cache_elems)
 } // namespace
 
 int select_cache_limit() { return 32768; }
+
+// A row of this length leaves about 2 k + 1 / 128 of its keys as candidates (the rank that select_part_kernel takes from the
+// sample).  Where the second launch does not hold that many, the row would go to the radix select behind two launches for
+// nothing (k = 2048: from 1.05 M keys; 1.1 M keys 745 us without, 755 with them).  The sample scatters by some 14 %: a row
+// shortly below the line may still get there, and gains tenfold where it does not (1 M keys 727 / 60 us).
+bool select_parts_fit(int k, int row_len) { return (int64_t)2 * k + row_len / 128 <= kFinishCap; }
 
 // Parts of a row when n_rows rows of up to max_row_len keys are selected together: enough for one workgroup per CU,
 // stretches of at least 256 keys per wave; 0 = the row-per-workgroup forms take the rows.

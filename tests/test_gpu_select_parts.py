@@ -77,3 +77,17 @@ def test_ragged_rows(ic, oracle):
             continue
         sc = oracle.indexer_scores(synth.bits(q[b:b + 1]), synth.bits(k[b:b + 1, :n].contiguous()), synth.bits(w[b:b + 1]), n - 1)
         parity.check_idx_row(idx[b, 0], sc[0, 0], n, ks, oracle)
+
+
+@pytest.mark.parametrize("ks, Lk, pos0", [(2048, 1052000, 1051999), (16, 1700000, 1568767), (2048, 1200000, 90000)])
+def test_rows_about_as_long_as_the_candidates_allow(ic, oracle, ks, Lk, pos0):
+    """Rows beyond what the candidate lists hold, about as long as that, and a short row of a long cache."""
+    print("[case] parts, k=%d Lk=%d pos0=%d" % (ks, Lk, pos0), flush=True)
+    g = torch.Generator().manual_seed(ks)
+    q = (torch.randn((1, 1, 2, 64), generator=g) / 8).to(torch.bfloat16)
+    k = torch.randn((1, Lk, 64), generator=g).to(torch.bfloat16)
+    w = torch.rand((1, 1, 2), generator=g)
+    idx = ic.indexer_topk(q.cuda(), k.cuda(), w.cuda(), ks, pos0).cpu().numpy()
+    n = pos0 + 1
+    sc = oracle.indexer_scores(synth.bits(q), synth.bits(k[:, :n].contiguous()), synth.bits(w), pos0)
+    parity.check_idx_row(idx[0, 0], sc[0, 0], n, ks, oracle)
