@@ -383,6 +383,9 @@ int prefix_queries(const ic_attn_desc *d, Causal c)
     return (int)(n < 0 ? 0 : (n > d->Tq ? d->Tq : n));
 }
 
+// It stores 16 bytes of O at a time; the row form takes any address of a bf16.
+bool dense_output(const void *O) { return (uintptr_t)O % 16 == 0; }
+
 // Times in tiles of 64 keys of a row-form workgroup (about 2 us), launches and what a workgroup pays once included.
 // Rows of one or more layers in the row form: attn_splits() where they are split or all resident, otherwise chains of
 // queries, which leave the tiles behind a causal row's last entry out.
@@ -712,7 +715,7 @@ ic_status ic_sparse_attn_lead(const ic_attn_desc *d, const void *Q, const void *
     if (s != IC_OK) return s;
     hipStream_t st = (hipStream_t)stream;
     const size_t lb = lead_bytes(d, 1);
-    if (lb == 0) return run_attn(d, Q, KV, idx, O, lse, workspace, workspace_bytes, st);
+    if (lb == 0 || !dense_output(O)) return run_attn(d, Q, KV, idx, O, lse, workspace, workspace_bytes, st);
     int32_t *const lead = (int32_t *)workspace;
     s = count_lead(d, &idx, 1, lead, st);
     if (s != IC_OK) return s;
@@ -867,7 +870,7 @@ static ic_status forward_stack_impl(const ic_layer *layers, int32_t n_layers, co
         while (l + run < n_layers && !full_mask[l + run]) ++run;
         int m = attn_batch(L, run, pc);
         while (m > 1 && attn_best_bytes(&L->at, m) > workspace_bytes) --m;
-        const int nd = dense_queries(&L->at, m, known, workspace_bytes);
+        const int nd = dense_output(L->O) ? dense_queries(&L->at, m, known, workspace_bytes) : 0;
         s = nd ? run_attn_dense(L, nd, idx_cache, workspace, workspace_bytes, st, pc, known)
                : run_attn_layers(L, m, idx_cache, nullptr, workspace, workspace_bytes, st, pc, known);
         if (s != IC_OK) return s;
@@ -1015,6 +1018,8 @@ ic_status ic_similarity_matrix(const ic_layer *layers, int32_t n_layers, const i
     s = check_ws(workspace, workspace_bytes, min_ws);
     if (s != IC_OK) return s;
     if (workspace_bytes < min_ws + lb) lb = 0;
+    for (int l = 0; l < n_layers; ++l)
+        if (!dense_output(layers[l].O)) lb = 0;
     hipStream_t st = (hipStream_t)stream;
     char *ws = (char *)workspace;
     void *o_reuse = ws;

@@ -1324,7 +1324,7 @@ __global__ __launch_bounds__(512, 2) void attn_dense_kernel(AttnArgs a, DenseArg
         });
     }
     __syncthreads();
-    __bf16 *out = (__bf16 *)a.O + ((int64_t)b * a.Tq * a.H_q + R0) * D_V;
+    __bf16 *out = (__bf16 *)a.O + ((int64_t)b * a.Tq * a.H_q + R0) * D_V;   // (16-byte aligned: dense_output())
     if (__builtin_amdgcn_readfirstlane(moved[2])) {       // (rare: see finite_v above)
         const unsigned short *v0 = (const unsigned short *)a.KV + (PG && a.pv.page_table ? 0 : (int64_t)b * a.Lk * a.row_elems) + 8 * lane;
         for (int row = wave; row < kDenseRows && R0 + row < n_rows; row += 8) {
@@ -1430,7 +1430,13 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a)
             bf16xc r;
 #pragma unroll
             for (int e = 0; e < CPL; ++e) r[e] = (__bf16)(o[CPL * c + e] * inv);
-            *(bf16xc *)(out + v + c * (D_V / N16)) = r;
+            __bf16 *p = out + v + c * (D_V / N16);
+            if ((uintptr_t)a.Os[layer] % 16 == 0) {           // (any other address of a bf16 will do as well)
+                *(bf16xc *)p = r;
+            } else {
+#pragma unroll
+                for (int e = 0; e < CPL; ++e) p[e] = r[e];
+            }
         }
     } else {
         __shared__ __attribute__((aligned(16))) float o_sh[HEADS][SLOTS][D_V];
@@ -1456,8 +1462,8 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a)
             t1 += o_sh[grp][s][c + 1] * sc;
         }
         const float inv = (lt > 0.f) ? 1.f / lt : 0.f;
-        typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
-        *(bf16x2 *)(out + c) = bf16x2{(__bf16)(t0 * inv), (__bf16)(t1 * inv)};
+        out[c] = (__bf16)(t0 * inv);
+        out[c + 1] = (__bf16)(t1 * inv);
         m = mt;
         l = lt;
     }

@@ -223,3 +223,28 @@ def test_large_values_behind_a_rising_score(oracle, jump, power):
     lb = synth.bits_layer(t)
     want, _ = oracle.sparse_attn(lb["Q"], lb["KV"], idx.cpu().numpy(), 512, 0, scale)
     parity.check_attn(got.float().numpy(), want)
+
+
+@pytest.mark.parametrize("B, Tq, pos0, k", [(1, 300, 0, 512), (2, 40, 900, 512), (1, 3, 5000, 2048)])
+def test_any_output_address(B, Tq, pos0, k):
+    """Outputs two bytes past a 16-byte boundary (dense form, splits merged by a wave and by a workgroup): the same, to the order
+    of sums, as aligned ones, and nothing beside them is touched."""
+    import paper_2603_12201_amd as ic
+    print("[case] output address B=%d Tq=%d pos0=%d k=%d" % (B, Tq, pos0, k), flush=True)
+    cfg = synth.config("c2", B=B, Tq=Tq, Lk=pos0 + Tq, q_pos0=pos0, H_q=32, k_sel=k, row_elems=576, H_I=4, seed=Tq)
+    t = synth.indexer_layer(cfg, 0)
+    t.update(synth.attn_layer(cfg, 0))
+    g = {n: v.cuda() for n, v in t.items()}
+    n = B * Tq * 32 * 512
+    outs = []
+    for off in (0, 1):
+        buf = torch.full((n + 8,), 7.0, dtype=torch.bfloat16, device="cuda")
+        out = buf[off:off + n].view(B, Tq, 32, 512)
+        arr = ic.make_layers([g, g], k, pos0, 512, 0, 1 / 24.0, [out, torch.empty_like(out)])
+        idx = torch.empty((B, Tq, k), dtype=torch.int32, device="cuda")
+        ws = torch.empty(max(256, ic.forward_stack_workspace(arr)), dtype=torch.uint8, device="cuda")
+        ic.forward_stack(arr, [True, False], idx, ws)
+        torch.cuda.synchronize()
+        assert (buf[:off] == 7.0).all() and (buf[off + n:] == 7.0).all()
+        outs.append(out.float())
+    assert ((outs[0] - outs[1]).norm() / outs[0].norm()).item() < 4e-3
