@@ -867,30 +867,40 @@ __global__ __launch_bounds__(256, 1) void attn_slab_kernel(AttnArgs a, RestArgs 
             int tx = tid;
             asm volatile("" : "+v"(tx));
             const int o_lane = 32 * (tx >> 6) + (tx & 31), o_hh = (tx >> 5) & 1;
-            auto put = [&](auto *o_row) __attribute__((always_inline)) {
-                typedef std::remove_pointer_t<decltype(o_row)> T;
-#pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    const int hq = 8 * (i >> 2) + 4 * o_hh + (i & 3); // O row (head) of accumulator element i
-                    const float inv = inv4[i >> 2][i & 3];
-                    T *po = o_row + hq * D_V;
-                    if (all_heads) {
-#pragma unroll
-                        for (int nb = 0; nb < NBW; ++nb) po[128 * nb] = (T)(oacc[nb][i] * inv);
-                    } else if (hq < a.H_q) {
-#pragma unroll
-                        for (int nb = 0; nb < NBW; ++nb) po[128 * nb] = (T)(oacc[nb][i] * inv);
-                    }
-                }
-            };
+            // (the same loops twice: one body for all three destinations cost the chains 1 %)
             if constexpr (SPLIT) {
+                auto put = [&](auto *o_row) __attribute__((always_inline)) {
+                    typedef std::remove_pointer_t<decltype(o_row)> E;
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) {
+                        const int hq = 8 * (i >> 2) + 4 * o_hh + (i & 3); // O row (head) of accumulator element i
+                        const float inv = inv4[i >> 2][i & 3];
+                        if (all_heads || hq < a.H_q) {
+#pragma unroll
+                            for (int nb = 0; nb < NBW; ++nb) o_row[hq * D_V + 128 * nb] = (E)(oacc[nb][i] * inv);
+                        }
+                    }
+                };
                 const int64_t part = (qrow * a.n_splits + sp) * a.H_q * D_V + o_lane;
                 if (a.part_wide)
                     put((float *)a.part_o + part);
                 else
                     put((__bf16 *)a.part_o + part);
             } else {
-                put((__bf16 *)(MULTI ? a.Os[cs.layer] : a.O) + q_cur() * a.H_q * D_V + o_lane);
+                __bf16 *o_row = (__bf16 *)(MULTI ? a.Os[cs.layer] : a.O) + q_cur() * a.H_q * D_V + o_lane;
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    const int hq = 8 * (i >> 2) + 4 * o_hh + (i & 3);
+                    const float inv = inv4[i >> 2][i & 3];
+                    __bf16 *po = o_row + hq * D_V;
+                    if (all_heads) {
+#pragma unroll
+                        for (int nb = 0; nb < NBW; ++nb) po[128 * nb] = (__bf16)(oacc[nb][i] * inv);
+                    } else if (hq < a.H_q) {
+#pragma unroll
+                        for (int nb = 0; nb < NBW; ++nb) po[128 * nb] = (__bf16)(oacc[nb][i] * inv);
+                    }
+                }
             }
         }
     };
