@@ -405,7 +405,8 @@ def main():
                 "frac": kd["frac"], "traffic": kd.get("traffic"),
                 "traffic_unit": "HBM bytes per launch: rocprofv3 FETCH_SIZE + WRITE_SIZE, scaled by a plain copy",
                 "traffic_source": traffic.get("source"),
-                "avg_launch_ms": kd["ms_per_layer"] / kd["launches_per_layer"],
+                "avg_launch_ms": kd["ms_per_layer"] / kd["launches_per_layer"],   # (dense rows and the others are two launches a layer)
+                "launches_per_layer": kd["launches_per_layer"], "ms_per_layer": kd["ms_per_layer"],
                 "timing": "HIP events around every launch of one 1-in-4 step, a pass of its own after the timed region",
                 "share_of_step": share[dom] / sum(share.values())}
     if dom == "sparse_attn":
