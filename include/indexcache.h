@@ -329,7 +329,7 @@ ic_status ic_pattern_search_dp(const double *S, int32_t n_layers, int32_t n_full
  * Outputs (host): full_mask [n_layers]; order [n_shared], nullable: the flipped layers in commit
  * order; loss_curve [n_shared], nullable: the loss after each commit.
  * Workspace: the queries return room for the stack's fastest form (ic_forward_stack_workspace); both calls accept what one
- * layer at a time needs, the largest ic_sparse_attn_workspace() or strip of score rows, plus their own few kilobytes.
+ * layer at a time needs, the largest least workspace of ic_sparse_attn or strip of score rows, plus their own few kilobytes.
  * Errors: IC_ERR_NULL, IC_ERR_SHAPE (n_shared > candidates, bad block count, layer shapes),
  * IC_ERR_PATTERN never (the search keeps layer 0 Full), IC_ERR_WORKSPACE, IC_ERR_HIP.
  */
