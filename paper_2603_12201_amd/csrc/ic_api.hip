@@ -450,7 +450,7 @@ size_t dense_tail_bytes(const ic_attn_desc *d, int n_layers, Causal c)
 // and the dense form and what follows it read the counts.  Without the dense form a row costs k_sel / 64 tile times of a CU
 // however little of it is filled.  The rows behind the candidates go along with the candidates that the counts leave, or
 // are split over the chip on their own.  Whichever of the two gains more on a causal selection than it loses on any other is
-// taken if that difference is a tenth of the row form's time; the scan and the launches that find nothing to do cost 5.5
+// taken if that difference is a tenth of what the candidates take in the row form; the scan and the launches that find nothing to do cost 5.5
 // tile times.  Measured, k = 2048, row form / this for causal rows / for other rows: 2048 rows 414 / 161 / 429 us, 4096
 // rows 827 / 596 / 839, 4 x 2060 rows 1677 / 642 / 1703; not taken: 700 rows behind 1700 keys 160 / 173 / 166.
 struct LeadPlan {
@@ -475,7 +475,7 @@ LeadPlan lead_plan(const ic_attn_desc *d)
     } else {
         apart = along;                         // (nothing to split)
     }
-    if (std::max(along, apart) < 0.1 * whole) return none;
+    if (std::max(along, apart) < 0.1 * (whole - unsplit(t.Tq))) return none;
     return {n, along >= apart};
 }
 int lead_queries(const ic_attn_desc *d) { return lead_plan(d).n; }

@@ -1548,7 +1548,7 @@ hipError_t launch_slab(const AttnArgs &a, hipStream_t st)
 }
 
 // Counts of LeadArgs: a workgroup per chunk, a wave per row, whose entries are all requested before the first is looked at
-// (2048 rows of 2048 entries are 16 MB: 9 us; four rows per wave, a kilobyte at a time, were one latency after the other
+// (2048 rows of 2048 entries are 16 MB: 5 us; four rows per wave, a kilobyte at a time, were one latency after the other
 // and took 23).
 __global__ __launch_bounds__(64 * kLeadChunk) void lead_kernel(LeadArgs a)
 {

@@ -161,7 +161,7 @@ def test_lse_is_as_exact_as_the_row_forms(gain):
 
 
 @pytest.mark.parametrize("B, Tq, Lk, k, taken", [(1, 400, 400, 1022, True), (1, 1100, 1100, 1024, True), (3, 600, 600, 512, True),
-                                                 (2, 300, 500, 1024, True), (1, 2060, 2060, 2048, True), (4, 2100, 2100, 2048, True),
+                                                 (2, 300, 500, 1024, True), (1, 2060, 2060, 2048, True), (4, 2100, 2100, 2048, True), (1, 32768, 32768, 2048, True),
                                                  (1, 700, 2400, 2048, False), (1, 256, 2048, 2048, False), (1, 600, 600, 512, False)])
 def test_shapes_that_look_for_leading_rows(B, Tq, Lk, k, taken):
     """The cases above take the path that they mean to, and shapes with little to gain on causal rows do not."""
