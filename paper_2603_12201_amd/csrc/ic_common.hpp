@@ -34,6 +34,13 @@ __device__ __forceinline__ int64_t paged_row(const PagedView &pv, int b, int s)
     return ((int64_t)page << pv.page_shift) + (s & ((1 << pv.page_shift) - 1));
 }
 
+// Small read-only operands (head weights, lengths, page-table entries) are read through the constant address space: with a
+// uniform address that is a scalar load, which does not enter the vector-memory queue that waits by position count on.
+// (An ordinary load inside such a loop would make the compiler wait for "all its loads", i.e. drain the queue.)
+template <typename T> __device__ __forceinline__ T load_uniform(const T *p)
+{
+    return *(const __attribute__((address_space(4))) T *)(uintptr_t)p;
+}
 
 // Indexer scoring of query rows [i0, i0+Ri) of sequences [b0, b0+Bc) against their keys.
 // Scores land in a strip: row (b-b0)*Ri + (i-i0), element s, row stride ld floats.

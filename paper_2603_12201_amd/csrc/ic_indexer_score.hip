@@ -477,14 +477,6 @@ template <int N> __device__ __forceinline__ void wait_vm_le()
 {
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
-// Small read-only operands (head weights, lengths, page table) are read through the constant address space: with a
-// uniform address that is a scalar load, which does not enter the vector-memory queue the ring's waits count on.
-// (An ordinary load inside the loop would make the compiler wait for "all its loads", i.e. drain the ring.)
-template <typename T> __device__ __forceinline__ T load_uniform(const T *p)
-{
-    return *(const __attribute__((address_space(4))) T *)(uintptr_t)p;
-}
-
 template <int HT, int NW, int R, bool PG>
 __global__ __launch_bounds__(64 * NW, 1) void score_stream_kernel(ScoreArgs a, int T, int G)
 {

@@ -1,10 +1,10 @@
 // Sparse MQA core attention over the selected KV rows (paper Sec. 2.1: the main attention is
 // computed only over the top-k subset; MLA form, one shared KV row per position).
 //
-// Two kernels.  MLA rows whose values are their first features (576 / 512) take the row-slab
-// form further down: one workgroup per CU, 64-row tiles, walking a chain of queries when there are
-// more queries than CUs, or one (query, split) each when there are fewer (decode).  Every other
-// supported layout takes the small-tile form described here.
+// MLA rows whose values are their first features (576 / 512) take one of three forms further down: the stream form, one
+// workgroup per CU that walks a chain of queries; the row-slab form, one (query, split) per workgroup where there are fewer
+// queries than CUs (decode); the dense form where a row selects all it sees.  Every other supported layout takes the
+// small-tile form described here.
 //
 // Small-tile form: one workgroup (4 waves) per query token and key-slot split; two workgroups
 // fit a CU (75 KB of LDS, <= 256 VGPRs each) so that one computes while the other waits for its
@@ -279,10 +279,6 @@ __global__ __launch_bounds__(256, 2) void attn_kernel(AttnArgs a)
 // The consumer role lags the producer role by one tile (a step = produce tile it, consume tile
 // it-1), so the previous tile's operand reads run under the softmax arithmetic and the staging
 // stores under the PV MFMAs.
-// Between two queries of a chain: the last two steps already gather and stage the next query's
-// first tiles; one wave loads the next Q straight into the accumulation registers while the
-// outputs are stored and hands it to the other waves through the tile buffer that is idle at
-// that moment (see the driver at the end of the kernel).
 constexpr int kSlabTile = 64;
 constexpr float kLazyLog2 = 8.f;
 
@@ -325,28 +321,11 @@ __device__ __forceinline__ unsigned rows_mask(unsigned long long ba, unsigned lo
     return lo | (hi << 8);
 }
 
-// SPLIT: blockIdx.y selects a.split_len key slots of the query and the result is a partial
-// (unnormalised accumulators, reference maximum, row sum) for the merge kernel.
-// MULTI: a.n_layers layers in one launch, or the last rows of several sequences (a.row_gap); a query's place in the tensors
-// is then not its number (its own instance: a chain that has to know a query's layer took 2 % longer).
-// REST: the rows of sequence blockIdx.y behind those that the dense form has taken.  How many that are is device data, so the
-// workgroups, as many as for all rows, find out first and share what is left (one round trip to memory, about 1 us).
-template <int D_QK, int D_V, bool PG, bool SPLIT, bool MULTI, bool REST>   // value columns = the first D_V features of a row; PG as above
-__global__ __launch_bounds__(256, 1) void attn_slab_kernel(AttnArgs a, RestArgs ra)
+// blockIdx.x: query of the launch, flattened (layer, b, t); blockIdx.y selects a.split_len of its key slots.  The result is a
+// partial for the merge kernel.
+template <int D_QK, int D_V, bool PG>   // value columns = the first D_V features of a row; PG as above
+__global__ __launch_bounds__(256, 1) void attn_slab_kernel(AttnArgs a)
 {
-    if constexpr (REST) {
-        const int64_t bs = blockIdx.y, o = bs * ra.n_chunks;
-        const int t0 = __builtin_amdgcn_readfirstlane(min(lead_rows(ra.lead + o, ra.n_chunks), lead_rows(ra.lead2 + o, ra.n_chunks)));
-        if (t0 + (int)blockIdx.x >= ra.n_rows && t0 + (int)gridDim.x > ra.n_rows) return;   // no chain, and no row for it
-        const int64_t row = bs * a.Tq + t0;
-        a.Tq = ra.n_rows - t0;
-        a.Q = (const __bf16 *)a.Q + row * a.H_q * D_QK;
-        a.KV = (const __bf16 *)a.KV + bs * a.Lk * a.row_elems;
-        a.O = (__bf16 *)a.O + row * a.H_q * D_V;
-        a.idx += row * a.k_sel;
-        if (a.lse) a.lse += row * a.H_q;
-        a.B = 1;
-    }
     constexpr int KS = D_QK / 32;                         // contraction steps of S^T = 16-byte chunks per gather lane
     constexpr int ROWB = D_QK * 2 + kSlabPad;             // LDS row stride
     static_assert((D_QK * 2) % 128 == 0 && D_V % 128 == 0 && KS % 2 == 0, "row = whole 128-byte windows");
@@ -364,75 +343,42 @@ __global__ __launch_bounds__(256, 1) void attn_slab_kernel(AttnArgs a, RestArgs 
     const int l16 = lane & 15, g = lane >> 4;
     const int l32 = lane & 31, hh = lane >> 5;
     const int gr = lane >> 3, gp = lane & 7;              // gather role: row (and row + 8), 16-byte piece
-    const int sp = SPLIT ? (int)blockIdx.y : 0;
-    const int slot0 = SPLIT ? sp * a.split_len : 0;
-    const int slot1 = SPLIT ? min(slot0 + a.split_len, a.k_sel) : a.k_sel;
+    // the arguments that the way to the first gather needs, requested together: left alone, each is loaded where it is first
+    // used, a chain of five memory latencies
+    // (24 queries in 8 splits: 23.8 us, 23.2 with this)
+    asm volatile("" ::"s"(a.n_layers), "s"(a.B), "s"(a.Tq), "s"(a.Lk), "s"(a.H_q), "s"(a.row_elems), "s"(a.k_sel), "s"(a.split_len), "s"(a.row_gap), "s"(a.idx));
+    const int sp = (int)blockIdx.y;
+    const int slot0 = sp * a.split_len;
+    const int slot1 = min(slot0 + a.split_len, a.k_sel);
     const int ntiles = (slot1 - slot0 + kSlabTile - 1) / kSlabTile;
-    // Chained form (whole selections of at least three tiles, grid smaller than the number of
-    // queries): the workgroup walks queries blockIdx.x, + gridDim.x, ... and treats their tiles as
-    // one stream, so that the gather and staging of the next query's first tiles and the load of
-    // its Q run under the last steps and the output stores of the current one.
-    const int64_t nq_layer = (int64_t)a.B * a.Tq, nq = MULTI ? nq_layer * a.n_layers : nq_layer;
-    const bool chain = !SPLIT && ntiles >= 3 && (int64_t)gridDim.x < nq;   // workgroup-uniform
-    int64_t qrow = blockIdx.x;
-    if (chain && (gridDim.x & 7u) == 0) {
-        // Workgroup ids are dealt round-robin over the 8 XCDs, each with its own L2.  Give XCD x the
-        // contiguous queries x * grid/8 .. of every round of `grid` queries: neighbouring queries
-        // select largely the same rows, which then meet in one L2.
-        const unsigned per = gridDim.x >> 3;
-        qrow = (int64_t)(blockIdx.x & 7u) * per + (blockIdx.x >> 3);
-    }
-    int64_t qnext = chain ? qrow + gridDim.x : nq;        // >= nq: this is the workgroup's last query
-
-    // what the gather needs to know about a query: its index row, its cache and its length
-    // nt: tiles of the query in the chained stream.  When the selection is known to be a causal top-k, a row near the
-    // start of a sequence holds fewer than k_sel entries and ends in -1s: its tiles behind the last entry are left
-    // out (never fewer than three per query: the stream looks three tiles ahead and knows two queries at a time).
-    struct Src { const int32_t *idx_row; const unsigned short *kv; int64_t q; int layer, b, len, nt; bool live; };   // q: row of the layer's tensors
-    auto src_of = [&](int64_t q) {
-        Src r;
-        r.live = q < nq;
-        const int64_t gq = r.live ? q : (int64_t)blockIdx.x;          // a dead source still reads valid memory
-        r.layer = MULTI ? layer_of(a, gq) : 0;
-        const int64_t qq = MULTI ? gq - r.layer * nq_layer : gq;
-        r.b = (int)(qq / a.Tq);
-        const int64_t row = MULTI ? qq + (int64_t)r.b * a.row_gap : qq;
-        if constexpr (MULTI) r.q = row;
-        r.nt = ntiles;
-        if (!SPLIT && a.causal_pos0 >= 0) {
-            const int64_t held = a.causal_pos0 + qq % a.Tq + 1;       // entries the row can hold
-            if (held < a.k_sel) r.nt = max(3, (int)((held + kSlabTile - 1) / kSlabTile));
-            r.nt = min(r.nt, ntiles);
-        }
-        r.idx_row = a.idx + row * a.k_sel;
-        r.kv = (const unsigned short *)(MULTI ? a.KVs[r.layer] : a.KV) + (PG && a.pv.page_table ? 0 : (int64_t)r.b * a.Lk * a.row_elems);
-        r.len = PG && a.pv.seq_lens ? min(a.pv.seq_lens[r.b], a.Lk) : a.Lk;   // ragged cache: rows of this sequence
-        return r;
-    };
-    Src cs = src_of(qrow), ns = src_of(qnext);            // current and next query
-    auto q_cur = [&]() { return MULTI ? cs.q : qrow; };
+    const int64_t gq = blockIdx.x;
+    const int layer = layer_of(a, gq);
+    int64_t qrow = gq - (int64_t)layer * a.B * a.Tq;
+    const int b = (int)((unsigned)qrow / (unsigned)a.Tq);
+    qrow += (int64_t)b * a.row_gap;
+    const void *const q_l = a.Qs[layer], *const kv_l = a.KVs[layer];
+    asm volatile("" ::"s"(q_l), "s"(kv_l));
+    const int32_t *idx_row = a.idx + qrow * a.k_sel;
+    const unsigned short *kv = (const unsigned short *)kv_l + (PG && a.pv.page_table ? 0 : (int64_t)b * a.Lk * a.row_elems);
+    const int len = PG && a.pv.seq_lens ? min(a.pv.seq_lens[b], a.Lk) : a.Lk;   // ragged cache: rows of this sequence
 
     // Loads inside the tile loop are unconditional (clamped addresses, result discarded when out
     // of range): the wait counters are positional, and a load that may or may not have been
     // issued would force every later wait down to "everything has landed".
     struct Ids { int32_t lo, hi; };                       // validated ids of tile rows 16w+gr and 16w+gr+8
-    // tile `it` of the stream: tiles at or beyond ntiles are the first tiles of the next query
     auto fetch_ids = [&](int it) -> Ids {
-        const bool nx = !SPLIT && it >= cs.nt;
-        const Src &q = nx ? ns : cs;
-        const int s_lo = slot0 + (nx ? it - cs.nt : it) * kSlabTile + 16 * wave + gr, s_hi = s_lo + 8;
-        const int32_t v_lo = q.idx_row[min(s_lo, a.k_sel - 1)], v_hi = q.idx_row[min(s_hi, a.k_sel - 1)];
+        const int s_lo = slot0 + it * kSlabTile + 16 * wave + gr, s_hi = s_lo + 8;
+        const int32_t v_lo = idx_row[min(s_lo, a.k_sel - 1)], v_hi = idx_row[min(s_hi, a.k_sel - 1)];
         Ids r;
         // no short-circuit: one basic block, so the loaded ids are not waited for before their use
-        r.lo = ((int)q.live & (int)(s_lo < slot1) & (int)(v_lo >= 0) & (int)(v_lo < q.len)) ? v_lo : -1;
-        r.hi = ((int)q.live & (int)(s_hi < slot1) & (int)(v_hi >= 0) & (int)(v_hi < q.len)) ? v_hi : -1;
+        r.lo = ((int)(s_lo < slot1) & (int)(v_lo >= 0) & (int)(v_lo < len)) ? v_lo : -1;
+        r.hi = ((int)(s_hi < slot1) & (int)(v_hi >= 0) & (int)(v_hi < len)) ? v_hi : -1;
         return r;
     };
-    auto row_ptr = [&](int32_t v, int it) {
-        const Src &q = (!SPLIT && it >= cs.nt) ? ns : cs;
+    auto row_ptr = [&](int32_t v) {
         // empty slots read row 0 of the cache (never a page-table entry: the sequence may own no page)
-        const int64_t prow = v < 0 ? 0 : (PG && a.pv.page_table ? paged_row(a.pv, q.b, v) : (int64_t)v);
-        return q.kv + prow * a.row_elems + 8 * gp;
+        const int64_t prow = v < 0 ? 0 : (PG && a.pv.page_table ? paged_row(a.pv, b, v) : (int64_t)v);
+        return kv + prow * a.row_elems + 8 * gp;
     };
     auto ids_mask = [&](const Ids &d) { return rows_mask(__ballot(d.lo >= 0), __ballot(d.hi >= 0)); };
 
@@ -440,12 +386,12 @@ __global__ __launch_bounds__(256, 1) void attn_slab_kernel(AttnArgs a, RestArgs 
     // loads are issued before anything waits for one of them, and the ids and rows of the first
     // tile are requested in their shadow.
     u32x4 qraw[2][KS];
-    auto load_q = [&](int64_t q, int layer) {
+    auto load_q = [&]() {
 #pragma unroll
         for (int hb = 0; hb < 2; ++hb) {
             const int head = 16 * hb + l16;
             const bool ok = head < a.H_q;
-            const unsigned short *qp = (const unsigned short *)(MULTI ? a.Qs[layer] : a.Q) + (q * a.H_q + (ok ? head : 0)) * D_QK + 8 * g;
+            const unsigned short *qp = (const unsigned short *)q_l + (qrow * a.H_q + (ok ? head : 0)) * D_QK + 8 * g;
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) {
                 qraw[hb][ks] = u32x4{0u, 0u, 0u, 0u};
@@ -479,8 +425,8 @@ __global__ __launch_bounds__(256, 1) void attn_slab_kernel(AttnArgs a, RestArgs 
     // The gather registers are refilled chunk by chunk: as soon as chunk ks of tile t+1 has been
     // stored to LDS, the same registers receive chunk ks of tile t+2.
     u32x4 cur[KS];
-    auto gload = [&](const Ids &d, int it) {
-        const unsigned short *pl = row_ptr(d.lo, it), *ph = row_ptr(d.hi, it);
+    auto gload = [&](const Ids &d) {
+        const unsigned short *pl = row_ptr(d.lo), *ph = row_ptr(d.hi);
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) cur[ks] = *(const u32x4 *)(((ks & 1) ? ph : pl) + 64 * (ks >> 1));
     };
@@ -499,91 +445,15 @@ __global__ __launch_bounds__(256, 1) void attn_slab_kernel(AttnArgs a, RestArgs 
                 qreg[hb][ks] = __builtin_bit_cast(bf16x8, raw);
             }
     };
-    // Chained form: Q of the next query is loaded while the outputs of the current one are stored.  Its
-    // only use is pinned to the accumulation registers (settle_q), so the loads target those registers
-    // directly and take no vector registers; they are issued before the epilogue and waited for in
-    // settle_q.  (With fewer than 32 heads the loads sit under a lane mask; there they are inline loads
-    // the compiler does not count, which only makes its own waits conservative, and settle_q's explicit
-    // wait ties every later use to them.)
-    // Only wave 0 loads (each load touches 16 rows of Q, so four waves loading the same 36 KB keep the
-    // CU's one address unit busy for 2.8 us); it then hands Q to the other waves through the tile
-    // buffer that is free between two queries, in the very lane order the operand has.
-    auto load_q_direct = [&](int64_t q, int layer) {
-        if (wave_u != 0) return;
-        // the lane's offset into Q is recomputed from the lane id here: kept live across the tile
-        // loop it would be spilled, and its reload would wait behind the gathers in flight
-        int ln = lane;
-        asm volatile("" : "+v"(ln));
-        const int hd = ln & 15, gq = ln >> 4;
-        const unsigned short *q0 = (const unsigned short *)(MULTI ? a.Qs[layer] : a.Q) + q * a.H_q * D_QK + 8 * gq;
-        if (a.H_q >= 32) {                                // workgroup-uniform: every lane has a head
-#pragma unroll
-            for (int hb = 0; hb < 2; ++hb)
-#pragma unroll
-                for (int ks = 0; ks < KS; ++ks) {
-                    const unsigned short *src = q0 + (16 * hb + hd) * D_QK + 32 * ks;
-                    qreg[hb][ks] = __builtin_bit_cast(bf16x8, *(const u32x4 *)src);
-                }
-        } else {
-#pragma unroll
-            for (int hb = 0; hb < 2; ++hb) {
-                const int head = 16 * hb + hd;
-                const bool ok = head < a.H_q;
-                u32x4 raw[KS];
-#pragma unroll
-                for (int ks = 0; ks < KS; ++ks) raw[ks] = u32x4{0u, 0u, 0u, 0u};
-                if (ok) {
-#pragma unroll
-                    for (int ks = 0; ks < KS; ++ks) {
-                        const unsigned short *src = q0 + head * D_QK + 32 * ks;
-                        asm volatile("global_load_dwordx4 %0, %1, off" : "+a"(raw[ks]) : "v"(src));
-                    }
-                }
-#pragma unroll
-                for (int ks = 0; ks < KS; ++ks) qreg[hb][ks] = __builtin_bit_cast(bf16x8, raw[ks]);
-            }
-        }
-    };
-    auto settle_q = [&](unsigned char *qx) {              // qx: 2 * KS KiB of free LDS
-        unsigned char *mine = qx + lane * 16;
-        if (wave_u == 0) {
-            asm volatile("s_waitcnt vmcnt(0)");
-#pragma unroll
-            for (int hb = 0; hb < 2; ++hb)
-#pragma unroll
-                for (int ks = 0; ks < KS; ++ks) {
-                    u32x4 raw = __builtin_bit_cast(u32x4, qreg[hb][ks]);
-                    asm volatile("" : "+a"(raw));
-                    qreg[hb][ks] = __builtin_bit_cast(bf16x8, raw);
-                    *(u32x4 *)(mine + (hb * KS + ks) * 1024) = raw;
-                }
-        }
-        __syncthreads();
-        if (wave_u != 0) {
-            u32x4 raw[2][KS];
-#pragma unroll
-            for (int hb = 0; hb < 2; ++hb)
-#pragma unroll
-                for (int ks = 0; ks < KS; ++ks) raw[hb][ks] = *(const u32x4 *)(mine + (hb * KS + ks) * 1024);
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int hb = 0; hb < 2; ++hb)
-#pragma unroll
-                for (int ks = 0; ks < KS; ++ks) {
-                    asm volatile("" : "+a"(raw[hb][ks]));
-                    qreg[hb][ks] = __builtin_bit_cast(bf16x8, raw[hb][ks]);
-                }
-        }
-    };
-    int g0 = 0;                                           // stream position of the query's tile 0 (buffer parity)
     {
         const Ids d0 = fetch_ids(0), d1 = fetch_ids(1);
         ids_n2 = fetch_ids(2);
         __builtin_amdgcn_sched_barrier(0);
-        // one wave loads Q (see load_q_direct above) and hands it over; its loads go out behind the
-        // id fetches, so that the ids, and with them the first gather, do not wait for Q
-        if (wave_u == 0) load_q(q_cur(), cs.layer);
-        gload(d0, 0);
+        // One wave loads Q (each load touches 16 rows of it, so four waves loading the same 36 KB keep the CU's one address
+        // unit busy for 2.8 us) and hands it over; its loads go out behind the id fetches, so that the ids, and with them the
+        // first gather, do not wait for Q
+        if (wave_u == 0) load_q();
+        gload(d0);
         __builtin_amdgcn_sched_barrier(0);
         {   // Q from wave 0 to the others through the second tile buffer (unused until step 0 stages tile 1)
             unsigned char *mine = tbuf + TBUFB + lane * 16;
@@ -605,7 +475,7 @@ __global__ __launch_bounds__(256, 1) void attn_slab_kernel(AttnArgs a, RestArgs 
         pin_q();
         vm_cur = ids_mask(d0);
         vm_n1 = ids_mask(d1);
-        const unsigned short *pl = row_ptr(d1.lo, 1), *ph = row_ptr(d1.hi, 1);
+        const unsigned short *pl = row_ptr(d1.lo), *ph = row_ptr(d1.hi);
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
             *(u32x4 *)(tbuf + st_off + (ks & 1) * 8 * ROWB + 128 * (ks >> 1)) = cur[ks];
@@ -624,7 +494,7 @@ __global__ __launch_bounds__(256, 1) void attn_slab_kernel(AttnArgs a, RestArgs 
     auto step = [&](int it, auto have_prev, auto have_cur, auto stage_next, auto load_next2) {
         constexpr bool kPrev = decltype(have_prev)::value, kCur = decltype(have_cur)::value;
         constexpr bool kStage = decltype(stage_next)::value, kLoad = decltype(load_next2)::value;
-        const int buf = (g0 + it) & 1;
+        const int buf = it & 1;
         Ids ids_n3 = ids_n2;
         if constexpr (kCur) ids_n3 = fetch_ids(it + 3);
         const unsigned char *tb = tbuf + buf * TBUFB;                 // tile it
@@ -782,7 +652,7 @@ __global__ __launch_bounds__(256, 1) void attn_slab_kernel(AttnArgs a, RestArgs 
         // O += P V for tile it-1, with the staging of tile it+1 (nobody reads that buffer any more)
         // and the gather of tile it+2 issued in the shadow of the MFMAs
         unsigned char *tn = tbuf + (buf ^ 1) * TBUFB + st_off;
-        const unsigned short *pl = row_ptr(ids_n2.lo, it + 2), *ph = row_ptr(ids_n2.hi, it + 2);
+        const unsigned short *pl = row_ptr(ids_n2.lo), *ph = row_ptr(ids_n2.hi);
         auto stage = [&](int ks) {
             if constexpr (kStage) {
                 if (ks < KS) {
@@ -836,18 +706,12 @@ __global__ __launch_bounds__(256, 1) void attn_slab_kernel(AttnArgs a, RestArgs 
         const float l_head = lbuf[l32] + lbuf[32 + l32] + lbuf[64 + l32] + lbuf[96 + l32];   // head l32
         const float m_head = m_c;
         {
-            if constexpr (SPLIT) {
-                // partial of this split: its reference maximum and row sum (the output below is
-                // normalised by that sum; the merge weighs the splits by their share of the total)
-                if (wave == 0 && hh == 0 && l32 < a.H_q) {
-                    float *ml = a.part_ml + ((qrow * a.n_splits + sp) * a.H_q + l32) * 2;
-                    ml[0] = m_head;
-                    ml[1] = l_head;
-                }
-            } else {
-                if (wave == 0 && hh == 0 && l32 < a.H_q && a.lse)
-                    a.lse[q_cur() * a.H_q + l32] =
-                        (l_head > 0.f) ? (m_head + __builtin_log2f(l_head)) * 0.6931471805599453f : -INFINITY;
+            // partial of this split: its reference maximum and row sum (the output below is
+            // normalised by that sum; the merge weighs the splits by their share of the total)
+            if (wave == 0 && hh == 0 && l32 < a.H_q) {
+                float *ml = a.part_ml + ((gq * a.n_splits + sp) * a.H_q + l32) * 2;
+                ml[0] = m_head;
+                ml[1] = l_head;
             }
             // accumulator element i belongs to head 8 (i / 4) + 4 hh + i % 4: the sums of the lane's
             // 16 heads come straight from the four waves' partials (independent 16-byte reads; a
@@ -867,99 +731,46 @@ __global__ __launch_bounds__(256, 1) void attn_slab_kernel(AttnArgs a, RestArgs 
             int tx = tid;
             asm volatile("" : "+v"(tx));
             const int o_lane = 32 * (tx >> 6) + (tx & 31), o_hh = (tx >> 5) & 1;
-            // (the same loops twice: one body for all three destinations cost the chains 1 %)
-            if constexpr (SPLIT) {
-                auto put = [&](auto *o_row) __attribute__((always_inline)) {
-                    typedef std::remove_pointer_t<decltype(o_row)> E;
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) {
-                        const int hq = 8 * (i >> 2) + 4 * o_hh + (i & 3); // O row (head) of accumulator element i
-                        const float inv = inv4[i >> 2][i & 3];
-                        if (all_heads || hq < a.H_q) {
-#pragma unroll
-                            for (int nb = 0; nb < NBW; ++nb) o_row[hq * D_V + 128 * nb] = (E)(oacc[nb][i] * inv);
-                        }
-                    }
-                };
-                const int64_t part = (qrow * a.n_splits + sp) * a.H_q * D_V + o_lane;
-                if (a.part_wide)
-                    put((float *)a.part_o + part);
-                else
-                    put((__bf16 *)a.part_o + part);
-            } else {
-                __bf16 *o_row = (__bf16 *)(MULTI ? a.Os[cs.layer] : a.O) + q_cur() * a.H_q * D_V + o_lane;
+            auto put = [&](auto *o_row) __attribute__((always_inline)) {
+                typedef std::remove_pointer_t<decltype(o_row)> E;
 #pragma unroll
                 for (int i = 0; i < 16; ++i) {
-                    const int hq = 8 * (i >> 2) + 4 * o_hh + (i & 3);
+                    const int hq = 8 * (i >> 2) + 4 * o_hh + (i & 3); // O row (head) of accumulator element i
                     const float inv = inv4[i >> 2][i & 3];
-                    __bf16 *po = o_row + hq * D_V;
-                    if (all_heads) {
+                    if (all_heads || hq < a.H_q) {
 #pragma unroll
-                        for (int nb = 0; nb < NBW; ++nb) po[128 * nb] = (__bf16)(oacc[nb][i] * inv);
-                    } else if (hq < a.H_q) {
-#pragma unroll
-                        for (int nb = 0; nb < NBW; ++nb) po[128 * nb] = (__bf16)(oacc[nb][i] * inv);
+                        for (int nb = 0; nb < NBW; ++nb) o_row[hq * D_V + 128 * nb] = (E)(oacc[nb][i] * inv);
                     }
                 }
-            }
+            };
+            const int64_t part = (gq * a.n_splits + sp) * a.H_q * D_V + o_lane;
+            if (a.part_wide)
+                put((float *)a.part_o + part);
+            else
+                put((__bf16 *)a.part_o + part);
         }
     };
 
     constexpr std::true_type T{};
     constexpr std::false_type F{};
-    if (!chain) {
-        // one query (or one split of it): step 0 has no previous tile, step ntiles has no current one
-        if (ntiles == 1) {
-            step(0, F, T, F, F);
-        } else if (ntiles == 2) {
-            step(0, F, T, T, F);
-            step(1, T, T, F, F);
-        } else {
-            step(0, F, T, T, T);
-            int it = 1;
+    // Step 0 has no previous tile, step ntiles has no current one.  (In this order of cases nothing is spilled; with the short ones
+    // first twelve values were, and scratch costs a launch 1.1 us.)
+    if (ntiles >= 3) {
+        step(0, F, T, T, T);
+        int it = 1;
 #pragma unroll 1
-            for (; it + 2 < ntiles; ++it) step(it, T, T, T, T);
-            step(it, T, T, T, F);
-            ++it;
-            step(it, T, T, F, F);
-        }
-        step(ntiles, T, F, F, F);
-        finish();
-        return;
+        for (; it + 2 < ntiles; ++it) step(it, T, T, T, T);
+        step(it, T, T, T, F);
+        ++it;
+        step(it, T, T, F, F);
+    } else if (ntiles == 2) {
+        step(0, F, T, T, F);
+        step(1, T, T, F, F);
+    } else {
+        step(0, F, T, F, F);
     }
-    if constexpr (!SPLIT) {
-        // Chained queries.  The last two steps of a query stage and gather the first tiles of the
-        // next one (dead tiles after the workgroup's last query: row 0, masked), so a query ends
-        // in exactly the state the prologue sets up: tile 0 in LDS, tile 1 in the gather
-        // registers, ids of tile 2 at hand.
-        for (;;) {
-            step(0, F, T, T, T);
-#pragma unroll 1
-            for (int it = 1; it < cs.nt; ++it) step(it, T, T, T, T);
-            step(cs.nt, T, F, F, F);
-            const bool more = qnext < nq;
-            if (more) load_q_direct(MULTI ? ns.q : qnext, ns.layer);               // lands while the outputs are stored
-            finish();
-            if (!more) break;
-            qrow = qnext;
-            qnext += gridDim.x;
-            g0 = (g0 + cs.nt) & 1;
-            cs = ns;
-            ns = src_of(qnext);
-#pragma unroll
-            for (int nb = 0; nb < NBW; ++nb)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) oacc[nb][i] = 0.f;
-#pragma unroll
-            for (int hb = 0; hb < 2; ++hb) {
-                m_all[hb] = -INFINITY;
-                m_ref[hb] = -INFINITY;
-                l_own[hb] = 0.f;
-            }
-            m_c = -INFINITY;
-            settle_q(tbuf + ((g0 ^ 1) & 1) * TBUFB);      // the drained tile's buffer: nobody touches it before step 0's barrier
-        }
-    }
+    step(ntiles, T, F, F, F);
+    finish();
 }
 
 // ---- dense form (rows whose selection is a whole prefix of the cache) ---------------------------------------------
@@ -1358,6 +1169,488 @@ __global__ __launch_bounds__(512, 2) void attn_dense_kernel(AttnArgs a, DenseArg
     }
 }
 
+// ---- stream form (unsplit rows of 576/512 features) ----------------------------------------------------------------
+// One workgroup of eight waves per CU walks queries q0, q0 + gridDim.x, ... as one stream of granules of 32 rows: the 32 heads of
+// a query's Q, then its selected rows, then the next query's Q.  A granule is gathered eight lanes to a 128-byte line and passes through
+// a ring of four LDS buffers; one barrier per granule ("period").  Two roles, one wave of each per SIMD:
+//   scores   waves 0-3 in two pairs, which take alternate granules and have two periods for one.  A wave holds all of Q (144
+//            registers, read from Q's granule) and scores 16 rows of it for 32 heads: every score operand crosses LDS once.
+//            Softmax against a reference that moves only when a score exceeds it by 2^kLazyLog2; P and the reference to LDS
+//   output   waves 4-7, value columns 128 w .. 128 w + 127, O^T += V^T P^T: a lane owns a head, so that references, factors
+//            and row sums are a lane's own.  They also bring the granules: two in registers, in flight for two periods, the
+//            ids six periods ahead
+// In period p granule p + 1 goes to LDS, p and p - 1 are scored, V and P of p - 2 go to registers and the product of p - 3 is
+// taken from registers: whatever a wave waits for was requested a period ago, and Q of the next query, its first rows and the
+// outputs of the last one take their places in the stream.
+// What bounds it.  A wave per SIMD and role issues an instruction every 4 to 5 clocks at best, and what a unit has not taken
+// blocks the ones behind it: with every phase in each of four waves (the row-slab form) 32 rows took 1950 clocks, and only the gather, the
+// LDS traffic or the MFMAs of a phase were busy at a time.  Here the output waves alone take 1000 clocks, the scores waves alone 1000, both
+// 1230, of which the matrix cores are busy 544.  The clock falls with it, from 2.35 GHz to 2.0, 1.85 with rows from beyond L2:
+// the rest is power.  2048 queries x 2048 of 32768 rows, 32 heads: 450 us in chains of the row-slab form, 355 here.  Ids requested two periods ahead, addresses worked out at the
+// start of a period, outputs stored straight from the accumulators: 20 % slower together.  Three granules in flight need more
+// registers than there are and gain nothing where two are enough; with 131072 rows (HBM) both forms take the gather's time.
+constexpr int kGranule = 32;                 // selected rows that reach LDS together
+constexpr int kStreamRing = 4;               // of them resident
+constexpr int kStreamDepth = 2;              // of them in registers on their way there
+constexpr int kStreamIds = 4;                // periods between the request of a granule's ids and that of its rows
+
+// PG: the KV cache may be ragged and / or paged.
+// MULTI: a.n_layers layers in one launch, or the last rows of several sequences (a.row_gap): a query's place in the tensors
+// is then not its number.
+// REST: the rows of sequence blockIdx.y behind those that the dense form has taken.  How many that are is device data, so the
+// workgroups, as many as for all rows, find out first and share what is left (one round trip to memory, about 1 us).
+template <bool PG, bool MULTI, bool REST>
+__global__ __launch_bounds__(512, 2) void attn_stream_kernel(AttnArgs a, RestArgs ra)
+{
+    constexpr int D_QK = 576, D_V = 512;
+    constexpr int KS = D_QK / 32, KS1 = 12;               // contraction steps; those of a granule's first period (8 .. 14: within 2 %)
+    constexpr int ROWB = D_QK * 2 + kSlabPad, GB = kGranule * ROWB;
+    constexpr int PSTR = kGranule * 2 + 16, PB = 32 * PSTR;
+    constexpr int RING = 6;                               // A-operand reads in flight
+    constexpr int D = kStreamDepth, DI = kStreamIds;      // (a set of registers is that of the granule's number modulo D, DI)
+    static_assert(DI % D == 0, "the loop is unrolled by DI");
+    if constexpr (REST) {
+        const int64_t bs = blockIdx.y, o = bs * ra.n_chunks;
+        const int t0 = __builtin_amdgcn_readfirstlane(min(lead_rows(ra.lead + o, ra.n_chunks), lead_rows(ra.lead2 + o, ra.n_chunks)));
+        if (t0 >= ra.n_rows) return;
+        const int64_t row = bs * a.Tq + t0;
+        a.Tq = ra.n_rows - t0;
+        a.Q = (const __bf16 *)a.Q + row * a.H_q * D_QK;
+        a.KV = (const __bf16 *)a.KV + bs * a.Lk * a.row_elems;
+        a.O = (__bf16 *)a.O + row * a.H_q * D_V;
+        a.idx += row * a.k_sel;
+        if (a.lse) a.lse += row * a.H_q;
+        a.B = 1;
+    }
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    unsigned char *tbuf = smem;                           // [kStreamRing][32][ROWB]
+    unsigned char *pbuf = smem + kStreamRing * GB;        // [2][32 heads][PSTR]
+    float *lsum = (float *)(pbuf + 2 * PB);               // [2 by query][32 heads][4 waves] row sums
+    float *lref = lsum + 2 * 32 * 4;                      // [2][32][4] and the references they have
+    float *mbuf = lref + 2 * 32 * 4;                      // [2 by granule][32 heads][2 key halves] references of P
+    unsigned char *filled = (unsigned char *)(mbuf + 2 * 32 * 2);            // [kStreamRing][32 rows][8] 1: the slot holds an entry
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l16 = lane & 15, l32 = lane & 31, hh = lane >> 5, g = lane >> 4;
+    const int w = wave & 3;
+    // queries of the workgroup: q0, q0 + gridDim.x, ...
+    const unsigned nq_layer = (unsigned)(a.B * a.Tq), nq = MULTI ? nq_layer * a.n_layers : nq_layer;
+    unsigned q0 = blockIdx.x;
+    if ((gridDim.x & 7u) == 0) q0 = (blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+    if (q0 >= nq) return;
+    const int n_mine = (int)((nq - q0 + gridDim.x - 1) / gridDim.x);
+    auto granules = [&](unsigned gq) -> int {             // of a query, at least one
+        int n = a.k_sel;
+        if (a.causal_pos0 >= 0) {
+            const int64_t held = a.causal_pos0 + (MULTI ? gq % nq_layer : gq) % (unsigned)a.Tq + 1;
+            if (held < n) n = (int)held;
+        }
+        return max(1, (n + kGranule - 1) / kGranule);
+    };
+
+    if (wave < 4) {
+        const int pair = w >> 1, kh = w & 1;
+        bf16x8 qv[KS][2];
+        auto load_q = [&](int at) __attribute__((always_inline)) {
+            const unsigned char *qr = tbuf + (at & (kStreamRing - 1)) * GB + l16 * ROWB + 16 * g;
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+                for (int r = 0; r < 2; ++r) qv[ks][r] = *(const bf16x8 *)(qr + 16 * r * ROWB + 64 * ks);
+        };
+        const int ka_off = (16 * kh + dense_row(l16)) * ROWB + 16 * g;
+        const int pw_off = l16 * PSTR + 32 * kh + 8 * g;
+        float m_c[2] = {-INFINITY, -INFINITY}, l_own[2] = {0.f, 0.f};
+        auto publish = [&](int n) __attribute__((always_inline)) {       // row sums of query n, and a new start
+            float *ls = lsum + (n & 1) * 128 + w, *lr = lref + (n & 1) * 128 + w;
+#pragma unroll
+            for (int r = 0; r < 2; ++r) {
+                const float l = xsum16_32(l_own[r]);
+                if (g == 0) {
+                    ls[4 * (16 * r + l16)] = l;
+                    lr[4 * (16 * r + l16)] = m_c[r];
+                }
+                m_c[r] = -INFINITY;
+                l_own[r] = 0.f;
+            }
+        };
+        bf16x8 ka[RING];
+        f32x4 s4[2], odd[2];                              // two accumulation chains: half of the roundings in one
+        auto steps = [&](const unsigned char *tb, auto k0_c, auto k1_c) __attribute__((always_inline)) {
+            constexpr int k0 = decltype(k0_c)::value, k1 = decltype(k1_c)::value;
+            unroll<k1 - k0>([&](auto i_c) __attribute__((always_inline)) {
+                constexpr int ks = k0 + decltype(i_c)::value;
+#pragma unroll
+                for (int r = 0; r < 2; ++r) {
+                    f32x4 &c = ks % 2 ? odd[r] : s4[r];
+                    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[ks % RING], qv[ks][r], ks < 2 ? f32x4{0.f, 0.f, 0.f, 0.f} : c, 0, 0, 0);
+                }
+                if constexpr (ks + RING < KS) ka[ks % RING] = *(const bf16x8 *)(tb + 64 * (ks + RING));
+                __builtin_amdgcn_sched_barrier(0);
+            });
+        };
+        constexpr std::integral_constant<int, 0> c0{};
+        constexpr std::integral_constant<int, KS1> c1{};
+        constexpr std::integral_constant<int, KS> c2{};
+
+        __syncthreads();                                  // period -1
+        if (pair) __syncthreads();                        // period 0
+        int at_q = 0;                                     // the query's Q in the stream, its granules behind it
+#pragma unroll 1
+        for (int n = 0; n < n_mine; ++n) {
+            const int last = at_q + granules(q0 + (unsigned)n * gridDim.x);
+            const bool own = ((at_q ^ pair) & 1) == 0;    // Q takes the place of a granule of this pair
+            if (n > 0) publish(n - 1);
+            load_q(at_q);
+            if (own) {
+                __syncthreads();
+                __syncthreads();
+            }
+#pragma unroll 1
+            for (int at = at_q + (own ? 2 : 1); at <= last; at += 2) {
+                const unsigned char *tb = tbuf + (at & (kStreamRing - 1)) * GB + ka_off;
+#pragma unroll
+                for (int r = 0; r < RING; ++r) ka[r] = *(const bf16x8 *)(tb + 64 * r);
+                __builtin_amdgcn_sched_barrier(0);
+                steps(tb, c0, c1);
+                __syncthreads();
+                typedef __attribute__((ext_vector_type(2))) float f32x2;
+                const int vm = *(const int *)(filled + (at & (kStreamRing - 1)) * 256 + (16 * kh + l16) * 8);
+                f32x2 mk[2];
+#pragma unroll
+                for (int r = 0; r < 2; ++r) mk[r] = *(const f32x2 *)(mbuf + ((at - 1) & 1) * 64 + 2 * (16 * r + l16));
+                __builtin_amdgcn_sched_barrier(0);
+                steps(tb, c1, c2);
+#pragma unroll
+                for (int r = 0; r < 2; ++r)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) s4[r][i] += odd[r][i];
+                const unsigned rows = (unsigned)__ballot(vm != 0) & 0xFFFFu;
+                if (rows != 0xFFFFu) {
+                    const unsigned mine = rows >> (8 * (g >> 1) + (g & 1));    // the lane's keys are two apart
+#pragma unroll
+                    for (int r = 0; r < 2; ++r)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) s4[r][i] = (mine >> 2 * i) & 1u ? s4[r][i] : -INFINITY;
+                }
+                float m_use[2], mx[2];
+#pragma unroll
+                for (int r = 0; r < 2; ++r) {
+                    m_use[r] = at - 1 > at_q ? fmaxf(m_c[r], fmaxf(mk[r][0], mk[r][1])) : m_c[r];
+                    mx[r] = fmaxf(fmaxf(s4[r][0], s4[r][1]), fmaxf(s4[r][2], s4[r][3])) * a.scale_log2e;
+                }
+                if (__ballot(mx[0] > m_use[0] + kLazyLog2 || mx[1] > m_use[1] + kLazyLog2) != 0ull) {
+#pragma unroll
+                    for (int r = 0; r < 2; ++r) {
+                        mx[r] = xmax16_32(mx[r]);
+                        m_use[r] = mx[r] > m_use[r] + kLazyLog2 ? mx[r] : m_use[r];
+                    }
+                }
+                if (__ballot(m_use[0] != m_c[0] || m_use[1] != m_c[1]) != 0ull) {
+#pragma unroll
+                    for (int r = 0; r < 2; ++r) {
+                        l_own[r] *= m_use[r] == m_c[r] ? 1.f : fast_exp2(m_c[r] - m_use[r]);
+                        m_c[r] = m_use[r];
+                    }
+                }
+#pragma unroll
+                for (int r = 0; r < 2; ++r) {
+                    const float m_safe = m_c[r] == -INFINITY ? 0.f : m_c[r];   // (no key so far: every p is 2^-inf = 0)
+                    s16x4 pk;
+                    float p[4];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        p[i] = fast_exp2(__builtin_fmaf(s4[r][i], a.scale_log2e, -m_safe));
+                        pk[i] = __builtin_bit_cast(short, (__bf16)p[i]);
+                    }
+                    *(s16x4 *)(pbuf + (at & 1) * PB + pw_off + 16 * r * PSTR) = pk;
+                    if (g == 0) mbuf[(at & 1) * 64 + 2 * (16 * r + l16) + kh] = m_c[r];
+                    l_own[r] += (p[0] + p[1]) + (p[2] + p[3]);
+                }
+                __syncthreads();
+            }
+            at_q = last + 1;
+        }
+        publish(n_mine - 1);
+        // as many barriers as the output waves have: those of the periods -1 .. at_q + 3, in whole rounds of DI
+        const int done = at_q + (((at_q ^ pair) & 1) == 0 ? 1 : 2);
+        for (int i = done; i < (at_q + 4 + DI) / DI * DI; ++i) __syncthreads();
+        return;
+    }
+
+    // ---- output waves ----
+    const int gr = lane >> 3, gp = lane & 7;              // gather role: row 8 w + gr, 16-byte piece
+    const int my_row = 8 * w + gr;
+    struct Place { int n, ng; bool is_q; const int32_t *idx; const unsigned short *kv, *q, *src; int len, b; } pl;
+    auto tensor_row = [&](unsigned gq, int &layer, int &b) -> int64_t {
+        layer = MULTI ? layer_of(a, gq) : 0;
+        const unsigned qq = MULTI ? gq - layer * nq_layer : gq;
+        b = (int)(qq / (unsigned)a.Tq);
+        return MULTI ? (int64_t)qq + (int64_t)b * a.row_gap : (int64_t)qq;
+    };
+    auto open = [&](unsigned gq) {
+        int layer;
+        const int64_t row = tensor_row(gq, layer, pl.b);
+        pl.idx = a.idx + row * a.k_sel;
+        pl.q = (const unsigned short *)(MULTI ? a.Qs[layer] : a.Q) + row * a.H_q * D_QK;
+        pl.kv = (const unsigned short *)(MULTI ? a.KVs[layer] : a.KV) + (PG && a.pv.page_table ? 0 : (int64_t)pl.b * a.Lk * a.row_elems);
+        pl.len = PG && a.pv.seq_lens ? min(load_uniform(a.pv.seq_lens + pl.b), a.Lk) : a.Lk;
+        pl.ng = granules(gq);
+    };
+    pl.n = 0;
+    open(q0);
+    pl.is_q = true;
+    pl.src = pl.q;
+    // per register set: ids of a granule and what they belong to
+    int32_t ids[DI];
+    const unsigned short *base[DI];
+    int n_slots[DI], len[DI], seq[DI];                    // n_slots < 0: the rows are Q
+    int64_t prow[DI];
+    int ok_pg[DI];
+    const unsigned short *base_pg[DI];
+    int n_slots_pg[DI];
+    int vm[D];
+    u32x4 cur[D][9];
+    // the place: granules of the query behind this one, the slots left, the byte of the index row that the lane's slot starts at
+    int left = 0, n_run = -1;
+    unsigned slot_b = 4 * my_row;
+    const unsigned last_b = 4 * (a.k_sel - 1);
+    auto request = [&](auto s_c) __attribute__((always_inline)) {
+        constexpr int s = decltype(s_c)::value;
+        ids[s] = *(const int32_t *)((const char *)pl.idx + min(slot_b, last_b));
+        base[s] = pl.src;
+        n_slots[s] = n_run;
+        len[s] = pl.len;
+        seq[s] = pl.b;
+    };
+    auto advance = [&]() __attribute__((always_inline)) {
+        n_run -= kGranule;
+        slot_b += 4 * kGranule;
+        if (__builtin_expect(--left < 0, 0)) {
+            slot_b = 4 * my_row;
+            if (pl.is_q && pl.n < n_mine) {               // behind Q: the query's granules
+                pl.is_q = false;
+                pl.src = pl.kv;
+                left = pl.ng - 1;
+                n_run = a.k_sel;
+            } else {                                      // the next query's Q; at the end of the stream the last one's, for nobody
+                if (pl.n < n_mine) ++pl.n;
+                if (pl.n < n_mine) open(q0 + (unsigned)pl.n * gridDim.x);
+                pl.is_q = true;
+                pl.src = pl.q;
+                left = 0;
+                n_run = -1;
+            }
+        }
+    };
+    auto take = [&](auto s_c) __attribute__((always_inline)) {
+        request(s_c);
+        advance();
+    };
+    const int q_row = min(my_row, a.H_q - 1);
+    // the ids of a set -> what gather() needs (paged: a table entry per row, requested here)
+    auto place = [&](auto s_c) __attribute__((always_inline)) {
+        constexpr int s = decltype(s_c)::value;
+        if constexpr (PG) {
+            const int32_t v = ids[s];
+            const bool ok = (int)(my_row < n_slots[s]) & (int)((unsigned)v < (unsigned)len[s]);
+            // empty slots read row 0 of the cache (never a page-table entry: the sequence may own no page)
+            int64_t row = ok ? v : 0;
+            if (a.pv.page_table && ok) row = paged_row(a.pv, seq[s], v);
+            prow[s] = row;
+            ok_pg[s] = ok;
+            base_pg[s] = base[s];
+            n_slots_pg[s] = n_slots[s];
+        }
+    };
+    auto gather_src = [&](auto s_c) __attribute__((always_inline)) -> uint64_t {
+        constexpr int s = decltype(s_c)::value;
+        const bool isq = (PG ? n_slots_pg[s] : n_slots[s]) < 0;
+        const int stride = isq ? D_QK : a.row_elems;
+        if constexpr (PG) {
+            vm[s % D] = ok_pg[s];
+            return (uint64_t)base_pg[s] + ((isq ? (int64_t)q_row : prow[s]) * stride + 8 * gp) * 2;
+        } else {
+            const int32_t v = ids[s];
+            const bool ok = (int)(my_row < n_slots[s]) & (int)((unsigned)v < (unsigned)a.Lk);
+            vm[s % D] = ok;
+            const int row = isq ? q_row : (ok ? v : 0);
+            return (uint64_t)base[s] + ((uint64_t)(unsigned)row * (unsigned)(2 * stride) + 16 * gp);
+        }
+    };
+    auto load = [&](auto s_c, uint64_t from, int c0, int n) __attribute__((always_inline)) {
+        constexpr int s = decltype(s_c)::value;
+#pragma unroll
+        for (int c = c0; c < c0 + n; ++c) cur[s][c] = *(const __attribute__((address_space(1))) u32x4 *)(from + 128 * c);
+    };
+    // Granules 0 .. D - 1 on their way, the source of granule D, the ids behind; requested in the order that the periods
+    // below have, so that waits by position find the same queue behind the first period as behind any other.
+    uint64_t src, first[D];
+    unroll<DI>([&](auto s_c) __attribute__((always_inline)) { take(s_c); });
+    if constexpr (PG) unroll<DI>([&](auto s_c) __attribute__((always_inline)) {
+        place(s_c);
+        take(s_c);
+    });
+    unroll<D>([&](auto s_c) __attribute__((always_inline)) {
+        constexpr int s = decltype(s_c)::value;
+        __builtin_amdgcn_sched_barrier(0);
+        first[s] = gather_src(s_c);
+        place(s_c);
+        load(s_c, first[s], 0, 5);
+        __builtin_amdgcn_sched_barrier(0);
+        take(s_c);
+        __builtin_amdgcn_sched_barrier(0);
+        load(s_c, first[s], 5, 4);
+        __builtin_amdgcn_sched_barrier(0);
+    });
+    src = gather_src(std::integral_constant<int, D % DI>{});
+    place(std::integral_constant<int, D % DI>{});
+    take(std::integral_constant<int, D % DI>{});
+
+    f32x16 o_acc[4];                                      // O^T: columns 32 nb .., the lane's row is head l32
+#pragma unroll
+    for (int nb = 0; nb < 4; ++nb)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) o_acc[nb][e] = 0.f;
+    typedef __attribute__((ext_vector_type(8))) short s16x8;
+    typedef __attribute__((ext_vector_type(2))) float f32x2;
+    typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+    const int st_off = my_row * ROWB + 16 * gp;
+    const int tr_off = (8 * hh + 2 * (l16 >> 2)) * ROWB + 256 * w + 32 * (g & 1) + 8 * (l16 & 3);
+    const int pr_off = l32 * PSTR + 16 * hh;
+    bf16x8 pa[2];
+    s16x4 vq[2][4][2];
+    float m_c = -INFINITY;                                // reference of the accumulators
+    int m = 0, to_q = 4;                                  // Q seen by the product so far, periods until the next one
+
+    // Outputs of a query, through the rows of the ring that this wave is about to fill (nobody else touches them in this
+    // period): lanes of a store then cover whole lines.  Straight from the accumulators (8 bytes of 32 rows in each of 16
+    // stores) a query's outputs kept the four waves for 5000 clocks.
+    auto finish = [&](int slot) __attribute__((always_inline)) {
+        int ln = lane;                                    // (kept from before the loop, what follows from it would be spilled)
+        asm volatile("" : "+v"(ln));
+        const int row_l = ln & 31, half = ln >> 5;
+        const f32x4 ls = *(const f32x4 *)(lsum + ((m - 1) & 1) * 128 + 4 * row_l), lr = *(const f32x4 *)(lref + ((m - 1) & 1) * 128 + 4 * row_l);
+        float l = 0.f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) l += lr[i] == -INFINITY ? 0.f : ls[i] * fast_exp2(lr[i] - m_c);
+        const float inv = l > 0.f ? __builtin_amdgcn_rcpf(l) : 0.f;
+        int layer, b;
+        const unsigned gq = q0 + (unsigned)(m - 1) * gridDim.x;
+        const int64_t row = tensor_row(gq, layer, b);
+        if (w == 0 && half == 0 && row_l < a.H_q && a.lse) {
+            // (in 64 bits: the reference of 16 keys leaves a larger logarithm, and so a coarser sum, than that of more)
+            a.lse[row * a.H_q + row_l] = l > 0.f ? (float)(((double)m_c + (double)__builtin_log2f(l)) * 0.6931471805599453) : -INFINITY;
+        }
+        constexpr int OSTR = 256 + 16;
+        static_assert(32 * OSTR <= 8 * ROWB, "32 heads of 256 bytes");
+        unsigned char *ob = tbuf + slot * GB + 8 * w * ROWB;
+#pragma unroll
+        for (int nb = 0; nb < 4; ++nb)
+#pragma unroll
+            for (int qd = 0; qd < 4; ++qd) {
+                s16x4 v;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] = __builtin_bit_cast(short, (__bf16)(o_acc[nb][4 * qd + e] * inv));
+                *(s16x4 *)(ob + row_l * OSTR + (32 * nb + 8 * qd + 4 * half) * 2) = v;
+            }
+        unsigned short *const o = (unsigned short *)(MULTI ? a.Os[layer] : a.O) + row * a.H_q * D_V + 128 * w;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const int head = 4 * k + (ln >> 4);
+            const u32x4 v = *(const u32x4 *)(ob + head * OSTR + 16 * (ln & 15));
+            unsigned short *d = o + head * D_V + 8 * (ln & 15);
+            if (head < a.H_q) {
+                if ((uintptr_t)o % 16 == 0) {
+                    *(u32x4 *)d = v;
+                } else {                                  // (any address of a bf16 will do)
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) d[e] = (unsigned short)(v[e / 2] >> 16 * (e & 1));
+                }
+            }
+        }
+    };
+
+    // Period p: output product of granule p - 3 from operands read a period ago; those of granule p - 2 take their
+    // registers, granule p + 1 goes to LDS and granule p + 1 + D into its registers.  Where granule p - 3 is Q, the outputs of
+    // the query before it leave first and the product, of nothing, is dropped.  The source of the next period's gather is
+    // worked out here, between the MFMAs.  A wave issues an instruction every 4 to 5 clocks at best and this one has the most
+    // of them: unrolled over the ring's buffers, so that their addresses are constants.
+    static_assert(DI == kStreamRing, "a period's buffers are known where it is unrolled");
+    auto pin = [](auto &x) __attribute__((always_inline)) { asm volatile("" : "+v"(x)); };   // worked out here, not where it is used
+    int st[2] = {st_off, st_off + 2 * GB}, vb[2] = {tr_off, tr_off + 2 * GB};     // (offsets have 16 bits)
+    pin(st[1]);
+    pin(vb[1]);
+    auto period = [&](auto s_c) __attribute__((always_inline)) {
+        constexpr int g1 = decltype(s_c)::value;          // granule p + 1 modulo DI
+        constexpr int s = g1 % D, s_next = (s + 1) % D, g2 = (g1 + 1) % DI;      // g2: granule p - 2
+        constexpr std::integral_constant<int, (g1 + 1 + D) % DI> s1{};
+        if (__builtin_expect(to_q == 0, 0)) {
+            if (m > 0) finish(g1);
+        }
+        f32x2 mj;
+        uint64_t src1 = 0;
+        bool moved = false;
+        unroll<8>([&](auto i_c) __attribute__((always_inline)) {
+            constexpr int i = decltype(i_c)::value, h = i >> 2, nb = i & 3;
+            const s16x8 v = {vq[h][nb][0][0], vq[h][nb][0][1], vq[h][nb][0][2], vq[h][nb][0][3], vq[h][nb][1][0], vq[h][nb][1][1], vq[h][nb][1][2], vq[h][nb][1][3]};
+            o_acc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, v), pa[h], o_acc[nb], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+                vq[h][nb][u] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(tbuf + vb[g2 / 2] + (g2 % 2) * GB + 16 * h * ROWB + 64 * nb + u * ROWB));
+            if constexpr (nb == 3) pa[h] = *(const bf16x8 *)(pbuf + pr_off + (g2 % 2) * PB + 32 * h);
+            if constexpr (i == 0) mj = *(const f32x2 *)(mbuf + (g2 % 2) * 64 + 2 * l32);
+#pragma unroll
+            for (int c = i; c < (i == 7 ? 9 : i + 1); ++c) *(u32x4 *)(tbuf + st[g1 / 2] + (g1 % 2) * GB + 128 * c) = cur[s][c];
+            __builtin_amdgcn_sched_barrier(0);            // (loads ahead of the stores would need registers of their own)
+            load(std::integral_constant<int, s>{}, src, i, i == 7 ? 2 : 1);
+            if constexpr (i == 3) {
+                filled[g2 * 256 + w * 64 + lane] = (unsigned char)vm[s_next];      // granule p + 2
+                src1 = gather_src(s1);
+                pin(src1);
+                pin(vm[s_next]);
+                place(s1);
+            }
+            if constexpr (i == 4) request(s1);
+            if constexpr (i == 5) advance();
+            if constexpr (i == 6) moved = __ballot(mj[0] != m_c || mj[1] != m_c) != 0ull;
+            __builtin_amdgcn_sched_barrier(0);
+        });
+        if (__builtin_expect(moved | (to_q <= 1), 0)) {
+            if (to_q != 1) {                              // (granule p - 2 is Q: it has no P)
+                // another query, or P of granule p - 2 has another reference than the accumulators
+                const bool is_q = to_q == 0;
+                const float old = is_q ? -INFINITY : m_c;
+                m_c = fmaxf(old, fmaxf(mj[0], mj[1]));
+                const float f = old == m_c ? 1.f : fast_exp2(old - m_c);
+#pragma unroll
+                for (int nb = 0; nb < 4; ++nb)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) o_acc[nb][e] = is_q ? 0.f : o_acc[nb][e] * f;
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const float fp = mj[h] == m_c ? 1.f : fast_exp2(mj[h] - m_c);
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) pa[h][e] = (__bf16)((float)pa[h][e] * fp);
+                }
+                if (is_q) {
+                    to_q = m < n_mine ? granules(q0 + (unsigned)m * gridDim.x) + 1 : INT32_MAX;
+                    ++m;
+                }
+            }
+        }
+        --to_q;
+        src = src1;
+        __syncthreads();
+    };
+#pragma unroll 1
+    do {
+        unroll<DI>([&](auto s_c) __attribute__((always_inline)) { period(s_c); });
+    } while (m <= n_mine);
+}
+
 // Combine the per-split partials of one (query, head): O = sum_s w_s O_s / sum_s w_s with O_s the split's own
 // normalised output and w_s = l_s 2^(m_s-m) its share of the row sum.
 // D_V / 8 lanes (16 bytes each) per split, SLOTS splits side by side, and each slot requests all of its splits (8 per batch)
@@ -1510,41 +1803,47 @@ hipError_t launch_t(const AttnArgs &a, hipStream_t st)
     return hipGetLastError();
 }
 
-template <int D_QK, int D_V, bool PG, bool SPLIT, bool MULTI, bool REST = false>
-hipError_t launch_slab_t(const AttnArgs &a, size_t lds, hipStream_t st, const RestArgs &ra = RestArgs{})
+template <bool PG>
+hipError_t launch_slab(const AttnArgs &a, hipStream_t st)
 {
-    static hipError_t attr = hipFuncSetAttribute((const void *)attn_slab_kernel<D_QK, D_V, PG, SPLIT, MULTI, REST>,
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    constexpr int lds = 2 * kSlabTile * (576 * 2 + kSlabPad) + 2 * 32 * (kSlabTile * 2 + 16) + (4 * 32 + 4 * 32) * (int)sizeof(float);
+    static hipError_t attr = hipFuncSetAttribute((const void *)attn_slab_kernel<576, 512, PG>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (attr != hipSuccess) return attr;
-    int64_t wgs = (int64_t)a.n_layers * a.B * a.Tq;
-    if (!SPLIT && a.k_sel > 2 * kSlabTile) {
-        // whole selections of three or more tiles: one workgroup per CU walks a chain of queries
-        static int n_cu = 0;
-        if (n_cu == 0) {
-            int dev = 0, v = 0;
-            if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v <= 0)
-                return hipErrorInvalidDevice;
-            n_cu = v;
-        }
-        if (wgs > n_cu) wgs = n_cu;
-    }
-    if (REST) wgs = ra.wgs;
-    dim3 grid((unsigned)wgs, (unsigned)(REST ? a.B : SPLIT ? a.n_splits : 1));
-    hipLaunchKernelGGL((attn_slab_kernel<D_QK, D_V, PG, SPLIT, MULTI, REST>), grid, dim3(256), lds, st, a, ra);
+    const dim3 grid((unsigned)((int64_t)a.n_layers * a.B * a.Tq), (unsigned)a.n_splits);
+    hipLaunchKernelGGL((attn_slab_kernel<576, 512, PG>), grid, dim3(256), lds, st, a);
     return hipGetLastError();
 }
 
-template <int D_QK>
-constexpr size_t slab_lds = (size_t)2 * kSlabTile * (D_QK * 2 + kSlabPad) + 2 * 32 * (kSlabTile * 2 + 16) + (4 * 32 + 4 * 32) * sizeof(float);
+constexpr int kStreamLds = kStreamRing * kGranule * (576 * 2 + kSlabPad) + 2 * 32 * (kGranule * 2 + 16) + (4 * 32 * 4 + 2 * 32 * 2) * 4 + kStreamRing * kGranule * 8;
 
-template <int D_QK, int D_V>
-hipError_t launch_slab(const AttnArgs &a, hipStream_t st)
+template <bool PG, bool MULTI, bool REST = false>
+hipError_t launch_stream(const AttnArgs &a, hipStream_t st, const RestArgs &ra = RestArgs{})
 {
-    constexpr size_t lds = slab_lds<D_QK>;
+    static hipError_t attr = hipFuncSetAttribute((const void *)attn_stream_kernel<PG, MULTI, REST>,
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, kStreamLds);
+    if (attr != hipSuccess) return attr;
+    int64_t wgs = (int64_t)a.n_layers * a.B * a.Tq;
+    // one workgroup per CU walks a chain of queries
+    static int n_cu = 0;
+    if (n_cu == 0) {
+        int dev = 0, v = 0;
+        if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v <= 0)
+            return hipErrorInvalidDevice;
+        n_cu = v;
+    }
+    if (wgs > n_cu) wgs = n_cu;
+    if (REST) wgs = ra.wgs;
+    const dim3 grid((unsigned)wgs, (unsigned)(REST ? a.B : 1));
+    hipLaunchKernelGGL((attn_stream_kernel<PG, MULTI, REST>), grid, dim3(512), kStreamLds, st, a, ra);
+    return hipGetLastError();
+}
+
+hipError_t launch_mla(const AttnArgs &a, hipStream_t st)
+{
     const bool pg = a.pv.seq_lens || a.pv.page_table;
-    if (a.n_splits > 1) return pg ? launch_slab_t<D_QK, D_V, true, true, true>(a, lds, st) : launch_slab_t<D_QK, D_V, false, true, true>(a, lds, st);
-    if (a.n_layers > 1 || a.row_gap) return pg ? launch_slab_t<D_QK, D_V, true, false, true>(a, lds, st) : launch_slab_t<D_QK, D_V, false, false, true>(a, lds, st);
-    return pg ? launch_slab_t<D_QK, D_V, true, false, false>(a, lds, st) : launch_slab_t<D_QK, D_V, false, false, false>(a, lds, st);
+    if (a.n_splits > 1) return pg ? launch_slab<true>(a, st) : launch_slab<false>(a, st);
+    if (a.n_layers > 1 || a.row_gap) return pg ? launch_stream<true, true>(a, st) : launch_stream<false, true>(a, st);
+    return pg ? launch_stream<true, false>(a, st) : launch_stream<false, false>(a, st);
 }
 
 // Counts of LeadArgs: a workgroup per chunk, a wave per row, whose entries are all requested before the first is looked at
@@ -1608,7 +1907,7 @@ hipError_t launch_lead(const LeadArgs &a, int n_tensors, hipStream_t st)
 // The rows that RestArgs leaves, unsplit.
 hipError_t launch_attn_rest(const AttnArgs &a, const RestArgs &ra, hipStream_t st)
 {
-    return launch_slab_t<576, 512, false, false, false, true>(a, slab_lds<576>, st, ra);
+    return launch_stream<false, false, true>(a, st, ra);
 }
 
 // Rows 0 .. n_queries - 1 of every sequence, row t seeing exactly the keys 0 .. pos0 + t (576 / 512 rows, values in front).
@@ -1640,7 +1939,7 @@ hipError_t launch_attn(const AttnArgs &a, int d_qk, int d_v, hipStream_t st)
         // the row-slab form: one workgroup per query, or per split of a query's selection when
         // there are too few queries to fill the chip (decode); rows with the values elsewhere than
         // in their first features take the small-tile form
-        if (a.v_off == 0) return launch_slab<576, 512>(a, st);
+        if (a.v_off == 0) return launch_mla(a, st);
         return launch_t<576, 512, 576>(a, st);
     }
     if (d_qk == 64 && d_v == 64) return launch_t<64, 64, 128>(a, st);

@@ -1,0 +1,135 @@
+"""Unsplit sparse attention of 576 / 512 rows against a 64-bit reference at the sizes where its stream of 32-row granules can go
+wrong: selections of one entry to a few granules and their remainders, query counts around the number of workgroups (chains of
+one, two and unequal lengths), few heads, empty slots and rows, ragged and paged caches, outputs at any address, several layers."""
+import pytest
+import torch
+
+import paper_2603_12201_amd as ic
+
+pytestmark = pytest.mark.gpu
+D_QK, D_V, SCALE = 576, 512, 1.0 / 24.0
+
+
+def _case(B, T, L, H, k, seed, holes):
+    g = torch.Generator().manual_seed(seed)
+    Q = torch.randn((B, T, H, D_QK), generator=g).to(torch.bfloat16)
+    KV = torch.randn((B, L, D_QK), generator=g).to(torch.bfloat16)
+    idx = torch.rand((B, T, L), generator=g).topk(k, dim=-1).indices.sort(dim=-1).values.to(torch.int32)
+    if holes:                                # empty slots anywhere, and some rows without any entry
+        idx[torch.rand((B, T, k), generator=g) < 0.3] = -1
+        idx[:, ::7] = -1
+    return Q, KV, idx
+
+
+def _reference(Q, KV, idx):
+    rows, valid = idx.clamp_min(0).long(), idx >= 0
+    O, lse = [], []
+    for b in range(Q.shape[0]):
+        kv = KV[b].double()[rows[b]]                                             # [T, k, 576]
+        s = torch.matmul(Q[b].double(), kv.transpose(1, 2).contiguous()) * SCALE   # [T, H, k]
+        s = s.masked_fill(~valid[b][:, None, :], -float("inf"))
+        l = torch.logsumexp(s, dim=-1)
+        p = torch.exp(s - l.clamp_min(-1e300)[..., None]).nan_to_num(0.0)
+        O.append(torch.matmul(p, kv[..., :D_V].contiguous()))
+        lse.append(l)
+    return torch.stack(O), torch.stack(lse)
+
+
+def _check(O, lse, ref_O, ref_lse):
+    # the probabilities and the output are rounded to bf16 once each: 2^-9 of a value at the worst, 2^-9 / sqrt(3) on average for
+    # either, 0.0016 together; 0.004 leaves room for the few entries of the short selections
+    assert ((O.double().cpu() - ref_O).norm() / ref_O.norm()).item() < 4e-3
+    if lse is not None:
+        full = torch.isfinite(ref_lse)
+        assert torch.equal(torch.isfinite(lse.cpu()), full)
+        # 576 products of unit values scaled by 1 / 24, summed in fp32: 2^-24 * sqrt(576) of a score's size of 1 each, ten times that
+        assert (lse.double().cpu()[full] - ref_lse[full]).abs().max().item() < 2e-5
+
+
+@pytest.mark.parametrize("k", [1, 31, 32, 33, 63, 64, 65, 96, 129])
+@pytest.mark.parametrize("T,H,holes", [(257, 32, False), (300, 5, True), (515, 32, True), (1024, 17, False)])
+def test_sizes(k, T, H, holes):
+    Q, KV, idx = _case(1, T, 200, H, k, seed=k + T, holes=holes)
+    O, lse = ic.sparse_attn(Q.cuda(), KV.cuda(), idx.cuda(), D_V, 0, SCALE, want_lse=True)
+    _check(O, lse, *_reference(Q, KV, idx))
+
+
+@pytest.mark.parametrize("shift", [1, 4])
+def test_output_address(shift):
+    B, T, H, k = 2, 260, 3, 70
+    Q, KV, idx = _case(B, T, 150, H, k, seed=5, holes=True)
+    buf = torch.full((B * T * H * D_V + 16,), 7.0, dtype=torch.bfloat16, device="cuda")
+    O = buf[shift:shift + B * T * H * D_V].view(B, T, H, D_V)
+    ic.sparse_attn(Q.cuda(), KV.cuda(), idx.cuda(), D_V, 0, SCALE, out=O)
+    _check(O, None, *_reference(Q, KV, idx))
+    assert bool((buf[:shift] == 7).all()) and bool((buf[shift + B * T * H * D_V:] == 7).all())
+
+
+@pytest.mark.parametrize("k", [40, 300])
+def test_large_scores_and_moving_reference(k):
+    # scores that grow along the selection: the reference moves in most granules, the last of which decide the row
+    Q, KV, idx = _case(1, 270, 400, 32, k, seed=11, holes=False)
+    KV *= torch.linspace(0.05, 4.0, 400)[None, :, None].to(torch.bfloat16)
+    Q *= 6
+    O, _ = ic.sparse_attn(Q.cuda(), KV.cuda(), idx.cuda(), D_V, 0, SCALE, want_lse=True)
+    ref, _ = _reference(Q, KV, idx)
+    # two roundings of relative size 2^-9 each, and one of them again where a reference moves: of the largest term, at most
+    assert ((O.double().cpu() - ref).norm() / ref.norm()).item() < 8e-3
+
+
+@pytest.mark.parametrize("page", [0, 64])
+def test_ragged_paged(page):
+    B, T, H, k, L = 70, 4, 8, 100, 256
+    Q, KV, idx = _case(B, T, L, H, k, seed=3, holes=False)
+    g = torch.Generator().manual_seed(1)
+    lens = torch.randint(0, L + 1, (B,), generator=g)
+    lens[0], lens[1] = 0, L
+    seen = idx.clone()
+    seen[idx >= lens[:, None, None]] = -1
+    if page:
+        per = L // page
+        order = torch.randperm(B * per, generator=g)
+        pool = torch.full((B * per * page, D_QK), 3e4, dtype=torch.bfloat16)
+        table = order.view(B, per).to(torch.int32)
+        for b in range(B):
+            for j in range(-(-int(lens[b]) // page)):
+                n = min(page, int(lens[b]) - j * page)
+                pool[int(table[b, j]) * page:int(table[b, j]) * page + n] = KV[b, j * page:j * page + n]
+        pool[:1] = KV[1, :1]                 # (an empty slot reads row 0, whose values have to be finite)
+        if int(order[0]) >= 0:
+            owner = int((order == 0).nonzero()[0])
+            if int(lens[owner // per]) > (owner % per) * page:
+                pool[:1] = KV[owner // per, (owner % per) * page:(owner % per) * page + 1]
+        pc = ic.paged_cache(lens.to(torch.int32).cuda(), table.cuda(), page)
+        O = ic.sparse_attn_paged(Q.cuda(), pool.cuda(), idx.cuda(), L, D_V, 0, SCALE, pc)
+    else:
+        pc = ic.paged_cache(lens.to(torch.int32).cuda(), None, 0)
+        O = ic.sparse_attn_paged(Q.cuda(), KV.cuda(), idx.cuda(), L, D_V, 0, SCALE, pc)
+    O = O[0] if isinstance(O, tuple) else O
+    ref, _ = _reference(Q, KV, seen)
+    _check(O, None, ref, None)
+
+
+def test_layers_and_short_causal_rows():
+    # three layers behind one index tensor; the first rows of a sequence hold fewer entries than k
+    B, T, H, k, n = 2, 150, 32, 96, 3
+    g = torch.Generator().manual_seed(9)
+    layers = []
+    for i in range(n):
+        t = {"Q": torch.randn((B, T, H, D_QK), generator=g).to(torch.bfloat16).cuda(),
+             "KV": torch.randn((B, T, D_QK), generator=g).to(torch.bfloat16).cuda()}
+        if i == 0:
+            t["q"] = (torch.randn((B, T, 32, 128), generator=g) / 11).to(torch.bfloat16).cuda()
+            t["k"] = torch.randn((B, T, 128), generator=g).to(torch.bfloat16).cuda()
+            t["w"] = torch.rand((B, T, 32), generator=g).cuda()
+        layers.append(t)
+    flat = torch.zeros((n, B * T * H * D_V + 8), dtype=torch.bfloat16, device="cuda")
+    # (outputs two bytes off 16 keep the dense form out of it)
+    outs = [flat[i, 1:1 + B * T * H * D_V].view(B, T, H, D_V) for i in range(n)]
+    arr = ic.make_layers(layers, k, 0, D_V, 0, SCALE, outs)
+    idx = torch.empty((B, T, k), dtype=torch.int32, device="cuda")
+    ws = torch.empty(max(ic.forward_stack_workspace(arr), 256), dtype=torch.uint8, device="cuda")
+    ic.forward_stack(arr, [True, False, False], idx, ws)
+    for t, out in zip(layers, outs):
+        ref, _ = _reference(t["Q"].cpu(), t["KV"].cpu(), idx.cpu())
+        _check(out, None, ref, None)
