@@ -212,6 +212,7 @@ hipError_t launch_cosine_sum(const void *A, const void *B, int64_t n_rows, int64
 hipError_t launch_sim_init(double *S, int n, hipStream_t st);
 hipError_t launch_sim_finish(double *S, int n, int64_t n_rows, hipStream_t st);
 hipError_t launch_loss_finish(const double *sims, int n, double *loss, hipStream_t st);
+hipError_t launch_probs_stream(const ProbsArgs &a, hipStream_t st);
 hipError_t launch_attn_probs(const ProbsArgs &a, int d_qk, hipStream_t st);
 hipError_t launch_distill(const DistillArgs &a, int64_t nq, double *loss_multi, double *loss_avg, hipStream_t st);
 hipError_t launch_calib(int kind, const void *src, void *dst, const int32_t *idx, int64_t n, int64_t table_rows, int row_bytes,

@@ -8,7 +8,8 @@
 //                       v_mfma_f32_16x16x32_bf16 with Q in registers and the gathered rows turned
 //                       into the A-operand layout through a per-wave LDS tile; the per-head
 //                       normalisers are the log-sum-exps the attention kernel already produced;
-//                       the head sum is a 16-lane row reduction.
+//                       the head sum is a 16-lane row reduction.  (64-feature rows; rows of 576
+//                       features are served by the attention kernel's stream form.)
 //   distill_row_kernel  (and its register-resident form for k <= 2048, which reads every input once)
 //                       per query: q = Softmax(I) over the selected scores (in the log domain),
 //                       sum_j 1/(m+1) KL(p_j || q), KL(p_bar || q), and q * |p_bar| - p_bar, the
@@ -104,7 +105,7 @@ __global__ __launch_bounds__(256, 2) void attn_probs_kernel(ProbsArgs a)
     };
 
     // Groups behind the last selected row hold nothing: one pass over the index row (512 entries at a time in flight) finds
-    // them, and their zeros are written here.  Causal selections of 2048: 4096 rows 560 -> 457 us, 600 rows 117 -> 39 us.
+    // them, and their zeros are written here.
     int filled = 0;
     for (int s0 = 0; s0 < a.k_sel; s0 += 64 * 8) {
         int32_t v[8];
@@ -346,13 +347,8 @@ hipError_t launch_attn_probs(const ProbsArgs &a, int d_qk, hipStream_t st)
 {
     const int64_t nq = (int64_t)a.B * a.Tq;
     if (nq <= 0) return hipSuccess;
-    if (d_qk == 576) {
-        constexpr int lds = 4 * kProbRows * (576 * 2 + kProbPad);      // above the default limit of dynamic LDS: opt in once
-        static hipError_t attr = hipFuncSetAttribute((const void *)attn_probs_kernel<576>,
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-        if (attr != hipSuccess) return attr;
-        hipLaunchKernelGGL(attn_probs_kernel<576>, dim3((unsigned)nq), dim3(256), lds, st, a);
-    } else if (d_qk == 64) {
+    if (d_qk == 576) return launch_probs_stream(a, st);
+    if (d_qk == 64) {
         hipLaunchKernelGGL(attn_probs_kernel<64>, dim3((unsigned)nq), dim3(256), 4 * kProbRows * (64 * 2 + kProbPad), st, a);
     } else {
         return hipErrorInvalidValue;

@@ -24,6 +24,8 @@
 // reference maximum and row sum; attn_merge_kernel weighs the splits by their share of the total
 // row sum.
 #include "ic_common.hpp"
+#include <algorithm>
+#include <cstring>
 #include <type_traits>
 
 namespace ic {
@@ -1192,6 +1194,7 @@ __global__ __launch_bounds__(512, 2) void attn_dense_kernel(AttnArgs a, DenseArg
 constexpr int kGranule = 32;                 // selected rows that reach LDS together
 constexpr int kStreamRing = 4;               // of them resident
 constexpr int kStreamDepth = 2;              // of them in registers on their way there
+constexpr int kProbsQueries = 1024;          // PROBS: queries of a workgroup, at most
 constexpr int kStreamIds = 4;                // periods between the request of a granule's ids and that of its rows
 
 // PG: the KV cache may be ragged and / or paged.
@@ -1199,7 +1202,11 @@ constexpr int kStreamIds = 4;                // periods between the request of a
 // is then not its number.
 // REST: the rows of sequence blockIdx.y behind those that the dense form has taken.  How many that are is device data, so the
 // workgroups, as many as for all rows, find out first and share what is left (one round trip to memory, about 1 us).
-template <bool PG, bool MULTI, bool REST>
+// PROBS: the scores waves write each row's probability, summed over the heads, with the log-sum-exps that an attention launch
+// has left (a.lse) instead of P, to a.O as fp32 [B,Tq,k_sel]; the output waves only bring the granules.  A workgroup per query
+// whose four waves gathered and scored 16 rows each on their own loaded Q four times over (36 KB in pieces of 64 bytes) and took 442 us
+// for 4096 causal rows, 350 here; 4096 x 2048 of 32768 rows 893 and 589, one query 51 and 32.
+template <bool PG, bool MULTI, bool REST, bool PROBS>
 __global__ __launch_bounds__(512, 2) void attn_stream_kernel(AttnArgs a, RestArgs ra)
 {
     constexpr int D_QK = 576, D_V = 512;
@@ -1238,16 +1245,42 @@ __global__ __launch_bounds__(512, 2) void attn_stream_kernel(AttnArgs a, RestArg
     const unsigned nq_layer = (unsigned)(a.B * a.Tq), nq = MULTI ? nq_layer * a.n_layers : nq_layer;
     unsigned q0 = blockIdx.x;
     if ((gridDim.x & 7u) == 0) q0 = (blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3);
-    if (q0 >= nq) return;
-    const int n_mine = (int)((nq - q0 + gridDim.x - 1) / gridDim.x);
-    auto granules = [&](unsigned gq) -> int {             // of a query, at least one
+    // (PROBS: every other round the other way round: causal rows hold more and more entries, 8 % more in the last workgroup's of a round)
+    auto query = [&](int n) -> unsigned { return (unsigned)n * gridDim.x + (PROBS && (n & 1) ? gridDim.x - 1 - q0 : q0); };
+    const int n_mine = (int)(nq / gridDim.x) + (query((int)(nq / gridDim.x)) < nq);
+    if (n_mine == 0) return;
+    int *const counts = (int *)pbuf;                      // PROBS: [n_mine] granules of the queries
+    auto granules = [&](int i) -> int {                   // of the workgroup's query i, at least one
+        if constexpr (PROBS) return __builtin_amdgcn_readfirstlane(counts[i]);
         int n = a.k_sel;
         if (a.causal_pos0 >= 0) {
+            const unsigned gq = query(i);
             const int64_t held = a.causal_pos0 + (MULTI ? gq % nq_layer : gq) % (unsigned)a.Tq + 1;
             if (held < n) n = (int)held;
         }
         return max(1, (n + kGranule - 1) / kGranule);
     };
+    if constexpr (PROBS) {
+        // Granules behind the last selected row hold nothing: their zeros are written here (512 entries at a time in flight)
+        for (int i = wave; i < n_mine; i += 8) {
+            const int32_t *idx_row = a.idx + (int64_t)query(i) * a.k_sel;
+            float *out = (float *)a.O + (int64_t)query(i) * a.k_sel;
+            int n = 1;
+            for (int s0 = 0; s0 < a.k_sel; s0 += 64 * 8) {
+                int32_t v[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) v[u] = idx_row[min(s0 + 64 * u + lane, a.k_sel - 1)];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const unsigned long long some = __ballot(v[u] >= 0 && s0 + 64 * u + lane < a.k_sel);
+                    if (some != 0ull) n = (s0 + 64 * u) / kGranule + (some >> kGranule ? 2 : 1);
+                }
+            }
+            if (lane == 0) counts[i] = n;
+            for (int k = kGranule * n + lane; k < a.k_sel; k += 64) out[k] = 0.f;
+        }
+        __syncthreads();
+    }
 
     if (wave < 4) {
         const int pair = w >> 1, kh = w & 1;
@@ -1259,7 +1292,7 @@ __global__ __launch_bounds__(512, 2) void attn_stream_kernel(AttnArgs a, RestArg
 #pragma unroll
                 for (int r = 0; r < 2; ++r) qv[ks][r] = *(const bf16x8 *)(qr + 16 * r * ROWB + 64 * ks);
         };
-        const int ka_off = (16 * kh + dense_row(l16)) * ROWB + 16 * g;
+        const int ka_off = (16 * kh + (PROBS ? l16 : dense_row(l16))) * ROWB + 16 * g;
         const int pw_off = l16 * PSTR + 32 * kh + 8 * g;
         float m_c[2] = {-INFINITY, -INFINITY}, l_own[2] = {0.f, 0.f};
         auto publish = [&](int n) __attribute__((always_inline)) {       // row sums of query n, and a new start
@@ -1275,6 +1308,7 @@ __global__ __launch_bounds__(512, 2) void attn_stream_kernel(AttnArgs a, RestArg
                 l_own[r] = 0.f;
             }
         };
+        const float inv_h = 1.f / (float)a.H_q;
         bf16x8 ka[RING];
         f32x4 s4[2], odd[2];                              // two accumulation chains: half of the roundings in one
         auto steps = [&](const unsigned char *tb, auto k0_c, auto k1_c) __attribute__((always_inline)) {
@@ -1297,11 +1331,26 @@ __global__ __launch_bounds__(512, 2) void attn_stream_kernel(AttnArgs a, RestArg
         __syncthreads();                                  // period -1
         if (pair) __syncthreads();                        // period 0
         int at_q = 0;                                     // the query's Q in the stream, its granules behind it
+        // PROBS: log-sum-exps of heads l16 and 16 + l16 (a head that is not there counts nothing), the next query's on their way
+        float lse2[2] = {INFINITY, INFINITY};
+        auto load_lse = [&](int n, float (&l)[2]) __attribute__((always_inline)) {
+#pragma unroll
+            for (int r = 0; r < 2; ++r)
+                l[r] = 16 * r + l16 < a.H_q ? a.lse[(int64_t)query(n) * a.H_q + 16 * r + l16] * 1.4426950408889634f : INFINITY;
+        };
+        float lse_n[2];
+        if constexpr (PROBS) load_lse(0, lse_n);
 #pragma unroll 1
         for (int n = 0; n < n_mine; ++n) {
-            const int last = at_q + granules(q0 + (unsigned)n * gridDim.x);
+            const int last = at_q + granules(n);
             const bool own = ((at_q ^ pair) & 1) == 0;    // Q takes the place of a granule of this pair
-            if (n > 0) publish(n - 1);
+            if constexpr (PROBS) {
+                lse2[0] = lse_n[0];
+                lse2[1] = lse_n[1];
+                if (n + 1 < n_mine) load_lse(n + 1, lse_n);
+            } else {
+                if (n > 0) publish(n - 1);
+            }
             load_q(at_q);
             if (own) {
                 __syncthreads();
@@ -1319,7 +1368,7 @@ __global__ __launch_bounds__(512, 2) void attn_stream_kernel(AttnArgs a, RestArg
                 const int vm = *(const int *)(filled + (at & (kStreamRing - 1)) * 256 + (16 * kh + l16) * 8);
                 f32x2 mk[2];
 #pragma unroll
-                for (int r = 0; r < 2; ++r) mk[r] = *(const f32x2 *)(mbuf + ((at - 1) & 1) * 64 + 2 * (16 * r + l16));
+                for (int r = 0; r < 2 && !PROBS; ++r) mk[r] = *(const f32x2 *)(mbuf + ((at - 1) & 1) * 64 + 2 * (16 * r + l16));
                 __builtin_amdgcn_sched_barrier(0);
                 steps(tb, c1, c2);
 #pragma unroll
@@ -1327,6 +1376,29 @@ __global__ __launch_bounds__(512, 2) void attn_stream_kernel(AttnArgs a, RestArg
 #pragma unroll
                     for (int i = 0; i < 4; ++i) s4[r][i] += odd[r][i];
                 const unsigned rows = (unsigned)__ballot(vm != 0) & 0xFFFFu;
+                if constexpr (PROBS) {
+                    // lane: rows 4 g + i of the half, heads l16 and 16 + l16
+                    float p[4];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        float sum = 0.f;
+#pragma unroll
+                        for (int r = 0; r < 2; ++r) {
+                            const float e = fast_exp2(__builtin_fmaf(s4[r][i], a.scale_log2e, -lse2[r]));
+                            sum += (rows >> (4 * g + i) & 1u) && lse2[r] != INFINITY ? e : 0.f;
+                        }
+                        p[i] = row16_sum(sum);            // lane 15 of the 16: the sum over the heads
+                    }
+                    if (l16 == 15) {
+                        const int k = kGranule * (at - at_q - 1) + 16 * kh + 4 * g;
+                        float *out = (float *)a.O + (int64_t)query(n) * a.k_sel + k;
+#pragma unroll
+                        for (int i = 0; i < 4; ++i)
+                            if (k + i < a.k_sel) out[i] = p[i] * inv_h;
+                    }
+                    __syncthreads();
+                    continue;
+                }
                 if (rows != 0xFFFFu) {
                     const unsigned mine = rows >> (8 * (g >> 1) + (g & 1));    // the lane's keys are two apart
 #pragma unroll
@@ -1372,7 +1444,7 @@ __global__ __launch_bounds__(512, 2) void attn_stream_kernel(AttnArgs a, RestArg
             }
             at_q = last + 1;
         }
-        publish(n_mine - 1);
+        if constexpr (!PROBS) publish(n_mine - 1);
         // as many barriers as the output waves have: those of the periods -1 .. at_q + 3, in whole rounds of DI
         const int done = at_q + (((at_q ^ pair) & 1) == 0 ? 1 : 2);
         for (int i = done; i < (at_q + 4 + DI) / DI * DI; ++i) __syncthreads();
@@ -1389,17 +1461,18 @@ __global__ __launch_bounds__(512, 2) void attn_stream_kernel(AttnArgs a, RestArg
         b = (int)(qq / (unsigned)a.Tq);
         return MULTI ? (int64_t)qq + (int64_t)b * a.row_gap : (int64_t)qq;
     };
-    auto open = [&](unsigned gq) {
+    auto open = [&](int i) {
+        const unsigned gq = query(i);
         int layer;
         const int64_t row = tensor_row(gq, layer, pl.b);
         pl.idx = a.idx + row * a.k_sel;
         pl.q = (const unsigned short *)(MULTI ? a.Qs[layer] : a.Q) + row * a.H_q * D_QK;
         pl.kv = (const unsigned short *)(MULTI ? a.KVs[layer] : a.KV) + (PG && a.pv.page_table ? 0 : (int64_t)pl.b * a.Lk * a.row_elems);
         pl.len = PG && a.pv.seq_lens ? min(load_uniform(a.pv.seq_lens + pl.b), a.Lk) : a.Lk;
-        pl.ng = granules(gq);
+        pl.ng = granules(i);
     };
     pl.n = 0;
-    open(q0);
+    open(0);
     pl.is_q = true;
     pl.src = pl.q;
     // per register set: ids of a granule and what they belong to
@@ -1436,7 +1509,7 @@ __global__ __launch_bounds__(512, 2) void attn_stream_kernel(AttnArgs a, RestArg
                 n_run = a.k_sel;
             } else {                                      // the next query's Q; at the end of the stream the last one's, for nobody
                 if (pl.n < n_mine) ++pl.n;
-                if (pl.n < n_mine) open(q0 + (unsigned)pl.n * gridDim.x);
+                if (pl.n < n_mine) open(pl.n);
                 pl.is_q = true;
                 pl.src = pl.q;
                 left = 0;
@@ -1537,7 +1610,7 @@ __global__ __launch_bounds__(512, 2) void attn_stream_kernel(AttnArgs a, RestArg
         for (int i = 0; i < 4; ++i) l += lr[i] == -INFINITY ? 0.f : ls[i] * fast_exp2(lr[i] - m_c);
         const float inv = l > 0.f ? __builtin_amdgcn_rcpf(l) : 0.f;
         int layer, b;
-        const unsigned gq = q0 + (unsigned)(m - 1) * gridDim.x;
+        const unsigned gq = query(m - 1);
         const int64_t row = tensor_row(gq, layer, b);
         if (w == 0 && half == 0 && row_l < a.H_q && a.lse) {
             // (in 64 bits: the reference of 16 keys leaves a larger logarithm, and so a coarser sum, than that of more)
@@ -1587,21 +1660,23 @@ __global__ __launch_bounds__(512, 2) void attn_stream_kernel(AttnArgs a, RestArg
         constexpr int s = g1 % D, s_next = (s + 1) % D, g2 = (g1 + 1) % DI;      // g2: granule p - 2
         constexpr std::integral_constant<int, (g1 + 1 + D) % DI> s1{};
         if (__builtin_expect(to_q == 0, 0)) {
-            if (m > 0) finish(g1);
+            if (!PROBS && m > 0) finish(g1);
         }
         f32x2 mj;
         uint64_t src1 = 0;
         bool moved = false;
         unroll<8>([&](auto i_c) __attribute__((always_inline)) {
             constexpr int i = decltype(i_c)::value, h = i >> 2, nb = i & 3;
-            const s16x8 v = {vq[h][nb][0][0], vq[h][nb][0][1], vq[h][nb][0][2], vq[h][nb][0][3], vq[h][nb][1][0], vq[h][nb][1][1], vq[h][nb][1][2], vq[h][nb][1][3]};
-            o_acc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, v), pa[h], o_acc[nb], 0, 0, 0);
-            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (!PROBS) {
+                const s16x8 v = {vq[h][nb][0][0], vq[h][nb][0][1], vq[h][nb][0][2], vq[h][nb][0][3], vq[h][nb][1][0], vq[h][nb][1][1], vq[h][nb][1][2], vq[h][nb][1][3]};
+                o_acc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, v), pa[h], o_acc[nb], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int u = 0; u < 2; ++u)
-                vq[h][nb][u] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(tbuf + vb[g2 / 2] + (g2 % 2) * GB + 16 * h * ROWB + 64 * nb + u * ROWB));
-            if constexpr (nb == 3) pa[h] = *(const bf16x8 *)(pbuf + pr_off + (g2 % 2) * PB + 32 * h);
-            if constexpr (i == 0) mj = *(const f32x2 *)(mbuf + (g2 % 2) * 64 + 2 * l32);
+                for (int u = 0; u < 2; ++u)
+                    vq[h][nb][u] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(tbuf + vb[g2 / 2] + (g2 % 2) * GB + 16 * h * ROWB + 64 * nb + u * ROWB));
+                if constexpr (nb == 3) pa[h] = *(const bf16x8 *)(pbuf + pr_off + (g2 % 2) * PB + 32 * h);
+                if constexpr (i == 0) mj = *(const f32x2 *)(mbuf + (g2 % 2) * 64 + 2 * l32);
+            }
 #pragma unroll
             for (int c = i; c < (i == 7 ? 9 : i + 1); ++c) *(u32x4 *)(tbuf + st[g1 / 2] + (g1 % 2) * GB + 128 * c) = cur[s][c];
             __builtin_amdgcn_sched_barrier(0);            // (loads ahead of the stores would need registers of their own)
@@ -1615,10 +1690,14 @@ __global__ __launch_bounds__(512, 2) void attn_stream_kernel(AttnArgs a, RestArg
             }
             if constexpr (i == 4) request(s1);
             if constexpr (i == 5) advance();
-            if constexpr (i == 6) moved = __ballot(mj[0] != m_c || mj[1] != m_c) != 0ull;
+            if constexpr (i == 6 && !PROBS) moved = __ballot(mj[0] != m_c || mj[1] != m_c) != 0ull;
             __builtin_amdgcn_sched_barrier(0);
         });
-        if (__builtin_expect(moved | (to_q <= 1), 0)) {
+        if (PROBS && to_q == 0) {
+            to_q = m < n_mine ? granules(m) + 1 : INT32_MAX;
+            ++m;
+        }
+        if (!PROBS && __builtin_expect(moved | (to_q <= 1), 0)) {
             if (to_q != 1) {                              // (granule p - 2 is Q: it has no P)
                 // another query, or P of granule p - 2 has another reference than the accumulators
                 const bool is_q = to_q == 0;
@@ -1636,7 +1715,7 @@ __global__ __launch_bounds__(512, 2) void attn_stream_kernel(AttnArgs a, RestArg
                     for (int e = 0; e < 8; ++e) pa[h][e] = (__bf16)((float)pa[h][e] * fp);
                 }
                 if (is_q) {
-                    to_q = m < n_mine ? granules(q0 + (unsigned)m * gridDim.x) + 1 : INT32_MAX;
+                    to_q = m < n_mine ? granules(m) + 1 : INT32_MAX;
                     ++m;
                 }
             }
@@ -1816,10 +1895,10 @@ hipError_t launch_slab(const AttnArgs &a, hipStream_t st)
 
 constexpr int kStreamLds = kStreamRing * kGranule * (576 * 2 + kSlabPad) + 2 * 32 * (kGranule * 2 + 16) + (4 * 32 * 4 + 2 * 32 * 2) * 4 + kStreamRing * kGranule * 8;
 
-template <bool PG, bool MULTI, bool REST = false>
+template <bool PG, bool MULTI, bool REST = false, bool PROBS = false>
 hipError_t launch_stream(const AttnArgs &a, hipStream_t st, const RestArgs &ra = RestArgs{})
 {
-    static hipError_t attr = hipFuncSetAttribute((const void *)attn_stream_kernel<PG, MULTI, REST>,
+    static hipError_t attr = hipFuncSetAttribute((const void *)attn_stream_kernel<PG, MULTI, REST, PROBS>,
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, kStreamLds);
     if (attr != hipSuccess) return attr;
     int64_t wgs = (int64_t)a.n_layers * a.B * a.Tq;
@@ -1833,8 +1912,10 @@ hipError_t launch_stream(const AttnArgs &a, hipStream_t st, const RestArgs &ra =
     }
     if (wgs > n_cu) wgs = n_cu;
     if (REST) wgs = ra.wgs;
+    // (the counts of a workgroup's queries have to fit where P and the references are otherwise)
+    if (PROBS) wgs = std::max(wgs, ((int64_t)a.B * a.Tq + kProbsQueries - 1) / kProbsQueries);
     const dim3 grid((unsigned)wgs, (unsigned)(REST ? a.B : 1));
-    hipLaunchKernelGGL((attn_stream_kernel<PG, MULTI, REST>), grid, dim3(512), kStreamLds, st, a, ra);
+    hipLaunchKernelGGL((attn_stream_kernel<PG, MULTI, REST, PROBS>), grid, dim3(512), kStreamLds, st, a, ra);
     return hipGetLastError();
 }
 
@@ -1902,6 +1983,28 @@ hipError_t launch_lead(const LeadArgs &a, int n_tensors, hipStream_t st)
 {
     hipLaunchKernelGGL(lead_kernel, dim3((unsigned)a.n_chunks, (unsigned)a.B, (unsigned)n_tensors), dim3(64 * kLeadChunk), 0, st, a);
     return hipGetLastError();
+}
+
+// Head-aggregated probabilities of 576-feature rows: the stream form without its output product.
+hipError_t launch_probs_stream(const ProbsArgs &p, hipStream_t st)
+{
+    AttnArgs a;
+    memset(&a, 0, sizeof a);
+    a.Q = p.Q;
+    a.KV = p.KV;
+    a.idx = p.idx;
+    a.lse = const_cast<float *>(p.lse);
+    a.O = p.probs;
+    a.B = p.B;
+    a.Tq = p.Tq;
+    a.Lk = p.Lk;
+    a.H_q = p.H_q;
+    a.row_elems = p.row_elems;
+    a.k_sel = p.k_sel;
+    a.n_layers = 1;
+    a.scale_log2e = p.scale_log2e;
+    a.causal_pos0 = -1;
+    return launch_stream<false, false, false, true>(a, st);
 }
 
 // The rows that RestArgs leaves, unsplit.

@@ -133,3 +133,21 @@ def test_layers_and_short_causal_rows():
     for t, out in zip(layers, outs):
         ref, _ = _reference(t["Q"].cpu(), t["KV"].cpu(), idx.cpu())
         _check(out, None, ref, None)
+
+
+@pytest.mark.parametrize("k", [1, 31, 32, 33, 64, 100, 1030])
+@pytest.mark.parametrize("B,T,H", [(1, 1, 32), (3, 3, 5), (1, 257, 32), (2, 300, 17)])
+def test_probs(k, B, T, H):
+    # chains of one to three queries, the second in reverse; rows without entries, with entries in front only and anywhere
+    Q, KV, idx = _case(B, T, max(200, k), H, k, seed=k + T, holes=k != 64)
+    idx[:, 1::3, (k + 1) // 2:] = -1
+    ref_O, ref_lse = _reference(Q, KV, idx)
+    lse = ref_lse.float().cuda()
+    got = ic.attn_probs(Q.cuda(), KV.cuda(), idx.cuda(), SCALE, lse).double().cpu()
+    rows, valid = idx.clamp_min(0).long(), idx >= 0
+    for b in range(B):
+        s = torch.matmul(Q[b].double(), KV[b].double()[rows[b]].transpose(1, 2).contiguous()) * SCALE
+        p = torch.exp(s - ref_lse[b].clamp_min(-1e300)[..., None]).masked_fill(~valid[b][:, None, :], 0.0).mean(dim=1)
+        # scores to 2^-24 * sqrt(576) as above and lse rounded to 2^-24 of about 8: 2e-6 of a probability of at most 1, five times that
+        assert (got[b] - p).abs().max().item() < 1e-5
+        assert bool((got[b][~valid[b]] == 0).all())
