@@ -795,8 +795,10 @@ __global__ __launch_bounds__(256, 1) void attn_slab_kernel(AttnArgs a)
 // 2400 clocks, 1800 with the operands read a step ahead.  1088 of them are matrix clocks; staging the tiles costs about 300
 // (it may not move to the scores waves: 1900).  One layer of 32 heads, 2048 rows of a prefix: 180 us before, 145 now.
 // LDS layout as in the row-slab form (rows 1184 bytes apart, transpose reads over rows two apart); the A operand presents
-// the tile rows in the order dense_row(), so that the four scores of a lane are neighbours in P.  Q and O pass through the
-// tile ring.
+// the tile rows in the order dense_row(), so that the four scores of a lane are neighbours in P.
+// A workgroup walks a chain of blocks as one stream of tiles, the next block's Q and first keys behind the last one's, and the outputs
+// leave under the next block's first steps: with a workgroup per block, its start (Q, first tile, two steps until the first
+// product) and end were about 6 us of the 12 to 25 that a block takes.  Four layers of 3 x 1021 rows 569 -> 513 us.
 // Registers.  The two roles need 249 of the 256 that a wave may have: Q of 32 rows takes 144 in the scores waves, the output
 // accumulators 128 in the others.  The compiler places all of it: state that it is not told of (registers named in asm
 // statements) is only safe as long as it happens to put no value of its own there.
@@ -813,6 +815,7 @@ template <int N, typename F> __device__ __forceinline__ void unroll(F f)
 constexpr int kDenseRows = 64;               // (query, head) rows per workgroup
 constexpr int kDenseTile = 32;               // keys per tile
 constexpr int kDenseRing = 4;
+constexpr int kDenseChain = 64;              // blocks of a workgroup, at most (their list is in LDS)
 
 // tile row (within 16) behind result row r of S^T
 __device__ __forceinline__ int dense_row(int r) { return 8 * (r >> 3) + 2 * (r & 3) + ((r >> 2) & 1); }
@@ -824,74 +827,70 @@ __global__ __launch_bounds__(512, 2) void attn_dense_kernel(AttnArgs a, DenseArg
     constexpr int KS = D_QK / 32;                         // contraction steps
     constexpr int ROWB = D_QK * 2 + kSlabPad, TBUFB = kDenseTile * ROWB;
     constexpr int PSTR = kDenseTile * 2 + 16, PBUFB = kDenseRows * PSTR;
-    constexpr int OSTR = D_V * 2 + 16;
+    constexpr int OSTR = 256 + 16;                        // a wave's 128 columns of an output row
     constexpr int RING = 9;                              // A-operand reads in flight
-    static_assert(2 * TBUFB == kDenseRows * ROWB && kDenseRows * OSTR <= 2 * TBUFB, "Q and O take two tile buffers");
+    static_assert(kDenseRows == 2 * kDenseTile && 32 * OSTR <= 8 * ROWB, "Q takes two tiles' places, half of a wave's outputs its eight rows of one");
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     unsigned char *tbuf = smem;                           // [kDenseRing][32][ROWB]
     unsigned char *pbuf = smem + kDenseRing * TBUFB;      // [2][64 rows][PSTR]
     float *mref = (float *)(pbuf + 2 * PBUFB);            // [64] common references
     float *mnew = mref + kDenseRows;                      // [2][64] per key half: reference of the latest tile, then row sums
     float *fac = mnew + 2 * kDenseRows;                   // [3][64] factors of a moved reference: O, P of either key half
-    int *moved = (int *)(fac + 3 * kDenseRows);           // [2] by tile parity; [2]: a key some row does not see has no finite score
+    int *moved = (int *)(fac + 3 * kDenseRows);           // [2] by step; [2] by block: a key some row does not see has no finite score
+    int *list = moved + 4;                                // [kDenseChain] queries of the block's sequence, 0: no such block
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, l32 = lane & 31, hh = lane >> 5, g = lane >> 4;
     const int gr = lane >> 3, gp = lane & 7;
     const int w = wave & 3;
-    const int b = blockIdx.y;
-    int n_queries = da.n_queries;
-    if (da.lead) n_queries = __builtin_amdgcn_readfirstlane(min(n_queries, lead_rows(da.lead + (int64_t)b * da.n_chunks, da.n_chunks)));
-    const int n_rows = n_queries * a.H_q;                 // flattened rows of a sequence
-    const int R0 = ((int)gridDim.x - 1 - (int)blockIdx.x) * kDenseRows;   // longest first
-    if (R0 >= n_rows) return;
-    const int nt = (da.pos0 + min(R0 + kDenseRows - 1, n_rows - 1) / a.H_q) / kDenseTile + 1;
-    const int t_edge = (da.pos0 + R0 / a.H_q + 1) / kDenseTile;      // first tile with keys that some row does not see
-
+    // blocks of the workgroup, all sequences' blocks ranked by length: there and back over the workgroups, which evens them out
+    const int n_blk = (da.n_queries * a.H_q + kDenseRows - 1) / kDenseRows, n_all = n_blk * a.B;
+    auto rank = [&](int n) -> int { return n * (int)gridDim.x + (n & 1 ? (int)gridDim.x - 1 - (int)blockIdx.x : (int)blockIdx.x); };
+    int n_list = n_all / (int)gridDim.x;
+    n_list += rank(n_list) < n_all;
+    for (int n = wave; n < n_list; n += 8) {
+        const int b = rank(n) % a.B, R0 = (n_blk - 1 - rank(n) / a.B) * kDenseRows;
+        int nq = da.n_queries;
+        if (da.lead) nq = __builtin_amdgcn_readfirstlane(min(nq, lead_rows(da.lead + (int64_t)b * da.n_chunks, da.n_chunks)));
+        if (lane == 0) list[n] = R0 < nq * a.H_q ? nq : 0;
+    }
     if (tid < kDenseRows) mref[tid] = mnew[tid] = mnew[kDenseRows + tid] = -INFINITY;
-    if (tid < 3) moved[tid] = 0;
-    // Q in the shape of two tiles, through buffers 2 and 3, by everybody
-    unsigned char *qb = tbuf + 2 * TBUFB;
-    auto load_q = [&](u32x4 (&raw)[9]) __attribute__((always_inline)) {
-        const unsigned short *qp = (const unsigned short *)a.Q + ((int64_t)b * a.Tq * a.H_q + min(R0 + 8 * wave + gr, n_rows - 1)) * D_QK + 8 * gp;
-#pragma unroll
-        for (int c = 0; c < 9; ++c) raw[c] = *(const u32x4 *)(qp + 64 * c);
+    if (tid < 4) moved[tid] = 0;
+    __syncthreads();
+    struct Block { int n, odd, b, R0, n_queries, n_rows, nt, t_edge; };  // n = n_list: none
+    auto open = [&](int n, int odd) {                     // block n of the list, or the first one behind it that exists
+        Block k;
+        k.odd = odd;                                      // (odd and even ones alternate)
+        int nq = 0;
+        while (n < n_list && (nq = __builtin_amdgcn_readfirstlane(list[n])) == 0) ++n;
+        const int r = rank(min(n, n_list - 1));
+        k.n = n;
+        k.b = r % a.B;
+        k.R0 = (n_blk - 1 - r / a.B) * kDenseRows;
+        k.n_queries = nq;
+        k.n_rows = nq * a.H_q;                            // flattened rows of a sequence
+        k.nt = (da.pos0 + min(k.R0 + kDenseRows - 1, k.n_rows - 1) / a.H_q) / kDenseTile + 1;
+        k.t_edge = (da.pos0 + k.R0 / a.H_q + 1) / kDenseTile;            // first tile with keys that some row does not see
+        return k;
     };
-    auto store_q = [&](const u32x4 (&raw)[9]) __attribute__((always_inline)) {
-#pragma unroll
-        for (int c = 0; c < 9; ++c) *(u32x4 *)(qb + (8 * wave + gr) * ROWB + 16 * gp + 128 * c) = raw[c];
-    };
+    const Block first = open(0, 0);
+    if (first.n == n_list) return;
 
-    // Barriers: Q and tile 0 in LDS; Q read; then one at the end of every tile t's step (of step 0 .. nt - 1), one more
-    // within step t + 1 if a reference moved in tile t; row sums in LDS.
+    // The blocks are one stream of tiles: the two of Q (its rows in the shape of keys), then the block's nt of keys, then the
+    // next block's.  Step i: tile i is scored (Q: read), the operands of tile i - 1 and the product of tile i - 2 are taken, tile
+    // i + 2 goes to LDS and tile i + 3 into registers.  Barriers: one before step 0 and one at the end of every step, one more within
+    // step i + 1 if a reference moved in tile i.
     if (wave < 4) {
         const int rh = w & 1, kh = w >> 1;
-        {
-            u32x4 raw[9];
-            load_q(raw);
-            store_q(raw);
-        }
-        __syncthreads();
         bf16x8 qv[KS][2];
-        const unsigned char *qr = qb + (32 * rh + l16) * ROWB + 16 * g;
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
-#pragma unroll
-            for (int r = 0; r < 2; ++r) qv[ks][r] = *(const bf16x8 *)(qr + 16 * r * ROWB + 64 * ks);
         __syncthreads();
-
-        int lim[2];                                       // last key the lane's rows see
-#pragma unroll
-        for (int r = 0; r < 2; ++r) lim[r] = da.pos0 + min(R0 + 32 * rh + 16 * r + l16, n_rows - 1) / a.H_q;
-        const int lim0 = __builtin_amdgcn_readfirstlane(lim[0]);   // the smallest of the wave
+        int lim[2], lim0;                                 // last key the lane's rows see, the smallest of the wave
         const int ka_off = (16 * kh + dense_row(l16)) * ROWB + 16 * g;
         const int pw_off = (32 * rh + l16) * PSTR + 32 * kh + 8 * g;
         float m_c[2] = {-INFINITY, -INFINITY}, l_own[2] = {0.f, 0.f}, psum[2] = {0.f, 0.f};
         bf16x8 ka[RING];
         f32x4 s4[2], odd[2];                              // two accumulation chains, as in the row form: half of the roundings in one
-#pragma unroll
-        for (int r = 0; r < RING; ++r) ka[r] = *(const bf16x8 *)(tbuf + ka_off + 64 * r);
         auto scores = [&](int t) __attribute__((always_inline)) {
             const unsigned char *tb = tbuf + (t & (kDenseRing - 1)) * TBUFB + ka_off;
             const unsigned char *tb1 = tbuf + ((t + 1) & (kDenseRing - 1)) * TBUFB + ka_off;
@@ -906,7 +905,7 @@ __global__ __launch_bounds__(512, 2) void attn_dense_kernel(AttnArgs a, DenseArg
                 __builtin_amdgcn_sched_barrier(0);
             });
         };
-        auto softmax = [&](int t) __attribute__((always_inline)) {
+        auto softmax = [&](int i, int t, int parity) __attribute__((always_inline)) { // tile t of an even or odd block, step i
             // lane: row l16 of either block, keys dense_row(4 g + i)
 #pragma unroll
             for (int r = 0; r < 2; ++r)
@@ -918,7 +917,7 @@ __global__ __launch_bounds__(512, 2) void attn_dense_kernel(AttnArgs a, DenseArg
                 float z = 0.f;                            // NaN if any of the scores is not finite
 #pragma unroll
                 for (int i = 0; i < 4; ++i) z = __builtin_fmaf(s4[1][i], 0.f, __builtin_fmaf(s4[0][i], 0.f, z));
-                if (__ballot(z != 0.f) != 0ull) moved[2] = 1;
+                if (__ballot(z != 0.f) != 0ull) moved[2 + parity] = 1;
 #pragma unroll
                 for (int r = 0; r < 2; ++r)
 #pragma unroll
@@ -938,7 +937,7 @@ __global__ __launch_bounds__(512, 2) void attn_dense_kernel(AttnArgs a, DenseArg
                     m_use[r] = mx[r] > m_c[r] + kLazyLog2 ? mx[r] : m_c[r];
                     if (g == 0) mnew[kDenseRows * kh + 32 * rh + 16 * r + l16] = m_use[r];
                 }
-                moved[t & 1] = 1;
+                moved[i & 1] = 1;
             }
 #pragma unroll
             for (int r = 0; r < 2; ++r) {
@@ -950,19 +949,13 @@ __global__ __launch_bounds__(512, 2) void attn_dense_kernel(AttnArgs a, DenseArg
                     p[i] = fast_exp2(__builtin_fmaf(s4[r][i], a.scale_log2e, -m_safe));
                     pk[i] = __builtin_bit_cast(short, (__bf16)p[i]);
                 }
-                *(s16x4 *)(pbuf + (t & 1) * PBUFB + pw_off + 16 * r * PSTR) = pk;
+                *(s16x4 *)(pbuf + (i & 1) * PBUFB + pw_off + 16 * r * PSTR) = pk;
                 psum[r] = (p[0] + p[1]) + (p[2] + p[3]);
             }
         };
-        scores(0);
-        softmax(0);
-        __syncthreads();
-#pragma unroll 1
-        for (int t = 1;; ++t) {
-            const int flag = moved[(t - 1) & 1];
-            __builtin_amdgcn_sched_barrier(0);
-            if (t < nt) scores(t);
-            if (__builtin_amdgcn_readfirstlane(flag)) {   // a reference moved in tile t - 1 (uniform over the workgroup)
+        // a reference moved in the tile of the step before (flag: uniform over the workgroup); its row sums
+        auto settle = [&](int i, int flag) __attribute__((always_inline)) {
+            if (__builtin_amdgcn_readfirstlane(flag)) {
                 if (tid < kDenseRows) {
                     const float m0 = mnew[tid], m1 = mnew[kDenseRows + tid], m = fmaxf(m0, m1), old = mref[tid];
                     fac[tid] = m == -INFINITY ? 1.f : fast_exp2(old - m);
@@ -971,7 +964,7 @@ __global__ __launch_bounds__(512, 2) void attn_dense_kernel(AttnArgs a, DenseArg
                     mref[tid] = mnew[tid] = mnew[kDenseRows + tid] = m;
                 }
                 __syncthreads();                          // (everybody has read the flag)
-                if (tid == 0) moved[(t - 1) & 1] = 0;     // next raised behind the barrier that ends this step
+                if (tid == 0) moved[(i - 1) & 1] = 0;     // next raised behind the barrier that ends this step
 #pragma unroll
                 for (int r = 0; r < 2; ++r) {
                     const int row = 32 * rh + 16 * r + l16;
@@ -982,33 +975,86 @@ __global__ __launch_bounds__(512, 2) void attn_dense_kernel(AttnArgs a, DenseArg
             }
 #pragma unroll
             for (int r = 0; r < 2; ++r) l_own[r] += psum[r];
-            if (t >= nt) break;
-            softmax(t);
-            __syncthreads();
-        }
+        };
+        int i = 0;
+        Block k = first;
+#pragma unroll 1
+        for (;;) {
+            // Q's steps.  Of the block before: what its last tile moved, then its sums and references for the output waves, where
+            // the factors are otherwise
+            if (i > 0) settle(i, moved[(i - 1) & 1]);
+            if (k.n < n_list) {
+                const unsigned char *qr = tbuf + ((i + rh) & (kDenseRing - 1)) * TBUFB + l16 * ROWB + 16 * g;
 #pragma unroll
-        for (int r = 0; r < 2; ++r) {
-            const float l = xsum16_32(l_own[r]);
-            if (g == 0) mnew[kDenseRows * kh + 32 * rh + 16 * r + l16] = l;
-        }
-        __syncthreads();
-        if (a.lse && tid < kDenseRows && R0 + tid < n_rows) {
-            const float l = mnew[tid] + mnew[kDenseRows + tid];
-            // (in 64 bits: the reference of 32 keys leaves a larger logarithm, and so a coarser sum, than that of the row form's 64)
-            a.lse[(int64_t)b * a.Tq * a.H_q + R0 + tid] =
-                l > 0.f ? (float)(((double)mref[tid] + (double)__builtin_log2f(l)) * 0.6931471805599453) : -INFINITY;
+                for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+                    for (int r = 0; r < 2; ++r) qv[ks][r] = *(const bf16x8 *)(qr + 16 * r * ROWB + 64 * ks);
+            }
+            __syncthreads();
+#pragma unroll
+            for (int r = 0; r < 2; ++r) {
+                const int row = 32 * rh + 16 * r + l16;
+                const float l = xsum16_32(l_own[r]);
+                if (g == 0) {
+                    fac[kDenseRows * kh + row] = l;
+                    fac[2 * kDenseRows + row] = m_c[r];   // (either half writes the same)
+                }
+                l_own[r] = psum[r] = 0.f;
+                m_c[r] = -INFINITY;
+                lim[r] = da.pos0 + min(k.R0 + row, k.n_rows - 1) / a.H_q;
+            }
+            lim0 = __builtin_amdgcn_readfirstlane(lim[0]);
+            if (tid < kDenseRows) mref[tid] = mnew[tid] = mnew[kDenseRows + tid] = -INFINITY;
+            if (tid == 0) moved[2 + k.odd] = 0;       // (that of the block before the last one)
+            __syncthreads();
+            if (k.n == n_list) return;
+            i += 2;
+#pragma unroll
+            for (int r = 0; r < RING; ++r) ka[r] = *(const bf16x8 *)(tbuf + (i & (kDenseRing - 1)) * TBUFB + ka_off + 64 * r);
+            scores(i);
+            softmax(i, 0, k.odd);
+            __syncthreads();
+            ++i;
+#pragma unroll 1
+            for (int t = 1; t < k.nt; ++t, ++i) {
+                const int flag = moved[(i - 1) & 1];
+                __builtin_amdgcn_sched_barrier(0);
+                scores(i);
+                settle(i, flag);
+                softmax(i, t, k.odd);
+                __syncthreads();
+            }
+            k = open(k.n + 1, k.odd ^ 1);
         }
     } else {
         // A tile is fetched eight lanes to a 128-byte line: rows 8 w + gr, nine lines.
-        const unsigned short *kv = (const unsigned short *)a.KV + (PG && a.pv.page_table ? 0 : (int64_t)b * a.Lk * a.row_elems) + 8 * gp;
         u32x4 cur[9];
-        auto tile_src = [&](int t) -> const unsigned short * {   // (past the last tile: that one again, for nobody)
-            const int s0 = min(t, nt - 1) * kDenseTile;                // (a tile never straddles a page)
-            const int64_t row = PG && a.pv.page_table ? paged_row(a.pv, b, s0) : (int64_t)s0;
-            return kv + (row + min(8 * w + gr, da.pos0 + n_queries - 1 - s0)) * a.row_elems;
+        Block ab = first;                                 // the next tile to request: tile aj of block ab, Q is 0 and 1
+        int aj = 0;
+        auto tile_src = [&]() -> const unsigned short * { // (past the last block: its last tile of Q again, for nobody)
+            const unsigned short *p;
+            if (aj < 2) {
+                p = (const unsigned short *)a.Q + ((int64_t)ab.b * a.Tq * a.H_q + min(ab.R0 + 32 * aj + 8 * w + gr, ab.n_rows - 1)) * D_QK;
+            } else {
+                const int s0 = (aj - 2) * kDenseTile;                      // (a tile never straddles a page)
+                const int64_t row = PG && a.pv.page_table ? paged_row(a.pv, ab.b, s0) : (int64_t)ab.b * a.Lk + s0;
+                p = (const unsigned short *)a.KV + (row + min(8 * w + gr, da.pos0 + ab.n_queries - 1 - s0)) * a.row_elems;
+            }
+            if (__builtin_expect(++aj == ab.nt + 2, 0)) {
+                const Block nx = open(ab.n + 1, 0);
+                if (nx.n < n_list) {
+                    ab = nx;
+                    aj = 0;
+                } else {
+                    aj = 1;
+                    ab.nt = INT32_MAX - 2;                // (never to come round)
+                }
+            }
+            if (ab.nt == INT32_MAX - 2) aj = 1;
+            return p + 8 * gp;
         };
-        auto load = [&](int t) __attribute__((always_inline)) {
-            const unsigned short *p = tile_src(t);
+        auto load = [&]() __attribute__((always_inline)) {
+            const unsigned short *p = tile_src();
 #pragma unroll
             for (int c = 0; c < 9; ++c) cur[c] = *(const u32x4 *)(p + 64 * c);
         };
@@ -1018,10 +1064,18 @@ __global__ __launch_bounds__(512, 2) void attn_dense_kernel(AttnArgs a, DenseArg
             for (int c = c0; c < c0 + n; ++c) *(u32x4 *)(d + 128 * c) = cur[c];
         };
         {
-            u32x4 raw[9];
-            load_q(raw);
-            load(0);
-            store_q(raw);
+            u32x4 q0[9];
+            load();
+#pragma unroll
+            for (int c = 0; c < 9; ++c) q0[c] = cur[c];
+            load();
+            {
+                unsigned char *d = tbuf + st_off;
+#pragma unroll
+                for (int c = 0; c < 9; ++c) *(u32x4 *)(d + 128 * c) = q0[c];
+            }
+            store(1, 0, 9);
+            load();
         }
         f32x16 o_acc[2][4];                               // [rows 32 r ..][columns 32 nb ..]
 #pragma unroll
@@ -1030,15 +1084,6 @@ __global__ __launch_bounds__(512, 2) void attn_dense_kernel(AttnArgs a, DenseArg
             for (int nb = 0; nb < 4; ++nb)
 #pragma unroll
                 for (int e = 0; e < 16; ++e) o_acc[r][nb][e] = 0.f;
-        store(0, 0, 9);
-        load(1);
-        __syncthreads();
-        store(1, 0, 9);
-        load(2);
-        __syncthreads();
-        store(2, 0, 9);
-        load(3);
-
         typedef __attribute__((ext_vector_type(8))) short s16x8;
         typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
         const int tr_off = (8 * hh + 2 * (l16 >> 2)) * ROWB + 256 * w + 32 * (g & 1) + 8 * (l16 & 3);
@@ -1071,15 +1116,17 @@ __global__ __launch_bounds__(512, 2) void attn_dense_kernel(AttnArgs a, DenseArg
 #pragma unroll
             for (int r = 0; r < 2; ++r) pa[s][r] = *(const bf16x8 *)(pb + 32 * r * PSTR + 32 * s);
         };
-        // Step t: output product of tile t - 2 (kMma) in two steps of 16 keys, from operands read a step ago; those of tile
-        // t - 1 take their registers, tile t + 2 goes to LDS and tile t + 3 into its registers (kNext)
-        auto step = [&](int t, auto mma_c, auto next_c) __attribute__((always_inline)) {
-            constexpr bool kMma = decltype(mma_c)::value, kNext = decltype(next_c)::value;
-            const int flag = kNext ? moved[(t - 1) & 1] : 0;
-            const unsigned short *src = tile_src(t + 3);
+        // Step i: output product of tile i - 2 (kMma) in two steps of 16 keys, from operands read a step ago; those of tile i - 1
+        // (kRead: tile t of block k) take their registers, tile i + 2 goes to LDS and tile i + 3 into its registers
+        int i = 0;
+        Block k = first;
+        auto step = [&](int t, auto mma_c, auto read_c) __attribute__((always_inline)) {
+            constexpr bool kMma = decltype(mma_c)::value, kRead = decltype(read_c)::value;
+            const int flag = kRead ? moved[(i - 1) & 1] : 0;
+            const unsigned short *src = tile_src();
             __builtin_amdgcn_sched_barrier(0);
-            unroll<8>([&](auto i_c) __attribute__((always_inline)) {
-                constexpr int i = decltype(i_c)::value, s = i >> 2, nb = i & 3;
+            unroll<8>([&](auto u_c) __attribute__((always_inline)) {
+                constexpr int u = decltype(u_c)::value, s = u >> 2, nb = u & 3;
                 if constexpr (kMma) {
                     const s16x8 v = {vq[s][nb][0][0], vq[s][nb][0][1], vq[s][nb][0][2], vq[s][nb][0][3], vq[s][nb][1][0], vq[s][nb][1][1], vq[s][nb][1][2], vq[s][nb][1][3]};
 #pragma unroll
@@ -1087,19 +1134,19 @@ __global__ __launch_bounds__(512, 2) void attn_dense_kernel(AttnArgs a, DenseArg
                         o_acc[r][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, v), pa[s][r], o_acc[r][nb], 0, 0, 0);
                     __builtin_amdgcn_sched_barrier(0);
                 }
-                if constexpr (kNext) {
-                    read_v(t - 1, s, nb);
-                    if constexpr (nb == 3) read_p(t - 1, s);
-#pragma unroll
-                    for (int c = i; c < (i == 7 ? 9 : i + 1); ++c) {
-                        store(t + 2, c, 1);
-                        cur[c] = *(const u32x4 *)(src + 64 * c);
-                    }
-                    __builtin_amdgcn_sched_barrier(0);
+                if constexpr (kRead) {
+                    read_v(i - 1, s, nb);
+                    if constexpr (nb == 3) read_p(i - 1, s);
                 }
+#pragma unroll
+                for (int c = u; c < (u == 7 ? 9 : u + 1); ++c) {
+                    store(i + 2, c, 1);
+                    cur[c] = *(const u32x4 *)(src + 64 * c);
+                }
+                __builtin_amdgcn_sched_barrier(0);
             });
-            if (kNext && t - 1 >= t_edge && __builtin_amdgcn_readfirstlane(moved[2])) finite_v();
-            if (kNext && __builtin_amdgcn_readfirstlane(flag)) {       // see above
+            if (kRead && t >= k.t_edge && __builtin_amdgcn_readfirstlane(moved[2 + k.odd])) finite_v();
+            if (kRead && __builtin_amdgcn_readfirstlane(flag)) {       // see above
                 __syncthreads();
                 if constexpr (kMma) {
 #pragma unroll
@@ -1120,54 +1167,86 @@ __global__ __launch_bounds__(512, 2) void attn_dense_kernel(AttnArgs a, DenseArg
                         for (int e = 0; e < 8; ++e) pa[s][r][e] = (__bf16)((float)pa[s][r][e] * f);
                     }
             }
+            ++i;
+        };
+        // Outputs of block k, in halves of 32 rows, through the rows of the ring that this wave fills in this step (nobody else
+        // touches them now): a store covers whole lines.  (O is 16-byte aligned: dense_output())
+        auto finish = [&]() __attribute__((always_inline)) {
+            int ln = lane;                                // (kept from before the loop, what follows from it would be spilled)
+            asm volatile("" : "+v"(ln));
+            const int c32 = ln & 31, half = ln >> 5;
+            unsigned char *ob = tbuf + ((i + 2) & (kDenseRing - 1)) * TBUFB + 8 * w * ROWB;
+            const int64_t row0 = (int64_t)k.b * a.Tq * a.H_q + k.R0;
+            const bool odd_keys = __builtin_amdgcn_readfirstlane(moved[2 + k.odd]);    // (rare: see finite_v above)
+            unroll<2>([&](auto r_c) __attribute__((always_inline)) {
+                constexpr int r = decltype(r_c)::value;
+                const float l = fac[32 * r + c32] + fac[kDenseRows + 32 * r + c32];
+                const float inv = l > 0.f ? __builtin_amdgcn_rcpf(l) : 0.f;
+                // (in 64 bits: the reference of 32 keys leaves a larger logarithm, and so a coarser sum, than that of the row form's 64)
+                if (a.lse && w == 0 && half == 0 && k.R0 + 32 * r + c32 < k.n_rows)
+                    a.lse[row0 + 32 * r + c32] =
+                        l > 0.f ? (float)(((double)fac[2 * kDenseRows + 32 * r + c32] + (double)__builtin_log2f(l)) * 0.6931471805599453) : -INFINITY;
+                unroll<16>([&](auto q_c) __attribute__((always_inline)) {
+                    constexpr int nb = decltype(q_c)::value >> 2, qd = decltype(q_c)::value & 3;
+                    s16x4 o;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) o[e] = __builtin_bit_cast(short, (__bf16)(o_acc[r][nb][4 * qd + e] * inv));
+                    *(s16x4 *)(ob + c32 * OSTR + 2 * (32 * nb + 8 * qd + 4 * half)) = o;
+                });
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const int row = 4 * j + (ln >> 4), R = k.R0 + 32 * r + row;
+                    u32x4 o = *(const u32x4 *)(ob + row * OSTR + 16 * (ln & 15));
+                    if (odd_keys && R < k.n_rows) {
+                        const unsigned short *v0 = (const unsigned short *)a.KV + 128 * w + 8 * (ln & 15);
+                        for (int key = k.t_edge * kDenseTile; key <= da.pos0 + R / a.H_q; ++key) {
+                            const int64_t at = PG && a.pv.page_table ? paged_row(a.pv, k.b, key) : (int64_t)k.b * a.Lk + key;
+                            const u32x4 v = *(const u32x4 *)(v0 + at * a.row_elems);
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) {
+                                if ((v[e] & 0x7f80u) == 0x7f80u) o[e] |= 0x7fc0u;
+                                if ((v[e] & 0x7f800000u) == 0x7f800000u) o[e] |= 0x7fc00000u;
+                            }
+                        }
+                    }
+                    if (R < k.n_rows) *(u32x4 *)((__bf16 *)a.O + (row0 + 32 * r + row) * D_V + 128 * w + 8 * (ln & 15)) = o;
+                }
+            });
+#pragma unroll
+            for (int r = 0; r < 2; ++r)
+#pragma unroll
+                for (int nb = 0; nb < 4; ++nb)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) o_acc[r][nb][e] = 0.f;
         };
         constexpr std::true_type T{};
         constexpr std::false_type F{};
         __syncthreads();
-        step(1, F, T);
-#pragma unroll 1
-        for (int t = 2; t <= nt; ++t) {
-            __syncthreads();
-            step(t, T, T);
-        }
-        step(nt + 1, T, F);
+        step(0, F, F);
         __syncthreads();
-        float inv[2];
-#pragma unroll
-        for (int r = 0; r < 2; ++r) {
-            const float l = mnew[32 * r + l32] + mnew[kDenseRows + 32 * r + l32];
-            inv[r] = l > 0.f ? __builtin_amdgcn_rcpf(l) : 0.f;
-        }
-        unroll<32>([&](auto q_c) __attribute__((always_inline)) {
-            constexpr int q = decltype(q_c)::value, r = q >> 4, nb = (q >> 2) & 3, qd = q & 3;
-            s16x4 o;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) o[e] = __builtin_bit_cast(short, (__bf16)(o_acc[r][nb][4 * qd + e] * inv[r]));
-            *(s16x4 *)(tbuf + (32 * r + l32) * OSTR + 2 * (128 * w + 32 * nb + 8 * qd + 4 * hh)) = o;
-        });
-    }
-    __syncthreads();
-    __bf16 *out = (__bf16 *)a.O + ((int64_t)b * a.Tq * a.H_q + R0) * D_V;   // (16-byte aligned: dense_output())
-    if (__builtin_amdgcn_readfirstlane(moved[2])) {       // (rare: see finite_v above)
-        const unsigned short *v0 = (const unsigned short *)a.KV + (PG && a.pv.page_table ? 0 : (int64_t)b * a.Lk * a.row_elems) + 8 * lane;
-        for (int row = wave; row < kDenseRows && R0 + row < n_rows; row += 8) {
-            u32x4 o = *(const u32x4 *)(tbuf + row * OSTR + 16 * lane);
-            for (int key = t_edge * kDenseTile; key <= da.pos0 + (R0 + row) / a.H_q; ++key) {
-                const u32x4 v = *(const u32x4 *)(v0 + (PG && a.pv.page_table ? paged_row(a.pv, b, key) : (int64_t)key) * a.row_elems);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    if ((v[e] & 0x7f80u) == 0x7f80u) o[e] |= 0x7fc0u;
-                    if ((v[e] & 0x7f800000u) == 0x7f800000u) o[e] |= 0x7fc00000u;
-                }
+        step(0, F, F);
+        __syncthreads();
+        step(0, F, F);
+        __syncthreads();
+#pragma unroll 1
+        for (;;) {
+            // tile i - 2 is the second one of Q
+            step(0, F, T);
+            __syncthreads();
+#pragma unroll 1
+            for (int t = 1; t < k.nt; ++t) {
+                step(t, T, T);
+                __syncthreads();
             }
-            *(u32x4 *)(out + (int64_t)row * D_V + 8 * lane) = o;
+            step(0, T, F);
+            __syncthreads();
+            const Block nx = open(k.n + 1, k.odd ^ 1);    // tile i - 2 is its first one of Q
+            finish();
+            if (nx.n == n_list) return;
+            k = nx;
+            step(0, F, F);
+            __syncthreads();
         }
-        return;
-    }
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        const int row = 8 * j + wave;
-        if (R0 + row < n_rows) *(u32x4 *)(out + (int64_t)row * D_V + 8 * lane) = *(const u32x4 *)(tbuf + row * OSTR + 16 * lane);
     }
 }
 
@@ -1893,6 +1972,16 @@ hipError_t launch_slab(const AttnArgs &a, hipStream_t st)
     return hipGetLastError();
 }
 
+int cu_count()
+{
+    static int n_cu = 0;
+    if (n_cu == 0) {
+        int dev = 0, v = 0;
+        if (hipGetDevice(&dev) == hipSuccess && hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess) n_cu = v;
+    }
+    return n_cu;
+}
+
 constexpr int kStreamLds = kStreamRing * kGranule * (576 * 2 + kSlabPad) + 2 * 32 * (kGranule * 2 + 16) + (4 * 32 * 4 + 2 * 32 * 2) * 4 + kStreamRing * kGranule * 8;
 
 template <bool PG, bool MULTI, bool REST = false, bool PROBS = false>
@@ -1902,14 +1991,8 @@ hipError_t launch_stream(const AttnArgs &a, hipStream_t st, const RestArgs &ra =
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, kStreamLds);
     if (attr != hipSuccess) return attr;
     int64_t wgs = (int64_t)a.n_layers * a.B * a.Tq;
-    // one workgroup per CU walks a chain of queries
-    static int n_cu = 0;
-    if (n_cu == 0) {
-        int dev = 0, v = 0;
-        if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v <= 0)
-            return hipErrorInvalidDevice;
-        n_cu = v;
-    }
+    const int n_cu = cu_count();                          // one workgroup per CU walks a chain of queries
+    if (n_cu <= 0) return hipErrorInvalidDevice;
     if (wgs > n_cu) wgs = n_cu;
     if (REST) wgs = ra.wgs;
     // (the counts of a workgroup's queries have to fit where P and the references are otherwise)
@@ -2017,12 +2100,15 @@ hipError_t launch_attn_rest(const AttnArgs &a, const RestArgs &ra, hipStream_t s
 hipError_t launch_attn_dense(const AttnArgs &a, const DenseArgs &da, hipStream_t st)
 {
     if (da.n_queries <= 0) return hipSuccess;
-    constexpr int lds = kDenseRing * kDenseTile * (576 * 2 + kSlabPad) + 2 * kDenseRows * (kDenseTile * 2 + 16) + (6 * kDenseRows + 3) * 4;
+    constexpr int lds = kDenseRing * kDenseTile * (576 * 2 + kSlabPad) + 2 * kDenseRows * (kDenseTile * 2 + 16) + (6 * kDenseRows + 4 + kDenseChain) * 4;
     static hipError_t attr = hipFuncSetAttribute((const void *)attn_dense_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     static hipError_t attr_pg = hipFuncSetAttribute((const void *)attn_dense_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (attr != hipSuccess) return attr;
     if (attr_pg != hipSuccess) return attr_pg;
-    const dim3 grid((unsigned)((da.n_queries * a.H_q + kDenseRows - 1) / kDenseRows), (unsigned)a.B);
+    const int64_t blocks = ((int64_t)da.n_queries * a.H_q + kDenseRows - 1) / kDenseRows * a.B;
+    const int n_cu = cu_count();
+    if (n_cu <= 0) return hipErrorInvalidDevice;
+    const dim3 grid((unsigned)std::max(std::min<int64_t>(blocks, n_cu), (blocks + kDenseChain - 1) / kDenseChain));
     if (a.pv.page_table)
         hipLaunchKernelGGL(attn_dense_kernel<true>, grid, dim3(512), lds, st, a, da);
     else

@@ -1,4 +1,4 @@
-"""Unsplit sparse attention of 576 / 512 rows against a 64-bit reference at the sizes where its stream of 32-row granules can go
+"""Unsplit sparse attention of 576 / 512 rows against a 64-bit reference at the sizes where its streams of rows can go
 wrong: selections of one entry to a few granules and their remainders, query counts around the number of workgroups (chains of
 one, two and unequal lengths), few heads, empty slots and rows, ragged and paged caches, outputs at any address, several layers."""
 import pytest
@@ -151,3 +151,29 @@ def test_probs(k, B, T, H):
         # scores to 2^-24 * sqrt(576) as above and lse rounded to 2^-24 of about 8: 2e-6 of a probability of at most 1, five times that
         assert (got[b] - p).abs().max().item() < 1e-5
         assert bool((got[b][~valid[b]] == 0).all())
+
+
+@pytest.mark.parametrize("B,T,H,broken", [(1, 1100, 32, ()), (2, 900, 20, (300,)), (3, 700, 32, (650, 1)), (5, 520, 17, (0, 519, 64, 65))])
+def test_prefix_rows_in_chains(B, T, H, broken):
+    # whole prefixes: more blocks of 64 (query, head) rows than workgroups, so that a workgroup walks several; from a sequence's
+    # broken row on (two entries swapped) its rows are not counted and their blocks leave gaps in the chains
+    g = torch.Generator().manual_seed(T)
+    Q = torch.randn((B, T, H, D_QK), generator=g).to(torch.bfloat16)
+    KV = torch.randn((B, T, D_QK), generator=g).to(torch.bfloat16)
+    pos = torch.arange(T, dtype=torch.int32)
+    idx = torch.where(pos[None, :] <= pos[:, None], pos[None, :], torch.tensor(-1, dtype=torch.int32)).repeat(B, 1, 1)
+    for b, t in enumerate(broken):
+        if t > 0:
+            idx[b, t, :2] = torch.tensor([1, 0], dtype=torch.int32)
+        else:
+            idx[b, 0, :2] = torch.tensor([-1, 0], dtype=torch.int32)
+    O, lse = ic.sparse_attn(Q.cuda(), KV.cuda(), idx.cuda(), D_V, 0, SCALE, want_lse=True)
+    ref_O, ref_lse = [], []
+    mask = pos[None, :] <= pos[:, None]
+    for b in range(B):
+        kv = KV[b].double()
+        s = torch.einsum("thd,sd->ths", Q[b].double(), kv) * SCALE
+        s = s.masked_fill(~mask[:, None, :], -float("inf"))
+        ref_lse.append(torch.logsumexp(s, dim=-1))
+        ref_O.append(torch.einsum("ths,sd->thd", torch.softmax(s, dim=-1), kv[:, :D_V]))
+    _check(O, lse, torch.stack(ref_O), torch.stack(ref_lse))
