@@ -30,6 +30,7 @@
 // never holds more rows than the caller's workspace allows.  Keys hidden by the causal mask
 // are not written.
 #include "ic_common.hpp"
+#include <algorithm>
 
 #include <type_traits>
 
@@ -709,7 +710,16 @@ hipError_t launch_score(const ScoreArgs &a_in, int dtype, int d_I, int Bc, hipSt
     // several times; the streaming variant wants exactly one resident round (3 per CU).
     const int64_t want_wgs = few_rows ? 768 : 2048;
     int64_t kc = (max_vis * a.n_qblocks * Bc / want_wgs + 63) / 64 * 64;
-    kc = kc < 512 ? 512 : (kc > 8192 ? 8192 : kc);
+    // At least 512 keys a workgroup, which pay for its q rows; fewer where that leaves CUs idle: a problem this small takes as long
+    // as one workgroup, so its visible pairs are dealt out to one workgroup per CU.  Measured with 512 / with this rule, top-k
+    // included: 512 x 512 (4 heads of 64) 20.5 / 14.6 us, 1024 x 1024 20.8 / 17.5, 64 rows before 5000 keys (32 heads of 128)
+    // 28.9 / 21.2; where 512 keys already give a workgroup per CU, smaller ones lose: 300 rows before 5000 keys 30.9, with 256 keys 32.8.
+    int64_t least = 512;
+    if (!few_rows) {
+        const int64_t mean_vis = a.pv.seq_lens ? max_vis : std::max<int64_t>(1, std::min(max_vis, a.q_pos0 + a.i0 + (i_last - a.i0) / 2 + 1));
+        least = std::min<int64_t>(512, std::max<int64_t>(64, (mean_vis * a.n_qblocks * Bc / 256 + 63) / 64 * 64));
+    }
+    kc = kc < least ? least : (kc > 8192 ? 8192 : kc);
     a.KC = (int)kc;
     const bool fp8 = dtype == IC_FP8_E4M3;
     if (few_rows && !fp8 && d_I == 128)
