@@ -89,10 +89,11 @@ __global__ __launch_bounds__(256, 2) void attn_kernel(AttnArgs a)
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int l16 = lane & 15, g = lane >> 4;
     const int mh = wave & 1, vh = wave >> 1;
+    asm volatile("" ::"s"(a.n_layers), "s"(a.B), "s"(a.Tq), "s"(a.Lk), "s"(a.H_q), "s"(a.row_elems), "s"(a.k_sel), "s"(a.split_len), "s"(a.idx));   // (together: see attn_slab_kernel)
     const int64_t gq = blockIdx.x;                        // query of the launch: flattened (layer, b, t)
     const int layer = layer_of(a, gq);
     const int64_t qrow = gq - (int64_t)layer * a.B * a.Tq;
-    const int b = (int)(qrow / a.Tq);
+    const int b = (int)((unsigned)qrow / (unsigned)a.Tq);
     const int sp = blockIdx.y;
     const int slot0 = sp * a.split_len;
     const int slot1 = min(slot0 + a.split_len, a.k_sel);
@@ -1823,6 +1824,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a)
     constexpr int LPS = D_V / 8, kBatch = 8;
     constexpr int GROUP = LPS * SLOTS, HEADS = 256 / GROUP;  // threads of a head, heads of a workgroup
     static_assert(SLOTS == 1 || 2 * GROUP >= D_V, "two columns per thread at the end");
+    asm volatile("" ::"s"(a.n_layers), "s"(a.B), "s"(a.Tq), "s"(a.H_q), "s"(a.n_splits), "s"(a.row_gap), "s"(a.part_o), "s"(a.part_ml), "s"(a.lse));   // (together: see attn_slab_kernel)
     const int64_t gq = blockIdx.x;
     const int layer = layer_of(a, gq);
     int64_t qrow = gq - (int64_t)layer * a.B * a.Tq;

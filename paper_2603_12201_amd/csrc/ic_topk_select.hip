@@ -353,10 +353,18 @@ __device__ __forceinline__ void select_row_generic(const SelectArgs &a, uint32_t
     }
 }
 
+// The arguments that the way to a row's first load needs, requested together: left alone each is loaded where it is first used, a
+// chain of memory latencies in front of a launch of 10 to 20 us.
+__device__ __forceinline__ void request_args(const SelectArgs &a)
+{
+    asm volatile("" ::"s"(a.strip), "s"(a.ld), "s"(a.q_pos0), "s"(a.Tq), "s"(a.Lk), "s"(a.k_sel), "s"(a.b0), "s"(a.i0), "s"(a.Ri), "s"(a.idx), "s"(a.seq_lens));
+}
+
 template <int NT>
 __global__ __launch_bounds__(NT) void select_kernel(SelectArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) uint32_t smem[];
+    request_args(a);
     select_row_generic<NT>(a, smem);
 }
 
@@ -408,6 +416,7 @@ template <int NT, int MAXLEN, int CAP, bool RES>
 __global__ __launch_bounds__(NT) void select_cand_kernel(SelectArgs a)
 {
     static_assert(kCandSample % (4 * NT) == 0 && (MAXLEN / 32) % NT == 0, "whole sample vectors and bitmap words per thread");
+    request_args(a);
     constexpr int NW = NT / 64;
     constexpr int SV = kCandSample / (4 * NT); // sample vectors per thread
     constexpr int BW = MAXLEN / 32 / NT;       // bitmap words per thread
@@ -728,6 +737,7 @@ __device__ __forceinline__ bool part_row(const SelectArgs &a, int nv) { return n
 __global__ __launch_bounds__(kPartThreads) void select_part_kernel(SelectArgs a, PartArgs pa)
 {
     constexpr int NT = kPartThreads, NW = kPartWaves;
+    request_args(a);
     __shared__ __attribute__((aligned(16))) uint32_t hist[kBins1];
     __shared__ uint32_t wsum[2 * NW], bc[4], red[2 * NW];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -827,6 +837,7 @@ __global__ __launch_bounds__(kPartThreads) void select_finish_kernel(SelectArgs 
     static_assert(kBoundaryCap <= NT && kPartMax * NW <= NT && kFinishCap / 32 <= NT, "one list, one bitmap word per thread");
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int r = blockIdx.x;
+    request_args(a);
     const RowView rv = row_view(a, r);
     if (rv.i >= a.Tq) return;
     auto finish = [&]() -> bool {              // false: the generic form takes the row (one call site, see below)
