@@ -42,6 +42,21 @@ template <typename T> __device__ __forceinline__ T load_uniform(const T *p)
     return *(const __attribute__((address_space(4))) T *)(uintptr_t)p;
 }
 
+// Inclusive prefix sum over the 64 lanes of a wave on the data-parallel-primitive path of the
+// vector ALU (no LDS traffic): shifts by 1, 2, 4, 8 lanes inside each row of 16 lanes, then the
+// last lane of rows 0 and 2 is added to rows 1 and 3, then lane 31 to rows 2 and 3.  Lanes
+// without a source add zero.  Packed fields are summed independently as long as none overflows.
+__device__ __forceinline__ uint32_t wave_incl_scan(uint32_t x)
+{
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, false);   // row_shr:1
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, false);   // row_shr:2
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, false);   // row_shr:4
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, false);   // row_shr:8
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, false);   // row_bcast:15 into rows 1, 3
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, false);   // row_bcast:31 into rows 2, 3
+    return x;
+}
+
 // Indexer scoring of query rows [i0, i0+Ri) of sequences [b0, b0+Bc) against their keys.
 // Scores land in a strip: row (b-b0)*Ri + (i-i0), element s, row stride ld floats.
 struct ScoreArgs {

@@ -465,10 +465,11 @@ __global__ void fill_kernel(float *p, int64_t n, float v)
 // same piece for all lanes) spread over all banks.  The q rows of a token (32 heads x 256 B = one slot per head
 // tile) travel through the same ring as items of their own, ahead of the token's keys.
 // Order.  Reading the cache as a few wide windows that slide is faster than many narrow streams (measured: 32
-// concurrent per-token windows 100 us, 8 windows 90 us, one window 87 us for 537 MB).  So only G tokens are in
-// flight, each with the workgroups of one residue mod G (for G = 8 that is one XCD: workgroup ids are dealt
-// round-robin over the eight XCDs; the kernel itself is a little faster with G = 16, two tokens per XCD); all waves
-// of those workgroups interleave slot by slot over the token's keys, then move to the token G further on together.
+// concurrent per-token windows 100 us, 8 windows 90 us, one window 87 us for 537 MB).  So there are G windows, each with
+// the workgroups of one residue mod G (for G = 16 two per XCD: workgroup ids are dealt round-robin over the eight
+// XCDs), all waves of which interleave slot by slot.  A window takes an even share of the slots of all tokens, not
+// whole tokens: 40 sequences of 700 to 49152 keys are two or three tokens a window, some of them short, and windows that
+// are through leave CUs without loads in flight.  (Decode step of four layers on those: 189 us with whole tokens, 173 with shares.)
 // ---------------------------------------------------------------------------------------------------------
 __device__ __forceinline__ void dma_lanes(const void *lane_addr, unsigned lds_addr /*uniform*/)
 {
@@ -479,7 +480,7 @@ template <int N> __device__ __forceinline__ void wait_vm_le()
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 template <int HT, int NW, int R, bool PG>
-__global__ __launch_bounds__(64 * NW, 1) void score_stream_kernel(ScoreArgs a, int T, int G)
+__global__ __launch_bounds__(64 * NW, 1) void score_stream_kernel(ScoreArgs a, int T, int lg)       // T tokens, 2^lg windows
 {
     constexpr int RB = 256;                     // bytes per key row (and per q row)
     constexpr int SUB = 32;                     // rows per slot
@@ -489,44 +490,64 @@ __global__ __launch_bounds__(64 * NW, 1) void score_stream_kernel(ScoreArgs a, i
     static_assert(R >= 2 && NI * (R - 1) < 64, "the vector-memory counter holds 63");
     extern __shared__ __attribute__((aligned(1024))) unsigned char ring[];   // [NW][R][SLOT]
 
+    // (requested together: left alone each is loaded where it is first used, one memory latency after another)
+    asm volatile("" ::"s"(a.q), "s"(a.k), "s"(a.w), "s"(a.strip), "s"(a.ld), "s"(a.q_pos0), "s"(a.Tq), "s"(a.Lk), "s"(a.H_I), "s"(a.b0), "s"(a.i0), "s"(a.Ri), "s"(T), "s"(lg));
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r32 = lane & 31, half = lane >> 5;
-    const int wdw = (int)blockIdx.x % G;                    // this workgroup's tokens: wdw, wdw + G, ...
-    const int wstride = NW * ((int)gridDim.x / G);          // waves that share a token
-    const int wfirst = ((int)blockIdx.x / G) * NW + wave;   // this wave's slots of a token: wfirst, wfirst + wstride, ...
+    const int G = 1 << lg, wdw = (int)blockIdx.x & (G - 1); // this workgroup's window
+    const unsigned wstride = NW * (gridDim.x >> lg);        // waves that share it
+    const unsigned wfirst = (blockIdx.x >> lg) * NW + wave;   // this wave's slots of the window: wfirst, wfirst + wstride, ...
     const bool ragged = PG && a.pv.seq_lens, paged = PG && a.pv.page_table;
     const int i_end = min(a.i0 + a.Ri, a.Tq);
+    // Order of the tokens: 0, G, 2 G, .., 1, G + 1, ..: windows over equal tokens then slide through neighbouring ones together (32
+    // tokens of 65536 keys, decode step of four layers: 184 us, 189 in ascending order).  Places that hold no token have no slots.
+    const int n_col = (T + G - 1) >> lg, n_place = n_col * G;
+    auto token = [&](int place) -> int { return n_col == 1 ? place : place % n_col * G + place / n_col; };
+    auto seq_of = [&](int tk) -> int { return a.Ri == 1 ? tk : tk / a.Ri; };     // (a division is 0.1 us in front of everything)
 
-    // A cursor walks the wave's items: per token HT q items (jj = -HT .. -1), then its key slots (jj = 0 .. n_w - 1).
+    // keys that query row t sees, of a sequence that holds Lk_b
+    auto visible = [&](int t, int Lk_b) -> int {
+        const int64_t vis = (ragged ? (int64_t)Lk_b - a.Tq : a.q_pos0) + (int64_t)t + 1;
+        return t >= i_end || vis < 0 ? 0 : (vis > Lk_b ? Lk_b : (int)vis);
+    };
+    // A cursor walks the wave's items: per token HT q items (jj = -HT .. -1), then its key slots (jj = 0).
     // Two cursors run over the same sequence: the one that issues loads stays R - 1 items ahead of the one that
     // computes.
     struct Cur {
-        int tk, jj, n_w;
+        int at, jj;                             // place of the token, item
+        unsigned sub, nsub, left;               // slot within the token, the token's slots, slots left to the wave
         int bz, t, Lk_b, vis;                   // sequence within the launch, query row, visible keys
     };
-    auto enter = [&](Cur &c) {                  // first item of token c.tk or of the next token that has work
-        for (; c.tk < T; c.tk += G) {
-            c.bz = c.tk / a.Ri;
-            c.t = a.i0 + c.tk % a.Ri;
-            if (c.t >= i_end) continue;
-            const int b = a.b0 + c.bz;
-            c.Lk_b = ragged ? max(0, min(load_uniform(a.pv.seq_lens + b), a.Lk)) : a.Lk;
-            const int64_t q_pos0 = ragged ? (int64_t)c.Lk_b - a.Tq : a.q_pos0;
-            int64_t vis64 = q_pos0 + (int64_t)c.t + 1;
-            vis64 = vis64 < 0 ? 0 : (vis64 > c.Lk_b ? c.Lk_b : vis64);
-            c.vis = (int)vis64;
-            const int nsub = (c.vis + SUB - 1) / SUB;
-            c.n_w = nsub > wfirst ? (nsub - wfirst + wstride - 1) / wstride : 0;
-            if (c.n_w > 0) {
+    auto enter = [&](Cur &c) {                  // slot c.sub counted from place c.at on: its token
+        for (; c.at < n_place; ++c.at) {
+            const int tk = token(c.at);
+            if (tk >= T) continue;
+            c.bz = seq_of(tk);
+            c.t = a.i0 + (tk - c.bz * a.Ri);
+            c.Lk_b = ragged ? max(0, min(load_uniform(a.pv.seq_lens + a.b0 + c.bz), a.Lk)) : a.Lk;
+            c.vis = visible(c.t, c.Lk_b);
+            c.nsub = (unsigned)(c.vis + SUB - 1) / SUB;
+            if (c.sub < c.nsub) {
                 c.jj = -HT;
                 return;
             }
+            c.sub -= c.nsub;
         }
     };
     auto next = [&](Cur &c) {
-        if (++c.jj >= c.n_w) {
-            c.tk += G;
+        if (c.jj < 0) {
+            ++c.jj;
+            return;
+        }
+        if (--c.left == 0) {
+            c.at = n_place;
+            return;
+        }
+        c.sub += wstride;
+        if (c.sub >= c.nsub) {
+            c.sub -= c.nsub;
+            ++c.at;
             enter(c);
         }
     };
@@ -543,7 +564,7 @@ __global__ __launch_bounds__(64 * NW, 1) void score_stream_kernel(ScoreArgs a, i
             base = (const unsigned char *)a.q + (((int64_t)b * a.Tq + c.t) * a.H_I + min(h0, a.H_I - 1)) * RB;
             last = max(a.H_I - 1 - h0, 0);
         } else {
-            const int s0 = (wfirst + c.jj * wstride) * SUB;             // < vis <= Lk_b
+            const int s0 = (int)c.sub * SUB;    // < vis <= Lk_b
             int64_t krow = (int64_t)b * a.Lk + s0;
             if (paged) {                        // a slot never straddles a page: pages hold a multiple of 64 positions
                 const int32_t page = load_uniform(a.pv.page_table + (int64_t)b * a.pv.max_pages + (s0 >> a.pv.page_shift));
@@ -561,15 +582,45 @@ __global__ __launch_bounds__(64 * NW, 1) void score_stream_kernel(ScoreArgs a, i
         }
     };
 
+    // The slots of all tokens, one after the other, are shared out to the windows evenly (a score strip of less than 512 GB
+    // has fewer than 2^32).  Slots up to and with place p0 + lane, counted from place p0:
+    auto slots = [&](int p0) -> unsigned {
+        const int tk = token(p0 + lane), bz = seq_of(tk);
+        unsigned n = 0;
+        if (p0 + lane < n_place && tk < T) n = (unsigned)(visible(a.i0 + (tk - bz * a.Ri), ragged ? max(0, min(a.pv.seq_lens[a.b0 + bz], a.Lk)) : a.Lk) + SUB - 1) / SUB;
+        return wave_incl_scan(n);
+    };
+    auto lane_of = [&](unsigned v, int l) -> unsigned { return (unsigned)__builtin_amdgcn_readlane((int)v, l); };
     Cur pc, cc;                                 // producer, consumer
-    pc.tk = wdw;
+    unsigned share;                             // slots of the window
+    if (!ragged && a.Ri == 1 && T == n_place) { // as many tokens of one length in every window: nothing to look for
+        share = (unsigned)n_col * ((unsigned)(visible(a.i0, a.Lk) + SUB - 1) / SUB);
+        pc.at = wdw * n_col;
+        pc.sub = wfirst;
+    } else {
+        unsigned upto = slots(0), total = lane_of(upto, 63);
+        for (int p0 = 64; p0 < n_place; p0 += 64) total += lane_of(slots(p0), 63);
+        const unsigned lo = (unsigned)((uint64_t)total * (unsigned)wdw >> lg);
+        share = (unsigned)((uint64_t)total * (unsigned)(wdw + 1) >> lg) - lo;
+        if (wfirst >= share) return;
+        pc.at = 0;
+        pc.sub = lo + wfirst;
+        for (; pc.sub >= lane_of(upto, 63); upto = slots(pc.at)) {
+            pc.sub -= lane_of(upto, 63);
+            pc.at += 64;
+        }
+        const int behind = __popcll(__ballot(upto <= pc.sub));  // places of the 64 that end in front of the slot
+        if (behind) pc.sub -= lane_of(upto, behind - 1);
+        pc.at += behind;
+    }
+    if (wfirst >= share) return;                // nothing for this wave (no barrier in this kernel)
+    pc.left = (share - wfirst + wstride - 1) / wstride;
     enter(pc);
-    if (pc.tk >= T) return;                     // nothing for this wave (no barrier in this kernel)
     cc = pc;
     int p_slot = 0, c_slot = 0;
 #pragma unroll
     for (int d = 0; d < R - 1; ++d)
-        if (pc.tk < T) {
+        if (pc.at < n_place) {
             issue(pc, p_slot);
             p_slot = p_slot + 1 == R ? 0 : p_slot + 1;
             next(pc);
@@ -586,8 +637,8 @@ __global__ __launch_bounds__(64 * NW, 1) void score_stream_kernel(ScoreArgs a, i
     }
     const unsigned char *my = ring + wave * (R * SLOT) + r32 * RB;       // this lane's row within a slot
 
-    while (cc.tk < T) {
-        if (pc.tk < T) {
+    while (cc.at < n_place) {
+        if (pc.at < n_place) {
             issue(pc, p_slot);                                           // the slot consumed in the previous iteration
             p_slot = p_slot + 1 == R ? 0 : p_slot + 1;
             next(pc);
@@ -641,7 +692,7 @@ __global__ __launch_bounds__(64 * NW, 1) void score_stream_kernel(ScoreArgs a, i
         asm volatile("" ::: "memory");
         const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(s_acc), __float_as_uint(s_acc), false, false);
         const float v = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
-        const int s = (wfirst + cc.jj * wstride) * SUB + r32;
+        const int s = (int)cc.sub * SUB + r32;
         if (half == 0 && s < cc.vis) a.strip[((int64_t)cc.bz * a.Ri + (cc.t - a.i0)) * a.ld + s] = v;
         next(cc);
     }
@@ -652,8 +703,10 @@ hipError_t launch_stream(const ScoreArgs &a, int Bc, hipStream_t st)
 {
     const int T = Bc * a.Ri;                    // tokens of the launch
     if (T <= 0) return hipSuccess;
-    const int G = T < 16 ? T : 16;              // tokens in flight (measured at 32 tokens: 2 -> 99.2, 4 -> 97.7, 8 -> 98.4, 16 -> 97.1, 32 -> 102.1 us)
-    const int W = G * (256 / G);                // one workgroup per CU (the ring takes most of a CU's LDS)
+    // windows (measured at 32 tokens of 65536 keys: 2 -> 99.2, 4 -> 97.7, 8 -> 98.4, 16 -> 97.1, 32 -> 102.1 us); no more than
+    // tokens, and a power of two, so that they share one workgroup per CU (the ring takes most of a CU's LDS)
+    const int lg = T < 2 ? 0 : (T < 4 ? 1 : (T < 8 ? 2 : (T < 16 ? 3 : 4)));
+    const int W = 256;
     constexpr int lds = NW * R * 32 * 256;
     static hipError_t attr = hipFuncSetAttribute((const void *)score_stream_kernel<HT, NW, R, false>,
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, lds);
@@ -662,9 +715,9 @@ hipError_t launch_stream(const ScoreArgs &a, int Bc, hipStream_t st)
     if (attr != hipSuccess) return attr;
     if (attr_pg != hipSuccess) return attr_pg;
     if (a.pv.seq_lens || a.pv.page_table)
-        hipLaunchKernelGGL((score_stream_kernel<HT, NW, R, true>), dim3(W), dim3(64 * NW), lds, st, a, T, G);
+        hipLaunchKernelGGL((score_stream_kernel<HT, NW, R, true>), dim3(W), dim3(64 * NW), lds, st, a, T, lg);
     else
-        hipLaunchKernelGGL((score_stream_kernel<HT, NW, R, false>), dim3(W), dim3(64 * NW), lds, st, a, T, G);
+        hipLaunchKernelGGL((score_stream_kernel<HT, NW, R, false>), dim3(W), dim3(64 * NW), lds, st, a, T, lg);
     return hipGetLastError();
 }
 

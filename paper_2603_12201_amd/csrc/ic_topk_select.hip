@@ -44,21 +44,6 @@ __device__ __forceinline__ float key_score(uint32_t key)
 
 constexpr int kBins1 = 4096;   // histogram bins: digits of 12, 12 and 8 key bits
 
-// Inclusive prefix sum over the 64 lanes of a wave on the data-parallel-primitive path of the
-// vector ALU (no LDS traffic): shifts by 1, 2, 4, 8 lanes inside each row of 16 lanes, then the
-// last lane of rows 0 and 2 is added to rows 1 and 3, then lane 31 to rows 2 and 3.  Lanes
-// without a source add zero.  Packed fields are summed independently as long as none overflows.
-__device__ __forceinline__ uint32_t wave_incl_scan(uint32_t x)
-{
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, false);   // row_shr:1
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, false);   // row_shr:2
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, false);   // row_shr:4
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, false);   // row_shr:8
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, false);   // row_bcast:15 into rows 1, 3
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, false);   // row_bcast:31 into rows 2, 3
-    return x;
-}
-
 // Workgroup-wide descending scan over `nbins` counters: finds the digit d with
 // count(bins > d) < need <= count(bins >= d) and writes {d, need - count(bins > d), count(bin d)} to bc.
 // Every thread owns BPT consecutive bins, highest bins first.  A bin is the sum of R adjacent

@@ -40,3 +40,45 @@ def test_chunks(B, T, L, H, d, k, fp8):
         kth = s.topk(min(k, L), dim=1).values[:, -1]
         low = at.masked_fill(~valid, float("inf")).min(dim=1).values
         assert bool((low >= kth - tol).all())
+
+
+@pytest.mark.parametrize("B,T,L,H,page,low", [
+    (1, 1, 40, 32, 0, 40), (2, 1, 6000, 32, 64, 0), (3, 2, 2100, 20, 64, 1), (5, 4, 900, 64, 0, 0), (17, 1, 3000, 32, 128, 1), (40, 1, 4096, 32, 64, 30),
+    (65, 1, 257, 32, 0, 0), (70, 2, 128, 40, 64, 0), (130, 1, 320, 32, 64, 0), (33, 1, 2050, 32, 0, 2050),
+])
+def test_ragged_shares(B, T, L, H, page, low):
+    # decode rows whose slots of 32 keys are shared out to windows and waves across sequences: empty and one-key sequences, more
+    # tokens than a wave has lanes, fewer slots than waves, several tokens in one wave; every score that a token sees is checked
+    g = torch.Generator().manual_seed(B + L)
+    d, k = 128, min(L, 2048)
+    q = (torch.randn((B, T, H, d), generator=g) / d ** 0.5).to(torch.bfloat16)
+    kk, w = torch.randn((B, L, d), generator=g).to(torch.bfloat16), torch.rand((B, T, H), generator=g)
+    lens = torch.randint(low, L + 1, (B,), generator=g)
+    lens[B // 2] = L
+    cache, table = kk, None
+    if page:
+        per = -(-L // page)
+        order = torch.randperm(B * per, generator=g)
+        table = order.view(B, per).to(torch.int32)
+        cache = torch.full((B * per, page, d), 3e4, dtype=torch.bfloat16)
+        padded = torch.cat([kk, torch.zeros((B, per * page - L, d), dtype=torch.bfloat16)], 1).view(B * per, page, d)
+        cache[order] = padded
+        cache = cache.view(B * per * page, d)
+    pc = ic.paged_cache(lens.to(torch.int32).cuda(), table.cuda() if page else None, page)
+    idx, sel = ic.indexer_topk_paged(q.cuda(), cache.cuda(), w.cuda(), k, L, pc, want_scores=True)
+    idx, sel = idx.cpu().long(), sel.cpu().double()
+    s = torch.matmul(q.double().view(B, T * H, d), kk.double().transpose(1, 2).contiguous()).view(B, T, H, L)
+    s = (torch.relu(s) * w.double()[..., None]).sum(2)
+    seen = torch.arange(L)[None, None, :] < (lens[:, None, None] - T + torch.arange(T)[None, :, None] + 1)
+    s = s.masked_fill(~seen, -float("inf"))
+    valid, n_seen = idx >= 0, seen.sum(-1)
+    assert torch.equal(valid.sum(-1), n_seen.clamp_max(k))
+    assert bool(seen.gather(2, idx.clamp_min(0))[valid].all())
+    # 128 products and 64 terms at most summed in fp32: 2^-24 * sqrt(192) of the largest score, ten times that
+    tol = 1e-5 * s.max().item()
+    at = s.gather(2, idx.clamp_min(0))
+    assert not bool(valid.any()) or (at - sel)[valid].abs().max().item() < tol
+    low = at.masked_fill(~valid, float("inf")).min(dim=-1).values
+    assert bool((low >= s.topk(k, dim=-1).values[..., -1] - tol).all())
+    full = (n_seen <= k)[..., None] & (torch.arange(k) < n_seen[..., None])       # whatever a token sees: all of it, in order
+    assert torch.equal(idx[full], torch.arange(k).expand_as(idx)[full])
