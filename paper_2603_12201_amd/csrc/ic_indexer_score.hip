@@ -112,21 +112,23 @@ __device__ __forceinline__ float relu(float x)
     return __int_as_float(xi > 0 ? xi : 0);
 }
 
-// STREAM = true is the few-query-rows form (decode): the workgroup owns ONE token, every wave
-// keeps its q rows, and the waves take turns on the key subtiles (wave w multiplies subtile
+// STREAM = true is the few-query-rows form (decode): the workgroup owns TPW tokens, every wave
+// keeps their q rows, and the waves take turns on the key subtiles (wave w multiplies subtile
 // w & 1 of the tiles with parity w >> 1) so that all four SIMDs share the little matrix work
-// while the kernel streams the key cache.
+// while the kernel streams the key cache.  fp8 key scales are requested with their tile: a load
+// in the epilogue waits for every tile in flight behind it.  fp8 score and top-k, 64 heads: 12 sequences of one row before 30000
+// keys 31 -> 28.8 us with that.
 // PG: the key cache may be ragged and / or paged (a.pv); false compiles the dense layout only.
 template <int HT, int DI, int TPW, int NW, int PD, int MINB, bool STREAM, bool FP8, bool PG>
 __global__ __launch_bounds__(64 * NW, MINB) void score_kernel(ScoreArgs a)
 {
-    static_assert(!STREAM || (TPW == 1 && NW == 4), "the streaming form is one token, four waves");
+    static_assert(!STREAM || NW == 4, "the streaming form deals its tiles to four waves");
     typedef Fmt<FP8> F;
     typedef typename F::Op Op;
     constexpr int NT = 64 * NW;                 // threads per workgroup
     constexpr int KS = DI / F::kStep;           // MFMA k-steps over the head dim
     constexpr int OPB = F::kStep / 2 * F::kElemBytes;   // operand bytes per lane per k-step
-    constexpr int BT = STREAM ? 1 : NW * TPW;   // tokens per workgroup
+    constexpr int BT = STREAM ? TPW : NW * TPW; // tokens per workgroup
     constexpr int RB = DI * F::kElemBytes;      // bytes per key row
     constexpr int ROWB = RB + 16;               // LDS row stride (bytes), padded against bank conflicts
     constexpr int TILE = 64;                    // keys per LDS tile
@@ -200,10 +202,16 @@ __global__ __launch_bounds__(64 * NW, MINB) void score_kernel(ScoreArgs a)
     // copied to LDS one iteration before it is multiplied.
     u32x4 pre[PD][LPT];
     const int ntiles = (kend - kc0 + TILE - 1) / TILE;
+    float pre_k[PD];                            // STREAM, fp8: the scale of the lane's key in the wave's subtile
+    auto load_k = [&](int d, int it) { if (FP8 && STREAM) pre_k[d] = ksc[min(kc0 + it * TILE + (wave & 1) * 32 + r32, Lk_b - 1)]; };
+    load_k(0, 0);
     tile_gload<RB, LPT, NT>(pre[0], tile_ptr(kc0), Lk_b - kc0, tid);
 #pragma unroll
     for (int d = 1; d < PD; ++d)
-        if (d < ntiles) tile_gload<RB, LPT, NT>(pre[d], tile_ptr(kc0 + d * TILE), Lk_b - (kc0 + d * TILE), tid);
+        if (d < ntiles) {
+            load_k(d, d);
+            tile_gload<RB, LPT, NT>(pre[d], tile_ptr(kc0 + d * TILE), Lk_b - (kc0 + d * TILE), tid);
+        }
     tile_lstore<RB, LPT, ROWB, NT>(pre[0], &lds[0][0], tid);
     if (FP8 && !STREAM) lds_ks[0][lane] = ksc[min(kc0 + lane, Lk_b - 1)];
     __syncthreads();
@@ -211,7 +219,7 @@ __global__ __launch_bounds__(64 * NW, MINB) void score_kernel(ScoreArgs a)
     // Combine the two half-wave partial sums of a token pair (or of one token with itself) and
     // store 32 scores per row.  permlane32_swap(x, y) returns {[x.lo, y.lo], [x.hi, y.hi]}: their
     // sum is token A's total in lanes 0-31 and token B's in lanes 32-63.
-    auto emit = [&](float pa, float pb, bool pair, int j, int s0, int r32_x, int half_x) {
+    auto emit = [&](float pa, float pb, bool pair, int j, int s0, int r32_x, int half_x, float sk) {
         const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(pa), __float_as_uint(pb), false, false);
         float v = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
         const int t = t_w0 + j + half_x;
@@ -220,7 +228,7 @@ __global__ __launch_bounds__(64 * NW, MINB) void score_kernel(ScoreArgs a)
         if (FP8) {
             // positive per-token scales commute with the ReLU gate: I = sq[t] sk[s] sum_j w_j ReLU(q8_j . k8)
             const float sq = (pair && half_x) ? sqr[(j + 1) % TPW] : sqr[j];
-            v *= sq * ksc[min(s, Lk_b - 1)];
+            v *= sq * sk;
         }
         if (lane_on && t < i_end && s < Lk_b && (int64_t)s <= q_pos0 + t) {
             const int64_t srow = (int64_t)blockIdx.z * a.Ri + (t - a.i0);
@@ -236,7 +244,11 @@ __global__ __launch_bounds__(64 * NW, MINB) void score_kernel(ScoreArgs a)
             if (it >= ntiles) break;                        // workgroup-uniform
             const int kt = kc0 + it * TILE;
             const int buf = it & 1;
-            if (it + PD < ntiles) tile_gload<RB, LPT, NT>(pre[ph], tile_ptr(kt + PD * TILE), Lk_b - (kt + PD * TILE), tid);
+            const float sk = FP8 ? pre_k[ph] : 1.f;
+            if (it + PD < ntiles) {
+                load_k(ph, it + PD);
+                tile_gload<RB, LPT, NT>(pre[ph], tile_ptr(kt + PD * TILE), Lk_b - (kt + PD * TILE), tid);
+            }
             const int sub = wave & 1;                       // this wave's subtile; tiles alternate between wave pairs
             const int s0 = kt + sub * 32;
             if (s0 < wave_vis && (it & 1) == (wave >> 1)) {
@@ -244,20 +256,25 @@ __global__ __launch_bounds__(64 * NW, MINB) void score_kernel(ScoreArgs a)
 #pragma unroll
                 for (int ks = 0; ks < KS; ++ks)
                     kb[ks] = F::load(&lds[buf][(sub * 32 + r32) * ROWB + (ks * 2 + half) * OPB]);
-                float s_acc = 0.f;
+                float ps[TPW];
 #pragma unroll
-                for (int ht = 0; ht < HT; ++ht) {
-                    f32x16 acc;
+                for (int j = 0; j < TPW; ++j) {
+                    ps[j] = 0.f;
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+                    for (int ht = 0; ht < HT; ++ht) {
+                        f32x16 acc;
 #pragma unroll
-                    for (int ks = 0; ks < KS; ++ks)
-                        acc = F::mma(qa[0][ht][ks], kb[ks], acc);
+                        for (int i = 0; i < 16; ++i) acc[i] = 0.f;
 #pragma unroll
-                    for (int i = 0; i < 16; ++i)
-                        s_acc = fmaf(relu(acc[i]), wr[0][ht][i], s_acc);
+                        for (int ks = 0; ks < KS; ++ks)
+                            acc = F::mma(qa[j][ht][ks], kb[ks], acc);
+#pragma unroll
+                        for (int i = 0; i < 16; ++i)
+                            ps[j] = fmaf(relu(acc[i]), wr[j][ht][i], ps[j]);
+                    }
                 }
-                emit(s_acc, s_acc, false, 0, s0, r32, half);
+#pragma unroll
+                for (int j = 0; j < TPW; j += 2) emit(ps[j], ps[j + 1 < TPW ? j + 1 : j], j + 1 < TPW, j, s0, r32, half, sk);
             }
             if (it + 1 < ntiles) tile_lstore<RB, LPT, ROWB, NT>(pre[(ph + 1) % PD], &lds[buf ^ 1][0], tid);
             __syncthreads();
@@ -438,7 +455,7 @@ __global__ __launch_bounds__(64 * NW, MINB) void score_kernel(ScoreArgs a)
 #pragma unroll
                 for (int j = 0; j < TPW; j += 2) {
                     const bool pair = j + 1 < TPW;
-                    emit(ps[j], pair ? ps[j + 1] : ps[j], pair, j, s0, r32_c, half_c);
+                    emit(ps[j], pair ? ps[j + 1] : ps[j], pair, j, s0, r32_c, half_c, FP8 ? ksc[min(s0 + r32_c, Lk_b - 1)] : 1.f);
                 }
             }
             stage(it, tid_c, std::false_type{});
@@ -752,7 +769,10 @@ hipError_t launch_score(const ScoreArgs &a_in, int dtype, int d_I, int Bc, hipSt
     // per CU and three key tiles in flight per workgroup.
     // Otherwise 3 tokens per wave (2 for 64 heads) and the matrix pipe is the limit.
     const bool few_rows = a.Ri <= 4;
-    const int BT = few_rows ? 1 : (a.H_I <= 32 ? 12 : 8);   // 4 waves x tokens per wave of the chosen form
+    const bool fp8 = dtype == IC_FP8_E4M3;
+    const bool pairs = few_rows && fp8 && a.Ri > 1;         // two tokens per read of the keys: 12 sequences of two rows before
+    // 30011 keys 39.3 -> 35.3 us (64 heads, top-k included), 32 of two before 20000 51.3 -> 41.8, 8 of three 33.0 -> 32.2
+    const int BT = few_rows ? (pairs ? 2 : 1) : (a.H_I <= 32 ? 12 : 8);   // 4 waves x tokens per wave of the chosen form
     a.n_qblocks = (a.Ri + BT - 1) / BT;
     const int i_last = min(a.i0 + a.Ri, a.Tq) - 1;
     int64_t max_vis = a.q_pos0 + i_last + 1;
@@ -760,21 +780,27 @@ hipError_t launch_score(const ScoreArgs &a_in, int dtype, int d_I, int Bc, hipSt
     if (a.pv.seq_lens) max_vis = a.Lk;          // ragged: the lengths live on the device, Lk is their bound
     if (max_vis == 0) return hipSuccess;
     // keys per workgroup (tiles of 64 keys): prefill wants enough workgroups to fill 256 CUs
-    // several times; the streaming variant wants exactly one resident round (3 per CU).
-    const int64_t want_wgs = few_rows ? 768 : 2048;
+    // several times; the streaming variant wants exactly one resident round (3 per CU, 2 with pairs of 64 heads: registers).
+    const int64_t want_wgs = few_rows ? (pairs && a.H_I > 32 ? 512 : 768) : 2048;
     int64_t kc = (max_vis * a.n_qblocks * Bc / want_wgs + 63) / 64 * 64;
+    if (few_rows) {                             // (a few workgroups more than a round take two)
+        const int64_t chunks = std::max<int64_t>(1, want_wgs / ((int64_t)a.n_qblocks * Bc));
+        kc = ((max_vis + chunks - 1) / chunks + 63) / 64 * 64;
+    }
     // At least 512 keys a workgroup, which pay for its q rows; fewer where that leaves CUs idle: a problem this small takes as long
     // as one workgroup, so its visible pairs are dealt out to one workgroup per CU.  Measured with 512 / with this rule, top-k
     // included: 512 x 512 (4 heads of 64) 20.5 / 14.6 us, 1024 x 1024 20.8 / 17.5, 64 rows before 5000 keys (32 heads of 128)
     // 28.9 / 21.2; where 512 keys already give a workgroup per CU, smaller ones lose: 300 rows before 5000 keys 30.9, with 256 keys 32.8.
     int64_t least = 512;
-    if (!few_rows) {
+    if (few_rows) {
+        least = std::min<int64_t>(512, std::max<int64_t>(128, (max_vis * a.n_qblocks * Bc / 256 + 127) / 128 * 128));
+        // (128: a subtile for each wave.  One row before 5000 keys, fp8, top-k included: 18.4 us with 512 at the least, 15.5 with this)
+    } else {
         const int64_t mean_vis = a.pv.seq_lens ? max_vis : std::max<int64_t>(1, std::min(max_vis, a.q_pos0 + a.i0 + (i_last - a.i0) / 2 + 1));
         least = std::min<int64_t>(512, std::max<int64_t>(64, (mean_vis * a.n_qblocks * Bc / 256 + 63) / 64 * 64));
     }
     kc = kc < least ? least : (kc > 8192 ? 8192 : kc);
     a.KC = (int)kc;
-    const bool fp8 = dtype == IC_FP8_E4M3;
     if (few_rows && !fp8 && d_I == 128)
         return a.H_I <= 32 ? launch_stream<1, 4, 4>(a, Bc, st) : launch_stream<2, 4, 4>(a, Bc, st);
     if (!fp8) {
@@ -787,9 +813,9 @@ hipError_t launch_score(const ScoreArgs &a_in, int dtype, int d_I, int Bc, hipSt
         }
     } else {
         if (a.H_I <= 32) {
-            if (d_I == 128) return few_rows ? launch_t<1, 128, 1, 4, 3, 3, true, true>(a, Bc, max_vis, st) : launch_t<1, 128, 3, 4, 1, 2, false, true>(a, Bc, max_vis, st);
+            if (d_I == 128) return pairs ? launch_t<1, 128, 2, 4, 3, 3, true, true>(a, Bc, max_vis, st) : few_rows ? launch_t<1, 128, 1, 4, 3, 3, true, true>(a, Bc, max_vis, st) : launch_t<1, 128, 3, 4, 1, 2, false, true>(a, Bc, max_vis, st);
         } else {
-            if (d_I == 128) return few_rows ? launch_t<2, 128, 1, 4, 3, 2, true, true>(a, Bc, max_vis, st) : launch_t<2, 128, 2, 4, 1, 2, false, true>(a, Bc, max_vis, st);
+            if (d_I == 128) return pairs ? launch_t<2, 128, 2, 4, 3, 2, true, true>(a, Bc, max_vis, st) : few_rows ? launch_t<2, 128, 1, 4, 3, 2, true, true>(a, Bc, max_vis, st) : launch_t<2, 128, 2, 4, 1, 2, false, true>(a, Bc, max_vis, st);
         }
     }
     return hipErrorInvalidValue;

@@ -82,3 +82,28 @@ def test_ragged_shares(B, T, L, H, page, low):
     assert bool((low >= s.topk(k, dim=-1).values[..., -1] - tol).all())
     full = (n_seen <= k)[..., None] & (torch.arange(k) < n_seen[..., None])       # whatever a token sees: all of it, in order
     assert torch.equal(idx[full], torch.arange(k).expand_as(idx)[full])
+
+
+@pytest.mark.parametrize("B,T,L,H,k", [
+    (1, 1, 100, 64, 20), (3, 2, 3001, 64, 200), (2, 3, 1090, 32, 100), (5, 4, 640, 40, 64), (2, 2, 65, 32, 30), (1, 1, 9000, 20, 512),
+    (40, 3, 700, 64, 128), (1, 2, 40000, 64, 1024), (7, 4, 2500, 20, 300),
+])
+def test_fp8_decode_rows(B, T, L, H, k):
+    # few rows per sequence, in pairs where there are several: odd counts, both head counts, one chunk to many, ragged tiles.  Whole
+    # numbers, and powers of two as weights and scales: every sum is below 2^24 and exact, so the scores are those of 64 bits
+    g = torch.Generator().manual_seed(B * T + L)
+    d = 128
+    q, kk = torch.randint(-3, 4, (B, T, H, d), generator=g).float(), torch.randint(-3, 4, (B, L, d), generator=g).float()
+    two = lambda *shape: 2.0 ** torch.randint(-1, 2, shape, generator=g)
+    w, qs, ks = two(B, T, H), two(B, T), two(B, L)
+    f8 = torch.float8_e4m3fn
+    idx, sel = ic.indexer_topk(q.to(f8).cuda(), kk.to(f8).cuda(), w.cuda(), k, L - T, qs.cuda(), ks.cuda(), want_scores=True)
+    idx, sel = idx.cpu().long(), sel.cpu().double()
+    s = torch.matmul(q.double().view(B, T * H, d), kk.double().transpose(1, 2).contiguous()).view(B, T, H, L)
+    s = (torch.relu(s) * w.double()[..., None]).sum(2) * qs.double()[..., None] * ks.double()[:, None, :]
+    s = s.masked_fill(torch.arange(L)[None, :] > torch.arange(T)[:, None] + L - T, -float("inf"))
+    valid = idx >= 0
+    assert torch.equal(valid.sum(-1), (torch.arange(T) + L - T + 1).clamp_max(k).expand(B, T))
+    at = s.gather(2, idx.clamp_min(0))
+    assert torch.equal(at[valid], sel[valid])
+    assert torch.equal(at.masked_fill(~valid, float("inf")).min(dim=-1).values, s.topk(k, dim=-1).values.masked_fill(~valid, float("inf")).min(dim=-1).values)
