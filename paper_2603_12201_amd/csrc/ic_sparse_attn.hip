@@ -2127,9 +2127,8 @@ hipError_t launch_attn(const AttnArgs &a, int d_qk, int d_v, hipStream_t st)
 {
     if ((int64_t)a.B * a.Tq <= 0) return hipSuccess;
     if (d_qk == 576 && d_v == 512) {
-        // the row-slab form: one workgroup per query, or per split of a query's selection when
-        // there are too few queries to fill the chip (decode); rows with the values elsewhere than
-        // in their first features take the small-tile form
+        // the stream form, or the row-slab form per split of a query's selection when there are too few queries to fill the
+        // chip (decode); rows with the values elsewhere than in their first features take the small-tile form
         if (a.v_off == 0) return launch_mla(a, st);
         return launch_t<576, 512, 576>(a, st);
     }
