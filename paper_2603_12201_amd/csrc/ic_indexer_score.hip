@@ -792,12 +792,23 @@ hipError_t launch_score(const ScoreArgs &a_in, int dtype, int d_I, int Bc, hipSt
     // included: 512 x 512 (4 heads of 64) 20.5 / 14.6 us, 1024 x 1024 20.8 / 17.5, 64 rows before 5000 keys (32 heads of 128)
     // 28.9 / 21.2; where 512 keys already give a workgroup per CU, smaller ones lose: 300 rows before 5000 keys 30.9, with 256 keys 32.8.
     int64_t least = 512;
+    const bool one_per_cu = !fp8 && d_I == 128 && a.H_I > 32;      // (registers: the 64-head form; two per CU otherwise)
     if (few_rows) {
         least = std::min<int64_t>(512, std::max<int64_t>(128, (max_vis * a.n_qblocks * Bc / 256 + 127) / 128 * 128));
         // (128: a subtile for each wave.  One row before 5000 keys, fp8, top-k included: 18.4 us with 512 at the least, 15.5 with this)
     } else {
         const int64_t mean_vis = a.pv.seq_lens ? max_vis : std::max<int64_t>(1, std::min(max_vis, a.q_pos0 + a.i0 + (i_last - a.i0) / 2 + 1));
         least = std::min<int64_t>(512, std::max<int64_t>(64, (mean_vis * a.n_qblocks * Bc / 256 + 63) / 64 * 64));
+        // A workgroup over one per CU is a second round where only one is resident: 1024 x 1024 of 64 heads 26.9 us with 512
+        // keys (192 workgroups), 31.7 with 256 (320)
+        for (; one_per_cu && least < 512; least += 64) {
+            int64_t n = 0;                      // workgroups that see keys: blocks behind the first key of each chunk
+            for (int64_t k0 = 0; k0 < max_vis && n <= 256; k0 += least) {
+                const int64_t hidden = a.pv.seq_lens ? 0 : std::max<int64_t>(0, k0 - a.q_pos0 - a.i0);   // rows that see none of it
+                n += (a.n_qblocks - std::min<int64_t>(a.n_qblocks, hidden / BT)) * Bc;
+            }
+            if (n <= 256) break;
+        }
     }
     kc = kc < least ? least : (kc > 8192 ? 8192 : kc);
     a.KC = (int)kc;

@@ -12,6 +12,7 @@ pytestmark = pytest.mark.gpu
     (1, 5, 70, 4, 64, 8, False), (1, 64, 64, 4, 64, 16, False), (1, 200, 200, 4, 64, 64, False), (2, 513, 513, 32, 64, 64, False),
     (1, 1025, 1025, 4, 64, 64, False), (1, 33, 3001, 32, 128, 300, False), (1, 65, 5000, 32, 128, 256, False),
     (2, 31, 1500, 20, 128, 100, False), (1, 40, 2000, 64, 128, 128, True), (1, 300, 700, 32, 128, 96, True), (1, 17, 900, 40, 128, 64, False),
+    (1, 600, 600, 64, 128, 64, False), (2, 700, 700, 64, 128, 64, False), (1, 1100, 1100, 64, 128, 64, False), (1, 9, 3000, 64, 128, 64, False),
 ])
 def test_chunks(B, T, L, H, d, k, fp8):
     g = torch.Generator().manual_seed(T + L)
