@@ -484,9 +484,11 @@ __global__ void fill_kernel(float *p, int64_t n, float v)
 // Order.  Reading the cache as a few wide windows that slide is faster than many narrow streams (measured: 32
 // concurrent per-token windows 100 us, 8 windows 90 us, one window 87 us for 537 MB).  So there are G windows, each with
 // the workgroups of one residue mod G (for G = 16 two per XCD: workgroup ids are dealt round-robin over the eight
-// XCDs), all waves of which interleave slot by slot.  A window takes an even share of the slots of all tokens, not
-// whole tokens: 40 sequences of 700 to 49152 keys are two or three tokens a window, some of them short, and windows that
-// are through leave CUs without loads in flight.  (Decode step of four layers on those: 189 us with whole tokens, 173 with shares.)
+// XCDs), all waves of which interleave slot by slot.  Where tokens are of one length and as many for every window, a
+// window takes whole tokens; otherwise an even share of the slots of all tokens: 40 sequences of 700 to 49152 keys are two or
+// three tokens a window, some of them short, and windows that are through leave CUs without loads in flight.  (Decode step
+// of four layers on those: 189 us with whole tokens, 173 with shares.)  A share ends within a token, whose q rows then travel
+// once more for every wave: 3 tokens of 40000 keys, top-k included, 24.8 us with two shares and 22.7 with a window each.
 // ---------------------------------------------------------------------------------------------------------
 __device__ __forceinline__ void dma_lanes(const void *lane_addr, unsigned lds_addr /*uniform*/)
 {
@@ -496,8 +498,15 @@ template <int N> __device__ __forceinline__ void wait_vm_le()
 {
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
+struct StreamWindows {
+    int T, G;               // tokens, windows
+    int n_col;              // tokens a window, rounded up
+    int whole;              // windows take whole tokens; otherwise even shares, or whole tokens if the lengths are found to allow it
+    unsigned stride;        // waves that share a window
+    unsigned inv_g, inv_col, inv_ri;         // 2^32 / G, / n_col, / Ri, the last two rounded up (0: divide)
+};
 template <int HT, int NW, int R, bool PG>
-__global__ __launch_bounds__(64 * NW, 1) void score_stream_kernel(ScoreArgs a, int T, int lg)       // T tokens, 2^lg windows
+__global__ __launch_bounds__(64 * NW, 1) void score_stream_kernel(ScoreArgs a, StreamWindows sw)    // grid (G, workgroups of a window)
 {
     constexpr int RB = 256;                     // bytes per key row (and per q row)
     constexpr int SUB = 32;                     // rows per slot
@@ -508,20 +517,25 @@ __global__ __launch_bounds__(64 * NW, 1) void score_stream_kernel(ScoreArgs a, i
     extern __shared__ __attribute__((aligned(1024))) unsigned char ring[];   // [NW][R][SLOT]
 
     // (requested together: left alone each is loaded where it is first used, one memory latency after another)
-    asm volatile("" ::"s"(a.q), "s"(a.k), "s"(a.w), "s"(a.strip), "s"(a.ld), "s"(a.q_pos0), "s"(a.Tq), "s"(a.Lk), "s"(a.H_I), "s"(a.b0), "s"(a.i0), "s"(a.Ri), "s"(T), "s"(lg));
+    asm volatile("" ::"s"(a.q), "s"(a.k), "s"(a.w), "s"(a.strip), "s"(a.ld), "s"(a.q_pos0), "s"(a.Tq), "s"(a.Lk), "s"(a.H_I), "s"(a.b0), "s"(a.i0), "s"(a.Ri), "s"(sw.T), "s"(sw.G), "s"(sw.n_col), "s"(sw.whole), "s"(sw.stride), "s"(sw.inv_g), "s"(sw.inv_col), "s"(sw.inv_ri));
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r32 = lane & 31, half = lane >> 5;
-    const int G = 1 << lg, wdw = (int)blockIdx.x & (G - 1); // this workgroup's window
-    const unsigned wstride = NW * (gridDim.x >> lg);        // waves that share it
-    const unsigned wfirst = (blockIdx.x >> lg) * NW + wave;   // this wave's slots of the window: wfirst, wfirst + wstride, ...
+    const int T = sw.T, G = sw.G, n_col = sw.n_col, wdw = (int)blockIdx.x;  // this workgroup's window
+    const unsigned wstride = sw.stride;
+    const unsigned wfirst = blockIdx.y * NW + wave;         // this wave's slots of the window: wfirst, wfirst + wstride, ...
     const bool ragged = PG && a.pv.seq_lens, paged = PG && a.pv.page_table;
     const int i_end = min(a.i0 + a.Ri, a.Tq);
     // Order of the tokens: 0, G, 2 G, .., 1, G + 1, ..: windows over equal tokens then slide through neighbouring ones together (32
     // tokens of 65536 keys, decode step of four layers: 184 us, 189 in ascending order).  Places that hold no token have no slots.
-    const int n_col = (T + G - 1) >> lg, n_place = n_col * G;
-    auto token = [&](int place) -> int { return n_col == 1 ? place : place % n_col * G + place / n_col; };
-    auto seq_of = [&](int tk) -> int { return a.Ri == 1 ? tk : tk / a.Ri; };     // (a division is 0.1 us in front of everything)
+    const int n_place = n_col * G;
+    // (a division is 0.1 us in front of everything: products with rounded-up reciprocals are exact here, see launch_stream)
+    auto token = [&](int place) -> int {
+        if (n_col == 1) return place;
+        const int row = sw.inv_col ? (int)__umulhi((unsigned)place, sw.inv_col) : place / n_col;
+        return (place - row * n_col) * G + row;
+    };
+    auto seq_of = [&](int tk) -> int { return a.Ri == 1 ? tk : (int)__umulhi((unsigned)tk, sw.inv_ri); };
 
     // keys that query row t sees, of a sequence that holds Lk_b
     auto visible = [&](int t, int Lk_b) -> int {
@@ -532,17 +546,25 @@ __global__ __launch_bounds__(64 * NW, 1) void score_stream_kernel(ScoreArgs a, i
     // Two cursors run over the same sequence: the one that issues loads stays R - 1 items ahead of the one that
     // computes.
     struct Cur {
-        int at, jj;                             // place of the token, item
+        int at, tk, jj;                         // place of the token, token, item
         unsigned sub, nsub, left;               // slot within the token, the token's slots, slots left to the wave
         int bz, t, Lk_b, vis;                   // sequence within the launch, query row, visible keys
     };
+    int len_l[2] = {a.Lk, a.Lk};                // ragged: keys of the sequences at places lane and 64 + lane
+    auto step = [&](Cur &c) {
+        ++c.at;
+        c.tk += G;
+        if (c.tk >= n_place) c.tk -= n_place - 1;
+    };
     auto enter = [&](Cur &c) {                  // slot c.sub counted from place c.at on: its token
-        for (; c.at < n_place; ++c.at) {
-            const int tk = token(c.at);
-            if (tk >= T) continue;
-            c.bz = seq_of(tk);
-            c.t = a.i0 + (tk - c.bz * a.Ri);
-            c.Lk_b = ragged ? max(0, min(load_uniform(a.pv.seq_lens + a.b0 + c.bz), a.Lk)) : a.Lk;
+        for (; c.at < n_place; step(c)) {
+            if (c.tk >= T) continue;
+            c.bz = seq_of(c.tk);
+            c.t = a.i0 + (c.tk - c.bz * a.Ri);
+            c.Lk_b = a.Lk;
+            if (ragged)
+                c.Lk_b = n_place <= 128 ? __builtin_amdgcn_readlane(c.at < 64 ? len_l[0] : len_l[1], c.at & 63)
+                                        : max(0, min(load_uniform(a.pv.seq_lens + a.b0 + c.bz), a.Lk));
             c.vis = visible(c.t, c.Lk_b);
             c.nsub = (unsigned)(c.vis + SUB - 1) / SUB;
             if (c.sub < c.nsub) {
@@ -564,7 +586,7 @@ __global__ __launch_bounds__(64 * NW, 1) void score_stream_kernel(ScoreArgs a, i
         c.sub += wstride;
         if (c.sub >= c.nsub) {
             c.sub -= c.nsub;
-            ++c.at;
+            step(c);
             enter(c);
         }
     };
@@ -599,36 +621,78 @@ __global__ __launch_bounds__(64 * NW, 1) void score_stream_kernel(ScoreArgs a, i
         }
     };
 
-    // The slots of all tokens, one after the other, are shared out to the windows evenly (a score strip of less than 512 GB
-    // has fewer than 2^32).  Slots up to and with place p0 + lane, counted from place p0:
-    auto slots = [&](int p0) -> unsigned {
-        const int tk = token(p0 + lane), bz = seq_of(tk);
-        unsigned n = 0;
-        if (p0 + lane < n_place && tk < T) n = (unsigned)(visible(a.i0 + (tk - bz * a.Ri), ragged ? max(0, min(a.pv.seq_lens[a.b0 + bz], a.Lk)) : a.Lk) + SUB - 1) / SUB;
-        return wave_incl_scan(n);
-    };
+    // Slots of token tk whose sequence holds Lk_b keys.  (Those of a launch: a score strip of less than 512 GB has fewer than 2^32.)
+    auto slots = [&](int tk, int Lk_b) -> unsigned { return (unsigned)(visible(a.i0 + (tk - seq_of(tk) * a.Ri), Lk_b) + SUB - 1) / SUB; };
     auto lane_of = [&](unsigned v, int l) -> unsigned { return (unsigned)__builtin_amdgcn_readlane((int)v, l); };
     Cur pc, cc;                                 // producer, consumer
-    unsigned share;                             // slots of the window
-    if (!ragged && a.Ri == 1 && T == n_place) { // as many tokens of one length in every window: nothing to look for
-        share = (unsigned)n_col * ((unsigned)(visible(a.i0, a.Lk) + SUB - 1) / SUB);
-        pc.at = wdw * n_col;
-        pc.sub = wfirst;
-    } else {
-        unsigned upto = slots(0), total = lane_of(upto, 63);
-        for (int p0 = 64; p0 < n_place; p0 += 64) total += lane_of(slots(p0), 63);
-        const unsigned lo = (unsigned)((uint64_t)total * (unsigned)wdw >> lg);
-        share = (unsigned)((uint64_t)total * (unsigned)(wdw + 1) >> lg) - lo;
-        if (wfirst >= share) return;
-        pc.at = 0;
-        pc.sub = lo + wfirst;
-        for (; pc.sub >= lane_of(upto, 63); upto = slots(pc.at)) {
-            pc.sub -= lane_of(upto, 63);
-            pc.at += 64;
+    unsigned share = 0;                         // slots of the window
+    pc.at = wdw * n_col;
+    pc.tk = wdw;
+    pc.sub = wfirst;
+    if (T == 1) {
+        if (ragged) len_l[0] = max(0, min(load_uniform(a.pv.seq_lens + a.b0), a.Lk));
+        share = slots(0, __builtin_amdgcn_readfirstlane(len_l[0]));
+    } else if (sw.whole && a.Ri == 1) {         // tokens of one length: wdw, wdw + G, ..
+        share = (unsigned)(wdw + (n_col - 1) * G < T ? n_col : n_col - 1) * slots(wdw, a.Lk);
+    } else if (sw.whole) {
+        for (int c0 = 0; c0 < n_col; c0 += 64) {
+            const int tk = wdw + (c0 + lane) * G;
+            share += lane_of(wave_incl_scan(c0 + lane < n_col && tk < T ? slots(tk, a.Lk) : 0u), 63);
         }
-        const int behind = __popcll(__ballot(upto <= pc.sub));  // places of the 64 that end in front of the slot
-        if (behind) pc.sub -= lane_of(upto, behind - 1);
-        pc.at += behind;
+    } else {                                    // the slots of all tokens, one after the other, in even shares
+        auto keys = [&](int p0) -> int {        // of the sequence at place p0 + lane
+            const int tk = token(p0 + lane);
+            return !ragged ? a.Lk : (p0 + lane < n_place && tk < T ? max(0, min(a.pv.seq_lens[a.b0 + seq_of(tk)], a.Lk)) : 0);
+        };
+        auto n_at = [&](int p0, int Lk_b) -> unsigned {
+            const int tk = token(p0 + lane);
+            return p0 + lane < n_place && tk < T ? slots(tk, Lk_b) : 0u;
+        };
+        // (requested together, and kept: a cursor that enters a token then waits for nothing)
+        len_l[0] = keys(0);
+        if (n_place > 64) len_l[1] = keys(64);
+        // slots up to and with places lane, 64 + lane
+        const unsigned n0 = n_at(0, len_l[0]), upto0 = wave_incl_scan(n0), upto1 = n_place > 64 ? wave_incl_scan(n_at(64, len_l[1])) : 0u;
+        unsigned total = lane_of(upto0, 63) + lane_of(upto1, 63);
+        for (int p0 = 128; p0 < n_place; p0 += 64) total += lane_of(wave_incl_scan(n_at(p0, keys(p0))), 63);
+        // A share ends within a token, whose q rows then travel once more for every wave and keep it as long as some three slots do
+        // (their weights are loaded in front of the first product).  So whole tokens unless that leaves the longest window's waves
+        // more behind.  Top-k included, in shares and whole: 16 sequences of 60000 to 65536 keys 59.4 and 57.5 us, 12 of 100 to
+        // 32768 (64 heads) 29.6 and 25.4; 40 of 700 to 49152 54.7 and 61.3.
+        const uint64_t most = (uint64_t)total + 3u * HT * wstride * (unsigned)G;     // G times the slots of a window
+        if (n_col == 1 && __ballot((uint64_t)n0 * (unsigned)G > most) == 0ull) {
+            share = lane_of(n0, wdw);
+        } else {
+            // (shares need not be exact, only the last one's end)
+            auto bound = [&](int w) -> unsigned { return w == G ? total : (unsigned)((uint64_t)total * (unsigned)w * sw.inv_g >> 32); };
+            unsigned lo = bound(wdw);
+            share = bound(wdw + 1) - lo;
+            if (n_col > 1 && n_place <= 128) {
+                auto at_place = [&](int p) -> unsigned {
+                    const unsigned x = (unsigned)__shfl((int)upto0, p & 63), y = (unsigned)__shfl((int)upto1, p & 63);
+                    return p < 64 ? x : lane_of(upto0, 63) + y;
+                };
+                const int w = min(lane, G - 1);
+                const unsigned end = at_place((w + 1) * n_col - 1), before = at_place(max(w * n_col - 1, 0)), begin = w == 0 ? 0u : before;
+                if (__ballot((uint64_t)(end - begin) * (unsigned)G > most) == 0ull) {
+                    lo = lane_of(begin, wdw);
+                    share = lane_of(end, wdw) - lo;
+                }
+            }
+            if (wfirst >= share) return;
+            pc.at = 0;
+            pc.sub = lo + wfirst;
+            unsigned upto = upto0;
+            while (pc.sub >= lane_of(upto, 63)) {
+                pc.sub -= lane_of(upto, 63);
+                pc.at += 64;
+                upto = pc.at == 64 ? upto1 : wave_incl_scan(n_at(pc.at, keys(pc.at)));
+            }
+            const int behind = __popcll(__ballot(upto <= pc.sub));  // places of the 64 that end in front of the slot
+            if (behind) pc.sub -= lane_of(upto, behind - 1);
+            pc.at += behind;
+            pc.tk = token(pc.at);
+        }
     }
     if (wfirst >= share) return;                // nothing for this wave (no barrier in this kernel)
     pc.left = (share - wfirst + wstride - 1) / wstride;
@@ -707,8 +771,8 @@ __global__ __launch_bounds__(64 * NW, 1) void score_stream_kernel(ScoreArgs a, i
         // the reads of this slot have returned (the MFMAs consumed them) before the next iteration's loads
         // overwrite it; the statement below keeps the compiler from moving them
         asm volatile("" ::: "memory");
-        const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(s_acc), __float_as_uint(s_acc), false, false);
-        const float v = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
+        const auto both = __builtin_amdgcn_permlane32_swap(__float_as_uint(s_acc), __float_as_uint(s_acc), false, false);
+        const float v = __uint_as_float(both[0]) + __uint_as_float(both[1]);
         const int s = (int)cc.sub * SUB + r32;
         if (half == 0 && s < cc.vis) a.strip[((int64_t)cc.bz * a.Ri + (cc.t - a.i0)) * a.ld + s] = v;
         next(cc);
@@ -720,10 +784,22 @@ hipError_t launch_stream(const ScoreArgs &a, int Bc, hipStream_t st)
 {
     const int T = Bc * a.Ri;                    // tokens of the launch
     if (T <= 0) return hipSuccess;
-    // windows (measured at 32 tokens of 65536 keys: 2 -> 99.2, 4 -> 97.7, 8 -> 98.4, 16 -> 97.1, 32 -> 102.1 us); no more than
-    // tokens, and a power of two, so that they share one workgroup per CU (the ring takes most of a CU's LDS)
-    const int lg = T < 2 ? 0 : (T < 4 ? 1 : (T < 8 ? 2 : (T < 16 ? 3 : 4)));
-    const int W = 256;
+    // Windows (measured at 32 tokens of 65536 keys: 2 -> 99.2, 4 -> 97.7, 8 -> 98.4, 16 -> 97.1, 32 -> 102.1 us), no more than
+    // tokens, that share one workgroup per CU (the ring takes most of a CU's LDS).  Of whole tokens where all are of one length
+    // and at most one in 50 places is empty.
+    StreamWindows sw;
+    sw.T = T;
+    sw.G = std::min(T, 16);
+    sw.n_col = (T + sw.G - 1) / sw.G;
+    const int64_t places = (int64_t)sw.n_col * sw.G;
+    sw.whole = !a.pv.seq_lens && places * 50 <= (int64_t)T * 51;
+    const dim3 grid((unsigned)sw.G, (unsigned)(256 / sw.G));
+    sw.stride = NW * grid.y;
+    // x * ceil(2^32 / d) >> 32 is x / d as long as x * (d - 1) < 2^32
+    auto up = [](int d, int64_t x) { return d > 1 && x * (d - 1) < (int64_t)1 << 32 ? (unsigned)((((uint64_t)1 << 32) + d - 1) / d) : 0u; };
+    sw.inv_g = (unsigned)std::min<uint64_t>(((uint64_t)1 << 32) / sw.G, UINT32_MAX);
+    sw.inv_col = up(sw.n_col, places + 64);
+    sw.inv_ri = up(a.Ri, 1);                    // (d <= 4 and x < 2^30: few rows)
     constexpr int lds = NW * R * 32 * 256;
     static hipError_t attr = hipFuncSetAttribute((const void *)score_stream_kernel<HT, NW, R, false>,
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, lds);
@@ -732,9 +808,9 @@ hipError_t launch_stream(const ScoreArgs &a, int Bc, hipStream_t st)
     if (attr != hipSuccess) return attr;
     if (attr_pg != hipSuccess) return attr_pg;
     if (a.pv.seq_lens || a.pv.page_table)
-        hipLaunchKernelGGL((score_stream_kernel<HT, NW, R, true>), dim3(W), dim3(64 * NW), lds, st, a, T, lg);
+        hipLaunchKernelGGL((score_stream_kernel<HT, NW, R, true>), grid, dim3(64 * NW), lds, st, a, sw);
     else
-        hipLaunchKernelGGL((score_stream_kernel<HT, NW, R, false>), dim3(W), dim3(64 * NW), lds, st, a, T, lg);
+        hipLaunchKernelGGL((score_stream_kernel<HT, NW, R, false>), grid, dim3(64 * NW), lds, st, a, sw);
     return hipGetLastError();
 }
 

@@ -1,5 +1,7 @@
 """Indexer scores of problems too small for a workgroup per 512 keys (their keys are dealt out in chunks of 64 up to 512), against
 64-bit scores: around the sizes where the chunk changes, ragged ends, both dtypes, rows whose first positions see nothing."""
+import ctypes
+
 import pytest
 import torch
 
@@ -46,6 +48,11 @@ def test_chunks(B, T, L, H, d, k, fp8):
 @pytest.mark.parametrize("B,T,L,H,page,low", [
     (1, 1, 40, 32, 0, 40), (2, 1, 6000, 32, 64, 0), (3, 2, 2100, 20, 64, 1), (5, 4, 900, 64, 0, 0), (17, 1, 3000, 32, 128, 1), (40, 1, 4096, 32, 64, 30),
     (65, 1, 257, 32, 0, 0), (70, 2, 128, 40, 64, 0), (130, 1, 320, 32, 64, 0), (33, 1, 2050, 32, 0, 2050),
+    # lengths that allow windows of whole sequences (one, two to eight a window, the last ones fewer) and lengths that do not; more
+    # places than lanes and than two waves' worth of them
+    (2, 1, 20000, 64, 0, 19000), (2, 1, 20000, 32, 64, 0), (15, 1, 3000, 40, 0, 2900), (16, 1, 9000, 32, 64, 8900), (12, 1, 9000, 64, 0, 0),
+    (40, 1, 1500, 64, 64, 1450), (30, 3, 700, 32, 0, 690), (64, 2, 600, 64, 64, 590), (100, 1, 900, 32, 0, 880), (43, 3, 300, 32, 64, 290),
+    (300, 2, 96, 32, 0, 0),
 ])
 def test_ragged_shares(B, T, L, H, page, low):
     # decode rows whose slots of 32 keys are shared out to windows and waves across sequences: empty and one-key sequences, more
@@ -108,3 +115,58 @@ def test_fp8_decode_rows(B, T, L, H, k):
     at = s.gather(2, idx.clamp_min(0))
     assert torch.equal(at[valid], sel[valid])
     assert torch.equal(at.masked_fill(~valid, float("inf")).min(dim=-1).values, s.topk(k, dim=-1).values.masked_fill(~valid, float("inf")).min(dim=-1).values)
+
+
+@pytest.mark.parametrize("B,T,L,H,k", [
+    (1, 1, 9000, 64, 500), (1, 3, 9000, 64, 500), (2, 4, 6000, 32, 300), (13, 1, 3000, 32, 200), (15, 3, 2000, 64, 150), (16, 2, 2000, 20, 150),
+    (17, 1, 2500, 64, 200), (33, 4, 500, 32, 64), (85, 3, 200, 40, 32), (200, 4, 150, 32, 20),
+])
+def test_windows_of_whole_tokens(B, T, L, H, k):
+    # decode rows of one length: as many whole tokens for every window (fewer than 16, 16 and several times that) or shares of them
+    # all.  Whole numbers and powers of two as above: the scores are those of 64 bits
+    g = torch.Generator().manual_seed(B * T + L)
+    d = 128
+    q, kk = torch.randint(-3, 4, (B, T, H, d), generator=g).float(), torch.randint(-3, 4, (B, L, d), generator=g).float()
+    w = 2.0 ** torch.randint(-1, 2, (B, T, H), generator=g)
+    idx, sel = ic.indexer_topk(q.to(torch.bfloat16).cuda(), kk.to(torch.bfloat16).cuda(), w.cuda(), k, L - T, want_scores=True)
+    idx, sel = idx.cpu().long(), sel.cpu().double()
+    s = torch.matmul(q.double().view(B, T * H, d), kk.double().transpose(1, 2).contiguous()).view(B, T, H, L)
+    s = (torch.relu(s) * w.double()[..., None]).sum(2)
+    s = s.masked_fill(torch.arange(L)[None, :] > torch.arange(T)[:, None] + L - T, -float("inf"))
+    assert bool((idx >= 0).all())
+    at = s.gather(2, idx)
+    assert torch.equal(at, sel)
+    assert torch.equal(at.min(dim=-1).values, s.topk(k, dim=-1).values[..., -1])
+
+
+@pytest.mark.parametrize("T", [1, 2, 3, 4])
+@pytest.mark.parametrize("H", [32, 64])
+def test_fp8_ragged_rows(T, H):
+    # fp8 rows of ragged sequences (no page table): empty ones, fewer keys than rows, ends off a tile, the full length.  Exact as above
+    lens = torch.tensor([0, 1, max(T - 1, 0), T, 63, 64, 65, 130, 700, 1001, 2048], dtype=torch.int32)
+    B, L, d, k = len(lens), 2048, 128, 100
+    g = torch.Generator().manual_seed(T * H)
+    q, kk = torch.randint(-3, 4, (B, T, H, d), generator=g).float(), torch.randint(-3, 4, (B, L, d), generator=g).float()
+    two = lambda *shape: 2.0 ** torch.randint(-1, 2, shape, generator=g)
+    w, qs, ks = two(B, T, H), two(B, T), two(B, L)
+    f8 = torch.float8_e4m3fn
+    qd, kd, wd, qsd, ksd, ld = q.to(f8).cuda(), kk.to(f8).cuda(), w.cuda(), qs.cuda(), ks.cuda(), lens.cuda()
+    desc = ic.IndexerDesc(B, T, L, H, d, k, 0, 1, 0, qsd.data_ptr(), ksd.data_ptr())
+    pc = ic.paged_cache(ld)
+    ws = torch.empty(ic.indexer_topk_workspace(desc), dtype=torch.uint8, device="cuda")
+    idx = torch.empty((B, T, k), dtype=torch.int32, device="cuda")
+    sel = torch.empty((B, T, k), dtype=torch.float32, device="cuda")
+    p = lambda t: ctypes.c_void_p(t.data_ptr())
+    assert ic.lib().ic_indexer_topk_paged(ctypes.byref(desc), ctypes.byref(pc), p(qd), p(kd), p(wd), p(idx), p(sel), p(ws), ws.numel(),
+                                          ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)) == 0
+    idx, sel = idx.cpu().long(), sel.cpu().double()
+    s = torch.matmul(q.double().view(B, T * H, d), kk.double().transpose(1, 2).contiguous()).view(B, T, H, L)
+    s = (torch.relu(s) * w.double()[..., None]).sum(2) * qs.double()[..., None] * ks.double()[:, None, :]
+    n_seen = (lens[:, None].long() - T + 1 + torch.arange(T)[None, :]).clamp_min(0)
+    s = s.masked_fill(torch.arange(L) >= n_seen[..., None], -float("inf"))
+    valid = idx >= 0
+    assert torch.equal(valid.sum(-1), n_seen.clamp_max(k))
+    at = s.gather(2, idx.clamp_min(0))
+    assert torch.equal(at[valid], sel[valid])
+    low = at.masked_fill(~valid, float("inf")).min(dim=-1).values
+    assert torch.equal(low, s.topk(k, dim=-1).values.masked_fill(~valid, float("inf")).min(dim=-1).values)
