@@ -1548,7 +1548,7 @@ __global__ __launch_bounds__(512, 2) void attn_stream_kernel(AttnArgs a, RestArg
         pl.idx = a.idx + row * a.k_sel;
         pl.q = (const unsigned short *)(MULTI ? a.Qs[layer] : a.Q) + row * a.H_q * D_QK;
         pl.kv = (const unsigned short *)(MULTI ? a.KVs[layer] : a.KV) + (PG && a.pv.page_table ? 0 : (int64_t)pl.b * a.Lk * a.row_elems);
-        pl.len = PG && a.pv.seq_lens ? min(load_uniform(a.pv.seq_lens + pl.b), a.Lk) : a.Lk;
+        pl.len = PG && a.pv.seq_lens ? max(0, min(load_uniform(a.pv.seq_lens + pl.b), a.Lk)) : a.Lk;     // (ids are compared unsigned)
         pl.ng = granules(i);
     };
     pl.n = 0;

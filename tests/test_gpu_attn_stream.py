@@ -177,3 +177,21 @@ def test_prefix_rows_in_chains(B, T, H, broken):
         ref_lse.append(torch.logsumexp(s, dim=-1))
         ref_O.append(torch.einsum("ths,sd->thd", torch.softmax(s, dim=-1), kv[:, :D_V]))
     _check(O, lse, torch.stack(ref_O), torch.stack(ref_lse))
+
+
+@pytest.mark.parametrize("page", [0, 64])
+def test_negative_length_holds_nothing(page):
+    # a length below zero is that of an empty sequence: no id of it counts, and nothing is read behind it
+    B, H, k, L = 300, 8, 40, 128
+    Q, KV, idx = _case(B, 1, L, H, k, seed=13, holes=False)
+    lens = torch.full((B,), L, dtype=torch.int32)
+    lens[::3] = -5
+    lens[1::3] = 60
+    lens[6] = -2 ** 31
+    seen = idx.clone()
+    seen[idx >= lens[:, None, None]] = -1
+    table = torch.arange(B * (L // 64), dtype=torch.int32).view(B, L // 64).cuda() if page else None
+    pc = ic.paged_cache(lens.cuda(), table, page)
+    O, lse = ic.sparse_attn_paged(Q.cuda(), (KV.view(B * L, D_QK) if page else KV).cuda(), idx.cuda(), L, D_V, 0, SCALE, pc, want_lse=True)
+    _check(O, lse, *_reference(Q, KV, seen))
+    assert bool((O[::3] == 0).all())
