@@ -1465,7 +1465,7 @@ __global__ __launch_bounds__(512, 2) void attn_stream_kernel(AttnArgs a, RestArg
 #pragma unroll
                         for (int r = 0; r < 2; ++r) {
                             const float e = fast_exp2(__builtin_fmaf(s4[r][i], a.scale_log2e, -lse2[r]));
-                            sum += (rows >> (4 * g + i) & 1u) && lse2[r] != INFINITY ? e : 0.f;
+                            sum += (rows >> (4 * g + i) & 1u) && 16 * r + l16 < a.H_q ? e : 0.f;
                         }
                         p[i] = row16_sum(sum);            // lane 15 of the 16: the sum over the heads
                     }

@@ -195,3 +195,25 @@ def test_negative_length_holds_nothing(page):
     O, lse = ic.sparse_attn_paged(Q.cuda(), (KV.view(B * L, D_QK) if page else KV).cuda(), idx.cuda(), L, D_V, 0, SCALE, pc, want_lse=True)
     _check(O, lse, *_reference(Q, KV, seen))
     assert bool((O[::3] == 0).all())
+
+
+@pytest.mark.parametrize("H", [5, 16, 32])
+def test_probs_of_infinite_lse(H):
+    # exp(s - inf) is 0 for a finite score and NaN for an infinite one, for every head there is
+    Q, KV, idx = _case(1, 6, 100, H, 50, seed=H, holes=False)
+    Q[..., 0] = 1.0
+    KV[0, 7, 0] = float("inf")
+    KV[0, 8, 0] = -float("inf")
+    lse = torch.zeros((1, 6, H), dtype=torch.float32)
+    lse[:, 1] = float("inf")
+    lse[:, 2, H - 1] = float("inf")
+    lse[:, 3, 0] = -float("inf")
+    lse[:, 4, 0] = float("nan")
+    lse[:, 5] = 10.0
+    got = ic.attn_probs(Q.cuda(), KV.cuda(), idx.cuda(), SCALE, lse.cuda()).double().cpu()
+    s = torch.matmul(Q[0].double(), KV[0].double()[idx[0].long()].transpose(1, 2).contiguous()) * SCALE
+    p = torch.exp(s - lse[0].double()[..., None]).mean(dim=1)
+    assert torch.equal(torch.isnan(got[0]), torch.isnan(p)) and torch.equal(torch.isinf(got[0]), torch.isinf(p))
+    fin = torch.isfinite(p)
+    # scores to 1e-6 (see above), so probabilities to 1e-6 of themselves, ten times that
+    assert ((got[0] - p)[fin].abs() <= 1e-5 * p[fin].abs() + 1e-30).all()
