@@ -3,7 +3,7 @@
 //
 // MLA rows whose values are their first features (576 / 512) take one of three forms further down: the stream form, one
 // workgroup per CU that walks a chain of queries; the row-slab form, one (query, split) per workgroup where there are fewer
-// queries than CUs (decode); the dense form where a row selects all it sees.  Every other supported layout takes the
+// queries than CUs (decode) and one query where their selections are short; the dense form where a row selects all it sees.  Every other supported layout takes the
 // small-tile form described here.
 //
 // Small-tile form: one workgroup (4 waves) per query token and key-slot split; two workgroups
@@ -324,9 +324,9 @@ __device__ __forceinline__ unsigned rows_mask(unsigned long long ba, unsigned lo
     return lo | (hi << 8);
 }
 
-// blockIdx.x: query of the launch, flattened (layer, b, t); blockIdx.y selects a.split_len of its key slots.  The result is a
-// partial for the merge kernel.
-template <int D_QK, int D_V, bool PG>   // value columns = the first D_V features of a row; PG as above
+// blockIdx.x: query of the launch, flattened (layer, b, t).  SPLIT: blockIdx.y selects a.split_len of its key slots and the result
+// is a partial for the merge kernel; otherwise all of them, and O and lse.
+template <int D_QK, int D_V, bool PG, bool SPLIT>   // value columns = the first D_V features of a row; PG as above
 __global__ __launch_bounds__(256, 1) void attn_slab_kernel(AttnArgs a)
 {
     constexpr int KS = D_QK / 32;                         // contraction steps of S^T = 16-byte chunks per gather lane
@@ -361,6 +361,7 @@ __global__ __launch_bounds__(256, 1) void attn_slab_kernel(AttnArgs a)
     qrow += (int64_t)b * a.row_gap;
     const void *const q_l = a.Qs[layer], *const kv_l = a.KVs[layer];
     asm volatile("" ::"s"(q_l), "s"(kv_l));
+    void *const o_l = SPLIT ? nullptr : a.Os[layer];
     const int32_t *idx_row = a.idx + qrow * a.k_sel;
     const unsigned short *kv = (const unsigned short *)kv_l + (PG && a.pv.page_table ? 0 : (int64_t)b * a.Lk * a.row_elems);
     const int len = PG && a.pv.seq_lens ? min(a.pv.seq_lens[b], a.Lk) : a.Lk;   // ragged cache: rows of this sequence
@@ -709,12 +710,17 @@ __global__ __launch_bounds__(256, 1) void attn_slab_kernel(AttnArgs a)
         const float l_head = lbuf[l32] + lbuf[32 + l32] + lbuf[64 + l32] + lbuf[96 + l32];   // head l32
         const float m_head = m_c;
         {
-            // partial of this split: its reference maximum and row sum (the output below is
-            // normalised by that sum; the merge weighs the splits by their share of the total)
-            if (wave == 0 && hh == 0 && l32 < a.H_q) {
-                float *ml = a.part_ml + ((gq * a.n_splits + sp) * a.H_q + l32) * 2;
-                ml[0] = m_head;
-                ml[1] = l_head;
+            if constexpr (SPLIT) {
+                // partial of this split: its reference maximum and row sum (the output below is
+                // normalised by that sum; the merge weighs the splits by their share of the total)
+                if (wave == 0 && hh == 0 && l32 < a.H_q) {
+                    float *ml = a.part_ml + ((gq * a.n_splits + sp) * a.H_q + l32) * 2;
+                    ml[0] = m_head;
+                    ml[1] = l_head;
+                }
+            } else {
+                if (wave == 0 && hh == 0 && l32 < a.H_q && a.lse)
+                    a.lse[qrow * a.H_q + l32] = l_head > 0.f ? (float)(((double)m_head + (double)__builtin_log2f(l_head)) * 0.6931471805599453) : -INFINITY;
             }
             // accumulator element i belongs to head 8 (i / 4) + 4 hh + i % 4: the sums of the lane's
             // 16 heads come straight from the four waves' partials (independent 16-byte reads; a
@@ -747,7 +753,9 @@ __global__ __launch_bounds__(256, 1) void attn_slab_kernel(AttnArgs a)
                 }
             };
             const int64_t part = (gq * a.n_splits + sp) * a.H_q * D_V + o_lane;
-            if (a.part_wide)
+            if constexpr (!SPLIT)
+                put((__bf16 *)o_l + qrow * a.H_q * D_V + o_lane);
+            else if (a.part_wide)
                 put((float *)a.part_o + part);
             else
                 put((__bf16 *)a.part_o + part);
@@ -1963,14 +1971,14 @@ hipError_t launch_t(const AttnArgs &a, hipStream_t st)
     return hipGetLastError();
 }
 
-template <bool PG>
+template <bool PG, bool SPLIT>
 hipError_t launch_slab(const AttnArgs &a, hipStream_t st)
 {
     constexpr int lds = 2 * kSlabTile * (576 * 2 + kSlabPad) + 2 * 32 * (kSlabTile * 2 + 16) + (4 * 32 + 4 * 32) * (int)sizeof(float);
-    static hipError_t attr = hipFuncSetAttribute((const void *)attn_slab_kernel<576, 512, PG>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    static hipError_t attr = hipFuncSetAttribute((const void *)attn_slab_kernel<576, 512, PG, SPLIT>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (attr != hipSuccess) return attr;
     const dim3 grid((unsigned)((int64_t)a.n_layers * a.B * a.Tq), (unsigned)a.n_splits);
-    hipLaunchKernelGGL((attn_slab_kernel<576, 512, PG>), grid, dim3(256), lds, st, a);
+    hipLaunchKernelGGL((attn_slab_kernel<576, 512, PG, SPLIT>), grid, dim3(256), lds, st, a);
     return hipGetLastError();
 }
 
@@ -2007,7 +2015,15 @@ hipError_t launch_stream(const AttnArgs &a, hipStream_t st, const RestArgs &ra =
 hipError_t launch_mla(const AttnArgs &a, hipStream_t st)
 {
     const bool pg = a.pv.seq_lens || a.pv.page_table;
-    if (a.n_splits > 1) return pg ? launch_slab<true>(a, st) : launch_slab<false>(a, st);
+    if (a.n_splits > 1) return pg ? launch_slab<true, true>(a, st) : launch_slab<false, true>(a, st);
+    const int n_cu = cu_count();                          // one workgroup per CU, in the stream form a chain of queries
+    if (n_cu <= 0) return hipErrorInvalidDevice;
+    // Queries that are all resident, of a few tiles: the stream's start (its granules are gathered two behind one another, their
+    // ids and table entries before that) is most of the launch.  Stream / row-slab, 160 queries of 512 rows: k = 32 11.0 / 9.2 us,
+    // 128 11.9 / 11.3, 160 11.9 / 14.0; paged 13.1 / 10.1, 15.0 / 12.6, 15.3 / 16.7, and 8 queries, k = 192, 14.3 / 12.5.
+    const int64_t nq = (int64_t)a.n_layers * a.B * a.Tq, tiles = (a.k_sel + kSlabTile - 1) / kSlabTile;
+    if (nq <= n_cu && (tiles <= 2 || (pg && tiles == 3 && 4 * nq <= n_cu)))
+        return pg ? launch_slab<true, false>(a, st) : launch_slab<false, false>(a, st);
     if (a.n_layers > 1 || a.row_gap) return pg ? launch_stream<true, true>(a, st) : launch_stream<false, true>(a, st);
     return pg ? launch_stream<true, false>(a, st) : launch_stream<false, false>(a, st);
 }

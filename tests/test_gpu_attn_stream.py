@@ -217,3 +217,44 @@ def test_probs_of_infinite_lse(H):
     fin = torch.isfinite(p)
     # scores to 1e-6 (see above), so probabilities to 1e-6 of themselves, ten times that
     assert ((got[0] - p)[fin].abs() <= 1e-5 * p[fin].abs() + 1e-30).all()
+
+
+@pytest.mark.parametrize("k", [1, 16, 63, 64, 65, 128, 129, 192])
+@pytest.mark.parametrize("B,T,H,page", [(1, 1, 32, 0), (3, 21, 5, 0), (256, 1, 32, 0), (2, 129, 17, 0), (64, 1, 32, 64), (65, 1, 8, 64), (16, 16, 20, -1)])
+def test_short_selections_of_resident_queries(k, B, T, H, page):
+    # up to a query per CU and up to three tiles of 64: row-slab form or stream (one query more; a tile more).  page -1: ragged only
+    L = 256
+    Q, KV, idx = _case(B, T, L, H, k, seed=B + k, holes=k % 2 == 1 and T > 1)   # (holes: row 0 is empty)
+    Qd, KVd, idxd, seen = Q.cuda(), KV.cuda(), idx.cuda(), idx
+    if page == 0:
+        O, lse = ic.sparse_attn(Qd, KVd, idxd, D_V, 0, SCALE, want_lse=True)
+    else:
+        lens = torch.randint(-1, L + 1, (B,), generator=torch.Generator().manual_seed(k)).to(torch.int32)
+        table = torch.arange(B * (L // 64), dtype=torch.int32).view(B, L // 64).cuda() if page > 0 else None
+        pc = ic.paged_cache(lens.cuda(), table, max(page, 0))
+        O, lse = ic.sparse_attn_paged(Qd, KVd.view(B * L, D_QK) if page > 0 else KVd, idxd, L, D_V, 0, SCALE, pc, want_lse=True)
+        seen = torch.where(idx >= lens[:, None, None], torch.tensor(-1, dtype=torch.int32), idx)
+    _check(O, lse, *_reference(Q, KV, seen))
+
+
+def test_short_selections_of_several_layers_at_any_address():
+    # decode of three layers behind one index tensor in one launch, outputs two bytes off 16
+    B, H, k, n, L = 40, 32, 64, 3, 300
+    g = torch.Generator().manual_seed(21)
+    layers = []
+    for i in range(n):
+        t = {"Q": torch.randn((B, 1, H, D_QK), generator=g).to(torch.bfloat16).cuda(), "KV": torch.randn((B, L, D_QK), generator=g).to(torch.bfloat16).cuda()}
+        if i == 0:
+            t["q"] = (torch.randn((B, 1, 32, 128), generator=g) / 11).to(torch.bfloat16).cuda()
+            t["k"] = torch.randn((B, L, 128), generator=g).to(torch.bfloat16).cuda()
+            t["w"] = torch.rand((B, 1, 32), generator=g).cuda()
+        layers.append(t)
+    flat = torch.full((n, B * H * D_V + 8), 7.0, dtype=torch.bfloat16, device="cuda")
+    outs = [flat[i, 1:1 + B * H * D_V].view(B, 1, H, D_V) for i in range(n)]
+    arr = ic.make_layers(layers, k, L - 1, D_V, 0, SCALE, outs)
+    idx = torch.empty((B, 1, k), dtype=torch.int32, device="cuda")
+    ws = torch.empty(max(ic.forward_stack_workspace(arr), 256), dtype=torch.uint8, device="cuda")
+    ic.forward_stack(arr, [True, False, False], idx, ws)
+    for t, out in zip(layers, outs):
+        _check(out, None, _reference(t["Q"].cpu(), t["KV"].cpu(), idx.cpu())[0], None)
+    assert bool((flat[:, :1] == 7).all()) and bool((flat[:, 1 + B * H * D_V:] == 7).all())
