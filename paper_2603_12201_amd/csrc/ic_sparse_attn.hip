@@ -807,7 +807,9 @@ __global__ __launch_bounds__(256, 1) void attn_slab_kernel(AttnArgs a)
 // the tile rows in the order dense_row(), so that the four scores of a lane are neighbours in P.
 // A workgroup walks a chain of blocks as one stream of tiles, the next block's Q and first keys behind the last one's, and the outputs
 // leave under the next block's first steps: with a workgroup per block, its start (Q, first tile, two steps until the first
-// product) and end were about 6 us of the 12 to 25 that a block takes.  Four layers of 3 x 1021 rows 569 -> 513 us.
+// product) and end were about 6 us of the 12 to 25 that a block takes.  Four layers of 3 x 1021 rows 569 -> 505 us.  Where a workgroup
+// has one block the chain's start is what counts: its Q and first keys are requested together and it has no step 0 (64 rows, one launch
+// 11.1 -> 10.4 us; with a workgroup per block and no chain 9.5).
 // Registers.  The two roles need 249 of the 256 that a wave may have: Q of 32 rows takes 144 in the scores waves, the output
 // accumulators 128 in the others.  The compiler places all of it: state that it is not told of (registers named in asm
 // statements) is only safe as long as it happens to put no value of its own there.
@@ -826,11 +828,16 @@ constexpr int kDenseTile = 32;               // keys per tile
 constexpr int kDenseRing = 4;
 constexpr int kDenseChain = 64;              // blocks of a workgroup, at most (their list is in LDS)
 
+struct DenseShape {
+    int n_blk, n_wgs, n_round;               // blocks of a sequence, workgroups, whole rounds of them
+    unsigned inv_b, inv_h;                   // 2^32 / B and / H_q, rounded up (inv_b 0: divide)
+};
+
 // tile row (within 16) behind result row r of S^T
 __device__ __forceinline__ int dense_row(int r) { return 8 * (r >> 3) + 2 * (r & 3) + ((r >> 2) & 1); }
 
 template <bool PG>
-__global__ __launch_bounds__(512, 2) void attn_dense_kernel(AttnArgs a, DenseArgs da)
+__global__ __launch_bounds__(512, 2) void attn_dense_kernel(AttnArgs a, DenseArgs da, DenseShape ds)
 {
     constexpr int D_QK = 576, D_V = 512;
     constexpr int KS = D_QK / 32;                         // contraction steps
@@ -853,34 +860,40 @@ __global__ __launch_bounds__(512, 2) void attn_dense_kernel(AttnArgs a, DenseArg
     const int l16 = lane & 15, l32 = lane & 31, hh = lane >> 5, g = lane >> 4;
     const int gr = lane >> 3, gp = lane & 7;
     const int w = wave & 3;
+    // (requested together, and divided by reciprocals: a division is a tenth of a us, and there are ten in front of the first load)
+    asm volatile("" ::"s"(a.Q), "s"(a.KV), "s"(a.B), "s"(a.Tq), "s"(a.Lk), "s"(a.H_q), "s"(a.row_elems), "s"(da.n_queries), "s"(da.pos0), "s"(da.lead), "s"(ds.n_blk), "s"(ds.n_wgs), "s"(ds.inv_b), "s"(ds.inv_h));
+    auto div_b = [&](int x) -> int { return a.B == 1 ? x : ds.inv_b ? (int)__umulhi((unsigned)x, ds.inv_b) : x / a.B; };
+    auto div_h = [&](int x) -> int { return a.H_q == 1 ? x : (int)__umulhi((unsigned)x, ds.inv_h); };
     // blocks of the workgroup, all sequences' blocks ranked by length: there and back over the workgroups, which evens them out
-    const int n_blk = (da.n_queries * a.H_q + kDenseRows - 1) / kDenseRows, n_all = n_blk * a.B;
-    auto rank = [&](int n) -> int { return n * (int)gridDim.x + (n & 1 ? (int)gridDim.x - 1 - (int)blockIdx.x : (int)blockIdx.x); };
-    int n_list = n_all / (int)gridDim.x;
+    const int n_blk = ds.n_blk, n_all = n_blk * a.B, n_wgs = ds.n_wgs;
+    auto rank = [&](int n) -> int { return n * n_wgs + (n & 1 ? n_wgs - 1 - (int)blockIdx.x : (int)blockIdx.x); };
+    int n_list = ds.n_round;
     n_list += rank(n_list) < n_all;
-    for (int n = wave; n < n_list; n += 8) {
-        const int b = rank(n) % a.B, R0 = (n_blk - 1 - rank(n) / a.B) * kDenseRows;
-        int nq = da.n_queries;
-        if (da.lead) nq = __builtin_amdgcn_readfirstlane(min(nq, lead_rows(da.lead + (int64_t)b * da.n_chunks, da.n_chunks)));
-        if (lane == 0) list[n] = R0 < nq * a.H_q ? nq : 0;
-    }
     if (tid < kDenseRows) mref[tid] = mnew[tid] = mnew[kDenseRows + tid] = -INFINITY;
     if (tid < 4) moved[tid] = 0;
-    __syncthreads();
+    if (da.lead) {
+        for (int n = wave; n < n_list; n += 8) {
+            const int r_b = div_b(rank(n)), b = rank(n) - r_b * a.B, R0 = (n_blk - 1 - r_b) * kDenseRows;
+            const int nq = __builtin_amdgcn_readfirstlane(min(da.n_queries, lead_rows(da.lead + (int64_t)b * da.n_chunks, da.n_chunks)));
+            if (lane == 0) list[n] = R0 < nq * a.H_q ? nq : 0;
+        }
+        __syncthreads();
+    }
     struct Block { int n, odd, b, R0, n_queries, n_rows, nt, t_edge; };  // n = n_list: none
     auto open = [&](int n, int odd) {                     // block n of the list, or the first one behind it that exists
         Block k;
         k.odd = odd;                                      // (odd and even ones alternate)
-        int nq = 0;
-        while (n < n_list && (nq = __builtin_amdgcn_readfirstlane(list[n])) == 0) ++n;
-        const int r = rank(min(n, n_list - 1));
+        int nq = da.n_queries;
+        if (da.lead)
+            while (n < n_list && (nq = __builtin_amdgcn_readfirstlane(list[n])) == 0) ++n;
+        const int r = rank(min(n, n_list - 1)), r_b = div_b(r);
         k.n = n;
-        k.b = r % a.B;
-        k.R0 = (n_blk - 1 - r / a.B) * kDenseRows;
+        k.b = r - r_b * a.B;
+        k.R0 = (n_blk - 1 - r_b) * kDenseRows;
         k.n_queries = nq;
         k.n_rows = nq * a.H_q;                            // flattened rows of a sequence
-        k.nt = (da.pos0 + min(k.R0 + kDenseRows - 1, k.n_rows - 1) / a.H_q) / kDenseTile + 1;
-        k.t_edge = (da.pos0 + k.R0 / a.H_q + 1) / kDenseTile;            // first tile with keys that some row does not see
+        k.nt = (da.pos0 + div_h(max(min(k.R0 + kDenseRows, k.n_rows) - 1, 0))) / kDenseTile + 1;
+        k.t_edge = (da.pos0 + div_h(k.R0) + 1) / kDenseTile;             // first tile with keys that some row does not see
         return k;
     };
     const Block first = open(0, 0);
@@ -888,8 +901,8 @@ __global__ __launch_bounds__(512, 2) void attn_dense_kernel(AttnArgs a, DenseArg
 
     // The blocks are one stream of tiles: the two of Q (its rows in the shape of keys), then the block's nt of keys, then the
     // next block's.  Step i: tile i is scored (Q: read), the operands of tile i - 1 and the product of tile i - 2 are taken, tile
-    // i + 2 goes to LDS and tile i + 3 into registers.  Barriers: one before step 0 and one at the end of every step, one more within
-    // step i + 1 if a reference moved in tile i.
+    // i + 2 goes to LDS and tile i + 3 into registers.  Barriers: one before step 1 (Q and the first keys are there: there is no step 0)
+    // and one at the end of every step, one more within step i + 1 if a reference moved in tile i.
     if (wave < 4) {
         const int rh = w & 1, kh = w >> 1;
         bf16x8 qv[KS][2];
@@ -992,14 +1005,14 @@ __global__ __launch_bounds__(512, 2) void attn_dense_kernel(AttnArgs a, DenseArg
             // Q's steps.  Of the block before: what its last tile moved, then its sums and references for the output waves, where
             // the factors are otherwise
             if (i > 0) settle(i, moved[(i - 1) & 1]);
-            if (k.n < n_list) {
+            if (k.n < n_list) {                           // (at the start both of its tiles are there)
                 const unsigned char *qr = tbuf + ((i + rh) & (kDenseRing - 1)) * TBUFB + l16 * ROWB + 16 * g;
 #pragma unroll
                 for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
                     for (int r = 0; r < 2; ++r) qv[ks][r] = *(const bf16x8 *)(qr + 16 * r * ROWB + 64 * ks);
             }
-            __syncthreads();
+            if (i > 0) __syncthreads();
 #pragma unroll
             for (int r = 0; r < 2; ++r) {
                 const int row = 32 * rh + 16 * r + l16;
@@ -1010,7 +1023,7 @@ __global__ __launch_bounds__(512, 2) void attn_dense_kernel(AttnArgs a, DenseArg
                 }
                 l_own[r] = psum[r] = 0.f;
                 m_c[r] = -INFINITY;
-                lim[r] = da.pos0 + min(k.R0 + row, k.n_rows - 1) / a.H_q;
+                lim[r] = da.pos0 + div_h(max(min(k.R0 + row, k.n_rows - 1), 0));
             }
             lim0 = __builtin_amdgcn_readfirstlane(lim[0]);
             if (tid < kDenseRows) mref[tid] = mnew[tid] = mnew[kDenseRows + tid] = -INFINITY;
@@ -1040,26 +1053,26 @@ __global__ __launch_bounds__(512, 2) void attn_dense_kernel(AttnArgs a, DenseArg
         u32x4 cur[9];
         Block ab = first;                                 // the next tile to request: tile aj of block ab, Q is 0 and 1
         int aj = 0;
-        auto tile_src = [&]() -> const unsigned short * { // (past the last block: its last tile of Q again, for nobody)
+        auto tile_src = [&]() -> const unsigned short * { // (past the last block: one row of its Q, for nobody)
             const unsigned short *p;
-            if (aj < 2) {
+            if (ab.nt == INT32_MAX) {
+                p = (const unsigned short *)a.Q + ((int64_t)ab.b * a.Tq * a.H_q + ab.R0) * D_QK;
+            } else if (aj < 2) {
                 p = (const unsigned short *)a.Q + ((int64_t)ab.b * a.Tq * a.H_q + min(ab.R0 + 32 * aj + 8 * w + gr, ab.n_rows - 1)) * D_QK;
             } else {
                 const int s0 = (aj - 2) * kDenseTile;                      // (a tile never straddles a page)
                 const int64_t row = PG && a.pv.page_table ? paged_row(a.pv, ab.b, s0) : (int64_t)ab.b * a.Lk + s0;
                 p = (const unsigned short *)a.KV + (row + min(8 * w + gr, da.pos0 + ab.n_queries - 1 - s0)) * a.row_elems;
             }
-            if (__builtin_expect(++aj == ab.nt + 2, 0)) {
+            if (__builtin_expect(++aj - 2 == ab.nt, 0)) {
                 const Block nx = open(ab.n + 1, 0);
                 if (nx.n < n_list) {
                     ab = nx;
                     aj = 0;
                 } else {
-                    aj = 1;
-                    ab.nt = INT32_MAX - 2;                // (never to come round)
+                    ab.nt = INT32_MAX;                    // (never to come round)
                 }
             }
-            if (ab.nt == INT32_MAX - 2) aj = 1;
             return p + 8 * gp;
         };
         auto load = [&]() __attribute__((always_inline)) {
@@ -1073,17 +1086,20 @@ __global__ __launch_bounds__(512, 2) void attn_dense_kernel(AttnArgs a, DenseArg
             for (int c = c0; c < c0 + n; ++c) *(u32x4 *)(d + 128 * c) = cur[c];
         };
         {
-            u32x4 q0[9];
-            load();
+            u32x4 q0[2][9];                               // Q and the first keys, requested together
 #pragma unroll
-            for (int c = 0; c < 9; ++c) q0[c] = cur[c];
-            load();
-            {
-                unsigned char *d = tbuf + st_off;
+            for (int t = 0; t < 2; ++t) {
+                load();
 #pragma unroll
-                for (int c = 0; c < 9; ++c) *(u32x4 *)(d + 128 * c) = q0[c];
+                for (int c = 0; c < 9; ++c) q0[t][c] = cur[c];
             }
-            store(1, 0, 9);
+            load();
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int c = 0; c < 9; ++c) *(u32x4 *)(tbuf + t * TBUFB + st_off + 128 * c) = q0[t][c];
+            store(2, 0, 9);
             load();
         }
         f32x16 o_acc[2][4];                               // [rows 32 r ..][columns 32 nb ..]
@@ -1127,7 +1143,7 @@ __global__ __launch_bounds__(512, 2) void attn_dense_kernel(AttnArgs a, DenseArg
         };
         // Step i: output product of tile i - 2 (kMma) in two steps of 16 keys, from operands read a step ago; those of tile i - 1
         // (kRead: tile t of block k) take their registers, tile i + 2 goes to LDS and tile i + 3 into its registers
-        int i = 0;
+        int i = 1;
         Block k = first;
         auto step = [&](int t, auto mma_c, auto read_c) __attribute__((always_inline)) {
             constexpr bool kMma = decltype(mma_c)::value, kRead = decltype(read_c)::value;
@@ -1230,8 +1246,6 @@ __global__ __launch_bounds__(512, 2) void attn_dense_kernel(AttnArgs a, DenseArg
         };
         constexpr std::true_type T{};
         constexpr std::false_type F{};
-        __syncthreads();
-        step(0, F, F);
         __syncthreads();
         step(0, F, F);
         __syncthreads();
@@ -2127,10 +2141,18 @@ hipError_t launch_attn_dense(const AttnArgs &a, const DenseArgs &da, hipStream_t
     const int n_cu = cu_count();
     if (n_cu <= 0) return hipErrorInvalidDevice;
     const dim3 grid((unsigned)std::max(std::min<int64_t>(blocks, n_cu), (blocks + kDenseChain - 1) / kDenseChain));
+    // x * ceil(2^32 / d) >> 32 is x / d as long as x * (d - 1) < 2^32; a sequence has at most IC_MAX_K * IC_MAX_HEADS_Q rows
+    auto up = [](int64_t d) { return d > 1 ? (unsigned)((((uint64_t)1 << 32) + d - 1) / d) : 0u; };
+    DenseShape ds;
+    ds.n_blk = (int)(blocks / a.B);
+    ds.n_wgs = (int)grid.x;
+    ds.n_round = (int)(blocks / grid.x);
+    ds.inv_b = blocks * (a.B - 1) < (int64_t)1 << 32 ? up(a.B) : 0u;
+    ds.inv_h = up(a.H_q);
     if (a.pv.page_table)
-        hipLaunchKernelGGL(attn_dense_kernel<true>, grid, dim3(512), lds, st, a, da);
+        hipLaunchKernelGGL(attn_dense_kernel<true>, grid, dim3(512), lds, st, a, da, ds);
     else
-        hipLaunchKernelGGL(attn_dense_kernel<false>, grid, dim3(512), lds, st, a, da);
+        hipLaunchKernelGGL(attn_dense_kernel<false>, grid, dim3(512), lds, st, a, da, ds);
     return hipGetLastError();
 }
 
