@@ -137,6 +137,22 @@ ic_status check_attn(const ic_attn_desc *d)
 // layouts two.
 int64_t attn_resident(const ic_attn_desc *d) { return (d->d_qk == 576 && d->v_off == 0) ? 256 : 512; }
 
+// What is known about an index tensor: the causal top-k of this library for query rows at positions pos0 + t over the
+// first lk keys (row t then holds the min(k_sel, pos0 + t + 1, lk) best of them and -1s behind); pos0 < 0: nothing.  lk
+// is the Full layer's: a Shared layer's cache may be longer.
+struct Causal {
+    int64_t pos0;
+    int32_t lk;
+};
+constexpr Causal kUnknown = {-1, 0};
+
+// Entries that the longest row can hold, all of them in front.
+int32_t held_entries(const ic_attn_desc *d, Causal c)
+{
+    if (c.pos0 < 0) return d->k_sel;
+    return (int32_t)std::max<int64_t>(1, std::min<int64_t>(std::min(d->k_sel, c.lk), c.pos0 + d->Tq));
+}
+
 // The most key-slot splits per query a launch of n_layers layers uses, which sizes the workspace: one when the queries
 // alone fill the chip, otherwise what brings their number up to that.
 int64_t attn_max_splits(const ic_attn_desc *d, int n_layers)
@@ -168,12 +184,12 @@ struct Splits {
     bool wide;
     size_t bytes;
 };
-Splits attn_splits(const ic_attn_desc *d, int n_layers, size_t ws_bytes, int64_t narrow)
+Splits attn_splits(const ic_attn_desc *d, int n_layers, size_t ws_bytes, int64_t narrow, Causal c = kUnknown)
 {
-    const int64_t nq = (int64_t)n_layers * d->B * d->Tq, wgs = attn_resident(d), tiles = (d->k_sel + 63) / 64;
+    const int64_t nq = (int64_t)n_layers * d->B * d->Tq, wgs = attn_resident(d), tiles = (held_entries(d, c) + 63) / 64;
     int64_t best = 0;
     Splits r = {1, (int)tiles * 64, false, 0};
-    for (int64_t ns = 1, most = attn_max_splits(d, n_layers); ns <= most; ++ns) {
+    for (int64_t ns = 1, most = std::min(tiles, attn_max_splits(d, n_layers)); ns <= most; ++ns) {
         const int64_t per = (tiles + ns - 1) / ns, n = (tiles + per - 1) / per;
         const bool wide = n > 1 && n < narrow;
         const size_t bytes = n > 1 ? split_bytes(d, nq * n, wide) : 0;
@@ -205,8 +221,10 @@ size_t attn_query_bytes(const ic_attn_desc *d)
 // tensor, so what is left is that their shapes agree and that no layer's output overlaps another one's inputs or output
 // (called one after the other such layers would see each other's results).  Per layer, launches with few queries are
 // mostly latency (a launch and its merge of one decode token: 13.5 us for 2.4 MB of rows) and a last round of a few
-// workgroups; together they are taken where that saves an eighth of the tile times or more (700 queries a layer, 11 rounds
-// instead of 12, came out even: a last round with CUs to spare runs faster).
+// workgroups.  576 / 512 rows: together up to twelve rounds of queries a layer, from where on the layers' caches in turn are
+// worth as much as the launches saved.  Four layers of causal rows, together / a launch each: 64 rows 11.9 / 36.5 us, 256 40 / 64, 700
+// behind 1700 476 / 545, 2100 821 / 863, 3000 1430 / 1449, 4096 2195 / 2155.  Other rows: where an eighth of the tile
+// times or more is saved.
 struct Range {
     const char *p;
     size_t n;
@@ -230,8 +248,9 @@ int attn_batch(const ic_layer *layers, int n, const ic_paged_cache *pc)
                     !o(layers[j]).meets(q(l)) && !o(layers[j]).meets(kv(l));
         if (!apart) break;
     }
-    // in tile times, as in attn_splits(): rounds of (tiles + 2), 2 per launch
     const int64_t wgs = attn_resident(&d), tiles = (d.k_sel + 63) / 64;
+    if (wgs == 256) return (int64_t)nq < 12 * wgs ? m : 1;
+    // in tile times, as in attn_splits(): rounds of (tiles + 2), 2 per launch
     const int64_t together = ((int64_t)(m * nq) + wgs - 1) / wgs * (tiles + 2) + 2, alone = m * (((int64_t)nq + wgs - 1) / wgs * (tiles + 2) + 2);
     return together * 8 <= alone * 7 ? m : 1;
 }
@@ -364,20 +383,11 @@ size_t indexer_strip_ws(const ic_indexer_desc *d)
     return align_up(want / row_bytes * row_bytes);
 }
 
-// What is known about an index tensor: the causal top-k of this library for query rows at positions pos0 + t over the
-// first lk keys (row t then holds the min(k_sel, pos0 + t + 1, lk) best of them and -1s behind); pos0 < 0: nothing.  lk
-// is the Full layer's: a Shared layer's cache may be longer.
-struct Causal {
-    int64_t pos0;
-    int32_t lk;
-};
-constexpr Causal kUnknown = {-1, 0};
-
 // Leading query rows of every sequence that the dense form can take: the rows that select exactly the keys 0 .. pos0 + t, of
 // which they see at most k_sel and all below lk.
 int prefix_queries(const ic_attn_desc *d, Causal c)
 {
-    if (c.pos0 < 0 || attn_resident(d) != 256 || d->d_v != 512 || d->B > 65535) return 0;   // (B: grid.y)
+    if (c.pos0 < 0 || attn_resident(d) != 256 || d->d_v != 512) return 0;
     const int32_t keys = c.lk < d->Lk ? c.lk : d->Lk;
     const int64_t n = (d->k_sel < keys ? d->k_sel : keys) - c.pos0;
     return (int)(n < 0 ? 0 : (n > d->Tq ? d->Tq : n));
@@ -386,30 +396,52 @@ int prefix_queries(const ic_attn_desc *d, Causal c)
 // It stores 16 bytes of O at a time; the row form takes any address of a bf16.
 bool dense_output(const void *O) { return (uintptr_t)O % 16 == 0; }
 
-// Times in tiles of 64 keys of a row-form workgroup (about 2 us), launches and what a workgroup pays once included.
-// Rows of one or more layers in the row form: attn_splits() where they are split or all resident, otherwise chains of
-// queries, which leave the tiles behind a causal row's last entry out.
+// The rules below weigh launches of 576 / 512 rows by their time in us, to about a tenth: fitted to 250 launches and runs of up to
+// eight layers, 1 to 128 sequences of 1 to 2048 rows, of which the form taken is within 5 % of the fastest in all but eight (13 %).
+constexpr double kLaunchUs = 9;                // an attention launch of the row forms until its workgroups are busy, and its end
+constexpr double kGranuleUs = 0.61;            // 32 rows in the stream form; a query's Q is as many again
+constexpr double kSplitTileUs = 3;             // 64 rows in the row-slab form with its queries split, merge included
+constexpr double kDenseLaunchUs = 7;
+constexpr double kDenseTileUs = 0.9;           // 32 keys of a block in the dense form
+constexpr double kDenseBlockUs = 5;            // another block in a workgroup's chain
+// Q and O of n queries at 5 TB/s
+double query_us(const ic_attn_desc *d, int64_t n) { return (double)n * d->H_q * (d->d_qk + d->d_v) * 2 / 5e6; }
+
+// Rows of one or more layers in the row forms: split, in short selections of resident queries, or in the stream form, in which the
+// longest chain counts and which leaves the granules behind a causal row's last entry out.
 double row_time(const ic_attn_desc *d, int n_layers, Causal c, size_t ws_bytes, int64_t narrow)
 {
-    const int64_t nq = (int64_t)n_layers * d->B * d->Tq, wgs = attn_resident(d), tiles = (d->k_sel + 63) / 64;
-    if (nq <= wgs) {
-        const Splits sp = attn_splits(d, n_layers, ws_bytes, narrow);
-        return (double)((nq * sp.n + wgs - 1) / wgs * (sp.len / 64 + 2)) + (sp.n > 1 ? 2 : 0);
-    }
-    double mean = (double)tiles;
-    if (c.pos0 >= 0 && c.pos0 < d->k_sel) {    // rows that hold fewer entries than k, and the others
+    const int64_t nq = (int64_t)n_layers * d->B * d->Tq, wgs = attn_resident(d), rounds = (nq + wgs - 1) / wgs;
+    const Splits sp = attn_splits(d, n_layers, ws_bytes, narrow, c);
+    if (sp.n > 1) return kLaunchUs + kSplitTileUs * (double)((nq * sp.n + wgs - 1) / wgs * (sp.len / 64));
+    if (nq <= wgs && sp.len <= 128) return 6.5 + 2. * (sp.len / 64);
+    const double longest = held_entries(d, c);
+    double granules;
+    if (rounds == 1) {
+        granules = longest / 32 + 1;
+    } else if (c.pos0 < 0 || c.pos0 >= d->k_sel) {
+        granules = (double)rounds * (longest / 32 + 1);
+    } else if (c.pos0 + d->Tq <= d->k_sel && (d->Tq % wgs == 0 || wgs % d->Tq == 0)) {
+        // a chain takes the same places of every sequence and layer: the last one those at the end
+        granules = (double)rounds * ((c.pos0 + 0.5 * (d->Tq + std::min<double>(d->Tq, (double)wgs))) / 32 + 1);
+    } else {                                   // rows that hold fewer entries than k, and the others
         const double few = (double)std::min<int64_t>(d->Tq, d->k_sel - c.pos0);
-        mean = (few * std::min(mean, std::max(3.0, (c.pos0 + 0.5 * (few + 1)) / 64)) + (d->Tq - few) * mean) / d->Tq;
+        const double mean = (few * (c.pos0 + 0.5 * (few + 1)) + (d->Tq - few) * d->k_sel) / d->Tq;
+        granules = (double)rounds * (mean / 32 + 1) + 0.5 * longest / 32 * (double)std::min<int64_t>(rounds, n_layers);
     }
-    return (double)((nq + wgs - 1) / wgs) * mean + 2;
+    return kLaunchUs + std::max(kGranuleUs * granules + 0.3 * query_us(d, nq), query_us(d, nq));
 }
 
-// The first n rows of every sequence in the dense form: a workgroup per 64 (query, head) rows, longest first, 0.83 times per
-// 64 keys; more workgroups than CUs leave half of the longest's walk uneven at the end.
+// The first n rows of every sequence in the dense form: blocks of 64 (query, head) rows ranked by length, in chains there and back
+// over the CUs, as long as the longest block or as a chain of those that all rounds of them have a block for.
 double dense_time(const ic_attn_desc *d, int n, int64_t pos0)
 {
-    const double blocks = (double)(((int64_t)n * d->H_q + 63) / 64 * d->B), longest = (pos0 + n) / 64.0, mean = (pos0 + 0.5 * n) / 64;
-    return 0.83 * (blocks <= 256 ? longest + 2 : std::max(longest + 2, blocks * (mean + 2) / 256 + 0.5 * longest));
+    const int64_t blocks = ((int64_t)n * d->H_q + 63) / 64 * d->B, rounds = (blocks + 255) / 256;
+    auto tiles = [&](double rank) { return (pos0 + std::max(0., n * (1 - rank / (double)blocks))) / 32 + 0.5; };
+    // two rounds, there and back: twice the block at the turn
+    const double pairs = (double)(rounds / 2), chain = 2 * pairs * tiles(256 * pairs) + (rounds % 2 ? tiles(256. * (double)(rounds - 1)) : 0.);
+    const double walk = std::max(kDenseTileUs * tiles(0), kDenseTileUs * chain + kDenseBlockUs * (double)(rounds - 1));
+    return kDenseLaunchUs + std::max(walk, query_us(d, (int64_t)n * d->B));
 }
 
 ic_attn_desc rows_behind(const ic_attn_desc *d, int n)
@@ -419,21 +451,20 @@ ic_attn_desc rows_behind(const ic_attn_desc *d, int n)
     return t;
 }
 
-// How many of them it takes, for one of n_layers layers that the row form would take together.  Its workgroups walk their
-// keys one tile after the other and do not share them between sequences, so it has to fill the chip or be short; and the rows
-// behind (ws_bytes: workspace for their splits) are a launch of their own, which has to save more than it costs.  Measured,
-// four layers, k = 2048, row form / dense form and what is left: 4 x 256 rows behind 1800 keys 897 / 671 us, behind 1900 keys
-// 897 / 966; 64 x 8 rows behind 2044 keys 575 / 643; 128 x 1 rows behind 2000 keys, four layers together 222 / 261.
+// How many of them it takes, for one of n_layers layers that the row forms would take together.  The rows behind (ws_bytes:
+// workspace for their splits) are a launch of their own, with some 11 us for the two ends between them.  Measured, k = 2048, row forms / dense form (and
+// what is left): 128 rows 12.5 / 12.6 us, 320 21.2 / 18.0, 1024 64 / 46, 4 x 64 11.8 / 11.9, 16 x 32 19.0 / 13.3, 256 rows behind 1792
+// 48.5 / 54.7, 512 behind 1536 84 / 67; four layers: 64 rows 11.9 / 37.5, 512 82 / 90, 768 144 / 120, 16 x 32 39 / 51, 4 x 256
+// 125 / 104; with rows left: 4 x 256 behind 1800 204 / 182, behind 1900 198 / 229, four layers 684 / 621 and 724 / 860.
 int dense_queries(const ic_attn_desc *d, int n_layers, Causal c, size_t ws_bytes)
 {
     const int n = prefix_queries(d, c);
-    const int64_t blocks = ((int64_t)n * d->H_q + 63) / 64 * d->B, tiles = (c.pos0 + n + 63) / 64;
-    if (n == 0 || (blocks < 128 && tiles > 4)) return 0;
-    const double whole = row_time(d, n_layers, c, ws_bytes, attn_max_splits(d, 1)) / n_layers, dense = dense_time(d, n, c.pos0);
-    if (n == d->Tq) return dense <= 1.08 * whole ? n : 0;
+    if (n == 0) return 0;
+    const double whole = row_time(d, n_layers, c, ws_bytes, attn_max_splits(d, 1)), dense = dense_time(d, n, c.pos0);
+    if (n == d->Tq) return 0.97 * n_layers * dense <= whole ? n : 0;
     const ic_attn_desc t = rows_behind(d, n);
     const double behind = row_time(&t, 1, Causal{c.pos0 + n, c.lk}, ws_bytes, INT64_MAX);
-    return dense + 2 <= 0.75 * (whole - behind) ? n : 0;
+    return n_layers * (dense + 11 + behind) <= whole ? n : 0;
 }
 
 // Workspace that serves the rows behind best.
@@ -447,35 +478,36 @@ size_t dense_tail_bytes(const ic_attn_desc *d, int n_layers, Causal c)
 
 // Leading query rows of every sequence that may be whole prefixes when nothing is known about idx: in a causal selection
 // for the last Tq of Lk positions, rows t < k_sel - (Lk - Tq).  Their number is then counted on the device (lead_kernel)
-// and the dense form and what follows it read the counts.  Without the dense form a row costs k_sel / 64 tile times of a CU
+// and the dense form and what follows it read the counts.  Without the dense form a row costs k_sel / 32 granules
 // however little of it is filled.  The rows behind the candidates go along with the candidates that the counts leave, or
 // are split over the chip on their own.  Whichever of the two gains more on a causal selection than it loses on any other is
-// taken if that difference is a tenth of what the candidates take in the row form; the scan and the launches that find nothing to do cost 5.5
-// tile times.  Measured, k = 2048, row form / this for causal rows / for other rows: 2048 rows 414 / 161 / 429 us, 4096
-// rows 827 / 596 / 839, 4 x 2060 rows 1677 / 642 / 1703; not taken: 700 rows behind 1700 keys 160 / 173 / 166.
+// taken if that difference is a seventh of what the candidates take in the row form; the scan and the launches that find nothing
+// to do cost 8 us.  Measured, k = 2048, row form / this for causal rows / for other rows: 256 rows 43 / 21 / 49 us, 2048 rows
+// 328 / 147 / 347, 4096 rows 667 / 490 / 696, 4 x 2060 rows 1354 / 601 / 1410; not taken: 700 rows behind 1700 keys 126 / 152
+// / 131, 1000 behind 1500 161 / 184 / 176, 64 x 8 rows behind 2036 95 / 76 / 184.
 struct LeadPlan {
     int n;
     bool along;
 };
 LeadPlan lead_plan(const ic_attn_desc *d)
 {
-    const int64_t pos0 = (int64_t)d->Lk - d->Tq, tiles = (d->k_sel + 63) / 64;
+    const int64_t pos0 = (int64_t)d->Lk - d->Tq;
     const int n = pos0 < 0 ? 0 : prefix_queries(d, Causal{pos0, d->Lk});
     const LeadPlan none = {0, false};
     if (n == 0) return none;
-    auto unsplit = [&](int64_t rows) { return rows == 0 ? 0. : (double)((d->B * rows + 255) / 256 * tiles + 2); };
-    const double whole = row_time(d, 1, kUnknown, SIZE_MAX, attn_max_splits(d, 1)), dense = dense_time(d, n, pos0) + 5.5;
+    auto unsplit = [&](int64_t rows) { return rows == 0 ? 0. : kLaunchUs + kGranuleUs * (double)((d->B * rows + 255) / 256) * (d->k_sel / 32. + 1); };
+    const double whole = row_time(d, 1, kUnknown, SIZE_MAX, attn_max_splits(d, 1)), dense = dense_time(d, n, pos0) + 8;
     const ic_attn_desc t = rows_behind(d, n);
     // gain on causal rows minus loss on others
-    const double along = whole - (dense + unsplit(t.Tq)) - (unsplit(d->Tq) + 5.5 - whole);
+    const double along = whole - (dense + unsplit(t.Tq)) - (unsplit(d->Tq) + 8 - whole);
     double apart = 2 * whole;
     if (t.Tq > 0 && (int64_t)d->B * t.Tq < 256) {
         const double tail = row_time(&t, 1, kUnknown, SIZE_MAX, INT64_MAX);
-        apart -= dense + tail + unsplit(n) + tail + 5.5;
+        apart -= dense + tail + unsplit(n) + tail + 8;
     } else {
         apart = along;                         // (nothing to split)
     }
-    if (std::max(along, apart) < 0.1 * (whole - unsplit(t.Tq))) return none;
+    if (std::max(along, apart) < 0.15 * (whole - unsplit(t.Tq))) return none;
     return {n, along >= apart};
 }
 int lead_queries(const ic_attn_desc *d) { return lead_plan(d).n; }
@@ -488,18 +520,17 @@ size_t lead_bytes(const ic_attn_desc *d, int n_tensors)
     return n ? align_up((size_t)n_tensors * d->B * lead_chunks(n) * sizeof(int32_t)) : 0;
 }
 
-// Workgroups per sequence that share the rows left of it, in tile times: rounds of all sequences' workgroups, each as long as
-// the longest chain and two tiles.
+// Workgroups per sequence that share the rows left of it: rounds of all sequences' workgroups, each as long as the longest
+// chain.
 int rest_workgroups(const ic_attn_desc *d, int rows)
 {
-    const int64_t tiles = (d->k_sel + 63) / 64;
-    if (tiles < 3) return rows;                // (no chains)
+    const double query = kGranuleUs * ((d->k_sel + 31) / 32 + 1);
     int best = 1;
-    int64_t cost = INT64_MAX;
+    double time = 1e30;
     for (int g = 1; g <= rows && g <= 256; ++g) {
-        const int64_t c = ((int64_t)d->B * g + 255) / 256 * ((rows + g - 1) / g * tiles + 2);
-        if (c <= cost) {
-            cost = c;
+        const double t = (double)(((int64_t)d->B * g + 255) / 256) * ((rows + g - 1) / g * query + kLaunchUs);
+        if (t <= time) {
+            time = t;
             best = g;
         }
     }
@@ -610,7 +641,7 @@ ic_status run_attn_layers(const ic_layer *layers, int n_layers, const int32_t *i
     const ic_attn_desc *d = &layers[0].at;
     ic::AttnArgs a = attn_args(layers, n_layers, idx, lse, pc, c);
     if (d->B > 1) a.row_gap = skipped;
-    const Splits sp = attn_splits(d, n_layers, ws_bytes, skipped > 0 ? INT64_MAX : attn_max_splits(d, 1));
+    const Splits sp = attn_splits(d, n_layers, ws_bytes, skipped > 0 ? INT64_MAX : attn_max_splits(d, 1), c);
     a.n_splits = sp.n;
     a.split_len = sp.len;
     if (sp.n > 1) {

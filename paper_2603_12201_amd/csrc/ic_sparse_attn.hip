@@ -2035,7 +2035,7 @@ hipError_t launch_mla(const AttnArgs &a, hipStream_t st)
     // Queries that are all resident, of a few tiles: the stream's start (its granules are gathered two behind one another, their
     // ids and table entries before that) is most of the launch.  Stream / row-slab, 160 queries of 512 rows: k = 32 11.0 / 9.2 us,
     // 128 11.9 / 11.3, 160 11.9 / 14.0; paged 13.1 / 10.1, 15.0 / 12.6, 15.3 / 16.7, and 8 queries, k = 192, 14.3 / 12.5.
-    const int64_t nq = (int64_t)a.n_layers * a.B * a.Tq, tiles = (a.k_sel + kSlabTile - 1) / kSlabTile;
+    const int64_t nq = (int64_t)a.n_layers * a.B * a.Tq, tiles = a.split_len / kSlabTile;
     if (nq <= n_cu && (tiles <= 2 || (pg && tiles == 3 && 4 * nq <= n_cu)))
         return pg ? launch_slab<true, false>(a, st) : launch_slab<false, false>(a, st);
     if (a.n_layers > 1 || a.row_gap) return pg ? launch_stream<true, true>(a, st) : launch_stream<false, true>(a, st);
