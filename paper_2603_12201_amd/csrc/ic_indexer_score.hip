@@ -658,7 +658,9 @@ __global__ __launch_bounds__(64 * NW, 1) void score_stream_kernel(ScoreArgs a, S
         // A share ends within a token, whose q rows then travel once more for every wave and keep it as long as some three slots do
         // (their weights are loaded in front of the first product).  So whole tokens unless that leaves the longest window's waves
         // more behind.  Top-k included, in shares and whole: 16 sequences of 60000 to 65536 keys 59.4 and 57.5 us, 12 of 100 to
-        // 32768 (64 heads) 29.6 and 25.4; 40 of 700 to 49152 54.7 and 61.3.
+        // 32768 (64 heads) 29.6 and 25.4; 40 of 700 to 49152 54.7 and 61.3.  (Tokens of one length that do not come out even are
+        // shared: no more of them meet in a share than in a window of whole ones.  24 of 3228 keys, two score launches and
+        // four layers of attention: 110.3 us whole, 109.1.)
         const uint64_t most = (uint64_t)total + 3u * HT * wstride * (unsigned)G;     // G times the slots of a window
         if (n_col == 1 && __ballot((uint64_t)n0 * (unsigned)G > most) == 0ull) {
             share = lane_of(n0, wdw);
@@ -667,7 +669,7 @@ __global__ __launch_bounds__(64 * NW, 1) void score_stream_kernel(ScoreArgs a, S
             auto bound = [&](int w) -> unsigned { return w == G ? total : (unsigned)((uint64_t)total * (unsigned)w * sw.inv_g >> 32); };
             unsigned lo = bound(wdw);
             share = bound(wdw + 1) - lo;
-            if (n_col > 1 && n_place <= 128) {
+            if (ragged && n_col > 1 && n_place <= 128) {
                 auto at_place = [&](int p) -> unsigned {
                     const unsigned x = (unsigned)__shfl((int)upto0, p & 63), y = (unsigned)__shfl((int)upto1, p & 63);
                     return p < 64 ? x : lane_of(upto0, 63) + y;
