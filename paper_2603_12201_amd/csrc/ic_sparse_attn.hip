@@ -1514,11 +1514,15 @@ __global__ __launch_bounds__(512, 2) void attn_stream_kernel(AttnArgs a, RestArg
                     m_use[r] = at - 1 > at_q ? fmaxf(m_c[r], fmaxf(mk[r][0], mk[r][1])) : m_c[r];
                     mx[r] = fmaxf(fmaxf(s4[r][0], s4[r][1]), fmaxf(s4[r][2], s4[r][3])) * a.scale_log2e;
                 }
-                if (__ballot(mx[0] > m_use[0] + kLazyLog2 || mx[1] > m_use[1] + kLazyLog2) != 0ull) {
+                // A pair's first granule takes any larger score for its reference, so that the common one is the largest of 64 rows, as
+                // in the row-slab form: a row's largest p is then 1 and not rounded the more often.  (Peaked rows of 100 entries: relative
+                // distance from 64 bits 0.00188 with the largest of 32, 0.00181 with this.)
+                const float lazy = m_c[0] == -INFINITY ? 0.f : kLazyLog2;
+                if (__ballot(mx[0] > m_use[0] + lazy || mx[1] > m_use[1] + lazy) != 0ull) {
 #pragma unroll
                     for (int r = 0; r < 2; ++r) {
                         mx[r] = xmax16_32(mx[r]);
-                        m_use[r] = mx[r] > m_use[r] + kLazyLog2 ? mx[r] : m_use[r];
+                        m_use[r] = mx[r] > m_use[r] + lazy ? mx[r] : m_use[r];
                     }
                 }
                 if (__ballot(m_use[0] != m_c[0] || m_use[1] != m_c[1]) != 0ull) {

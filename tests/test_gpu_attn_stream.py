@@ -258,3 +258,36 @@ def test_short_selections_of_several_layers_at_any_address():
     for t, out in zip(layers, outs):
         _check(out, None, _reference(t["Q"].cpu(), t["KV"].cpu(), idx.cpu())[0], None)
     assert bool((flat[:, :1] == 7).all()) and bool((flat[:, 1 + B * H * D_V:] == 7).all())
+
+
+@pytest.mark.parametrize("k", [40, 130])
+@pytest.mark.parametrize("T,H", [(300, 32), (530, 7)])
+def test_infinities_and_nan_stay_where_they_belong(T, H, k):
+    # a NaN or +inf score makes its row NaN, a score of -inf leaves NaN in the columns in which the key is not finite; other heads, other
+    # queries and what follows in the same workgroup see nothing of it
+    L = 400
+    Q, KV, idx = _case(1, T, L, H, k, seed=T + k, holes=True)
+    Q[..., 570] = 1.0
+    Q[:, 3::50, :, 570] = -1.0
+    KV[0, 11, 570] = float("inf")                        # (a feature that is no value)
+    KV[0, 12, 570] = -float("inf")
+    KV[0, 13, 5] = float("nan")
+    KV[0, 14, 7], KV[0, 14, 570] = float("inf"), -float("inf")
+    Q[0, 20, H - 1, 3] = float("nan")
+    Q[0, 21, 0, 3] = float("inf")
+    Q[..., 7] = Q[..., 7].abs().clamp_min(0.1)           # (KV[14] scores -inf + inf = NaN for Q[570] = 1, +inf for -1)
+    O, _ = ic.sparse_attn(Q.cuda(), KV.cuda(), idx.cuda(), D_V, 0, SCALE, want_lse=True)
+    O = O.double().cpu()[0]
+    rows, valid = idx[0].clamp_min(0).long(), idx[0] >= 0
+    kv = KV[0].double()[rows]
+    s = torch.einsum("thd,tkd->thk", Q[0].double(), kv) * SCALE
+    s = s.masked_fill(~valid[:, None, :], -float("inf"))
+    m = s.amax(-1, keepdim=True)
+    p = torch.exp(s - torch.where(m == -float("inf"), torch.zeros_like(m), m)).masked_fill(~valid[:, None, :], 0.0)
+    ref = torch.einsum("thk,tkd->thd", p, torch.where(valid[..., None], kv[..., :D_V], torch.zeros((), dtype=torch.float64)))
+    l = p.sum(-1, keepdim=True)
+    ref = torch.where(l > 0, ref / l, ref)
+    assert torch.equal(torch.isnan(O), torch.isnan(ref)) and not bool(torch.isinf(O).any())
+    fin = torch.isfinite(ref)
+    assert 0 < int((~fin).sum()) < fin.numel() // 2
+    assert ((O - ref)[fin].norm() / ref[fin].norm()).item() < 4e-3       # (as in _check)
