@@ -167,10 +167,9 @@ def kernel_table(alg, prof, n_full, n_layers, traffic, workload, fp8):
         t = traffic.get((name, workload))
         if t is not None:
             v["traffic"] = t
-            # what the HBM side of L2 moved per second for this kernel (profiler counters of a tracked run over this
-            # kernel's time in THIS run): near the chip's stream rate means the kernel waits for memory beyond L2
+            # what crossed the L2 boundary per second for this kernel, from the Infinity Cache or from HBM (profiler counters of
+            # a tracked run over this kernel's time in THIS run)
             v["traffic_GBs"] = t / (v["ms_per_layer"] * 1e-3) / 1e9
-            v["traffic_frac_of_hbm_peak"] = v["traffic_GBs"] / HBM_PEAK_GBS
     return k
 
 
@@ -289,7 +288,7 @@ def calibration(ic, synth, idx_prefill, kv_rows):
         out["prefill_row_gather"] = {"bytes": gb, "ms": ms, "GBs": gb / (ms * 1e-3) / 1e9, "workgroups": 512,
                                      "note": "served out of L2 / Infinity Cache; no compute attached; 512 workgroups of 4 waves "
                                              "(about 72 KB in flight per CU) is the fastest schedule found: 256 give 11, 8192 give 10.8 TB/s"}
-        # the attention kernel's tile loop without its arithmetic: the same rows through the same registers and LDS
+        # the row-slab form's tile loop without its arithmetic: the rows through registers and LDS
         tp = {}
         for kind, name in ((ic.CALIB_TILE_GATHER, "gather_into_registers"), (ic.CALIB_TILE_STORE, "plus_lds_store"),
                            (ic.CALIB_TILE_READ, "plus_score_operand_reads"), (ic.CALIB_TILE_READ2, "plus_both_lds_reads"),
@@ -297,7 +296,7 @@ def calibration(ic, synth, idx_prefill, kv_rows):
             tp[name + "_ms"] = event_ms(lambda: ic.calibrate(kind, table, scratch, idx=flat, n=flat.numel(), table_rows=kv_rows,
                                                              row_bytes=1152, wgs=256), reps=2, warmup=1)
         tp["note"] = ("64-row tiles, 4 waves, one workgroup per CU, one tile of gathers ahead, one barrier per tile: what the data "
-                      "movement of the prefill attention kernel takes with no MFMA and no softmax (what is read is folded with XORs); "
+                      "movement of the row-slab attention kernel would take with no MFMA and no softmax (what is read is folded with XORs); "
                       "same_bytes_phases_merged: stores and gathers spread between the reads; same_bytes_eight_waves: the work "
                       "dealt to eight waves, no byte read twice")
         out["prefill_attn_tile_path"] = tp
@@ -429,12 +428,11 @@ def main():
         arms["calibration"] = calibration(ic, synth, stack.idx_cache if cfg["Tq"] == 32768 else None, cfg["Lk"])
         cal = arms["calibration"]
         if "prefill_attn_tile_path" in cal:
-            # the kernel's own ceilings: its rows fetched in its own order with nothing done to them, and all of its
-            # data movement (gather, LDS stores, both operand reads) with no arithmetic, in its best four-wave order
+            # the same rows fetched with nothing done to them, and with their way through LDS (stores, both operand reads) but no
+            # arithmetic; in 64-row tiles of four waves, not in the kernel's granules of 32 rows: for comparison, no bound
             tp = cal["prefill_attn_tile_path"]
             kernels["sparse_attn"]["gather_only_ms"] = min(tp["gather_into_registers_ms"], tp["plus_lds_store_ms"])
             kernels["sparse_attn"]["data_movement_only_ms"] = tp["same_bytes_phases_merged_ms"]
-            kernels["sparse_attn"]["frac_of_data_movement_only"] = tp["same_bytes_phases_merged_ms"] / kernels["sparse_attn"]["ms_per_layer"]
         elif "prefill_row_gather" in cal:
             kernels["sparse_attn"]["gather_only_ms"] = cal["prefill_row_gather"]["ms"]
         kernels["sparse_attn"]["frac_of_measured_mfma"] = kernels["sparse_attn"]["achieved"] / cal["mfma_bf16"]["TFLOPs"]
@@ -655,14 +653,14 @@ def main():
         prof4 = profile_pass(ic, s4, m4_14)
         k4 = kernel_table(alg4, prof4, sum(m4_14), n4, traffic, "prefill131k_fp8", fp8=True)
         # the rows the last Full layer really selects out of its 151 MB cache, fetched with no compute attached (the
-        # index tensor left by the profiled step is that layer's)
+        # index tensor left by the profiled step is that layer's), in an order of its own: all workgroups on one query at a
+        # time, so that less of it hits in L2 than in the kernel; for comparison, no bound
         l_last = max(l for l in range(n4) if m4_14[l])
         flat4 = s4.idx_cache.reshape(-1)
         scratch4 = torch.empty((1 << 16,), dtype=torch.int32, device="cuda")
         ms_g4 = event_ms(lambda: ic.calibrate(ic.CALIB_GATHER, s4.layers[l_last]["KV"], scratch4, idx=flat4, n=flat4.numel(),
                                               table_rows=c4["Lk"], row_bytes=1152, wgs=512), reps=2, warmup=1)
         k4["sparse_attn"]["gather_only_ms"] = ms_g4
-        k4["sparse_attn"]["frac_of_gather_only"] = ms_g4 / k4["sparse_attn"]["ms_per_layer"]
         arms["prefill_fp8_131k"] = {
             "workload": "configs[4]: 1 sequence, L=131072, %d layers, H_I=64 d_I=128 e4m3 q/k with per-token scales, k=2048, "
                         "MQA 32 heads, KV row 576 bf16; every layer has its own KV and indexer inputs, Q cycles over %d tensors "

@@ -377,7 +377,7 @@ uint64_t ic_debug_indexer_launch_count(void);
  *                       lanes per 128-byte line as the attention kernels do; dst as for READ
  *   IC_CALIB_MFMA_BF16  n back-to-back rounds of four v_mfma_f32_32x32x16_bf16 per wave (4 waves per
  *   IC_CALIB_MFMA_FP8   workgroup), or of four 32x32x64 e4m3 instructions; dst: >= 1024 * wgs bytes
- *   IC_CALIB_TILE_*     the data movement of the prefill sparse-attention tile loop without its arithmetic, over
+ *   IC_CALIB_TILE_*     the data movement of the row-slab sparse-attention tile loop without its arithmetic, over
  *                       n rows (a multiple of 64; tiles of 64 rows) of 1152 bytes named by idx as for GATHER, one
  *                       workgroup per CU, row numbers fetched a tile ahead of the rows: _GATHER rows into
  *                       registers, one tile ahead; _STORE also stores each tile to LDS; _READ also reads it back

@@ -100,7 +100,7 @@ __global__ __launch_bounds__(256) void calib_mfma_kernel(int iters, float *out)
     if (s == 12345.678f) out[blockIdx.x * 256 + threadIdx.x] = s;
 }
 
-// The data movement of the prefill attention kernel's tile loop without its arithmetic: tiles of 64 table rows of
+// The data movement of the row-slab attention kernel's tile loop without its arithmetic: tiles of 64 table rows of
 // 1152 bytes, four waves, wave w rows 16 w .. 16 w + 15.  PARTS: 1 = gather into registers only (18 loads per lane
 // and tile, eight lanes per 128-byte line, one tile ahead); 2 = + store the tile to LDS (row-major, rows padded by 32 bytes, double
 // buffered, one barrier per tile); 3 = + read it back as an A operand would be (16-byte reads, once per byte);
