@@ -34,3 +34,18 @@ def test_forward(B, T, L, n, H, k):
     assert torch.equal((idx >= 0).sum(-1).cpu(), held.expand(B, T))
     for t, out in zip(layers, outs):
         _check(out, None, _reference(t["Q"].cpu(), t["KV"].cpu(), idx.cpu()[..., :min(k, L)])[0], None)
+
+
+def test_more_sequences_than_a_grid_dimension():
+    # 65540 sequences of two rows: as many blocks of the dense form, whose numbers times sequences do not fit 32 bits
+    B, T, L, H, k = 65540, 2, 2, 32, 64
+    g = torch.Generator(device="cuda").manual_seed(3)
+    rnd = lambda *s: torch.randn(s, generator=g, device="cuda", dtype=torch.bfloat16)
+    t = {"Q": rnd(B, T, H, D_QK), "KV": rnd(B, L, D_QK), "q": rnd(B, T, 4, 64), "k": rnd(B, L, 64), "w": torch.rand((B, T, 4), generator=g, device="cuda")}
+    out = torch.full((B, T, H, D_V), 7.0, dtype=torch.bfloat16, device="cuda")
+    arr = ic.make_layers([t], k, 0, D_V, 0, SCALE, [out])
+    idx = torch.empty((B, T, k), dtype=torch.int32, device="cuda")
+    ws = torch.empty(max(ic.forward_stack_workspace(arr), 256), dtype=torch.uint8, device="cuda")
+    ic.forward_stack(arr, [True], idx, ws)
+    some = torch.cat([torch.arange(0, B, 331), torch.arange(B - 40, B)])
+    _check(out.cpu()[some], None, _reference(t["Q"].cpu()[some], t["KV"].cpu()[some], idx.cpu()[some][..., :L])[0], None)
