@@ -807,7 +807,7 @@ __global__ __launch_bounds__(256, 1) void attn_slab_kernel(AttnArgs a)
 // the tile rows in the order dense_row(), so that the four scores of a lane are neighbours in P.
 // A workgroup walks a chain of blocks as one stream of tiles, the next block's Q and first keys behind the last one's, and the outputs
 // leave under the next block's first steps: with a workgroup per block, its start (Q, first tile, two steps until the first
-// product) and end were about 6 us of the 12 to 25 that a block takes.  Four layers of 3 x 1021 rows 569 -> 505 us.  Where a workgroup
+// product) and end were about 6 us of the 12 to 25 that a block takes.  Four layers of 3 x 1021 rows 578 -> 511 us.  Where a workgroup
 // has one block the chain's start is what counts: its Q and first keys are requested together and it has no step 0 (64 rows, one launch
 // 11.1 -> 10.4 us; with a workgroup per block and no chain 9.5).
 // Registers.  The two roles need 249 of the 256 that a wave may have: Q of 32 rows takes 144 in the scores waves, the output
@@ -1289,8 +1289,8 @@ __global__ __launch_bounds__(512, 2) void attn_dense_kernel(AttnArgs a, DenseArg
 // What bounds it.  A wave per SIMD and role issues an instruction every 4 to 5 clocks at best, and what a unit has not taken
 // blocks the ones behind it: with every phase in each of four waves (the row-slab form) 32 rows took 1950 clocks, and only the gather, the
 // LDS traffic or the MFMAs of a phase were busy at a time.  Here the output waves alone take 1000 clocks, the scores waves alone 1000, both
-// 1230, of which the matrix cores are busy 544.  The clock falls with it, from 2.35 GHz to 2.0, 1.85 with rows from beyond L2:
-// the rest is power.  2048 queries x 2048 of 32768 rows, 32 heads: 450 us in chains of the row-slab form, 355 here.  Ids requested two periods ahead, addresses worked out at the
+// 1240, of which the matrix cores are busy 540, and the clock is 1.8 to 1.9 GHz; with rows from beyond L2 (131072 of them, 7.1 TB/s
+// across its boundary) 1430 clocks.  2048 queries x 2048 of 32768 rows, 32 heads: 450 us in chains of the row-slab form, 355 here.  Ids requested two periods ahead, addresses worked out at the
 // start of a period, outputs stored straight from the accumulators: 20 % slower together.  Three granules in flight need more
 // registers than there are and gain nothing where two are enough; with 131072 rows (HBM) both forms take the gather's time.
 constexpr int kGranule = 32;                 // selected rows that reach LDS together
