@@ -866,27 +866,43 @@ hipError_t launch_score(const ScoreArgs &a_in, int dtype, int d_I, int Bc, hipSt
         kc = ((max_vis + chunks - 1) / chunks + 63) / 64 * 64;
     }
     // At least 512 keys a workgroup, which pay for its q rows; fewer where that leaves CUs idle: a problem this small takes as long
-    // as one workgroup, so its visible pairs are dealt out to one workgroup per CU.  Measured with 512 / with this rule, top-k
-    // included: 512 x 512 (4 heads of 64) 20.5 / 14.6 us, 1024 x 1024 20.8 / 17.5, 64 rows before 5000 keys (32 heads of 128)
-    // 28.9 / 21.2; where 512 keys already give a workgroup per CU, smaller ones lose: 300 rows before 5000 keys 30.9, with 256 keys 32.8.
+    // as its longest workgroup.  Top-k included: 512 x 512 (4 heads of 64) 20.5 us with 512 keys, 14.2 with this rule, 1024 x 1024
+    // 20.8 / 16.7, 64 rows before 5000 keys (32 heads of 128) 28.9 / 21.2.
     int64_t least = 512;
-    const bool one_per_cu = !fp8 && d_I == 128 && a.H_I > 32;      // (registers: the 64-head form; two per CU otherwise)
     if (few_rows) {
         least = std::min<int64_t>(512, std::max<int64_t>(128, (max_vis * a.n_qblocks * Bc / 256 + 127) / 128 * 128));
         // (128: a subtile for each wave.  One row before 5000 keys, fp8, top-k included: 18.4 us with 512 at the least, 15.5 with this)
     } else {
-        const int64_t mean_vis = a.pv.seq_lens ? max_vis : std::max<int64_t>(1, std::min(max_vis, a.q_pos0 + a.i0 + (i_last - a.i0) / 2 + 1));
-        least = std::min<int64_t>(512, std::max<int64_t>(64, (mean_vis * a.n_qblocks * Bc / 256 + 63) / 64 * 64));
-        // A workgroup over one per CU is a second round where only one is resident: 1024 x 1024 of 64 heads 26.9 us with 512
-        // keys (192 workgroups), 31.7 with 256 (320)
-        for (; one_per_cu && least < 512; least += 64) {
-            int64_t n = 0;                      // workgroups that see keys: blocks behind the first key of each chunk
-            for (int64_t k0 = 0; k0 < max_vis && n <= 256; k0 += least) {
-                const int64_t hidden = a.pv.seq_lens ? 0 : std::max<int64_t>(0, k0 - a.q_pos0 - a.i0);   // rows that see none of it
-                n += (a.n_qblocks - std::min<int64_t>(a.n_qblocks, hidden / BT)) * Bc;
+        const bool one_per_cu = !fp8 && d_I == 128 && a.H_I > 32;      // (registers: the 64-head form; two per CU otherwise)
+        const bool matrix_bound = a.H_I > 32 || (!fp8 && d_I == 128);  // two on a CU share its matrix pipes; the others wait for keys
+        const int64_t plain = a.pv.seq_lens ? max_vis : std::min<int64_t>(max_vis, std::max<int64_t>(0, a.q_pos0 + a.i0 + 1));
+        // Workgroups of `keys` each: every block sees the first `plain` keys, and later chunks only the blocks behind them.
+        // `hidden`: what one that sees nothing counts, in halves (it ends at once, but took a place on a CU).
+        auto fit = [&](int64_t keys, int64_t limit, int hidden) {
+            const int64_t chunks = (max_vis + keys - 1) / keys, full = std::min(chunks, (plain + keys - 1) / keys);
+            if (chunks > limit) return false;
+            int64_t n = full * a.n_qblocks * Bc * 2;
+            for (int64_t c = full; c < chunks && n <= limit * 2; ++c) {
+                const int64_t none = std::min<int64_t>(a.n_qblocks, (c * keys - a.q_pos0 - a.i0) / BT);
+                n += ((a.n_qblocks - none) * 2 + none * hidden) * Bc;
             }
-            if (n <= 256) break;
-        }
+            return n <= limit * 2;
+        };
+        auto fewest = [&](int64_t limit, int hidden) {
+            int64_t keys = 64;
+            while (keys <= 512 && !fit(keys, limit, hidden)) keys += 64;
+            return keys;                                                // 576: none
+        };
+        // One workgroup per CU, or two.  The 64-head form holds one: a second is a second round (1024 x 1024: 26.9 us with 512 keys
+        // and 192 workgroups, 31.7 with 256 and 320).  Where two are resident, two take measurably the time of one with 1.6 times
+        // the keys and 170 where the matrix pipe is the limit, with 100 more keys where it is not.  So rows that all see
+        // about the same keys take one (4 x 200 before 1000, 64 heads of fp8: 22.2 us with 512 keys, 24.5 with 384 and 300
+        // workgroups; 8 x 64 before 2000, 32 heads: 25.9 with 448, 30 with 384) and a triangle, whose later chunks are short of
+        // blocks, takes two (3 x 600 x 600, 64 heads of fp8: 28.2 with 512, 25.2 with 192).
+        const int64_t one = fewest(256, matrix_bound && !one_per_cu ? 1 : 0);
+        const int64_t two = one_per_cu ? 576 : fewest(512, 0);
+        const int64_t two_cost = matrix_bound ? two * 8 / 5 + 170 : two + 100;
+        least = std::min<int64_t>(512, one <= 512 && (one_per_cu || one <= two_cost) ? one : two);
     }
     kc = kc < least ? least : (kc > 8192 ? 8192 : kc);
     a.KC = (int)kc;

@@ -170,3 +170,56 @@ def test_fp8_ragged_rows(T, H):
     assert torch.equal(at[valid], sel[valid])
     low = at.masked_fill(~valid, float("inf")).min(dim=-1).values
     assert torch.equal(low, s.topk(k, dim=-1).values.masked_fill(~valid, float("inf")).min(dim=-1).values)
+
+
+@pytest.mark.parametrize("B,T,L,H,d,fp8,low,q0", [
+    # one workgroup a CU: rows that see about the same keys (448 and 512 keys a workgroup), the last chunk hidden from half of the blocks
+    (8, 64, 2000, 32, 128, 0, None, None), (4, 200, 1000, 64, 128, 1, None, None), (4, 200, 1000, 64, 64, 0, None, None), (1, 300, 2000, 64, 128, 1, None, None),
+    # two a CU: triangles, and more than one a CU at 512 keys (16 x 17 rows)
+    (1, 1024, 1024, 64, 128, 1, None, None), (3, 600, 600, 32, 128, 0, None, None), (16, 17, 3000, 64, 64, 0, None, None), (1, 701, 701, 64, 128, 1, None, None),
+    (4, 201, 1001, 32, 128, 1, None, None), (2, 701, 701, 4, 64, 0, None, None), (1, 5, 40000, 4, 64, 0, None, None),
+    # neither
+    (5, 700, 700, 64, 128, 1, None, None),
+    # more rows than keys: the first see nothing; keys behind the last row
+    (2, 300, 170, 32, 128, 1, None, None), (2, 90, 900, 32, 128, 0, None, 64),
+    # ragged lengths, whose visible keys the host does not know
+    (8, 64, 2000, 32, 128, 0, 500, None), (16, 60, 1000, 32, 128, 0, 0, None), (8, 64, 2000, 64, 128, 0, 0, None), (3, 130, 700, 64, 128, 1, 0, None),
+])
+def test_workgroups_per_cu(B, T, L, H, d, fp8, low, q0):
+    # whole numbers and powers of two: every sum is exact, so every score is
+    g = torch.Generator().manual_seed(B * T + L)
+    q, kk = torch.randint(-2, 3, (B, T, H, d), generator=g).float(), torch.randint(-2, 3, (B, L, d), generator=g).float()
+    w = 2.0 ** torch.randint(-1, 2, (B, T, H), generator=g)
+    k, dtype = min(L, 40), torch.float8_e4m3fn if fp8 else torch.bfloat16
+    qd, kd, wd = q.to(dtype).cuda(), kk.to(dtype).cuda(), w.cuda()
+    one = (torch.ones((B, T)).cuda(), torch.ones((B, L)).cuda()) if fp8 else (None, None)
+    if low is None:
+        q0 = L - T if q0 is None else q0
+        idx, sel = ic.indexer_topk(qd, kd, wd, k, q0, *one, want_scores=True)
+        n_seen = (torch.arange(T) + q0 + 1).clamp(0, L).expand(B, T)
+    else:
+        lens = torch.randint(low, L + 1, (B,), generator=g)
+        lens[0], lens[B // 2] = low, L
+        pc = ic.paged_cache(lens.to(torch.int32).cuda())
+        desc = ic.IndexerDesc(B, T, L, H, d, k, 0, 1 if fp8 else 0, 0, one[0].data_ptr() if fp8 else None, one[1].data_ptr() if fp8 else None)
+        ws = torch.empty(ic.indexer_topk_workspace(desc), dtype=torch.uint8, device="cuda")
+        idx = torch.empty((B, T, k), dtype=torch.int32, device="cuda")
+        sel = torch.empty((B, T, k), dtype=torch.float32, device="cuda")
+        p = lambda t: ctypes.c_void_p(t.data_ptr())
+        assert ic.lib().ic_indexer_topk_paged(ctypes.byref(desc), ctypes.byref(pc), p(qd), p(kd), p(wd), p(idx), p(sel), p(ws), ws.numel(),
+                                              ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)) == 0
+        n_seen = (lens[:, None] - T + 1 + torch.arange(T)[None, :]).clamp_min(0)
+    idx, sel = idx.cpu().long(), sel.cpu()
+    for b in range(B):
+        s = torch.zeros((T, L))
+        for h in range(H):
+            s += w[b, :, h, None] * torch.relu(q[b, :, h] @ kk[b].T)
+        s = s.masked_fill(torch.arange(L) >= n_seen[b][:, None], -float("inf"))
+        valid = idx[b] >= 0
+        assert torch.equal(valid.sum(-1), n_seen[b].clamp_max(k))
+        at = s.gather(1, idx[b].clamp_min(0))
+        assert torch.equal(at[valid], sel[b][valid])
+        top = s.topk(k, dim=-1).values
+        assert torch.equal(at.masked_fill(~valid, float("inf")).min(-1).values, top.masked_fill(~valid, float("inf")).min(-1).values)
+        once = idx[b].masked_fill(~valid, 0).sort(-1).values                     # no key twice
+        assert bool(((once[:, 1:] > once[:, :-1]) | (once[:, 1:] == 0)).all())
