@@ -206,7 +206,6 @@ __device__ __forceinline__ float row16_sum(float x)
 hipError_t launch_score(const ScoreArgs &a, int dtype, int d_I, int Bc, hipStream_t st);
 hipError_t launch_fill(float *p, int64_t n, float v, hipStream_t st);
 hipError_t launch_select(const SelectArgs &a, int n_rows, int max_row_len, hipStream_t st);
-int select_cache_limit();
 int select_parts(int n_rows, int max_row_len);
 bool select_parts_fit(int k, int row_len);
 size_t select_parts_bytes(int n_rows, int max_row_len);

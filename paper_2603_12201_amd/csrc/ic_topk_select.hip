@@ -17,11 +17,10 @@
 //            wave scan per word on the DPP path, one scan over the (sweep, wave) cells, two
 //            barriers in all.  When ties are cut at the boundary: per-sweep scans of packed
 //            greater / equal counts.
-// Forms by row length: the radix select with the keys cached in LDS (launches whose rows have up to 8192 keys; up to
-// 32768 when k exceeds a quarter of the row), the candidate form further down (8193 to 131072 keys; two instances, the
-// one for rows of up to 32768 keys sized so that two rows are in flight per CU), the candidate form with a row spread
-// over several workgroups (few rows of more than 65536 keys), and the radix select re-reading the row on every sweep
-// (whatever is left).
+// That is the form for whatever the others leave over.  Forms by row length: the bins form (launches whose rows have up to
+// 32768 keys), the candidate form (32769 to 131072 keys, k up to a quarter of them), the candidate form with a row spread
+// over several workgroups (few rows of more than 65536 keys), and the radix select, with the keys cached in LDS (up to
+// 32768) or re-reading the row on every sweep.
 #include "ic_common.hpp"
 
 namespace ic {
@@ -46,9 +45,8 @@ constexpr int kBins1 = 4096;   // histogram bins: digits of 12, 12 and 8 key bit
 
 // Workgroup-wide descending scan over `nbins` counters: finds the digit d with
 // count(bins > d) < need <= count(bins >= d) and writes {d, need - count(bins > d), count(bin d)} to bc.
-// Every thread owns BPT consecutive bins, highest bins first.  A bin is the sum of R adjacent
-// counters (R > 1: the histogram was spread over R copies against same-address collisions).
-template <int NT, int BPT, int R = 1>
+// Every thread owns BPT consecutive bins, highest bins first.
+template <int NT, int BPT>
 __device__ __forceinline__ void find_digit(const uint32_t *cnt, uint32_t need, uint32_t *wsum, uint32_t *bc,
                                            int tid, int lane, int wave)
 {
@@ -58,17 +56,7 @@ __device__ __forceinline__ void find_digit(const uint32_t *cnt, uint32_t need, u
     uint32_t mine = 0;
 #pragma unroll
     for (int j = 0; j < BPT; ++j) {
-        if constexpr (R == 1) {
-            c[j] = cnt[top - j];
-        } else {
-            static_assert(R % 4 == 0, "copies are read as 16-byte vectors");
-            c[j] = 0;
-#pragma unroll
-            for (int q = 0; q < R / 4; ++q) {
-                const u32x4 v = *(const u32x4 *)(cnt + (top - j) * R + 4 * q);
-                c[j] += v[0] + v[1] + v[2] + v[3];
-            }
-        }
+        c[j] = cnt[top - j];
         mine += c[j];
     }
     uint32_t incl = wave_incl_scan(mine);
@@ -370,16 +358,9 @@ __global__ __launch_bounds__(NT) void select_kernel(SelectArgs a)
 // too many ties in the boundary bin) the workgroup falls back to the generic radix select on the same row.
 constexpr int kCandCap = 12288;          // candidate list entries (6 k for k = 2048)
 constexpr int kCandMinLen = 8192;        // shorter rows of a launch take the generic form at once
-constexpr int kCandFrom = 8192;          // launches whose longest row exceeds this use the candidate form (measured: with
-                                         // two rows in flight per CU it beats the LDS-cached generic form from here on;
-                                         // with one it did so only from 16384)
 constexpr int kCandMaxLen = 131072;      // bitmap capacity
 constexpr int kCandSample = 4096;
 constexpr int kBoundaryCap = 1024;       // boundary-bin members ranked exactly
-// A second instance for rows of up to kCandSmallLen keys: half the threads and half the LDS, so that two rows are in
-// flight per CU (a row's phases are chains of latencies; a second workgroup fills them)
-constexpr int kCandSmallLen = 32768;
-constexpr int kCandSmallCap = 6144;
 constexpr int cand_aux_words(int maxlen) { return maxlen / 32 > 2 * kBoundaryCap ? maxlen / 32 : 2 * kBoundaryCap; }
 constexpr int cand_lds_words(int nt, int maxlen, int cap)
 {
@@ -393,11 +374,7 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t x)
     return x;
 }
 
-// RES: every row of the launch has at most 16 vectors per thread, and all of them are requested before anything is
-// waited for (the row sits in registers while the sample is worked on).  Used by the half-size instance, where it
-// is worth 4 % of a strip; for the 64K-key rows of a decode step it changed nothing (their sweep is bound by the
-// vector ALU of the one CU a row has, not by the loads).
-template <int NT, int MAXLEN, int CAP, bool RES>
+template <int NT, int MAXLEN, int CAP>
 __global__ __launch_bounds__(NT) void select_cand_kernel(SelectArgs a)
 {
     static_assert(kCandSample % (4 * NT) == 0 && (MAXLEN / 32) % NT == 0, "whole sample vectors and bitmap words per thread");
@@ -430,7 +407,6 @@ __global__ __launch_bounds__(NT) void select_cand_kernel(SelectArgs a)
     // memory by every thread of every row).
     auto candidate_form = [&]() -> bool {
     if (nv < kCandMinLen || nv < 4 * a.k_sel || nv > MAXLEN) return false;   // workgroup-uniform
-    if (RES && nv > 16 * 4 * NT) return false;
     const float *row = a.strip + (int64_t)r * a.ld;
     int32_t *oidx = a.idx + ((int64_t)b * a.Tq + i) * a.k_sel;
     float *osel = a.sel ? a.sel + ((int64_t)b * a.Tq + i) * a.k_sel : nullptr;
@@ -449,9 +425,7 @@ __global__ __launch_bounds__(NT) void select_cand_kernel(SelectArgs a)
             if (p < nv) dst[j] = *(const f32x4 *)(row + p);   // may run past nv inside the row's padding; masked below
         }
     };
-    constexpr int NG = RES ? 4 : 2;
-    f32x4 rv[NG][kGroup];
-    f32x4 (&ga)[kGroup] = rv[0], (&gb)[kGroup] = rv[1];
+    f32x4 ga[kGroup], gb[kGroup];
     f32x4 sv[SV];
 #pragma unroll
     for (int u = 0; u < SV; ++u) {
@@ -459,12 +433,7 @@ __global__ __launch_bounds__(NT) void select_cand_kernel(SelectArgs a)
         const int p = (int)(((int64_t)blk * nv / 32) & ~(int64_t)3) + (tid & 31) * 4;   // p + 3 < nv: blocks are nv / 32 >= 256 apart
         sv[u] = *(const f32x4 *)(row + p);
     }
-    if constexpr (RES) {
-#pragma unroll
-        for (int gi = 0; gi < NG; ++gi) load_group(gi * kGroup, rv[gi]);
-    } else {
-        load_group(0, ga);
-    }
+    load_group(0, ga);
 
     // ---- sample: 32 blocks of 128 keys, a histogram of 4096 linear bins between the smallest and the largest of
     //      them (the scores of a row share a few exponents: bins of a key digit would be hit a hundred times each,
@@ -551,19 +520,13 @@ __global__ __launch_bounds__(NT) void select_cand_kernel(SelectArgs a)
                         }
             }
         };
-        if constexpr (RES) {
-#pragma unroll
-            for (int gi = 0; gi < NG; ++gi)
-                if (gi * kGroup < nsteps) sweep_group(gi * kGroup, rv[gi]);
-        } else {
 #pragma unroll 1
-            for (int c0 = 0; c0 < nsteps; c0 += 2 * kGroup) {
-                if (c0 + kGroup < nsteps) load_group(c0 + kGroup, gb);
-                sweep_group(c0, ga);
-                if (c0 + kGroup >= nsteps) break;
-                if (c0 + 2 * kGroup < nsteps) load_group(c0 + 2 * kGroup, ga);
-                sweep_group(c0 + kGroup, gb);
-            }
+        for (int c0 = 0; c0 < nsteps; c0 += 2 * kGroup) {
+            if (c0 + kGroup < nsteps) load_group(c0 + kGroup, gb);
+            sweep_group(c0, ga);
+            if (c0 + kGroup >= nsteps) break;
+            if (c0 + 2 * kGroup < nsteps) load_group(c0 + 2 * kGroup, ga);
+            sweep_group(c0 + kGroup, gb);
         }
         if (lane == 0) {
             atomicAdd(&misc[0], my_cnt);
@@ -675,6 +638,360 @@ __global__ __launch_bounds__(NT) void select_cand_kernel(SelectArgs a)
     }
 }
 
+struct RowView {
+    int b, i, nv;
+};
+__device__ __forceinline__ RowView row_view(const SelectArgs &a, int r)
+{
+    RowView v;
+    v.b = a.b0 + r / a.Ri;
+    v.i = a.i0 + r % a.Ri;
+    const int Lk_b = a.seq_lens ? max(0, min(a.seq_lens[v.b], a.Lk)) : a.Lk;
+    const int64_t nv64 = (a.seq_lens ? (int64_t)Lk_b - a.Tq : a.q_pos0) + (int64_t)v.i + 1;
+    v.nv = (int)(nv64 < 0 ? 0 : (nv64 > Lk_b ? Lk_b : nv64));
+    return v;
+}
+
+// ---- bins form -----------------------------------------------------------------------------------------------------
+// The whole row sits in registers (4 NV scores a thread), and one histogram of NB bins, LINEAR between the row's smallest
+// and largest score, finds the bin of the k-th largest: the scores of a row are spread over all of them, while bins of a
+// key's leading bits (the radix form's) are hit by a few exponents, a hundred times each, and LDS atomics on one address
+// take turns.  The few members of that bin are ranked exactly, which gives the k-th score and the position up to which
+// entries equal to it belong to the result.  Where the bin has more members than kRankCap (an outlier stretches the range,
+// ties), or a score is no finite number, keys take the scores' place, in bins linear between the smallest and the largest
+// one that is left, until that bin is small enough, or all of it is equal and the position is counted.  The selected
+// positions leave through a bitmap of the row, in whole lines.
+// What bounds it: with few rows a chain of nine barriers, with many their LDS atomics, one per key (before, rows of up to 8192
+// keys took the radix form, longer ones the candidate form; us, one row in parentheses the number of them): 10007 keys (1) 13.2
+// -> 7.8, 30011 (24) 17.0 -> 14.9, 64 of 1 to 512 (512) 8.7 -> 5.6, 2048 of 1 to 4096 (4096) 27 -> 20, of 6145 to 8192 (2048)
+// 44 -> 25, of 12289 to 16384 (4096) 137 -> 67, of 30721 to 32768 (2048) 93 -> 71.  With 64 keys a thread it is no faster
+// than the candidate form (64 K keys, 32 rows: 20.6 and 19.4).
+constexpr int kBinsLen = 32768;
+constexpr int kRankCap = 512;
+
+// Largest value over the 64 lanes of a wave, in every lane (no LDS traffic; lanes without a source keep their own).
+__device__ __forceinline__ uint32_t wave_max_dpp(uint32_t x)
+{
+#define IC_DPP_MAX(ctrl, rows) x = max(x, (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, ctrl, rows, 0xf, false))
+    IC_DPP_MAX(0x111, 0xf);              // row_shr:1, 2, 4, 8
+    IC_DPP_MAX(0x112, 0xf);
+    IC_DPP_MAX(0x114, 0xf);
+    IC_DPP_MAX(0x118, 0xf);
+    IC_DPP_MAX(0x142, 0xa);              // row_bcast:15 into rows 1, 3
+    IC_DPP_MAX(0x143, 0xc);              // row_bcast:31 into rows 2, 3
+#undef IC_DPP_MAX
+    return (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
+}
+
+template <int NT, int NV, int NB, int WPE>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE))) void select_bins_kernel(SelectArgs a)
+{
+    constexpr int NW = NT / 64;
+    constexpr int kWords = NT * NV / 8;        // bitmap
+    constexpr int kList = kRankCap * 2 > IC_MAX_K ? kRankCap * 2 : IC_MAX_K;
+    static_assert(NB % NT == 0, "whole bins per thread");
+    // the histogram; once it is read the boundary bin's members (keys, positions), then the selected positions, and behind
+    // them the bitmap
+    __shared__ __attribute__((aligned(16))) uint32_t smem[NB > kList + kWords ? NB : kList + kWords];
+    __shared__ uint32_t wsum[NW], bc[4], red[2 * NW];
+    __shared__ uint32_t misc[5];               // 0 members listed, 1 k-th key, 2 its position, 3 equal ones behind it, 4 odd scores
+    uint32_t *hist = smem, *member = smem, *member_at = smem + kRankCap, *out = smem, *bitmap = smem + kList;
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    request_args(a);
+    const int r = blockIdx.x;
+    const RowView rw = row_view(a, r);
+    if (rw.i >= a.Tq) return;
+    const int nv = rw.nv;
+    const float *row = a.strip + (int64_t)r * a.ld;
+    int32_t *oidx = a.idx + ((int64_t)rw.b * a.Tq + rw.i) * a.k_sel;
+    float *osel = a.sel ? a.sel + ((int64_t)rw.b * a.Tq + rw.i) * a.k_sel : nullptr;
+    const int k = a.k_sel;
+    if (nv <= k) {                             // every visible key is selected
+        for (int s = tid; s < k; s += NT) {
+            oidx[s] = s < nv ? s : -1;
+            if (osel) osel[s] = s < nv ? row[s] : -INFINITY;
+        }
+        return;
+    }
+    const int nsteps = (nv + 4 * NT - 1) / (4 * NT);
+    u32x4 v[NV];                               // scores, later maybe keys
+#pragma unroll
+    for (int j = 0; j < NV; ++j) {
+        const int p = (j * NT + tid) * 4;
+        if (p < nv) v[j] = *(const u32x4 *)(row + p);          // may run past nv inside the row's padding
+    }
+    const float f0 = row[0];
+    for (int e = tid; e < NB; e += NT) hist[e] = 0;
+    if (tid < 5) misc[tid] = 0;
+    __syncthreads();
+    // Slots behind the row hold its first score, so that the sweeps below need no test; what they add is taken off the
+    // counts again, and their bits off the bitmap.
+    const uint32_t pad = (uint32_t)(nsteps * 4 * NT - nv);
+    // (opaque values: the compiler would keep the steps' conditions, positions and bins from one sweep to the next)
+    auto again = [](int n) { asm volatile("" : "+s"(n)); return n; };
+    auto each = [&](auto f) __attribute__((always_inline)) {
+        const int steps = again(nsteps);
+        int at = 4 * tid;
+        asm volatile("" : "+v"(at));
+#pragma unroll
+        for (int j = 0; j < NV; ++j)
+            if (j < steps) {                   // workgroup-uniform
+#pragma unroll
+                for (int e = 0; e < 4; ++e) f(v[j][e], at + j * NT * 4 + e);
+            }
+    };
+    uint32_t lo, hi;
+    auto bounds = [&](uint32_t mx, uint32_t mn) {              // of the threads' largest and smallest keys
+        mx = wave_max_dpp(mx);
+        mn = wave_max_dpp(~mn);
+        if constexpr (NW > 1) {
+            if (lane == 0) {
+                red[wave] = mx;
+                red[NW + wave] = mn;
+            }
+            __syncthreads();
+            mx = wave_max_dpp(red[lane % NW]);
+            mn = wave_max_dpp(red[NW + lane % NW]);
+        }
+        hi = mx;
+        lo = ~mn;
+    };
+    bool odd;                                  // a score is infinite or none
+    {
+        float mx = f0, mn = f0, z = 0.f;
+        const int end = again(nv);
+#pragma unroll
+        for (int j = 0; j < NV; ++j)
+            if (j < nsteps) {
+                const int p = (j * NT + tid) * 4;
+                if (p + 3 >= end) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) v[j][e] = p + e < end ? v[j][e] : __float_as_uint(f0);
+                }
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float x = __uint_as_float(v[j][e]);
+                    mx = fmaxf(mx, x);
+                    mn = fminf(mn, x);
+                    z = __builtin_fmaf(x, 0.f, z);
+                }
+            }
+        if (__ballot(!(z == 0.f)) != 0ull && lane == 0) misc[4] = 1u;
+        bounds(score_key(mx), score_key(mn));
+        if constexpr (NW == 1) __syncthreads();
+        odd = misc[4] != 0u;
+    }
+    auto mark = [&](auto pred) __attribute__((always_inline)) {    // bit p of the bitmap: pred(key, p); eight lanes make a word
+        const int steps = again(nsteps);
+        int at = 4 * tid;
+        asm volatile("" : "+v"(at));
+#pragma unroll
+        for (int j = 0; j < NV; ++j)
+            if (j < steps) {
+                uint32_t m = 0;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) m |= (pred(v[j][e], (uint32_t)(at + j * NT * 4 + e)) ? 1u : 0u) << e;
+                m <<= 4 * (lane & 7);
+                m |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)m, 0xB1, 0xf, 0xf, true);    // the neighbour in a pair,
+                m |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)m, 0x4E, 0xf, 0xf, true);    // the other pair of four,
+                m |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)m, 0x141, 0xf, 0xf, true);   // the other four of eight lanes
+                if ((lane & 7) == 0) bitmap[(at >> 5) + j * (NT / 8)] = m;
+            }
+    };
+    // this thread's 4 NV bits of it, from position at0, and the number of set ones in front of them
+    constexpr int MW = NV >= 8 ? NV / 8 : 1;
+    const int at0 = tid * 4 * NV;
+    auto mine = [&](uint32_t (&m)[MW]) __attribute__((always_inline)) -> uint32_t {
+        uint32_t n = 0;
+#pragma unroll
+        for (int q = 0; q < MW; ++q) {
+            const int left = nv - (at0 + 32 * q);
+            m[q] = 0;
+            if (left > 0) {
+                m[q] = bitmap[(at0 >> 5) + q];
+                if constexpr (NV < 8) m[q] = (m[q] >> (at0 & 31)) & ((1u << (4 * NV)) - 1);
+                if (left < 32) m[q] &= (1u << left) - 1;
+            }
+            n += (uint32_t)__popc(m[q]);
+        }
+        uint32_t before = wave_incl_scan(n);
+        if (lane == 63) wsum[wave] = before;
+        __syncthreads();
+        before -= n;
+#pragma unroll
+        for (int wv = 0; wv < NW - 1; ++wv)
+            if (wv < wave) before += wsum[wv];
+        return before;
+    };
+    uint32_t need = (uint32_t)k;
+    // the members of the boundary bin, listed, ranked (keys descending, positions ascending): the last one wanted
+    auto rank = [&](uint32_t n_b) __attribute__((always_inline)) {
+        __syncthreads();
+        for (uint32_t m = tid; m < n_b; m += NT) {
+            const uint32_t xm = member[m], pm = member_at[m];
+            uint32_t ahead = 0, behind = 0;    // members that beat this one: larger, or equal at a lower position
+#pragma unroll 4
+            for (uint32_t o = 0; o < n_b; ++o) {
+                const uint32_t xo = member[o], po = member_at[o];
+                ahead += (xo > xm || (xo == xm && po < pm)) ? 1u : 0u;
+                behind += (xo == xm && po > pm) ? 1u : 0u;
+            }
+            if (ahead + 1 == need) {
+                misc[1] = xm;
+                misc[2] = pm;
+                misc[3] = behind;
+            }
+        }
+        __syncthreads();
+    };
+    auto list = [&](uint32_t key, int p) {
+        const uint32_t m = atomicAdd(&misc[0], 1u);
+        member[m] = key;
+        member_at[m] = (uint32_t)p;
+    };
+    auto clear = [&]() {
+        for (int e = tid; e < NB; e += NT) hist[e] = 0;
+    };
+    // bins of scores
+    const float first = key_score(lo), scale = (NB - 0.5f) / (key_score(hi) - first);
+    bool scores = false;                       // they decide
+    if (!odd && scale > 0.f && scale < 3e38f) {                // (one value only, or a range beyond floats: no bins)
+        // (monotone, NB - 1 at most)
+        auto bin = [](float x, float from, float by) { return (uint32_t)((x - from) * by); };
+        if (tid == 0) atomicSub(&hist[bin(f0, first, scale)], pad);
+        each([&](uint32_t x, int) { atomicAdd(&hist[bin(__uint_as_float(x), first, scale)], 1u); });
+        __syncthreads();
+        find_digit<NT, NB / NT>(hist, need, wsum, bc, tid, lane, wave);
+        const uint32_t b = bc[0], n_b = bc[2];
+        need = bc[1];
+        float from = first;                    // (opaque: bins are worked out again)
+        asm volatile("" : "+v"(from));
+        if (n_b <= (uint32_t)kRankCap) {
+            const int len = again(nv);
+            each([&](uint32_t x, int p) {
+                if (bin(__uint_as_float(x), from, scale) == b && p < len) list(score_key(__uint_as_float(x)), p);
+            });
+            rank(n_b);
+            scores = true;
+        } else {
+            uint32_t mx = 0u, mn = 0xFFFFFFFFu;                // (a thread without members has neither)
+            each([&](uint32_t x, int) {
+                if (bin(__uint_as_float(x), from, scale) == b) {
+                    mx = max(mx, score_key(__uint_as_float(x)));
+                    mn = min(mn, score_key(__uint_as_float(x)));
+                }
+            });
+            __syncthreads();                   // (everybody has read hist, bc and red)
+            clear();
+            bounds(mx, mn);
+        }
+    } else if (odd) {                          // (the bounds so far know no NaN)
+        uint32_t mx = 0u, mn = 0xFFFFFFFFu;
+        each([&](uint32_t x, int) {
+            mx = max(mx, score_key(__uint_as_float(x)));
+            mn = min(mn, score_key(__uint_as_float(x)));
+        });
+        __syncthreads();
+        bounds(mx, mn);
+    }
+    uint32_t tau, ptau;
+    bool cut;                                  // entries equal to tau behind ptau are left out
+    if (!scores) {
+        // bins of keys
+#pragma unroll
+        for (int j = 0; j < NV; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[j][e] = score_key(__uint_as_float(v[j][e]));
+        const uint32_t x0 = score_key(f0);
+        while (lo != hi) {
+#pragma unroll
+            for (int j = 0; j < NV; ++j) asm volatile("" : "+v"(v[j]));   // (nothing is worked out ahead of the loop and kept)
+            const int bits = 32 - __clz((int)(hi - lo));
+            constexpr int kBits = 31 - __builtin_clz(NB);
+            const int sh = bits > kBits ? bits - kBits : 0;
+            const uint32_t span = hi - lo;
+            if constexpr (NW == 1) __syncthreads();
+            if (tid == 0 && x0 - lo <= span) atomicSub(&hist[(x0 - lo) >> sh], pad);
+            each([&](uint32_t x, int) { if (x - lo <= span) atomicAdd(&hist[(x - lo) >> sh], 1u); });
+            __syncthreads();
+            find_digit<NT, NB / NT>(hist, need, wsum, bc, tid, lane, wave);
+            const uint32_t n_b = bc[2];
+            need = bc[1];
+            // the bin's keys (`from` opaque: differences are worked out again)
+            uint32_t from = lo + (bc[0] << sh);
+            const uint32_t last = min((1u << sh) - 1u, hi - from);
+            asm volatile("" : "+v"(from));
+            if (n_b <= (uint32_t)kRankCap) {
+                const int len = again(nv);
+                each([&](uint32_t x, int p) { if (x - from <= last && p < len) list(x, p); });
+                rank(n_b);
+                break;
+            }
+            uint32_t mx = 0u, mn = 0xFFFFFFFFu;
+            each([&](uint32_t x, int) {
+                if (x - from <= last) {
+                    mx = max(mx, x);
+                    mn = min(mn, x);
+                }
+            });
+            __syncthreads();
+            clear();
+            bounds(mx, mn);
+        }
+    }
+    if (!scores && lo == hi) {                 // all members are equal: count up to the last one wanted
+        __syncthreads();
+        tau = lo;
+        cut = true;
+        mark([&](uint32_t x, uint32_t) { return x == tau; });
+        __syncthreads();
+        uint32_t m[MW];
+        uint32_t before = mine(m);
+#pragma unroll
+        for (int q = 0; q < MW; ++q) {
+            const uint32_t n = (uint32_t)__popc(m[q]);
+            if (before < need && need <= before + n) {
+                for (uint32_t d = need - before; d > 1; --d) m[q] &= m[q] - 1;
+                misc[2] = (uint32_t)(at0 + 32 * q + __builtin_ctz(m[q]));
+            }
+            before += n;
+        }
+        __syncthreads();
+    } else {
+        tau = misc[1];
+        cut = misc[3] != 0u;
+    }
+    ptau = misc[2];
+    if (scores) {
+        const float t = key_score(tau);
+        if (!cut)
+            mark([&](uint32_t x, uint32_t) { return __uint_as_float(x) >= t; });
+        else
+            mark([&](uint32_t x, uint32_t p) { return __uint_as_float(x) > t || (__uint_as_float(x) == t && p <= ptau); });
+    } else if (!cut)
+        mark([&](uint32_t x, uint32_t) { return x >= tau; });
+    else
+        mark([&](uint32_t x, uint32_t p) { return x > tau || (x == tau && p <= ptau); });
+    __syncthreads();
+    {
+        uint32_t m[MW];
+        uint32_t slot = mine(m);
+#pragma unroll
+        for (int q = 0; q < MW; ++q)
+            while (m[q]) {
+                if (slot < (uint32_t)k) out[slot] = (uint32_t)(at0 + 32 * q + __builtin_ctz(m[q]));   // (always, for a consistent select)
+                m[q] &= m[q] - 1;
+                ++slot;
+            }
+    }
+    __syncthreads();
+    for (int s = tid; s < k; s += NT) {
+        oidx[s] = (int32_t)out[s];
+        if (osel) osel[s] = key_score(score_key(row[out[s]]));   // (-0 as +0)
+    }
+}
+
 // ---- parts form (few long rows) ---------------------------------------------------------------------------------
 // A long row of a decode step has one workgroup in the forms above, and that one CU is what bounds it (a 200 000-key row,
 // past the candidate form's bitmap, was streamed four times by it: 150 us).  Here a row is cut into parts with a
@@ -703,19 +1020,6 @@ constexpr int kFinishCap = 12288;        // candidates of a row
 // per row: [0] T0, then the lists' lengths; the lists follow the heads of all rows
 __host__ __device__ inline size_t part_head_words(int n_parts) { return (size_t)(4 + n_parts * kPartWaves + 63) / 64 * 64; }
 
-struct RowView {
-    int b, i, nv;
-};
-__device__ __forceinline__ RowView row_view(const SelectArgs &a, int r)
-{
-    RowView v;
-    v.b = a.b0 + r / a.Ri;
-    v.i = a.i0 + r % a.Ri;
-    const int Lk_b = a.seq_lens ? max(0, min(a.seq_lens[v.b], a.Lk)) : a.Lk;
-    const int64_t nv64 = (a.seq_lens ? (int64_t)Lk_b - a.Tq : a.q_pos0) + (int64_t)v.i + 1;
-    v.nv = (int)(nv64 < 0 ? 0 : (nv64 > Lk_b ? Lk_b : nv64));
-    return v;
-}
 // rows the sample can speak for
 __device__ __forceinline__ bool part_row(const SelectArgs &a, int nv) { return nv >= kCandMinLen && nv >= 4 * a.k_sel; }
 
@@ -956,8 +1260,6 @@ size_t select_lds_bytes(int cache_elems)
 
 } // namespace
 
-int select_cache_limit() { return 32768; }
-
 // A row of this length leaves about 2 k + 1 / 128 of its keys as candidates (the rank that select_part_kernel takes from the
 // sample).  Where the second launch does not hold that many, the row would go to the radix select behind two launches for
 // nothing (k = 2048: from 1.05 M keys; 1.1 M keys 745 us without, 755 with them).  The sample scatters by some 14 %: a row
@@ -1012,45 +1314,42 @@ hipError_t launch_select_parts(const SelectArgs &a_in, int n_rows, int max_row_l
     return hipGetLastError();
 }
 
+namespace {
+template <int NT, int NV, int NB, int WPE>
+hipError_t launch_bins(const SelectArgs &a, int n_rows, int max_row_len, hipStream_t st)
+{
+    if (max_row_len > NT * NV * 4) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((select_bins_kernel<NT, NV, NB, WPE>), dim3((unsigned)n_rows), dim3(NT), 0, st, a);
+    return hipGetLastError();
+}
+} // namespace
+
 hipError_t launch_select(const SelectArgs &a_in, int n_rows, int max_row_len, hipStream_t st)
 {
     if (n_rows <= 0) return hipSuccess;
     SelectArgs a = a_in;
-    int cache = max_row_len <= select_cache_limit() ? (max_row_len + 63) / 64 * 64 : 0;
-    if (max_row_len <= a.k_sel) cache = 0;     // short rows never reach the radix path
-    a.cache_elems = cache;
-    const size_t lds = select_lds_bytes(cache);
-    // opt in once per process to the largest LDS footprint either cached variant can ask for
-    static hipError_t attr256 = hipFuncSetAttribute((const void *)select_kernel<256>,
-                                                    hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                    (int)select_lds_bytes(8192));
-    static hipError_t attr1024 = hipFuncSetAttribute((const void *)select_kernel<1024>,
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                     (int)select_lds_bytes(select_cache_limit()));
-    if (attr256 != hipSuccess) return attr256;
-    if (attr1024 != hipSuccess) return attr1024;
-    constexpr int lds_big = cand_lds_words(1024, kCandMaxLen, kCandCap) * (int)sizeof(uint32_t);
-    constexpr int lds_small = cand_lds_words(512, kCandSmallLen, kCandSmallCap) * (int)sizeof(uint32_t);
-    static hipError_t attr_cand = hipFuncSetAttribute((const void *)select_cand_kernel<1024, kCandMaxLen, kCandCap, false>,
-                                                      hipFuncAttributeMaxDynamicSharedMemorySize, lds_big);
-    static hipError_t attr_cand_s = hipFuncSetAttribute((const void *)select_cand_kernel<512, kCandSmallLen, kCandSmallCap, true>,
-                                                        hipFuncAttributeMaxDynamicSharedMemorySize, lds_small);
-    if (attr_cand != hipSuccess) return attr_cand;
-    if (attr_cand_s != hipSuccess) return attr_cand_s;
-    if (max_row_len > kCandFrom && max_row_len <= kCandMaxLen && max_row_len >= 4 * a.k_sel) {
+    a.cache_elems = 0;
+    // The bins form, in the smallest workgroup that holds the row: its barriers and its start cost less, and more rows are
+    // in flight per CU.  Rows of 16384 keys take 512 threads where there are few of them (1 row of 10007 keys: 7.8 us,
+    // 10.5 with 256; 4096 rows of 14336 on average 73 and 67).
+    if (max_row_len <= 1024) return launch_bins<128, 2, 512, 8>(a, n_rows, max_row_len, st);
+    if (max_row_len <= 2048) return launch_bins<128, 4, 512, 8>(a, n_rows, max_row_len, st);
+    if (max_row_len <= 4096) return launch_bins<256, 4, 1024, 8>(a, n_rows, max_row_len, st);
+    if (max_row_len <= 8192) return launch_bins<256, 8, 1024, 7>(a, n_rows, max_row_len, st);
+    if (max_row_len <= 16384 && n_rows > 512) return launch_bins<256, 16, 2048, 4>(a, n_rows, max_row_len, st);
+    if (max_row_len <= 16384) return launch_bins<512, 8, 2048, 6>(a, n_rows, max_row_len, st);
+    if (max_row_len <= kBinsLen) return launch_bins<512, 16, 4096, 4>(a, n_rows, max_row_len, st);
+    if (max_row_len <= kCandMaxLen && max_row_len >= 4 * a.k_sel) {
         // one read of the row, a sampled threshold and a candidate list (falls back row by row)
-        if (max_row_len <= kCandSmallLen)
-            hipLaunchKernelGGL((select_cand_kernel<512, kCandSmallLen, kCandSmallCap, true>), dim3((unsigned)n_rows), dim3(512), lds_small, st, a);
-        else
-            hipLaunchKernelGGL((select_cand_kernel<1024, kCandMaxLen, kCandCap, false>), dim3((unsigned)n_rows), dim3(1024), lds_big, st, a);
+        constexpr int lds = cand_lds_words(1024, kCandMaxLen, kCandCap) * (int)sizeof(uint32_t);
+        static hipError_t attr = hipFuncSetAttribute((const void *)select_cand_kernel<1024, kCandMaxLen, kCandCap>,
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        if (attr != hipSuccess) return attr;
+        hipLaunchKernelGGL((select_cand_kernel<1024, kCandMaxLen, kCandCap>), dim3((unsigned)n_rows), dim3(1024), lds, st, a);
         return hipGetLastError();
     }
-    if (max_row_len <= 8192)
-        hipLaunchKernelGGL((select_kernel<256>), dim3((unsigned)n_rows), dim3(256), lds, st, a);
-    else
-        // rows up to the cache limit stay in LDS after one read; longer ones (beyond the candidate form's range and
-        // too many for the parts form, or with k above a quarter of the row) are streamed on every sweep
-        hipLaunchKernelGGL((select_kernel<1024>), dim3((unsigned)n_rows), dim3(1024), lds, st, a);
+    // longer rows, too many for the parts form, are streamed on every sweep
+    hipLaunchKernelGGL((select_kernel<1024>), dim3((unsigned)n_rows), dim3(1024), select_lds_bytes(0), st, a);
     return hipGetLastError();
 }
 

@@ -1,0 +1,76 @@
+"""Top-k of rows of up to 32768 keys: lengths around the limits of every instance, with few and with many rows, and scores
+that drive a row through every way out (a full boundary bin, bins of a bin, ties cut at any place, infinite scores)."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ic():
+    import paper_2603_12201_amd as m
+    m.lib()
+    return m
+
+
+def check(ic, oracle, q, k, w, ks, p0):
+    """The kernel's choice against the oracle's on the kernel's own scores: equal, position for position."""
+    idx, sel = ic.indexer_topk(q, k, w, ks, p0, want_scores=True)
+    sc = ic.debug_indexer_scores(q, k, w, p0, 0, q.shape[1]).cpu().numpy()
+    idx, sel = idx.cpu().numpy(), sel.cpu().numpy()
+    for b in range(q.shape[0]):
+        for i in range(q.shape[1]):
+            n = min(p0 + i + 1, k.shape[1])
+            want = oracle.topk_row(sc[b, i], n, ks)["idx"]
+            want = np.sort(want[want >= 0])
+            assert np.array_equal(idx[b, i][:len(want)], want), (b, i, n)
+            assert np.all(idx[b, i][len(want):] == -1)
+            assert np.array_equal(sel[b, i][:len(want)], sc[b, i][want])
+
+
+@pytest.mark.parametrize("L", [1, 5, 511, 1024, 1025, 2048, 2049, 4096, 4097, 8192, 8193, 16384, 16385, 32767, 32768])
+@pytest.mark.parametrize("ks", [1, 64, 2048])
+def test_lengths(ic, oracle, L, ks):
+    print("[case] bins L=%d k=%d" % (L, ks), flush=True)
+    T = min(L, 3)
+    g = torch.Generator().manual_seed(L + ks)
+    q = (torch.randn((1, T, 4, 64), generator=g) / 8).to(torch.bfloat16).cuda()
+    k = torch.randn((1, L, 64), generator=g).to(torch.bfloat16).cuda()
+    w = torch.randn((1, T, 4), generator=g).cuda()
+    check(ic, oracle, q, k, w, ks, L - T)
+
+
+def test_many_rows(ic, oracle):
+    """More rows than the few-row rule of 16384 keys, from a row with one key on."""
+    print("[case] bins, 1100 rows of 15000", flush=True)
+    g = torch.Generator().manual_seed(8)
+    q = (torch.randn((1, 1100, 4, 64), generator=g) / 8).to(torch.bfloat16).cuda()
+    k = torch.randn((1, 15000, 64), generator=g).to(torch.bfloat16).cuda()
+    w = torch.rand((1, 1100, 4), generator=g).cuda()
+    idx = ic.indexer_topk(q, k, w, 300, 13900).cpu().numpy()
+    for i in range(0, 1100, 90):
+        sc = ic.debug_indexer_scores(q, k, w, 13900, i, 1).cpu().numpy()
+        assert np.array_equal(idx[0, i], np.sort(oracle.topk_row(sc[0, 0], 13901 + i, 300)["idx"])), i
+
+
+@pytest.mark.parametrize("L", [700, 1500, 4000, 7000, 12000, 30000])
+@pytest.mark.parametrize("kind", ["rising", "falling", "constant", "two_values", "levels", "outlier", "wide", "signed", "infinite", "lowest"])
+def test_score_shapes(ic, oracle, L, kind):
+    # one head, one-hot q: the score of a key is w times the key's own feature where that is positive
+    print("[case] bins, %s scores, L=%d" % (kind, L), flush=True)
+    x = torch.arange(L, dtype=torch.float32)
+    g = torch.Generator().manual_seed(L)
+    r = torch.rand(L, generator=g)
+    inf = float("inf")
+    v = {"rising": 1 + x / 64, "falling": 1 + (L - x) / 64, "constant": torch.ones(L), "two_values": 1.0 + (x % 41 == 0).float(),
+         "levels": 1.0 + (x % 3), "outlier": 1 + r + (x == L // 2).float() * 1e30, "wide": torch.exp2(200 * r - 100),
+         "signed": 1 + r, "infinite": torch.where(x % 50 == 7, torch.tensor(inf), 1 + r), "lowest": torch.where(x % 5 != 0, torch.tensor(inf), 1 + r)}[kind]
+    q = torch.zeros((1, 2, 1, 64)); q[..., 5] = 1.0
+    k = torch.zeros((1, L, 64)); k[0, :, 5] = v
+    w = torch.ones((1, 2, 1))
+    if kind in ("signed", "lowest"):           # every score negative, or -inf
+        w = -w
+    q, k, w = q.to(torch.bfloat16).cuda(), k.to(torch.bfloat16).cuda(), w.cuda()
+    for ks in (7, 600):
+        check(ic, oracle, q, k, w, ks, L - 2)
