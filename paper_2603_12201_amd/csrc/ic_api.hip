@@ -75,7 +75,7 @@ size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 // Default strip budget when the caller asks how much workspace to bring.
 constexpr size_t kStripBudget = (size_t)1 << 30;   // 1 GiB of score rows in flight
-constexpr size_t kSmallStrip = (size_t)64 << 20;    // problems whose whole score matrix is below this keep it in one strip
+constexpr size_t kSmallStrip = (size_t)128 << 20;   // problems whose whole score matrix is below this keep it in one strip
 constexpr int kMinStripRows = 16;
 
 ic_status check_indexer(const ic_indexer_desc *d)
@@ -520,23 +520,6 @@ size_t lead_bytes(const ic_attn_desc *d, int n_tensors)
     return n ? align_up((size_t)n_tensors * d->B * lead_chunks(n) * sizeof(int32_t)) : 0;
 }
 
-// Workgroups per sequence that share the rows left of it: rounds of all sequences' workgroups, each as long as the longest
-// chain.
-int rest_workgroups(const ic_attn_desc *d, int rows)
-{
-    const double query = kGranuleUs * ((d->k_sel + 31) / 32 + 1);
-    int best = 1;
-    double time = 1e30;
-    for (int g = 1; g <= rows && g <= 256; ++g) {
-        const double t = (double)(((int64_t)d->B * g + 255) / 256) * ((rows + g - 1) / g * query + kLaunchUs);
-        if (t <= time) {
-            time = t;
-            best = g;
-        }
-    }
-    return best;
-}
-
 // Partials of the rows behind the candidates where they are split over the chip on their own.
 size_t lead_tail_bytes(const ic_attn_desc *d)
 {
@@ -599,38 +582,80 @@ ic::AttnArgs attn_args(const ic_layer *layers, int n_layers, const int32_t *idx,
 ic_status run_attn_layers(const ic_layer *layers, int n_layers, const int32_t *idx, float *lse, void *ws, size_t ws_bytes,
                           hipStream_t st, const ic_paged_cache *pc, Causal c, int skipped = 0);
 
-// One layer whose index tensor has counted leading rows: those (lead) in the dense form unless `dense` is off, then the
-// others.  lead2: counts of a second index tensor; only the rows that are leading in both are left out.
-ic_status run_attn_lead(const ic_layer *L, const int32_t *idx, const int32_t *lead, const int32_t *lead2, bool dense, float *lse,
-                        void *ws, size_t ws_bytes, hipStream_t st)
+// A layer with an index tensor whose leading rows are counted (lead); lead2: counts of a second tensor, only the rows that are
+// leading in both are left out.
+struct LeadJob {
+    ic_layer L;
+    const int32_t *idx, *lead, *lead2;
+};
+
+ic_status run_lead_dense(const LeadJob &j, float *lse, hipStream_t st)
 {
-    const ic_attn_desc *d = &L->at;
+    const ic_attn_desc *d = &j.L.at;
+    const int n = lead_queries(d);
+    ProfScope ps(2, st);
+    const ic::DenseArgs da{n, d->Lk - d->Tq, j.lead, lead_chunks(n)};
+    hipError_t e = ic::launch_attn_dense(attn_args(&j.L, 1, j.idx, lse, nullptr, kUnknown), da, st);
+    if (e != hipSuccess) return fail(IC_ERR_HIP, "dense attention launch failed: %s", hipGetErrorString(e));
+    return IC_OK;
+}
+
+// The other rows of up to kMaxBatchLayers layers of one shape.  (A launch takes up to kRestSeqs sequences; lse: one layer only.)
+ic_status run_lead_rest(const LeadJob *jobs, int n_jobs, float *lse, void *ws, size_t ws_bytes, hipStream_t st)
+{
+    const ic_attn_desc *d = &jobs[0].L.at;
     const LeadPlan lp = lead_plan(d);
     const int n = lp.n, n_chunks = lead_chunks(n);
-    if (dense) {
-        ProfScope ps(2, st);
-        const ic::DenseArgs da{n, d->Lk - d->Tq, lead, n_chunks};
-        hipError_t e = ic::launch_attn_dense(attn_args(L, 1, idx, lse, nullptr, kUnknown), da, st);
-        if (e != hipSuccess) return fail(IC_ERR_HIP, "dense attention launch failed: %s", hipGetErrorString(e));
-    }
     const bool along = lp.along;
-    {
+    const int most = std::max(1, ic::kRestSeqs / n_jobs);
+    for (int b0 = 0; b0 < d->B; b0 += most) {
         ProfScope ps(2, st);
-        ic::AttnArgs a = attn_args(L, 1, idx, lse, nullptr, kUnknown);
+        ic::AttnArgs a = attn_args(&jobs[0].L, 1, jobs[0].idx, lse ? lse + (int64_t)b0 * d->Tq * d->H_q : nullptr, nullptr, kUnknown);
         a.n_splits = 1;
         a.split_len = (d->k_sel + 63) / 64 * 64;
-        const int rows = along ? d->Tq : n;
-        const ic::RestArgs ra{lead, lead2, n_chunks, rows, rest_workgroups(d, rows)};
+        a.B = std::min(most, d->B - b0);
+        ic::RestArgs ra;
+        memset(&ra, 0, sizeof ra);
+        ra.n_jobs = n_jobs;
+        ra.n_chunks = n_chunks;
+        ra.n_rows = along ? d->Tq : n;
+        const int64_t r0 = (int64_t)b0 * d->Tq;
+        for (int i = 0; i < n_jobs; ++i) {
+            const LeadJob &j = jobs[i];
+            a.Qs[i] = (const char *)j.L.Q + r0 * d->H_q * d->d_qk * 2;
+            a.KVs[i] = (const char *)j.L.KV + (int64_t)b0 * d->Lk * d->row_elems * 2;
+            a.Os[i] = (char *)j.L.O + r0 * d->H_q * d->d_v * 2;
+            ra.idx[i] = j.idx + r0 * d->k_sel;
+            ra.lead[i] = j.lead + (int64_t)b0 * n_chunks;
+            ra.lead2[i] = j.lead2 + (int64_t)b0 * n_chunks;
+        }
         hipError_t e = ic::launch_attn_rest(a, ra, st);
         if (e != hipSuccess) return fail(IC_ERR_HIP, "sparse attention launch failed: %s", hipGetErrorString(e));
     }
     if (along || n == d->Tq) return IC_OK;
-    ic_layer r = *L;
-    r.at = rows_behind(d, n);
-    r.Q = (const char *)r.Q + (int64_t)n * d->H_q * d->d_qk * 2;
-    r.O = (char *)r.O + (int64_t)n * d->H_q * d->d_v * 2;
-    return run_attn_layers(&r, 1, idx + (int64_t)n * d->k_sel, lse ? lse + (int64_t)n * d->H_q : nullptr, ws, ws_bytes, st, nullptr,
-                           kUnknown, n);
+    for (int i = 0; i < n_jobs; ++i) {
+        ic_layer r = jobs[i].L;
+        r.at = rows_behind(d, n);
+        r.Q = (const char *)r.Q + (int64_t)n * d->H_q * d->d_qk * 2;
+        r.O = (char *)r.O + (int64_t)n * d->H_q * d->d_v * 2;
+        const ic_status s = run_attn_layers(&r, 1, jobs[i].idx + (int64_t)n * d->k_sel, lse ? lse + (int64_t)n * d->H_q : nullptr, ws,
+                                            ws_bytes, st, nullptr, kUnknown, n);
+        if (s != IC_OK) return s;
+    }
+    return IC_OK;
+}
+
+// Launches of consecutive jobs of one shape, at most `most` together.
+template <typename F> ic_status lead_groups(const std::vector<LeadJob> &jobs, int most, F run)
+{
+    for (size_t i = 0; i < jobs.size();) {
+        size_t n = 1;
+        while (i + n < jobs.size() && n < (size_t)most && memcmp(&jobs[i].L.at, &jobs[i + n].L.at, sizeof jobs[i].L.at) == 0) ++n;
+        const ic_status s = run(i, (int)n);
+        if (s != IC_OK) return s;
+        i += n;
+    }
+    return IC_OK;
 }
 
 // c: idx is this library's own (rows that can hold fewer than k_sel entries end in -1s, and the kernels leave their empty
@@ -750,8 +775,9 @@ ic_status ic_sparse_attn_lead(const ic_attn_desc *d, const void *Q, const void *
     int32_t *const lead = (int32_t *)workspace;
     s = count_lead(d, &idx, 1, lead, st);
     if (s != IC_OK) return s;
-    const ic_layer l = attn_layer(d, Q, KV, O);
-    return run_attn_lead(&l, idx, lead, lead, true, lse, (char *)workspace + lb, workspace_bytes - lb, st);
+    const LeadJob job = {attn_layer(d, Q, KV, O), idx, lead, lead};
+    s = run_lead_dense(job, lse, st);
+    return s != IC_OK ? s : run_lead_rest(&job, 1, lse, (char *)workspace + lb, workspace_bytes - lb, st);
 }
 
 ic_status ic_sparse_attn(const ic_attn_desc *d, const void *Q, const void *KV, const int32_t *idx, void *O,
@@ -1019,6 +1045,108 @@ size_t sim_lead_bytes(const ic_layer *layers, int n_layers)
 
 size_t sim_o_bytes(const ic_attn_desc *a) { return align_up((size_t)a->B * a->Tq * a->H_q * a->d_v * 2); }
 
+// What the rows that are the same in both outputs of a pair compare to, per layer.
+size_t sim_self_bytes(const ic_attn_desc *a, int n_layers) { return align_up((size_t)n_layers * a->B * a->Tq * sizeof(double)); }
+
+// Outputs under reused indices that are computed, and compared, together where leading rows are counted: few rows of a pair are
+// left (a third of 3000), and every launch of them ends in a round of a part of the CUs (952 rows: 3.7 rounds in four).  Up to
+// 1 GiB of them: a launch of more rows loses less.
+constexpr size_t kSimOutputs = (size_t)1 << 30;
+int sim_outputs(const ic_attn_desc *a, int n_layers)
+{
+    const int64_t pairs = (int64_t)n_layers * (n_layers - 1) / 2, fit = (int64_t)(kSimOutputs / sim_o_bytes(a));
+    return (int)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(pairs, fit), ic::kMaxBatchLayers));
+}
+
+// Whether no layer's output overlaps another one's output or inputs: only then may they all be written before the first pair
+// is compared.
+bool sim_apart(const ic_layer *layers, int n_layers)
+{
+    const ic_attn_desc *d = &layers[0].at;
+    const size_t nq = (size_t)d->B * d->Tq, ob = nq * d->H_q * d->d_v * 2, qb = nq * d->H_q * d->d_qk * 2;
+    for (int i = 0; i < n_layers; ++i) {
+        const Range o{(const char *)layers[i].O, ob};
+        for (int j = 0; j < n_layers; ++j) {
+            if (j == i) continue;
+            const ic_layer &l = layers[j];
+            if (o.meets(Range{(const char *)l.O, ob}) || o.meets(Range{(const char *)l.Q, qb}) ||
+                o.meets(Range{(const char *)l.KV, (size_t)d->B * l.at.Lk * l.at.row_elems * 2}))
+                return false;
+        }
+    }
+    return true;
+}
+
+// The layers whose leading rows are counted: outputs under their own indices, and for every pair those under reused ones.  Rows
+// that are whole prefixes in both index tensors of a pair select the same keys in the same order, so their outputs are the
+// layer's own and nothing is left to compute.  Layers that are not apart are finished one after the other.
+ic_status run_similarity(const ic_layer *layers, int n_layers, const int32_t *const *idx, double *S, int32_t *lead, double *self,   // (self: or nullptr)
+                         char *o_reuse, int n_out, void *ws, size_t ws_bytes, hipStream_t st)
+{
+    const ic_attn_desc *d = &layers[0].at;
+    const int64_t n_rows = (int64_t)d->B * d->Tq;
+    const int n_chunks = lead_chunks(lead_queries(d));
+    auto counts = [&](int l) { return lead + (int64_t)l * d->B * n_chunks; };
+    ic::CosineArgs c0;
+    memset(&c0, 0, sizeof c0);
+    c0.n_rows = n_rows;
+    c0.row_len = (int64_t)d->H_q * d->d_v;
+    c0.n_chunks = n_chunks;
+    c0.Tq = d->Tq;
+    const int step = sim_apart(layers, n_layers) ? n_layers : 1;
+    std::vector<LeadJob> jobs;
+    std::vector<std::pair<int, int>> pairs;
+    for (int first = 0; first < n_layers; first += step) {
+        jobs.clear();
+        for (int i = first; i < first + step; ++i) {
+            jobs.push_back(LeadJob{layers[i], idx[i], counts(i), counts(i)});
+            const ic_status s = run_lead_dense(jobs.back(), nullptr, st);
+            if (s != IC_OK) return s;
+        }
+        ic_status s = lead_groups(jobs, ic::kMaxBatchLayers, [&](size_t at, int n) {
+            const ic_status r = run_lead_rest(&jobs[at], n, nullptr, ws, ws_bytes, st);
+            if (r != IC_OK || !self) return r;
+            ic::CosineArgs c = c0;
+            c.self_out = 1;
+            for (int i = 0; i < n; ++i) {
+                const int l = first + (int)at + i;
+                c.A[i] = c.B[i] = (const unsigned short *)layers[l].O;
+                c.lead[i] = c.lead2[i] = counts(l);
+                c.self[i] = self + l * n_rows;
+            }
+            const hipError_t e = ic::launch_cosines(c, n, st);
+            return e == hipSuccess ? IC_OK : fail(IC_ERR_HIP, "cosine launch failed: %s", hipGetErrorString(e));
+        });
+        if (s != IC_OK) return s;
+        jobs.clear();
+        pairs.clear();
+        for (int i = first; i < first + step; ++i)
+            for (int j = 0; j < i; ++j) {
+                jobs.push_back(LeadJob{layers[i], idx[j], counts(j), counts(i)});
+                pairs.push_back({i, j});
+            }
+        s = lead_groups(jobs, n_out, [&](size_t at, int n) {
+            for (int p = 0; p < n; ++p) jobs[at + p].L.O = o_reuse + p * sim_o_bytes(d);
+            const ic_status r = run_lead_rest(&jobs[at], n, nullptr, ws, ws_bytes, st);
+            if (r != IC_OK) return r;
+            ic::CosineArgs c = c0;
+            for (int p = 0; p < n; ++p) {
+                const int i = pairs[at + p].first, j = pairs[at + p].second;
+                c.A[p] = (const unsigned short *)layers[i].O;
+                c.B[p] = (const unsigned short *)jobs[at + p].L.O;
+                c.acc[p] = S + (size_t)i * n_layers + j;
+                c.lead[p] = counts(j);
+                c.lead2[p] = counts(i);
+                c.self[p] = self ? self + i * n_rows : nullptr;
+            }
+            const hipError_t e = ic::launch_cosines(c, n, st);
+            return e == hipSuccess ? IC_OK : fail(IC_ERR_HIP, "cosine launch failed: %s", hipGetErrorString(e));
+        });
+        if (s != IC_OK) return s;
+    }
+    return IC_OK;
+}
+
 } // namespace
 
 size_t ic_similarity_matrix_workspace(const ic_layer *layers, int32_t n_layers)
@@ -1029,9 +1157,11 @@ size_t ic_similarity_matrix_workspace(const ic_layer *layers, int32_t n_layers)
         const size_t a = attn_query_bytes(&layers[l].at);
         if (a > at) at = a;
     }
+    const ic_attn_desc *a0 = &layers[0].at;
     const size_t lb = sim_lead_bytes(layers, n_layers);
-    if (lb) at = std::max(at, lead_tail_bytes(&layers[0].at));
-    return sim_o_bytes(&layers[0].at) + align_up(at) + lb;
+    if (!lb) return sim_o_bytes(a0) + align_up(at);
+    at = std::max(at, lead_tail_bytes(a0));
+    return sim_outputs(a0, n_layers) * sim_o_bytes(a0) + align_up(at) + lb + sim_self_bytes(a0, n_layers);
 }
 
 ic_status ic_similarity_matrix(const ic_layer *layers, int32_t n_layers, const int32_t *const *idx_layers, double *S,
@@ -1042,10 +1172,16 @@ ic_status ic_similarity_matrix(const ic_layer *layers, int32_t n_layers, const i
     if (!idx_layers || !S) return fail(IC_ERR_NULL, "idx_layers and S must not be NULL");
     for (int l = 0; l < n_layers; ++l)
         if (!idx_layers[l]) return fail(IC_ERR_NULL, "idx_layers[%d] is NULL", l);
-    // the counts of leading rows and wide partials are for more speed or precision: a workspace without room for them will do
-    size_t lb = sim_lead_bytes(layers, n_layers), at = 0;
-    for (int l = 0; l < n_layers; ++l) at = std::max(at, attn_ws_bytes(&layers[l].at));
-    const size_t min_ws = sim_o_bytes(&layers[0].at) + align_up(at);
+    // the counts of leading rows, wide partials and several outputs at a time are for more speed or precision: a workspace
+    // without room for them will do
+    const ic_attn_desc *a0 = &layers[0].at;
+    const size_t ob = sim_o_bytes(a0);
+    size_t lb = sim_lead_bytes(layers, n_layers), at = 0, best = lead_tail_bytes(a0);
+    for (int l = 0; l < n_layers; ++l) {
+        at = std::max(at, attn_ws_bytes(&layers[l].at));
+        best = std::max(best, attn_query_bytes(&layers[l].at));
+    }
+    const size_t min_ws = ob + align_up(at);
     s = check_ws(workspace, workspace_bytes, min_ws);
     if (s != IC_OK) return s;
     if (workspace_bytes < min_ws + lb) lb = 0;
@@ -1053,37 +1189,38 @@ ic_status ic_similarity_matrix(const ic_layer *layers, int32_t n_layers, const i
         if (!dense_output(layers[l].O)) lb = 0;
     hipStream_t st = (hipStream_t)stream;
     char *ws = (char *)workspace;
-    void *o_reuse = ws;
-    int32_t *const lead = (int32_t *)(ws + sim_o_bytes(&layers[0].at));
-    void *attn_ws = (char *)lead + lb;
-    const size_t attn_bytes = workspace_bytes - sim_o_bytes(&layers[0].at) - lb;
     hipError_t e = ic::launch_sim_init(S, n_layers, st);
     if (e != hipSuccess) return fail(IC_ERR_HIP, "similarity init failed: %s", hipGetErrorString(e));
-    const ic_attn_desc *a0 = &layers[0].at;
-    const int64_t n_rows = (int64_t)a0->B * a0->Tq, row_len = (int64_t)a0->H_q * a0->d_v;
-    const int n_chunks = lead_chunks(lead_queries(a0));
+    const int64_t n_rows = (int64_t)a0->B * a0->Tq;
     if (lb) {
+        const size_t one = ob + align_up(best) + lb, sb = workspace_bytes >= one + sim_self_bytes(a0, n_layers) ? sim_self_bytes(a0, n_layers) : 0;
+        const size_t more = workspace_bytes > one + sb ? (workspace_bytes - one - sb) / ob : 0;
+        const int n_out = (int)std::min<size_t>(1 + more, sim_outputs(a0, n_layers));
+        int32_t *const lead = (int32_t *)(ws + n_out * ob);
+        double *const self = sb ? (double *)((char *)lead + lb) : nullptr;
+        lb += sb;
         s = count_lead(a0, idx_layers, n_layers, lead, st);
         if (s != IC_OK) return s;
-    }
-    for (int i = 0; i < n_layers; ++i) {
-        const ic_layer *L = &layers[i];
-        const int32_t *const lead_i = lead + (int64_t)i * a0->B * n_chunks;
-        s = lb ? run_attn_lead(L, idx_layers[i], lead_i, lead_i, true, nullptr, attn_ws, attn_bytes, st)
-               : run_attn(&L->at, L->Q, L->KV, idx_layers[i], L->O, nullptr, attn_ws, attn_bytes, st);         // own indices
+        s = run_similarity(layers, n_layers, idx_layers, S, lead, self, ws, n_out, (char *)lead + lb, workspace_bytes - n_out * ob - lb, st);
         if (s != IC_OK) return s;
-        for (int j = 0; j < i; ++j) {
-            // As a Shared layer reading j.  Rows that are whole prefixes in both index tensors select the same keys in the
-            // same order, so their outputs are those above and nothing is left to compute but their comparison.
-            const int32_t *const lead_j = lead + (int64_t)j * a0->B * n_chunks;
-            ic_layer R = *L;
-            R.O = o_reuse;
-            s = lb ? run_attn_lead(&R, idx_layers[j], lead_j, lead_i, false, nullptr, attn_ws, attn_bytes, st)
-                   : run_attn(&L->at, L->Q, L->KV, idx_layers[j], o_reuse, nullptr, attn_ws, attn_bytes, st);
+    } else {
+        for (int i = 0; i < n_layers; ++i) {
+            const ic_layer *L = &layers[i];
+            s = run_attn(&L->at, L->Q, L->KV, idx_layers[i], L->O, nullptr, ws + ob, workspace_bytes - ob, st);      // own indices
             if (s != IC_OK) return s;
-            const ic::SameRows same{lb ? lead_j : nullptr, lead_i, n_chunks, a0->Tq};
-            e = ic::launch_cosine_sum(L->O, o_reuse, n_rows, row_len, nullptr, S + (size_t)i * n_layers + j, same, st);
-            if (e != hipSuccess) return fail(IC_ERR_HIP, "cosine launch failed: %s", hipGetErrorString(e));
+            for (int j = 0; j < i; ++j) {      // as a Shared layer reading j
+                s = run_attn(&L->at, L->Q, L->KV, idx_layers[j], ws, nullptr, ws + ob, workspace_bytes - ob, st);
+                if (s != IC_OK) return s;
+                ic::CosineArgs c;
+                memset(&c, 0, sizeof c);
+                c.A[0] = (const unsigned short *)L->O;
+                c.B[0] = (const unsigned short *)ws;
+                c.acc[0] = S + (size_t)i * n_layers + j;
+                c.n_rows = n_rows;
+                c.row_len = (int64_t)a0->H_q * a0->d_v;
+                e = ic::launch_cosines(c, 1, st);
+                if (e != hipSuccess) return fail(IC_ERR_HIP, "cosine launch failed: %s", hipGetErrorString(e));
+            }
         }
     }
     e = ic::launch_sim_finish(S, n_layers, n_rows, st);

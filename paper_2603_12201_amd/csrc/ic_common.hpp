@@ -155,17 +155,25 @@ struct DenseArgs {
     int32_t n_chunks;
 };
 
-// The rows that are left: of every sequence, from the first row that is not a leading one in both tensors up to n_rows.
+// The rows that are left: of every sequence of each of n_jobs layers (AttnArgs' Qs, KVs, Os; index tensors of their own), from
+// the first row that is not a leading one in both of two tensors up to n_rows.  n_jobs * B is at most kRestSeqs.
+constexpr int kRestSeqs = 512;
 struct RestArgs {
-    const int32_t *lead, *lead2;                 // [B][n_chunks] chunk counts
-    int32_t n_chunks, n_rows;
-    int32_t wgs;                                 // workgroups per sequence
+    const int32_t *idx[kMaxBatchLayers];
+    const int32_t *lead[kMaxBatchLayers], *lead2[kMaxBatchLayers];   // [B][n_chunks] chunk counts
+    int32_t n_jobs, n_chunks, n_rows;
 };
 
-// Rows of a comparison whose second tensor is the first one: the rows that are leading in both index tensors.
-struct SameRows {
-    const int32_t *lead, *lead2;                 // [B][n_chunks] or nullptr: no such rows
-    int32_t n_chunks, Tq;
+// Comparisons of n_rows rows each.  Rows that are leading in both index tensors of a pair are the same in A and B: their
+// similarity is read from `self`, which an earlier launch has left (self_out: it writes those of A's leading rows, and no sum).
+struct CosineArgs {
+    const unsigned short *A[kMaxBatchLayers], *B[kMaxBatchLayers];
+    double *acc[kMaxBatchLayers];                // the sum of the similarities is added here
+    const int32_t *lead[kMaxBatchLayers], *lead2[kMaxBatchLayers];   // [B][n_chunks] or nullptr: no such rows
+    double *self[kMaxBatchLayers];               // [n_rows] or nullptr: worked out again
+    float *per_row;                              // [n_rows] or nullptr (one comparison only)
+    int64_t n_rows, row_len;
+    int32_t n_chunks, Tq, self_out;
 };
 
 // Head-aggregated attention probabilities over the selected rows (the indexer's training target).
@@ -221,8 +229,7 @@ hipError_t launch_overlap(const int32_t *const *idx_layers, int n_layers, int64_
                           unsigned long long *inter_out, unsigned long long *sizes_out, void *ws, hipStream_t st);
 hipError_t launch_cosine(const void *A, const void *B, int64_t n_rows, int64_t row_len, double *mean, float *per_row,
                          double *acc, hipStream_t st);
-hipError_t launch_cosine_sum(const void *A, const void *B, int64_t n_rows, int64_t row_len, float *per_row, double *acc,
-                             const SameRows &same, hipStream_t st);
+hipError_t launch_cosines(const CosineArgs &a, int n, hipStream_t st);
 hipError_t launch_sim_init(double *S, int n, hipStream_t st);
 hipError_t launch_sim_finish(double *S, int n, int64_t n_rows, hipStream_t st);
 hipError_t launch_loss_finish(const double *sims, int n, double *loss, hipStream_t st);

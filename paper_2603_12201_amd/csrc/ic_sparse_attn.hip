@@ -1302,8 +1302,9 @@ constexpr int kStreamIds = 4;                // periods between the request of a
 // PG: the KV cache may be ragged and / or paged.
 // MULTI: a.n_layers layers in one launch, or the last rows of several sequences (a.row_gap): a query's place in the tensors
 // is then not its number.
-// REST: the rows of sequence blockIdx.y behind those that the dense form has taken.  How many that are is device data, so the
-// workgroups, as many as for all rows, find out first and share what is left (one round trip to memory, about 1 us).
+// REST: the rows of all sequences of one or more layers (RestArgs) behind those that the dense form has taken.  How many that
+// are is device data, so the workgroups, as many as for all rows, find out first and share what is left (one round trip to
+// memory, about 1 us).
 // PROBS: the scores waves write each row's probability, summed over the heads, with the log-sum-exps that an attention launch
 // has left (a.lse) instead of P, to a.O as fp32 [B,Tq,k_sel]; the output waves only bring the granules.  A workgroup per query
 // whose four waves gathered and scored 16 rows each on their own loaded Q four times over (36 KB in pieces of 64 bytes) and took 442 us
@@ -1318,19 +1319,6 @@ __global__ __launch_bounds__(512, 2) void attn_stream_kernel(AttnArgs a, RestArg
     constexpr int RING = 6;                               // A-operand reads in flight
     constexpr int D = kStreamDepth, DI = kStreamIds;      // (a set of registers is that of the granule's number modulo D, DI)
     static_assert(DI % D == 0, "the loop is unrolled by DI");
-    if constexpr (REST) {
-        const int64_t bs = blockIdx.y, o = bs * ra.n_chunks;
-        const int t0 = __builtin_amdgcn_readfirstlane(min(lead_rows(ra.lead + o, ra.n_chunks), lead_rows(ra.lead2 + o, ra.n_chunks)));
-        if (t0 >= ra.n_rows) return;
-        const int64_t row = bs * a.Tq + t0;
-        a.Tq = ra.n_rows - t0;
-        a.Q = (const __bf16 *)a.Q + row * a.H_q * D_QK;
-        a.KV = (const __bf16 *)a.KV + bs * a.Lk * a.row_elems;
-        a.O = (__bf16 *)a.O + row * a.H_q * D_V;
-        a.idx += row * a.k_sel;
-        if (a.lse) a.lse += row * a.H_q;
-        a.B = 1;
-    }
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     unsigned char *tbuf = smem;                           // [kStreamRing][32][ROWB]
     unsigned char *pbuf = smem + kStreamRing * GB;        // [2][32 heads][PSTR]
@@ -1344,7 +1332,39 @@ __global__ __launch_bounds__(512, 2) void attn_stream_kernel(AttnArgs a, RestArg
     const int l16 = lane & 15, l32 = lane & 31, hh = lane >> 5, g = lane >> 4;
     const int w = wave & 3;
     // queries of the workgroup: q0, q0 + gridDim.x, ...
-    const unsigned nq_layer = (unsigned)(a.B * a.Tq), nq = MULTI ? nq_layer * a.n_layers : nq_layer;
+    const unsigned nq_layer = (unsigned)(a.B * a.Tq);
+    unsigned nq = MULTI ? nq_layer * a.n_layers : nq_layer;
+    // REST: numbers of the sequences' first queries, [n_jobs * B] and their total
+    unsigned *const start = (unsigned *)(filled + kStreamRing * kGranule * 8);
+    const int n_seq = REST ? ra.n_jobs * a.B : 0;
+    if constexpr (REST) {
+        // lanes to a sequence: 64 for up to 8 of them, down to 8
+        const int bits = n_seq <= 8 ? 6 : (n_seq <= 16 ? 5 : (n_seq <= 32 ? 4 : 3)), per = 1 << bits;
+        for (int s = tid >> bits; s < n_seq; s += 512 >> bits) {
+            const int job = s / a.B;
+            const int64_t o = (int64_t)(s - job * a.B) * ra.n_chunks;
+            int t0 = kLeadChunk * ra.n_chunks;            // the first row that is not a leading one
+#pragma unroll 4
+            for (int c = tid & (per - 1); c < ra.n_chunks; c += per) {
+                const int n = min(ra.lead[job][o + c], ra.lead2[job][o + c]);
+                t0 = n < kLeadChunk ? min(t0, kLeadChunk * c + n) : t0;
+            }
+            for (int x = per >> 1; x; x >>= 1) t0 = min(t0, __shfl_xor(t0, x));
+            if ((tid & (per - 1)) == 0) start[s] = (unsigned)(ra.n_rows - min(t0, ra.n_rows));
+        }
+        __syncthreads();
+        unsigned carry = 0;
+        if (wave == 0) {
+            for (int s0 = 0; s0 < n_seq; s0 += 64) {
+                const unsigned n = s0 + lane < n_seq ? start[s0 + lane] : 0u, incl = wave_incl_scan(n);
+                if (s0 + lane < n_seq) start[s0 + lane] = carry + incl - n;
+                carry += (unsigned)__builtin_amdgcn_readlane((int)incl, 63);
+            }
+            if (lane == 0) start[n_seq] = carry;
+        }
+        __syncthreads();
+        nq = __builtin_amdgcn_readfirstlane(start[n_seq]);
+    }
     unsigned q0 = blockIdx.x;
     if ((gridDim.x & 7u) == 0) q0 = (blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3);
     // (PROBS: every other round the other way round: causal rows hold more and more entries, 8 % more in the last workgroup's of a round)
@@ -1562,19 +1582,30 @@ __global__ __launch_bounds__(512, 2) void attn_stream_kernel(AttnArgs a, RestArg
     const int gr = lane >> 3, gp = lane & 7;              // gather role: row 8 w + gr, 16-byte piece
     const int my_row = 8 * w + gr;
     struct Place { int n, ng; bool is_q; const int32_t *idx; const unsigned short *kv, *q, *src; int len, b; } pl;
-    auto tensor_row = [&](unsigned gq, int &layer, int &b) -> int64_t {
+    auto tensor_row = [&](unsigned gq, int &layer, int &b) __attribute__((always_inline)) -> int64_t {
+        if constexpr (REST) {
+            int s = -1;                                   // the last sequence that starts at gq or before it
+            for (int s0 = 0; s0 < n_seq; s0 += 64) {
+                const int n = __popcll(__ballot(s0 + lane < n_seq && start[min(s0 + lane, n_seq)] <= gq));
+                s += n;
+                if (n < 64) break;
+            }
+            layer = s / a.B;
+            b = s - layer * a.B;
+            return (int64_t)b * a.Tq + ra.n_rows - (int)(__builtin_amdgcn_readfirstlane(start[s + 1]) - gq);
+        }
         layer = MULTI ? layer_of(a, gq) : 0;
         const unsigned qq = MULTI ? gq - layer * nq_layer : gq;
         b = (int)(qq / (unsigned)a.Tq);
         return MULTI ? (int64_t)qq + (int64_t)b * a.row_gap : (int64_t)qq;
     };
-    auto open = [&](int i) {
+    auto open = [&](int i) __attribute__((always_inline)) {
         const unsigned gq = query(i);
         int layer;
         const int64_t row = tensor_row(gq, layer, pl.b);
-        pl.idx = a.idx + row * a.k_sel;
-        pl.q = (const unsigned short *)(MULTI ? a.Qs[layer] : a.Q) + row * a.H_q * D_QK;
-        pl.kv = (const unsigned short *)(MULTI ? a.KVs[layer] : a.KV) + (PG && a.pv.page_table ? 0 : (int64_t)pl.b * a.Lk * a.row_elems);
+        pl.idx = (REST ? ra.idx[layer] : a.idx) + row * a.k_sel;
+        pl.q = (const unsigned short *)(MULTI || REST ? a.Qs[layer] : a.Q) + row * a.H_q * D_QK;
+        pl.kv = (const unsigned short *)(MULTI || REST ? a.KVs[layer] : a.KV) + (PG && a.pv.page_table ? 0 : (int64_t)pl.b * a.Lk * a.row_elems);
         pl.len = PG && a.pv.seq_lens ? max(0, min(load_uniform(a.pv.seq_lens + pl.b), a.Lk)) : a.Lk;     // (ids are compared unsigned)
         pl.ng = granules(i);
     };
@@ -1735,7 +1766,7 @@ __global__ __launch_bounds__(512, 2) void attn_stream_kernel(AttnArgs a, RestArg
                 for (int e = 0; e < 4; ++e) v[e] = __builtin_bit_cast(short, (__bf16)(o_acc[nb][4 * qd + e] * inv));
                 *(s16x4 *)(ob + row_l * OSTR + (32 * nb + 8 * qd + 4 * half) * 2) = v;
             }
-        unsigned short *const o = (unsigned short *)(MULTI ? a.Os[layer] : a.O) + row * a.H_q * D_V + 128 * w;
+        unsigned short *const o = (unsigned short *)(MULTI || REST ? a.Os[layer] : a.O) + row * a.H_q * D_V + 128 * w;
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
             const int head = 4 * k + (ln >> 4);
@@ -2016,18 +2047,18 @@ constexpr int kStreamLds = kStreamRing * kGranule * (576 * 2 + kSlabPad) + 2 * 3
 template <bool PG, bool MULTI, bool REST = false, bool PROBS = false>
 hipError_t launch_stream(const AttnArgs &a, hipStream_t st, const RestArgs &ra = RestArgs{})
 {
+    constexpr int lds = kStreamLds + (REST ? (kRestSeqs + 1) * 4 : 0);
     static hipError_t attr = hipFuncSetAttribute((const void *)attn_stream_kernel<PG, MULTI, REST, PROBS>,
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, kStreamLds);
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (attr != hipSuccess) return attr;
     int64_t wgs = (int64_t)a.n_layers * a.B * a.Tq;
     const int n_cu = cu_count();                          // one workgroup per CU walks a chain of queries
     if (n_cu <= 0) return hipErrorInvalidDevice;
+    if (REST) wgs = (int64_t)ra.n_jobs * a.B * ra.n_rows;
     if (wgs > n_cu) wgs = n_cu;
-    if (REST) wgs = ra.wgs;
     // (the counts of a workgroup's queries have to fit where P and the references are otherwise)
     if (PROBS) wgs = std::max(wgs, ((int64_t)a.B * a.Tq + kProbsQueries - 1) / kProbsQueries);
-    const dim3 grid((unsigned)wgs, (unsigned)(REST ? a.B : 1));
-    hipLaunchKernelGGL((attn_stream_kernel<PG, MULTI, REST, PROBS>), grid, dim3(512), kStreamLds, st, a, ra);
+    hipLaunchKernelGGL((attn_stream_kernel<PG, MULTI, REST, PROBS>), dim3((unsigned)wgs), dim3(512), lds, st, a, ra);
     return hipGetLastError();
 }
 

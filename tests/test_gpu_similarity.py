@@ -70,3 +70,43 @@ def test_similarity_matrix_and_search_on_a_small_stack(ic, oracle):
         mask, total = ic.pattern_search_dp(S, m)
         best, arg = oracle.pattern_search_exhaustive(S, m)
         assert abs(total - best) <= 1e-12 and mask in arg
+
+
+@pytest.mark.parametrize("B, Tq, k", [(1, 1300, 1024), (2, 600, 512), (1, 1100, 1024)])
+def test_pairs_together_and_one_by_one(ic, B, Tq, k):
+    """Five layers with counted leading rows (ten pairs): all that the query asks for, room for one output and the counts, for one
+    output alone, and one output buffer for all layers.  The outputs are bf16 of two forms, or of one in another order of
+    its granules; a mean of cosines of B x Tq rows moves by less than 2e-4."""
+    say("similarity, pairs together B=%d Tq=%d k=%d" % (B, Tq, k))
+    n, H = 5, 32
+    g = torch.Generator().manual_seed(Tq)
+    t = [{"Q": torch.randn((B, Tq, H, 576), generator=g).to(torch.bfloat16).cuda(),
+          "KV": torch.randn((B, Tq, 576), generator=g).to(torch.bfloat16).cuda()} for _ in range(n)]
+    idx = []
+    for l in range(n):
+        sc = torch.rand((B, Tq, Tq), generator=g).masked_fill(torch.ones(Tq, Tq).triu(1).bool(), -1.0)
+        v, i = sc.topk(min(k, Tq), dim=-1)
+        i = torch.where(v < 0, Tq, i).sort(-1).values.to(torch.int32)
+        i = torch.where(i == Tq, -1, i)
+        if l == 2:
+            i[0, 20, 3] = -1                                                # fewer leading rows than the other layers
+        idx.append(torch.nn.functional.pad(i, (0, k - i.shape[-1]), value=-1).contiguous().cuda())
+    import ctypes
+    ob = B * Tq * H * 512 * 2
+    at = int(ic.lib().ic_sparse_attn_workspace(ctypes.byref(ic.AttnDesc(B, Tq, Tq, H, 576, 512, 0, 576, k, 1 / 24.0))))
+
+    def run(ws_bytes=None, one_buffer=False):
+        outs = [torch.empty((B, Tq, H, 512), dtype=torch.bfloat16, device="cuda") for _ in range(1 if one_buffer else n)]
+        arr = ic.make_layers(t, k, 0, 512, 0, 1 / 24.0, outs * n if one_buffer else outs)
+        need = int(ic.lib().ic_similarity_matrix_workspace(arr, n))
+        ws = torch.empty(need if ws_bytes is None else ws_bytes, dtype=torch.uint8, device="cuda")
+        assert ob + at < ws.numel() <= need
+        S = ic.similarity_matrix(arr, idx, workspace=ws).cpu().numpy()
+        return S, outs
+    S, outs = run()
+
+    for ws_bytes, one_buffer in ((ob + at + (1 << 16), False), (ob + at + 256, False), (None, True)):
+        S1, o1 = run(ws_bytes, one_buffer)
+        assert np.abs(S1 - S).max() < 2e-4, (ws_bytes, one_buffer)
+        assert one_buffer or all((a.float() - b.float()).abs().max() < 2e-2 for a, b in zip(outs, o1))
+    assert np.all(np.diag(S) == 1.0) and np.all(np.triu(S, 1) == 0.0) and np.all(S[np.tril_indices(n, -1)] < 1.0)
