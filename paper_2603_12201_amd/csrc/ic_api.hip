@@ -433,15 +433,20 @@ double row_time(const ic_attn_desc *d, int n_layers, Causal c, size_t ws_bytes, 
 }
 
 // The first n rows of every sequence in the dense form: blocks of 64 (query, head) rows ranked by length, in chains there and back
-// over the CUs, as long as the longest block or as a chain of those that all rounds of them have a block for.
-double dense_time(const ic_attn_desc *d, int n, int64_t pos0)
+// over the CUs, as long as the longest block or as a chain of those that all rounds of them have a block for.  Several layers
+// follow one another: their blocks of mean length, and half of what the longest has more.
+double dense_time(const ic_attn_desc *d, int n, int64_t pos0, int n_layers = 1)
 {
-    const int64_t blocks = ((int64_t)n * d->H_q + 63) / 64 * d->B, rounds = (blocks + 255) / 256;
+    const int64_t blocks = ((int64_t)n * d->H_q + 63) / 64 * d->B, rounds = (blocks * n_layers + 255) / 256;
     auto tiles = [&](double rank) { return (pos0 + std::max(0., n * (1 - rank / (double)blocks))) / 32 + 0.5; };
     // two rounds, there and back: twice the block at the turn
     const double pairs = (double)(rounds / 2), chain = 2 * pairs * tiles(256 * pairs) + (rounds % 2 ? tiles(256. * (double)(rounds - 1)) : 0.);
-    const double walk = std::max(kDenseTileUs * tiles(0), kDenseTileUs * chain + kDenseBlockUs * (double)(rounds - 1));
-    return kDenseLaunchUs + std::max(walk, query_us(d, (int64_t)n * d->B));
+    double walk = std::max(kDenseTileUs * tiles(0), kDenseTileUs * chain + kDenseBlockUs * (double)(rounds - 1));
+    if (n_layers > 1 && rounds > 1) {
+        const double mean = tiles(0.5 * (double)blocks), all = (double)(blocks * n_layers) / 256 * mean + 0.5 * (tiles(0) - mean);
+        walk = std::max(kDenseTileUs * tiles(0), kDenseTileUs * all + kDenseBlockUs * (double)(rounds - 1));
+    }
+    return kDenseLaunchUs + std::max(walk, query_us(d, (int64_t)n * d->B * n_layers));
 }
 
 ic_attn_desc rows_behind(const ic_attn_desc *d, int n)
@@ -450,6 +455,11 @@ ic_attn_desc rows_behind(const ic_attn_desc *d, int n)
     t.Tq = d->Tq - n;
     return t;
 }
+
+// Layers whose dense rows share a launch: up to four rounds of blocks a layer, from where on a launch's start and end count less
+// than what is lost where two layers' keys take turns in L2.  Four layers, together / a launch each: 256 rows 26.0 / 40.6 us, 512
+// 53 / 85, 1024 155 / 172, 2048 530 / 540, 4 x 256 79 / 101, 16 x 32 32.4 / 37.8, 3 x 1021 498 / 484.
+int dense_batch(const ic_attn_desc *d, int n) { return ((int64_t)n * d->H_q + 63) / 64 * d->B <= 4 * 256 ? ic::kMaxBatchLayers : 1; }
 
 // How many of them it takes, for one of n_layers layers that the row forms would take together.  The rows behind (ws_bytes:
 // workspace for their splits) are a launch of their own, with some 11 us for the two ends between them.  Measured, k = 2048, row forms / dense form (and
@@ -460,11 +470,12 @@ int dense_queries(const ic_attn_desc *d, int n_layers, Causal c, size_t ws_bytes
 {
     const int n = prefix_queries(d, c);
     if (n == 0) return 0;
-    const double whole = row_time(d, n_layers, c, ws_bytes, attn_max_splits(d, 1)), dense = dense_time(d, n, c.pos0);
-    if (n == d->Tq) return 0.97 * n_layers * dense <= whole ? n : 0;
+    const double whole = row_time(d, n_layers, c, ws_bytes, attn_max_splits(d, 1));
+    const int m = std::min(n_layers, dense_batch(d, n));
+    const double runs = (double)n_layers / m, dense = dense_time(d, n, c.pos0, m);
+    if (n == d->Tq) return 0.97 * runs * dense <= whole ? n : 0;
     const ic_attn_desc t = rows_behind(d, n);
-    const double behind = row_time(&t, 1, Causal{c.pos0 + n, c.lk}, ws_bytes, INT64_MAX);
-    return n_layers * (dense + 11 + behind) <= whole ? n : 0;
+    return runs * (dense + 11 + row_time(&t, m, Causal{c.pos0 + n, c.lk}, ws_bytes, INT64_MAX)) <= whole ? n : 0;
 }
 
 // Workspace that serves the rows behind best.
@@ -473,7 +484,7 @@ size_t dense_tail_bytes(const ic_attn_desc *d, int n_layers, Causal c)
     const int n = dense_queries(d, n_layers, c, SIZE_MAX);
     if (n == 0 || n == d->Tq) return 0;
     const ic_attn_desc t = rows_behind(d, n);
-    return attn_splits(&t, 1, SIZE_MAX, INT64_MAX).bytes;
+    return attn_splits(&t, std::min(n_layers, dense_batch(d, n)), SIZE_MAX, INT64_MAX).bytes;
 }
 
 // Leading query rows of every sequence that may be whole prefixes when nothing is known about idx: in a causal selection
@@ -589,13 +600,21 @@ struct LeadJob {
     const int32_t *idx, *lead, *lead2;
 };
 
-ic_status run_lead_dense(const LeadJob &j, float *lse, hipStream_t st)
+// The leading rows of layers of one shape whose counts follow one another.
+ic_status run_lead_dense(const LeadJob *jobs, int n_jobs, float *lse, hipStream_t st)
 {
-    const ic_attn_desc *d = &j.L.at;
+    const ic_attn_desc *d = &jobs[0].L.at;
     const int n = lead_queries(d);
     ProfScope ps(2, st);
-    const ic::DenseArgs da{n, d->Lk - d->Tq, j.lead, lead_chunks(n)};
-    hipError_t e = ic::launch_attn_dense(attn_args(&j.L, 1, j.idx, lse, nullptr, kUnknown), da, st);
+    const ic::DenseArgs da{n, d->Lk - d->Tq, jobs[0].lead, lead_chunks(n)};
+    ic::AttnArgs a = attn_args(&jobs[0].L, 1, jobs[0].idx, lse, nullptr, kUnknown);
+    a.n_layers = n_jobs;
+    for (int i = 0; i < n_jobs; ++i) {
+        a.Qs[i] = jobs[i].L.Q;
+        a.KVs[i] = jobs[i].L.KV;
+        a.Os[i] = jobs[i].L.O;
+    }
+    hipError_t e = ic::launch_attn_dense(a, da, st);
     if (e != hipSuccess) return fail(IC_ERR_HIP, "dense attention launch failed: %s", hipGetErrorString(e));
     return IC_OK;
 }
@@ -687,23 +706,26 @@ ic_status run_attn_layers(const ic_layer *layers, int n_layers, const int32_t *i
     return IC_OK;
 }
 
-// One layer whose first nd rows of every sequence are whole prefixes: those in the dense form, then the others.
-ic_status run_attn_dense(const ic_layer *L, int nd, const int32_t *idx, void *ws, size_t ws_bytes, hipStream_t st,
+// Layers whose first nd rows of every sequence are whole prefixes: those in the dense form, then the others.
+ic_status run_attn_dense(const ic_layer *L, int n_layers, int nd, const int32_t *idx, void *ws, size_t ws_bytes, hipStream_t st,
                          const ic_paged_cache *pc, Causal c)
 {
     const ic_attn_desc *d = &L->at;
     {
         ProfScope ps(2, st);                   // (the rows behind them are timed by their own launch)
         const ic::DenseArgs da{nd, (int32_t)c.pos0, nullptr, 0};
-        hipError_t e = ic::launch_attn_dense(attn_args(L, 1, idx, nullptr, pc, c), da, st);
+        hipError_t e = ic::launch_attn_dense(attn_args(L, n_layers, idx, nullptr, pc, c), da, st);
         if (e != hipSuccess) return fail(IC_ERR_HIP, "dense attention launch failed: %s", hipGetErrorString(e));
     }
     if (nd == d->Tq) return IC_OK;
-    ic_layer r = *L;
-    r.at = rows_behind(d, nd);
-    r.Q = (const char *)r.Q + (int64_t)nd * d->H_q * d->d_qk * 2;
-    r.O = (char *)r.O + (int64_t)nd * d->H_q * d->d_v * 2;
-    return run_attn_layers(&r, 1, idx + (int64_t)nd * d->k_sel, nullptr, ws, ws_bytes, st, pc, Causal{c.pos0 + nd, c.lk}, nd);
+    ic_layer r[ic::kMaxBatchLayers];
+    for (int l = 0; l < n_layers; ++l) {
+        r[l] = L[l];
+        r[l].at = rows_behind(d, nd);
+        r[l].Q = (const char *)r[l].Q + (int64_t)nd * d->H_q * d->d_qk * 2;
+        r[l].O = (char *)r[l].O + (int64_t)nd * d->H_q * d->d_v * 2;
+    }
+    return run_attn_layers(r, n_layers, idx + (int64_t)nd * d->k_sel, nullptr, ws, ws_bytes, st, pc, Causal{c.pos0 + nd, c.lk}, nd);
 }
 
 ic_layer attn_layer(const ic_attn_desc *d, const void *Q, const void *KV, void *O)
@@ -776,7 +798,7 @@ ic_status ic_sparse_attn_lead(const ic_attn_desc *d, const void *Q, const void *
     s = count_lead(d, &idx, 1, lead, st);
     if (s != IC_OK) return s;
     const LeadJob job = {attn_layer(d, Q, KV, O), idx, lead, lead};
-    s = run_lead_dense(job, lse, st);
+    s = run_lead_dense(&job, 1, lse, st);
     return s != IC_OK ? s : run_lead_rest(&job, 1, lse, (char *)workspace + lb, workspace_bytes - lb, st);
 }
 
@@ -875,7 +897,8 @@ size_t ic_forward_stack_workspace(const ic_layer *layers, int32_t n_layers)
         size_t a = ic_sparse_attn_workspace(&layers[l].at);
         size_t b = layers[l].q ? ic_indexer_topk_workspace(&layers[l].ix) : 0;
         const bool ok = check_attn(&layers[l].at) == IC_OK;
-        if (ok && layers[l].q && layers[l].ix.q_pos0 >= 0) a = std::max(a, dense_tail_bytes(&layers[l].at, 1, Causal{layers[l].ix.q_pos0, layers[l].ix.Lk}));
+        for (int m = 1; ok && layers[l].q && layers[l].ix.q_pos0 >= 0 && m <= std::min(n_layers - l, ic::kMaxBatchLayers); ++m)
+            a = std::max(a, dense_tail_bytes(&layers[l].at, m, Causal{layers[l].ix.q_pos0, layers[l].ix.Lk}));
         // which layers are Full is not known here: room for any run of layers of this shape
         if (ok && attn_ws_bytes(&layers[l].at) > 0) {
             const int run = n_layers - l < ic::kMaxBatchLayers ? n_layers - l : ic::kMaxBatchLayers;
@@ -927,11 +950,14 @@ static ic_status forward_stack_impl(const ic_layer *layers, int32_t n_layers, co
         while (l + run < n_layers && !full_mask[l + run]) ++run;
         int m = attn_batch(L, run, pc);
         while (m > 1 && attn_best_bytes(&L->at, m) > workspace_bytes) --m;
-        const int nd = dense_output(L->O) ? dense_queries(&L->at, m, known, workspace_bytes) : 0;
-        s = nd ? run_attn_dense(L, nd, idx_cache, workspace, workspace_bytes, st, pc, known)
+        bool whole = true;                     // outputs that the dense form can store
+        for (int i = 0; i < m; ++i) whole = whole && dense_output(L[i].O);
+        const int nd = whole ? dense_queries(&L->at, m, known, workspace_bytes) : 0;
+        if (nd) m = std::min(m, dense_batch(&L->at, nd));
+        s = nd ? run_attn_dense(L, m, nd, idx_cache, workspace, workspace_bytes, st, pc, known)
                : run_attn_layers(L, m, idx_cache, nullptr, workspace, workspace_bytes, st, pc, known);
         if (s != IC_OK) return s;
-        if (!nd) l += m - 1;
+        l += m - 1;
     }
     return IC_OK;
 }
@@ -1098,13 +1124,10 @@ ic_status run_similarity(const ic_layer *layers, int n_layers, const int32_t *co
     std::vector<std::pair<int, int>> pairs;
     for (int first = 0; first < n_layers; first += step) {
         jobs.clear();
-        for (int i = first; i < first + step; ++i) {
-            jobs.push_back(LeadJob{layers[i], idx[i], counts(i), counts(i)});
-            const ic_status s = run_lead_dense(jobs.back(), nullptr, st);
-            if (s != IC_OK) return s;
-        }
+        for (int i = first; i < first + step; ++i) jobs.push_back(LeadJob{layers[i], idx[i], counts(i), counts(i)});
         ic_status s = lead_groups(jobs, ic::kMaxBatchLayers, [&](size_t at, int n) {
-            const ic_status r = run_lead_rest(&jobs[at], n, nullptr, ws, ws_bytes, st);
+            ic_status r = run_lead_dense(&jobs[at], n, nullptr, st);
+            if (r == IC_OK) r = run_lead_rest(&jobs[at], n, nullptr, ws, ws_bytes, st);
             if (r != IC_OK || !self) return r;
             ic::CosineArgs c = c0;
             c.self_out = 1;

@@ -151,7 +151,7 @@ __device__ __forceinline__ int lead_rows(const int32_t *lead, int n_chunks)
 struct DenseArgs {
     int32_t n_queries;    // per sequence, from row 0
     int32_t pos0;         // row t sees the keys 0 .. pos0 + t, all of them below Lk
-    const int32_t *lead;  // [B][n_chunks] or nullptr: fewer rows where these counts say so
+    const int32_t *lead;  // [layers][B][n_chunks] or nullptr: fewer rows where these counts say so
     int32_t n_chunks;
 };
 

@@ -836,8 +836,9 @@ struct DenseShape {
 // tile row (within 16) behind result row r of S^T
 __device__ __forceinline__ int dense_row(int r) { return 8 * (r >> 3) + 2 * (r & 3) + ((r >> 2) & 1); }
 
-template <bool PG>
-__global__ __launch_bounds__(512, 2) void attn_dense_kernel(AttnArgs a, DenseArgs da, DenseShape ds)
+// MULTI: the rows of a.n_layers layers (with their layer a variable, one layer of 3 x 1021 rows took 1 us of 123 longer).
+template <bool PG, bool MULTI>
+__device__ __forceinline__ void dense_rows(const AttnArgs &a, const DenseArgs &da, const DenseShape &ds)
 {
     constexpr int D_QK = 576, D_V = 512;
     constexpr int KS = D_QK / 32;                         // contraction steps
@@ -861,11 +862,18 @@ __global__ __launch_bounds__(512, 2) void attn_dense_kernel(AttnArgs a, DenseArg
     const int gr = lane >> 3, gp = lane & 7;
     const int w = wave & 3;
     // (requested together, and divided by reciprocals: a division is a tenth of a us, and there are ten in front of the first load)
-    asm volatile("" ::"s"(a.Q), "s"(a.KV), "s"(a.B), "s"(a.Tq), "s"(a.Lk), "s"(a.H_q), "s"(a.row_elems), "s"(da.n_queries), "s"(da.pos0), "s"(da.lead), "s"(ds.n_blk), "s"(ds.n_wgs), "s"(ds.inv_b), "s"(ds.inv_h));
+    asm volatile("" ::"s"(a.Q), "s"(a.KV), "s"(a.B), "s"(a.Tq), "s"(a.Lk), "s"(a.H_q), "s"(a.row_elems), "s"(a.n_layers), "s"(da.n_queries), "s"(da.pos0), "s"(da.lead), "s"(ds.n_blk), "s"(ds.n_wgs), "s"(ds.inv_b), "s"(ds.inv_h));
     auto div_b = [&](int x) -> int { return a.B == 1 ? x : ds.inv_b ? (int)__umulhi((unsigned)x, ds.inv_b) : x / a.B; };
     auto div_h = [&](int x) -> int { return a.H_q == 1 ? x : (int)__umulhi((unsigned)x, ds.inv_h); };
-    // blocks of the workgroup, all sequences' blocks ranked by length: there and back over the workgroups, which evens them out
-    const int n_blk = ds.n_blk, n_all = n_blk * a.B, n_wgs = ds.n_wgs;
+    // blocks of the workgroup, all sequences' blocks of a layer ranked by length, layer behind layer (a layer's blocks share its
+    // keys): there and back over the workgroups, which evens them out
+    const int n_blk = ds.n_blk, n_layer = n_blk * a.B, n_all = MULTI ? n_layer * a.n_layers : n_layer, n_wgs = ds.n_wgs;
+    auto layer_at = [&](int &r) -> int {                  // of a rank, which becomes the one within the layer
+        if (!MULTI) return 0;
+        const int layer = (int)((unsigned)r / (unsigned)n_layer);
+        r -= layer * n_layer;
+        return layer;
+    };
     auto rank = [&](int n) -> int { return n * n_wgs + (n & 1 ? n_wgs - 1 - (int)blockIdx.x : (int)blockIdx.x); };
     int n_list = ds.n_round;
     n_list += rank(n_list) < n_all;
@@ -873,20 +881,23 @@ __global__ __launch_bounds__(512, 2) void attn_dense_kernel(AttnArgs a, DenseArg
     if (tid < 4) moved[tid] = 0;
     if (da.lead) {
         for (int n = wave; n < n_list; n += 8) {
-            const int r_b = div_b(rank(n)), b = rank(n) - r_b * a.B, R0 = (n_blk - 1 - r_b) * kDenseRows;
-            const int nq = __builtin_amdgcn_readfirstlane(min(da.n_queries, lead_rows(da.lead + (int64_t)b * da.n_chunks, da.n_chunks)));
+            int r = rank(n);
+            const int layer = layer_at(r), r_b = div_b(r), b = r - r_b * a.B, R0 = (n_blk - 1 - r_b) * kDenseRows;
+            const int nq = __builtin_amdgcn_readfirstlane(min(da.n_queries, lead_rows(da.lead + ((int64_t)layer * a.B + b) * da.n_chunks, da.n_chunks)));
             if (lane == 0) list[n] = R0 < nq * a.H_q ? nq : 0;
         }
         __syncthreads();
     }
-    struct Block { int n, odd, b, R0, n_queries, n_rows, nt, t_edge; };  // n = n_list: none
+    struct Block { int n, odd, layer, b, R0, n_queries, n_rows, nt, t_edge; };  // n = n_list: none
     auto open = [&](int n, int odd) {                     // block n of the list, or the first one behind it that exists
         Block k;
         k.odd = odd;                                      // (odd and even ones alternate)
         int nq = da.n_queries;
         if (da.lead)
             while (n < n_list && (nq = __builtin_amdgcn_readfirstlane(list[n])) == 0) ++n;
-        const int r = rank(min(n, n_list - 1)), r_b = div_b(r);
+        int r = rank(min(n, n_list - 1));
+        k.layer = layer_at(r);
+        const int r_b = div_b(r);
         k.n = n;
         k.b = r - r_b * a.B;
         k.R0 = (n_blk - 1 - r_b) * kDenseRows;
@@ -1051,27 +1062,37 @@ __global__ __launch_bounds__(512, 2) void attn_dense_kernel(AttnArgs a, DenseArg
     } else {
         // A tile is fetched eight lanes to a 128-byte line: rows 8 w + gr, nine lines.
         u32x4 cur[9];
-        Block ab = first;                                 // the next tile to request: tile aj of block ab, Q is 0 and 1
-        int aj = 0;
+        // the next tile to request: tile aj of block an, Q is 0 and 1; its rows' first addresses and their last rows
+        int an, aj, ant, aq_last, ak_last, ab = 0;
+        const unsigned short *aq, *ak;
+        auto aim = [&](const Block &x) __attribute__((always_inline)) {
+            an = x.n;
+            aj = 0;
+            ant = x.nt;
+            aq = (const unsigned short *)(MULTI ? a.Qs[x.layer] : a.Q) + ((int64_t)x.b * a.Tq * a.H_q + x.R0) * D_QK;
+            aq_last = x.n_rows - 1 - x.R0;
+            ak = (const unsigned short *)(MULTI ? a.KVs[x.layer] : a.KV) + (PG && a.pv.page_table ? 0 : (int64_t)x.b * a.Lk * a.row_elems);
+            ak_last = da.pos0 + x.n_queries - 1;
+            if constexpr (PG) ab = x.b;
+        };
+        aim(first);
         auto tile_src = [&]() -> const unsigned short * { // (past the last block: one row of its Q, for nobody)
             const unsigned short *p;
-            if (ab.nt == INT32_MAX) {
-                p = (const unsigned short *)a.Q + ((int64_t)ab.b * a.Tq * a.H_q + ab.R0) * D_QK;
+            if (ant == INT32_MAX) {
+                p = aq;
             } else if (aj < 2) {
-                p = (const unsigned short *)a.Q + ((int64_t)ab.b * a.Tq * a.H_q + min(ab.R0 + 32 * aj + 8 * w + gr, ab.n_rows - 1)) * D_QK;
+                p = aq + min(32 * aj + 8 * w + gr, aq_last) * D_QK;
             } else {
                 const int s0 = (aj - 2) * kDenseTile;                      // (a tile never straddles a page)
-                const int64_t row = PG && a.pv.page_table ? paged_row(a.pv, ab.b, s0) : (int64_t)ab.b * a.Lk + s0;
-                p = (const unsigned short *)a.KV + (row + min(8 * w + gr, da.pos0 + ab.n_queries - 1 - s0)) * a.row_elems;
+                const int64_t row = PG && a.pv.page_table ? paged_row(a.pv, ab, s0) : (int64_t)s0;
+                p = ak + (row + min(8 * w + gr, ak_last - s0)) * a.row_elems;
             }
-            if (__builtin_expect(++aj - 2 == ab.nt, 0)) {
-                const Block nx = open(ab.n + 1, 0);
-                if (nx.n < n_list) {
-                    ab = nx;
-                    aj = 0;
-                } else {
-                    ab.nt = INT32_MAX;                    // (never to come round)
-                }
+            if (__builtin_expect(++aj - 2 == ant, 0)) {
+                const Block nx = open(an + 1, 0);
+                if (nx.n < n_list)
+                    aim(nx);
+                else
+                    ant = INT32_MAX;                      // (never to come round)
             }
             return p + 8 * gp;
         };
@@ -1202,6 +1223,7 @@ __global__ __launch_bounds__(512, 2) void attn_dense_kernel(AttnArgs a, DenseArg
             const int c32 = ln & 31, half = ln >> 5;
             unsigned char *ob = tbuf + ((i + 2) & (kDenseRing - 1)) * TBUFB + 8 * w * ROWB;
             const int64_t row0 = (int64_t)k.b * a.Tq * a.H_q + k.R0;
+            __bf16 *const o_l = (__bf16 *)(MULTI ? a.Os[k.layer] : a.O);
             const bool odd_keys = __builtin_amdgcn_readfirstlane(moved[2 + k.odd]);    // (rare: see finite_v above)
             unroll<2>([&](auto r_c) __attribute__((always_inline)) {
                 constexpr int r = decltype(r_c)::value;
@@ -1223,7 +1245,7 @@ __global__ __launch_bounds__(512, 2) void attn_dense_kernel(AttnArgs a, DenseArg
                     const int row = 4 * j + (ln >> 4), R = k.R0 + 32 * r + row;
                     u32x4 o = *(const u32x4 *)(ob + row * OSTR + 16 * (ln & 15));
                     if (odd_keys && R < k.n_rows) {
-                        const unsigned short *v0 = (const unsigned short *)a.KV + 128 * w + 8 * (ln & 15);
+                        const unsigned short *v0 = (const unsigned short *)(MULTI ? a.KVs[k.layer] : a.KV) + 128 * w + 8 * (ln & 15);
                         for (int key = k.t_edge * kDenseTile; key <= da.pos0 + R / a.H_q; ++key) {
                             const int64_t at = PG && a.pv.page_table ? paged_row(a.pv, k.b, key) : (int64_t)k.b * a.Lk + key;
                             const u32x4 v = *(const u32x4 *)(v0 + at * a.row_elems);
@@ -1234,7 +1256,7 @@ __global__ __launch_bounds__(512, 2) void attn_dense_kernel(AttnArgs a, DenseArg
                             }
                         }
                     }
-                    if (R < k.n_rows) *(u32x4 *)((__bf16 *)a.O + (row0 + 32 * r + row) * D_V + 128 * w + 8 * (ln & 15)) = o;
+                    if (R < k.n_rows) *(u32x4 *)(o_l + (row0 + 32 * r + row) * D_V + 128 * w + 8 * (ln & 15)) = o;
                 }
             });
 #pragma unroll
@@ -1271,6 +1293,18 @@ __global__ __launch_bounds__(512, 2) void attn_dense_kernel(AttnArgs a, DenseArg
             __syncthreads();
         }
     }
+}
+
+template <bool PG>
+__global__ __launch_bounds__(512, 2) void attn_dense_kernel(AttnArgs a, DenseArgs da, DenseShape ds)
+{
+    dense_rows<PG, false>(a, da, ds);
+}
+
+template <bool PG>
+__global__ __launch_bounds__(512, 2) void attn_layers_dense_kernel(AttnArgs a, DenseArgs da, DenseShape ds)
+{
+    dense_rows<PG, true>(a, da, ds);
 }
 
 // ---- stream form (unsplit rows of 576/512 features) ----------------------------------------------------------------
@@ -2164,31 +2198,34 @@ hipError_t launch_attn_rest(const AttnArgs &a, const RestArgs &ra, hipStream_t s
     return launch_stream<false, false, true>(a, st, ra);
 }
 
-// Rows 0 .. n_queries - 1 of every sequence, row t seeing exactly the keys 0 .. pos0 + t (576 / 512 rows, values in front).
+// Rows 0 .. n_queries - 1 of every sequence of a.n_layers layers, row t seeing exactly the keys 0 .. pos0 + t (576 / 512 rows, values
+// in front).
 hipError_t launch_attn_dense(const AttnArgs &a, const DenseArgs &da, hipStream_t st)
 {
     if (da.n_queries <= 0) return hipSuccess;
     constexpr int lds = kDenseRing * kDenseTile * (576 * 2 + kSlabPad) + 2 * kDenseRows * (kDenseTile * 2 + 16) + (6 * kDenseRows + 4 + kDenseChain) * 4;
-    static hipError_t attr = hipFuncSetAttribute((const void *)attn_dense_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    static hipError_t attr_pg = hipFuncSetAttribute((const void *)attn_dense_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    typedef void (*Kernel)(AttnArgs, DenseArgs, DenseShape);
+    static const Kernel kernels[2][2] = {{attn_dense_kernel<false>, attn_dense_kernel<true>}, {attn_layers_dense_kernel<false>, attn_layers_dense_kernel<true>}};
+    static hipError_t attr = [] {
+        hipError_t e = hipSuccess;
+        for (int i = 0; i < 4 && e == hipSuccess; ++i)
+            e = hipFuncSetAttribute((const void *)kernels[i / 2][i % 2], hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        return e;
+    }();
     if (attr != hipSuccess) return attr;
-    if (attr_pg != hipSuccess) return attr_pg;
-    const int64_t blocks = ((int64_t)da.n_queries * a.H_q + kDenseRows - 1) / kDenseRows * a.B;
+    const int64_t blocks = ((int64_t)da.n_queries * a.H_q + kDenseRows - 1) / kDenseRows * a.B * a.n_layers;
     const int n_cu = cu_count();
     if (n_cu <= 0) return hipErrorInvalidDevice;
     const dim3 grid((unsigned)std::max(std::min<int64_t>(blocks, n_cu), (blocks + kDenseChain - 1) / kDenseChain));
     // x * ceil(2^32 / d) >> 32 is x / d as long as x * (d - 1) < 2^32; a sequence has at most IC_MAX_K * IC_MAX_HEADS_Q rows
     auto up = [](int64_t d) { return d > 1 ? (unsigned)((((uint64_t)1 << 32) + d - 1) / d) : 0u; };
     DenseShape ds;
-    ds.n_blk = (int)(blocks / a.B);
+    ds.n_blk = (int)(blocks / a.B / a.n_layers);
     ds.n_wgs = (int)grid.x;
     ds.n_round = (int)(blocks / grid.x);
     ds.inv_b = blocks * (a.B - 1) < (int64_t)1 << 32 ? up(a.B) : 0u;
     ds.inv_h = up(a.H_q);
-    if (a.pv.page_table)
-        hipLaunchKernelGGL(attn_dense_kernel<true>, grid, dim3(512), lds, st, a, da, ds);
-    else
-        hipLaunchKernelGGL(attn_dense_kernel<false>, grid, dim3(512), lds, st, a, da, ds);
+    hipLaunchKernelGGL(kernels[a.n_layers > 1][a.pv.page_table != nullptr], grid, dim3(512), lds, st, a, da, ds);
     return hipGetLastError();
 }
 

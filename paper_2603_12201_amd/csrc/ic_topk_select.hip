@@ -667,7 +667,7 @@ __device__ __forceinline__ RowView row_view(const SelectArgs &a, int r)
 // 44 -> 25, of 12289 to 16384 (4096) 137 -> 67, of 30721 to 32768 (2048) 93 -> 71.  With 64 keys a thread it is no faster
 // than the candidate form (64 K keys, 32 rows: 20.6 and 19.4).
 constexpr int kBinsLen = 32768;
-constexpr int kRankCap = 512;
+constexpr int kRankCap = 64;             // (each is compared with all others: 150 ties of 2400 keys cost more than the rest of the row)
 
 // Largest value over the 64 lanes of a wave, in every lane (no LDS traffic; lanes without a source keep their own).
 __device__ __forceinline__ uint32_t wave_max_dpp(uint32_t x)
@@ -708,10 +708,14 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE))) void 
     float *osel = a.sel ? a.sel + ((int64_t)rw.b * a.Tq + rw.i) * a.k_sel : nullptr;
     const int k = a.k_sel;
     if (nv <= k) {                             // every visible key is selected
-        for (int s = tid; s < k; s += NT) {
-            oidx[s] = s < nv ? s : -1;
-            if (osel) osel[s] = s < nv ? row[s] : -INFINITY;
+        if (k % 4 == 0 && (uintptr_t)oidx % 16 == 0) {
+            for (int s = 4 * tid; s < k; s += 4 * NT)
+                *(i32x4 *)(oidx + s) = i32x4{s < nv ? s : -1, s + 1 < nv ? s + 1 : -1, s + 2 < nv ? s + 2 : -1, s + 3 < nv ? s + 3 : -1};
+        } else {
+            for (int s = tid; s < k; s += NT) oidx[s] = s < nv ? s : -1;
         }
+        if (osel)
+            for (int s = tid; s < k; s += NT) osel[s] = s < nv ? row[s] : -INFINITY;
         return;
     }
     const int nsteps = (nv + 4 * NT - 1) / (4 * NT);

@@ -248,3 +248,46 @@ def test_any_output_address(B, Tq, pos0, k):
         assert (buf[:off] == 7.0).all() and (buf[off + n:] == 7.0).all()
         outs.append(out.float())
     assert ((outs[0] - outs[1]).norm() / outs[0].norm()).item() < 4e-3
+
+
+@pytest.mark.parametrize("B, Tq, pos0, k, n, page", [
+    (1, 300, 0, 2048, 4, 0), (3, 130, 0, 512, 3, 0), (1, 257, 40, 512, 8, 0), (2, 200, 0, 512, 2, 64),      # every row a whole prefix
+    (1, 600, 0, 512, 4, 0), (2, 400, 100, 450, 3, 0), (2, 400, 100, 450, 3, 64),                            # and rows behind them
+])
+def test_dense_rows_of_several_layers(B, Tq, pos0, k, n, page):
+    """Layers that share their dense launch give what each gives alone: a block does not know its neighbours, and the rows behind
+    (in other splits, maybe) are bf16 roundings of the same sums."""
+    import paper_2603_12201_amd as ic
+    print("[case] dense layers B=%d Tq=%d pos0=%d k=%d n=%d page=%d" % (B, Tq, pos0, k, n, page), flush=True)
+    H, Lk = 32, pos0 + Tq
+    g = torch.Generator(device="cuda").manual_seed(Tq + k)
+    rnd = lambda *s: torch.randn(s, generator=g, device="cuda", dtype=torch.bfloat16)
+    pages = -(-Lk // 64)
+    cache = (B * pages * 64,) if page else (B, Lk)
+    layers = [{"Q": rnd(B, Tq, H, 576), "KV": rnd(*cache, 576)} for _ in range(n)]
+    ixr = {"q": rnd(B, Tq, 4, 64), "k": rnd(*cache, 64), "w": torch.rand((B, Tq, 4), generator=g, device="cuda")}
+    for t in layers:
+        t.update(ixr)
+    if page:
+        table = torch.randperm(B * pages, generator=torch.Generator().manual_seed(1)).view(B, pages).to(torch.int32).cuda()
+        pc = ic.paged_cache(page_table=table, page_size=page)
+
+    def run(some):
+        outs = [torch.full((B, Tq, H, 512), 7.0, dtype=torch.bfloat16, device="cuda") for _ in some]
+        arr = ic.make_layers(some, k, pos0, 512, 0, 1 / 24.0, outs, Lk=Lk if page else None)
+        for l in arr:
+            l.ix.q_pos0 = pos0
+        ws = torch.empty(max(ic.forward_stack_workspace(arr), 256), dtype=torch.uint8, device="cuda")
+        idx = torch.empty((B, Tq, k), dtype=torch.int32, device="cuda")
+        mask = [True] + [False] * (len(some) - 1)
+        if page:
+            ic.forward_stack_paged(arr, mask, pc, idx, ws)
+        else:
+            ic.forward_stack(arr, mask, idx, ws)
+        return outs
+    together = run(layers)
+    for t, out in zip(layers, together):
+        alone = run([t])[0]
+        assert torch.isfinite(out.float()).all()
+        # two roundings of the same value to bf16 (of outputs below 4: at most 2^-7 apart, twice)
+        assert (out.float() - alone.float()).abs().max() <= 2 ** -6
