@@ -91,8 +91,8 @@ struct SelectArgs {
 // Candidate lists of rows that are selected in parts (workspace).
 struct PartArgs {
     uint32_t *heads;      // [rows][head_words]: threshold key, then the lengths of the row's lists
-    uint2 *lists;         // [rows][n_parts * waves][wcap] (key, position), ascending positions
-    int32_t n_parts, wcap, head_words;
+    uint32_t *lists;      // [rows][2][list entries]: keys, positions; the parts' lists in equal shares
+    int32_t n_parts, head_words;
 };
 
 // One launch covers n_layers layers of one shape that read the same index tensor (a Full layer and the Shared layers

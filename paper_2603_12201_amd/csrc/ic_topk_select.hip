@@ -367,11 +367,18 @@ constexpr int cand_lds_words(int nt, int maxlen, int cap)
     return kBins1 + 2 * (nt / 64) + 4 + 16 + 2 * cap + maxlen / 32 + cand_aux_words(maxlen);
 }
 
-__device__ __forceinline__ uint32_t wave_max_u32(uint32_t x)
+// Largest value over the 64 lanes of a wave, in every lane (no LDS traffic; lanes without a source keep their own).
+__device__ __forceinline__ uint32_t wave_max_dpp(uint32_t x)
 {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) x = max(x, (uint32_t)__shfl_xor((int)x, off));
-    return x;
+#define IC_DPP_MAX(ctrl, rows) x = max(x, (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, ctrl, rows, 0xf, false))
+    IC_DPP_MAX(0x111, 0xf);              // row_shr:1, 2, 4, 8
+    IC_DPP_MAX(0x112, 0xf);
+    IC_DPP_MAX(0x114, 0xf);
+    IC_DPP_MAX(0x118, 0xf);
+    IC_DPP_MAX(0x142, 0xa);              // row_bcast:15 into rows 1, 3
+    IC_DPP_MAX(0x143, 0xc);              // row_bcast:31 into rows 2, 3
+#undef IC_DPP_MAX
+    return (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
 }
 
 template <int NT, int MAXLEN, int CAP>
@@ -451,16 +458,16 @@ __global__ __launch_bounds__(NT) void select_cand_kernel(SelectArgs a)
         kmn = min(kmn, skey[e]);
     }
     {
-        const uint32_t mx = wave_max_u32(kmx);
-        const uint32_t mn = ~wave_max_u32(~kmn);
+        const uint32_t mx = wave_max_dpp(kmx);
+        const uint32_t mn = ~wave_max_dpp(~kmn);
         if (lane == 0) {                       // (wpre is free until the boundary list is built)
             wpre[wave] = mn;
             wpre[NW + wave] = mx;
         }
     }
     __syncthreads();
-    const uint32_t smin = ~wave_max_u32(~(lane < NW ? wpre[lane] : 0xFFFFFFFFu));
-    const uint32_t smax = wave_max_u32(lane < NW ? wpre[NW + lane] : 0u);
+    const uint32_t smin = ~wave_max_dpp(~(lane < NW ? wpre[lane] : 0xFFFFFFFFu));
+    const uint32_t smax = wave_max_dpp(lane < NW ? wpre[NW + lane] : 0u);
     const uint32_t srange = smax - smin;
     const int sbits = srange ? 32 - __clz((int)srange) : 0;
     const int ssh = sbits > 12 ? sbits - 12 : 0;
@@ -552,7 +559,7 @@ __global__ __launch_bounds__(NT) void select_cand_kernel(SelectArgs a)
             }
             tmax = max(tmax, key);
         }
-        tmax = wave_max_u32(tmax);
+        tmax = wave_max_dpp(tmax);
         if (lane == 0 && tmax != 0u) atomicMax(&misc[1], tmax);
     }
 
@@ -668,20 +675,6 @@ __device__ __forceinline__ RowView row_view(const SelectArgs &a, int r)
 // than the candidate form (64 K keys, 32 rows: 20.6 and 19.4).
 constexpr int kBinsLen = 32768;
 constexpr int kRankCap = 64;             // (each is compared with all others: 150 ties of 2400 keys cost more than the rest of the row)
-
-// Largest value over the 64 lanes of a wave, in every lane (no LDS traffic; lanes without a source keep their own).
-__device__ __forceinline__ uint32_t wave_max_dpp(uint32_t x)
-{
-#define IC_DPP_MAX(ctrl, rows) x = max(x, (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, ctrl, rows, 0xf, false))
-    IC_DPP_MAX(0x111, 0xf);              // row_shr:1, 2, 4, 8
-    IC_DPP_MAX(0x112, 0xf);
-    IC_DPP_MAX(0x114, 0xf);
-    IC_DPP_MAX(0x118, 0xf);
-    IC_DPP_MAX(0x142, 0xa);              // row_bcast:15 into rows 1, 3
-    IC_DPP_MAX(0x143, 0xc);              // row_bcast:31 into rows 2, 3
-#undef IC_DPP_MAX
-    return (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
-}
 
 template <int NT, int NV, int NB, int WPE>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE))) void select_bins_kernel(SelectArgs a)
@@ -1001,17 +994,22 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE))) void 
 // past the candidate form's bitmap, was streamed four times by it: 150 us).  Here a row is cut into parts with a
 // workgroup each, and a second launch finishes it:
 //   select_part_kernel    every part takes the candidate form's sample of the whole row (the same 4096 keys, so the same
-//                         threshold T0), then sweeps its own keys; a wave owns a contiguous stretch of them and writes its
-//                         candidates, ascending by position, to a list of its own in the workspace
-//   select_finish_kernel  one workgroup per row collects the lists in order, finds the k-th largest candidate with one
-//                         histogram and an exact ranking of its bin, and emits: the candidates are already ascending, so
-//                         a bitmap over their numbers (not over the row) gives the slots, and the row may be longer than a
-//                         bitmap over its positions; how long, select_parts_fit() says
+//                         threshold T0), then sweeps its own keys and leaves its candidates in a list of its own in the
+//                         workspace.  A part has every n-th block of 32 keys, so that the lists of a row whose best keys lie
+//                         together are as long as those of any other
+//   select_finish_kernel  one workgroup per row takes all lists into registers (32 slots a thread, requested before their
+//                         lengths are known), finds the k-th largest candidate with one histogram and an exact ranking of
+//                         its bin, and emits through a bitmap of the row in LDS
 // A row that the candidates cannot decide (fewer than k of them, a list that overflowed, too many ties in the boundary
 // bin) and a row too short for the sample take the generic radix select in the second launch.
+// What bounds it: two launches, each a chain of memory latencies and barriers.  One row of 200 000 keys: 6.1 + 12.3 us with
+// lists per wave that the second launch collected in LDS, 5.6 + 9.3 with this (of the second: lists 1.8, histogram and its scan
+// 2.1, marking 1.9, ranking 0.5, bitmap scan 1.1, entries 1.1); with 512 threads of 32 slots 12.4, two waves per SIMD do not
+// cover their LDS latencies.
 constexpr int kPartThreads = 1024;
 constexpr int kPartWaves = kPartThreads / 64;
 constexpr int kPartMax = 64;             // parts of a row
+constexpr int kPartBlock = 32;           // keys of a row that stay together: a line
 // Where the form is the better one (score + select of a call, parts against the forms above): one row of 65536 keys 22.9
 // against 22.5 us, 100 000 keys 24.3 / 32.3, 200 000 keys 29.5 / 139, 500 000 keys 40.6 / 378; 32 rows of 65536 keys 116 /
 // 114, of 131072 keys 218 / 226; 60 rows of 131072 keys 390 / 395, of 32768 keys 114 / 112; and past the candidate form's
@@ -1019,10 +1017,15 @@ constexpr int kPartMax = 64;             // parts of a row
 constexpr int kPartFrom = 65536;         // rows have more keys than this ...
 constexpr int kPartRows = 64;            // ... and are at most this many: more of them fill the chip by themselves,
 constexpr int kPartRowsLong = 512;       // which holds for longer where the alternative streams the row four times
-constexpr int kFinishCap = 12288;        // candidates of a row
+constexpr int kFinishThreads = 1024;
+constexpr int kFinishSlots = 16384;      // list entries of a row, its parts' lists in equal shares of them
+constexpr int kFinishCap = 12288;        // candidates of a row that are likely to find room in them
+constexpr int kFinishWindow = 1 << 20;   // keys that the bitmap covers at a time
 
-// per row: [0] T0, then the lists' lengths; the lists follow the heads of all rows
-__host__ __device__ inline size_t part_head_words(int n_parts) { return (size_t)(4 + n_parts * kPartWaves + 63) / 64 * 64; }
+// per row: T0, then the lists' lengths
+constexpr int kPartHead = 1 + kPartMax;
+__host__ __device__ inline int part_bits(int n_parts) { return n_parts > 1 ? 32 - __builtin_clz((unsigned)n_parts - 1) : 0; }
+__host__ __device__ inline int part_slots(int n_parts) { return kFinishSlots >> part_bits(n_parts); }
 
 // rows the sample can speak for
 __device__ __forceinline__ bool part_row(const SelectArgs &a, int nv) { return nv >= kCandMinLen && nv >= 4 * a.k_sel; }
@@ -1032,31 +1035,31 @@ __global__ __launch_bounds__(kPartThreads) void select_part_kernel(SelectArgs a,
     constexpr int NT = kPartThreads, NW = kPartWaves;
     request_args(a);
     __shared__ __attribute__((aligned(16))) uint32_t hist[kBins1];
-    __shared__ uint32_t wsum[2 * NW], bc[4], red[2 * NW];
+    __shared__ uint32_t wsum[2 * NW], bc[4], red[2 * NW], n_list;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int part = blockIdx.x, r = blockIdx.y;
     const RowView rv = row_view(a, r);
     if (rv.i >= a.Tq || !part_row(a, rv.nv)) return;
     const int nv = rv.nv;
     const float *row = a.strip + (int64_t)r * a.ld;
-    // this wave's stretch: whole 256-key vectors of the row, ascending over (part, wave)
-    const int span = ((nv + pa.n_parts * NW - 1) / (pa.n_parts * NW) + 255) / 256 * 256;
-    const int s0 = min((part * NW + wave) * span, nv), s1 = min(s0 + span, nv);
+    // eight lanes to a block; blocks part, part + n_parts, ...
     constexpr int kGroup = 4;
     f32x4 ga[kGroup];
-    auto load_group = [&](int p0) {
+    auto place = [&](int i0, int j) { return ((i0 + (j * NW + wave) * 8 + (lane >> 3)) * pa.n_parts + part) * kPartBlock + 4 * (lane & 7); };
+    auto load_group = [&](int i0) {
 #pragma unroll
         for (int j = 0; j < kGroup; ++j) {
-            const int p = p0 + 256 * j + 4 * lane;
+            const int p = place(i0, j);
             ga[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-            if (p < s1) ga[j] = *(const f32x4 *)(row + p);     // may run past s1 inside the row's padding; masked below
+            if (p < nv) ga[j] = *(const f32x4 *)(row + p);     // may run past nv inside the row's padding; masked below
         }
     };
     const int blk = tid >> 5;                                  // 32 blocks of 128 keys spread over the row
     const f32x4 sv = *(const f32x4 *)(row + (int)(((int64_t)blk * nv / 32) & ~(int64_t)3) + (tid & 31) * 4);
-    load_group(s0);
+    load_group(0);
     static_assert(kCandSample == 4 * NT, "one sample vector per thread");
     for (int e = tid; e < kBins1; e += NT) hist[e] = 0;
+    if (tid == 0) n_list = 0;
     uint32_t skey[4], kmx = 0u, kmn = 0xFFFFFFFFu;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -1064,15 +1067,15 @@ __global__ __launch_bounds__(kPartThreads) void select_part_kernel(SelectArgs a,
         kmx = max(kmx, skey[e]);
         kmn = min(kmn, skey[e]);
     }
-    kmx = wave_max_u32(kmx);
-    kmn = ~wave_max_u32(~kmn);
+    kmx = wave_max_dpp(kmx);
+    kmn = wave_max_dpp(~kmn);
     if (lane == 0) {
         red[wave] = kmn;
         red[NW + wave] = kmx;
     }
     __syncthreads();
-    const uint32_t smin = ~wave_max_u32(~(lane < NW ? red[lane] : 0xFFFFFFFFu));
-    const uint32_t smax = wave_max_u32(lane < NW ? red[NW + lane] : 0u);
+    const uint32_t smin = ~wave_max_dpp(red[lane % NW]);
+    const uint32_t smax = wave_max_dpp(red[NW + lane % NW]);
     const uint32_t srange = smax - smin;
     const int sbits = srange ? 32 - __clz((int)srange) : 0;
     const int ssh = sbits > 12 ? sbits - 12 : 0;
@@ -1085,177 +1088,214 @@ __global__ __launch_bounds__(kPartThreads) void select_part_kernel(SelectArgs a,
     const uint32_t T0 = smin + (bc[0] << ssh);
     const float T0f = key_score(T0);
 
-    uint32_t *head = pa.heads + (size_t)r * pa.head_words;
-    uint2 *list = pa.lists + ((size_t)r * pa.n_parts * NW + part * NW + wave) * pa.wcap;
-    uint32_t cnt = 0;                                          // wave-uniform
-    for (int p0 = s0; p0 < s1; p0 += 256 * kGroup) {
-        if (p0 != s0) load_group(p0);
+    const uint32_t slots = (uint32_t)part_slots(pa.n_parts);
+    uint32_t *keys = pa.lists + (size_t)r * 2 * kFinishSlots + part * slots, *pos = keys + kFinishSlots;
+    const int n_blk = ((nv + kPartBlock - 1) / kPartBlock - part + pa.n_parts - 1) / pa.n_parts;     // of this part
+    for (int i0 = 0; i0 < n_blk; i0 += NW * 8 * kGroup) {      // workgroup-uniform
+        if (i0) load_group(i0);
+        uint32_t m = 0;
 #pragma unroll
         for (int j = 0; j < kGroup; ++j) {
-            uint32_t m = 0;
-            const int p = p0 + 256 * j + 4 * lane;
+            const int p = place(i0, j);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) m |= (uint32_t)((int)(p + e < s1) & (int)(ga[j][e] >= T0f)) << e;
-            if (__ballot(m != 0u) == 0ull) continue;           // wave-uniform
-            const uint32_t n_t = (uint32_t)__popc(m);
-            const uint32_t incl = wave_incl_scan(n_t);
-            uint32_t off = cnt + incl - n_t;
-            cnt += (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+            for (int e = 0; e < 4; ++e) m |= (uint32_t)((int)(p + e < nv) & (int)(ga[j][e] >= T0f)) << (4 * j + e);
+        }
+        const uint32_t n_t = (uint32_t)__popc(m), incl = wave_incl_scan(n_t);
+        const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+        if (total == 0u) continue;                             // wave-uniform
+        uint32_t first = 0;
+        if (lane == 0) first = atomicAdd(&n_list, total);
+        uint32_t off = (uint32_t)__builtin_amdgcn_readfirstlane((int)first) + incl - n_t;
+#pragma unroll
+        for (int j = 0; j < kGroup; ++j)
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-                if ((m >> e) & 1u) {
-                    if (off < (uint32_t)pa.wcap) list[off] = uint2{max(score_key(ga[j][e]), T0), (uint32_t)(p + e)};
+                if ((m >> (4 * j + e)) & 1u) {
+                    if (off < slots) {
+                        keys[off] = max(score_key(ga[j][e]), T0);
+                        pos[off] = (uint32_t)(place(i0, j) + e);
+                    }
                     ++off;
                 }
-        }
     }
-    if (lane == 0) head[4 + part * NW + wave] = cnt;
+    __syncthreads();
+    uint32_t *head = pa.heads + (size_t)r * pa.head_words;
+    if (tid == 0) head[1 + part] = n_list;
     if (part == 0 && tid == 0) head[0] = T0;
 }
 
-__global__ __launch_bounds__(kPartThreads) void select_finish_kernel(SelectArgs a, PartArgs pa)
+constexpr int finish_bitmap_words(int row_len) { return ((row_len < kFinishWindow ? row_len : kFinishWindow) + 127) / 128 * 4; }
+
+__global__ __launch_bounds__(kFinishThreads) void select_finish_kernel(SelectArgs a, PartArgs pa)
 {
-    constexpr int NT = kPartThreads, NW = kPartWaves;
+    constexpr int NT = kFinishThreads, NW = NT / 64, NV = kFinishSlots / NT / 4;
     extern __shared__ __attribute__((aligned(16))) uint32_t smem[];
     uint32_t *hist = smem;                     // [kBins1]  (the generic form's layout starts the same way)
     uint32_t *wsum = hist + kBins1;            // [2 NW]
     uint32_t *bc = wsum + 2 * NW;              // [4]
-    uint32_t *misc = bc + 4;                   // [16]: 1 largest candidate key, 2 boundary-list count, 3 a list overflowed
-    uint32_t *ckey = misc + 16;                // [kFinishCap]
-    uint32_t *cpos = ckey + kFinishCap;        // [kFinishCap]
-    uint32_t *bitmap = cpos + kFinishCap;      // [kFinishCap / 32]
-    uint32_t *wpre = bitmap + kFinishCap / 32; // [kFinishCap / 32]
-    uint32_t *start = wpre + kFinishCap / 32;  // [NT] first candidate of a list; later the boundary bin's members
-    uint32_t *bl = start;                      // [kBoundaryCap] candidate numbers
-    static_assert(kBoundaryCap <= NT && kPartMax * NW <= NT && kFinishCap / 32 <= NT, "one list, one bitmap word per thread");
+    __shared__ uint32_t misc[2], red[NW];      // misc: 0 members listed
+    uint32_t *bl_key = bc + 4, *bl_pos = bl_key + kBoundaryCap;    // the boundary bin's members
+    uint32_t *bitmap = bl_pos + kBoundaryCap;  // [finish_bitmap_words] of the row
+    uint16_t *ahead_of = (uint16_t *)hist;     // [kFinishWindow / 128] selected entries ahead of every four words (the histogram is read by then)
+    static_assert(kFinishWindow / 128 <= 2 * kBins1 && (kBins1 + 2 * NW + 4) % 4 == 0, "they share its space");
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int r = blockIdx.x;
     request_args(a);
     const RowView rv = row_view(a, r);
     if (rv.i >= a.Tq) return;
-    auto finish = [&]() -> bool {              // false: the generic form takes the row (one call site, see below)
-    if (!part_row(a, rv.nv)) return false;
-    const uint32_t *head = pa.heads + (size_t)r * pa.head_words;
-    const int n_lists = pa.n_parts * NW;
-    const uint32_t T0 = head[0];
-    const uint32_t n_mine = tid < n_lists ? head[4 + tid] : 0u;
-    for (int e = tid; e < kBins1; e += NT) hist[e] = 0;
-    if (tid < kFinishCap / 32) bitmap[tid] = 0;
-    if (tid < 16) misc[tid] = 0;
-    const uint32_t incl = wave_incl_scan(n_mine);
-    if (lane == 63) wsum[wave] = incl;
-    __syncthreads();
-    if (n_mine > (uint32_t)pa.wcap) misc[3] = 1u;
-    uint32_t before = 0, n_cand = 0;
+    auto finish = [&]() -> bool {              // false: the generic form takes the row (one call site, see the candidate form)
+        if (!part_row(a, rv.nv)) return false;
+        const uint32_t *head = pa.heads + (size_t)r * pa.head_words;
+        const uint32_t *keys = pa.lists + (size_t)r * 2 * kFinishSlots;
+        const float *row = a.strip + (int64_t)r * a.ld;
+        const int lg = 14 - part_bits(pa.n_parts);             // slots of a list, 256 or more: a wave's vectors are of one
+        static_assert(kFinishSlots == 1 << 14 && kFinishSlots / kPartMax >= 256, "a list takes whole vectors of a wave");
+        u32x4 v[NV], at[NV];
 #pragma unroll
-    for (int wv = 0; wv < NW; ++wv) {
-        if (wv < wave) before += wsum[wv];
-        n_cand += wsum[wv];
-    }
-    start[tid] = before + incl - n_mine;
-    __syncthreads();
-    const uint32_t k = (uint32_t)a.k_sel;
-    if (n_cand < k || n_cand > (uint32_t)kFinishCap || misc[3] != 0u) {   // workgroup-uniform
-        __syncthreads();
-        return false;
-    }
-    // the lists, 16 lanes to a list: all of a thread's first entries are requested together
-    {
-        constexpr int kRounds = kPartMax * NW / (NT / 16);
-        const int sub = tid & 15, grp = tid >> 4;
-        const uint2 *lists = pa.lists + (size_t)r * n_lists * pa.wcap;
-        uint2 first[kRounds];
-        uint32_t at[kRounds], n[kRounds];
-#pragma unroll
-        for (int q = 0; q < kRounds; ++q) {
-            const int l = q * (NT / 16) + grp;
-            at[q] = l < n_lists ? start[l] : 0u;
-            n[q] = l < n_lists ? (l + 1 < NT ? start[l + 1] : n_cand) - at[q] : 0u;   // (lists past the last one start at n_cand)
-            first[q] = uint2{0u, 0u};
-            if ((uint32_t)sub < n[q]) first[q] = lists[(size_t)l * pa.wcap + sub];
+        for (int j = 0; j < NV; ++j) {
+            const int s = (j * NT + tid) * 4;
+            v[j] = u32x4{0u, 0u, 0u, 0u};
+            if (s >> lg < pa.n_parts) v[j] = *(const u32x4 *)(keys + s);
         }
-        uint32_t tmax = 0;
+        const uint32_t T0 = head[0];
+        const uint32_t n_lane = lane < pa.n_parts ? head[1 + lane] : 0u;
+        const uint32_t n_cand = (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan(n_lane), 63), k = (uint32_t)a.k_sel;
+        if (n_cand < k || __ballot(n_lane > 1u << lg) != 0ull) return false;   // workgroup-uniform
+        // slots behind a list's end: key 0, below every candidate (T0 is above the smallest sampled key or a bin's edge)
+        uint32_t mx = 0;
 #pragma unroll
-        for (int q = 0; q < kRounds; ++q) {
-            const int l = q * (NT / 16) + grp;
-            for (uint32_t e = sub; e < n[q]; e += 16) {
-                const uint2 c = e == (uint32_t)sub ? first[q] : lists[(size_t)l * pa.wcap + e];
-                ckey[at[q] + e] = c.x;
-                cpos[at[q] + e] = c.y;
-                tmax = max(tmax, c.x);
+        for (int j = 0; j < NV; ++j) {
+            const int s = (j * NT + tid) * 4, part = __builtin_amdgcn_readfirstlane(s >> lg);
+            const int left = (int)(__builtin_amdgcn_readlane((int)n_lane, part)) - (s & ((1 << lg) - 1));
+            at[j] = u32x4{0u, 0u, 0u, 0u};
+            if (left > 0) at[j] = *(const u32x4 *)(keys + kFinishSlots + s);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                v[j][e] = e < left ? v[j][e] : 0u;
+                mx = max(mx, v[j][e]);
             }
         }
-        tmax = wave_max_u32(tmax);
-        if (lane == 0 && tmax != 0u) atomicMax(&misc[1], tmax);
-    }
-    __syncthreads();
-    const uint32_t range = misc[1] - T0;
-    const int nbits = range ? 32 - __clz((int)range) : 0;
-    const int sh = nbits > 12 ? nbits - 12 : 0;
-    for (uint32_t j = tid; j < n_cand; j += NT) atomicAdd(&hist[(ckey[j] - T0) >> sh], 1u);
-    __syncthreads();
-    find_digit<NT, kBins1 / NT>(hist, k, wsum, bc, tid, lane, wave);
-    const uint32_t bstar = bc[0], need = bc[1], n_b = bc[2];
-    const bool ranked = need < n_b;            // the boundary bin is cut: rank its members exactly
-    if (ranked && n_b > (uint32_t)kBoundaryCap) {
+        for (int e = tid; e < kBins1; e += NT) hist[e] = 0;
+        const int words = finish_bitmap_words(rv.nv);
+        for (int e = 4 * tid; e < words; e += 4 * NT) *(u32x4 *)(bitmap + e) = u32x4{0u, 0u, 0u, 0u};
+        if (tid == 0) misc[0] = 0;
+        mx = wave_max_dpp(mx);
+        if (lane == 0) red[wave] = mx;
         __syncthreads();
-        return false;
-    }
-    for (uint32_t j = tid; j < n_cand; j += NT) {
-        const uint32_t bin = (ckey[j] - T0) >> sh;
-        if (bin > bstar || (bin == bstar && !ranked))
-            atomicOr(&bitmap[j >> 5], 1u << (j & 31u));
-        else if (bin == bstar)
-            bl[atomicAdd(&misc[2], 1u)] = j;
-    }
-    __syncthreads();
-    if (ranked) {
-        for (uint32_t m = tid; m < n_b; m += NT) {
-            const uint32_t jm = bl[m], km = ckey[jm];
-            uint32_t ahead = 0;                // members that beat this one: larger key, or equal key at a lower position
-            for (uint32_t x = 0; x < n_b; ++x) {
-                const uint32_t jx = bl[x];
-                ahead += (ckey[jx] > km || (ckey[jx] == km && jx < jm)) ? 1u : 0u;
-            }
-            if (ahead < need) atomicOr(&bitmap[jm >> 5], 1u << (jm & 31u));
-        }
-        __syncthreads();
-    }
-    // slots: selected candidates ahead of every bitmap word
-    {
-        const uint32_t mine = tid < kFinishCap / 32 ? (uint32_t)__popc(bitmap[tid]) : 0u;
-        const uint32_t inc = wave_incl_scan(mine);
-        if (lane == 63) wsum[wave] = inc;
-        __syncthreads();
-        uint32_t ahead = 0;
+        const uint32_t range = wave_max_dpp(red[lane % NW]) - T0;
+        const int nbits = range ? 32 - __clz((int)range) : 0;
+        const int sh = nbits > 12 ? nbits - 12 : 0;
+        auto each = [&](auto f) __attribute__((always_inline)) {
 #pragma unroll
-        for (int wv = 0; wv < NW; ++wv)
-            if (wv < wave) ahead += wsum[wv];
-        if (tid < kFinishCap / 32) wpre[tid] = ahead + inc - mine;
-    }
-    __syncthreads();
-    int32_t *oidx = a.idx + ((int64_t)rv.b * a.Tq + rv.i) * a.k_sel;
-    float *osel = a.sel ? a.sel + ((int64_t)rv.b * a.Tq + rv.i) * a.k_sel : nullptr;
-    for (uint32_t j = tid; j < n_cand; j += NT) {
-        const uint32_t word = bitmap[j >> 5], bit = j & 31u;
-        if ((word >> bit) & 1u) {
-            const uint32_t slot = wpre[j >> 5] + (uint32_t)__popc(word & ((1u << bit) - 1u));
-            if (slot < k) {                    // always true for a consistent select
-                oidx[slot] = (int32_t)cpos[j];
-                if (osel) osel[slot] = key_score(ckey[j]);
+            for (int j = 0; j < NV; ++j) {
+                asm volatile("" : "+v"(v[j]));                 // (bins and tests are not kept from one sweep to the next)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (v[j][e] != 0u) f(v[j][e], at[j][e]);
+            }
+        };
+        each([&](uint32_t x, uint32_t) { atomicAdd(&hist[(x - T0) >> sh], 1u); });
+        __syncthreads();
+        find_digit<NT, kBins1 / NT>(hist, k, wsum, bc, tid, lane, wave);
+        const uint32_t bstar = bc[0], need = bc[1], n_b = bc[2];
+        const bool ranked = need < n_b;        // the boundary bin is cut: rank its members exactly
+        if (ranked && n_b > (uint32_t)kBoundaryCap) {
+            __syncthreads();
+            return false;
+        }
+        // Selected entries of a window set their bits (the first window's, of all rows but the longest: together with the listing)
+        auto in_window = [&](uint32_t p, uint32_t w0) { return p - w0 < (uint32_t)kFinishWindow; };
+        auto set = [&](uint32_t p, uint32_t w0) { atomicOr(&bitmap[(p - w0) >> 5], 1u << (p & 31u)); };
+        const uint32_t least = bstar + (ranked ? 1u : 0u);     // bins from here on are selected whole
+        each([&](uint32_t x, uint32_t p) {
+            const uint32_t bin = (x - T0) >> sh;
+            if (bin >= least) {
+                if (in_window(p, 0u)) set(p, 0u);
+            } else if (bin == bstar) {
+                const uint32_t m = atomicAdd(&misc[0], 1u);
+                bl_key[m] = x;
+                bl_pos[m] = p;
+            }
+        });
+        __syncthreads();
+        bool in = false;                       // this thread's member
+        if (ranked) {
+            static_assert(kBoundaryCap <= NT, "a member per thread");
+            if ((uint32_t)tid < n_b) {
+                const uint32_t km = bl_key[tid], pm = bl_pos[tid];
+                uint32_t ahead = 0;            // members that beat this one: larger key, or equal key at a lower position
+#pragma unroll 4
+                for (uint32_t x = 0; x < n_b; ++x) ahead += (bl_key[x] > km || (bl_key[x] == km && bl_pos[x] < pm)) ? 1u : 0u;
+                in = ahead < need;
+                if (in && in_window(pm, 0u)) set(pm, 0u);
+            }
+            __syncthreads();
+        }
+        int32_t *oidx = a.idx + ((int64_t)rv.b * a.Tq + rv.i) * a.k_sel;
+        float *osel = a.sel ? a.sel + ((int64_t)rv.b * a.Tq + rv.i) * a.k_sel : nullptr;
+        uint32_t taken = 0;                    // entries of the windows before
+        for (uint32_t w0 = 0; w0 < (uint32_t)rv.nv; w0 += kFinishWindow) {
+            if (w0) {
+                __syncthreads();
+                for (int e = 4 * tid; e < words; e += 4 * NT) *(u32x4 *)(bitmap + e) = u32x4{0u, 0u, 0u, 0u};
+                __syncthreads();
+                each([&](uint32_t x, uint32_t p) {
+                    if ((x - T0) >> sh >= least && in_window(p, w0)) set(p, w0);
+                });
+                if (in && in_window(bl_pos[tid], w0)) set(bl_pos[tid], w0);
+                __syncthreads();
+            }
+            // a thread's words follow each other
+            const int groups = words / 4, mine = (groups + NT - 1) / NT, g0 = min(tid * mine, groups), g1 = min(g0 + mine, groups);
+            uint32_t n = 0;
+            for (int q = g0; q < g1; ++q) {
+                const u32x4 w = *(const u32x4 *)(bitmap + 4 * q);
+                n += (uint32_t)(__popc(w[0]) + __popc(w[1]) + __popc(w[2]) + __popc(w[3]));
+            }
+            uint32_t before = wave_incl_scan(n);
+            if (lane == 63) wsum[wave] = before;
+            __syncthreads();
+            before += taken - n;
+#pragma unroll
+            for (int wv = 0; wv < NW; ++wv) {
+                if (wv < wave) before += wsum[wv];
+                taken += wsum[wv];
+            }
+            for (int q = g0; q < g1; ++q) {
+                const u32x4 w = *(const u32x4 *)(bitmap + 4 * q);
+                ahead_of[q] = (uint16_t)before;    // (k_sel is at most 2048)
+                before += (uint32_t)(__popc(w[0]) + __popc(w[1]) + __popc(w[2]) + __popc(w[3]));
+            }
+            __syncthreads();
+            for (int q = tid; q < groups; q += NT) {           // (neighbouring groups in neighbouring threads: entries that lie together)
+                const u32x4 w = *(const u32x4 *)(bitmap + 4 * q);
+                uint32_t slot = ahead_of[q];
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    uint64_t m = w[2 * u] | (uint64_t)w[2 * u + 1] << 32;
+                    while (m) {
+                        const uint32_t p = w0 + 128 * (uint32_t)q + 64 * u + (uint32_t)__builtin_ctzll(m);
+                        m &= m - 1;
+                        if (slot < k) {        // always true for a consistent select
+                            oidx[slot] = (int32_t)p;
+                            if (osel) osel[slot] = key_score(score_key(row[p]));   // (-0 as +0)
+                        }
+                        ++slot;
+                    }
+                }
             }
         }
-    }
-    return true;
+        return true;
     };
     if (!finish()) {
         SelectArgs ga = a;
-        constexpr int kSpace = 16 + 2 * kFinishCap;
-        ga.cache_elems = kSpace / 64 * 64;
+        ga.cache_elems = 0;
+        __syncthreads();
         select_row_generic<NT>(ga, smem);
     }
 }
-constexpr int finish_lds_words() { return kBins1 + 2 * kPartWaves + 4 + 16 + 2 * kFinishCap + 2 * (kFinishCap / 32) + kPartThreads; }
+constexpr size_t finish_lds_bytes(int row_len) { return (size_t)(kBins1 + 2 * (kFinishThreads / 64) + 4 + 2 * kBoundaryCap + finish_bitmap_words(row_len)) * 4; }
+static_assert(finish_lds_bytes(kFinishWindow) <= 159 * 1024, "fits the LDS, static arrays beside it");
 
 size_t select_lds_bytes(int cache_elems)
 {
@@ -1281,21 +1321,9 @@ int select_parts(int n_rows, int max_row_len)
     return p < 1 ? 1 : (p > kPartMax ? kPartMax : p);
 }
 
-namespace {
-// list entries per wave: three times what a wave of a uniformly spread row keeps (about 2 k + 32 / 4096 of the row)
-int part_wcap(int n_parts, int max_row_len)
-{
-    const int64_t all = 3 * ((int64_t)2 * IC_MAX_K + (int64_t)max_row_len / 128);
-    const int64_t w = (all / (n_parts * kPartWaves) + 63) / 64 * 64;
-    return (int)(w < 128 ? 128 : w);
-}
-} // namespace
-
 size_t select_parts_bytes(int n_rows, int max_row_len)
 {
-    const int p = select_parts(n_rows, max_row_len);
-    if (p == 0) return 0;
-    return (size_t)n_rows * (part_head_words(p) * 4 + (size_t)p * kPartWaves * part_wcap(p, max_row_len) * sizeof(uint2));
+    return select_parts(n_rows, max_row_len) == 0 ? 0 : (size_t)n_rows * (((kPartHead + 63) / 64 * 64) + 2 * kFinishSlots) * 4;
 }
 
 hipError_t launch_select_parts(const SelectArgs &a_in, int n_rows, int max_row_len, void *ws, hipStream_t st)
@@ -1304,17 +1332,16 @@ hipError_t launch_select_parts(const SelectArgs &a_in, int n_rows, int max_row_l
     a.cache_elems = 0;
     PartArgs pa;
     pa.n_parts = select_parts(n_rows, max_row_len);
-    pa.wcap = part_wcap(pa.n_parts, max_row_len);
-    pa.head_words = (int)part_head_words(pa.n_parts);
+    pa.head_words = (kPartHead + 63) / 64 * 64;
     pa.heads = (uint32_t *)ws;
-    pa.lists = (uint2 *)(pa.heads + (size_t)n_rows * pa.head_words);
-    constexpr int lds = finish_lds_words() * (int)sizeof(uint32_t);
-    static hipError_t attr = hipFuncSetAttribute((const void *)select_finish_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    pa.lists = pa.heads + (size_t)n_rows * pa.head_words;
+    const size_t lds = finish_lds_bytes(max_row_len);
+    static hipError_t attr = hipFuncSetAttribute((const void *)select_finish_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)finish_lds_bytes(kFinishWindow));
     if (attr != hipSuccess) return attr;
     hipLaunchKernelGGL(select_part_kernel, dim3((unsigned)pa.n_parts, (unsigned)n_rows), dim3(kPartThreads), 0, st, a, pa);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(select_finish_kernel, dim3((unsigned)n_rows), dim3(kPartThreads), lds, st, a, pa);
+    hipLaunchKernelGGL(select_finish_kernel, dim3((unsigned)n_rows), dim3(kFinishThreads), lds, st, a, pa);
     return hipGetLastError();
 }
 

@@ -91,3 +91,20 @@ def test_rows_about_as_long_as_the_candidates_allow(ic, oracle, ks, Lk, pos0):
     n = pos0 + 1
     sc = oracle.indexer_scores(synth.bits(q), synth.bits(k[:, :n].contiguous()), synth.bits(w), pos0)
     parity.check_idx_row(idx[0, 0], sc[0, 0], n, ks, oracle)
+
+
+@pytest.mark.parametrize("Lk, run", [(100000, 2500), (300000, 5000), (1100000, 3000)])
+def test_best_keys_that_lie_together(ic, oracle, Lk, run):
+    """The best scores in one stretch of the row (what a query that looks at its neighbourhood selects), across a part's and the
+    bitmap's limits, with ties inside."""
+    print("[case] parts, best keys together, Lk=%d" % Lk, flush=True)
+    for at in (0, Lk - run, min(Lk, 1 << 20) - run // 2):
+        at = min(at, Lk - run)
+        v = torch.rand(Lk, generator=torch.Generator().manual_seed(Lk + at))
+        v[at:at + run] += 4
+        q = torch.zeros((1, 1, 1, 64)); q[..., 5] = 1.0
+        k = torch.zeros((1, Lk, 64)); k[0, :, 5] = v
+        q, k, w = q.to(torch.bfloat16), k.to(torch.bfloat16), torch.ones((1, 1, 1))
+        idx = ic.indexer_topk(q.cuda(), k.cuda(), w.cuda(), 2000, Lk - 1).cpu().numpy()
+        sc = k[0, :, 5].double().numpy()
+        assert np.array_equal(idx[0, 0], np.sort(oracle.topk_row(sc, Lk, 2000)["idx"]))
