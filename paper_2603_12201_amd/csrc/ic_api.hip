@@ -328,6 +328,15 @@ ic_status run_indexer(const ic_indexer_desc *d, const void *q, const void *k, co
             int64_t max_vis = d->q_pos0 + i0 + ri;
             max_vis = max_vis < 0 ? 0 : (max_vis > d->Lk ? d->Lk : max_vis);
             if (pc && pc->seq_lens) max_vis = d->Lk;   // ragged: lengths are device data, Lk bounds them
+            if ((max_vis > d->k_sel || sel) && ic::topk_short(sa, d->dtype, d->d_I, bc * ri, max_vis)) {
+                se.b0 = b0;
+                se.i0 = i0;
+                se.Ri = ri;
+                ProfScope ps(0, st);
+                hipError_t e = ic::launch_topk_short(sa, se, d->d_I, bc, st);
+                if (e != hipSuccess) return fail(IC_ERR_HIP, "indexer launch failed: %s", hipGetErrorString(e));
+                continue;
+            }
             if (max_vis > d->k_sel || sel) {   // rows with <= k_sel visible keys need no scores
                 ProfScope ps(0, st);
                 hipError_t e = ic::launch_score(sa, d->dtype, d->d_I, bc, st);

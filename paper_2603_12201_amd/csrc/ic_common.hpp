@@ -214,6 +214,8 @@ __device__ __forceinline__ float row16_sum(float x)
 hipError_t launch_score(const ScoreArgs &a, int dtype, int d_I, int Bc, hipStream_t st);
 hipError_t launch_fill(float *p, int64_t n, float v, hipStream_t st);
 hipError_t launch_select(const SelectArgs &a, int n_rows, int max_row_len, hipStream_t st);
+bool topk_short(const ScoreArgs &a, int dtype, int d_I, int n_rows, int64_t max_vis);
+hipError_t launch_topk_short(const ScoreArgs &a, const SelectArgs &se, int d_I, int Bc, hipStream_t st);
 int select_parts(int n_rows, int max_row_len);
 bool select_parts_fit(int k, int row_len);
 size_t select_parts_bytes(int n_rows, int max_row_len);

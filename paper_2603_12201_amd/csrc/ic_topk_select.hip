@@ -17,8 +17,8 @@
 //            wave scan per word on the DPP path, one scan over the (sweep, wave) cells, two
 //            barriers in all.  When ties are cut at the boundary: per-sweep scans of packed
 //            greater / equal counts.
-// That is the form for whatever the others leave over.  Forms by row length: the bins form (launches whose rows have up to
-// 32768 keys), the candidate form (32769 to 131072 keys, k up to a quarter of them), the candidate form with a row spread
+// That is the form for whatever the others leave over.  Forms by row length: scores and top-k in one launch (few rows of up
+// to 1024 keys), the bins form (launches whose rows have up to 32768), the candidate form (32769 to 131072 keys, k up to a quarter of them), the candidate form with a row spread
 // over several workgroups (few rows of more than 65536 keys), and the radix select, with the keys cached in LDS (up to
 // 32768) or re-reading the row on every sweep.
 #include "ic_common.hpp"
@@ -46,9 +46,22 @@ constexpr int kBins1 = 4096;   // histogram bins: digits of 12, 12 and 8 key bit
 // Workgroup-wide descending scan over `nbins` counters: finds the digit d with
 // count(bins > d) < need <= count(bins >= d) and writes {d, need - count(bins > d), count(bin d)} to bc.
 // Every thread owns BPT consecutive bins, highest bins first.
-template <int NT, int BPT>
+struct BlockSync {
+    __device__ __forceinline__ void operator()() const { __syncthreads(); }
+};
+// A wave that works by itself: LDS serves it in order, so the compiler has to keep that order.
+struct WaveSync {
+    __device__ __forceinline__ void operator()() const
+    {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    }
+};
+
+template <int NT, int BPT, typename Sync = BlockSync>
 __device__ __forceinline__ void find_digit(const uint32_t *cnt, uint32_t need, uint32_t *wsum, uint32_t *bc,
-                                           int tid, int lane, int wave)
+                                           int tid, int lane, int wave, Sync sync = Sync())
 {
     constexpr int NW = NT / 64;
     const int top = NT * BPT - 1 - BPT * tid;          // highest bin of this thread
@@ -61,7 +74,7 @@ __device__ __forceinline__ void find_digit(const uint32_t *cnt, uint32_t need, u
     }
     uint32_t incl = wave_incl_scan(mine);
     if (lane == 63) wsum[wave] = incl;
-    __syncthreads();
+    sync();
     uint32_t before = 0;
 #pragma unroll
     for (int wv = 0; wv < NW; ++wv)
@@ -80,7 +93,7 @@ __device__ __forceinline__ void find_digit(const uint32_t *cnt, uint32_t need, u
             run += c[j];
         }
     }
-    __syncthreads();
+    sync();
 }
 
 // The radix select of one row (workgroup-wide; smem: kBins1 + 2 NW + 4 + a.cache_elems words).
@@ -676,41 +689,40 @@ __device__ __forceinline__ RowView row_view(const SelectArgs &a, int r)
 constexpr int kBinsLen = 32768;
 constexpr int kRankCap = 64;             // (each is compared with all others: 150 ties of 2400 keys cost more than the rest of the row)
 
-template <int NT, int NV, int NB, int WPE>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE))) void select_bins_kernel(SelectArgs a)
-{
-    constexpr int NW = NT / 64;
-    constexpr int kWords = NT * NV / 8;        // bitmap
-    constexpr int kList = kRankCap * 2 > IC_MAX_K ? kRankCap * 2 : IC_MAX_K;
+template <int NT, int NV, int NB>
+struct BinsLds {
+    static constexpr int NW = NT / 64;
+    static constexpr int kWords = NT * NV / 8; // bitmap
+    static constexpr int kList = kRankCap * 2 > IC_MAX_K ? kRankCap * 2 : IC_MAX_K;
     static_assert(NB % NT == 0, "whole bins per thread");
     // the histogram; once it is read the boundary bin's members (keys, positions), then the selected positions, and behind
     // them the bitmap
-    __shared__ __attribute__((aligned(16))) uint32_t smem[NB > kList + kWords ? NB : kList + kWords];
-    __shared__ uint32_t wsum[NW], bc[4], red[2 * NW];
-    __shared__ uint32_t misc[5];               // 0 members listed, 1 k-th key, 2 its position, 3 equal ones behind it, 4 odd scores
-    uint32_t *hist = smem, *member = smem, *member_at = smem + kRankCap, *out = smem, *bitmap = smem + kList;
+    uint32_t smem[NB > kList + kWords ? NB : kList + kWords];
+    uint32_t wsum[NW], bc[4], red[2 * NW];
+    uint32_t misc[5];                          // 0 members listed, 1 k-th key, 2 its position, 3 equal ones behind it, 4 odd scores
+};
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    request_args(a);
-    const int r = blockIdx.x;
-    const RowView rw = row_view(a, r);
-    if (rw.i >= a.Tq) return;
-    const int nv = rw.nv;
-    const float *row = a.strip + (int64_t)r * a.ld;
-    int32_t *oidx = a.idx + ((int64_t)rw.b * a.Tq + rw.i) * a.k_sel;
-    float *osel = a.sel ? a.sel + ((int64_t)rw.b * a.Tq + rw.i) * a.k_sel : nullptr;
-    const int k = a.k_sel;
-    if (nv <= k) {                             // every visible key is selected
-        if (k % 4 == 0 && (uintptr_t)oidx % 16 == 0) {
-            for (int s = 4 * tid; s < k; s += 4 * NT)
-                *(i32x4 *)(oidx + s) = i32x4{s < nv ? s : -1, s + 1 < nv ? s + 1 : -1, s + 2 < nv ? s + 2 : -1, s + 3 < nv ? s + 3 : -1};
-        } else {
-            for (int s = tid; s < k; s += NT) oidx[s] = s < nv ? s : -1;
-        }
-        if (osel)
-            for (int s = tid; s < k; s += NT) osel[s] = s < nv ? row[s] : -INFINITY;
-        return;
+// every visible key is selected (nv <= k)
+template <int NT>
+__device__ __forceinline__ void select_all(const float *row, int nv, int k, int32_t *oidx, float *osel, int tid)
+{
+    if (k % 4 == 0 && (uintptr_t)oidx % 16 == 0) {
+        for (int s = 4 * tid; s < k; s += 4 * NT)
+            *(i32x4 *)(oidx + s) = i32x4{s < nv ? s : -1, s + 1 < nv ? s + 1 : -1, s + 2 < nv ? s + 2 : -1, s + 3 < nv ? s + 3 : -1};
+    } else {
+        for (int s = tid; s < k; s += NT) oidx[s] = s < nv ? s : -1;
     }
+    if (osel)
+        for (int s = tid; s < k; s += NT) osel[s] = s < nv ? row[s] : -INFINITY;
+}
+
+// One row of nv > k scores (16-byte aligned, readable up to the next multiple of four) by NT threads that sync() brings together.
+template <int NT, int NV, int NB, typename Sync>
+__device__ __forceinline__ void bins_select(const float *row, int nv, int k, int32_t *oidx, float *osel, BinsLds<NT, NV, NB> &lds, int tid, Sync sync)
+{
+    constexpr int NW = NT / 64, kList = BinsLds<NT, NV, NB>::kList;
+    uint32_t *const smem = lds.smem, *const wsum = lds.wsum, *const bc = lds.bc, *const red = lds.red, *const misc = lds.misc;
+    uint32_t *hist = smem, *member = smem, *member_at = smem + kRankCap, *out = smem, *bitmap = smem + kList;
     const int nsteps = (nv + 4 * NT - 1) / (4 * NT);
     u32x4 v[NV];                               // scores, later maybe keys
 #pragma unroll
@@ -719,9 +731,10 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE))) void 
         if (p < nv) v[j] = *(const u32x4 *)(row + p);          // may run past nv inside the row's padding
     }
     const float f0 = row[0];
+    const int lane = tid & 63, wave = tid >> 6;
     for (int e = tid; e < NB; e += NT) hist[e] = 0;
     if (tid < 5) misc[tid] = 0;
-    __syncthreads();
+    sync();
     // Slots behind the row hold its first score, so that the sweeps below need no test; what they add is taken off the
     // counts again, and their bits off the bitmap.
     const uint32_t pad = (uint32_t)(nsteps * 4 * NT - nv);
@@ -747,7 +760,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE))) void 
                 red[wave] = mx;
                 red[NW + wave] = mn;
             }
-            __syncthreads();
+            sync();
             mx = wave_max_dpp(red[lane % NW]);
             mn = wave_max_dpp(red[NW + lane % NW]);
         }
@@ -776,7 +789,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE))) void 
             }
         if (__ballot(!(z == 0.f)) != 0ull && lane == 0) misc[4] = 1u;
         bounds(score_key(mx), score_key(mn));
-        if constexpr (NW == 1) __syncthreads();
+        if constexpr (NW == 1) sync();
         odd = misc[4] != 0u;
     }
     auto mark = [&](auto pred) __attribute__((always_inline)) {    // bit p of the bitmap: pred(key, p); eight lanes make a word
@@ -814,7 +827,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE))) void 
         }
         uint32_t before = wave_incl_scan(n);
         if (lane == 63) wsum[wave] = before;
-        __syncthreads();
+        sync();
         before -= n;
 #pragma unroll
         for (int wv = 0; wv < NW - 1; ++wv)
@@ -824,7 +837,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE))) void 
     uint32_t need = (uint32_t)k;
     // the members of the boundary bin, listed, ranked (keys descending, positions ascending): the last one wanted
     auto rank = [&](uint32_t n_b) __attribute__((always_inline)) {
-        __syncthreads();
+        sync();
         for (uint32_t m = tid; m < n_b; m += NT) {
             const uint32_t xm = member[m], pm = member_at[m];
             uint32_t ahead = 0, behind = 0;    // members that beat this one: larger, or equal at a lower position
@@ -840,7 +853,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE))) void 
                 misc[3] = behind;
             }
         }
-        __syncthreads();
+        sync();
     };
     auto list = [&](uint32_t key, int p) {
         const uint32_t m = atomicAdd(&misc[0], 1u);
@@ -858,8 +871,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE))) void 
         auto bin = [](float x, float from, float by) { return (uint32_t)((x - from) * by); };
         if (tid == 0) atomicSub(&hist[bin(f0, first, scale)], pad);
         each([&](uint32_t x, int) { atomicAdd(&hist[bin(__uint_as_float(x), first, scale)], 1u); });
-        __syncthreads();
-        find_digit<NT, NB / NT>(hist, need, wsum, bc, tid, lane, wave);
+        sync();
+        find_digit<NT, NB / NT>(hist, need, wsum, bc, tid, lane, wave, sync);
         const uint32_t b = bc[0], n_b = bc[2];
         need = bc[1];
         float from = first;                    // (opaque: bins are worked out again)
@@ -879,7 +892,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE))) void 
                     mn = min(mn, score_key(__uint_as_float(x)));
                 }
             });
-            __syncthreads();                   // (everybody has read hist, bc and red)
+            sync();                   // (everybody has read hist, bc and red)
             clear();
             bounds(mx, mn);
         }
@@ -889,7 +902,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE))) void 
             mx = max(mx, score_key(__uint_as_float(x)));
             mn = min(mn, score_key(__uint_as_float(x)));
         });
-        __syncthreads();
+        sync();
         bounds(mx, mn);
     }
     uint32_t tau, ptau;
@@ -908,11 +921,11 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE))) void 
             constexpr int kBits = 31 - __builtin_clz(NB);
             const int sh = bits > kBits ? bits - kBits : 0;
             const uint32_t span = hi - lo;
-            if constexpr (NW == 1) __syncthreads();
+            if constexpr (NW == 1) sync();
             if (tid == 0 && x0 - lo <= span) atomicSub(&hist[(x0 - lo) >> sh], pad);
             each([&](uint32_t x, int) { if (x - lo <= span) atomicAdd(&hist[(x - lo) >> sh], 1u); });
-            __syncthreads();
-            find_digit<NT, NB / NT>(hist, need, wsum, bc, tid, lane, wave);
+            sync();
+            find_digit<NT, NB / NT>(hist, need, wsum, bc, tid, lane, wave, sync);
             const uint32_t n_b = bc[2];
             need = bc[1];
             // the bin's keys (`from` opaque: differences are worked out again)
@@ -932,17 +945,17 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE))) void 
                     mn = min(mn, x);
                 }
             });
-            __syncthreads();
+            sync();
             clear();
             bounds(mx, mn);
         }
     }
     if (!scores && lo == hi) {                 // all members are equal: count up to the last one wanted
-        __syncthreads();
+        sync();
         tau = lo;
         cut = true;
         mark([&](uint32_t x, uint32_t) { return x == tau; });
-        __syncthreads();
+        sync();
         uint32_t m[MW];
         uint32_t before = mine(m);
 #pragma unroll
@@ -954,7 +967,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE))) void 
             }
             before += n;
         }
-        __syncthreads();
+        sync();
     } else {
         tau = misc[1];
         cut = misc[3] != 0u;
@@ -970,7 +983,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE))) void 
         mark([&](uint32_t x, uint32_t) { return x >= tau; });
     else
         mark([&](uint32_t x, uint32_t p) { return x > tau || (x == tau && p <= ptau); });
-    __syncthreads();
+    sync();
     {
         uint32_t m[MW];
         uint32_t slot = mine(m);
@@ -982,11 +995,123 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE))) void 
                 ++slot;
             }
     }
-    __syncthreads();
+    sync();
     for (int s = tid; s < k; s += NT) {
         oidx[s] = (int32_t)out[s];
         if (osel) osel[s] = key_score(score_key(row[out[s]]));   // (-0 as +0)
     }
+}
+
+template <int NT, int NV, int NB, int WPE>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE))) void select_bins_kernel(SelectArgs a)
+{
+    __shared__ __attribute__((aligned(16))) BinsLds<NT, NV, NB> lds;
+    const int tid = threadIdx.x;
+    request_args(a);
+    const int r = blockIdx.x;
+    const RowView rw = row_view(a, r);
+    if (rw.i >= a.Tq) return;
+    const float *row = a.strip + (int64_t)r * a.ld;
+    int32_t *oidx = a.idx + ((int64_t)rw.b * a.Tq + rw.i) * a.k_sel;
+    float *osel = a.sel ? a.sel + ((int64_t)rw.b * a.Tq + rw.i) * a.k_sel : nullptr;
+    if (rw.nv <= a.k_sel)
+        select_all<NT>(row, rw.nv, a.k_sel, oidx, osel, tid);
+    else
+        bins_select<NT, NV, NB>(row, rw.nv, a.k_sel, oidx, osel, lds, tid, BlockSync());
+}
+
+// ---- scores and top-k together (short rows) ----------------------------------------------------------------------
+// Rows that see at most kShortLen keys, of up to 32 bf16 heads: a workgroup scores two tokens of a sequence against all of their
+// keys, its waves taking every fourth subtile of 32 keys straight from memory (they are in L2), into LDS, and then a wave
+// selects a row by itself, in the bins form.  The scores are those of score_kernel, operation for operation.
+// What bounds it: one launch and its latencies; 512 rows of up to 512 keys (4 heads of 64) took two launches of 6.6 and 5.6 us.
+constexpr int kShortLen = 1024;
+constexpr int kShortNB = 512;            // bins
+constexpr int kShortRows = 2;            // of a workgroup (4: 512 rows of up to 512 keys 10.0 us, 9.8 with 2)
+
+template <int DI>
+__global__ __launch_bounds__(256, 1) void topk_short_kernel(ScoreArgs a, SelectArgs se)
+{
+    constexpr int KS = DI / 16, NV = kShortLen / 256, TT = kShortRows;
+    static_assert(TT <= 4, "a wave per row");
+    __shared__ __attribute__((aligned(16))) float score[TT][kShortLen];
+    __shared__ __attribute__((aligned(16))) BinsLds<64, NV, kShortNB> lds[TT];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r32 = lane & 31, half = lane >> 5;
+    asm volatile("" ::"s"(a.q), "s"(a.k), "s"(a.w), "s"(a.q_pos0), "s"(a.Tq), "s"(a.Lk), "s"(a.H_I), "s"(a.i0), "s"(a.Ri), "s"(a.b0), "s"(se.k_sel), "s"(se.idx), "s"(se.sel));   // (together: see request_args)
+    const int b = a.b0 + (int)blockIdx.y, t0 = a.i0 + TT * (int)blockIdx.x, t_end = min(a.i0 + a.Ri, a.Tq);
+    auto visible = [&](int t) -> int {
+        const int64_t n = a.q_pos0 + t + 1;
+        return (int)(n < 0 ? 0 : (n > a.Lk ? a.Lk : n));
+    };
+    const int most = visible(min(t0 + TT, t_end) - 1);
+    // (rows that select all they see need no scores)
+    if (most > se.k_sel || se.sel) {
+        bf16x8 qa[TT][KS];
+        float wr[TT][16];
+#pragma unroll
+        for (int j = 0; j < TT; ++j) {
+            const int64_t trow = (int64_t)b * a.Tq + min(t0 + j, t_end - 1);
+            const bool hv = r32 < a.H_I;
+            const unsigned short *src = (const unsigned short *)a.q + (trow * a.H_I + (hv ? r32 : 0)) * DI + 8 * half;
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                u32x4 x = *(const u32x4 *)(src + 16 * ks);
+                if (!hv) x = u32x4{0u, 0u, 0u, 0u};
+                qa[j][ks] = __builtin_bit_cast(bf16x8, x);
+            }
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const int h = 8 * (i / 4) + 4 * half + (i % 4);
+                const float w = a.w[trow * a.H_I + min(h, a.H_I - 1)];
+                wr[j][i] = h < a.H_I ? w : 0.f;
+            }
+        }
+        const unsigned short *kp = (const unsigned short *)a.k + (int64_t)b * a.Lk * DI + 8 * half;
+        auto load = [&](int s0, bf16x8 (&kb)[KS]) {
+            const unsigned short *src = kp + (int64_t)min(s0 + r32, a.Lk - 1) * DI;
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) kb[ks] = *(const bf16x8 *)(src + 16 * ks);
+        };
+        bf16x8 kb[2][KS];
+        load(32 * wave, kb[0]);
+#pragma unroll 1
+        for (int s0 = 32 * wave; s0 < most; s0 += 256) {
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {      // two subtiles a turn, each requested one ahead
+                const int s = s0 + 128 * u;
+                if (s >= most) break;
+                load(min(s + 128, a.Lk - 1), kb[u ^ 1]);
+#pragma unroll
+                for (int j = 0; j < TT; ++j) {
+                    f32x16 acc;
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+#pragma unroll
+                    for (int ks = 0; ks < KS; ++ks) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qa[j][ks], kb[u][ks], acc, 0, 0, 0);
+                    float x = 0.f;
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) {
+                        const int bits = __float_as_int(acc[i]);
+                        x = fmaf(__int_as_float(bits > 0 ? bits : 0), wr[j][i], x);
+                    }
+                    const auto both = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+                    const float v = __uint_as_float(both[0]) + __uint_as_float(both[1]);
+                    if (half == 0) score[j][s + r32] = v;
+                }
+            }
+        }
+    }
+    __syncthreads();
+    const int t = t0 + wave;
+    if (wave >= TT || t >= t_end) return;
+    const int nv = visible(t);
+    int32_t *oidx = se.idx + ((int64_t)b * a.Tq + t) * se.k_sel;
+    float *osel = se.sel ? se.sel + ((int64_t)b * a.Tq + t) * se.k_sel : nullptr;
+    if (nv <= se.k_sel)
+        select_all<64>(score[wave], nv, se.k_sel, oidx, osel, lane);
+    else
+        bins_select<64, NV, kShortNB>(score[wave], nv, se.k_sel, oidx, osel, lds[wave], lane, WaveSync());
 }
 
 // ---- parts form (few long rows) ---------------------------------------------------------------------------------
@@ -1381,6 +1506,27 @@ hipError_t launch_select(const SelectArgs &a_in, int n_rows, int max_row_len, hi
     }
     // longer rows, too many for the parts form, are streamed on every sweep
     hipLaunchKernelGGL((select_kernel<1024>), dim3((unsigned)n_rows), dim3(1024), select_lds_bytes(0), st, a);
+    return hipGetLastError();
+}
+
+// Rows that topk_short_kernel takes: few enough that the launch it saves counts for more than what score_kernel gains by sharing
+// its keys among more rows.  us, two launches / one (the caller's own 9.7 us bound the shorter ones): 4 heads of 64, 512 rows of
+// up to 512 keys 12.5 / 9.8, 3 x 512 15.2 / 12.5, 1000 of 1000 14.0 / 12.7, 2 x 1000 18.5 / 19.4; 32 heads of 128, 512 rows of 512
+// 13.1 / 11.1, 64 of 900 12.3 / 15.2.
+bool topk_short(const ScoreArgs &a, int dtype, int d_I, int n_rows, int64_t max_vis)
+{
+    if (dtype != IC_BF16 || a.H_I > 32 || a.pv.seq_lens || a.pv.page_table) return false;
+    if (d_I == 64) return max_vis <= kShortLen && n_rows * max_vis <= 1 << 20;
+    return d_I == 128 && max_vis <= kShortLen / 2 && n_rows * max_vis <= 1 << 18;
+}
+
+hipError_t launch_topk_short(const ScoreArgs &a, const SelectArgs &se, int d_I, int Bc, hipStream_t st)
+{
+    const dim3 grid((unsigned)((a.Ri + kShortRows - 1) / kShortRows), (unsigned)Bc);
+    if (d_I == 64)
+        hipLaunchKernelGGL(topk_short_kernel<64>, grid, dim3(256), 0, st, a, se);
+    else
+        hipLaunchKernelGGL(topk_short_kernel<128>, grid, dim3(256), 0, st, a, se);
     return hipGetLastError();
 }
 

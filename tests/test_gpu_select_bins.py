@@ -21,7 +21,10 @@ def check(ic, oracle, q, k, w, ks, p0):
     idx, sel = idx.cpu().numpy(), sel.cpu().numpy()
     for b in range(q.shape[0]):
         for i in range(q.shape[1]):
-            n = min(p0 + i + 1, k.shape[1])
+            n = max(0, min(p0 + i + 1, k.shape[1]))
+            if n == 0:
+                assert np.all(idx[b, i] == -1)
+                continue
             want = oracle.topk_row(sc[b, i], n, ks)["idx"]
             want = np.sort(want[want >= 0])
             assert np.array_equal(idx[b, i][:len(want)], want), (b, i, n)
@@ -74,3 +77,36 @@ def test_score_shapes(ic, oracle, L, kind):
     q, k, w = q.to(torch.bfloat16).cuda(), k.to(torch.bfloat16).cuda(), w.cuda()
     for ks in (7, 600):
         check(ic, oracle, q, k, w, ks, L - 2)
+
+
+@pytest.mark.parametrize("L", [5, 511, 1024, 1025])
+@pytest.mark.parametrize("ks", [3, 200])
+def test_lengths_of_two_head_tiles(ic, oracle, L, ks):
+    """40 heads: scores and selection are launches of their own at any length."""
+    print("[case] bins, 40 heads, L=%d k=%d" % (L, ks), flush=True)
+    g = torch.Generator().manual_seed(L + ks)
+    T = min(L, 3)
+    q = (torch.randn((2, T, 40, 64), generator=g) / 8).to(torch.bfloat16).cuda()
+    k = torch.randn((2, L, 64), generator=g).to(torch.bfloat16).cuda()
+    check(ic, oracle, q, k, torch.randn((2, T, 40), generator=g).cuda(), ks, L - T)
+
+
+@pytest.mark.parametrize("B, T, L, H, d, p0, ks", [
+    (1, 512, 512, 4, 64, 0, 64), (3, 37, 200, 1, 64, 163, 20), (2, 31, 31, 17, 64, -3, 4), (1, 1, 1024, 32, 64, 1023, 1023),
+    (1, 5, 1024, 32, 64, 1020, 1024), (2, 9, 512, 32, 128, 503, 100), (1, 300, 300, 20, 128, 0, 33), (1, 511, 512, 31, 128, 0, 511),
+    (1, 40, 40, 8, 128, 100, 7), (1023, 1, 1024, 2, 64, 1023, 100),
+])
+def test_scores_and_selection_in_one_launch(ic, oracle, B, T, L, H, d, p0, ks):
+    """Against the scores of the kernel that writes them out: bit for bit the same, so the same choice and the same values."""
+    print("[case] short B=%d T=%d L=%d H=%d d=%d p0=%d k=%d" % (B, T, L, H, d, p0, ks), flush=True)
+    g = torch.Generator().manual_seed(B + T + L)
+    q = (torch.randn((B, T, H, d), generator=g) / d ** 0.5).to(torch.bfloat16).cuda()
+    k = torch.randn((B, L, d), generator=g).to(torch.bfloat16).cuda()
+    w = torch.randn((B, T, H), generator=g).cuda()
+    if B > 100:
+        idx = ic.indexer_topk(q, k, w, ks, p0).cpu().numpy()
+        sc = ic.debug_indexer_scores(q, k, w, p0, 0, T).cpu().numpy()
+        for b in range(0, B, 60):
+            assert np.array_equal(idx[b, 0], np.sort(oracle.topk_row(sc[b, 0], L, ks)["idx"])), b
+    else:
+        check(ic, oracle, q, k, w, ks, p0)
