@@ -374,11 +374,11 @@ constexpr int kCandMinLen = 8192;        // shorter rows of a launch take the ge
 constexpr int kCandMaxLen = 131072;      // bitmap capacity
 constexpr int kCandSample = 4096;
 constexpr int kBoundaryCap = 1024;       // boundary-bin members ranked exactly
-constexpr int cand_aux_words(int maxlen) { return maxlen / 32 > 2 * kBoundaryCap ? maxlen / 32 : 2 * kBoundaryCap; }
-constexpr int cand_lds_words(int nt, int maxlen, int cap)
-{
-    return kBins1 + 2 * (nt / 64) + 4 + 16 + 2 * cap + maxlen / 32 + cand_aux_words(maxlen);
-}
+// A second instance for launches of more rows than CUs: half the threads and half the LDS, so that two rows are in flight per CU
+// (a row's phases are chains of latencies; a second workgroup fills them), and a threshold nearer to the k-th key.  us, before /
+// with it: 257 rows of 41700 keys 34 / 21, 700 59 / 47, 2048 rows of up to 40000 keys 165 / 111, 65536 198 / 165, 131072 286 / 239.
+constexpr int kCandManyCap = 5632;
+constexpr int cand_lds_words(int nt, int maxlen, int cap) { return kBins1 + 2 * (nt / 64) + 4 + 16 + 2 * cap + maxlen / 32; }
 
 // Largest value over the 64 lanes of a wave, in every lane (no LDS traffic; lanes without a source keep their own).
 __device__ __forceinline__ uint32_t wave_max_dpp(uint32_t x)
@@ -394,7 +394,7 @@ __device__ __forceinline__ uint32_t wave_max_dpp(uint32_t x)
     return (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
 }
 
-template <int NT, int MAXLEN, int CAP>
+template <int NT, int MAXLEN, int CAP, bool MANY>
 __global__ __launch_bounds__(NT) void select_cand_kernel(SelectArgs a)
 {
     static_assert(kCandSample % (4 * NT) == 0 && (MAXLEN / 32) % NT == 0, "whole sample vectors and bitmap words per thread");
@@ -410,8 +410,9 @@ __global__ __launch_bounds__(NT) void select_cand_kernel(SelectArgs a)
     uint32_t *ckey = misc + 16;                // [CAP]
     uint32_t *cpos = ckey + CAP;               // [CAP]
     uint32_t *bitmap = cpos + CAP;             // [MAXLEN / 32]
-    uint32_t *wpre = bitmap + MAXLEN / 32;     // [max(MAXLEN / 32, 2 kBoundaryCap)] selected entries ahead of each bitmap
-                                               // word; before that: the boundary bin's members (key, position)
+    // once the histograms are read: the boundary bin's members (key, position), then the selected entries ahead of each bitmap word
+    uint32_t *wpre = hist;
+    static_assert(2 * kBoundaryCap <= kBins1 && MAXLEN / 32 <= kBins1, "they share its space");
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int r = blockIdx.x;
@@ -473,14 +474,14 @@ __global__ __launch_bounds__(NT) void select_cand_kernel(SelectArgs a)
     {
         const uint32_t mx = wave_max_dpp(kmx);
         const uint32_t mn = ~wave_max_dpp(~kmn);
-        if (lane == 0) {                       // (wpre is free until the boundary list is built)
-            wpre[wave] = mn;
-            wpre[NW + wave] = mx;
+        if (lane == 0) {
+            wsum[wave] = mn;
+            wsum[NW + wave] = mx;
         }
     }
     __syncthreads();
-    const uint32_t smin = ~wave_max_dpp(~(lane < NW ? wpre[lane] : 0xFFFFFFFFu));
-    const uint32_t smax = wave_max_dpp(lane < NW ? wpre[NW + lane] : 0u);
+    const uint32_t smin = ~wave_max_dpp(~(lane < NW ? wsum[lane] : 0xFFFFFFFFu));
+    const uint32_t smax = wave_max_dpp(lane < NW ? wsum[NW + lane] : 0u);
     const uint32_t srange = smax - smin;
     const int sbits = srange ? 32 - __clz((int)srange) : 0;
     const int ssh = sbits > 12 ? sbits - 12 : 0;
@@ -488,6 +489,10 @@ __global__ __launch_bounds__(NT) void select_cand_kernel(SelectArgs a)
     for (int e = 0; e < 4 * SV; ++e) atomicAdd(&hist[(skey[e] - smin) >> ssh], 1u);
     __syncthreads();
     uint32_t want = (uint32_t)(((int64_t)kCandSample * 2 * k) / nv) + 32u;
+    if (MANY) {                                // k of nv keys are `mean` of the sample, give or take its root
+        const float mean = (float)kCandSample * (float)k / (float)nv;
+        want = (uint32_t)(mean + 4.f * __builtin_sqrtf(mean)) + 16u;
+    }
     want = want > (uint32_t)kCandSample ? (uint32_t)kCandSample : want;
     find_digit<NT, kBins1 / NT>(hist, want, wsum, bc, tid, lane, wave);
     const uint32_t T0 = smin + (bc[0] << ssh); // a bin's lower edge: at least `want` sampled keys reach it
@@ -652,7 +657,7 @@ __global__ __launch_bounds__(NT) void select_cand_kernel(SelectArgs a)
     if (!candidate_form()) {
         SelectArgs ga = a;
         // the candidate arrays' space serves as the row cache (rows that do not fit it are streamed)
-        constexpr int kSpace = 16 + 2 * CAP + MAXLEN / 32 + cand_aux_words(MAXLEN);
+        constexpr int kSpace = 16 + 2 * CAP + MAXLEN / 32;
         ga.cache_elems = kSpace >= 32768 ? 32768 : kSpace / 64 * 64;
         select_row_generic<NT>(ga, smem);
     }
@@ -1498,10 +1503,18 @@ hipError_t launch_select(const SelectArgs &a_in, int n_rows, int max_row_len, hi
     if (max_row_len <= kCandMaxLen && max_row_len >= 4 * a.k_sel) {
         // one read of the row, a sampled threshold and a candidate list (falls back row by row)
         constexpr int lds = cand_lds_words(1024, kCandMaxLen, kCandCap) * (int)sizeof(uint32_t);
-        static hipError_t attr = hipFuncSetAttribute((const void *)select_cand_kernel<1024, kCandMaxLen, kCandCap>,
+        constexpr int lds_many = cand_lds_words(512, kCandMaxLen, kCandManyCap) * (int)sizeof(uint32_t);
+        static_assert(2 * lds_many <= 160 * 1024, "two workgroups per CU");
+        static hipError_t attr = hipFuncSetAttribute((const void *)select_cand_kernel<1024, kCandMaxLen, kCandCap, false>,
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        static hipError_t attr_many = hipFuncSetAttribute((const void *)select_cand_kernel<512, kCandMaxLen, kCandManyCap, true>,
+                                                          hipFuncAttributeMaxDynamicSharedMemorySize, lds_many);
         if (attr != hipSuccess) return attr;
-        hipLaunchKernelGGL((select_cand_kernel<1024, kCandMaxLen, kCandCap>), dim3((unsigned)n_rows), dim3(1024), lds, st, a);
+        if (attr_many != hipSuccess) return attr_many;
+        if (n_rows > 256)
+            hipLaunchKernelGGL((select_cand_kernel<512, kCandMaxLen, kCandManyCap, true>), dim3((unsigned)n_rows), dim3(512), lds_many, st, a);
+        else
+            hipLaunchKernelGGL((select_cand_kernel<1024, kCandMaxLen, kCandCap, false>), dim3((unsigned)n_rows), dim3(1024), lds, st, a);
         return hipGetLastError();
     }
     // longer rows, too many for the parts form, are streamed on every sweep

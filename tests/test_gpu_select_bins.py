@@ -110,3 +110,22 @@ def test_scores_and_selection_in_one_launch(ic, oracle, B, T, L, H, d, p0, ks):
             assert np.array_equal(idx[b, 0], np.sort(oracle.topk_row(sc[b, 0], L, ks)["idx"])), b
     else:
         check(ic, oracle, q, k, w, ks, p0)
+
+
+@pytest.mark.parametrize("L, ks", [(32900, 2048), (60001, 100), (131072, 2048)])
+def test_more_long_rows_than_workgroups(ic, oracle, L, ks):
+    """The candidate form with two rows per CU: rows at random, of one value, and with their best scores together."""
+    print("[case] many long rows L=%d k=%d" % (L, ks), flush=True)
+    T = 300
+    g = torch.Generator().manual_seed(L)
+    q = (torch.randn((1, T, 2, 64), generator=g) / 8)
+    q[0, 5] = 0                                                             # all scores equal
+    q[0, 7] = 0
+    q[0, 7, 0, 3] = 1.0                                                     # the score is the key's third feature: one stretch stands out
+    k = torch.randn((1, L, 64), generator=g)
+    k[0, 20000:23000, 3] = 5 + torch.rand(3000, generator=g)
+    q, k, w = q.to(torch.bfloat16).cuda(), k.to(torch.bfloat16).cuda(), torch.rand((1, T, 2), generator=g).cuda()
+    idx = ic.indexer_topk(q, k, w, ks, L - T).cpu().numpy()
+    for i in (0, 5, 7, 100, 256, 299):
+        sc = ic.debug_indexer_scores(q, k, w, L - T, i, 1).cpu().numpy()
+        assert np.array_equal(idx[0, i], np.sort(oracle.topk_row(sc[0, 0], L - T + i + 1, ks)["idx"])), i
