@@ -657,6 +657,10 @@ ic_status run_lead_rest(const LeadJob *jobs, int n_jobs, float *lse, void *ws, s
             ra.lead[i] = j.lead + (int64_t)b0 * n_chunks;
             ra.lead2[i] = j.lead2 + (int64_t)b0 * n_chunks;
         }
+        a.Q = a.Qs[0];                         // (one sequence of one layer is read here)
+        a.KV = a.KVs[0];
+        a.O = a.Os[0];
+        a.idx = ra.idx[0];
         hipError_t e = ic::launch_attn_rest(a, ra, st);
         if (e != hipSuccess) return fail(IC_ERR_HIP, "sparse attention launch failed: %s", hipGetErrorString(e));
     }

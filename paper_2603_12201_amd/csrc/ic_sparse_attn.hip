@@ -1371,7 +1371,9 @@ __global__ __launch_bounds__(512, 2) void attn_stream_kernel(AttnArgs a, RestArg
     // REST: numbers of the sequences' first queries, [n_jobs * B] and their total
     unsigned *const start = (unsigned *)(filled + kStreamRing * kGranule * 8);
     const int n_seq = REST ? ra.n_jobs * a.B : 0;
-    if constexpr (REST) {
+    if (REST && n_seq == 1) {                             // (every wave for itself)
+        nq = (unsigned)max(0, ra.n_rows - __builtin_amdgcn_readfirstlane(min(lead_rows(ra.lead[0], ra.n_chunks), lead_rows(ra.lead2[0], ra.n_chunks))));
+    } else if constexpr (REST) {
         // lanes to a sequence: 64 for up to 8 of them, down to 8
         const int bits = n_seq <= 8 ? 6 : (n_seq <= 16 ? 5 : (n_seq <= 32 ? 4 : 3)), per = 1 << bits;
         for (int s = tid >> bits; s < n_seq; s += 512 >> bits) {
@@ -1618,6 +1620,10 @@ __global__ __launch_bounds__(512, 2) void attn_stream_kernel(AttnArgs a, RestArg
     struct Place { int n, ng; bool is_q; const int32_t *idx; const unsigned short *kv, *q, *src; int len, b; } pl;
     auto tensor_row = [&](unsigned gq, int &layer, int &b) __attribute__((always_inline)) -> int64_t {
         if constexpr (REST) {
+            if (n_seq == 1) {                             // (a look at LDS per query: 333 us for 2048 rows, 327 without)
+                layer = b = 0;
+                return ra.n_rows - (int)(nq - gq);
+            }
             int s = -1;                                   // the last sequence that starts at gq or before it
             for (int s0 = 0; s0 < n_seq; s0 += 64) {
                 const int n = __popcll(__ballot(s0 + lane < n_seq && start[min(s0 + lane, n_seq)] <= gq));
@@ -1637,9 +1643,16 @@ __global__ __launch_bounds__(512, 2) void attn_stream_kernel(AttnArgs a, RestArg
         const unsigned gq = query(i);
         int layer;
         const int64_t row = tensor_row(gq, layer, pl.b);
-        pl.idx = (REST ? ra.idx[layer] : a.idx) + row * a.k_sel;
-        pl.q = (const unsigned short *)(MULTI || REST ? a.Qs[layer] : a.Q) + row * a.H_q * D_QK;
-        pl.kv = (const unsigned short *)(MULTI || REST ? a.KVs[layer] : a.KV) + (PG && a.pv.page_table ? 0 : (int64_t)pl.b * a.Lk * a.row_elems);
+        const void *idx_l = a.idx, *q_l = a.Q, *kv_l = a.KV;
+        if (MULTI || (REST && n_seq > 1)) {
+            if (REST) asm volatile("");                   // (a branch: the loads' latency is not for one sequence)
+            if (REST) idx_l = ra.idx[layer];
+            q_l = a.Qs[layer];
+            kv_l = a.KVs[layer];
+        }
+        pl.idx = (const int32_t *)idx_l + row * a.k_sel;
+        pl.q = (const unsigned short *)q_l + row * a.H_q * D_QK;
+        pl.kv = (const unsigned short *)kv_l + (PG && a.pv.page_table ? 0 : (int64_t)pl.b * a.Lk * a.row_elems);
         pl.len = PG && a.pv.seq_lens ? max(0, min(load_uniform(a.pv.seq_lens + pl.b), a.Lk)) : a.Lk;     // (ids are compared unsigned)
         pl.ng = granules(i);
     };
@@ -1800,7 +1813,12 @@ __global__ __launch_bounds__(512, 2) void attn_stream_kernel(AttnArgs a, RestArg
                 for (int e = 0; e < 4; ++e) v[e] = __builtin_bit_cast(short, (__bf16)(o_acc[nb][4 * qd + e] * inv));
                 *(s16x4 *)(ob + row_l * OSTR + (32 * nb + 8 * qd + 4 * half) * 2) = v;
             }
-        unsigned short *const o = (unsigned short *)(MULTI || REST ? a.Os[layer] : a.O) + row * a.H_q * D_V + 128 * w;
+        void *o_l = a.O;
+        if (MULTI || (REST && n_seq > 1)) {
+            if (REST) asm volatile("");
+            o_l = a.Os[layer];
+        }
+        unsigned short *const o = (unsigned short *)o_l + row * a.H_q * D_V + 128 * w;
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
             const int head = 4 * k + (ln >> 4);
