@@ -222,7 +222,7 @@ size_t attn_query_bytes(const ic_attn_desc *d)
 // (called one after the other such layers would see each other's results).  Per layer, launches with few queries are
 // mostly latency (a launch and its merge of one decode token: 13.5 us for 2.4 MB of rows) and a last round of a few
 // workgroups.  576 / 512 rows: together up to twelve rounds of queries a layer, from where on the layers' caches in turn are
-// worth as much as the launches saved.  Four layers of causal rows, together / a launch each: 64 rows 11.9 / 36.5 us, 256 40 / 64, 700
+// worth as much as the launches saved.  Four layers of causal rows in the row forms, together / a launch each: 64 rows 11.9 / 36.5 us, 256 40 / 64, 700
 // behind 1700 476 / 545, 2100 821 / 863, 3000 1430 / 1449, 4096 2195 / 2155.  Other rows: where an eighth of the tile
 // times or more is saved.
 struct Range {
@@ -470,11 +470,11 @@ ic_attn_desc rows_behind(const ic_attn_desc *d, int n)
 // 53 / 85, 1024 155 / 172, 2048 530 / 540, 4 x 256 79 / 101, 16 x 32 32.4 / 37.8, 3 x 1021 498 / 484.
 int dense_batch(const ic_attn_desc *d, int n) { return ((int64_t)n * d->H_q + 63) / 64 * d->B <= 4 * 256 ? ic::kMaxBatchLayers : 1; }
 
-// How many of them it takes, for one of n_layers layers that the row forms would take together.  The rows behind (ws_bytes:
+// How many of them it takes, for n_layers layers that the row forms would take together.  The rows behind (ws_bytes:
 // workspace for their splits) are a launch of their own, with some 11 us for the two ends between them.  Measured, k = 2048, row forms / dense form (and
 // what is left): 128 rows 12.5 / 12.6 us, 320 21.2 / 18.0, 1024 64 / 46, 4 x 64 11.8 / 11.9, 16 x 32 19.0 / 13.3, 256 rows behind 1792
-// 48.5 / 54.7, 512 behind 1536 84 / 67; four layers: 64 rows 11.9 / 37.5, 512 82 / 90, 768 144 / 120, 16 x 32 39 / 51, 4 x 256
-// 125 / 104; with rows left: 4 x 256 behind 1800 204 / 182, behind 1900 198 / 229, four layers 684 / 621 and 724 / 860.
+// 48.5 / 54.7, 512 behind 1536 84 / 67; four layers: 128 rows 22 / 15.6, 512 82 / 53, 768 144 / 95, 16 x 32 39 / 32, 4 x 256
+// 125 / 80; with rows left: 4 x 256 behind 1800 204 / 182, behind 1900 198 / 229, four layers 684 / 541 and 724 / 612.
 int dense_queries(const ic_attn_desc *d, int n_layers, Causal c, size_t ws_bytes)
 {
     const int n = prefix_queries(d, c);
