@@ -93,6 +93,8 @@ struct PartArgs {
     uint32_t *heads;      // [rows][head_words]: threshold key, then the lengths of the row's lists
     uint32_t *lists;      // [rows][2][list entries]: keys, positions; the parts' lists in equal shares
     int32_t n_parts, head_words;
+    int32_t slots;        // entries of a list
+    uint32_t inv_parts;   // 2^32 / n_parts, rounded up (two parts or more)
 };
 
 // One launch covers n_layers layers of one shape that read the same index tensor (a Full layer and the Shared layers
@@ -218,6 +220,7 @@ bool topk_short(const ScoreArgs &a, int dtype, int d_I, int n_rows, int64_t max_
 hipError_t launch_topk_short(const ScoreArgs &a, const SelectArgs &se, int d_I, int Bc, hipStream_t st);
 int select_parts(int n_rows, int max_row_len);
 bool select_parts_fit(int k, int row_len);
+int select_parts_slots(int n_rows, int max_row_len);
 size_t select_parts_bytes(int n_rows, int max_row_len);
 hipError_t launch_select_parts(const SelectArgs &a, int n_rows, int max_row_len, void *ws, hipStream_t st);
 hipError_t launch_attn(const AttnArgs &a, int d_qk, int d_v, hipStream_t st);

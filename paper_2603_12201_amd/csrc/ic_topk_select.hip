@@ -1127,7 +1127,7 @@ __global__ __launch_bounds__(256, 1) void topk_short_kernel(ScoreArgs a, SelectA
 //                         threshold T0), then sweeps its own keys and leaves its candidates in a list of its own in the
 //                         workspace.  A part has every n-th block of 32 keys, so that the lists of a row whose best keys lie
 //                         together are as long as those of any other
-//   select_finish_kernel  one workgroup per row takes all lists into registers (32 slots a thread, requested before their
+//   select_finish_kernel  one workgroup per row takes all lists into registers (16 slots a thread, requested before their
 //                         lengths are known), finds the k-th largest candidate with one histogram and an exact ranking of
 //                         its bin, and emits through a bitmap of the row in LDS
 // A row that the candidates cannot decide (fewer than k of them, a list that overflowed, too many ties in the boundary
@@ -1149,13 +1149,15 @@ constexpr int kPartRows = 64;            // ... and are at most this many: more 
 constexpr int kPartRowsLong = 512;       // which holds for longer where the alternative streams the row four times
 constexpr int kFinishThreads = 1024;
 constexpr int kFinishSlots = 16384;      // list entries of a row, its parts' lists in equal shares of them
-constexpr int kFinishCap = 12288;        // candidates of a row that are likely to find room in them
+constexpr int kFinishCap = 12288;        // candidates of a row that are likely to find room in them: the lists' lengths and the threshold scatter
 constexpr int kFinishWindow = 1 << 20;   // keys that the bitmap covers at a time
 
 // per row: T0, then the lists' lengths
 constexpr int kPartHead = 1 + kPartMax;
-__host__ __device__ inline int part_bits(int n_parts) { return n_parts > 1 ? 32 - __builtin_clz((unsigned)n_parts - 1) : 0; }
-__host__ __device__ inline int part_slots(int n_parts) { return kFinishSlots >> part_bits(n_parts); }
+// Entries of a part's list, in lines of 32.  (Shares of a power of two, one wave's vector of them or more, left 7 rows, of 36 parts, room
+// for 9216 entries: every second row of 500 000 keys overflowed them and took the radix select behind both launches.)
+constexpr int kListLine = 32;
+inline int part_slots(int n_parts) { return kFinishSlots / kListLine / n_parts * kListLine; }
 
 // rows the sample can speak for
 __device__ __forceinline__ bool part_row(const SelectArgs &a, int nv) { return nv >= kCandMinLen && nv >= 4 * a.k_sel; }
@@ -1218,7 +1220,7 @@ __global__ __launch_bounds__(kPartThreads) void select_part_kernel(SelectArgs a,
     const uint32_t T0 = smin + (bc[0] << ssh);
     const float T0f = key_score(T0);
 
-    const uint32_t slots = (uint32_t)part_slots(pa.n_parts);
+    const uint32_t slots = (uint32_t)pa.slots;
     uint32_t *keys = pa.lists + (size_t)r * 2 * kFinishSlots + part * slots, *pos = keys + kFinishSlots;
     const int n_blk = ((nv + kPartBlock - 1) / kPartBlock - part + pa.n_parts - 1) / pa.n_parts;     // of this part
     for (int i0 = 0; i0 < n_blk; i0 += NW * 8 * kGroup) {      // workgroup-uniform
@@ -1278,27 +1280,35 @@ __global__ __launch_bounds__(kFinishThreads) void select_finish_kernel(SelectArg
         const uint32_t *head = pa.heads + (size_t)r * pa.head_words;
         const uint32_t *keys = pa.lists + (size_t)r * 2 * kFinishSlots;
         const float *row = a.strip + (int64_t)r * a.ld;
-        const int lg = 14 - part_bits(pa.n_parts);             // slots of a list, 256 or more: a wave's vectors are of one
-        static_assert(kFinishSlots == 1 << 14 && kFinishSlots / kPartMax >= 256, "a list takes whole vectors of a wave");
+        // A vector's entry: all lists' first lines, then their second ones: empty slots lie together, and waves of them have nothing to
+        // do (list behind list 0.8 us longer for 48 lists of 117 entries).
+        auto list_of = [&](int j, int &first) {
+            const int line = (j * NT + tid) / (kListLine / 4);
+            const int of_list = pa.n_parts == 1 ? line : (int)__umulhi((unsigned)line, pa.inv_parts);
+            first = of_list * kListLine + 4 * (tid % (kListLine / 4));
+            return line - of_list * pa.n_parts;
+        };
         u32x4 v[NV], at[NV];
 #pragma unroll
         for (int j = 0; j < NV; ++j) {
-            const int s = (j * NT + tid) * 4;
+            int first;
+            const int list = list_of(j, first);
             v[j] = u32x4{0u, 0u, 0u, 0u};
-            if (s >> lg < pa.n_parts) v[j] = *(const u32x4 *)(keys + s);
+            if (first < pa.slots) v[j] = *(const u32x4 *)(keys + list * pa.slots + first);
         }
         const uint32_t T0 = head[0];
         const uint32_t n_lane = lane < pa.n_parts ? head[1 + lane] : 0u;
         const uint32_t n_cand = (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan(n_lane), 63), k = (uint32_t)a.k_sel;
-        if (n_cand < k || __ballot(n_lane > 1u << lg) != 0ull) return false;   // workgroup-uniform
+        if (n_cand < k || __ballot(n_lane > (uint32_t)pa.slots) != 0ull) return false;   // workgroup-uniform
         // slots behind a list's end: key 0, below every candidate (T0 is above the smallest sampled key or a bin's edge)
         uint32_t mx = 0;
 #pragma unroll
         for (int j = 0; j < NV; ++j) {
-            const int s = (j * NT + tid) * 4, part = __builtin_amdgcn_readfirstlane(s >> lg);
-            const int left = (int)(__builtin_amdgcn_readlane((int)n_lane, part)) - (s & ((1 << lg) - 1));
+            int first;
+            const int list = list_of(j, first);
+            const int left = first < pa.slots ? (int)__shfl(n_lane, list) - first : 0;
             at[j] = u32x4{0u, 0u, 0u, 0u};
-            if (left > 0) at[j] = *(const u32x4 *)(keys + kFinishSlots + s);
+            if (left > 0) at[j] = *(const u32x4 *)(keys + kFinishSlots + list * pa.slots + first);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 v[j][e] = e < left ? v[j][e] : 0u;
@@ -1435,13 +1445,13 @@ size_t select_lds_bytes(int cache_elems)
 } // namespace
 
 // A row of this length leaves about 2 k + 1 / 128 of its keys as candidates (the rank that select_part_kernel takes from the
-// sample).  Where the second launch does not hold that many, the row would go to the radix select behind two launches for
+// sample).  Where the lists (some kFinishSlots together at any number of parts) are unlikely to hold that many, the row would go to the radix select behind two launches for
 // nothing (k = 2048: from 1.05 M keys; 1.1 M keys 745 us without, 755 with them).  The sample scatters by some 14 %: a row
 // shortly below the line may still get there, and gains tenfold where it does not (1 M keys 727 / 60 us).
 bool select_parts_fit(int k, int row_len) { return (int64_t)2 * k + row_len / 128 <= kFinishCap; }
 
 // Parts of a row when n_rows rows of up to max_row_len keys are selected together: enough for one workgroup per CU,
-// stretches of at least 256 keys per wave; 0 = the row-per-workgroup forms take the rows.
+// of at least 4096 keys (a vector a thread); 0 = the row-per-workgroup forms take the rows.
 int select_parts(int n_rows, int max_row_len)
 {
     if (n_rows < 1 || max_row_len <= kPartFrom || n_rows > (max_row_len > kCandMaxLen ? kPartRowsLong : kPartRows)) return 0;
@@ -1449,6 +1459,13 @@ int select_parts(int n_rows, int max_row_len)
     const int most = max_row_len / (256 * kPartWaves);
     p = p > most ? most : p;
     return p < 1 ? 1 : (p > kPartMax ? kPartMax : p);
+}
+
+// Room in the list of each of them.
+int select_parts_slots(int n_rows, int max_row_len)
+{
+    const int p = select_parts(n_rows, max_row_len);
+    return p == 0 ? 0 : part_slots(p);
 }
 
 size_t select_parts_bytes(int n_rows, int max_row_len)
@@ -1462,6 +1479,8 @@ hipError_t launch_select_parts(const SelectArgs &a_in, int n_rows, int max_row_l
     a.cache_elems = 0;
     PartArgs pa;
     pa.n_parts = select_parts(n_rows, max_row_len);
+    pa.slots = part_slots(pa.n_parts);
+    pa.inv_parts = (uint32_t)((((uint64_t)1 << 32) + pa.n_parts - 1) / pa.n_parts);
     pa.head_words = (kPartHead + 63) / 64 * 64;
     pa.heads = (uint32_t *)ws;
     pa.lists = pa.heads + (size_t)n_rows * pa.head_words;

@@ -25,6 +25,11 @@ def ic():
     (1, 2, 150000, 4, 64, 7),
     (64, 1, 66000, 4, 64, 100),
     (66, 1, 131073, 1, 64, 33),
+    # parts that are no power of two, whose lists end inside a wave's slots: 36, 17, 42 and 9 of them
+    (1, 7, 400000, 2, 64, 2048),
+    (3, 5, 450000, 2, 64, 2048),
+    (1, 6, 700001, 2, 64, 2048),
+    (2, 14, 300000, 2, 64, 2000),
 ])
 def test_rows_in_parts(ic, oracle, case):
     B, Tq, Lk, H, d, ks = case
