@@ -221,6 +221,9 @@ hipError_t launch_topk_short(const ScoreArgs &a, const SelectArgs &se, int d_I, 
 int select_parts(int n_rows, int max_row_len);
 bool select_parts_fit(int k, int row_len);
 int select_parts_slots(int n_rows, int max_row_len);
+int select_cand_rank(int k, int row_len, int many);
+int select_cand_runs(int many);
+int select_cand_list(int many);
 size_t select_parts_bytes(int n_rows, int max_row_len);
 hipError_t launch_select_parts(const SelectArgs &a, int n_rows, int max_row_len, void *ws, hipStream_t st);
 hipError_t launch_attn(const AttnArgs &a, int d_qk, int d_v, hipStream_t st);

@@ -358,10 +358,10 @@ __global__ __launch_bounds__(NT) void select_kernel(SelectArgs a)
 // For rows much longer than k almost every key is far below the k-th score, and pushing all of them through
 // the digit histograms (LDS atomics into the few dozen bins a row's exponents fall into) is what the generic
 // form spends its time on.  Here the row is read ONCE:
-//   sample    4096 keys in 32 contiguous blocks spread over the row -> a histogram of 4096 linear bins between
+//   sample    4096 keys in 256 short stretches spread over the row -> a histogram of 4096 linear bins between
 //             the smallest and the largest sampled key -> a threshold T0 that about 2k keys of the row should reach
-//   sweep     one pass over the row: every wave appends its keys >= T0 to a candidate list of its own in LDS (no
-//             atomics: a wave scan places the entries), their maximum is tracked
+//   sweep     one pass over the row: the keys >= T0 go to a candidate list in LDS (one atomic per wave and step: a wave
+//             scan places the entries), their maximum is tracked
 //   select    one histogram over the candidates with 4096 LINEAR bins between T0 and that maximum (candidates
 //             spread over all of them), a scan for the bin of the k-th largest, and an exact ranking
 //             (key descending, position ascending) of the few members of that bin
@@ -375,9 +375,25 @@ constexpr int kCandMaxLen = 131072;      // bitmap capacity
 constexpr int kCandSample = 4096;
 constexpr int kBoundaryCap = 1024;       // boundary-bin members ranked exactly
 // A second instance for launches of more rows than CUs: half the threads and half the LDS, so that two rows are in flight per CU
-// (a row's phases are chains of latencies; a second workgroup fills them), and a threshold nearer to the k-th key.  us, before /
-// with it: 257 rows of 41700 keys 34 / 21, 700 59 / 47, 2048 rows of up to 40000 keys 165 / 111, 65536 198 / 165, 131072 286 / 239.
-constexpr int kCandManyCap = 5632;
+// (a row's phases are chains of latencies; a second workgroup fills them), and a threshold nearer to the k-th key.  us, one row per CU /
+// two: 257 rows of 41700 keys 39 / 25, 700 62 / 49, 2048 rows of up to 40000 keys 159 / 110, 65536 199 / 166, 131072 294 / 254; with
+// scores of which half is a component that decays over 64 keys 700 rows of 41700 64 / 46, 2048 of 65536 221 / 157, of 131072 421 / 361
+// (one row that leaves the form is a hundred us at the launch's end), over 256 keys 513 / 251.
+constexpr int kCandManyCap = 6112;
+// Stretches of the sample, 64 bytes each: neighbouring keys score alike, and fewer and longer ones count for less.  Half of the scores'
+// variance in a component that decays over 64 (256) keys, 131072 keys, k = 2048: with 32 stretches of 128 keys 8 (16) per cent of the rows
+// left too few or too many candidates for a list of 6112, with 256 none of 120; lists of 704 for every wave overflowed in another 20.
+constexpr int kCandRuns = 256;
+// Rank in the sample of the threshold that k of nv keys should reach.
+__host__ __device__ inline uint32_t cand_rank(int k, int nv, bool many)
+{
+    uint32_t rank = (uint32_t)(((int64_t)kCandSample * 2 * k) / nv) + 32u;
+    if (many) {                                // k of nv keys are `mean` of the sample, give or take its root or, of neighbours, more
+        const float mean = (float)kCandSample * (float)k / (float)nv;
+        rank = (uint32_t)(mean + 4.5f * __builtin_sqrtf(mean)) + 4u;
+    }
+    return rank > (uint32_t)kCandSample ? (uint32_t)kCandSample : rank;
+}
 constexpr int cand_lds_words(int nt, int maxlen, int cap) { return kBins1 + 2 * (nt / 64) + 4 + 16 + 2 * cap + maxlen / 32; }
 
 // Largest value over the 64 lanes of a wave, in every lane (no LDS traffic; lanes without a source keep their own).
@@ -406,7 +422,7 @@ __global__ __launch_bounds__(NT) void select_cand_kernel(SelectArgs a)
     uint32_t *hist = smem;                     // [kBins1]  (the generic form's layout starts the same way)
     uint32_t *wsum = hist + kBins1;            // [2 NW]
     uint32_t *bc = wsum + 2 * NW;              // [4]
-    uint32_t *misc = bc + 4;                   // [16]: 0 candidate count, 1 largest candidate key, 2 boundary-list count, 3 a list overflowed
+    uint32_t *misc = bc + 4;                   // [16]: 0 candidate count, 1 largest candidate key, 2 boundary-list count
     uint32_t *ckey = misc + 16;                // [CAP]
     uint32_t *cpos = ckey + CAP;               // [CAP]
     uint32_t *bitmap = cpos + CAP;             // [MAXLEN / 32]
@@ -436,7 +452,6 @@ __global__ __launch_bounds__(NT) void select_cand_kernel(SelectArgs a)
     // The row arrives in groups of kGroup vectors per thread, two groups in flight: a single workgroup has to
     // cover the whole memory latency by itself.  The sample and the first group are requested before anything else.
     constexpr int kGroup = 4;
-    constexpr int WCAP = CAP / NW;             // every wave keeps its candidates in a list of its own
     const int nsteps = (nv + 4 * NT - 1) / (4 * NT);
     auto load_group = [&](int c0, f32x4 (&dst)[kGroup]) {
 #pragma unroll
@@ -450,13 +465,14 @@ __global__ __launch_bounds__(NT) void select_cand_kernel(SelectArgs a)
     f32x4 sv[SV];
 #pragma unroll
     for (int u = 0; u < SV; ++u) {
-        const int blk = (tid >> 5) + (NT / 32) * u;
-        const int p = (int)(((int64_t)blk * nv / 32) & ~(int64_t)3) + (tid & 31) * 4;   // p + 3 < nv: blocks are nv / 32 >= 256 apart
+        constexpr int kLanes = kCandSample / kCandRuns / 4;    // to a stretch
+        static_assert(kCandMinLen / kCandRuns >= 4 * kLanes && (int64_t)kCandRuns * MAXLEN <= INT32_MAX, "p + 3 < nv");
+        const int p = ((u * NT + tid) / kLanes * nv / kCandRuns & ~(4 * kLanes - 1)) + tid % kLanes * 4;
         sv[u] = *(const f32x4 *)(row + p);
     }
     load_group(0, ga);
 
-    // ---- sample: 32 blocks of 128 keys, a histogram of 4096 linear bins between the smallest and the largest of
+    // ---- sample: a histogram of 4096 linear bins between the smallest and the largest of
     //      them (the scores of a row share a few exponents: bins of a key digit would be hit a hundred times each,
     //      and LDS atomics on one address take turns) ----
     for (int e = tid; e < kBins1; e += NT) hist[e] = 0;
@@ -488,23 +504,15 @@ __global__ __launch_bounds__(NT) void select_cand_kernel(SelectArgs a)
 #pragma unroll
     for (int e = 0; e < 4 * SV; ++e) atomicAdd(&hist[(skey[e] - smin) >> ssh], 1u);
     __syncthreads();
-    uint32_t want = (uint32_t)(((int64_t)kCandSample * 2 * k) / nv) + 32u;
-    if (MANY) {                                // k of nv keys are `mean` of the sample, give or take its root
-        const float mean = (float)kCandSample * (float)k / (float)nv;
-        want = (uint32_t)(mean + 4.f * __builtin_sqrtf(mean)) + 16u;
-    }
-    want = want > (uint32_t)kCandSample ? (uint32_t)kCandSample : want;
-    find_digit<NT, kBins1 / NT>(hist, want, wsum, bc, tid, lane, wave);
+    find_digit<NT, kBins1 / NT>(hist, cand_rank(a.k_sel, nv, MANY), wsum, bc, tid, lane, wave);
     const uint32_t T0 = smin + (bc[0] << ssh); // a bin's lower edge: at least `want` sampled keys reach it
     __syncthreads();
 
-    // ---- sweep: the row once, the positions of the candidates to the wave's list ----
+    // ---- sweep: the row once, the positions of the candidates to the list ----
     // The sweep is bound by vector-ALU instructions (sixteen keys per thread and group), so it does the least per
     // key: one float comparison against the threshold (the key order is the float order) into a bit mask; only the
     // set bits are visited afterwards, and only positions are stored -- the few candidates' keys are read back
     // from the row (still in L2) once the sweep is over.
-    uint32_t my_cnt = 0;                       // entries in this wave's list (uniform)
-    uint32_t *wkey = ckey + wave * WCAP, *wpos = cpos + wave * WCAP;
     // (rows of up to 65536 keys: a workgroup's row is still in L2 when its candidates are read back; longer rows of
     // a full grid push one another out, there the keys are stored during the sweep)
     const bool reread = nv <= 65536;           // workgroup-uniform
@@ -522,13 +530,14 @@ __global__ __launch_bounds__(NT) void select_cand_kernel(SelectArgs a)
             const uint32_t incl = wave_incl_scan(n_t);
             const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
             if (total == 0u) return;               // wave-uniform
-            uint32_t off = my_cnt + incl - n_t;
-            my_cnt += total;
+            uint32_t at = 0;
+            if (lane == 0) at = atomicAdd(&misc[0], total);
+            uint32_t off = (uint32_t)__builtin_amdgcn_readfirstlane((int)at) + incl - n_t;
             if (reread) {
                 while (m) {
                     const int bit = __builtin_ctz(m);
                     m &= m - 1u;
-                    if (off < (uint32_t)WCAP) wpos[off] = (uint32_t)(((c0 + (bit >> 2)) * NT + tid) * 4 + (bit & 3));
+                    if (off < (uint32_t)CAP) cpos[off] = (uint32_t)(((c0 + (bit >> 2)) * NT + tid) * 4 + (bit & 3));
                     ++off;
                 }
             } else {
@@ -537,9 +546,9 @@ __global__ __launch_bounds__(NT) void select_cand_kernel(SelectArgs a)
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
                         if ((m >> (4 * j + e)) & 1u) {
-                            if (off < (uint32_t)WCAP) {
-                                wpos[off] = (uint32_t)(((c0 + j) * NT + tid) * 4 + e);
-                                wkey[off] = max(score_key(v[j][e]), T0);
+                            if (off < (uint32_t)CAP) {
+                                cpos[off] = (uint32_t)(((c0 + j) * NT + tid) * 4 + e);
+                                ckey[off] = max(score_key(v[j][e]), T0);
                             }
                             ++off;
                         }
@@ -553,27 +562,23 @@ __global__ __launch_bounds__(NT) void select_cand_kernel(SelectArgs a)
             if (c0 + 2 * kGroup < nsteps) load_group(c0 + 2 * kGroup, ga);
             sweep_group(c0 + kGroup, gb);
         }
-        if (lane == 0) {
-            atomicAdd(&misc[0], my_cnt);
-            if (my_cnt > (uint32_t)WCAP) misc[3] = 1u;     // this wave's list overflowed
-        }
     }
     __syncthreads();
     const uint32_t n_cand = misc[0];
-    if (n_cand < k || misc[3] != 0u) {             // workgroup-uniform
+    if (n_cand < k || n_cand > (uint32_t)CAP) {    // workgroup-uniform
         __syncthreads();
         return false;
     }
     // the candidates' keys and their maximum
     {
         uint32_t tmax = 0;
-        for (uint32_t j = lane; j < my_cnt; j += 64) {
+        for (uint32_t j = tid; j < n_cand; j += NT) {
             uint32_t key;
             if (reread) {
-                key = max(score_key(row[wpos[j]]), T0);   // (>= T0 by construction; the bins below rely on it)
-                wkey[j] = key;
+                key = max(score_key(row[cpos[j]]), T0);   // (>= T0 by construction; the bins below rely on it)
+                ckey[j] = key;                 // (read again by this thread only)
             } else {
-                key = wkey[j];
+                key = ckey[j];
             }
             tmax = max(tmax, key);
         }
@@ -588,7 +593,7 @@ __global__ __launch_bounds__(NT) void select_cand_kernel(SelectArgs a)
     const uint32_t range = kmax - T0;
     const int nbits = range ? 32 - __clz((int)range) : 0;
     const int sh = nbits > 12 ? nbits - 12 : 0;
-    for (uint32_t j = lane; j < my_cnt; j += 64) atomicAdd(&hist[(wkey[j] - T0) >> sh], 1u);
+    for (uint32_t j = tid; j < n_cand; j += NT) atomicAdd(&hist[(ckey[j] - T0) >> sh], 1u);
     __syncthreads();
     find_digit<NT, kBins1 / NT>(hist, k, wsum, bc, tid, lane, wave);
     const uint32_t bstar = bc[0], need = bc[1], n_b = bc[2];
@@ -598,14 +603,14 @@ __global__ __launch_bounds__(NT) void select_cand_kernel(SelectArgs a)
 
     // ---- mark the selected positions ----
     uint32_t *bl_key = wpre, *bl_pos = wpre + kBoundaryCap;
-    for (uint32_t j = lane; j < my_cnt; j += 64) {
-        const uint32_t bin = (wkey[j] - T0) >> sh;
+    for (uint32_t j = tid; j < n_cand; j += NT) {
+        const uint32_t bin = (ckey[j] - T0) >> sh;
         if (bin > bstar || (bin == bstar && !ranked)) {
-            atomicOr(&bitmap[wpos[j] >> 5], 1u << (wpos[j] & 31u));
+            atomicOr(&bitmap[cpos[j] >> 5], 1u << (cpos[j] & 31u));
         } else if (bin == bstar) {
             const uint32_t s = atomicAdd(&misc[2], 1u);
-            bl_key[s] = wkey[j];
-            bl_pos[s] = wpos[j];
+            bl_key[s] = ckey[j];
+            bl_pos[s] = cpos[j];
         }
     }
     __syncthreads();
@@ -642,13 +647,13 @@ __global__ __launch_bounds__(NT) void select_cand_kernel(SelectArgs a)
         }
     }
     __syncthreads();
-    for (uint32_t j = lane; j < my_cnt; j += 64) {
-        const uint32_t pos = wpos[j], word = bitmap[pos >> 5], bit = pos & 31u;
+    for (uint32_t j = tid; j < n_cand; j += NT) {
+        const uint32_t pos = cpos[j], word = bitmap[pos >> 5], bit = pos & 31u;
         if ((word >> bit) & 1u) {
             const uint32_t slot = wpre[pos >> 5] + (uint32_t)__popc(word & ((1u << bit) - 1u));
             if (slot < k) {                    // always true for a consistent select
                 oidx[slot] = (int32_t)pos;
-                if (osel) osel[slot] = key_score(wkey[j]);
+                if (osel) osel[slot] = key_score(ckey[j]);
             }
         }
     }
@@ -1214,9 +1219,7 @@ __global__ __launch_bounds__(kPartThreads) void select_part_kernel(SelectArgs a,
 #pragma unroll
     for (int e = 0; e < 4; ++e) atomicAdd(&hist[(skey[e] - smin) >> ssh], 1u);
     __syncthreads();
-    uint32_t want = (uint32_t)(((int64_t)kCandSample * 2 * a.k_sel) / nv) + 32u;
-    want = want > (uint32_t)kCandSample ? (uint32_t)kCandSample : want;
-    find_digit<NT, kBins1 / NT>(hist, want, wsum, bc, tid, lane, wave);
+    find_digit<NT, kBins1 / NT>(hist, cand_rank(a.k_sel, nv, false), wsum, bc, tid, lane, wave);
     const uint32_t T0 = smin + (bc[0] << ssh);
     const float T0f = key_score(T0);
 
@@ -1467,6 +1470,11 @@ int select_parts_slots(int n_rows, int max_row_len)
     const int p = select_parts(n_rows, max_row_len);
     return p == 0 ? 0 : part_slots(p);
 }
+
+// The candidate forms' sample (rank of the threshold in it, stretches) and the entries of their list, for launches of few or of many rows.
+int select_cand_rank(int k, int row_len, int many) { return (int)cand_rank(k, row_len, many != 0); }
+int select_cand_runs(int many) { return kCandRuns; }
+int select_cand_list(int many) { return many ? kCandManyCap : kCandCap; }
 
 size_t select_parts_bytes(int n_rows, int max_row_len)
 {

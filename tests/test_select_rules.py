@@ -4,6 +4,7 @@ import ctypes
 
 import numpy as np
 import pytest
+from scipy.signal import lfilter
 
 import paper_2603_12201_amd as m
 
@@ -16,8 +17,9 @@ def rule(name, *args):
 
 
 def keys_of(x):
-    """Order-preserving keys of positive scores."""
-    return x.view(np.uint32).astype(np.int64) + 0x80000000
+    """Order-preserving keys of scores."""
+    u = (x + np.float32(0)).view(np.uint32)
+    return np.where(u >> 31, ~u, u | 0x80000000).astype(np.int64)
 
 
 def threshold(keys, runs, want):
@@ -53,3 +55,23 @@ def test_parts_decide_rows_of_independent_scores(rows, keys):
         cand = np.nonzero(x >= threshold(x, 32, 4096 * 2 * k // keys + 32))[0]
         assert len(cand) >= k
         assert np.bincount(cand // 32 % parts, minlength=parts).max() <= slots     # a part has every parts-th block of 32 keys
+
+
+@pytest.mark.parametrize("keys, memory", [(41700, 0), (131072, 0), (41700, 64), (65536, 64), (131072, 64), (131072, 256), (131072, 1024)])
+@pytest.mark.parametrize("mean", [5, 0])
+def test_candidate_form_decides_rows_of_correlated_scores(keys, memory, mean):
+    """Half of the variance in a component that decays over `memory` keys (neighbours score alike), all scores positive or around zero:
+    at most 2 of 100 rows of a launch of more rows than CUs leave fewer than k candidates or more than the list holds."""
+    k, many, rows, missed = 2048, 1, 100, 0
+    rng = np.random.default_rng(keys + memory)
+    rank, runs, room = rule("select_cand_rank", k, keys, many), rule("select_cand_runs", many), rule("select_cand_list", many)
+    for _ in range(rows):
+        x = rng.standard_normal(keys, dtype=np.float32)
+        if memory:
+            a = np.exp(-1 / memory)
+            slow = lfilter([np.sqrt(1 - a * a)], [1, -a], rng.standard_normal(keys, dtype=np.float32))
+            x = (np.sqrt(0.5) * (x + slow)).astype(np.float32)
+        x = keys_of(x + np.float32(mean))
+        n = int((x >= threshold(x, runs, rank)).sum())
+        missed += n < k or n > room
+    assert missed <= 2, missed
