@@ -221,6 +221,7 @@ hipError_t launch_topk_short(const ScoreArgs &a, const SelectArgs &se, int d_I, 
 int select_parts(int n_rows, int max_row_len);
 bool select_parts_fit(int k, int row_len);
 int select_parts_slots(int n_rows, int max_row_len);
+int select_parts_cache(int ragged);
 int select_cand_rank(int k, int row_len, int many);
 int select_cand_runs(int many);
 int select_cand_list(int many);

@@ -57,6 +57,11 @@ def test_parts_decide_rows_of_independent_scores(rows, keys):
         assert np.bincount(cand // 32 % parts, minlength=parts).max() <= slots     # a part has every parts-th block of 32 keys
 
 
+def test_short_rows_of_a_ragged_launch_in_parts_are_read_once():
+    """Sequences too short for the sample (less than 8192 keys, or 4 k) beside long ones keep their keys in LDS for the radix select's sweeps."""
+    assert rule("select_parts_cache", 1) >= max(8192, 4 * 2048)
+
+
 @pytest.mark.parametrize("keys, memory", [(41700, 0), (131072, 0), (41700, 64), (65536, 64), (131072, 64), (131072, 256), (131072, 1024)])
 @pytest.mark.parametrize("mean", [5, 0])
 def test_candidate_form_decides_rows_of_correlated_scores(keys, memory, mean):
