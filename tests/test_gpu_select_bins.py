@@ -112,6 +112,30 @@ def test_scores_and_selection_in_one_launch(ic, oracle, B, T, L, H, d, p0, ks):
         check(ic, oracle, q, k, w, ks, p0)
 
 
+@pytest.mark.parametrize("B, T, L, H, d, two", [
+    (1, 1, 1024, 4, 64, 1), (1, 1, 513, 4, 64, 1), (1, 1, 512, 4, 64, 0), (64, 1, 1024, 4, 64, 1), (96, 1, 1024, 4, 64, 0),
+    (4, 4, 512, 32, 64, 1), (4, 4, 256, 32, 64, 0), (1, 16, 1024, 32, 64, 1), (1, 16, 768, 32, 64, 0),
+    (1, 1, 512, 4, 128, 1), (1, 1, 256, 4, 128, 0), (1, 1, 129, 32, 128, 1), (1, 1, 128, 32, 128, 0), (1, 8, 512, 32, 128, 0),
+])
+def test_few_rows_take_the_launches_that_are_faster(ic, oracle, B, T, L, H, d, two):
+    """Scores and selection of few rows in one launch up to the length where a workgroup per row takes as long as two launches."""
+    print("[case] few rows B=%d T=%d L=%d H=%d d=%d" % (B, T, L, H, d), flush=True)
+    g = torch.Generator().manual_seed(B + T + L)
+    q = (torch.randn((B, T, H, d), generator=g) / d ** 0.5).to(torch.bfloat16).cuda()
+    k = torch.randn((B, L, d), generator=g).to(torch.bfloat16).cuda()
+    w = torch.randn((B, T, H), generator=g).cuda()
+    ic.prof_reset()
+    ic.prof_enable(True)
+    ic.indexer_topk(q, k, w, 64, L - T)
+    torch.cuda.synchronize()
+    ic.prof_collect()
+    launches = ic.prof_get(0)[0], ic.prof_get(1)[0]
+    ic.prof_enable(False)
+    ic.prof_reset()
+    assert launches == (1, two)
+    check(ic, oracle, q[:2], k[:2], w[:2], 64, L - T)
+
+
 @pytest.mark.parametrize("L, ks", [(32900, 2048), (60001, 100), (131072, 2048)])
 def test_more_long_rows_than_workgroups(ic, oracle, L, ks):
     """The candidate form with two rows per CU: rows at random, of one value, and with their best scores together."""
