@@ -1558,16 +1558,15 @@ hipError_t launch_select(const SelectArgs &a_in, int n_rows, int max_row_len, hi
 // sequence: the streaming forms of the scores, which spread the keys over the chip) or 10 (more), while here a workgroup goes
 // through a row's keys one subtile after another.  One row, 4 heads of 64: 512 keys 7.6 / 7.4, 768 8.2 / 8.7, 1024 7.9 / 9.9; 32 heads:
 // 256 7.4 / 7.1, 512 7.5 / 8.1, 1024 8.1 / 10.5; 4 heads of 128: 256 8.1 / 7.6, 320 8.0 / 8.4; 32 heads: 128 8.4 / 8.3, 256 8.2 / 8.7,
-// 512 8.2 / 10.7; 64 rows nearly the same, 96 at 1024 keys even.  16 rows of one sequence, 32 heads of 64: 768 10.3 / 9.7, 1024 10.2 / 10.9.
+// 512 8.2 / 10.7; 64 rows of 512 keys, 32 heads 8.2 / 8.8.  Past 128 keys for each CU the streaming forms take a second round: 64 rows, 4
+// heads of 64: 640 9.6 / 8.9, 768 9.6 / 9.2, 1024 9.4 / 10.4, 96 even.  16 rows of one sequence, 32 heads of 64: 768 10.3 / 9.7, 1024 10.2 / 10.9.
 bool topk_short(const ScoreArgs &a, int dtype, int d_I, int n_rows, int64_t max_vis)
 {
     if (dtype != IC_BF16 || a.H_I > 32 || a.pv.seq_lens || a.pv.page_table) return false;
     if (d_I != 64 && d_I != 128) return false;
     int64_t most = d_I == 64 ? kShortLen : kShortLen / 2;
-    if (n_rows < 96) {
-        if (a.Ri <= 4) most = (a.H_I > 8 ? most / 4 : most / 2);
-        else if (d_I == 64) most = most * 3 / 4;
-    }
+    if (n_rows < 96 && a.Ri <= 4 && n_rows * max_vis <= 256 * 128) most = a.H_I > 8 ? most / 4 : most / 2;
+    else if (n_rows < 96 && d_I == 64) most = most * 3 / 4;
     return max_vis <= most && n_rows * max_vis <= (d_I == 64 ? 1 << 20 : 1 << 18);
 }
 

@@ -113,7 +113,7 @@ def test_scores_and_selection_in_one_launch(ic, oracle, B, T, L, H, d, p0, ks):
 
 
 @pytest.mark.parametrize("B, T, L, H, d, two", [
-    (1, 1, 1024, 4, 64, 1), (1, 1, 513, 4, 64, 1), (1, 1, 512, 4, 64, 0), (64, 1, 1024, 4, 64, 1), (96, 1, 1024, 4, 64, 0),
+    (1, 1, 1024, 4, 64, 1), (1, 1, 513, 4, 64, 1), (1, 1, 512, 4, 64, 0), (64, 1, 1024, 4, 64, 1), (64, 1, 768, 4, 64, 0), (96, 1, 1024, 4, 64, 0),
     (4, 4, 512, 32, 64, 1), (4, 4, 256, 32, 64, 0), (1, 16, 1024, 32, 64, 1), (1, 16, 768, 32, 64, 0),
     (1, 1, 512, 4, 128, 1), (1, 1, 256, 4, 128, 0), (1, 1, 129, 32, 128, 1), (1, 1, 128, 32, 128, 0), (1, 8, 512, 32, 128, 0),
 ])
