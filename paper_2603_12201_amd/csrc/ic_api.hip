@@ -677,19 +677,6 @@ ic_status run_lead_rest(const LeadJob *jobs, int n_jobs, float *lse, void *ws, s
     return IC_OK;
 }
 
-// Launches of consecutive jobs of one shape, at most `most` together.
-template <typename F> ic_status lead_groups(const std::vector<LeadJob> &jobs, int most, F run)
-{
-    for (size_t i = 0; i < jobs.size();) {
-        size_t n = 1;
-        while (i + n < jobs.size() && n < (size_t)most && memcmp(&jobs[i].L.at, &jobs[i + n].L.at, sizeof jobs[i].L.at) == 0) ++n;
-        const ic_status s = run(i, (int)n);
-        if (s != IC_OK) return s;
-        i += n;
-    }
-    return IC_OK;
-}
-
 // c: idx is this library's own (rows that can hold fewer than k_sel entries end in -1s, and the kernels leave their empty
 // tiles out) or the caller's (kUnknown)
 ic_status run_attn_layers(const ic_layer *layers, int n_layers, const int32_t *idx, float *lse, void *ws, size_t ws_bytes,
@@ -1118,7 +1105,8 @@ bool sim_apart(const ic_layer *layers, int n_layers)
 
 // The layers whose leading rows are counted: outputs under their own indices, and for every pair those under reused ones.  Rows
 // that are whole prefixes in both index tensors of a pair select the same keys in the same order, so their outputs are the
-// layer's own and nothing is left to compute.  Layers that are not apart are finished one after the other.
+// layer's own and nothing is left to compute.  Layers that are not apart are finished one after the other.  (No containers: an
+// allocation that fails would throw through the C entry.)
 ic_status run_similarity(const ic_layer *layers, int n_layers, const int32_t *const *idx, double *S, int32_t *lead, double *self,   // (self: or nullptr)
                          char *o_reuse, int n_out, void *ws, size_t ws_bytes, hipStream_t st)
 {
@@ -1133,52 +1121,49 @@ ic_status run_similarity(const ic_layer *layers, int n_layers, const int32_t *co
     c0.n_chunks = n_chunks;
     c0.Tq = d->Tq;
     const int step = sim_apart(layers, n_layers) ? n_layers : 1;
-    std::vector<LeadJob> jobs;
-    std::vector<std::pair<int, int>> pairs;
+    LeadJob jobs[ic::kMaxBatchLayers];         // of one shape, collected until a launch is full
+    auto ends = [&](int i, int next) { return next >= n_layers || memcmp(&layers[i].at, &layers[next].at, sizeof layers[i].at) != 0; };
     for (int first = 0; first < n_layers; first += step) {
-        jobs.clear();
-        for (int i = first; i < first + step; ++i) jobs.push_back(LeadJob{layers[i], idx[i], counts(i), counts(i)});
-        ic_status s = lead_groups(jobs, ic::kMaxBatchLayers, [&](size_t at, int n) {
-            ic_status r = run_lead_dense(&jobs[at], n, nullptr, st);
-            if (r == IC_OK) r = run_lead_rest(&jobs[at], n, nullptr, ws, ws_bytes, st);
-            if (r != IC_OK || !self) return r;
-            ic::CosineArgs c = c0;
-            c.self_out = 1;
-            for (int i = 0; i < n; ++i) {
-                const int l = first + (int)at + i;
-                c.A[i] = c.B[i] = (const unsigned short *)layers[l].O;
-                c.lead[i] = c.lead2[i] = counts(l);
-                c.self[i] = self + l * n_rows;
-            }
-            const hipError_t e = ic::launch_cosines(c, n, st);
-            return e == hipSuccess ? IC_OK : fail(IC_ERR_HIP, "cosine launch failed: %s", hipGetErrorString(e));
-        });
-        if (s != IC_OK) return s;
-        jobs.clear();
-        pairs.clear();
-        for (int i = first; i < first + step; ++i)
-            for (int j = 0; j < i; ++j) {
-                jobs.push_back(LeadJob{layers[i], idx[j], counts(j), counts(i)});
-                pairs.push_back({i, j});
-            }
-        s = lead_groups(jobs, n_out, [&](size_t at, int n) {
-            for (int p = 0; p < n; ++p) jobs[at + p].L.O = o_reuse + p * sim_o_bytes(d);
-            const ic_status r = run_lead_rest(&jobs[at], n, nullptr, ws, ws_bytes, st);
+        const int end = first + step;
+        int n = 0;
+        for (int i = first; i < end; ++i) {
+            jobs[n++] = LeadJob{layers[i], idx[i], counts(i), counts(i)};
+            if (n < ic::kMaxBatchLayers && i + 1 < end && !ends(i, i + 1)) continue;
+            ic_status r = run_lead_dense(jobs, n, nullptr, st);
+            if (r == IC_OK) r = run_lead_rest(jobs, n, nullptr, ws, ws_bytes, st);
             if (r != IC_OK) return r;
-            ic::CosineArgs c = c0;
-            for (int p = 0; p < n; ++p) {
-                const int i = pairs[at + p].first, j = pairs[at + p].second;
-                c.A[p] = (const unsigned short *)layers[i].O;
-                c.B[p] = (const unsigned short *)jobs[at + p].L.O;
-                c.acc[p] = S + (size_t)i * n_layers + j;
-                c.lead[p] = counts(j);
-                c.lead2[p] = counts(i);
-                c.self[p] = self ? self + i * n_rows : nullptr;
+            if (self) {
+                ic::CosineArgs c = c0;
+                c.self_out = 1;
+                for (int p = 0; p < n; ++p) {
+                    const int l = i + 1 - n + p;
+                    c.A[p] = c.B[p] = (const unsigned short *)layers[l].O;
+                    c.lead[p] = c.lead2[p] = counts(l);
+                    c.self[p] = self + l * n_rows;
+                }
+                const hipError_t e = ic::launch_cosines(c, n, st);
+                if (e != hipSuccess) return fail(IC_ERR_HIP, "cosine launch failed: %s", hipGetErrorString(e));
             }
-            const hipError_t e = ic::launch_cosines(c, n, st);
-            return e == hipSuccess ? IC_OK : fail(IC_ERR_HIP, "cosine launch failed: %s", hipGetErrorString(e));
-        });
-        if (s != IC_OK) return s;
+            n = 0;
+        }
+        ic::CosineArgs c = c0;
+        for (int i = first; i < end; ++i)
+            for (int j = 0; j < i; ++j) {      // layer i as a Shared one reading j
+                c.A[n] = (const unsigned short *)layers[i].O;
+                c.B[n] = (const unsigned short *)(o_reuse + n * sim_o_bytes(d));
+                c.acc[n] = S + (size_t)i * n_layers + j;
+                c.lead[n] = counts(j);
+                c.lead2[n] = counts(i);
+                c.self[n] = self ? self + i * n_rows : nullptr;
+                jobs[n] = LeadJob{layers[i], idx[j], counts(j), counts(i)};
+                jobs[n].L.O = o_reuse + n * sim_o_bytes(d);
+                if (++n < n_out && (j + 1 < i || (i + 1 < end && !ends(i, i + 1)))) continue;
+                const ic_status r = run_lead_rest(jobs, n, nullptr, ws, ws_bytes, st);
+                if (r != IC_OK) return r;
+                const hipError_t e = ic::launch_cosines(c, n, st);
+                if (e != hipSuccess) return fail(IC_ERR_HIP, "cosine launch failed: %s", hipGetErrorString(e));
+                n = 0;
+            }
     }
     return IC_OK;
 }
