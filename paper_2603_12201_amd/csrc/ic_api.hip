@@ -950,10 +950,10 @@ static ic_status forward_stack_impl(const ic_layer *layers, int32_t n_layers, co
         while (l + run < n_layers && !full_mask[l + run]) ++run;
         int m = attn_batch(L, run, pc);
         while (m > 1 && attn_best_bytes(&L->at, m) > workspace_bytes) --m;
-        bool whole = true;                     // outputs that the dense form can store
-        for (int i = 0; i < m; ++i) whole = whole && dense_output(L[i].O);
-        const int nd = whole ? dense_queries(&L->at, m, known, workspace_bytes) : 0;
-        if (nd) m = std::min(m, dense_batch(&L->at, nd));
+        int stored = 0;                        // the first of them, whose outputs the dense form can store
+        while (stored < m && dense_output(L[stored].O)) ++stored;
+        const int nd = stored ? dense_queries(&L->at, stored, known, workspace_bytes) : 0;
+        if (nd) m = std::min(stored, dense_batch(&L->at, nd));
         s = nd ? run_attn_dense(L, m, nd, idx_cache, workspace, workspace_bytes, st, pc, known)
                : run_attn_layers(L, m, idx_cache, nullptr, workspace, workspace_bytes, st, pc, known);
         if (s != IC_OK) return s;

@@ -291,3 +291,30 @@ def test_dense_rows_of_several_layers(B, Tq, pos0, k, n, page):
         assert torch.isfinite(out.float()).all()
         # two roundings of the same value to bf16 (of outputs below 4: at most 2^-7 apart, twice)
         assert (out.float() - alone.float()).abs().max() <= 2 ** -6
+
+
+def test_layers_in_front_of_one_whose_output_is_at_an_odd_address():
+    """The dense form stores 16 bytes at a time: a layer whose output it cannot store takes the row form, those in front of it do not."""
+    import paper_2603_12201_amd as ic
+    print("[case] dense layers, the third output at an odd address", flush=True)
+    B, Tq, H, k, n = 1, 700, 32, 2048, 4
+    g = torch.Generator(device="cuda").manual_seed(3)
+    rnd = lambda *s: torch.randn(s, generator=g, device="cuda", dtype=torch.bfloat16)
+    layers = [{"Q": rnd(B, Tq, H, 576), "KV": rnd(B, Tq, 576)} for _ in range(n)]
+    ixr = {"q": rnd(B, Tq, 4, 64), "k": rnd(B, Tq, 64), "w": torch.rand((B, Tq, 4), generator=g, device="cuda")}
+    for t in layers:
+        t.update(ixr)
+    size = B * Tq * H * 512
+
+    def run(odd):
+        bufs = [torch.full((size + 8,), 7.0, dtype=torch.bfloat16, device="cuda") for _ in range(n)]
+        outs = [b[1 if l == odd else 0:][:size].view(B, Tq, H, 512) for l, b in enumerate(bufs)]
+        arr = ic.make_layers(layers, k, 0, 512, 0, 1 / 24.0, outs)
+        ws = torch.empty(max(ic.forward_stack_workspace(arr), 256), dtype=torch.uint8, device="cuda")
+        ic.forward_stack(arr, [True] + [False] * (n - 1), torch.empty((B, Tq, k), dtype=torch.int32, device="cuda"), ws)
+        return outs
+    even, odd = run(None), run(2)
+    for l in range(2):                            # the same form: bit for bit the same
+        assert torch.equal(even[l].view(torch.int16), odd[l].view(torch.int16)), l
+    for l in range(2, n):                         # the row form, for the layer behind it as well: two roundings to bf16
+        assert ((even[l].float() - odd[l].float()).norm() / even[l].float().norm()).item() < 4e-3
