@@ -1114,6 +1114,9 @@ ic_status run_similarity(const ic_layer *layers, int n_layers, const int32_t *co
     const int64_t n_rows = (int64_t)d->B * d->Tq;
     const int n_chunks = lead_chunks(lead_queries(d));
     auto counts = [&](int l) { return lead + (int64_t)l * d->B * n_chunks; };
+    // (of layers that more than one comparison asks: two layers of two sequences of 2500 rows took 1186 us with both layers' worked
+    // out first, 1120 without)
+    auto self_of = [&](int l) -> double * { return self && l >= 2 ? self + l * n_rows : nullptr; };
     ic::CosineArgs c0;
     memset(&c0, 0, sizeof c0);
     c0.n_rows = n_rows;
@@ -1132,16 +1135,17 @@ ic_status run_similarity(const ic_layer *layers, int n_layers, const int32_t *co
             ic_status r = run_lead_dense(jobs, n, nullptr, st);
             if (r == IC_OK) r = run_lead_rest(jobs, n, nullptr, ws, ws_bytes, st);
             if (r != IC_OK) return r;
-            if (self) {
-                ic::CosineArgs c = c0;
-                c.self_out = 1;
-                for (int p = 0; p < n; ++p) {
-                    const int l = i + 1 - n + p;
-                    c.A[p] = c.B[p] = (const unsigned short *)layers[l].O;
-                    c.lead[p] = c.lead2[p] = counts(l);
-                    c.self[p] = self + l * n_rows;
+            ic::CosineArgs c = c0;
+            c.self_out = 1;
+            int m = 0;
+            for (int l = i + 1 - n; l <= i; ++l)
+                if (self_of(l)) {
+                    c.A[m] = c.B[m] = (const unsigned short *)layers[l].O;
+                    c.lead[m] = c.lead2[m] = counts(l);
+                    c.self[m++] = self_of(l);
                 }
-                const hipError_t e = ic::launch_cosines(c, n, st);
+            if (m) {
+                const hipError_t e = ic::launch_cosines(c, m, st);
                 if (e != hipSuccess) return fail(IC_ERR_HIP, "cosine launch failed: %s", hipGetErrorString(e));
             }
             n = 0;
@@ -1154,7 +1158,7 @@ ic_status run_similarity(const ic_layer *layers, int n_layers, const int32_t *co
                 c.acc[n] = S + (size_t)i * n_layers + j;
                 c.lead[n] = counts(j);
                 c.lead2[n] = counts(i);
-                c.self[n] = self ? self + i * n_rows : nullptr;
+                c.self[n] = self_of(i);
                 jobs[n] = LeadJob{layers[i], idx[j], counts(j), counts(i)};
                 jobs[n].L.O = o_reuse + n * sim_o_bytes(d);
                 if (++n < n_out && (j + 1 < i || (i + 1 < end && !ends(i, i + 1)))) continue;
