@@ -879,11 +879,19 @@ __device__ __forceinline__ void bins_select(const float *row, int nv, int k, int
     if (!odd && scale > 0.f && scale < 3e38f) {                // (one value only, or a range beyond floats: no bins)
         // (monotone, NB - 1 at most)
         auto bin = [](float x, float from, float by) { return (uint32_t)((x - from) * by); };
-        if (tid == 0) atomicSub(&hist[bin(f0, first, scale)], pad);
-        each([&](uint32_t x, int) { atomicAdd(&hist[bin(__uint_as_float(x), first, scale)], 1u); });
+        // The lowest bin is what the others leave: a ReLU's zeros, or all of a row but its largest scores, would take turns there
+        // (one head of 30000 keys, half of them zero: 32.7 us with all keys counted, 21.8 without; 2048 rows of 32768 388 / 306).
+        if (tid == 0) {
+            if (bin(f0, first, scale)) atomicSub(&hist[bin(f0, first, scale)], pad);
+            hist[0] = (uint32_t)nv;            // (for the scan, which ends here at the latest)
+        }
+        each([&](uint32_t x, int) {
+            const uint32_t at = bin(__uint_as_float(x), first, scale);
+            if (at) atomicAdd(&hist[at], 1u);
+        });
         sync();
         find_digit<NT, NB / NT>(hist, need, wsum, bc, tid, lane, wave, sync);
-        const uint32_t b = bc[0], n_b = bc[2];
+        const uint32_t b = bc[0], n_b = b ? bc[2] : (uint32_t)(nv - k) + bc[1];
         need = bc[1];
         float from = first;                    // (opaque: bins are worked out again)
         asm volatile("" : "+v"(from));

@@ -79,6 +79,19 @@ def test_score_shapes(ic, oracle, L, kind):
         check(ic, oracle, q, k, w, ks, L - 2)
 
 
+@pytest.mark.parametrize("L, ks", [(40, 39), (700, 699), (700, 640), (1030, 1000), (2050, 2048), (2100, 2048)])
+@pytest.mark.parametrize("kind", ["rising", "zeros", "low", "first"])
+def test_last_key_wanted_lies_in_the_lowest_bin(ic, oracle, L, ks, kind):
+    """That bin's members are not counted: few of them, many, as many as are ranked, and slots behind the row that lie in it or do not."""
+    print("[case] bins, %s, L=%d k=%d" % (kind, L, ks), flush=True)
+    x = torch.arange(L, dtype=torch.float32)
+    r = torch.rand(L, generator=torch.Generator().manual_seed(L))
+    v = {"rising": 1 + x / 64, "zeros": (r - 0.5).clamp(min=0), "low": 1 + r + 1e4 * (x % 7 == 3), "first": 1 + r + 1e4 * (x == 0)}[kind]
+    q = torch.zeros((1, 2, 1, 64)); q[..., 5] = q[..., 6] = 1.0
+    k = torch.zeros((1, L, 64)); k[0, :, 5] = v.to(torch.bfloat16).float(); k[0, :, 6] = v - k[0, :, 5]
+    check(ic, oracle, q.to(torch.bfloat16).cuda(), k.to(torch.bfloat16).cuda(), torch.ones((1, 2, 1)).cuda(), ks, L - 2)
+
+
 @pytest.mark.parametrize("L", [5, 511, 1024, 1025])
 @pytest.mark.parametrize("ks", [3, 200])
 def test_lengths_of_two_head_tiles(ic, oracle, L, ks):
