@@ -465,9 +465,9 @@ ic_attn_desc rows_behind(const ic_attn_desc *d, int n)
     return t;
 }
 
-// Layers whose dense rows share a launch: up to four rounds of blocks a layer, from where on a launch's start and end count less
-// than what is lost where two layers' keys take turns in L2.  Four layers, together / a launch each: 256 rows 26.0 / 40.6 us, 512
-// 53 / 85, 1024 155 / 172, 2048 530 / 540, 4 x 256 79 / 101, 16 x 32 32.4 / 37.8, 3 x 1021 498 / 484.
+// Layers whose dense rows share a launch: up to four rounds of blocks a layer, from where on a launch's start and end count
+// nothing.  Four layers, together / a launch each, us a call: 256 rows 30 / 47, 512 62 / 101, 1000 169 / 196, 1024 173 / 200, 2048
+// 575 / 580, 4 x 256 88 / 112, 16 x 32 36 / 43, 3 x 1021 514 / 520, 2 x 2048 1104 / 1105.
 int dense_batch(const ic_attn_desc *d, int n) { return ((int64_t)n * d->H_q + 63) / 64 * d->B <= 4 * 256 ? ic::kMaxBatchLayers : 1; }
 
 // How many of them it takes, for n_layers layers that the row forms would take together.  The rows behind (ws_bytes:

@@ -831,6 +831,8 @@ constexpr int kDenseChain = 64;              // blocks of a workgroup, at most (
 struct DenseShape {
     int n_blk, n_wgs, n_round;               // blocks of a sequence, workgroups, whole rounds of them
     unsigned inv_b, inv_h;                   // 2^32 / B and / H_q, rounded up (inv_b 0: divide)
+    int n_whole;                             // several layers: rounds that a layer fills, 2^32 / n_layers, rounded up
+    unsigned inv_layers;
 };
 
 // tile row (within 16) behind result row r of S^T
@@ -865,24 +867,36 @@ __device__ __forceinline__ void dense_rows(const AttnArgs &a, const DenseArgs &d
     asm volatile("" ::"s"(a.Q), "s"(a.KV), "s"(a.B), "s"(a.Tq), "s"(a.Lk), "s"(a.H_q), "s"(a.row_elems), "s"(a.n_layers), "s"(da.n_queries), "s"(da.pos0), "s"(da.lead), "s"(ds.n_blk), "s"(ds.n_wgs), "s"(ds.inv_b), "s"(ds.inv_h));
     auto div_b = [&](int x) -> int { return a.B == 1 ? x : ds.inv_b ? (int)__umulhi((unsigned)x, ds.inv_b) : x / a.B; };
     auto div_h = [&](int x) -> int { return a.H_q == 1 ? x : (int)__umulhi((unsigned)x, ds.inv_h); };
-    // blocks of the workgroup, all sequences' blocks of a layer ranked by length, layer behind layer (a layer's blocks share its
-    // keys): there and back over the workgroups, which evens them out
-    const int n_blk = ds.n_blk, n_layer = n_blk * a.B, n_all = MULTI ? n_layer * a.n_layers : n_layer, n_wgs = ds.n_wgs;
-    auto layer_at = [&](int &r) -> int {                  // of a rank, which becomes the one within the layer
-        if (!MULTI) return 0;
-        const int layer = (int)((unsigned)r / (unsigned)n_layer);
-        r -= layer * n_layer;
-        return layer;
+    // blocks of the workgroup, all sequences' blocks of a layer ranked by length: there and back over the workgroups, which evens them
+    // out.  Several layers take turns (a layer's blocks share its keys): two rounds each, there and back, as long as they fill them, then
+    // one round each, then rank by rank.  Layer behind layer, the long blocks of one fell where the other's short ones should.  us, a
+    // launch each / layer behind layer / this: 3 layers of 1021 rows 144 / 158 / 132, 4 of 1000 196 / 207 / 169, of 1024 200 / 183 / 173.
+    const int n_blk = ds.n_blk, n_all = n_blk * (MULTI ? a.B * a.n_layers : a.B), n_wgs = ds.n_wgs;
+    auto place = [&](int n) -> int { return n & 1 ? n_wgs - 1 - (int)blockIdx.x : (int)blockIdx.x; };      // in round n
+    int whole = ds.n_whole, n_layers = a.n_layers;
+    unsigned inv_layers = ds.inv_layers;
+    if (MULTI) asm volatile("" : "+s"(whole), "+s"(n_layers), "+s"(inv_layers));      // (kept: loaded again for every block they cost a us each)
+    auto rank_of = [&](int n, int &layer) -> int {        // rank within the layer of block n of the list
+        layer = 0;
+        if (!MULTI) return n * n_wgs + place(n);
+        const int paired = (whole & ~1) * n_layers, all = whole * n_layers;
+        if (n < all && n >= paired) {
+            layer = n - paired;
+            return (whole - 1) * n_wgs + place(n);
+        }
+        const bool pair = n < paired;
+        const int x = pair ? n >> 1 : (n - all) * n_wgs + place(n), by = (int)__umulhi((unsigned)x, inv_layers);
+        layer = x - by * n_layers;
+        return pair ? (2 * by + (n & 1)) * n_wgs + place(n) : whole * n_wgs + by;
     };
-    auto rank = [&](int n) -> int { return n * n_wgs + (n & 1 ? n_wgs - 1 - (int)blockIdx.x : (int)blockIdx.x); };
     int n_list = ds.n_round;
-    n_list += rank(n_list) < n_all;
+    n_list += n_list * n_wgs + place(n_list) < n_all;
     if (tid < kDenseRows) mref[tid] = mnew[tid] = mnew[kDenseRows + tid] = -INFINITY;
     if (tid < 4) moved[tid] = 0;
     if (da.lead) {
         for (int n = wave; n < n_list; n += 8) {
-            int r = rank(n);
-            const int layer = layer_at(r), r_b = div_b(r), b = r - r_b * a.B, R0 = (n_blk - 1 - r_b) * kDenseRows;
+            int layer;
+            const int r = rank_of(n, layer), r_b = div_b(r), b = r - r_b * a.B, R0 = (n_blk - 1 - r_b) * kDenseRows;
             const int nq = __builtin_amdgcn_readfirstlane(min(da.n_queries, lead_rows(da.lead + ((int64_t)layer * a.B + b) * da.n_chunks, da.n_chunks)));
             if (lane == 0) list[n] = R0 < nq * a.H_q ? nq : 0;
         }
@@ -895,9 +909,7 @@ __device__ __forceinline__ void dense_rows(const AttnArgs &a, const DenseArgs &d
         int nq = da.n_queries;
         if (da.lead)
             while (n < n_list && (nq = __builtin_amdgcn_readfirstlane(list[n])) == 0) ++n;
-        int r = rank(min(n, n_list - 1));
-        k.layer = layer_at(r);
-        const int r_b = div_b(r);
+        const int r = rank_of(min(n, n_list - 1), k.layer), r_b = div_b(r);
         k.n = n;
         k.b = r - r_b * a.B;
         k.R0 = (n_blk - 1 - r_b) * kDenseRows;
@@ -2241,7 +2253,9 @@ hipError_t launch_attn_dense(const AttnArgs &a, const DenseArgs &da, hipStream_t
     ds.n_blk = (int)(blocks / a.B / a.n_layers);
     ds.n_wgs = (int)grid.x;
     ds.n_round = (int)(blocks / grid.x);
-    ds.inv_b = blocks * (a.B - 1) < (int64_t)1 << 32 ? up(a.B) : 0u;
+    ds.inv_b = blocks / a.n_layers * (a.B - 1) < (int64_t)1 << 32 ? up(a.B) : 0u;
+    ds.n_whole = (int)(blocks / a.n_layers / grid.x);
+    ds.inv_layers = up(a.n_layers);          // (of numbers below grid.x * n_layers)
     ds.inv_h = up(a.H_q);
     hipLaunchKernelGGL(kernels[a.n_layers > 1][a.pv.page_table != nullptr], grid, dim3(512), lds, st, a, da, ds);
     return hipGetLastError();

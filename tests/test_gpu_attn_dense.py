@@ -253,6 +253,7 @@ def test_any_output_address(B, Tq, pos0, k):
 @pytest.mark.parametrize("B, Tq, pos0, k, n, page", [
     (1, 300, 0, 2048, 4, 0), (3, 130, 0, 512, 3, 0), (1, 257, 40, 512, 8, 0), (2, 200, 0, 512, 2, 64),      # every row a whole prefix
     (1, 600, 0, 512, 4, 0), (2, 400, 100, 450, 3, 0), (2, 400, 100, 450, 3, 64),                            # and rows behind them
+    (1, 1021, 0, 2048, 3, 0), (1, 1100, 0, 2048, 2, 0), (1, 1600, 0, 2048, 3, 0), (1, 1600, 0, 2048, 3, 64),  # rounds that a layer fills: one, two, three
 ])
 def test_dense_rows_of_several_layers(B, Tq, pos0, k, n, page):
     """Layers that share their dense launch give what each gives alone: a block does not know its neighbours, and the rows behind
