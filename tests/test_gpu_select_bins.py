@@ -92,6 +92,31 @@ def test_last_key_wanted_lies_in_the_lowest_bin(ic, oracle, L, ks, kind):
     check(ic, oracle, q.to(torch.bfloat16).cuda(), k.to(torch.bfloat16).cuda(), torch.ones((1, 2, 1)).cuda(), ks, L - 2)
 
 
+@pytest.mark.parametrize("L, H", [(700, 1), (700, 40), (1500, 1), (4000, 1), (7000, 1), (12000, 1), (30000, 1)])
+@pytest.mark.parametrize("kind", ["few", "many", "all"])
+def test_scores_that_are_no_numbers(ic, L, H, kind):
+    """They are chosen by their bits, as larger than infinity (sign bit clear) or smaller than -infinity (set): the order of the keys."""
+    print("[case] bins, NaN, %s, L=%d H=%d" % (kind, L, H), flush=True)
+    x = torch.arange(L)
+    r = torch.rand(L, generator=torch.Generator().manual_seed(L))
+    hit = {"few": x % (L // 5) == 3, "many": x % 3 == 1, "all": x >= 0}[kind]
+    v = torch.where(hit, torch.tensor(float("nan")), 1 + r)
+    v = torch.where((x % 97 == 5) & ~hit, torch.tensor(float("inf")), v)
+    q = torch.zeros((1, 2, H, 64)); q[:, :, 0, 5] = 1.0
+    k = torch.zeros((1, L, 64)); k[0, :, 5] = v
+    q, k, w = q.to(torch.bfloat16).cuda(), k.to(torch.bfloat16).cuda(), torch.ones((1, 2, H)).cuda()
+    for ks in (7, 600):
+        idx, sel = ic.indexer_topk(q, k, w, ks, L - 2, want_scores=True)
+        sc = ic.debug_indexer_scores(q, k, w, L - 2, 0, 2).cpu().numpy()
+        idx, sel = idx.cpu().numpy(), sel.cpu().numpy()
+        for i in range(2):
+            u = sc[0, i][:L - 1 + i].view(np.uint32).astype(np.int64)
+            keys = np.where(u >> 31, 0xFFFFFFFF - u, u + 0x80000000)
+            want = np.sort(np.argsort(-keys, kind="stable")[:ks])
+            assert np.array_equal(idx[0, i], want), (i, ks)
+            assert np.array_equal(sel[0, i], sc[0, i][want], equal_nan=True)
+
+
 @pytest.mark.parametrize("L", [5, 511, 1024, 1025])
 @pytest.mark.parametrize("ks", [3, 200])
 def test_lengths_of_two_head_tiles(ic, oracle, L, ks):
