@@ -75,7 +75,12 @@ size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 // Default strip budget when the caller asks how much workspace to bring.
 constexpr size_t kStripBudget = (size_t)1 << 30;   // 1 GiB of score rows in flight
-constexpr size_t kSmallStrip = (size_t)128 << 20;   // problems whose whole score matrix is below this keep it in one strip
+// Problems whose whole score matrix is below this keep it in one strip, and larger ones have strips of at least as much: every strip ends in
+// rounds of a part of the CUs.  us, 32 heads of 128, with 64 / 128 / 256 MiB: 1000 rows before 20000 keys (76 MiB) 203 / 176 / 178, 2048
+// before 12000 (94) 218 / 193 / 193, 300 before 80000 (91) 234 / 198 / 198, 4096 before 8000 (125) 237 / 215 / 214; larger than that:
+// 1500 before 41700 (238) 546 / 495 / 466, 4096 before 16384 (256) 533 / 476 / 447, 4096 before 32768 (512) 1010 / 1009 / 952.  Not more, for the
+// memory that a caller brings.
+constexpr size_t kSmallStrip = (size_t)128 << 20;
 constexpr int kMinStripRows = 16;
 
 ic_status check_indexer(const ic_indexer_desc *d)

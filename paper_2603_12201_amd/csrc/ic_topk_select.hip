@@ -18,7 +18,7 @@
 //            barriers in all.  When ties are cut at the boundary: per-sweep scans of packed
 //            greater / equal counts.
 // That is the form for whatever the others leave over.  Forms by row length: scores and top-k in one launch (few rows of up
-// to 1024 keys), the bins form (launches whose rows have up to 32768), the candidate form (32769 to 131072 keys, k up to a quarter of them), the candidate form with a row spread
+// to 1024 keys), the bins form (launches whose rows have up to 32768), the candidate form (32769 to 131072 keys), the candidate form with a row spread
 // over several workgroups (few rows of more than 65536 keys), and the radix select, with the keys cached in LDS (up to
 // 32768) or re-reading the row on every sweep.
 #include "ic_common.hpp"
@@ -443,7 +443,7 @@ __global__ __launch_bounds__(NT) void select_cand_kernel(SelectArgs a)
     // through several calls is not inlined, and a kernel argument captured by a real function is copied to scratch
     // memory by every thread of every row).
     auto candidate_form = [&]() -> bool {
-    if (nv < kCandMinLen || nv < 4 * a.k_sel || nv > MAXLEN) return false;   // workgroup-uniform
+    if (nv < kCandMinLen || nv < 4 * a.k_sel) return false;    // (short rows of a ragged launch) workgroup-uniform
     const float *row = a.strip + (int64_t)r * a.ld;
     int32_t *oidx = a.idx + ((int64_t)b * a.Tq + i) * a.k_sel;
     float *osel = a.sel ? a.sel + ((int64_t)b * a.Tq + i) * a.k_sel : nullptr;
@@ -1157,10 +1157,10 @@ constexpr int kPartThreads = 1024;
 constexpr int kPartWaves = kPartThreads / 64;
 constexpr int kPartMax = 64;             // parts of a row
 constexpr int kPartBlock = 32;           // keys of a row that stay together: a line
-// Where the form is the better one (score + select of a call, parts against the forms above): one row of 65536 keys 22.9
-// against 22.5 us, 100 000 keys 24.3 / 32.3, 200 000 keys 29.5 / 139, 500 000 keys 40.6 / 378; 32 rows of 65536 keys 116 /
-// 114, of 131072 keys 218 / 226; 60 rows of 131072 keys 390 / 395, of 32768 keys 114 / 112; and past the candidate form's
-// bitmap 120 rows of 140 000 keys 816 / 1002, 250 rows 1679 / 1972.
+// Where the form is the better one (scores and select of a call, 2 heads of 64, k = 2048; us, parts / the forms above): one row of 40 000
+// keys 20.0 / 21.3, 66 000 20.7 / 27.0, 100 000 21.3 / 30.9, 131 072 22.9 / 36.6; 32 rows of 66 000 34.7 / 38.4, of 131 072 44.8 / 55.3;
+// 64 rows 48.2 / 50.3 and 64.1 / 71.8, 96 rows 55.9 / 56.1 and 77 / 81, 128 rows 64.3 / 63.2 and 96 / 97, 200 rows 85 / 80 and 134 / 127.
+// Past the candidate form's bitmap one row of 200 000 keys 24.9 / 148, 64 rows of 140 000 70 / 167, 200 rows 142 / 240, 500 rows 316 / 644.
 constexpr int kPartFrom = 65536;         // rows have more keys than this ...
 constexpr int kPartRows = 64;            // ... and are at most this many: more of them fill the chip by themselves,
 constexpr int kPartRowsLong = 512;       // which holds for longer where the alternative streams the row four times
@@ -1462,8 +1462,8 @@ size_t select_lds_bytes(int cache_elems)
 
 // A row of this length leaves about 2 k + 1 / 128 of its keys as candidates (the rank that select_part_kernel takes from the
 // sample).  Where the lists (some kFinishSlots together at any number of parts) are unlikely to hold that many, the row would go to the radix select behind two launches for
-// nothing (k = 2048: from 1.05 M keys; 1.1 M keys 745 us without, 755 with them).  The sample scatters by some 14 %: a row
-// shortly below the line may still get there, and gains tenfold where it does not (1 M keys 727 / 60 us).
+// nothing (k = 2048: from 1.05 M keys; 1.1 M keys 775 us without, 780 with them).  The sample scatters by some 14 %: a row
+// shortly below the line may still get there, and gains tenfold where it does not (1 M keys 652 / 45 us).
 bool select_parts_fit(int k, int row_len) { return (int64_t)2 * k + row_len / 128 <= kFinishCap; }
 
 // Parts of a row when n_rows rows of up to max_row_len keys are selected together: enough for one workgroup per CU,
@@ -1544,7 +1544,8 @@ hipError_t launch_select(const SelectArgs &a_in, int n_rows, int max_row_len, hi
     if (max_row_len <= 16384 && n_rows > 512) return launch_bins<256, 16, 2048, 4>(a, n_rows, max_row_len, st);
     if (max_row_len <= 16384) return launch_bins<512, 8, 2048, 6>(a, n_rows, max_row_len, st);
     if (max_row_len <= kBinsLen) return launch_bins<512, 16, 4096, 4>(a, n_rows, max_row_len, st);
-    if (max_row_len <= kCandMaxLen && max_row_len >= 4 * a.k_sel) {
+    static_assert(4 * IC_MAX_K <= kBinsLen, "a row of the candidate form is four times as long as its selection");
+    if (max_row_len <= kCandMaxLen) {
         // one read of the row, a sampled threshold and a candidate list (falls back row by row)
         constexpr int lds = cand_lds_words(1024, kCandMaxLen, kCandCap) * (int)sizeof(uint32_t);
         constexpr int lds_many = cand_lds_words(512, kCandMaxLen, kCandManyCap) * (int)sizeof(uint32_t);
