@@ -52,3 +52,18 @@ def test_dense_attention_of_several_layers_spills_no_vector_register():
         assert use["AGPRs"] == 0 and use["VGPRs Spill"] == 0 and use["ScratchSize [bytes/lane]"] == 0, (name, use)
         assert use["VGPRs"] <= 256, (name, use)
     assert seen == 2                              # contiguous and paged
+
+
+def test_scalar_spills_stay_out_of_the_products(tmp_path):
+    """Scalar registers that the attention kernels spill go to lanes of a vector register: between blocks and queries that costs
+    nothing to speak of, in a loop with matrix products each way would take its place among them."""
+    src, out = os.path.join(build.CSRC, "ic_sparse_attn.hip"), str(tmp_path / "attn.s")
+    subprocess.run(["hipcc"] + build.FLAGS + ["--offload-device-only", "-S", src, "-o", out], stderr=subprocess.DEVNULL, check=True)
+    seen = 0
+    for name, body in re.findall(r"^(_ZN2ic\S*(?:dense|stream)_kernel[^:\n]*):[^\n]*\n(.*?)\n\.Lfunc_end", open(out).read(), re.S | re.M):
+        seen += 1
+        for block in re.split(r"\n(?=\.LBB|; %bb)", body):
+            if block.count("v_mfma") >= 4:
+                moves = len(re.findall(r"v_readlane|v_writelane", block))
+                assert moves <= (2 if "dense_kernelILb1" in name else 0), (name, block.split("\n")[0], moves)
+    assert seen == 10                             # dense: one layer and several, contiguous and paged; stream: six
