@@ -709,9 +709,9 @@ struct BinsLds {
     static constexpr int kWords = NT * NV / 8; // bitmap
     static constexpr int kList = kRankCap * 2 > IC_MAX_K ? kRankCap * 2 : IC_MAX_K;
     static_assert(NB % NT == 0, "whole bins per thread");
-    // the histogram; once it is read the boundary bin's members (keys, positions), then the selected positions, and behind
-    // them the bitmap
-    uint32_t smem[NB > kList + kWords ? NB : kList + kWords];
+    // the histogram and a place per lane; once it is read the boundary bin's members (keys, positions), then the selected
+    // positions, and behind them the bitmap
+    uint32_t smem[NB + 64 > kList + kWords ? NB + 64 : kList + kWords];
     uint32_t wsum[NW], bc[4], red[2 * NW];
     uint32_t misc[5];                          // 0 members listed, 1 k-th key, 2 its position, 3 equal ones behind it, 4 odd scores
 };
@@ -883,19 +883,21 @@ __device__ __forceinline__ void bins_select(const float *row, int nv, int k, int
     if (!odd && scale > 0.f && scale < 3e38f) {                // (one value only, or a range beyond floats: no bins)
         // (monotone, NB - 1 at most)
         auto bin = [](float x, float from, float by) { return (uint32_t)((x - from) * by); };
-        // The lowest bin is what the others leave: a ReLU's zeros, or all of a row but its largest scores, would take turns there
-        // (one head of 30000 keys, half of them zero: 32.7 us with all keys counted, 21.8 without; 2048 rows of 32768 388 / 306).
+        // The lowest bin is what the others leave: a ReLU's zeros, or all of a row but its largest scores, would take turns there.  Its
+        // keys go to a place per lane behind the bins (one head of 30000 keys, half of them zero: 32.4 us counted, 21.3 so; 2048 rows of
+        // 32768 387 / 306; left out by a branch, 0.2 us more for 10007 other keys).  A single wave's rows are too short for that to matter.
+        constexpr bool all = NW == 1;
         if (tid == 0) {
-            if (bin(f0, first, scale)) atomicSub(&hist[bin(f0, first, scale)], pad);
-            hist[0] = (uint32_t)nv;            // (for the scan, which ends here at the latest)
+            if (all || bin(f0, first, scale)) atomicSub(&hist[bin(f0, first, scale)], pad);
+            if (!all) hist[0] = (uint32_t)nv;  // (for the scan, which ends here at the latest)
         }
         each([&](uint32_t x, int) {
             const uint32_t at = bin(__uint_as_float(x), first, scale);
-            if (at) atomicAdd(&hist[at], 1u);
+            atomicAdd(&hist[all || at ? at : NB + lane], 1u);
         });
         sync();
         find_digit<NT, NB / NT>(hist, need, wsum, bc, tid, lane, wave, sync);
-        const uint32_t b = bc[0], n_b = b ? bc[2] : (uint32_t)(nv - k) + bc[1];
+        const uint32_t b = bc[0], n_b = all || b ? bc[2] : (uint32_t)(nv - k) + bc[1];
         need = bc[1];
         float from = first;                    // (opaque: bins are worked out again)
         asm volatile("" : "+v"(from));
