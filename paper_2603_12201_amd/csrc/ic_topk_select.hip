@@ -883,18 +883,23 @@ __device__ __forceinline__ void bins_select(const float *row, int nv, int k, int
     if (!odd && scale > 0.f && scale < 3e38f) {                // (one value only, or a range beyond floats: no bins)
         // (monotone, NB - 1 at most)
         auto bin = [](float x, float from, float by) { return (uint32_t)((x - from) * by); };
-        // The lowest bin is what the others leave: a ReLU's zeros, or all of a row but its largest scores, would take turns there.  Its
-        // keys go to a place per lane behind the bins (one head of 30000 keys, half of them zero: 32.4 us counted, 21.3 so; 2048 rows of
-        // 32768 387 / 306; left out by a branch, 0.2 us more for 10007 other keys).  A single wave's rows are too short for that to matter.
-        constexpr bool all = NW == 1;
+        // A ReLU's zeros, or all of a row but its largest scores, would take turns in the lowest bin, so that bin is what the others
+        // leave: its keys go to a place per lane behind the bins (one head of 10000 keys, half of them zero: 19.9 us counted, 16.0 so;
+        // 2048 rows of 8192 106 / 86).  The largest instance asks each wave's first scores instead, and counts all where less than an
+        // eighth of them lie there (30000 keys 32.6 / 21.7; two instructions more for every key are 1.5 us of 89 for four layers of six rows
+        // of 21143).  A single wave's rows are too short for that to matter.
+        constexpr bool all = NW == 1, ask = NT * NV >= 8192;
         if (tid == 0) {
             if (all || bin(f0, first, scale)) atomicSub(&hist[bin(f0, first, scale)], pad);
-            if (!all) hist[0] = (uint32_t)nv;  // (for the scan, which ends here at the latest)
+            if (!all) atomicAdd(&hist[0], (uint32_t)nv);       // (for the scan, which ends here at the latest)
         }
-        each([&](uint32_t x, int) {
-            const uint32_t at = bin(__uint_as_float(x), first, scale);
-            atomicAdd(&hist[all || at ? at : NB + lane], 1u);
-        });
+        if (all || (ask && __popcll(__ballot(bin(__uint_as_float(v[0][0]), first, scale) == 0u)) < 8))
+            each([&](uint32_t x, int) { atomicAdd(&hist[bin(__uint_as_float(x), first, scale)], 1u); });
+        else
+            each([&](uint32_t x, int) {
+                const uint32_t at = bin(__uint_as_float(x), first, scale);
+                atomicAdd(&hist[at ? at : NB + lane], 1u);
+            });
         sync();
         find_digit<NT, NB / NT>(hist, need, wsum, bc, tid, lane, wave, sync);
         const uint32_t b = bc[0], n_b = all || b ? bc[2] : (uint32_t)(nv - k) + bc[1];
