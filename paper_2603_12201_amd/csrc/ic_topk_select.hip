@@ -883,17 +883,16 @@ __device__ __forceinline__ void bins_select(const float *row, int nv, int k, int
     if (!odd && scale > 0.f && scale < 3e38f) {                // (one value only, or a range beyond floats: no bins)
         // (monotone, NB - 1 at most)
         auto bin = [](float x, float from, float by) { return (uint32_t)((x - from) * by); };
-        // A ReLU's zeros, or all of a row but its largest scores, would take turns in the lowest bin, so that bin is what the others
-        // leave: its keys go to a place per lane behind the bins (one head of 10000 keys, half of them zero: 19.9 us counted, 16.0 so;
-        // 2048 rows of 8192 106 / 86).  The largest instance asks each wave's first scores instead, and counts all where less than an
-        // eighth of them lie there (30000 keys 32.6 / 21.7; two instructions more for every key are 1.5 us of 89 for four layers of six rows
-        // of 21143).  A single wave's rows are too short for that to matter.
-        constexpr bool all = NW == 1, ask = NT * NV >= 8192;
+        // A ReLU's zeros, or all of a row but its largest scores, would take turns in the lowest bin.  A wave that finds an eighth of its
+        // first scores there gives them a place per lane behind the bins, and that bin is what the others leave (one head of 30000 keys,
+        // half of them zero: 32.5 us counted, 21.7 so; 2048 rows of 32768 388 / 310).  Asked for every key, that took other rows 0.1 to 1.5
+        // us.  A single wave's rows are too short for it to matter.
+        constexpr bool all = NW == 1;
         if (tid == 0) {
             if (all || bin(f0, first, scale)) atomicSub(&hist[bin(f0, first, scale)], pad);
             if (!all) atomicAdd(&hist[0], (uint32_t)nv);       // (for the scan, which ends here at the latest)
         }
-        if (all || (ask && __popcll(__ballot(bin(__uint_as_float(v[0][0]), first, scale) == 0u)) < 8))
+        if (all || __builtin_expect(__popcll(__ballot(bin(__uint_as_float(v[0][0]), first, scale) == 0u)) < 8, 1))
             each([&](uint32_t x, int) { atomicAdd(&hist[bin(__uint_as_float(x), first, scale)], 1u); });
         else
             each([&](uint32_t x, int) {
