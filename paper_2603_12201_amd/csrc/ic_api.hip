@@ -1089,6 +1089,19 @@ int sim_outputs(const ic_attn_desc *a, int n_layers)
     return (int)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(pairs, fit), ic::kMaxBatchLayers));
 }
 
+// The first layer whose rows are compared to themselves ahead of the pairs (n_layers: none): layer i is asked by i pairs.  Few rows are
+// 16 us of latency a launch, 7 where all is known; many read an output at 4 TB/s.  us for all comparisons, ahead from layer 0 / 2 / none: 3 layers of
+// 557 rows 23 / 34 / 18; 2 of 5000 rows 122 / 41 / 41; 6 of 3000 about 155 / 127 / 360.
+int sim_self_from(const ic_attn_desc *a, int n_layers, int n_out)
+{
+    const double read = (double)sim_o_bytes(a) / 4e6;
+    const int pairs = n_layers * (n_layers - 1) / 2, launches = (pairs + n_out - 1) / n_out;
+    const double none = std::max(16. * launches, read * pairs);
+    const double one = std::max(16., read * (n_layers - 1)) + 7 * launches;
+    const double two = n_layers > 2 ? std::max(16., read * (n_layers - 2)) + std::max(16., read) + 7 * (launches - 1) : none;
+    return none <= std::min(one, two) ? n_layers : (one < two ? 1 : 2);
+}
+
 // Whether no layer's output overlaps another one's output or inputs: only then may they all be written before the first pair
 // is compared.
 bool sim_apart(const ic_layer *layers, int n_layers)
@@ -1119,9 +1132,8 @@ ic_status run_similarity(const ic_layer *layers, int n_layers, const int32_t *co
     const int64_t n_rows = (int64_t)d->B * d->Tq;
     const int n_chunks = lead_chunks(lead_queries(d));
     auto counts = [&](int l) { return lead + (int64_t)l * d->B * n_chunks; };
-    // (of layers that more than one comparison asks: two layers of two sequences of 2500 rows took 1186 us with both layers' worked
-    // out first, 1120 without)
-    auto self_of = [&](int l) -> double * { return self && l >= 2 ? self + l * n_rows : nullptr; };
+    const int self_from = self ? sim_self_from(d, n_layers, n_out) : n_layers;
+    auto self_of = [&](int l) -> double * { return l >= self_from ? self + l * n_rows : nullptr; };
     ic::CosineArgs c0;
     memset(&c0, 0, sizeof c0);
     c0.n_rows = n_rows;
