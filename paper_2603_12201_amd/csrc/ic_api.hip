@@ -448,7 +448,7 @@ double row_time(const ic_attn_desc *d, int n_layers, Causal c, size_t ws_bytes, 
 
 // The first n rows of every sequence in the dense form: blocks of 64 (query, head) rows ranked by length, in chains there and back
 // over the CUs, as long as the longest block or as a chain of those that all rounds of them have a block for.  Several layers
-// follow one another: their blocks of mean length, and half of what the longest has more.
+// take turns: their blocks of mean length, and half of what the longest has more.
 double dense_time(const ic_attn_desc *d, int n, int64_t pos0, int n_layers = 1)
 {
     const int64_t blocks = ((int64_t)n * d->H_q + 63) / 64 * d->B, rounds = (blocks * n_layers + 255) / 256;
